@@ -159,6 +159,8 @@ apmm_status check_gemm(int64_t M, int64_t N, int64_t K, int p, int q, const void
 
 constexpr int kMaxProblems = 256;  // entries of one apmm_gemm_grouped call
 
+constexpr int kAlgoMfmaI8 = -1;  // chosen by APMM_ALGO_AUTO only
+
 apmm_status run_gemm(const apmm::GemmArgs &g, int algo, hipStream_t s, void *workspace = nullptr, size_t workspace_bytes = 0)
 {
     if (algo == APMM_ALGO_AUTO) {
@@ -167,7 +169,7 @@ apmm_status run_gemm(const apmm::GemmArgs &g, int algo, hipStream_t s, void *wor
         if (apmm::gemm_decode_supported(g) && !(g.M > 32 && g.N > 8192 && !g.a_codes && apmm::gemm_mfma_ksplit_pays(g)))
             algo = APMM_ALGO_DECODE;
         else if (apmm::gemm_mfma_fp4_supported(g)) algo = apmm::gemm_mfma_ksplit_pays(g) ? APMM_ALGO_MFMA_KSPLIT : APMM_ALGO_MFMA_FP4;
-        else algo = APMM_ALGO_VALU_POPCOUNT;
+        else algo = apmm::gemm_mfma_i8_supported(g) ? kAlgoMfmaI8 : APMM_ALGO_VALU_POPCOUNT;
     }
     if (algo == APMM_ALGO_VALU_POPCOUNT || algo == APMM_ALGO_PLANE_PAIRS_GLOBAL || algo == APMM_ALGO_PLANES_REGISTERS)
         (void)apmm::take_kernel_timing();  // those kernels take no timing events
@@ -175,6 +177,9 @@ apmm_status run_gemm(const apmm::GemmArgs &g, int algo, hipStream_t s, void *wor
     switch (algo) {
     case APMM_ALGO_VALU_POPCOUNT:
         e = apmm::launch_gemm_valu(g, s);
+        break;
+    case kAlgoMfmaI8:
+        e = apmm::launch_gemm_mfma_i8(g, s);
         break;
     case APMM_ALGO_MFMA_FP4:
         if (!apmm::gemm_mfma_fp4_supported(g)) return fail(APMM_ERR_UNSUPPORTED, "gemm: FP4 MFMA kernel covers p, q in 1..4 while 4 K (2^p - 1)(2^q - 1) < 2^24");

@@ -36,15 +36,8 @@ constexpr int kRowsPerWg = 16;
 constexpr int kMaxLdsBytes = 128 * 1024;
 constexpr int kMfmaMinTokens = 1;  // the matrix-unit kernel serves every token count its code widths allow
 
-// Words 4*hh .. 4*hh+3 of plane i of an n-bit operand in the common form come from one 16-byte vector of the
-// slots of a row and k block (`slots` points at the uint4 of slot 0; consecutive slots are kPlaneWords / 4
-// apart): plane_half_src gives its address, plane_half_from turns the loaded vector into the words.
-__device__ __forceinline__ const uint4 *plane_half_src(const uint4 *slots, int n, int i, int hh)
-{
-    constexpr int kSlotVec = kPlaneWords / 4;
-    return slots + (i < 2 * pair_groups(n) ? (i / 2 * 2 + hh) : (n - 1)) * kSlotVec;
-}
-
+// Words 4*hh .. 4*hh+3 of plane i of an n-bit operand in the common form, from the 16-byte vectors of the slots of a
+// row and k block (`slots` points at the uint4 of slot 0; consecutive slots are kPlaneWords / 4 apart).
 __device__ __forceinline__ uint4 plane_half_from(const uint4 raw, int n, int i, int hh)
 {
     if (i < 2 * pair_groups(n)) {
@@ -60,6 +53,28 @@ __device__ __forceinline__ uint4 plane_half_from(const uint4 raw, int n, int i, 
                       ((l.z >> k0) & 0x11111111u) | (((l.w >> k0) & 0x11111111u) << 2),
                       ((l.x >> k1) & 0x11111111u) | (((l.y >> k1) & 0x11111111u) << 2),
                       ((l.z >> k1) & 0x11111111u) | (((l.w >> k1) & 0x11111111u) << 2));
+}
+
+__device__ __forceinline__ uint4 load_plane_half(const uint4 *slots, int n, int i, int hh)
+{
+    constexpr int kSlotVec = kPlaneWords / 4;
+    if (byte_form(n)) {  // word 4 hh + x: slot 4 hh + x, word 2 tt + jh, top bit of every byte inverted
+        uint32_t out[4];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            const uint4 b = slots[(4 * hh + x) * kSlotVec];
+            const uint32_t f = 0x80808080u, m = 0x01010101u;
+            out[x] = (((b.x ^ f) >> i) & m) | ((((b.y ^ f) >> i) & m) << 4) | ((((b.z ^ f) >> i) & m) << 2) | ((((b.w ^ f) >> i) & m) << 6);
+        }
+        return make_uint4(out[0], out[1], out[2], out[3]);
+    }
+    if (nibble_form(n) && i < 4) {  // words 4 hh, 4 hh + 1 from k step 2 hh, the other two from k step 2 hh + 1
+        const uint4 b0 = slots[2 * hh * kSlotVec], b1 = slots[(2 * hh + 1) * kSlotVec];
+        const uint32_t m = 0x11111111u;
+        return make_uint4(((b0.x >> i) & m) | (((b0.y >> i) & m) << 2), ((b0.z >> i) & m) | (((b0.w >> i) & m) << 2),
+                          ((b1.x >> i) & m) | (((b1.y >> i) & m) << 2), ((b1.z >> i) & m) | (((b1.w >> i) & m) << 2));
+    }
+    return plane_half_from(slots[(i < 2 * pair_groups(n) ? (i / 2 * 2 + hh) : (n - 1)) * kSlotVec], n, i, hh);
 }
 
 // The same from slots already in registers (weights of a Q-bit operand).
@@ -158,23 +173,17 @@ __global__ __launch_bounds__(kThreads) void gemm_decode_kernel(GroupArgs ga)
     const uint32_t chunks_per_kb = (uint32_t)(MT * p * 2);
     const uint32_t chunks_pass0 = (uint32_t)(chunk_kb < g.nkb ? chunk_kb : g.nkb) * chunks_per_kb;
     // chunk c of a pass that starts at k block kb0: (k block, row m, plane j, half hh)
-    auto chunk_src = [&](uint32_t c, int64_t kb0, uint32_t &j, uint32_t &hh) {
+    auto load_chunk = [&](uint32_t c, int64_t kb0) {
         const uint32_t ckb = c / chunks_per_kb;
         const uint32_t rem = c - ckb * chunks_per_kb, plane = rem >> 1, m = plane / p;
-        j = plane - m * p;
-        hh = rem & 1;
         const uint4 *slots = reinterpret_cast<const uint4 *>(g.a + tile_row_word(m, kb0 + ckb, g.nkb, p, 0));
-        return plane_half_src(slots, p, j, hh);
+        return load_plane_half(slots, p, (int)(plane - m * p), (int)(rem & 1));
     };
     uint4 a_first = make_uint4(0, 0, 0, 0);
-    uint32_t a_first_j = 0, a_first_hh = 0;
     if constexpr (!CODES) {
-        if ((uint32_t)tid < chunks_pass0) a_first = *chunk_src(tid, 0, a_first_j, a_first_hh);
+        if ((uint32_t)tid < chunks_pass0) a_first = load_chunk(tid, 0);
     }
 
-    // (Everything from here to the LDS writes is loaded without a condition, from clamped addresses where the
-    // thread has nothing to load: the wait for the activations may leave exactly these loads outstanding only
-    // if every thread issues all of them.)
     int64_t kb = 4 * (int64_t)wave + sub;
     uint4 wnext[Q];
     {
@@ -233,14 +242,10 @@ __global__ __launch_bounds__(kThreads) void gemm_decode_kernel(GroupArgs ga)
             const uint32_t total_chunks = (uint32_t)(kb_end - kb0) * chunks_per_kb;
             uint32_t c = tid;
             if (kb0 == 0) {  // the chunk requested at the top
-                if (c < total_chunks) a_lds[c] = plane_half_from(a_first, p, a_first_j, a_first_hh);
+                if (c < total_chunks) a_lds[c] = a_first;
                 c += kThreads;
             }
-            for (; c < total_chunks; c += kThreads) {
-                uint32_t j, hh;
-                const uint4 raw = *chunk_src(c, kb0, j, hh);
-                a_lds[c] = plane_half_from(raw, p, j, hh);
-            }
+            for (; c < total_chunks; c += kThreads) a_lds[c] = load_chunk(c, kb0);
         }
         __syncthreads();
 

@@ -27,6 +27,16 @@ constexpr int kTile = 16;
 // 8c + 4jh + 2tt.  `tile_row` points at word 0 of (row, slot 0).
 __device__ __forceinline__ uint32_t plane_half_word(const uint32_t *tile_row, int n, int i, int w)
 {
+    if (byte_form(n)) {  // slot w, word 2 tt + jh: bytes with the top bit inverted
+        const uint32_t *b = tile_row + w * kPlaneWords;
+        uint32_t out = 0;
+        for (int x = 0; x < 4; ++x) out |= (((b[x] ^ 0x80808080u) >> i) & 0x01010101u) << (4 * (x & 1) + 2 * (x >> 1));
+        return out;
+    }
+    if (nibble_form(n) && i < 4) {  // N[4 ks + 2 tp], N[4 ks + 2 tp + 1]
+        const uint32_t *b = tile_row + (w >> 1) * kPlaneWords + 2 * (w & 1);
+        return ((b[0] >> i) & 0x11111111u) | (((b[1] >> i) & 0x11111111u) << 2);
+    }
     if (i < 2 * pair_groups(n)) {
         const uint32_t s = tile_row[(i / 2 * 2 + (w >> 2)) * kPlaneWords + (w & 3)];  // S[w] of pair group i / 2
         return (s >> (i & 1)) & 0x55555555u;

@@ -29,6 +29,10 @@ bool gemm_mfma_ksplit_supported(const GemmArgs &args);
 bool gemm_mfma_ksplit_pays(const GemmArgs &args);  // the launch rule of launch_gemm_mfma_fp4 takes it for these
 hipError_t launch_gemm_mfma_ksplit(const GemmArgs &args, hipStream_t stream);
 
+// Codes of more than four bits, and 3- and 4-bit codes at a K beyond the bound above: int8 operands (apmm_gemm_mfma_i8.h).
+bool gemm_mfma_i8_supported(const GemmArgs &args);
+hipError_t launch_gemm_mfma_i8(const GemmArgs &args, hipStream_t stream);
+
 // Ablation kernels for the claim of paper Sec. 4.2 (apmm_gemm_ablation.hip): the planes as +-1 operands on the
 // matrix unit.  pairs != nullptr: every plane pair's product to global memory (p q M N int32 at `pairs`), then a
 // recovery pass; pairs == nullptr: one tile per workgroup, recovery in registers.

@@ -40,6 +40,13 @@
 // second sweep of K and no expansion at all, at the price of 6 instead of 4 bits per element in a buffer
 // that lives for one GEMM (weights always keep the compact group form).
 //
+// Codes of 5 to 8 bits go to the int8 matrix operations and are stored so that little is left to do there:
+//   5, 6, 7 bits: the four low bits fill slots 0 .. 3 as nibbles: word N[4 ks + t] (slot ks, word t) holds bits 0 .. 3 of element
+//       (ks, t, jh, c) at bits 8c + 4jh ...; bits 4, 5 are the pair group of slots 4, 5 and the top bit of an odd width is
+//       the single group of slot n - 1, both as above;
+//   8 bits: bytes.  Slot 2 ks + tp, word 2 tt + jh, byte c is the code of (ks, 2 tp + tt, jh, c) with its top bit inverted, i.e.
+//       u - 128 as a signed byte, in the order of the elements: the int8 operand as it stands.
+//
 // Behind the tiles follows one int32 per (padded) row: the sum of the row's codes over the padded K.
 // The MFMA kernels multiply codes u instead of values 2u - (2^n - 1) and need these sums to recover C.
 //
@@ -65,6 +72,11 @@ inline __host__ __device__ constexpr bool has_single_group(int n) { return (n & 
 
 // activations of 3 or 4 bits are stored in the field form (six slots), everything else in the group form
 inline __host__ __device__ constexpr bool activation_field_form(int p) { return p == 3 || p == 4; }
+// codes of 5 .. 7 bits keep their four low bits as nibbles, codes of 8 bits are stored as signed bytes
+inline __host__ __device__ constexpr bool nibble_form(int n) { return n >= 5 && n <= 7; }
+inline __host__ __device__ constexpr bool byte_form(int n) { return n == 8; }
+// first pair group that is stored as one (nibbles and bytes hold the lower bits otherwise)
+inline __host__ __device__ constexpr int first_pair_group(int n) { return n <= 4 ? 0 : nibble_form(n) ? 2 : 4; }
 inline __host__ __device__ constexpr int activation_slots(int p) { return activation_field_form(p) ? 6 : p; }
 
 // index of word g=0 of (row, slot s) in k block kb

@@ -20,17 +20,33 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kRowsPerWg = kThreads / 64;
 
+// nibbles of the four codes in lo (jh = 0) and in hi (jh = 1)
+__device__ __forceinline__ uint32_t nibble_word(uint32_t lo, uint32_t hi)
+{
+    return (lo & 0x0f0f0f0fu) | ((hi & 0x0f0f0f0fu) << 4);
+}
+
 // Packs one 32-element group kg of a row: d[2t + jh] = the four codes 8t + 4jh + (0..3), one per byte,
 // already masked to `bits` bits.  Adds the codes to `sum`.  The four lanes 4x .. 4x+3 of a wave must hold
 // the four groups ks = 0..3 of one k block and call this together (single groups exchange words).
+// `flip`: top bit of every byte for a row of an 8-bit operand that exists (signed bytes), else 0.
 __device__ __forceinline__ void pack_group(uint32_t *__restrict__ packed, int64_t row, int64_t nkb, int bits,
-                                           int64_t kg, const uint32_t (&d)[8], uint32_t &sum)
+                                           int64_t kg, const uint32_t (&d)[8], uint32_t flip, uint32_t &sum)
 {
 #pragma unroll
     for (int t4 = 0; t4 < 8; ++t4) sum = __builtin_amdgcn_sad_u8(d[t4], 0u, sum);  // + the four bytes
     const int64_t kb = kg / kWordsPerRow;
     const int ks = (int)(kg % kWordsPerRow);
-    for (int h = 0; h < pair_groups(bits); ++h) {
+    if (byte_form(bits)) {
+        uint4 *dst = reinterpret_cast<uint4 *>(packed + tile_row_word(row, kb, nkb, bits, 2 * ks));
+        dst[0] = make_uint4(d[0] ^ flip, d[1] ^ flip, d[2] ^ flip, d[3] ^ flip);
+        dst[kPlaneWords / 4] = make_uint4(d[4] ^ flip, d[5] ^ flip, d[6] ^ flip, d[7] ^ flip);
+        return;
+    }
+    if (nibble_form(bits))
+        *reinterpret_cast<uint4 *>(packed + tile_row_word(row, kb, nkb, bits, ks)) =
+            make_uint4(nibble_word(d[0], d[1]), nibble_word(d[2], d[3]), nibble_word(d[4], d[5]), nibble_word(d[6], d[7]));
+    for (int h = first_pair_group(bits); h < pair_groups(bits); ++h) {
         // S[2 ks + tp], tp = 0, 1: slot 2h + ks/2, words 2 (ks % 2) + tp
         uint32_t s[2];
 #pragma unroll
@@ -109,6 +125,7 @@ __global__ __launch_bounds__(kThreads) void pack_rows_kernel(const uint8_t *__re
     if (row >= rows_p) return;
     const int64_t groups = nkb * kWordsPerRow;  // 32-element groups per row, a multiple of 16
     const uint32_t code_mask = 0x01010101u * ((1u << bits) - 1u);
+    const uint32_t flip = byte_form(bits) && row < rows ? 0x80808080u : 0u;
     uint32_t sum = 0;                           // sum of the codes of this lane's groups
 
     auto load_group = [&](int64_t kg, uint32_t (&d)[8]) __attribute__((always_inline)) {
@@ -152,8 +169,8 @@ __global__ __launch_bounds__(kThreads) void pack_rows_kernel(const uint8_t *__re
             pack_group_fields(packed, row, nkb, kg, d0, sum);
             if (second) pack_group_fields(packed, row, nkb, kg + 64, d1, sum);
         } else {
-            pack_group(packed, row, nkb, bits, kg, d0, sum);
-            if (second) pack_group(packed, row, nkb, bits, kg + 64, d1, sum);
+            pack_group(packed, row, nkb, bits, kg, d0, flip, sum);
+            if (second) pack_group(packed, row, nkb, bits, kg + 64, d1, flip, sum);
         }
     }
 #pragma unroll
@@ -240,8 +257,24 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const uint8_t *__restric
             uint4 *dst = reinterpret_cast<uint4 *>(packed + tile_row_word(row, kb, nkb, 6, 3 * h));
 #pragma unroll
             for (int v = 0; v < 3; ++v) dst[v * kSlotVec] = make_uint4(dw[4 * v], dw[4 * v + 1], dw[4 * v + 2], dw[4 * v + 3]);
+        } else if (byte_form(bits)) {
+            const uint32_t flip = row < rows ? 0x80808080u : 0u;
+            uint4 *dst = reinterpret_cast<uint4 *>(packed + tile_row_word(row, kb, nkb, bits, 4 * h));
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+#pragma unroll
+                for (int tp = 0; tp < 2; ++tp)
+                    dst[(2 * e + tp) * kSlotVec] = make_uint4(d[e][4 * tp] ^ flip, d[e][4 * tp + 1] ^ flip, d[e][4 * tp + 2] ^ flip,
+                                                              d[e][4 * tp + 3] ^ flip);
         } else {
-            for (int g = 0; g < pair_groups(bits); ++g) {
+            if (nibble_form(bits)) {
+                uint4 *dst = reinterpret_cast<uint4 *>(packed + tile_row_word(row, kb, nkb, bits, 2 * h));
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+                    dst[e * kSlotVec] = make_uint4(nibble_word(d[e][0], d[e][1]), nibble_word(d[e][2], d[e][3]),
+                                                   nibble_word(d[e][4], d[e][5]), nibble_word(d[e][6], d[e][7]));
+            }
+            for (int g = first_pair_group(bits); g < pair_groups(bits); ++g) {
                 // S[2 ks + tp] of k steps 2h, 2h + 1 = S[4h .. 4h + 3] = slot 2 g + h
                 uint32_t sw[4];
 #pragma unroll
@@ -388,6 +421,7 @@ __global__ __launch_bounds__(kThreads) void quantize_pack_kernel(const uint16_t 
     const float half_r = s > 0.0f ? (1.0f / s) * 0.5f : 0.0f;  // scale 0: every code becomes 2^(bits-1)
     const float mid = (float)(1u << (bits - 1)), ftop = (float)top;
 
+    const uint32_t flip = byte_form(bits) && live ? 0x80808080u : 0u;
     uint32_t sum = 0;
     // codes of group kg from its halves h (elements past K: the all-ones padding code), then the packing
     auto quantize_group = [&](int64_t kg, const uint32_t (&h)[16]) __attribute__((always_inline)) {
@@ -414,7 +448,7 @@ __global__ __launch_bounds__(kThreads) void quantize_pack_kernel(const uint16_t 
             d[t4] = v;
         }
         if (field) pack_group_fields(packed, row, nkb, kg, d, sum);
-        else pack_group(packed, row, nkb, bits, kg, d, sum);
+        else pack_group(packed, row, nkb, bits, kg, d, flip, sum);
     };
     auto fill_group = [&](int64_t kg) __attribute__((always_inline)) {
         // a whole group of padding (every plane bit set) or a padding row (zero words)
@@ -423,7 +457,7 @@ __global__ __launch_bounds__(kThreads) void quantize_pack_kernel(const uint16_t 
 #pragma unroll
         for (int t4 = 0; t4 < 8; ++t4) d[t4] = fill;
         if (field) pack_group_fields(packed, row, nkb, kg, d, sum);
-        else pack_group(packed, row, nkb, bits, kg, d, sum);
+        else pack_group(packed, row, nkb, bits, kg, d, flip, sum);
     };
     // The four lanes that pack a k block together must take the same call: a k block with any live group
     // quantises all four of its groups (elements past K become padding codes inside quantize_group).
@@ -494,7 +528,17 @@ __global__ __launch_bounds__(kThreads) void unpack_kernel(const uint32_t *__rest
                 for (int c = 0; c < 4; ++c)
                     d[2 * t + jh] |= ((uint32_t)(chunk[t] >> (12 * c + 6 * jh)) & code_mask) << (8 * c);
     }
-    for (int h = 0; !field && h < pair_groups(bits); ++h) {
+    if (byte_form(bits)) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            d[i] = packed[tile_row_word(row, kb, nkb, bits, 2 * ks + (i >> 2)) + (i & 3)] ^ 0x80808080u;
+    }
+    if (nibble_form(bits)) {
+        const uint32_t *src = packed + tile_row_word(row, kb, nkb, bits, ks);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) d[i] = (src[i >> 1] >> (4 * (i & 1))) & 0x0f0f0f0fu;
+    }
+    for (int h = first_pair_group(bits); !field && h < pair_groups(bits); ++h) {
         const uint32_t *src = packed + tile_row_word(row, kb, nkb, bits, 2 * h + (ks >> 1)) + 2 * (ks & 1);
 #pragma unroll
         for (int tp = 0; tp < 2; ++tp) {

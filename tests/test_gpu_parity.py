@@ -178,6 +178,37 @@ def test_wide_codes(gpu, oracle, p, q):
     assert np.array_equal(c32.astype(np.int64), want)
 
 
+@pytest.mark.parametrize("p,q", [(p, q) for p in range(1, 9) for q in range(1, 9) if p > 4 or q > 4])
+def test_int8_kernel_all_wide_widths(gpu, oracle, p, q):
+    """The int8 kernel with K split across waves: every pair of widths that it serves, ragged borders in M, N and K, the extreme
+    codes among the inputs."""
+    torch, binding = gpu
+    case = dict(M=70, N=203, K=700, p=p, q=q, a_dist="bernoulli", scaled=True)
+    data = inputs.make_case(case, 2400 + 17 * p + q)
+    data["a_codes"][0], data["a_codes"][1] = 0, (1 << p) - 1
+    data["w_codes"][0], data["w_codes"][1] = 0, (1 << q) - 1
+    want = oracle.gemm_i64(data["a_codes"], data["w_codes"], p, q)
+    data["a_scale"] = (data["a_scale"] * np.float16(1 / 256)).astype(np.float16)
+    c32, c16 = run_case(gpu, data, case)
+    assert binding.apmm_last_gemm_kernel() == "gemm_mfma_i8_kernel<%d,%d,ksplit>" % (p, q)
+    assert np.array_equal(c32.astype(np.int64), want)
+    check_f16(c16, want, data, oracle)
+
+
+@pytest.mark.parametrize("p,q,M,N,K", [(8, 8, 1100, 4000, 600), (6, 5, 1001, 4123, 515), (4, 7, 1100, 4000, 129), (4, 4, 1100, 4000, 18500)])
+def test_int8_kernel_large_tiles(gpu, oracle, p, q, M, N, K):
+    """The int8 kernel's 128 x 256 tile, whole and ragged borders, and narrow codes at a K beyond the fp32 exactness bound."""
+    torch, binding = gpu
+    case = dict(M=M, N=N, K=K, p=p, q=q, a_dist="bernoulli", scaled=True)
+    data = inputs.make_case(case, 2500 + 17 * p + q)
+    data["a_scale"] = (data["a_scale"] * np.float16(1 / 256)).astype(np.float16)
+    want = oracle.gemm_i64(data["a_codes"], data["w_codes"], p, q)
+    c32, c16 = run_case(gpu, data, case)
+    assert binding.apmm_last_gemm_kernel() == "gemm_mfma_i8_kernel<%d,%d,tiles>" % (p, q)
+    assert np.array_equal(c32.astype(np.int64), want)
+    check_f16(c16, want, data, oracle)
+
+
 @pytest.mark.parametrize("p,q", [(3, 3), (4, 4), (4, 1), (3, 2), (4, 2), (3, 1)])
 @pytest.mark.parametrize("M", [1, 7, 16, 17, 32, 33, 50, 64, 65])
 def test_few_tokens_with_field_form_activations(gpu, oracle, M, p, q):

@@ -6,9 +6,12 @@
 // MFMA kernels need for the recovery and which costs one byte-sum per four codes here instead of
 // popcounts per word and output tile there.
 //
+// Widths and row ends are compile-time (a launch fetches only the code it runs: one 4096-code row of two bits 2.4 ->
+// 2.2 us, 64 rows 2.6 -> 2.3 us).
+//
 // pack_kernel works tile by tile (one wave per 32 rows x 128 k, whole cache lines written by one instruction)
 // with separate waves for the code sums; pack_rows_kernel and the fused quantise + pack kernel work row by row
-// (one wave per row; the quantiser has to see the whole row for its scale first).  No atomics.  The work is HBM bound: 1 byte
+// (one wave or a few per row; the quantiser has to see the whole row for its scale first).  No atomics.  The work is HBM bound: 1 byte
 // read and bits/8 bytes written per element.
 #include <hip/hip_fp16.h>
 
@@ -24,6 +27,42 @@ constexpr int kRowsPerWg = kThreads / 64;
 __device__ __forceinline__ uint32_t nibble_word(uint32_t lo, uint32_t hi)
 {
     return (lo & 0x0f0f0f0fu) | ((hi & 0x0f0f0f0fu) << 4);
+}
+
+// 4 * NW codes of a row from k0 on, at any alignment (unaligned 16-byte and dword loads are single instructions here).
+// WHOLE: K is a multiple of 4 NW, a piece lies inside the row or past it.  Else a piece that crosses the row's end takes dwords clamped to the last four codes and shifts the ones that lie before it
+// out; positions past K become 0xff (pad: every plane bit set).  All loads of a piece are in flight together: byte loads
+// under a condition each, the earlier form, waited one by one (fresh 5003 x 3001 and 1000 x 3001 three-bit codes, packing
+// and product: 103 -> 47 us).
+struct __attribute__((packed, aligned(1))) AnyVec { uint32_t x, y, z, w; };
+struct __attribute__((packed, aligned(1))) AnyWord { uint32_t x; };
+
+template <bool WHOLE, int NW>
+__device__ __forceinline__ void load_codes(const uint8_t *__restrict__ row, int64_t K, int64_t k0, uint32_t (&d)[NW])
+{
+    const uint8_t *src = row + k0;
+    if (k0 + 4 * NW <= K) {
+#pragma unroll
+        for (int i = 0; i < NW / 4; ++i) {
+            const AnyVec v = reinterpret_cast<const AnyVec *>(src)[i];
+            d[4 * i] = v.x; d[4 * i + 1] = v.y; d[4 * i + 2] = v.z; d[4 * i + 3] = v.w;
+        }
+    } else if (!WHOLE && K >= 4) {
+        const int last = (int)(K - 4 - k0);  // of the row's last whole dword, from src on: above -512 - 4, below 4 NW
+#pragma unroll
+        for (int i = 0; i < NW; ++i) d[i] = reinterpret_cast<const AnyWord *>(src + (4 * i < last ? 4 * i : last))->x;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            const int past = 4 * i - last;  // codes of the clamped dword that lie before position k0 + 4 i
+            const int shift = past <= 0 ? 0 : past >= 4 ? 32 : 8 * past;
+            d[i] = (uint32_t)((d[i] | 0xffffffff00000000ull) >> shift);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < NW; ++i) d[i] = 0xffffffffu;
+        if (!WHOLE && k0 == 0)
+            for (int k = 0; k < (int)K; ++k) d[0] ^= (uint32_t)(src[k] ^ 0xffu) << (8 * k);
+    }
 }
 
 // Packs one 32-element group kg of a row: d[2t + jh] = the four codes 8t + 4jh + (0..3), one per byte,
@@ -88,27 +127,19 @@ __device__ __forceinline__ uint64_t spread_bytes_12(uint32_t x)
     return (uint64_t)((x & 0xffu) | ((x & 0xff00u) << 4) | ((x & 0xff0000u) << 8)) | ((uint64_t)(x >> 24) << 36);
 }
 
-__device__ __forceinline__ void pack_group_fields(uint32_t *__restrict__ packed, int64_t row, int64_t nkb, int64_t kg,
-                                                  const uint32_t (&d)[8], uint32_t &sum)
+// words 6 ks .. 6 ks + 5 of the row's 24: slot w / 4, word w % 4
+__device__ __forceinline__ void store_fields(uint32_t *__restrict__ packed, int64_t row, int64_t nkb, int64_t kg,
+                                             const uint32_t (&dw)[6])
 {
-#pragma unroll
-    for (int t4 = 0; t4 < 8; ++t4) sum = __builtin_amdgcn_sad_u8(d[t4], 0u, sum);
     const int64_t kb = kg / kWordsPerRow;
     const int ks = (int)(kg % kWordsPerRow);
-    uint64_t chunk[4];  // the 48 bits of t = 0..3
-#pragma unroll
-    for (int t = 0; t < 4; ++t) chunk[t] = spread_bytes_12(d[2 * t]) | (spread_bytes_12(d[2 * t + 1]) << 6);
-    const uint32_t dw0 = (uint32_t)chunk[0], dw1 = (uint32_t)(chunk[0] >> 32) | ((uint32_t)chunk[1] << 16),
-                   dw2 = (uint32_t)(chunk[1] >> 16), dw3 = (uint32_t)chunk[2],
-                   dw4 = (uint32_t)(chunk[2] >> 32) | ((uint32_t)chunk[3] << 16), dw5 = (uint32_t)(chunk[3] >> 16);
-    // words 6 ks .. 6 ks + 5 of the row's 24: slot w / 4, word w % 4
     uint32_t *base = packed + tile_row_word(row, kb, nkb, 6, 0) + 3 * (ks >> 1) * kPlaneWords;
     if ((ks & 1) == 0) {
-        *reinterpret_cast<uint4 *>(base) = make_uint4(dw0, dw1, dw2, dw3);
-        *reinterpret_cast<uint2 *>(base + kPlaneWords) = make_uint2(dw4, dw5);
+        *reinterpret_cast<uint4 *>(base) = make_uint4(dw[0], dw[1], dw[2], dw[3]);
+        *reinterpret_cast<uint2 *>(base + kPlaneWords) = make_uint2(dw[4], dw[5]);
     } else {
-        *reinterpret_cast<uint2 *>(base + kPlaneWords + 2) = make_uint2(dw0, dw1);
-        *reinterpret_cast<uint4 *>(base + 2 * kPlaneWords) = make_uint4(dw2, dw3, dw4, dw5);
+        *reinterpret_cast<uint2 *>(base + kPlaneWords + 2) = make_uint2(dw[0], dw[1]);
+        *reinterpret_cast<uint4 *>(base + 2 * kPlaneWords) = make_uint4(dw[2], dw[3], dw[4], dw[5]);
     }
 }
 
@@ -116,40 +147,21 @@ __device__ __forceinline__ void pack_group_fields(uint32_t *__restrict__ packed,
 // each, 1 KB contiguous per load instruction) and keeps a running code sum; the wave adds the 64 partial sums
 // with lane shuffles.  Reads are ideal, writes are 8- and 16-byte pieces that other waves complete to whole
 // lines later.  Used for group-form operands of one or two bits, where little is written.
+template <int bits, bool WHOLE>
 __global__ __launch_bounds__(kThreads) void pack_rows_kernel(const uint8_t *__restrict__ codes, int64_t rows,
-                                                        int64_t K, int bits, uint32_t *__restrict__ packed,
-                                                        int64_t rows_p, int64_t nkb, bool field)
+                                                        int64_t K, uint32_t *__restrict__ packed,
+                                                        int64_t rows_p, int64_t nkb)
 {
     const int lane = threadIdx.x & 63;
     const int64_t row = (int64_t)blockIdx.x * kRowsPerWg + (threadIdx.x >> 6);
     if (row >= rows_p) return;
     const int64_t groups = nkb * kWordsPerRow;  // 32-element groups per row, a multiple of 16
     const uint32_t code_mask = 0x01010101u * ((1u << bits) - 1u);
-    const uint32_t flip = byte_form(bits) && row < rows ? 0x80808080u : 0u;
     uint32_t sum = 0;                           // sum of the codes of this lane's groups
 
     auto load_group = [&](int64_t kg, uint32_t (&d)[8]) __attribute__((always_inline)) {
         if (row < rows) {
-            const int64_t k0 = kg * 32;
-            const uint8_t *src = codes + row * K + k0;
-            if (k0 + 32 <= K && (((uintptr_t)src) & 15) == 0) {
-                const uint4 lo = *reinterpret_cast<const uint4 *>(src);
-                const uint4 hi = *reinterpret_cast<const uint4 *>(src + 16);
-                d[0] = lo.x; d[1] = lo.y; d[2] = lo.z; d[3] = lo.w;
-                d[4] = hi.x; d[5] = hi.y; d[6] = hi.z; d[7] = hi.w;
-            } else {
-#pragma unroll
-                for (int t4 = 0; t4 < 8; ++t4) {
-                    uint32_t v = 0;
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const int64_t k = k0 + 4 * t4 + c;
-                        const uint32_t code = (k < K) ? src[4 * t4 + c] : 0xffu;  // pad: every plane bit set
-                        v |= code << (8 * c);
-                    }
-                    d[t4] = v;
-                }
-            }
+            load_codes<WHOLE>(codes + row * K, K, kg * 32, d);
 #pragma unroll
             for (int t4 = 0; t4 < 8; ++t4) d[t4] &= code_mask;
         } else {
@@ -165,17 +177,12 @@ __global__ __launch_bounds__(kThreads) void pack_rows_kernel(const uint8_t *__re
         const bool second = kg + 64 < groups;
         load_group(kg, d0);
         if (second) load_group(kg + 64, d1);
-        if (field) {
-            pack_group_fields(packed, row, nkb, kg, d0, sum);
-            if (second) pack_group_fields(packed, row, nkb, kg + 64, d1, sum);
-        } else {
-            pack_group(packed, row, nkb, bits, kg, d0, flip, sum);
-            if (second) pack_group(packed, row, nkb, bits, kg + 64, d1, flip, sum);
-        }
+        pack_group(packed, row, nkb, bits, kg, d0, 0u, sum);
+        if (second) pack_group(packed, row, nkb, bits, kg + 64, d1, 0u, sum);
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
-    if (lane == 0) packed[row_sum_word(rows_p, nkb, field ? 6 : bits) + row] = sum;
+    if (lane == 0) packed[row_sum_word(rows_p, nkb, bits) + row] = sum;
 }
 
 // pack_kernel: one wave per packed tile (32 rows x 128 k), plus one wave per row for the code sums.
@@ -189,9 +196,12 @@ __global__ __launch_bounds__(kThreads) void pack_rows_kernel(const uint8_t *__re
 //   form reaches the bandwidth of the copy.)
 //   Sum wave: adds the codes of one row and the padding; the sum waves of a row block follow its tile waves in
 //   the grid, so that they find the rows in L2.
+enum PackForm { kFieldForm, kByteForm, kOtherForm };  // compile-time: a launch fetches the code of its own form only
+
+template <PackForm FORM, bool WHOLE>
 __global__ __launch_bounds__(kThreads) void pack_kernel(const uint8_t *__restrict__ codes, int64_t rows,
                                                         int64_t K, int bits, uint32_t *__restrict__ packed,
-                                                        int64_t rows_p, int64_t nkb, bool field)
+                                                        int64_t rows_p, int64_t nkb)
 {
     const int lane = threadIdx.x & 63;
     // jobs of a row block: its nkb tiles, then the sums of its 32 rows (which find the rows in L2)
@@ -207,38 +217,16 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const uint8_t *__restric
         // d[e][2t + jh] = the four codes 8t + 4jh + (0..3) of k step 2h + e, one per byte
         uint32_t d[2][8];
         if (row < rows) {
-            const int64_t k0 = kb * kKBlock + 64 * h;
-            const uint8_t *src = codes + row * K + k0;
-            if (k0 + 64 <= K && (((uintptr_t)src) & 15) == 0) {
-                uint4 v[4];
+            uint32_t v[16];
+            load_codes<WHOLE>(codes + row * K, K, kb * kKBlock + 64 * h, v);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = reinterpret_cast<const uint4 *>(src)[i];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    d[i >> 1][4 * (i & 1)] = v[i].x; d[i >> 1][4 * (i & 1) + 1] = v[i].y;
-                    d[i >> 1][4 * (i & 1) + 2] = v[i].z; d[i >> 1][4 * (i & 1) + 3] = v[i].w;
-                }
-            } else {  // ragged end of the row, or rows that do not start at multiples of 16 bytes
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    uint32_t v = 0;
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const int64_t k = k0 + 4 * i + c;
-                        const uint32_t code = (k < K) ? src[4 * i + c] : 0xffu;  // pad: every plane bit set
-                        v |= code << (8 * c);
-                    }
-                    d[i >> 3][i & 7] = v;
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < 16; ++i) d[i >> 3][i & 7] &= code_mask;
+            for (int i = 0; i < 16; ++i) d[i >> 3][i & 7] = v[i] & code_mask;
         } else {
 #pragma unroll
             for (int i = 0; i < 16; ++i) d[i >> 3][i & 7] = 0u;  // rows past the operand are zero words
         }
         constexpr int kSlotVec = kPlaneWords / 4;
-        if (field) {
+        if constexpr (FORM == kFieldForm) {
             // k step ks: words 6 ks .. 6 ks + 5 of the row's 24, the 32 codes as 6-bit fields, field 8t + 2c + jh
             uint32_t dw[12];
 #pragma unroll
@@ -257,7 +245,7 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const uint8_t *__restric
             uint4 *dst = reinterpret_cast<uint4 *>(packed + tile_row_word(row, kb, nkb, 6, 3 * h));
 #pragma unroll
             for (int v = 0; v < 3; ++v) dst[v * kSlotVec] = make_uint4(dw[4 * v], dw[4 * v + 1], dw[4 * v + 2], dw[4 * v + 3]);
-        } else if (byte_form(bits)) {
+        } else if constexpr (FORM == kByteForm) {
             const uint32_t flip = row < rows ? 0x80808080u : 0u;
             uint4 *dst = reinterpret_cast<uint4 *>(packed + tile_row_word(row, kb, nkb, bits, 4 * h));
 #pragma unroll
@@ -315,24 +303,21 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const uint8_t *__restric
         uint32_t sum = 0;
         if (row < rows) {
             const uint8_t *src = codes + row * K;
-            if ((K & 15) == 0 && (((uintptr_t)codes) & 15) == 0) {
-                const int64_t vecs = K / 16;
+            const int64_t vecs = K / 16;
 #pragma unroll 8
-                for (int64_t i = lane; i < vecs; i += 64) {
-                    const uint4 v = reinterpret_cast<const uint4 *>(src)[i];
-                    sum = __builtin_amdgcn_sad_u8(v.x & code_mask, 0u, sum);
-                    sum = __builtin_amdgcn_sad_u8(v.y & code_mask, 0u, sum);
-                    sum = __builtin_amdgcn_sad_u8(v.z & code_mask, 0u, sum);
-                    sum = __builtin_amdgcn_sad_u8(v.w & code_mask, 0u, sum);
-                }
-            } else {
-                for (int64_t k = lane; k < K; k += 64) sum += src[k] & (code_mask & 0xffu);
+            for (int64_t i = lane; i < vecs; i += 64) {
+                const AnyVec v = reinterpret_cast<const AnyVec *>(src)[i];
+                sum = __builtin_amdgcn_sad_u8(v.x & code_mask, 0u, sum);
+                sum = __builtin_amdgcn_sad_u8(v.y & code_mask, 0u, sum);
+                sum = __builtin_amdgcn_sad_u8(v.z & code_mask, 0u, sum);
+                sum = __builtin_amdgcn_sad_u8(v.w & code_mask, 0u, sum);
             }
+            if (16 * vecs + lane < K) sum += src[16 * vecs + lane] & (code_mask & 0xffu);  // at most 15 codes
 #pragma unroll
             for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
             sum += (uint32_t)(nkb * kKBlock - K) * (code_mask & 0xffu);  // the all-ones codes of the padding
         }
-        if (lane == 0) packed[row_sum_word(rows_p, nkb, field ? 6 : bits) + row] = sum;
+        if (lane == 0) packed[row_sum_word(rows_p, nkb, FORM == kFieldForm ? 6 : bits) + row] = sum;
     }
 }
 
@@ -346,39 +331,54 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const uint8_t *__restric
 // Rows of up to 8192 elements stay in registers between the two steps; longer rows are read again (from
 // L2).  The codes are those of exact arithmetic on the binary16 inputs and the binary16 scale.  A row whose
 // scale rounds to zero gets the code of +1 everywhere.
+//
+// WAVES waves of a workgroup share a row, one 32-element group per lane and step, so that a row takes one or two round
+// trips to memory however long it is.  With one wave per row, the earlier form, a lane worked through up to eleven groups
+// in turn.  Four bits, one launch inside a graph: 16 x 5120 6.0 -> 3.2 us, 16 x 13824 12.5 -> 4.1 us, 1024 x 11008 15.1 ->
+// 13.0 us; two bits 4096 x 4096 12.5 -> 10.0 us.  Large matrices are bound by the phases (read, quantise, write) that every
+// resident workgroup goes through at the same time: 2.4 - 3.8 TB/s.
+// The eight rows that share the 128-byte lines of a slot are packed on one XCD, whose L2 joins their 16-byte pieces.
 typedef unsigned short us2 __attribute__((ext_vector_type(2)));
-constexpr int kCachedGroups = 4;  // 32-element groups per lane kept in registers
+constexpr int kCachedGroups = 2;  // 32-element groups per lane kept in registers
 
+template <int WAVES, bool WHOLE, bool FIELD>
 __global__ __launch_bounds__(kThreads) void quantize_pack_kernel(const uint16_t *__restrict__ x, int64_t rows,
                                                                  int64_t K, int bits,
                                                                  uint32_t *__restrict__ packed,
                                                                  uint16_t *__restrict__ scale_out, int64_t rows_p,
-                                                                 int64_t nkb, bool field)
+                                                                 int64_t nkb)
 {
-    const int lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)blockIdx.x * kRowsPerWg + (threadIdx.x >> 6);
-    if (row >= rows_p) return;
+    constexpr int T = 64 * WAVES, ROWS = kThreads / T, C = 8 / ROWS;  // threads of a row, rows of a workgroup, workgroups of eight rows
+    const int tid = threadIdx.x % T, sub = threadIdx.x / T;
+    const int xcd = blockIdx.x % 8, turn = blockIdx.x / 8;  // workgroups go to the XCDs in turn
+    const int64_t row = (((int64_t)(turn / C) * 8 + xcd) * C + turn % C) * ROWS + sub;
+    if (row >= rows_p) return;  // (rows_p is a multiple of ROWS: the whole workgroup leaves)
     const int64_t groups = nkb * kWordsPerRow;
     const uint16_t *xrow = x + row * K;
-    const bool vec_ok = ((K & 7) == 0) && ((((uintptr_t)x) & 15) == 0);  // every group start is 16-byte aligned
 
     // h[i] = elements 2i, 2i+1 of group kg as two binary16 bit patterns; elements past K read as +0
     auto load_halves = [&](int64_t kg, uint32_t (&h)[16]) __attribute__((always_inline)) {
         const int64_t k0 = kg * 32;
-        if (vec_ok && k0 + 32 <= K) {
-            const uint4 *src = reinterpret_cast<const uint4 *>(xrow + k0);
+        if (k0 + 32 <= K) {
+            const AnyVec *src = reinterpret_cast<const AnyVec *>(xrow + k0);
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const uint4 q = src[v];
+                const AnyVec q = src[v];
                 h[4 * v] = q.x; h[4 * v + 1] = q.y; h[4 * v + 2] = q.z; h[4 * v + 3] = q.w;
+            }
+        } else if (!WHOLE && K >= 2) {  // the row's end: dwords clamped to the last two elements, those before position k shifted out
+            const int last = (int)(K - 2 - k0);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) h[i] = reinterpret_cast<const AnyWord *>(xrow + k0 + (2 * i < last ? 2 * i : last))->x;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int past = 2 * i - last;
+                h[i] = past <= 0 ? h[i] : past == 1 ? h[i] >> 16 : 0u;
             }
         } else {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int64_t k = k0 + 2 * i;
-                const uint32_t lo = k < K ? xrow[k] : 0u, hi = k + 1 < K ? xrow[k + 1] : 0u;
-                h[i] = lo | (hi << 16);
-            }
+            for (int i = 0; i < 16; ++i) h[i] = 0u;
+            if (!WHOLE && kg == 0) h[0] = xrow[0];
         }
     };
     auto fold_max = [](us2 m, const uint32_t (&h)[16]) __attribute__((always_inline)) {
@@ -396,13 +396,13 @@ __global__ __launch_bounds__(kThreads) void quantize_pack_kernel(const uint16_t 
     us2 m2 = {0, 0};
 #pragma unroll
     for (int it = 0; it < kCachedGroups; ++it) {
-        const int64_t kg = lane + 64 * it;
+        const int64_t kg = tid + T * it;
         if (kg < live_groups) {
             load_halves(kg, cache[it]);
             m2 = fold_max(m2, cache[it]);
         }
     }
-    for (int64_t kg = lane + 64 * kCachedGroups; kg < live_groups; kg += 64) {
+    for (int64_t kg = tid + T * kCachedGroups; kg < live_groups; kg += T) {
         uint32_t h[16];
         load_halves(kg, h);
         m2 = fold_max(m2, h);
@@ -413,11 +413,21 @@ __global__ __launch_bounds__(kThreads) void quantize_pack_kernel(const uint16_t 
         const uint32_t o = __shfl_xor(mbits, off);
         mbits = o > mbits ? o : mbits;
     }
+    __shared__ uint32_t joint[2][kThreads / 64];
+    if constexpr (WAVES > 1) {
+        if ((threadIdx.x & 63) == 0) joint[0][threadIdx.x / 64] = mbits;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            const uint32_t o = joint[0][sub * WAVES + w];
+            mbits = o > mbits ? o : mbits;
+        }
+    }
     const float amax = __half2float(__ushort_as_half((uint16_t)mbits));
     const uint32_t top = (1u << bits) - 1u;
     const __half sh = __float2half_rn(amax / (float)top);
     const float s = __half2float(sh);
-    if (live && lane == 0) scale_out[row] = __half_as_ushort(sh);
+    if (live && tid == 0) scale_out[row] = __half_as_ushort(sh);
     const float half_r = s > 0.0f ? (1.0f / s) * 0.5f : 0.0f;  // scale 0: every code becomes 2^(bits-1)
     const float mid = (float)(1u << (bits - 1)), ftop = (float)top;
 
@@ -425,46 +435,73 @@ __global__ __launch_bounds__(kThreads) void quantize_pack_kernel(const uint16_t 
     uint32_t sum = 0;
     // codes of group kg from its halves h (elements past K: the all-ones padding code), then the packing
     auto quantize_group = [&](int64_t kg, const uint32_t (&h)[16]) __attribute__((always_inline)) {
-        uint32_t d[8];
-        const bool whole = kg * 32 + 32 <= K;
+        const bool whole = WHOLE || kg * 32 + 32 <= K;
+        auto code = [&](int i) __attribute__((always_inline)) {  // of element i, as a float
+            const uint32_t pair = h[i >> 1];
+            const float xf = __half2float(__ushort_as_half((uint16_t)((i & 1) ? pair >> 16 : pair & 0xffffu)));
+            // t = x / (2 s) up to 2^-23 relative (rounded reciprocal, rounded product); the cell is floor of
+            // the exact quotient.  An exact quotient that is an integer c (x on a border, ties upward) may
+            // come out just below c; any other exact quotient is at least 2^-12 away from every integer
+            // (x and 2 c s are binary16 numbers times small integers), and |t| <= 129.  Moving t up by
+            // 2^-21 |t| (between 2^-23 |t| and 2^-12) therefore gives the exact floor in every case.
+            const float t = fmaf(xf, half_r, 0.0f);  // the rounded product, with the conversion of xf in the same instruction
+            const float u = floorf(fmaf(fabsf(t), 0x1p-21f, t)) + mid;  // exact: |floor| is far below 2^24
+            return !whole && kg * 32 + i >= K ? ftop : __builtin_amdgcn_fmed3f(u, 0.0f, ftop);
+        };
+        if constexpr (FIELD) {
+            // four fields of six bits make an integer below 2^24, which a float holds: three fused multiply-adds and one
+            // conversion for four codes, and the group's code sum
+            uint32_t quad[8];
+            float total = 0.f;
 #pragma unroll
-        for (int t4 = 0; t4 < 8; ++t4) {
-            uint32_t v = 0;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const uint32_t pair = h[2 * t4 + (c >> 1)];
-                const float xf = __half2float(__ushort_as_half((uint16_t)((c & 1) ? pair >> 16 : pair & 0xffffu)));
-                // t = x / (2 s) up to 2^-23 relative (rounded reciprocal, rounded product); the cell is floor of
-                // the exact quotient.  An exact quotient that is an integer c (x on a border, ties upward) may
-                // come out just below c; any other exact quotient is at least 2^-12 away from every integer
-                // (x and 2 c s are binary16 numbers times small integers), and |t| <= 129.  Moving t up by
-                // 2^-21 |t| (between 2^-23 |t| and 2^-12) therefore gives the exact floor in every case.
-                const float t = xf * half_r;
-                float u = floorf(fmaf(fabsf(t), 0x1p-21f, t)) + mid;  // exact: |floor| is far below 2^24
-                u = __builtin_amdgcn_fmed3f(u, 0.0f, ftop);
-                if (!whole && kg * 32 + 4 * t4 + c >= K) u = ftop;
-                v = __builtin_amdgcn_cvt_pk_u8_f32(u, c, v);  // byte c of v = u
+            for (int i = 0; i < 8; ++i) {  // fields 4 i .. 4 i + 3: elements c = 2 (i % 2), 2 (i % 2) + 1, jh = 0, 1 of t = i / 2
+                const int at = 8 * (i >> 1) + 2 * (i & 1);
+                const float u0 = code(at), u1 = code(at + 4), u2 = code(at + 1), u3 = code(at + 5);
+                total += (u0 + u1) + (u2 + u3);
+                quad[i] = (uint32_t)fmaf(u3, 262144.f, fmaf(u2, 4096.f, fmaf(u1, 64.f, u0)));
             }
-            d[t4] = v;
+            sum += (uint32_t)total;
+            uint32_t dw[6];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                dw[3 * i] = quad[4 * i] | (quad[4 * i + 1] << 24);
+                dw[3 * i + 1] = (quad[4 * i + 1] >> 8) | (quad[4 * i + 2] << 16);
+                dw[3 * i + 2] = (quad[4 * i + 2] >> 16) | (quad[4 * i + 3] << 8);
+            }
+            store_fields(packed, row, nkb, kg, dw);
+        } else {
+            uint32_t d[8];
+#pragma unroll
+            for (int t4 = 0; t4 < 8; ++t4) {
+                d[t4] = 0;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) d[t4] = __builtin_amdgcn_cvt_pk_u8_f32(code(4 * t4 + c), c, d[t4]);  // byte c = u
+            }
+            pack_group(packed, row, nkb, bits, kg, d, flip, sum);
         }
-        if (field) pack_group_fields(packed, row, nkb, kg, d, sum);
-        else pack_group(packed, row, nkb, bits, kg, d, flip, sum);
     };
     auto fill_group = [&](int64_t kg) __attribute__((always_inline)) {
         // a whole group of padding (every plane bit set) or a padding row (zero words)
-        uint32_t d[8];
-        const uint32_t fill = live ? 0x01010101u * top : 0u;
+        const uint32_t fill = live ? top : 0u;
+        if constexpr (FIELD) {
+            const uint32_t quad = fill * 0x41041u;
+            const uint32_t w0 = quad | (quad << 24), w1 = (quad >> 8) | (quad << 16), w2 = (quad >> 16) | (quad << 8);
+            const uint32_t dw[6] = {w0, w1, w2, w0, w1, w2};
+            sum += 32u * fill;
+            store_fields(packed, row, nkb, kg, dw);
+        } else {
+            uint32_t d[8];
 #pragma unroll
-        for (int t4 = 0; t4 < 8; ++t4) d[t4] = fill;
-        if (field) pack_group_fields(packed, row, nkb, kg, d, sum);
-        else pack_group(packed, row, nkb, bits, kg, d, flip, sum);
+            for (int t4 = 0; t4 < 8; ++t4) d[t4] = 0x01010101u * fill;
+            pack_group(packed, row, nkb, bits, kg, d, flip, sum);
+        }
     };
     // The four lanes that pack a k block together must take the same call: a k block with any live group
     // quantises all four of its groups (elements past K become padding codes inside quantize_group).
     const int64_t live_blocks4 = (live_groups + 3) / 4 * 4;
 #pragma unroll
     for (int it = 0; it < kCachedGroups; ++it) {
-        const int64_t kg = lane + 64 * it;
+        const int64_t kg = tid + T * it;
         if (kg < live_blocks4) {
             if (kg >= live_groups) {
 #pragma unroll
@@ -475,7 +512,7 @@ __global__ __launch_bounds__(kThreads) void quantize_pack_kernel(const uint16_t 
             fill_group(kg);
         }
     }
-    for (int64_t kg = lane + 64 * kCachedGroups; kg < groups; kg += 64) {
+    for (int64_t kg = tid + T * kCachedGroups; kg < groups; kg += T) {
         if (kg < live_blocks4) {
             uint32_t h[16];
 #pragma unroll
@@ -488,7 +525,14 @@ __global__ __launch_bounds__(kThreads) void quantize_pack_kernel(const uint16_t 
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
-    if (lane == 0) packed[row_sum_word(rows_p, nkb, field ? 6 : bits) + row] = sum;
+    if constexpr (WAVES > 1) {
+        if ((threadIdx.x & 63) == 0) joint[1][threadIdx.x / 64] = sum;
+        __syncthreads();
+        sum = 0;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) sum += joint[1][sub * WAVES + w];
+    }
+    if (tid == 0) packed[row_sum_word(rows_p, nkb, FIELD ? 6 : bits) + row] = sum;
 }
 
 __global__ __launch_bounds__(kThreads) void unpack_kernel(const uint32_t *__restrict__ packed, int64_t rows,
@@ -581,15 +625,20 @@ hipError_t launch_pack(const uint8_t *codes, int64_t rows, int64_t K, int bits, 
         // takes the code sums on the way); 22.6 us against 12.0 us for 2048 x 11008 four-bit activations
         const int64_t blocks = (rows_p + kRowsPerWg - 1) / kRowsPerWg;
         if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(pack_rows_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, codes, rows, K, bits,
-                           packed, rows_p, nkb, field);
+        const bool whole = K % 32 == 0;
+        const auto kernel = bits == 1 ? (whole ? pack_rows_kernel<1, true> : pack_rows_kernel<1, false>)
+                                      : (whole ? pack_rows_kernel<2, true> : pack_rows_kernel<2, false>);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, codes, rows, K, packed, rows_p, nkb);
         return hipGetLastError();
     }
     const int64_t jobs = rows_p / kRowBlock * (nkb + kRowBlock);  // per row block: tile waves, then sum waves
     const int64_t blocks = (jobs + kRowsPerWg - 1) / kRowsPerWg;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(pack_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, codes, rows, K, bits,
-                       packed, rows_p, nkb, field);
+    const bool whole = K % 64 == 0;
+    const auto kernel = field ? (whole ? pack_kernel<kFieldForm, true> : pack_kernel<kFieldForm, false>)
+                      : byte_form(bits) ? (whole ? pack_kernel<kByteForm, true> : pack_kernel<kByteForm, false>)
+                                        : (whole ? pack_kernel<kOtherForm, true> : pack_kernel<kOtherForm, false>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, codes, rows, K, bits, packed, rows_p, nkb);
     return hipGetLastError();
 }
 
@@ -599,10 +648,21 @@ hipError_t launch_quantize_pack(const uint16_t *x, int64_t rows, int64_t K, int 
     const int64_t rows_p = round_up(rows, kRowBlock);
     const int64_t nkb = round_up(K, kKPad) / kKBlock;
     if (rows_p == 0) return hipSuccess;
-    const int64_t blocks = (rows_p + kRowsPerWg - 1) / kRowsPerWg;
+    // waves per row: a group of 32 elements for every lane, as far as the row goes
+    const int waves = nkb <= 16 ? 1 : nkb <= 32 ? 2 : 4;
+    const int64_t blocks = (rows_p + 63) / 64 * 64 * waves / (kThreads / 64);  // eight rows for each of the eight XCDs
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(quantize_pack_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, x, rows, K, bits,
-                       packed, scale, rows_p, nkb, field);
+    const bool whole = K % 128 == 0;  // every k block is packed whole or is all padding
+    decltype(&quantize_pack_kernel<1, true, true>) kernel;
+    if (field)
+        kernel = waves == 1 ? (whole ? quantize_pack_kernel<1, true, true> : quantize_pack_kernel<1, false, true>)
+               : waves == 2 ? (whole ? quantize_pack_kernel<2, true, true> : quantize_pack_kernel<2, false, true>)
+                            : (whole ? quantize_pack_kernel<4, true, true> : quantize_pack_kernel<4, false, true>);
+    else
+        kernel = waves == 1 ? (whole ? quantize_pack_kernel<1, true, false> : quantize_pack_kernel<1, false, false>)
+               : waves == 2 ? (whole ? quantize_pack_kernel<2, true, false> : quantize_pack_kernel<2, false, false>)
+                            : (whole ? quantize_pack_kernel<4, true, false> : quantize_pack_kernel<4, false, false>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, x, rows, K, bits, packed, scale, rows_p, nkb);
     return hipGetLastError();
 }
 

@@ -440,6 +440,36 @@ def test_quantize_pack_matches_the_oracle(gpu, oracle, M, K, p):
     assert torch.equal(packed, again)
 
 
+@pytest.mark.parametrize("p", [1, 2, 3, 4, 6, 8])
+@pytest.mark.parametrize("M,K,shift", [(3, 1, 1), (9, 2, 0), (2, 3, 3), (33, 33, 1), (8, 63, 0), (70, 129, 5), (5, 2047, 0), (1, 2049, 1),
+                                       (17, 4095, 0), (2, 4224, 2), (65, 8193, 0), (3, 16385, 1)])
+def test_packing_row_ends_and_alignments(gpu, oracle, M, K, shift, p):
+    """Rows that end inside a piece of 4, 32, 64 or 128 codes or start at any byte, every number of waves per row:
+    codes (weights and activations form, code sums through a product with all-ones codes) and binary16 features."""
+    torch, binding = gpu
+    dev = torch.device("cuda:0")
+    codes = inputs.bernoulli_codes(8200 + M + K + p, inputs.TAG_A, M, K, p)
+    room = torch.full((M * K + 64,), 0xee, dtype=torch.uint8, device=dev)
+    a = room[shift:shift + M * K].view(M, K)   # starts `shift` bytes after an aligned address, foreign bytes behind it
+    a.copy_(torch.from_numpy(codes))
+    assert np.array_equal(binding.apmm_unpack(binding.apmm_pack_weights(a, p), M, K, p).cpu().numpy(), codes)
+    packed = binding.apmm_pack_activations(a, p)
+    assert np.array_equal(binding.apmm_unpack_activations(packed, M, K, p).cpu().numpy(), codes)
+    ones = np.ones((1, K), np.uint8)
+    want = oracle.gemm_i64(codes, ones, p, 1)
+    c32, _ = binding.apmm_gemm(M, 1, K, p, 1, packed, binding.apmm_pack_weights(torch.from_numpy(ones).to(dev), 1))
+    assert np.array_equal(c32.cpu().numpy().astype(np.int64), want)
+    x = inputs.normal_features_f16(8200 + M + K + p, inputs.TAG_A, M, K, outlier_every=37)
+    room16 = torch.full((M * K + 64,), 60000.0, dtype=torch.float16, device=dev)
+    f = room16[shift:shift + M * K].view(M, K)
+    f.copy_(torch.from_numpy(x))
+    want_codes, want_scale = oracle.quantize_rows(x, p)
+    got, scale = binding.apmm_quantize_pack_activations(f, p)
+    assert np.array_equal(scale.cpu().numpy().view(np.uint16), want_scale)
+    assert np.array_equal(binding.apmm_unpack_activations(got, M, K, p).cpu().numpy(), want_codes)
+    assert torch.equal(got, binding.apmm_pack_activations(torch.from_numpy(want_codes).to(dev), p))
+
+
 def test_quantized_activations_through_the_gemm(gpu, oracle):
     """float16 activations -> quantise + pack -> GEMM with the fp16 epilogue, against the oracle's
     quantiser, integer GEMM and double-precision scaling."""

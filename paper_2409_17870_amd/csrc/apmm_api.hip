@@ -159,7 +159,7 @@ apmm_status check_gemm(int64_t M, int64_t N, int64_t K, int p, int q, const void
 
 constexpr int kMaxProblems = 256;  // entries of one apmm_gemm_grouped call
 
-constexpr int kAlgoMfmaI8 = -1;  // chosen by APMM_ALGO_AUTO only
+constexpr int kAlgoMfmaI8 = -1, kAlgoDecodeI8 = -2;  // chosen by APMM_ALGO_AUTO only
 
 apmm_status run_gemm(const apmm::GemmArgs &g, int algo, hipStream_t s, void *workspace = nullptr, size_t workspace_bytes = 0)
 {
@@ -169,6 +169,7 @@ apmm_status run_gemm(const apmm::GemmArgs &g, int algo, hipStream_t s, void *wor
         if (apmm::gemm_decode_supported(g) && !(g.M > 32 && g.N > 8192 && !g.a_codes && apmm::gemm_mfma_ksplit_pays(g)))
             algo = APMM_ALGO_DECODE;
         else if (apmm::gemm_mfma_fp4_supported(g)) algo = apmm::gemm_mfma_ksplit_pays(g) ? APMM_ALGO_MFMA_KSPLIT : APMM_ALGO_MFMA_FP4;
+        else if (apmm::gemm_decode_i8_supported(g)) algo = kAlgoDecodeI8;
         else algo = apmm::gemm_mfma_i8_supported(g) ? kAlgoMfmaI8 : APMM_ALGO_VALU_POPCOUNT;
     }
     if (algo == APMM_ALGO_VALU_POPCOUNT || algo == APMM_ALGO_PLANE_PAIRS_GLOBAL || algo == APMM_ALGO_PLANES_REGISTERS)
@@ -177,6 +178,9 @@ apmm_status run_gemm(const apmm::GemmArgs &g, int algo, hipStream_t s, void *wor
     switch (algo) {
     case APMM_ALGO_VALU_POPCOUNT:
         e = apmm::launch_gemm_valu(g, s);
+        break;
+    case kAlgoDecodeI8:
+        e = apmm::launch_gemm_decode(g, s);
         break;
     case kAlgoMfmaI8:
         e = apmm::launch_gemm_mfma_i8(g, s);
@@ -257,7 +261,12 @@ apmm_status apmm_gemm_from_codes(int64_t M, int64_t N, int64_t K, int p, int q, 
     // W2A4 at 11008 x 4096 6.0 / 7.5 / 9.6 us for 1 / 8 / 16 tokens against about 8 - 8.8 us in two launches)
     const bool fused_pays = apmm::activation_field_form(p) ? (M <= 8 || M * N <= 65536) : (M <= 16 || M * N <= 65536);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (fused_ok && (fused_pays || !room)) {
+    // Codes of more than four bits are int8 operands as they stand (every width with a workspace: the entry point has always
+    // asked for one where the XOR/popcount kernel does not go).  32 tokens, one launch against two: 4096 x 4096 W4A8 / W8A8 /
+    // W2A6 7.2 / 8.0 / 6.9 against 7.4 / 9.7 / 8.3 us, 11008 x 4096 13.3 / 15.5 / 11.9 against 13.7 / 17.1 / 13.3 us, 4096 x
+    // 11008 15.2 / 17.7 / 14.3 against 13.9 / 17.7 / 14.1 us; 64 tokens: two launches win at most widths.
+    const bool wide_pays = apmm::gemm_decode_i8_supported(g) && (M <= 16 || (M <= 32 && K <= 8192));
+    if ((fused_ok && (fused_pays || !room)) || (wide_pays && room)) {
         const hipError_t e = apmm::launch_gemm_decode(g, s);
         if (e != hipSuccess) return fail_hip(e, "apmm_gemm_from_codes");
         return APMM_OK;

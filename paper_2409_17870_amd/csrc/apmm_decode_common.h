@@ -1,0 +1,61 @@
+// Pieces shared by the small-M kernels: workgroup shape, the problem descriptor of a launch, group descriptors.
+#pragma once
+#include "apmm_mfma_common.h"
+
+namespace apmm {
+
+constexpr int kDecodeWaves = 8;
+constexpr int kDecodeThreads = 64 * kDecodeWaves;
+constexpr int kRowsPerWg = 16;  // output channels per channel tile
+
+struct DecodeProblem {
+    const uint32_t *w;
+    const void *a;          // packed activations, or codes (CODES)
+    int64_t N, K, M;
+    uint16_t *c_f16;
+    int32_t *c_i32;
+    const uint16_t *w_scale, *a_scale;
+};
+
+// problem of this workgroup and its index among the problem's workgroups
+__device__ __forceinline__ int pick_problem(DecodeProblem &pr, uint32_t misc, const GroupArgs &ga)
+{
+    int block = (int)blockIdx.x;
+    const int count = (int)((misc >> 12) & 0xffu);
+    if (count > 1) {
+        int idx = 0;
+        for (int i = 0; i + 1 < count; ++i)
+            if ((int)blockIdx.x >= ga.wg_end[i]) idx = i + 1;
+        if (idx > 0) {
+            const GemmArgs &g = ga.g[idx];
+            pr.w = g.w;
+            pr.a = g.a_codes ? static_cast<const void *>(g.a_codes) : static_cast<const void *>(g.a);
+            pr.N = g.N; pr.K = g.K; pr.M = g.M;
+            pr.c_f16 = g.c_f16; pr.c_i32 = g.c_i32;
+            pr.w_scale = g.w_scale; pr.a_scale = g.a_scale;
+            block -= ga.wg_end[idx - 1];
+        }
+    }
+    return block;
+}
+
+// Builds the launch descriptor of `count` problems (16 output channels per workgroup each).
+template <class PassKb>
+inline bool make_group(const GemmArgs *gs, int count, int rows_per_wg, PassKb pass_kb, GroupArgs &ga)
+{
+    if (count < 1 || count > kMaxGroup) return false;
+    int64_t end = 0;
+    ga.count = count;
+    for (int i = 0; i < kMaxGroup; ++i) {
+        const GemmArgs &g = gs[i < count ? i : count - 1];
+        if (i < count) end += (g.N + rows_per_wg - 1) / rows_per_wg;
+        if (end > 0x7fffffffLL) return false;
+        ga.wg_end[i] = (int)end;
+        ga.g[i] = g;
+        ga.chunk_kb[i] = (int)pass_kb(g);
+        if (ga.chunk_kb[i] < 1) return false;
+    }
+    return true;
+}
+
+}  // namespace apmm

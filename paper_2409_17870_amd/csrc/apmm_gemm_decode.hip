@@ -25,14 +25,13 @@
 
 #include <algorithm>
 
-#include "apmm_mfma_common.h"
+#include "apmm_decode_common.h"
 
 namespace apmm {
 namespace {
 
-constexpr int kWaves = 8;
-constexpr int kThreads = 64 * kWaves;
-constexpr int kRowsPerWg = 16;
+constexpr int kWaves = kDecodeWaves;
+constexpr int kThreads = kDecodeThreads;
 constexpr int kMaxLdsBytes = 128 * 1024;
 constexpr int kMfmaMinTokens = 1;  // the matrix-unit kernel serves every token count its code widths allow
 
@@ -327,25 +326,6 @@ size_t decode_lds_bytes(const GemmArgs &g, int mt)
 
 int decode_mt(int64_t M) { return M <= 1 ? 1 : M <= 2 ? 2 : M <= 4 ? 4 : M <= 8 ? 8 : 16; }
 
-// Builds the launch descriptor of `count` problems (16 output channels per workgroup each).
-template <class PassKb>
-bool make_group(const GemmArgs *gs, int count, int rows_per_wg, PassKb pass_kb, GroupArgs &ga)
-{
-    if (count < 1 || count > kMaxGroup) return false;
-    int64_t end = 0;
-    ga.count = count;
-    for (int i = 0; i < kMaxGroup; ++i) {
-        const GemmArgs &g = gs[i < count ? i : count - 1];
-        if (i < count) end += (g.N + rows_per_wg - 1) / rows_per_wg;
-        if (end > 0x7fffffffLL) return false;
-        ga.wg_end[i] = (int)end;
-        ga.g[i] = g;
-        ga.chunk_kb[i] = (int)pass_kb(g);
-        if (ga.chunk_kb[i] < 1) return false;
-    }
-    return true;
-}
-
 template <class Kernel>
 hipError_t launch_group(Kernel kernel, bool &attr_set, const GroupArgs &ga, size_t lds, hipStream_t stream)
 {
@@ -419,37 +399,6 @@ hipError_t launch_mt(const GroupArgs &ga, hipStream_t stream)
 // operands, 8 tokens 3.6 -> 3.1 / 5.1 -> 4.4 / 5.8 -> 4.6; from codes, 1 token (then on the XOR/popcount
 // kernel) 4.3 -> 3.2 / 7.6 -> 4.7 / 6.1 -> 4.9, 16 tokens 5.7 -> 4.4 / 9.8 -> 7.3 / 10.1 -> 7.1.
 // ---------------------------------------------------------------------------------------------
-struct DecodeProblem {
-    const uint32_t *w;
-    const void *a;          // packed activations, or codes (CODES)
-    int64_t N, K, M;
-    uint16_t *c_f16;
-    int32_t *c_i32;
-    const uint16_t *w_scale, *a_scale;
-};
-
-// problem of this workgroup and its index among the problem's workgroups
-__device__ __forceinline__ int pick_problem(DecodeProblem &pr, uint32_t misc, const GroupArgs &ga)
-{
-    int block = (int)blockIdx.x;
-    const int count = (int)((misc >> 12) & 0xffu);
-    if (count > 1) {
-        int idx = 0;
-        for (int i = 0; i + 1 < count; ++i)
-            if ((int)blockIdx.x >= ga.wg_end[i]) idx = i + 1;
-        if (idx > 0) {
-            const GemmArgs &g = ga.g[idx];
-            pr.w = g.w;
-            pr.a = g.a_codes ? static_cast<const void *>(g.a_codes) : static_cast<const void *>(g.a);
-            pr.N = g.N; pr.K = g.K; pr.M = g.M;
-            pr.c_f16 = g.c_f16; pr.c_i32 = g.c_i32;
-            pr.w_scale = g.w_scale; pr.a_scale = g.a_scale;
-            block -= ga.wg_end[idx - 1];
-        }
-    }
-    return block;
-}
-
 template <int P, int Q, int TT, int RT, int CODES, int NJ = 8>
 __global__ __launch_bounds__(kThreads, (CODES == 1 && TT == 1) ? (NJ == 1 && RT == 1 ? 6 : 4) - (Q > 2 ? 1 : 0) : 2)  // waves per SIMD aimed at (weights of two plane groups hold twice the raw words)
 void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg, int k_arg,
@@ -964,22 +913,32 @@ hipError_t launch_decode_mfma(const GroupArgs &ga, int rt, hipStream_t stream)
          : p == 3 ? launch_decode_mfma_pq<3, 4>(ga, tt, rt, stream) : launch_decode_mfma_pq<4, 4>(ga, tt, rt, stream);
 }
 
-// kernel variant that serves a problem: 0 = none, 100 + token tiles = matrix unit, else the token tile of the
-// XOR/popcount kernel
+// token tile of the XOR/popcount kernel, 0 where it does not cover the problem (it reads the group form only)
+int decode_valu_variant(const GemmArgs &g)
+{
+    if (g.M < 1 || g.M > 16 || g.q > 4 || activation_field_form(g.p)) return 0;
+    return decode_pass_kb(g, decode_mt(g.M)) > 0 ? decode_mt(g.M) : 0;
+}
+
+// kernel variant that serves a problem: 0 = none, 100 + token tiles = fp4 matrix operations, 200 + token tiles = int8
+// matrix operations, else the token tile of the XOR/popcount kernel
 int decode_variant(const GemmArgs &g, bool xor_only = false)
 {
-    if (g.M < 1 || g.M > 64 || g.q < 1 || g.q > 4) return 0;
-    if (!xor_only && decode_mfma_supported(g)) return 100 + decode_token_tiles(g);
-    if (activation_field_form(g.p)) return 0;  // the XOR/popcount kernel reads the group form only
-    if (g.M > 16) return 0;
-    return decode_pass_kb(g, decode_mt(g.M)) > 0 ? decode_mt(g.M) : 0;
+    if (xor_only) return decode_valu_variant(g);
+    if (decode_mfma_supported(g)) return 100 + decode_token_tiles(g);
+    // (one token of packed 5- to 7-bit codes against single-bit weights: the matrix form expands sixteen rows for one; W1A5
+    // 4096 x 4096 3.6 us on the vector ALU against 4.2 us, 11008 x 4096 5.3 against 6.8 us; two tokens and W2 are even)
+    if (!g.a_codes && nibble_form(g.p) && g.M * g.p * g.q <= 8 && decode_valu_variant(g)) return decode_valu_variant(g);
+    if (gemm_decode_i8_supported(g)) return 200 + (g.M <= 16 ? 1 : g.M <= 32 ? 2 : 4);
+    return decode_valu_variant(g);
 }
 
 }  // namespace
 
-// M <= 16 with q <= 4, or M <= 64 with p, q <= 2; never activations in the field form (p = 3, 4).
-bool gemm_decode_supported(const GemmArgs &g) { return decode_variant(g) != 0; }
-bool gemm_decode_valu_supported(const GemmArgs &g) { return decode_variant(g, true) != 0; }
+// What the small-M algo ids and activations without a workspace cover: p, q <= 4 up to 64 tokens (codes of 3 and 4 bits: 32)
+// within the exactness bound, weights of up to 4 bits under the other activation widths up to 16 tokens.
+bool gemm_decode_supported(const GemmArgs &g) { return decode_mfma_supported(g) || decode_valu_variant(g) != 0; }
+bool gemm_decode_valu_supported(const GemmArgs &g) { return decode_valu_variant(g) != 0; }
 
 bool gemm_decode_group_supported(const GemmArgs *gs, int count)
 {
@@ -988,7 +947,7 @@ bool gemm_decode_group_supported(const GemmArgs *gs, int count)
     for (int i = 0; i < count; ++i)
         if (decode_variant(gs[i]) != v || gs[i].p != gs[0].p || gs[i].q != gs[0].q ||
             (gs[i].a_codes != nullptr) != (gs[0].a_codes != nullptr) ||
-            (count > 1 && v > 100 && decode_token_groups(gs[i]) > 1))  // token groups: single-problem launches only
+            (count > 1 && v > 100 && v < 200 && decode_token_groups(gs[i]) > 1))  // token groups: single-problem launches only
             return false;
     return v != 0;
 }
@@ -1006,6 +965,7 @@ hipError_t launch_gemm_decode_group(const GemmArgs *problems, int count, hipStre
     for (int i = 0; i < count; ++i) gs[i] = problems[i];
     std::stable_sort(gs, gs + count, [](const GemmArgs &x, const GemmArgs &y) { return x.nkb > y.nkb; });
     const int variant = decode_variant(gs[0], xor_only);
+    if (variant > 200) return launch_gemm_decode_i8(gs, count, variant - 200, stream);
     if (variant > 100) {
         // two row tiles per workgroup once that still leaves two workgroups per CU
         int64_t rows = 0;

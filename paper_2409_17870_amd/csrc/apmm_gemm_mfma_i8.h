@@ -33,28 +33,6 @@ using mfma::vec_word;
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
-// Compile-time forms.  1 .. 4: that many bits in the group form.
-constexpr int kNibbles = 5, kFields = 6, kBytes = 8;  // 5 .. 7 bits; 6-bit fields (activations of 3, 4 bits); 8 bits
-constexpr int form_loads(int form) { return form <= 2 ? 1 : form <= 4 ? 2 : form == kFields ? 3 : 4; }
-
-// Run-time part of an operand: slots per row and k block; for kNibbles where the bits above the nibble are.
-struct Operand {
-    int slots;
-    int pair_slot, single_slot;          // kNibbles: slots of S of bits 4, 5 (first of two) and of the single top bit
-    uint32_t pair_mask, single_mask;     // 0 where the width has no such group
-    int single_pos;                      // bit position of the single group
-};
-template <int FORM>
-__device__ __forceinline__ Operand make_operand(int n)
-{
-    Operand o = {FORM == kFields ? 6 : FORM == kNibbles ? n : FORM, 0, 0, 0, 0, 0};
-    if constexpr (FORM == kNibbles) {
-        if (n >= 6) { o.pair_slot = 4; o.pair_mask = 0x30303030u; }
-        if (n & 1) { o.single_slot = n - 1; o.single_mask = 0x01010101u; o.single_pos = n - 1; }
-    }
-    return o;
-}
-
 // slot of load i of half KK
 template <int FORM, int KK>
 __device__ __forceinline__ int load_slot(const Operand &o, int i)
@@ -66,13 +44,6 @@ __device__ __forceinline__ int load_slot(const Operand &o, int i)
     if (FORM == kFields) return 3 * KK + i;
     if (FORM == kNibbles) return i < 2 ? 2 * KK + i : i == 2 ? o.pair_slot + KK : o.single_slot;
     return 4 * KK + i;
-}
-
-// shift right by S, or left for a negative S
-template <int S>
-__device__ __forceinline__ uint32_t shifted(uint32_t x)
-{
-    return S >= 0 ? x >> (S >= 0 ? S : 0) : x << (S < 0 ? -S : 0);
 }
 
 // dword D = 2 tt + jh of operand chunk I = 2 e + tp of half KK
@@ -99,12 +70,7 @@ __device__ __forceinline__ int operand_dword(const Operand &o, const uint4 (&raw
         };
         const uint32_t w0 = word(std::integral_constant<int, w>{}), w1 = word(std::integral_constant<int, w + 1>{}),
                        w2 = word(std::integral_constant<int, w + 2>{});
-        // the 48 bits of (e, t) start at bit 48 tt of the three words; byte c is the field at their bit 12 c + 6 jh: bytes
-        // 0 .. 2 lie in the 32 bits from there on, byte 3 is cut out of w1 (tt = 0) or w2
-        constexpr int at = 48 * tt + 6 * jh;
-        const uint32_t lo = at < 32 ? __builtin_amdgcn_alignbit(w1, w0, at & 31) : __builtin_amdgcn_alignbit(w2, w1, at & 31);
-        return (int)((lo & 0x0fu) | ((lo >> 4) & 0x0f00u) | ((lo >> 8) & 0x0f0000u) |
-                     (shifted<at + 36 - (tt ? 64 : 32) - 24>(tt ? w2 : w1) & 0x0f000000u));
+        return (int)field_dword<tt, jh>(w0, w1, w2);
     } else if constexpr (FORM == kNibbles) {
         uint32_t v = (vec_word<t>(raw[e]) >> (4 * jh)) & 0x0f0f0f0fu;
         v |= shifted<pair_at - 4>(vec_word<2 * e + tp>(raw[2])) & o.pair_mask;

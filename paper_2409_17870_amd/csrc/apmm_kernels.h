@@ -52,12 +52,17 @@ KernelTiming take_kernel_timing();  // returns the pair and clears it
 void note_kernel(const char *fmt, ...) __attribute__((format(printf, 1, 2)));
 const char *last_kernel();
 
-// Small-M weight-streaming kernels: on the matrix unit for p, q <= 4 (M <= 64; unpacked activation codes of 3 and 4 bits: M <= 32), XOR/popcount for wider codes (M <= 16, p not 3 or 4).
+// Small-M weight-streaming kernels: on the fp4 matrix operations for p, q <= 4 (M <= 64; unpacked activation codes of 3 and 4
+// bits: M <= 32), on the int8 ones where gemm_decode_i8_supported, XOR/popcount for what is left (M <= 16).
+// gemm_decode_supported is what the public small-M algo covers; launch_gemm_decode takes both sets.
 bool gemm_decode_supported(const GemmArgs &args);
 hipError_t launch_gemm_decode(const GemmArgs &args, hipStream_t stream);
 // The XOR/popcount small-M kernel whatever the code widths (M <= 16, q <= 4): design B at decode shapes.
 bool gemm_decode_valu_supported(const GemmArgs &args);
 hipError_t launch_gemm_decode_valu(const GemmArgs &args, hipStream_t stream);
+// The int8 small-M kernels (apmm_gemm_decode_i8.h); `tt`: tiles of 16 tokens, 1, 2 or 4.
+bool gemm_decode_i8_supported(const GemmArgs &args);
+hipError_t launch_gemm_decode_i8(const GemmArgs *args, int count, int tt, hipStream_t stream);
 // Up to kMaxGroup small-M problems of equal p, q in one launch; they must all be covered by the same
 // kernel variant (gemm_decode_group_supported).
 bool gemm_decode_group_supported(const GemmArgs *args, int count);

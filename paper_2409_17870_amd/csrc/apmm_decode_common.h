@@ -39,6 +39,21 @@ __device__ __forceinline__ int pick_problem(DecodeProblem &pr, uint32_t misc, co
     return block;
 }
 
+struct __attribute__((packed, aligned(1))) Codes16 { uint32_t x, y, z, w; };  // 16 codes at any address
+
+// Codes k .. k + 15 of a row from a load clamped to the row's last sixteen: `past` codes before position k are shifted out
+// and the row is followed by ones.
+__device__ __forceinline__ uint4 shift_past(uint4 v, int past)
+{
+    if (past <= 0) return v;
+    if (past >= 16) return make_uint4(~0u, ~0u, ~0u, ~0u);
+    if (past & 8) v = make_uint4(v.z, v.w, ~0u, ~0u);
+    if (past & 4) v = make_uint4(v.y, v.z, v.w, ~0u);
+    const int s = 8 * (past & 3);
+    return make_uint4(__builtin_amdgcn_alignbit(v.y, v.x, s), __builtin_amdgcn_alignbit(v.z, v.y, s),
+                      __builtin_amdgcn_alignbit(v.w, v.z, s), __builtin_amdgcn_alignbit(~0u, v.w, s));
+}
+
 // Builds the launch descriptor of `count` problems (16 output channels per workgroup each).
 template <class PassKb>
 inline bool make_group(const GemmArgs *gs, int count, int rows_per_wg, PassKb pass_kb, GroupArgs &ga)

@@ -67,11 +67,17 @@ __device__ __forceinline__ uint4 load_plane_half(const uint4 *slots, int n, int 
         }
         return make_uint4(out[0], out[1], out[2], out[3]);
     }
-    if (nibble_form(n) && i < 4) {  // words 4 hh, 4 hh + 1 from k step 2 hh, the other two from k step 2 hh + 1
-        const uint4 b0 = slots[2 * hh * kSlotVec], b1 = slots[(2 * hh + 1) * kSlotVec];
+    if (nibble_form(n)) {
+        // bits 0 .. 3: words 4 hh, 4 hh + 1 from k step 2 hh, the other two from k step 2 hh + 1; higher bits as in the group
+        // form.  Neighbouring lanes hold different planes: the loads are the same for all (under a branch each they
+        // would be waited for in turn), only what is done with them differs.
+        const int group = i < 2 * pair_groups(n) ? i / 2 * 2 + hh : n - 1;
+        const uint4 b0 = slots[(i < 4 ? 2 * hh : group) * kSlotVec], b1 = slots[(i < 4 ? 2 * hh + 1 : group) * kSlotVec];
         const uint32_t m = 0x11111111u;
-        return make_uint4(((b0.x >> i) & m) | (((b0.y >> i) & m) << 2), ((b0.z >> i) & m) | (((b0.w >> i) & m) << 2),
-                          ((b1.x >> i) & m) | (((b1.y >> i) & m) << 2), ((b1.z >> i) & m) | (((b1.w >> i) & m) << 2));
+        if (i < 4)
+            return make_uint4(((b0.x >> i) & m) | (((b0.y >> i) & m) << 2), ((b0.z >> i) & m) | (((b0.w >> i) & m) << 2),
+                              ((b1.x >> i) & m) | (((b1.y >> i) & m) << 2), ((b1.z >> i) & m) | (((b1.w >> i) & m) << 2));
+        return plane_half_from(b0, n, i, hh);
     }
     return plane_half_from(slots[(i < 2 * pair_groups(n) ? (i / 2 * 2 + hh) : (n - 1)) * kSlotVec], n, i, hh);
 }
@@ -489,7 +495,9 @@ void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg
     // any condition on the lane (lanes with nothing to load read the first chunk of the matrix instead and mask it
     // away at the point of use): a load inside a divergent branch makes the wave wait for it, and for everything
     // requested before it, at the end of the branch.
-    // CODES == 2: any K and alignment, byte by byte (correct, slow).
+    // CODES == 2: any K and alignment.  The same loads at any address, clamped to the row's last sixteen codes; what lies
+    // before the chunk is shifted out where the chunk is used (byte by byte, the earlier form: 16 tokens at 4096 x 4097
+    // 22 us, 8 tokens 12.7 us).  Rows of fewer than sixteen codes byte by byte.
     auto load_chunks = [&](int tt, int it, uint4 (&v)[NJ]) __attribute__((always_inline)) {
         const int64_t k0 = (int64_t)4 * kKBlock * (wave + (int64_t)kWaves * it) + 16 * (lane & 31);
         const int64_t m_tile = pr.M - tt * 16;  // tokens of this tile that exist
@@ -501,7 +509,11 @@ void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg
         // with nothing to load (odd token past M, chunk in the padding) read the first chunk of the pair's first
         // token, which exists whenever the load is issued at all.
         uint32_t lane_off = 0;
-        if (k0 + 16 <= row_len) lane_off = (uint32_t)((lane >> 5) * row_len + k0);
+        if constexpr (CODES == 1) {
+            if (k0 + 16 <= row_len) lane_off = (uint32_t)((lane >> 5) * row_len + k0);
+        } else {
+            lane_off = (uint32_t)((lane >> 5) * row_len + (k0 < row_len - 16 ? k0 : row_len - 16));
+        }
 #pragma unroll
         for (int jj = 0; jj < NJ; ++jj) {
             const int64_t t = tt * 16 + 2 * jj + (lane >> 5);
@@ -510,22 +522,23 @@ void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg
                 const uint32_t off = t < pr.M ? lane_off : 0u;
                 if (2 * jj < m_tile) v[jj] = *reinterpret_cast<const uint4 *>(pair_row + off);  // uniform: token pairs that exist
                 else v[jj] = make_uint4(0, 0, 0, 0);
+            } else if (row_len >= 16) {
+                const uint8_t *pair_row = static_cast<const uint8_t *>(pr.a) + (int64_t)(tt * 16 + 2 * jj) * row_len;
+                const uint32_t off = t < pr.M ? lane_off : lane_off - (uint32_t)((lane >> 5) * row_len);  // (an odd last token's neighbour reads its row)
+                v[jj] = make_uint4(0, 0, 0, 0);
+                if (2 * jj < m_tile) {
+                    const Codes16 c = *reinterpret_cast<const Codes16 *>(pair_row + off);
+                    v[jj] = make_uint4(c.x, c.y, c.z, c.w);
+                }
             } else {
-                uint32_t d[4] = {0u, 0u, 0u, 0u};  // tokens past M: zero words, as the padded rows of a packed operand
-                if (t < pr.M) {
-                    const uint8_t *src = static_cast<const uint8_t *>(pr.a) + t * row_len + k0;
-                    const int64_t left = row_len - k0;
-                    const int count = left >= 16 ? 16 : (left > 0 ? (int)left : 0);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) d[i] = 0xffffffffu;  // positions past K hold the all-ones padding code
-#pragma unroll 1
-                    for (int e = 0; e < count; ++e) {
-                        const uint32_t flip = (uint32_t)(src[e] ^ 0xffu) << (8 * (e & 3));
+                uint32_t d[4] = {~0u, ~0u, ~0u, ~0u};
+                if (t < pr.M && k0 == 0)
+                    for (int e = 0; e < (int)row_len; ++e) {
+                        const uint32_t flip = (uint32_t)(static_cast<const uint8_t *>(pr.a)[t * row_len + e] ^ 0xffu) << (8 * (e & 3));
 #pragma unroll
                         for (int i = 0; i < 4; ++i)
                             if (i == (e >> 2)) d[i] ^= flip;
                     }
-                }
                 v[jj] = make_uint4(d[0], d[1], d[2], d[3]);
             }
         }
@@ -545,15 +558,17 @@ void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg
             if (2 * jj >= m_tile) continue;  // uniform; the slots of tokens that do not exist are never stored outputs
             // what the lane loaded counts only for a token that exists and a chunk inside the row; a chunk in the
             // padding of an existing token holds the all-ones code, a token past M zero words
-            uint32_t m_and = code_mask, m_or = 0u;
+            const bool valid = tt * 16 + 2 * jj + (lane >> 5) < pr.M;
+            uint32_t m_and = valid ? code_mask : 0u, m_or = 0u;
+            uint4 c = v[jj];
             if constexpr (CODES == 1) {
-                const bool valid = tt * 16 + 2 * jj + (lane >> 5) < pr.M;
                 m_and = valid && inside ? code_mask : 0u;
                 m_or = valid && !inside ? code_mask : 0u;
+            } else if (pr.K >= 16) {
+                c = shift_past(c, (int)(k0 - (pr.K - 16)));
             }
             // dword i = 2 t2 + jh of the chunk holds the elements (t = 2 tp + t2, jh, c = 0..3) of the word
-            const uint32_t d0 = (v[jj].x & m_and) | m_or, d1 = (v[jj].y & m_and) | m_or, d2 = (v[jj].z & m_and) | m_or,
-                           d3 = (v[jj].w & m_and) | m_or;
+            const uint32_t d0 = (c.x & m_and) | m_or, d1 = (c.y & m_and) | m_or, d2 = (c.z & m_and) | m_or, d3 = (c.w & m_and) | m_or;
             if constexpr (AF) {
                 // Field form: the chunk's 16 codes are the fields 16 tp ... 16 tp + 15 of k step w / 2 (tp = w % 2), i.e. words
                 // 6 (w / 2) + 3 tp ... + 2 of the row's 24: byte c of dword i goes to field 8 (i / 2) + 2 c + i % 2, six bits each.

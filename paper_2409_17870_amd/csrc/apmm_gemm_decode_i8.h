@@ -103,21 +103,6 @@ __device__ __forceinline__ uint32_t unit_dword(const Operand &o, const LaneUnit<
     }
 }
 
-struct __attribute__((packed, aligned(1))) Codes16 { uint32_t x, y, z, w; };  // 16 codes at any address
-
-// Codes k .. k + 15 of a row from a load clamped to the row's last sixteen: `past` codes before position k are shifted out
-// and the row is followed by ones.
-__device__ __forceinline__ uint4 shift_past(uint4 v, int past)
-{
-    if (past <= 0) return v;
-    if (past >= 16) return make_uint4(~0u, ~0u, ~0u, ~0u);
-    if (past & 8) v = make_uint4(v.z, v.w, ~0u, ~0u);
-    if (past & 4) v = make_uint4(v.y, v.z, v.w, ~0u);
-    const int s = 8 * (past & 3);
-    return make_uint4(__builtin_amdgcn_alignbit(v.y, v.x, s), __builtin_amdgcn_alignbit(v.z, v.y, s),
-                      __builtin_amdgcn_alignbit(v.w, v.z, s), __builtin_amdgcn_alignbit(~0u, v.w, s));
-}
-
 template <int FA, int FB, int TT, int RT>
 __global__ __launch_bounds__(kDecodeThreads, TT * RT == 1 ? 4 : 2)  // waves per SIMD aimed at
 void gemm_decode_i8_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg, int k_arg, uint32_t misc_arg /* M | problems << 12 */,

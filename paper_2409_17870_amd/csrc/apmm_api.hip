@@ -265,7 +265,7 @@ apmm_status apmm_gemm_from_codes(int64_t M, int64_t N, int64_t K, int p, int q, 
     // asked for one where the XOR/popcount kernel does not go).  32 tokens, one launch against two: 4096 x 4096 W4A8 / W8A8 /
     // W2A6 7.2 / 8.0 / 6.9 against 7.4 / 9.7 / 8.3 us, 11008 x 4096 13.3 / 15.5 / 11.9 against 13.7 / 17.1 / 13.3 us, 4096 x
     // 11008 15.2 / 17.7 / 14.3 against 13.9 / 17.7 / 14.1 us; 64 tokens: two launches win at most widths.
-    const bool wide_pays = apmm::gemm_decode_i8_supported(g) && (M <= 16 || (M <= 32 && K <= 8192));
+    const bool wide_pays = !fused_ok && apmm::gemm_decode_i8_supported(g) && (M <= 16 || (M <= 32 && K <= 8192));
     if ((fused_ok && (fused_pays || !room)) || (wide_pays && room)) {
         const hipError_t e = apmm::launch_gemm_decode(g, s);
         if (e != hipSuccess) return fail_hip(e, "apmm_gemm_from_codes");

@@ -386,6 +386,17 @@ def test_gemm_from_codes_through_the_workspace(gpu, oracle, M, N, K, p, q):
     check_f16(c16, want, data, oracle)
 
 
+@pytest.mark.parametrize("M,p,q,packs", [(8, 4, 4, False), (9, 4, 4, True), (32, 3, 3, True), (16, 2, 4, False), (16, 8, 4, False), (17, 8, 4, False),
+                                         (33, 8, 8, True)])
+def test_from_codes_route_with_a_workspace(gpu, oracle, M, p, q, packs):
+    """Which token counts are taken in one launch and which are packed first."""
+    case = dict(M=M, N=4096, K=1024, p=p, q=q, a_dist="bernoulli", scaled=True)
+    data = inputs.make_case(case, 7100 + M + 10 * p + q)
+    c32, _ = run_from_codes(gpu, data, case, workspace=True)
+    assert gpu[1].apmm_last_gemm_kernel().endswith(",packed>" if packs else ",codes>")
+    assert np.array_equal(c32.astype(np.int64), oracle.gemm_i64(data["a_codes"], data["w_codes"], p, q))
+
+
 @pytest.mark.parametrize("M,K,p,q", [(16, 11008, 8, 4), (8, 9000, 8, 2), (13, 20000, 5, 3), (64, 11008, 2, 2),
                                      (33, 20000, 2, 1), (48, 8200, 1, 2), (16, 40000, 2, 2), (2, 70000, 2, 2)])
 def test_decode_kernels_with_k_beyond_one_pass(gpu, oracle, M, K, p, q):

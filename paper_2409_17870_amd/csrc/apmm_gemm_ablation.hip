@@ -18,6 +18,7 @@
 // Same tile map and operand loads as the product kernel (apmm_gemm_mfma_direct.h): 128 x 128 tile, 2 x 2 waves
 // of 64 x 64, lane l owns row l % 32 and k block l / 32 of a two-block stage, raw words double buffered in
 // registers.  Activations of 1 or 2 bits only (wider ones are stored in the field form).
+#include "apmm_fields.h"
 #include "apmm_mfma_common.h"
 
 namespace apmm {
@@ -91,7 +92,8 @@ __global__ __launch_bounds__(256) void gemm_mfma_planes_kernel(GemmArgs g, int32
                 for (int bj = 0; bj < WN; ++bj)
 #pragma unroll
                     for (int v = 0; v < 16; ++v) acc[j][bi][bj][v] = 0.f;
-        uint4 ra[2][WM][2], rb[2][WN][2];  // raw words by stage parity
+        constexpr bool FOLDED = weight_folded_form(Q);  // all slots, plane bb of the whole code
+        uint4 ra[2][WM][2], rb[2][WN][FOLDED ? Q : 2];  // raw words by stage parity
         auto load_stage = [&](int buf, int64_t st) __attribute__((always_inline)) {
 #pragma unroll
             for (int bi = 0; bi < WM; ++bi) {
@@ -100,6 +102,11 @@ __global__ __launch_bounds__(256) void gemm_mfma_planes_kernel(GemmArgs g, int32
             }
 #pragma unroll
             for (int bj = 0; bj < WN; ++bj) {
+                if constexpr (FOLDED) {
+#pragma unroll
+                    for (int sl = 0; sl < Q; ++sl) rb[buf][bj][sl] = pb_src[bj][st * kStageVecB + sl * kSlotVec];
+                    continue;
+                }
                 rb[buf][bj][0] = pb_src[bj][st * kStageVecB + slot_b * kSlotVec];
                 if constexpr (!BS) rb[buf][bj][1] = pb_src[bj][st * kStageVecB + (slot_b + 1) * kSlotVec];
             }
@@ -127,7 +134,18 @@ __global__ __launch_bounds__(256) void gemm_mfma_planes_kernel(GemmArgs g, int32
                     b8[bj] = v8i{0, 0, 0, 0, 0, 0, 0, 0};
                     mfma::static_for<4>([&](auto d_c) __attribute__((always_inline)) {
                         constexpr int d = decltype(d_c)::value;
-                        b8[bj][d] = (int)plane_dword<BS, ks, d>(nb[bj][0], nb[bj][1], bb);
+                        if constexpr (FOLDED) {  // nibbles of t = d
+                            auto word = [&](auto j_c) __attribute__((always_inline)) {
+                                constexpr int w = decltype(j_c)::value < Q ? fold_word_at(Q, ks, decltype(j_c)::value) : 0;
+                                return mfma::vec_word<w & 3>(rb[buf][bj][w >> 2]);
+                            };
+                            const uint32_t u = folded_nibbles<Q, d / 2, d % 2>(
+                                word(std::integral_constant<int, 0>{}), word(std::integral_constant<int, 1>{}),
+                                word(std::integral_constant<int, 2>{}), word(std::integral_constant<int, 3>{}));
+                            b8[bj][d] = (int)(((~u << (3 - bb)) & 0x88888888u) | 0x22222222u);
+                        } else {
+                            b8[bj][d] = (int)plane_dword<BS, ks, d>(nb[bj][0], nb[bj][1], bb);
+                        }
                     });
                 }
 #pragma unroll
@@ -157,6 +175,10 @@ __global__ __launch_bounds__(256) void gemm_mfma_planes_kernel(GemmArgs g, int32
     };
     // weight plane i: bit b of the pair group at slots 2 (i / 2), 2 (i / 2) + 1, or the single group at slot Q - 1
     auto sweep_plane = [&](int i, int j0, auto &&fold) __attribute__((always_inline)) {
+        if constexpr (weight_folded_form(Q)) {
+            sweep(std::false_type{}, 0, i, j0, fold);
+            return;
+        }
         if (i < 2 * pair_groups(Q)) sweep(std::false_type{}, 2 * (i / 2), i & 1, j0, fold);
         else sweep(std::true_type{}, Q - 1, 0, j0, fold);
     };

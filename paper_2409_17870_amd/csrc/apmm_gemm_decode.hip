@@ -26,6 +26,7 @@
 #include <algorithm>
 
 #include "apmm_decode_common.h"
+#include "apmm_fields.h"
 
 namespace apmm {
 namespace {
@@ -82,22 +83,29 @@ __device__ __forceinline__ uint4 load_plane_half(const uint4 *slots, int n, int 
     return plane_half_from(slots[(i < 2 * pair_groups(n) ? (i / 2 * 2 + hh) : (n - 1)) * kSlotVec], n, i, hh);
 }
 
-// The same from slots already in registers (weights of a Q-bit operand).
-template <int Q>
-__device__ __forceinline__ uint4 plane_half_words_reg(const uint4 (&slot)[Q], int i, int hh)
+// The same from slots already in registers (weights of a Q-bit operand): words 4 HH .. 4 HH + 3.
+template <int Q, int HH>
+__device__ __forceinline__ uint4 plane_half_words_reg(const uint4 (&slot)[Q], int i)
 {
-    if (i < 2 * pair_groups(Q)) {
-        const uint4 s = slot[i / 2 * 2 + hh];
-        const int b = i & 1;
-        return make_uint4((s.x >> b) & 0x55555555u, (s.y >> b) & 0x55555555u, (s.z >> b) & 0x55555555u,
-                          (s.w >> b) & 0x55555555u);
+    if constexpr (Q == 2) {
+        const uint4 s = slot[HH];
+        return make_uint4((s.x >> i) & 0x55555555u, (s.y >> i) & 0x55555555u, (s.z >> i) & 0x55555555u, (s.w >> i) & 0x55555555u);
+    } else if constexpr (Q == 1) {
+        const uint4 l = slot[0];
+        constexpr int k0 = 2 * HH, k1 = 2 * HH + 1;
+        return make_uint4(((l.x >> k0) & 0x11111111u) | (((l.y >> k0) & 0x11111111u) << 2),
+                          ((l.z >> k0) & 0x11111111u) | (((l.w >> k0) & 0x11111111u) << 2),
+                          ((l.x >> k1) & 0x11111111u) | (((l.y >> k1) & 0x11111111u) << 2),
+                          ((l.z >> k1) & 0x11111111u) | (((l.w >> k1) & 0x11111111u) << 2));
+    } else {  // folded form: k steps 2 HH and 2 HH + 1
+        uint32_t in[2][4] = {};
+        mfma::static_for<2 * Q>([&](auto j_c) __attribute__((always_inline)) {
+            constexpr int e = decltype(j_c)::value / Q, j = decltype(j_c)::value % Q, w = fold_word_at(Q, 2 * HH + e, j);
+            in[e][j] = mfma::vec_word<w & 3>(slot[w >> 2]);
+        });
+        return make_uint4(folded_plane<Q, 0>(in[0][0], in[0][1], in[0][2], in[0][3], i), folded_plane<Q, 1>(in[0][0], in[0][1], in[0][2], in[0][3], i),
+                          folded_plane<Q, 0>(in[1][0], in[1][1], in[1][2], in[1][3], i), folded_plane<Q, 1>(in[1][0], in[1][1], in[1][2], in[1][3], i));
     }
-    const uint4 l = slot[Q - 1];
-    const int k0 = 2 * hh, k1 = 2 * hh + 1;
-    return make_uint4(((l.x >> k0) & 0x11111111u) | (((l.y >> k0) & 0x11111111u) << 2),
-                      ((l.z >> k0) & 0x11111111u) | (((l.w >> k0) & 0x11111111u) << 2),
-                      ((l.x >> k1) & 0x11111111u) | (((l.y >> k1) & 0x11111111u) << 2),
-                      ((l.z >> k1) & 0x11111111u) | (((l.w >> k1) & 0x11111111u) << 2));
 }
 
 // The 128 codes of k block kb of activation row m as bytes: d[8 ks + 2 t + jh] holds the codes of elements
@@ -266,9 +274,10 @@ __global__ __launch_bounds__(kThreads) void gemm_decode_kernel(GroupArgs ga)
             }
             uint4 w[Q][2];
 #pragma unroll
-            for (int i = 0; i < Q; ++i)
-#pragma unroll
-                for (int hh = 0; hh < 2; ++hh) w[i][hh] = plane_half_words_reg<Q>(wraw, i, hh);
+            for (int i = 0; i < Q; ++i) {
+                w[i][0] = plane_half_words_reg<Q, 0>(wraw, i);
+                w[i][1] = plane_half_words_reg<Q, 1>(wraw, i);
+            }
             const uint4 *arow = a_lds + (kb - kb0) * chunks_per_kb;
 #pragma unroll
             for (int m = 0; m < MT; ++m) {
@@ -414,8 +423,6 @@ void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg
     static_assert((P <= 2 || (activation_field_form(P) && NJ == 8)) && Q <= 4,
                   "one plane group per activation, or activations in the field form (ready-made E2M3 operands); "
                   "weights of one or two plane groups");
-    constexpr int WS = Q > 2 ? Q : 2;        // weight slots held per channel tile
-    constexpr int NG = pair_groups(Q) + (has_single_group(Q) ? 1 : 0);  // plane groups of the weights
     constexpr bool AF = activation_field_form(P);
     constexpr int SA = activation_slots(P);  // slots of an activation row and k block
     static_assert(NJ == 8 || (NJ == 1 && CODES == 1 && TT == 1), "NJ = 1: codes of at most two tokens");
@@ -467,7 +474,7 @@ void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg
         }
     }
 
-    uint4 wnext[RT][WS], anext[TT][AF ? 6 : 2];
+    uint4 wnext[RT][Q], anext[TT][SA];
     auto load_packed = [&](int it) __attribute__((always_inline)) {
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
@@ -543,7 +550,7 @@ void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg
             }
         }
     };
-    auto chunks_to_fragment = [&](int tt, int it, const uint4 (&v)[NJ], uint4 (&aq)[AF ? 6 : 2]) __attribute__((always_inline)) {
+    auto chunks_to_fragment = [&](int tt, int it, const uint4 (&v)[NJ], uint4 (&aq)[SA]) __attribute__((always_inline)) {
         constexpr uint32_t code_mask = 0x01010101u * ca;
         // the wave's previous fragment has been read by every lane before anything is overwritten
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -660,7 +667,7 @@ void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg
     for (int tt = 0; tt < TT; ++tt) acc_pa[tt] = mfma::v4f{0.f, 0.f, 0.f, 0.f};
 
     for (int it = 0; it < iters; ++it) {
-        uint4 wq[RT][WS], aq[TT][AF ? 6 : 2];
+        uint4 wq[RT][Q], aq[TT][SA];
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
@@ -689,64 +696,40 @@ void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg
         }
         mfma::static_for<4>([&](auto ks_c) __attribute__((always_inline)) {
             constexpr int ks = decltype(ks_c)::value;
+            constexpr int format_w = mfma::operand_format(Q), format_a = mfma::operand_format(P);
             mfma::v8i b8[TT];
 #pragma unroll
-            for (int tt = 0; tt < TT; ++tt) b8[tt] = mfma::v8i{0, 0, 0, 0, 0, 0, 0, 0};
-            mfma::static_for<4>([&](auto d_c) __attribute__((always_inline)) {
-                constexpr int d = decltype(d_c)::value;
-#pragma unroll
-                for (int tt = 0; tt < TT; ++tt) {
-                    if constexpr (AF) {
-                    } else if constexpr (P == 1) {
-                        b8[tt][d] = (int)mfma::fp4_single_dword<ks, d>(aq[tt][0]);
-                    } else {
-                        b8[tt][d] = (int)mfma::fp4_pair_dword<ks, d>(aq[tt][0], aq[tt][1]);
-                    }
+            for (int tt = 0; tt < TT; ++tt) {
+                if constexpr (AF) {
+                    b8[tt] = mfma::field_operand<ks>(aq[tt]);
+                } else {
+                    mfma::v4i b;
+                    mfma::static_for<4>([&](auto d_c) __attribute__((always_inline)) {
+                        constexpr int d = decltype(d_c)::value;
+                        b[d] = (int)mfma::operand_dword<P, ks, d>(aq[tt]);
+                    });
+                    b8[tt] = mfma::widen(b);
                 }
-            });
-            if constexpr (AF) {
-                // field form: words 6 ks .. 6 ks + 5 of the lane's 24 are the E2M3 operand of this k step as they stand
-                mfma::static_for<6>([&](auto w_c) __attribute__((always_inline)) {
-                    constexpr int w = 6 * ks + decltype(w_c)::value;
-#pragma unroll
-                    for (int tt = 0; tt < TT; ++tt) b8[tt][decltype(w_c)::value] = (int)mfma::vec_word<w & 3>(aq[tt][w >> 2]);
-                });
             }
-            // One MFMA per plane group of the weights (pair groups at code bits 2 g, a single group at bit Q - 1), all into
-            // the same accumulator: the group's bit position goes into the weights' power-of-two operand scale.
-            // E8M0 exponents: 2^2 per operand turns (ua/2)(uw/2) into 4 ua uw; field form: (ua/8)(uw/2) 2^6.
-            // Operand formats: 4 = E2M1, 2 = E2M3.
-            mfma::static_for<NG>([&](auto g_c) __attribute__((always_inline)) {
-                constexpr int grp = decltype(g_c)::value;
-                constexpr bool SINGLE = grp >= pair_groups(Q);
-                constexpr int slot = SINGLE ? Q - 1 : 2 * grp;
-                mfma::v8i a8[RT];
 #pragma unroll
-                for (int rt = 0; rt < RT; ++rt) a8[rt] = mfma::v8i{0, 0, 0, 0, 0, 0, 0, 0};
-                mfma::static_for<4>([&](auto d_c) __attribute__((always_inline)) {
+            for (int rt = 0; rt < RT; ++rt) {
+                mfma::OperandFrag<Q> a;
+                mfma::static_for<mfma::operand_dwords(Q)>([&](auto d_c) __attribute__((always_inline)) {
                     constexpr int d = decltype(d_c)::value;
-#pragma unroll
-                    for (int rt = 0; rt < RT; ++rt) {
-                        if constexpr (SINGLE) a8[rt][d] = (int)mfma::fp4_single_dword<ks, d>(wq[rt][slot]);
-                        else a8[rt][d] = (int)mfma::fp4_pair_dword<ks, d>(wq[rt][slot], wq[rt][slot + 1]);
-                    }
+                    a[d] = (int)mfma::operand_dword<Q, ks, d>(wq[rt]);
                 });
 #pragma unroll
-                for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-                    for (int tt = 0; tt < TT; ++tt)
-                        acc[rt][tt] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
-                            a8[rt], b8[tt], acc[rt][tt], 4, AF ? 2 : 4, 0,
-                            (AF ? 130 : 129) + slot + (SINGLE ? mfma::fp4_single_exponent(ks) : 0), 0,
-                            AF ? 130 : 129 + (P == 1 ? mfma::fp4_single_exponent(ks) : 0));
-            });
+                for (int tt = 0; tt < TT; ++tt)
+                    acc[rt][tt] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
+                        mfma::widen(a), b8[tt], acc[rt][tt], format_w, format_a, 0, mfma::operand_exponent(Q, ks), 0,
+                        mfma::operand_exponent(P, ks));
+            }
             if constexpr (CODES) {
                 const mfma::v8i ones = {0x11111111, 0x11111111, 0x11111111, 0x11111111, 0, 0, 0, 0};  // E2M1 0.5 = the code 1
 #pragma unroll
                 for (int tt = 0; tt < TT; ++tt)
                     acc_pa[tt] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
-                        ones, b8[tt], acc_pa[tt], 4, AF ? 2 : 4, 0, AF ? 130 : 129, 0,
-                        AF ? 130 : 129 + (P == 1 ? mfma::fp4_single_exponent(ks) : 0));
+                        ones, b8[tt], acc_pa[tt], 4, format_a, 0, 129, 0, mfma::operand_exponent(P, ks));
             }
         });
     }

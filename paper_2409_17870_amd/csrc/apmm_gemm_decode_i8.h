@@ -31,12 +31,14 @@ using mfma::v4i;
 
 constexpr int kCodes = 9;  // unpacked codes, one per byte
 
-// What a lane loads of its 32 codes: whole vectors and two-word halves of slot vectors.
+// What a lane loads of its 32 codes: whole slot vectors, two-word halves of them, single words.
 template <int FORM>
 struct LaneUnit {
-    static constexpr int kVecs = FORM == 1 || FORM == 3 ? 1 : FORM == kNibbles || FORM == kBytes || FORM == kCodes ? 2 : 0;
-    static constexpr int kHalves = FORM == 2 || FORM == 3 || FORM == kNibbles ? 1 : FORM == 4 ? 2 : FORM == kFields ? 3 : 0;
-    static constexpr int kWords = 4 * kVecs + 2 * kHalves;
+    static constexpr int kVecs = FORM == 1 || FORM == 4 ? 1 : FORM == kNibbles || FORM == kBytes || FORM == kCodes ? 2 : 0;
+    static constexpr int kHalves = FORM == 2 || FORM == 3 || FORM == kNibbles ? 1 : FORM == kFields ? 3 : 0;
+    static constexpr int kSingles = FORM == 3 ? 1 : 0;
+    static constexpr int kWords = 4 * kVecs + 2 * kHalves + kSingles;
+    uint32_t s[kSingles ? kSingles : 1];
     uint4 v[kVecs ? kVecs : 1];
     uint2 h[kHalves ? kHalves : 1];
 };
@@ -58,10 +60,9 @@ __device__ __forceinline__ void load_unit(const Operand &o, const uint32_t *src,
         u.h[0] = words(2 * ks);
     } else if constexpr (FORM == 3) {
         u.h[0] = words(2 * ks);
-        u.v[0] = vec(2);
+        u.s[0] = src[2 * kPlaneWords + ks];
     } else if constexpr (FORM == 4) {
-        u.h[0] = words(2 * ks);
-        u.h[1] = words(8 + 2 * ks);
+        u.v[0] = vec(ks);
     } else if constexpr (FORM == kNibbles) {
         u.v[0] = vec(ks);
         u.h[0] = words(4 * o.pair_slot + 2 * ks);
@@ -88,9 +89,9 @@ __device__ __forceinline__ uint32_t unit_dword(const Operand &o, const LaneUnit<
     } else if constexpr (FORM == 2) {
         return (half_word<TP>(u.h[0]) >> pair_at) & 0x03030303u;
     } else if constexpr (FORM == 3) {
-        return ((half_word<TP>(u.h[0]) >> pair_at) & 0x03030303u) | ((((vec_word<t>(u.v[0]) >> ks) >> (4 * jh)) & 0x01010101u) << 2);
+        return folded_dword<3, TP, tt, jh>(u.h[0].x, u.h[0].y, u.s[0], 0u);
     } else if constexpr (FORM == 4) {
-        return ((half_word<TP>(u.h[0]) >> pair_at) & 0x03030303u) | (shifted<pair_at - 2>(half_word<TP>(u.h[1])) & 0x0c0c0c0cu);
+        return folded_dword<4, TP, tt, jh>(u.v[0].x, u.v[0].y, u.v[0].z, u.v[0].w);
     } else if constexpr (FORM == kNibbles) {
         uint32_t v = (vec_word<t>(u.v[0]) >> (4 * jh)) & 0x0f0f0f0fu;
         v |= shifted<pair_at - 4>(half_word<TP>(u.h[0])) & o.pair_mask;

@@ -126,47 +126,34 @@ __global__ __launch_bounds__(256) void gemm_mfma_direct_kernel(const uint32_t *a
     const int64_t m_lane = m0 + wave_m * WM * 32 + kh * 4, n_lane = n0 + wave_n * WN * 32 + r32;
 
     v16f acc[WM][WN];  // by row block of the wave tile; phase ph owns blocks split_row0(ph) ...
-    uint4 ra[2][WMX][AF ? 6 : 2], rb[2][WN][2];  // raw words of a group (a single group uses [0] only; the field
-                                                 // form all six slots), by stage parity
-    v4i af[2][WMX], bf[2][WN];          // expanded fragments, by k step parity
+    uint4 ra[2][WMX][SLOTS_A], rb[2][WN][Q];  // raw words, by stage parity
+    v4i af[2][AF ? 1 : WMX];                  // formed fragments, by k step parity
+    OperandFrag<Q> bf[2][WN];
     const int64_t nst = g.nkb / 2;      // the packed K is a multiple of 512: an even number of whole stages
     using I0 = std::integral_constant<int, 0>;
 
-    // raw words of stage st of phase ph into buffer buf: the activation group at slot slot_a, the weight group at
-    // slot slot_b (AS / BS: the group is a single one)
-    auto load_stage_of = [&](auto ph_c, auto as_c, auto bs_c, auto buf_c, int64_t st, int slot_a, int slot_b)
-                             __attribute__((always_inline)) {
+    // raw words of stage st of phase ph into buffer buf
+    auto load_stage_of = [&](auto ph_c, auto buf_c, int64_t st) __attribute__((always_inline)) {
         constexpr int ph = decltype(ph_c)::value, buf = decltype(buf_c)::value;
-        constexpr bool AS = decltype(as_c)::value, BS = decltype(bs_c)::value;
         constexpr int WMP = split_rows(WM, SPLIT, ph), ROW0 = split_row0(WM, SPLIT, ph);
 #pragma unroll
-        for (int bi = 0; bi < WMP; ++bi) {
-            const uint4 *src = pa_src[ROW0 + bi];
-            if constexpr (AF) {
+        for (int bi = 0; bi < WMP; ++bi)
 #pragma unroll
-                for (int sl = 0; sl < 6; ++sl) ra[buf][bi][sl] = src[st * kStageVecA + sl * kSlotVec];
-            } else {
-                ra[buf][bi][0] = src[st * kStageVecA + slot_a * kSlotVec];
-                if constexpr (!AS) ra[buf][bi][1] = src[st * kStageVecA + (slot_a + 1) * kSlotVec];
-            }
-        }
+            for (int sl = 0; sl < SLOTS_A; ++sl) ra[buf][bi][sl] = pa_src[ROW0 + bi][st * kStageVecA + sl * kSlotVec];
 #pragma unroll
-        for (int bj = 0; bj < WN; ++bj) {
-            rb[buf][bj][0] = pb_src[bj][st * kStageVecB + slot_b * kSlotVec];
-            if constexpr (!BS) rb[buf][bj][1] = pb_src[bj][st * kStageVecB + (slot_b + 1) * kSlotVec];
-        }
+        for (int bj = 0; bj < WN; ++bj)
+#pragma unroll
+            for (int sl = 0; sl < Q; ++sl) rb[buf][bj][sl] = pb_src[bj][st * kStageVecB + sl * kSlotVec];
     };
 
     // Order of the first requests.  A kernel starts with cold caches and every dependent round trip to memory
     // costs about a microsecond, so everything the prologue needs is requested before anything is used: the
-    // operands of stage 0 of the first sweep (slots 0 of both operands), then the code sums, then the scales.
+    // operands of stage 0, then the code sums, then the scales.
     // (The one-phase 256 x 256 kernel has no registers to hold the operands while all 256 accumulators are being
     // set up; it requests them after that, one round trip later.  The kernels with 4-bit activations in the
     // field form measured 1 - 2 us slower with the early request and keep the old order too.)
-    constexpr bool AS0 = !AF && pair_groups(P) == 0, BS0 = pair_groups(Q) == 0;  // the first sweep's groups
     constexpr bool PRELOAD = !(WM == 4 && WN == 4 && SPLIT == 1) && !AF;
-    if constexpr (PRELOAD)
-        load_stage_of(I0{}, std::integral_constant<bool, AS0>{}, std::integral_constant<bool, BS0>{}, I0{}, 0, 0, 0);
+    if constexpr (PRELOAD) load_stage_of(I0{}, I0{}, 0);
     uint32_t pw_raw[WN], pa_raw[WM];
 #pragma unroll
     for (int bj = 0; bj < WN; ++bj) {
@@ -286,40 +273,28 @@ __global__ __launch_bounds__(256) void gemm_mfma_direct_kernel(const uint32_t *a
         __builtin_nontemporal_store((int32_t)acc[bi][bj][v], reinterpret_cast<int32_t *>(st_ptr + bj * 128));
     };
 
-    // One sweep of K for phase ph, the activation group at slot slot_a and the weight group at slot slot_b
-    // (AS / BS: the group is a single one).  exp_a + exp_b - 254 = 4 + the bit positions of the two groups.
+    // The sweep of K for phase ph.
     // STORES: the first STORE_STAGES stages also store phase ph - 1.
     // PRELOADED: stage 0 is already in buffer 0 (the prologue's request).
-    auto sweep = [&](auto ph_c, auto stores_c, auto as_c, auto bs_c, int slot_a, int slot_b, int exp_a, int exp_b,
-                     auto preloaded_c) __attribute__((always_inline)) {
+    auto sweep = [&](auto ph_c, auto stores_c, auto preloaded_c) __attribute__((always_inline)) {
         constexpr int ph = decltype(ph_c)::value;
         constexpr bool STORES = decltype(stores_c)::value, PRELOADED = decltype(preloaded_c)::value;
-        constexpr bool AS = decltype(as_c)::value, BS = decltype(bs_c)::value;
         constexpr int WMP = split_rows(WM, SPLIT, ph), ROW0 = split_row0(WM, SPLIT, ph);  // this phase's row blocks
         constexpr int PER_KS = WMP * WN;         // MFMAs per k step
-        constexpr int FRAG0 = AF ? WMP : 0;      // first fragment that needs expanding (A blocks come first)
-        constexpr int FRAGS = WMP + WN;          // operand fragments per k step
-        constexpr int TASKS = 4 * (FRAGS - FRAG0);  // expansion dwords per k step
+        constexpr int TASKS_A = AF ? 0 : 4 * WMP, DB = operand_dwords(Q);
+        constexpr int TASKS = TASKS_A + DB * WN;  // operand dwords to form per k step, A blocks first
         constexpr int TPM = (TASKS + PER_KS - 1) / PER_KS;  // tasks per MFMA (the last MFMAs of a step may get fewer)
         constexpr int STAGE_ELEMS = KS * PER_KS / STORE_EVERY;  // outputs of the previous phase stored under one stage
-        auto load_stage = [&](auto buf_c, int64_t st) __attribute__((always_inline)) {
-            load_stage_of(ph_c, as_c, bs_c, buf_c, st, slot_a, slot_b);
-        };
-        // dword d of fragment f (f < WMP: A block f, else B block f - WMP) of k step ks, from buffer buf
-        auto expand = [&](auto buf_c, auto ks_c, auto f_c, auto d_c) __attribute__((always_inline)) {
-            constexpr int buf = decltype(buf_c)::value, ks = decltype(ks_c)::value, f = decltype(f_c)::value,
-                          d = decltype(d_c)::value;
-            if constexpr (f < WMP) {
-                if constexpr (AF) {
-                    // nothing to expand
-                } else if constexpr (AS) {
-                    af[ks & 1][f][d] = (int)fp4_single_dword<ks, d>(ra[buf][f][0]);
-                } else {
-                    af[ks & 1][f][d] = (int)fp4_pair_dword<ks, d>(ra[buf][f][0], ra[buf][f][1]);
-                }
+        auto load_stage = [&](auto buf_c, int64_t st) __attribute__((always_inline)) { load_stage_of(ph_c, buf_c, st); };
+        // operand dword `task` of k step ks, from buffer buf
+        auto form = [&](auto buf_c, auto ks_c, auto task_c) __attribute__((always_inline)) {
+            constexpr int buf = decltype(buf_c)::value, ks = decltype(ks_c)::value, task = decltype(task_c)::value;
+            if constexpr (task < TASKS_A) {
+                constexpr int f = task / 4, d = task % 4;
+                if constexpr (!AF) af[ks & 1][f][d] = (int)operand_dword<P, ks, d>(ra[buf][f]);
             } else {
-                if constexpr (BS) bf[ks & 1][f - WMP][d] = (int)fp4_single_dword<ks, d>(rb[buf][f - WMP][0]);
-                else bf[ks & 1][f - WMP][d] = (int)fp4_pair_dword<ks, d>(rb[buf][f - WMP][0], rb[buf][f - WMP][1]);
+                constexpr int f = (task - TASKS_A) / DB, d = (task - TASKS_A) % DB;
+                bf[ks & 1][f][d] = (int)operand_dword<Q, ks, d>(rb[buf][f]);
             }
         };
         // one stage with its raw words in buffer `buf`; loads stage st+1 (clamped) into the other buffer;
@@ -332,37 +307,20 @@ __global__ __launch_bounds__(256) void gemm_mfma_direct_kernel(const uint32_t *a
             static_for<KS * PER_KS>([&](auto i_c) __attribute__((always_inline)) {
                 constexpr int i = decltype(i_c)::value;
                 constexpr int ks = i / PER_KS, j = i % PER_KS, bi = j / WN, bj = j % WN;
-                const v4i b = bf[ks & 1][bj];
-                const v8i b8 = {b[0], b[1], b[2], b[3], 0, 0, 0, 0};
-                // operand formats: 4 = E2M1, 2 = E2M3; the scales are E8M0 exponents (127 = 2^0)
-                if constexpr (AF) {
-                    // words 6 ks .. 6 ks + 5 of the lane's 24 raw words
-                    auto raw = [&](auto w_c) __attribute__((always_inline)) {
-                        constexpr int w = 6 * ks + decltype(w_c)::value;
-                        return (int)vec_word<w & 3>(ra[buf][bi][w >> 2]);
-                    };
-                    const v8i a8 = {raw(std::integral_constant<int, 0>{}), raw(std::integral_constant<int, 1>{}),
-                                    raw(std::integral_constant<int, 2>{}), raw(std::integral_constant<int, 3>{}),
-                                    raw(std::integral_constant<int, 4>{}), raw(std::integral_constant<int, 5>{}), 0, 0};
-                    acc[ROW0 + bi][bj] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                        a8, b8, acc[ROW0 + bi][bj], 2, 4, 0, exp_a, 0, exp_b + (BS ? fp4_single_exponent(ks) : 0));
-                } else {
-                    const v4i a = af[ks & 1][bi];
-                    const v8i a8 = {a[0], a[1], a[2], a[3], 0, 0, 0, 0};
-                    acc[ROW0 + bi][bj] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                        a8, b8, acc[ROW0 + bi][bj], 4, 4, 0, exp_a + (AS ? fp4_single_exponent(ks) : 0), 0,
-                        exp_b + (BS ? fp4_single_exponent(ks) : 0));
-                }
+                constexpr int format_a = operand_format(P), format_b = operand_format(Q);
+                v8i a8;
+                if constexpr (AF) a8 = field_operand<ks>(ra[buf][bi]);
+                else a8 = widen(af[ks & 1][bi]);
+                acc[ROW0 + bi][bj] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                    a8, widen(bf[ks & 1][bj]), acc[ROW0 + bi][bj], format_a, format_b, 0, operand_exponent(P, ks), 0,
+                    operand_exponent(Q, ks));
                 // this MFMA's share of the next k step's operands (after the last step: step 0 of stage st+1)
                 static_for<TPM>([&](auto t_c) __attribute__((always_inline)) {
                     constexpr int task = j * TPM + decltype(t_c)::value;
                     if constexpr (task < TASKS) {
-                        using F = std::integral_constant<int, FRAG0 + task / 4>;
-                        using D = std::integral_constant<int, task % 4>;
-                        if constexpr (ks + 1 < KS)
-                            expand(buf_c, std::integral_constant<int, ks + 1>{}, F{}, D{});
-                        else
-                            expand(Other{}, I0{}, F{}, D{});
+                        using X = std::integral_constant<int, task>;
+                        if constexpr (ks + 1 < KS) form(buf_c, std::integral_constant<int, ks + 1>{}, X{});
+                        else form(Other{}, I0{}, X{});
                     }
                 });
                 if constexpr (chunk >= 0 && i % STORE_EVERY == 0)
@@ -373,10 +331,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_direct_kernel(const uint32_t *a
         };
         if constexpr (!PRELOADED) load_stage(I0{}, 0);
         // fragments of (stage 0, k step 0)
-        static_for<FRAGS - FRAG0>([&](auto f_c) __attribute__((always_inline)) {
-            using F = std::integral_constant<int, FRAG0 + decltype(f_c)::value>;
-            static_for<4>([&](auto d_c) __attribute__((always_inline)) { expand(I0{}, I0{}, F{}, d_c); });
-        });
+        static_for<TASKS>([&](auto t_c) __attribute__((always_inline)) { form(I0{}, I0{}, t_c); });
         int64_t st = 0;
         if constexpr (STORES) {
             static_for<STORE_STAGES / 2>([&](auto h_c) __attribute__((always_inline)) {
@@ -392,55 +347,16 @@ __global__ __launch_bounds__(256) void gemm_mfma_direct_kernel(const uint32_t *a
         }
     };
 
-    using T = std::true_type;
-    using F = std::false_type;
     static_for<PHASES>([&](auto ph_c) __attribute__((always_inline)) {
         constexpr int ph = decltype(ph_c)::value;
         init_phase(ph_c);
         if constexpr (ph > 0)  // row pointer of element 0 of the previous phase
             st_ptr = reinterpret_cast<char *>(g.c_i32 + (m_lane + split_row0(WM, SPLIT, ph - 1) * 32) * g.N + n_lane);
-        // the first sweep of a later phase carries the stores of the phase before it
-        using First = std::integral_constant<bool, (ph > 0)>;
-        using Pre = std::integral_constant<bool, (ph == 0 && PRELOAD)>;  // stage 0 of the very first sweep came with the prologue
-        if constexpr (AF) {
-            // one sweep per weight group; (ua / 8)(uw / 2) 2^6 = 4 ua uw
-            if constexpr (pair_groups(Q) > 0) {
-                sweep(ph_c, First{}, F{}, F{}, 0, 0, 130, 130, Pre{});
-                for (int hb = 1; hb < pair_groups(Q); ++hb) sweep(ph_c, F{}, F{}, F{}, 0, 2 * hb, 130, 130 + 2 * hb, F{});
-                if constexpr (has_single_group(Q)) sweep(ph_c, F{}, F{}, T{}, 0, Q - 1, 130, 130 + Q - 1, F{});
-            } else {
-                sweep(ph_c, First{}, F{}, T{}, 0, 0, 130, 130, Pre{});
-            }
-        } else
-        // pair x pair, pair x single, single x pair, single x single
-        if constexpr (pair_groups(P) > 0) {
-            if constexpr (pair_groups(Q) > 0) {
-                sweep(ph_c, First{}, F{}, F{}, 0, 0, 129, 129, Pre{});
-                for (int hb = 1; hb < pair_groups(Q); ++hb) sweep(ph_c, F{}, F{}, F{}, 0, 2 * hb, 129, 129 + 2 * hb, F{});
-                if constexpr (has_single_group(Q)) sweep(ph_c, F{}, F{}, T{}, 0, Q - 1, 129, 129 + Q - 1, F{});
-            } else {
-                sweep(ph_c, First{}, F{}, T{}, 0, Q - 1, 129, 129 + Q - 1, Pre{});
-            }
-            for (int ha = 1; ha < pair_groups(P); ++ha) {
-                for (int hb = 0; hb < pair_groups(Q); ++hb)
-                    sweep(ph_c, F{}, F{}, F{}, 2 * ha, 2 * hb, 129 + 2 * ha, 129 + 2 * hb, F{});
-                if constexpr (has_single_group(Q)) sweep(ph_c, F{}, F{}, T{}, 2 * ha, Q - 1, 129 + 2 * ha, 129 + Q - 1, F{});
-            }
-            if constexpr (has_single_group(P)) {
-                for (int hb = 0; hb < pair_groups(Q); ++hb)
-                    sweep(ph_c, F{}, T{}, F{}, P - 1, 2 * hb, 129 + P - 1, 129 + 2 * hb, F{});
-                if constexpr (has_single_group(Q)) sweep(ph_c, F{}, T{}, T{}, P - 1, Q - 1, 129 + P - 1, 129 + Q - 1, F{});
-            }
-        } else {  // P == 1
-            if constexpr (pair_groups(Q) > 0) {
-                sweep(ph_c, First{}, T{}, F{}, 0, 0, 129, 129, Pre{});
-                for (int hb = 1; hb < pair_groups(Q); ++hb) sweep(ph_c, F{}, T{}, F{}, 0, 2 * hb, 129, 129 + 2 * hb, F{});
-                if constexpr (has_single_group(Q)) sweep(ph_c, F{}, T{}, T{}, 0, Q - 1, 129, 129 + Q - 1, F{});
-            } else {
-                sweep(ph_c, First{}, T{}, T{}, 0, 0, 129, 129, Pre{});
-            }
-        }
+        // a later phase carries the stores of the phase before it; stage 0 of the first came with the prologue
+        sweep(ph_c, std::integral_constant<bool, (ph > 0)>{}, std::integral_constant<bool, (ph == 0 && PRELOAD)>{});
     });
+    using T = std::true_type;
+    using F = std::false_type;
 
     // Store of the last phase.  The output mode and the border test are uniform over the workgroup, so
     // straight-line store sequences are chosen per output instead of testing per element.

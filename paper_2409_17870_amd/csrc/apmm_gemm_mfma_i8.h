@@ -40,7 +40,7 @@ __device__ __forceinline__ int load_slot(const Operand &o, int i)
     if (FORM == 1) return 0;
     if (FORM == 2) return KK;
     if (FORM == 3) return i == 0 ? KK : 2;
-    if (FORM == 4) return i == 0 ? KK : 2 + KK;
+    if (FORM == 4) return 2 * KK + i;
     if (FORM == kFields) return 3 * KK + i;
     if (FORM == kNibbles) return i < 2 ? 2 * KK + i : i == 2 ? o.pair_slot + KK : o.single_slot;
     return 4 * KK + i;
@@ -57,11 +57,9 @@ __device__ __forceinline__ int operand_dword(const Operand &o, const uint4 (&raw
     } else if constexpr (FORM == 2) {
         return (int)((vec_word<2 * e + tp>(raw[0]) >> pair_at) & 0x03030303u);
     } else if constexpr (FORM == 3) {
-        return (int)(((vec_word<2 * e + tp>(raw[0]) >> pair_at) & 0x03030303u) |
-                     (shifted<single_at - 2>(vec_word<t>(raw[1])) & 0x04040404u));
+        return (int)folded_dword<3, tp, tt, jh>(vec_word<2 * e>(raw[0]), vec_word<2 * e + 1>(raw[0]), vec_word<ks>(raw[1]), 0u);
     } else if constexpr (FORM == 4) {
-        return (int)(((vec_word<2 * e + tp>(raw[0]) >> pair_at) & 0x03030303u) |
-                     (shifted<pair_at - 2>(vec_word<2 * e + tp>(raw[1])) & 0x0c0c0c0cu));
+        return (int)folded_dword<4, tp, tt, jh>(raw[e].x, raw[e].y, raw[e].z, raw[e].w);
     } else if constexpr (FORM == kFields) {
         constexpr int w = 6 * e + 3 * tp;  // first of the three words of (e, tp)
         auto word = [&](auto i_c) __attribute__((always_inline)) {

@@ -30,7 +30,8 @@ constexpr int ksplit_owner(int wm, int wn, int bi, int bj)
 constexpr int ksplit_lds_bytes(int wm, int wn) { return wm * wn * 3 * 4 * 64 * 16; }
 
 template <int P, int Q, int WM, int WN>
-__global__ __launch_bounds__(256) void gemm_mfma_ksplit_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32_t *ci_arg,
+__global__ __launch_bounds__(256, WN == 2 ? 2 : 1)  // two workgroups of the 64 x 64 tile share a compute unit
+void gemm_mfma_ksplit_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32_t *ci_arg,
                                                                uint16_t *cf_arg, int m_arg, int n_arg, int k_arg, int nkb_arg,
                                                                int tiles_n, int tiles_m_xn, const uint16_t *ws_arg,
                                                                const uint16_t *as_arg)
@@ -91,37 +92,29 @@ __global__ __launch_bounds__(256) void gemm_mfma_ksplit_kernel(const uint32_t *a
     }
 
     v16f acc[WM][WN];
-    uint4 ra[2][WM][AF ? 6 : 2], rb[2][WN][2];  // raw words of a stage, by stage parity
-    v4i af[2][AF ? 1 : WM], bf[2][WN];          // expanded fragments, by k step parity
+    uint4 ra[2][WM][SLOTS_A], rb[2][WN][Q];  // raw words of a stage, by stage parity
+    v4i af[2][AF ? 1 : WM];                  // formed fragments, by k step parity
+    OperandFrag<Q> bf[2][WN];
 
-    auto load_stage_of = [&](auto as_c, auto bs_c, auto buf_c, int st, int slot_a, int slot_b) __attribute__((always_inline)) {
+    auto load_stage = [&](auto buf_c, int st) __attribute__((always_inline)) {
         constexpr int buf = decltype(buf_c)::value;
-        constexpr bool AS = decltype(as_c)::value, BS = decltype(bs_c)::value;
 #pragma unroll
         for (int bi = 0; bi < WM; ++bi) {
             const char *src = pa_blk[bi] + (int64_t)st * kStageBytesA + voff_a;
-            if constexpr (AF) {
 #pragma unroll
-                for (int sl = 0; sl < 6; ++sl) ra[buf][bi][sl] = *reinterpret_cast<const uint4 *>(src + sl * kSlotBytes);
-            } else {
-                ra[buf][bi][0] = *reinterpret_cast<const uint4 *>(src + slot_a * kSlotBytes);
-                if constexpr (!AS) ra[buf][bi][1] = *reinterpret_cast<const uint4 *>(src + (slot_a + 1) * kSlotBytes);
-            }
+            for (int sl = 0; sl < SLOTS_A; ++sl) ra[buf][bi][sl] = *reinterpret_cast<const uint4 *>(src + sl * kSlotBytes);
         }
 #pragma unroll
         for (int bj = 0; bj < WN; ++bj) {
             const char *src = pb_blk[bj] + (int64_t)st * kStageBytesB + voff_b;
-            rb[buf][bj][0] = *reinterpret_cast<const uint4 *>(src + slot_b * kSlotBytes);
-            if constexpr (!BS) rb[buf][bj][1] = *reinterpret_cast<const uint4 *>(src + (slot_b + 1) * kSlotBytes);
+#pragma unroll
+            for (int sl = 0; sl < Q; ++sl) rb[buf][bj][sl] = *reinterpret_cast<const uint4 *>(src + sl * kSlotBytes);
         }
     };
 
-    // First requests: the wave's first stage of the first sweep, then the code sums (wave 0 seeds the
+    // First requests: the wave's first stage, then the code sums (wave 0 seeds the
     // accumulators with the recovery terms, the others start at zero).
-    constexpr bool AS0 = !AF && pair_groups(P) == 0, BS0 = pair_groups(Q) == 0;
-    constexpr int SLOT_A0 = 0, SLOT_B0 = pair_groups(Q) > 0 ? 0 : Q - 1;
-    if (s_count > 0)
-        load_stage_of(std::integral_constant<bool, AS0>{}, std::integral_constant<bool, BS0>{}, I0{}, s_begin, SLOT_A0, SLOT_B0);
+    if (s_count > 0) load_stage(I0{}, s_begin);
     {
         float a_init[WM], b_init[WN];
 #pragma unroll
@@ -148,120 +141,58 @@ __global__ __launch_bounds__(256) void gemm_mfma_ksplit_kernel(const uint32_t *a
                 acc[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x2f32(a_init[bi], b_init[bj], zero, 0, 0, 0);
     }
 
-    // One sweep of this wave's stages for the activation group at slot slot_a and the weight group at slot slot_b
-    // (AS / BS: the group is a single one); exp_a + exp_b - 254 = 4 + the bit positions of the two groups.
-    auto sweep = [&](auto as_c, auto bs_c, int slot_a, int slot_b, int exp_a, int exp_b, auto preloaded_c) __attribute__((always_inline)) {
-        constexpr bool AS = decltype(as_c)::value, BS = decltype(bs_c)::value, PRELOADED = decltype(preloaded_c)::value;
+    // This wave's stages of the sweep of K.
+    if (s_count > 0) {
         constexpr int PER_KS = NB;
-        constexpr int FRAG0 = AF ? WM : 0, FRAGS = WM + WN;
-        constexpr int TASKS = 4 * (FRAGS - FRAG0);
+        constexpr int TASKS_A = AF ? 0 : 4 * WM, DB = operand_dwords(Q);
+        constexpr int TASKS = TASKS_A + DB * WN;  // operand dwords to form per k step, A blocks first
         constexpr int TPM = (TASKS + PER_KS - 1) / PER_KS;
-        auto expand = [&](auto buf_c, auto ks_c, auto f_c, auto d_c) __attribute__((always_inline)) {
-            constexpr int buf = decltype(buf_c)::value, ks = decltype(ks_c)::value, f = decltype(f_c)::value,
-                          d = decltype(d_c)::value;
-            if constexpr (f < WM) {
-                if constexpr (AF) {
-                } else if constexpr (AS) {
-                    af[ks & 1][f][d] = (int)fp4_single_dword<ks, d>(ra[buf][f][0]);
-                } else {
-                    af[ks & 1][f][d] = (int)fp4_pair_dword<ks, d>(ra[buf][f][0], ra[buf][f][1]);
-                }
+        auto form = [&](auto buf_c, auto ks_c, auto task_c) __attribute__((always_inline)) {
+            constexpr int buf = decltype(buf_c)::value, ks = decltype(ks_c)::value, task = decltype(task_c)::value;
+            if constexpr (task < TASKS_A) {
+                constexpr int f = task / 4, d = task % 4;
+                if constexpr (!AF) af[ks & 1][f][d] = (int)operand_dword<P, ks, d>(ra[buf][f]);
             } else {
-                if constexpr (BS) bf[ks & 1][f - WM][d] = (int)fp4_single_dword<ks, d>(rb[buf][f - WM][0]);
-                else bf[ks & 1][f - WM][d] = (int)fp4_pair_dword<ks, d>(rb[buf][f - WM][0], rb[buf][f - WM][1]);
+                constexpr int f = (task - TASKS_A) / DB, d = (task - TASKS_A) % DB;
+                bf[ks & 1][f][d] = (int)operand_dword<Q, ks, d>(rb[buf][f]);
             }
         };
         auto stage = [&](auto buf_c, int st) __attribute__((always_inline)) {
             constexpr int buf = decltype(buf_c)::value;
             using Other = std::integral_constant<int, buf ^ 1>;
-            load_stage_of(as_c, bs_c, Other{}, st + 1 < s_end ? st + 1 : st, slot_a, slot_b);  // the surplus load is discarded
+            load_stage(Other{}, st + 1 < s_end ? st + 1 : st);  // the surplus load is discarded
             __builtin_amdgcn_sched_barrier(0);
             static_for<KS * PER_KS>([&](auto i_c) __attribute__((always_inline)) {
                 constexpr int i = decltype(i_c)::value;
                 constexpr int ks = i / PER_KS, j = i % PER_KS, bi = j / WN, bj = j % WN;
-                const v4i b = bf[ks & 1][bj];
-                const v8i b8 = {b[0], b[1], b[2], b[3], 0, 0, 0, 0};
-                if constexpr (AF) {
-                    auto raw = [&](auto w_c) __attribute__((always_inline)) {
-                        constexpr int w = 6 * ks + decltype(w_c)::value;
-                        return (int)vec_word<w & 3>(ra[buf][bi][w >> 2]);
-                    };
-                    const v8i a8 = {raw(std::integral_constant<int, 0>{}), raw(std::integral_constant<int, 1>{}),
-                                    raw(std::integral_constant<int, 2>{}), raw(std::integral_constant<int, 3>{}),
-                                    raw(std::integral_constant<int, 4>{}), raw(std::integral_constant<int, 5>{}), 0, 0};
-                    acc[bi][bj] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                        a8, b8, acc[bi][bj], 2, 4, 0, exp_a, 0, exp_b + (BS ? fp4_single_exponent(ks) : 0));
-                } else {
-                    const v4i a = af[ks & 1][bi];
-                    const v8i a8 = {a[0], a[1], a[2], a[3], 0, 0, 0, 0};
-                    acc[bi][bj] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                        a8, b8, acc[bi][bj], 4, 4, 0, exp_a + (AS ? fp4_single_exponent(ks) : 0), 0,
-                        exp_b + (BS ? fp4_single_exponent(ks) : 0));
-                }
+                constexpr int format_a = operand_format(P), format_b = operand_format(Q);
+                v8i a8;
+                if constexpr (AF) a8 = field_operand<ks>(ra[buf][bi]);
+                else a8 = widen(af[ks & 1][bi]);
+                acc[bi][bj] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                    a8, widen(bf[ks & 1][bj]), acc[bi][bj], format_a, format_b, 0, operand_exponent(P, ks), 0, operand_exponent(Q, ks));
                 static_for<TPM>([&](auto t_c) __attribute__((always_inline)) {
                     constexpr int task = j * TPM + decltype(t_c)::value;
                     if constexpr (task < TASKS) {
-                        using F = std::integral_constant<int, FRAG0 + task / 4>;
-                        using D = std::integral_constant<int, task % 4>;
-                        if constexpr (ks + 1 < KS)
-                            expand(buf_c, std::integral_constant<int, ks + 1>{}, F{}, D{});
-                        else
-                            expand(Other{}, I0{}, F{}, D{});
+                        using X = std::integral_constant<int, task>;
+                        if constexpr (ks + 1 < KS) form(buf_c, std::integral_constant<int, ks + 1>{}, X{});
+                        else form(Other{}, I0{}, X{});
                     }
                 });
                 __builtin_amdgcn_sched_barrier(0);
             });
         };
-        if (s_count == 0) return;
-        if constexpr (!PRELOADED) load_stage_of(as_c, bs_c, I0{}, s_begin, slot_a, slot_b);
-        static_for<FRAGS - FRAG0>([&](auto f_c) __attribute__((always_inline)) {
-            using F = std::integral_constant<int, FRAG0 + decltype(f_c)::value>;
-            static_for<4>([&](auto d_c) __attribute__((always_inline)) { expand(I0{}, I0{}, F{}, d_c); });
-        });
+        static_for<TASKS>([&](auto t_c) __attribute__((always_inline)) { form(I0{}, I0{}, t_c); });
         int st = s_begin;
         for (; st + 1 < s_end; st += 2) {
             stage(I0{}, st);
             stage(I1{}, st + 1);
         }
         if (st < s_end) stage(I0{}, st);
-    };
+    }
 
     using T = std::true_type;
     using F = std::false_type;
-    if constexpr (AF) {
-        // one sweep per weight group; (ua / 8)(uw / 2) 2^6 = 4 ua uw
-        if constexpr (pair_groups(Q) > 0) {
-            sweep(F{}, F{}, 0, 0, 130, 130, T{});
-            for (int hb = 1; hb < pair_groups(Q); ++hb) sweep(F{}, F{}, 0, 2 * hb, 130, 130 + 2 * hb, F{});
-            if constexpr (has_single_group(Q)) sweep(F{}, T{}, 0, Q - 1, 130, 130 + Q - 1, F{});
-        } else {
-            sweep(F{}, T{}, 0, 0, 130, 130, T{});
-        }
-    } else if constexpr (pair_groups(P) > 0) {
-        if constexpr (pair_groups(Q) > 0) {
-            sweep(F{}, F{}, 0, 0, 129, 129, T{});
-            for (int hb = 1; hb < pair_groups(Q); ++hb) sweep(F{}, F{}, 0, 2 * hb, 129, 129 + 2 * hb, F{});
-            if constexpr (has_single_group(Q)) sweep(F{}, T{}, 0, Q - 1, 129, 129 + Q - 1, F{});
-        } else {
-            sweep(F{}, T{}, 0, Q - 1, 129, 129 + Q - 1, T{});
-        }
-        for (int ha = 1; ha < pair_groups(P); ++ha) {
-            for (int hb = 0; hb < pair_groups(Q); ++hb) sweep(F{}, F{}, 2 * ha, 2 * hb, 129 + 2 * ha, 129 + 2 * hb, F{});
-            if constexpr (has_single_group(Q)) sweep(F{}, T{}, 2 * ha, Q - 1, 129 + 2 * ha, 129 + Q - 1, F{});
-        }
-        if constexpr (has_single_group(P)) {
-            for (int hb = 0; hb < pair_groups(Q); ++hb) sweep(T{}, F{}, P - 1, 2 * hb, 129 + P - 1, 129 + 2 * hb, F{});
-            if constexpr (has_single_group(Q)) sweep(T{}, T{}, P - 1, Q - 1, 129 + P - 1, 129 + Q - 1, F{});
-        }
-    } else {  // P == 1
-        if constexpr (pair_groups(Q) > 0) {
-            sweep(T{}, F{}, 0, 0, 129, 129, T{});
-            for (int hb = 1; hb < pair_groups(Q); ++hb) sweep(T{}, F{}, 0, 2 * hb, 129, 129 + 2 * hb, F{});
-            if constexpr (has_single_group(Q)) sweep(T{}, T{}, 0, Q - 1, 129, 129 + Q - 1, F{});
-        } else {
-            sweep(T{}, T{}, 0, 0, 129, 129, T{});
-        }
-    }
     // ---- the four partial tiles meet ----
     // Scales of the blocks this wave will store, requested before the exchange so that they are there after it:
     // the 16 token scales of this lane's rows (all of a wave's blocks lie in row block bi_own), one channel scale

@@ -13,12 +13,13 @@ namespace {
 
 // Tile width (column blocks of 32: 2, 4, 5 or 6; the tile has two row blocks): the one that fills most of the 256
 // compute units in a single round of tiles, i.e. the narrowest with at most 256 tiles, or 0 when every width needs
-// more than one round.  Activations in the group form (1 and 2 bits) have the 64 x 64 and 64 x 128 tiles only.
+// more than one round.  Activations in the group form (1 and 2 bits) have the 64 x 64 and 64 x 128 tiles only, weights of
+// 3 and 4 bits no 64 x 192 tile (their words would not fit the registers).
 int one_round_width(const GemmArgs &g)
 {
     int best = 0;
     int64_t best_tiles = 0;
-    for (int wn = 2; wn <= (activation_field_form(g.p) ? 6 : 4); ++wn) {
+    for (int wn = 2; wn <= (!activation_field_form(g.p) ? 4 : g.q <= 2 ? 6 : 5); ++wn) {
         if (wn == 3) continue;
         const int64_t tiles = ((g.M + 63) / 64) * ((g.N + 32 * wn - 1) / (32 * wn));
         if (tiles <= 256 && tiles > best_tiles) {

@@ -16,6 +16,7 @@
 // 3 p q operations per output and 16 elements, i.e. about 0.2 effective POP/s for W1A2 if every issue slot
 // of the chip did nothing else.
 #include "apmm_epilogue.h"
+#include "apmm_fields.h"
 #include "apmm_kernels.h"
 
 namespace apmm {
@@ -36,6 +37,16 @@ __device__ __forceinline__ uint32_t plane_half_word(const uint32_t *tile_row, in
     if (nibble_form(n) && i < 4) {  // N[4 ks + 2 tp], N[4 ks + 2 tp + 1]
         const uint32_t *b = tile_row + (w >> 1) * kPlaneWords + 2 * (w & 1);
         return ((b[0] >> i) & 0x11111111u) | (((b[1] >> i) & 0x11111111u) << 2);
+    }
+    if (weight_folded_form(n)) {  // (activations of these widths are in the field form)
+        const int ks = w >> 1;
+        uint32_t in[4] = {0, 0, 0, 0};
+        for (int j = 0; j < n; ++j) {
+            const int at = fold_word_at(n, ks, j);
+            in[j] = tile_row[(at >> 2) * kPlaneWords + (at & 3)];
+        }
+        if (n == 3) return (w & 1) ? folded_plane<3, 1>(in[0], in[1], in[2], 0u, i) : folded_plane<3, 0>(in[0], in[1], in[2], 0u, i);
+        return (w & 1) ? folded_plane<4, 1>(in[0], in[1], in[2], in[3], i) : folded_plane<4, 0>(in[0], in[1], in[2], in[3], i);
     }
     if (i < 2 * pair_groups(n)) {
         const uint32_t s = tile_row[(i / 2 * 2 + (w >> 2)) * kPlaneWords + (w & 3)];  // S[w] of pair group i / 2

@@ -13,7 +13,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
-#include "apmm_layout.h"
+#include "apmm_fields.h"
 
 namespace apmm {
 namespace i8 {
@@ -21,7 +21,7 @@ namespace i8 {
 __host__ __device__ inline uint32_t code_bias(int n) { return n == 8 ? 128u : 0u; }                       // z
 __host__ __device__ inline uint32_t value_offset(int n) { return n == 8 ? ~0u : (1u << n) - 1u; }         // c' modulo 2^32
 
-// Compile-time forms.  1 .. 4: that many bits in the group form.
+// Compile-time forms.  1, 2: that many bits in the group form; 3, 4: weights in the folded form.
 constexpr int kNibbles = 5, kFields = 6, kBytes = 8;  // 5 .. 7 bits; 6-bit fields (activations of 3, 4 bits); 8 bits
 constexpr int form_loads(int form) { return form <= 2 ? 1 : form <= 4 ? 2 : form == kFields ? 3 : 4; }
 
@@ -48,17 +48,6 @@ template <int S>
 __device__ __forceinline__ uint32_t shifted(uint32_t x)
 {
     return S >= 0 ? x >> (S >= 0 ? S : 0) : x << (S < 0 ? -S : 0);
-}
-
-// Dword (tt, jh) of the chunk whose three words of 6-bit fields are w0 .. w2: the 48 bits of tt start at bit 48 tt; byte c
-// is the field at their bit 12 c + 6 jh: bytes 0 .. 2 lie in the 32 bits from there on, byte 3 is cut out of w1 (tt = 0) or w2.
-template <int tt, int jh>
-__device__ __forceinline__ uint32_t field_dword(uint32_t w0, uint32_t w1, uint32_t w2)
-{
-    constexpr int at = 48 * tt + 6 * jh;
-    const uint32_t lo = at < 32 ? __builtin_amdgcn_alignbit(w1, w0, at & 31) : __builtin_amdgcn_alignbit(w2, w1, at & 31);
-    return (lo & 0x0fu) | ((lo >> 4) & 0x0f00u) | ((lo >> 8) & 0x0f0000u) |
-           (shifted<at + 36 - (tt ? 64 : 32) - 24>(tt ? w2 : w1) & 0x0f000000u);
 }
 
 }  // namespace i8

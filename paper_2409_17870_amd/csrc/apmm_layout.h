@@ -38,7 +38,18 @@
 // the low bits: exactly the E2M3 (fp6) MFMA operand of that k step, in which a 4-bit code u is the number
 // u / 8.  The matrix unit multiplies fp6 and fp4 operands at the same rate, so 4-bit activations need no
 // second sweep of K and no expansion at all, at the price of 6 instead of 4 bits per element in a buffer
-// that lives for one GEMM (weights always keep the compact group form).
+// that lives for one GEMM.
+//
+// Weights of 3 or 4 bits use the FOLDED form: the same six field words F0 .. F5 per k step, folded into n words without
+// losing a bit.  The fields of words 0, 1, 2 (and again 3, 4, 5) start at bit offsets 0, 4 and 2 modulo 6, so the holes of
+// one word are where another has its codes, and unfolding is masks:
+//   4 bits: words F0 | F4 & a, F1 | F5 & b, F2 | F4 & c, F3 | F5 & a   (a, b, c: bits 4,5 / 2,3 / 0,1 modulo 6);
+//           word j of k step ks is word j of slot ks
+//   3 bits: the bit pairs 0, 1 of F0, F1, F2 in one word (planes 0 and 1 at its even and odd bits), those of F3, F4, F5 in
+//           another, the top bits of all six in a third (of F0 .. F2 at its even, of F3 .. F5 at its odd bits): words 2 ks,
+//           2 ks + 1 of slots 0, 1 and word ks of slot 2
+// Eight (4 bits) or thirteen (3 bits) operations give the E2M3 operand of 32 codes.  The two plane groups of the group
+// form took twelve, and K was swept once for each: half the matrix instructions now, for the same bytes.
 //
 // Codes of 5 to 8 bits go to the int8 matrix operations and are stored so that little is left to do there:
 //   5, 6, 7 bits: the four low bits fill slots 0 .. 3 as nibbles: word N[4 ks + t] (slot ks, word t) holds bits 0 .. 3 of element
@@ -77,7 +88,44 @@ inline __host__ __device__ constexpr bool nibble_form(int n) { return n >= 5 && 
 inline __host__ __device__ constexpr bool byte_form(int n) { return n == 8; }
 // first pair group that is stored as one (nibbles and bytes hold the lower bits otherwise)
 inline __host__ __device__ constexpr int first_pair_group(int n) { return n <= 4 ? 0 : nibble_form(n) ? 2 : 4; }
+// weights of 3 or 4 bits
+inline __host__ __device__ constexpr bool weight_folded_form(int n) { return n == 3 || n == 4; }
 inline __host__ __device__ constexpr int activation_slots(int p) { return activation_field_form(p) ? 6 : p; }
+
+// Folded form: n words from the six field words of a k step (fold_words), field word D from the n words (unfold_word), and
+// the place of word j of k step ks among the 4 n words of the row and k block (slot: / 4).
+constexpr uint32_t kFoldBits45 = 0x30c30c30u, kFoldBits23 = 0x0c30c30cu, kFoldBits01 = 0xc30c30c3u;  // bits modulo 6
+constexpr uint32_t kFoldBit0 = 0x41041041u, kFoldBit2 = 0x04104104u, kFoldBit4 = 0x10410410u;
+inline __host__ __device__ constexpr int fold_word_at(int n, int ks, int j) { return n == 4 ? 4 * ks + j : j < 2 ? 2 * ks + j : 8 + ks; }
+template <int N>
+inline __host__ __device__ void fold_words(const uint32_t (&f)[6], uint32_t (&w)[N])
+{
+    static_assert(N == 3 || N == 4, "folded widths");
+    if constexpr (N == 4) {
+        w[0] = f[0] | (f[4] & kFoldBits45);
+        w[1] = f[1] | (f[5] & kFoldBits23);
+        w[2] = f[2] | (f[4] & kFoldBits01);
+        w[3] = f[3] | (f[5] & kFoldBits45);
+    } else {
+        w[0] = (f[0] & kFoldBits01) | (f[1] & kFoldBits45) | (f[2] & kFoldBits23);
+        w[1] = (f[3] & kFoldBits01) | (f[4] & kFoldBits45) | (f[5] & kFoldBits23);
+        w[2] = (f[0] & kFoldBit2) | (f[1] & kFoldBit0) | (f[2] & kFoldBit4) |
+               (((f[3] & kFoldBit2) | (f[4] & kFoldBit0) | (f[5] & kFoldBit4)) << 1);
+    }
+}
+template <int N, int D>
+inline __host__ __device__ uint32_t unfold_word(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3)
+{
+    static_assert((N == 3 || N == 4) && D >= 0 && D < 6, "folded widths");
+    if constexpr (N == 4) {
+        return D == 0 ? w0 & ~kFoldBits45 : D == 1 ? w1 & ~kFoldBits23 : D == 2 ? w2 & ~kFoldBits01 : D == 3 ? w3 & ~kFoldBits45
+             : D == 4 ? (w0 & kFoldBits45) | (w2 & kFoldBits01) : (w1 & kFoldBits23) | (w3 & kFoldBits45);
+    } else {
+        const uint32_t pairs = D < 3 ? w0 : w1, top = D < 3 ? w2 : w2 >> 1;
+        return D % 3 == 0 ? (pairs & kFoldBits01) | (top & kFoldBit2) : D % 3 == 1 ? (pairs & kFoldBits45) | (top & kFoldBit0)
+                                                                                  : (pairs & kFoldBits23) | (top & kFoldBit4);
+    }
+}
 
 // index of word g=0 of (row, slot s) in k block kb
 inline __host__ __device__ int64_t tile_row_word(int64_t row, int64_t kb, int64_t nkb, int n, int s)

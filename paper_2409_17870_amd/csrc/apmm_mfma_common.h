@@ -12,6 +12,7 @@ namespace apmm {
 namespace mfma {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v6i __attribute__((ext_vector_type(6)));
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -61,6 +62,34 @@ __device__ __forceinline__ uint32_t fp4_single_dword(const uint4 &u)
     return KS < 3 ? l & (0x11111111u << KS) : (l >> 1) & 0x44444444u;
 }
 constexpr int fp4_single_exponent(int ks) { return ks < 3 ? -ks : -2; }
+
+// ---- Operands of an N-bit code from the raw vectors (slots) of a row and k block ----
+// One or two bits: E2M1, four dwords (u / 2).  Weights of 3 or 4 bits: E2M3, six dwords (u / 8) from the folded form.
+// With these E8M0 exponents (127 = 2^0) either operand counts 2 u, so that a product is 4 ua uw.
+constexpr int operand_dwords(int n) { return n <= 2 ? 4 : 6; }
+constexpr int operand_format(int n) { return n <= 2 ? 4 : 2; }  // E2M1, E2M3
+constexpr int operand_exponent(int n, int ks) { return n == 1 ? 129 + fp4_single_exponent(ks) : n == 2 ? 129 : 131; }
+template <int N> using OperandFrag = std::conditional_t<(N > 2), v6i, v4i>;
+template <int N, int KS, int D>
+__device__ __forceinline__ uint32_t operand_dword(const uint4 (&raw)[N])
+{
+    if constexpr (N == 1) return fp4_single_dword<KS, D>(raw[0]);
+    else if constexpr (N == 2) return fp4_pair_dword<KS, D>(raw[0], raw[1]);
+    else if constexpr (N == 3)
+        return unfold_word<3, D>(pair_word<2 * KS>(raw[0], raw[1]), pair_word<2 * KS + 1>(raw[0], raw[1]), vec_word<KS>(raw[2]), 0u);
+    else return unfold_word<4, D>(raw[KS].x, raw[KS].y, raw[KS].z, raw[KS].w);
+}
+__device__ __forceinline__ v8i widen(const v4i &v) { return v8i{v[0], v[1], v[2], v[3], 0, 0, 0, 0}; }
+__device__ __forceinline__ v8i widen(const v6i &v) { return v8i{v[0], v[1], v[2], v[3], v[4], v[5], 0, 0}; }
+// E2M3 operand of k step KS from the six slots of a field-form row: words 6 KS .. 6 KS + 5 of its 24, as they stand
+template <int KS>
+__device__ __forceinline__ v8i field_operand(const uint4 (&raw)[6])
+{
+    constexpr int w = 6 * KS;
+    return v8i{(int)vec_word<w & 3>(raw[w >> 2]), (int)vec_word<(w + 1) & 3>(raw[(w + 1) >> 2]),
+               (int)vec_word<(w + 2) & 3>(raw[(w + 2) >> 2]), (int)vec_word<(w + 3) & 3>(raw[(w + 3) >> 2]),
+               (int)vec_word<(w + 4) & 3>(raw[(w + 4) >> 2]), (int)vec_word<(w + 5) & 3>(raw[(w + 5) >> 2]), 0, 0};
+}
 
 // Workgroups are dealt round-robin to the 8 XCDs; give each XCD a contiguous run of tiles so that
 // the packed rows it re-reads stay in its own L2.

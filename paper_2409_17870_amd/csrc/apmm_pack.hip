@@ -15,6 +15,8 @@
 // read and bits/8 bytes written per element.
 #include <hip/hip_fp16.h>
 
+#include <type_traits>
+
 #include "apmm_kernels.h"
 
 namespace apmm {
@@ -196,7 +198,7 @@ __global__ __launch_bounds__(kThreads) void pack_rows_kernel(const uint8_t *__re
 //   form reaches the bandwidth of the copy.)
 //   Sum wave: adds the codes of one row and the padding; the sum waves of a row block follow its tile waves in
 //   the grid, so that they find the rows in L2.
-enum PackForm { kFieldForm, kByteForm, kOtherForm };  // compile-time: a launch fetches the code of its own form only
+enum PackForm { kFieldForm, kFold3, kFold4, kByteForm, kOtherForm };  // compile-time: a launch fetches the code of its own form only
 
 template <PackForm FORM, bool WHOLE>
 __global__ __launch_bounds__(kThreads) void pack_kernel(const uint8_t *__restrict__ codes, int64_t rows,
@@ -226,7 +228,7 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const uint8_t *__restric
             for (int i = 0; i < 16; ++i) d[i >> 3][i & 7] = 0u;  // rows past the operand are zero words
         }
         constexpr int kSlotVec = kPlaneWords / 4;
-        if constexpr (FORM == kFieldForm) {
+        if constexpr (FORM == kFieldForm || FORM == kFold3 || FORM == kFold4) {
             // k step ks: words 6 ks .. 6 ks + 5 of the row's 24, the 32 codes as 6-bit fields, field 8t + 2c + jh
             uint32_t dw[12];
 #pragma unroll
@@ -241,6 +243,29 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const uint8_t *__restric
                 dw[6 * e + 3] = (uint32_t)chunk[2];
                 dw[6 * e + 4] = (uint32_t)(chunk[2] >> 32) | ((uint32_t)chunk[3] << 16);
                 dw[6 * e + 5] = (uint32_t)(chunk[3] >> 16);
+            }
+            if constexpr (FORM == kFold4) {
+                uint4 *dst = reinterpret_cast<uint4 *>(packed + tile_row_word(row, kb, nkb, 4, 2 * h));
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const uint32_t f[6] = {dw[6 * e], dw[6 * e + 1], dw[6 * e + 2], dw[6 * e + 3], dw[6 * e + 4], dw[6 * e + 5]};
+                    uint32_t w[4];
+                    fold_words<4>(f, w);
+                    dst[e * kSlotVec] = make_uint4(w[0], w[1], w[2], w[3]);
+                }
+                return;
+            }
+            if constexpr (FORM == kFold3) {  // pair words of both k steps = slot h; top words 2 h, 2 h + 1 of slot 2
+                uint32_t w[2][3];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const uint32_t f[6] = {dw[6 * e], dw[6 * e + 1], dw[6 * e + 2], dw[6 * e + 3], dw[6 * e + 4], dw[6 * e + 5]};
+                    fold_words<3>(f, w[e]);
+                }
+                uint32_t *dst = packed + tile_row_word(row, kb, nkb, 3, 0);
+                *reinterpret_cast<uint4 *>(dst + h * kPlaneWords) = make_uint4(w[0][0], w[0][1], w[1][0], w[1][1]);
+                *reinterpret_cast<uint2 *>(dst + 2 * kPlaneWords + 2 * h) = make_uint2(w[0][2], w[1][2]);
+                return;
             }
             uint4 *dst = reinterpret_cast<uint4 *>(packed + tile_row_word(row, kb, nkb, 6, 3 * h));
 #pragma unroll
@@ -550,14 +575,30 @@ __global__ __launch_bounds__(kThreads) void unpack_kernel(const uint32_t *__rest
     uint32_t d[8];
 #pragma unroll
     for (int t4 = 0; t4 < 8; ++t4) d[t4] = 0u;
-    if (field) {
-        // words 6 ks .. 6 ks + 5 of the row's 24 hold the 32 six-bit fields of this group
-        const uint32_t *base = packed + tile_row_word(row, kb, nkb, 6, 0);
+    const bool folded = !field && weight_folded_form(bits);
+    if (field || folded) {
+        // the six field words of the k step: words 6 ks .. 6 ks + 5 of the row's 24, or folded into n words
         uint32_t dw[6];
+        if (field) {
+            const uint32_t *base = packed + tile_row_word(row, kb, nkb, 6, 0);
 #pragma unroll
-        for (int i = 0; i < 6; ++i) {
-            const int w = 6 * ks + i;
-            dw[i] = base[(w >> 2) * kPlaneWords + (w & 3)];
+            for (int i = 0; i < 6; ++i) {
+                const int w = 6 * ks + i;
+                dw[i] = base[(w >> 2) * kPlaneWords + (w & 3)];
+            }
+        } else {
+            const uint32_t *base = packed + tile_row_word(row, kb, nkb, bits, 0);
+            uint32_t in[4] = {0, 0, 0, 0};
+            for (int i = 0; i < bits; ++i) {
+                const int w = fold_word_at(bits, ks, i);
+                in[i] = base[(w >> 2) * kPlaneWords + (w & 3)];
+            }
+            auto word = [&](auto d_c) __attribute__((always_inline)) {
+                constexpr int D = decltype(d_c)::value;
+                dw[D] = bits == 4 ? unfold_word<4, D>(in[0], in[1], in[2], in[3]) : unfold_word<3, D>(in[0], in[1], in[2], 0u);
+            };
+            word(std::integral_constant<int, 0>{}); word(std::integral_constant<int, 1>{}); word(std::integral_constant<int, 2>{});
+            word(std::integral_constant<int, 3>{}); word(std::integral_constant<int, 4>{}); word(std::integral_constant<int, 5>{});
         }
         const uint64_t chunk[4] = {(uint64_t)dw[0] | ((uint64_t)(dw[1] & 0xffffu) << 32),
                                    (uint64_t)(dw[1] >> 16) | ((uint64_t)dw[2] << 16),
@@ -582,7 +623,7 @@ __global__ __launch_bounds__(kThreads) void unpack_kernel(const uint32_t *__rest
 #pragma unroll
         for (int i = 0; i < 8; ++i) d[i] = (src[i >> 1] >> (4 * (i & 1))) & 0x0f0f0f0fu;
     }
-    for (int h = first_pair_group(bits); !field && h < pair_groups(bits); ++h) {
+    for (int h = first_pair_group(bits); !field && !folded && h < pair_groups(bits); ++h) {
         const uint32_t *src = packed + tile_row_word(row, kb, nkb, bits, 2 * h + (ks >> 1)) + 2 * (ks & 1);
 #pragma unroll
         for (int tp = 0; tp < 2; ++tp) {
@@ -594,7 +635,7 @@ __global__ __launch_bounds__(kThreads) void unpack_kernel(const uint32_t *__rest
                     d[2 * (2 * tp + tt) + jh] |= ((word >> (4 * jh + 2 * tt)) & 0x03030303u) << (2 * h);
         }
     }
-    if (!field && has_single_group(bits)) {
+    if (!field && !folded && has_single_group(bits)) {
         const uint32_t *src = packed + tile_row_word(row, kb, nkb, bits, bits - 1);
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
@@ -636,6 +677,8 @@ hipError_t launch_pack(const uint8_t *codes, int64_t rows, int64_t K, int bits, 
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const bool whole = K % 64 == 0;
     const auto kernel = field ? (whole ? pack_kernel<kFieldForm, true> : pack_kernel<kFieldForm, false>)
+                      : bits == 3 ? (whole ? pack_kernel<kFold3, true> : pack_kernel<kFold3, false>)
+                      : bits == 4 ? (whole ? pack_kernel<kFold4, true> : pack_kernel<kFold4, false>)
                       : byte_form(bits) ? (whole ? pack_kernel<kByteForm, true> : pack_kernel<kByteForm, false>)
                                         : (whole ? pack_kernel<kOtherForm, true> : pack_kernel<kOtherForm, false>);
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, codes, rows, K, bits, packed, rows_p, nkb);

@@ -390,7 +390,7 @@ def test_gemm_from_codes_through_the_workspace(gpu, oracle, M, N, K, p, q):
                                          (33, 8, 8, True)])
 def test_from_codes_route_with_a_workspace(gpu, oracle, M, p, q, packs):
     """Which token counts are taken in one launch and which are packed first."""
-    case = dict(M=M, N=4096, K=1024, p=p, q=q, a_dist="bernoulli", scaled=True)
+    case = dict(M=M, N=8192, K=1024, p=p, q=q, a_dist="bernoulli", scaled=True)
     data = inputs.make_case(case, 7100 + M + 10 * p + q)
     c32, _ = run_from_codes(gpu, data, case, workspace=True)
     assert gpu[1].apmm_last_gemm_kernel().endswith(",packed>" if packs else ",codes>")
@@ -788,6 +788,19 @@ def test_field_form_tile_arrangements(gpu, oracle, p, q, M, N, K):
     against the oracle."""
     case = dict(M=M, N=N, K=K, p=p, q=q, a_dist="normal" if p == 4 else "bernoulli", scaled=True)
     full_check(gpu, oracle, case, 7300 + 10 * p + q + M)
+
+
+@pytest.mark.parametrize("p", [1, 2, 3, 4])
+@pytest.mark.parametrize("q", [3, 4])
+@pytest.mark.parametrize("M,N,K", [(130, 140, 513), (1500, 2100, 129), (300, 8100, 600), (2049, 4096, 128)])
+def test_folded_weights_on_the_large_tiles(gpu, oracle, M, N, K, p, q):
+    """3- and 4-bit weights (folded form) through every tile the launch rule has for them, first and last stages of K."""
+    case = dict(M=M, N=N, K=K, p=p, q=q, a_dist="bernoulli", scaled=True)
+    data = inputs.make_case(case, 8500 + M + 10 * p + q)
+    want = oracle.gemm_i64(data["a_codes"], data["w_codes"], p, q)
+    c32, c16 = run_case(gpu, data, case, algo=FP4, want_i32=True, want_f16=True)
+    assert np.array_equal(c32.astype(np.int64), want)
+    check_f16(c16, want, data, oracle)
 
 
 @pytest.mark.parametrize("p,q", [(p, q) for p in range(1, 5) for q in range(1, 5)])

@@ -27,7 +27,12 @@ constexpr int ksplit_owner(int wm, int wn, int bi, int bj)
 {
     return wm == 1 ? bj * 4 / wn : wm == 2 ? 2 * bi + (bj >= (wn + 1) / 2 ? 1 : 0) : bi;
 }
-constexpr int ksplit_lds_bytes(int wm, int wn) { return wm * wn * 3 * 4 * 64 * 16; }
+// The 128 x 128 tile (4 x 4 blocks, 256 accumulators per wave): stages of half a k block, for which the raw words of two
+// stages fit beside the accumulators, and the partial tiles meet in two rounds of half the column blocks.  10 KB per k step
+// of 16 MFMAs (W4A4), where four wave tiles of 64 x 64 ask L1 for 20: half the time per k, for 6 us more at the end.
+constexpr bool ksplit_half(int wm, int wn) { return wm * wn > 12; }
+constexpr int ksplit_rounds(int wm, int wn) { return ksplit_half(wm, wn) ? 2 : 1; }
+constexpr int ksplit_lds_bytes(int wm, int wn) { return wm * wn / ksplit_rounds(wm, wn) * (ksplit_half(wm, wn) ? 4 : 3) * 4 * 64 * 16; }
 
 template <int P, int Q, int WM, int WN>
 __global__ __launch_bounds__(256, WN == 2 ? 2 : 1)  // two workgroups of the 64 x 64 tile share a compute unit
@@ -38,12 +43,14 @@ void gemm_mfma_ksplit_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32
 {
     static_assert(P >= 1 && P <= 4 && Q >= 1 && Q <= 4, "instantiated for codes of up to four bits");
     static_assert(WM == 1 || WM == 2 || WM == 4, "row blocks per tile");
-    static_assert(WM * WN <= 13, "three partial copies of every block must fit the 160 KB of LDS");
+    static_assert(ksplit_lds_bytes(WM, WN) <= 160 * 1024, "the partial copies of every block of a round must fit the LDS");
     extern __shared__ __align__(16) float4 red[];  // [block][partial 0..2][register quad 0..3][lane]
     constexpr bool AF = activation_field_form(P);
     constexpr int SLOTS_A = activation_slots(P);
     constexpr int NB = WM * WN;
-    constexpr int KS = 4;
+    constexpr bool HALF = ksplit_half(WM, WN);
+    constexpr int KS = HALF ? 2 : 4;  // MFMA k steps per stage
+    constexpr int LOADS_A = HALF ? half_slots(P, AF) : SLOTS_A, LOADS_B = HALF ? half_slots(Q, false) : Q;
     constexpr uint32_t ca = (1u << P) - 1, cw = (1u << Q) - 1;
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
@@ -92,7 +99,7 @@ void gemm_mfma_ksplit_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32
     }
 
     v16f acc[WM][WN];
-    uint4 ra[2][WM][SLOTS_A], rb[2][WN][Q];  // raw words of a stage, by stage parity
+    uint4 ra[2][WM][LOADS_A], rb[2][WN][LOADS_B];  // raw words of a stage, by stage parity (HALF: by half of the k block)
     v4i af[2][AF ? 1 : WM];                  // formed fragments, by k step parity
     OperandFrag<Q> bf[2][WN];
 
@@ -102,13 +109,15 @@ void gemm_mfma_ksplit_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32
         for (int bi = 0; bi < WM; ++bi) {
             const char *src = pa_blk[bi] + (int64_t)st * kStageBytesA + voff_a;
 #pragma unroll
-            for (int sl = 0; sl < SLOTS_A; ++sl) ra[buf][bi][sl] = *reinterpret_cast<const uint4 *>(src + sl * kSlotBytes);
+            for (int i = 0; i < LOADS_A; ++i)
+                ra[buf][bi][i] = *reinterpret_cast<const uint4 *>(src + (HALF ? half_slot(P, AF, buf, i) : i) * kSlotBytes);
         }
 #pragma unroll
         for (int bj = 0; bj < WN; ++bj) {
             const char *src = pb_blk[bj] + (int64_t)st * kStageBytesB + voff_b;
 #pragma unroll
-            for (int sl = 0; sl < Q; ++sl) rb[buf][bj][sl] = *reinterpret_cast<const uint4 *>(src + sl * kSlotBytes);
+            for (int i = 0; i < LOADS_B; ++i)
+                rb[buf][bj][i] = *reinterpret_cast<const uint4 *>(src + (HALF ? half_slot(Q, false, buf, i) : i) * kSlotBytes);
         }
     };
 
@@ -151,16 +160,19 @@ void gemm_mfma_ksplit_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32
             constexpr int buf = decltype(buf_c)::value, ks = decltype(ks_c)::value, task = decltype(task_c)::value;
             if constexpr (task < TASKS_A) {
                 constexpr int f = task / 4, d = task % 4;
-                if constexpr (!AF) af[ks & 1][f][d] = (int)operand_dword<P, ks, d>(ra[buf][f]);
+                if constexpr (AF) {
+                } else if constexpr (HALF) af[ks & 1][f][d] = (int)half_operand_dword<P, buf, ks, d>(ra[buf][f]);
+                else af[ks & 1][f][d] = (int)operand_dword<P, ks, d>(ra[buf][f]);
             } else {
                 constexpr int f = (task - TASKS_A) / DB, d = (task - TASKS_A) % DB;
-                bf[ks & 1][f][d] = (int)operand_dword<Q, ks, d>(rb[buf][f]);
+                if constexpr (HALF) bf[ks & 1][f][d] = (int)half_operand_dword<Q, buf, ks, d>(rb[buf][f]);
+                else bf[ks & 1][f][d] = (int)operand_dword<Q, ks, d>(rb[buf][f]);
             }
         };
         auto stage = [&](auto buf_c, int st) __attribute__((always_inline)) {
             constexpr int buf = decltype(buf_c)::value;
             using Other = std::integral_constant<int, buf ^ 1>;
-            load_stage(Other{}, st + 1 < s_end ? st + 1 : st);  // the surplus load is discarded
+            load_stage(Other{}, (HALF && buf == 0) || st + 1 >= s_end ? st : st + 1);  // the surplus load is discarded
             __builtin_amdgcn_sched_barrier(0);
             static_for<KS * PER_KS>([&](auto i_c) __attribute__((always_inline)) {
                 constexpr int i = decltype(i_c)::value;
@@ -170,7 +182,8 @@ void gemm_mfma_ksplit_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32
                 if constexpr (AF) a8 = field_operand<ks>(ra[buf][bi]);
                 else a8 = widen(af[ks & 1][bi]);
                 acc[bi][bj] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                    a8, widen(bf[ks & 1][bj]), acc[bi][bj], format_a, format_b, 0, operand_exponent(P, ks), 0, operand_exponent(Q, ks));
+                    a8, widen(bf[ks & 1][bj]), acc[bi][bj], format_a, format_b, 0, operand_exponent(P, HALF ? 2 * buf + ks : ks), 0,
+                    operand_exponent(Q, HALF ? 2 * buf + ks : ks));
                 static_for<TPM>([&](auto t_c) __attribute__((always_inline)) {
                     constexpr int task = j * TPM + decltype(t_c)::value;
                     if constexpr (task < TASKS) {
@@ -184,11 +197,18 @@ void gemm_mfma_ksplit_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32
         };
         static_for<TASKS>([&](auto t_c) __attribute__((always_inline)) { form(I0{}, I0{}, t_c); });
         int st = s_begin;
-        for (; st + 1 < s_end; st += 2) {
-            stage(I0{}, st);
-            stage(I1{}, st + 1);
+        if constexpr (HALF) {
+            for (; st < s_end; ++st) {
+                stage(I0{}, st);
+                stage(I1{}, st);
+            }
+        } else {
+            for (; st + 1 < s_end; st += 2) {
+                stage(I0{}, st);
+                stage(I1{}, st + 1);
+            }
+            if (st < s_end) stage(I0{}, st);
         }
-        if (st < s_end) stage(I0{}, st);
     }
 
     using T = std::true_type;
@@ -201,11 +221,11 @@ void gemm_mfma_ksplit_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32
     const int64_t m_own = m0 + bi_own * 32 + 4 * kh;  // row of register v: m_own + 8 (v / 4) + v % 4
     // (Unconditional loads from clamped addresses, one uniform branch around each set: a load under a per-lane
     // condition is followed by a wait, and 26 such waits in a row cost 2 us here.)
-    uint32_t sa_bits[16], sw_bits[NB];
+    uint32_t sa_bits[16], sw_bits[WN];
 #pragma unroll
     for (int v = 0; v < 16; ++v) sa_bits[v] = 0x3c00u;
 #pragma unroll
-    for (int b = 0; b < NB; ++b) sw_bits[b] = 0x3c00u;
+    for (int bj = 0; bj < WN; ++bj) sw_bits[bj] = 0x3c00u;
     if (cf_arg && as_arg) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
@@ -219,25 +239,9 @@ void gemm_mfma_ksplit_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32
         for (int bj = 0; bj < WN; ++bj) {
             int64_t n = n0 + bj * 32 + r32;
             if (n >= N) n = N - 1;
-            const uint32_t h = ws_arg[n];
-#pragma unroll
-            for (int bi = 0; bi < WM; ++bi) sw_bits[bi * WN + bj] = h;
+            sw_bits[bj] = ws_arg[n];
         }
     }
-    static_for<NB>([&](auto b_c) __attribute__((always_inline)) {
-        constexpr int b = decltype(b_c)::value, bi = b / WN, bj = b % WN;
-        constexpr int own = ksplit_owner(WM, WN, bi, bj);
-        if (wave != own) {
-            const int part = ((wave - own + 4) & 3) - 1;
-            float4 *dst = red + (b * 3 + part) * 256 + lane;
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4)
-                dst[q4 * 64] = make_float4(acc[bi][bj][4 * q4], acc[bi][bj][4 * q4 + 1], acc[bi][bj][4 * q4 + 2],
-                                           acc[bi][bj][4 * q4 + 3]);
-        }
-    });
-    __syncthreads();
-
     // Store of one owned block.  GUARD: border tile, every element tested.  PAIR (interior, even N, 4-byte aligned
     // fp16 output): neighbouring lanes hold neighbouring columns; rows are taken in pairs, the even lane of a lane
     // pair collects both columns of the first row, the odd lane both columns of the second (one lane exchange),
@@ -249,25 +253,12 @@ void gemm_mfma_ksplit_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32
     float sa_f[16];
 #pragma unroll
     for (int v = 0; v < 16; ++v) sa_f[v] = half_bits_to_float((uint16_t)use_here(sa_bits[v]));
-    static_for<NB>([&](auto b_c) __attribute__((always_inline)) {
-        constexpr int b = decltype(b_c)::value, bi = b / WN, bj = b % WN;
-        constexpr int own = ksplit_owner(WM, WN, bi, bj);
-        if (wave != own) return;
-        // all twelve reads of the three other partials in flight before the first add
-        float4 t[12];
-#pragma unroll
-        for (int i = 0; i < 12; ++i) t[i] = red[(b * 3 + i / 4) * 256 + (i % 4) * 64 + lane];
-        __builtin_amdgcn_sched_barrier(0);
-        v16f c = acc[bi][bj];
-#pragma unroll
-        for (int i = 0; i < 12; ++i) {
-            c[4 * (i % 4)] += t[i].x; c[4 * (i % 4) + 1] += t[i].y; c[4 * (i % 4) + 2] += t[i].z; c[4 * (i % 4) + 3] += t[i].w;
-        }
-        const int64_t n = n0 + bj * 32 + r32;
+    // stores the finished block in this wave's row block and the columns from n on
+    auto finish = [&](const v16f &c, int64_t n, uint32_t sw_h) __attribute__((always_inline)) {
         auto emit = [&](auto guard_c, auto i32_c, auto f16_c, auto pair_c, auto nt_c) __attribute__((always_inline)) {
             constexpr bool GUARD = decltype(guard_c)::value, I32 = decltype(i32_c)::value, F16 = decltype(f16_c)::value,
                            PAIR = decltype(pair_c)::value, NT = decltype(nt_c)::value;
-            const float sw = half_bits_to_float((uint16_t)use_here(sw_bits[b]));
+            const float sw = half_bits_to_float((uint16_t)use_here(sw_h));
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int64_t m = m_own + 8 * (v / 4) + (v % 4);
@@ -303,6 +294,71 @@ void gemm_mfma_ksplit_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32
             else if (interior && pair_ok) emit(F{}, F{}, T{}, T{}, F{});
             else if (interior) emit(F{}, F{}, T{}, F{}, F{});
             else emit(T{}, F{}, T{}, F{}, F{});
+        }
+    };
+    constexpr int ROUNDS = ksplit_rounds(WM, WN), WNR = WN / ROUNDS, NBR = NB / ROUNDS;  // column blocks and blocks of a round
+    static_for<ROUNDS>([&](auto round_c) __attribute__((always_inline)) {
+        constexpr int round = decltype(round_c)::value;
+        if constexpr (round > 0) __syncthreads();  // every wave has read the partials of the round before
+        if constexpr (HALF) {
+            // The same code for every wave: each block of the round goes to LDS from all four waves and is taken from there by
+            // the wave that owns its row block.  With code of its own per block and owner, as for the smaller tiles, the
+            // registers spilled and the straight-line code of sixteen blocks was fetched cold: 1024 x 4096 x 4096 W4A4 23.7 ->
+            // 16.8 us.  (The smaller tiles are better off without the fourth copy: 65 x 4096 x 4096 W2A2 5.7 against 6.2 us.)
+            static_for<NBR>([&](auto b_c) __attribute__((always_inline)) {
+                constexpr int b = decltype(b_c)::value, bi = b / WNR, bj = round * WNR + b % WNR;
+                float4 *dst = red + (b * 4 + wave) * 256 + lane;
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4)
+                    dst[q4 * 64] = make_float4(acc[bi][bj][4 * q4], acc[bi][bj][4 * q4 + 1], acc[bi][bj][4 * q4 + 2], acc[bi][bj][4 * q4 + 3]);
+            });
+            __syncthreads();
+#pragma unroll 1
+            for (int jj = 0; jj < WNR; ++jj) {
+                float4 t[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) t[i] = red[((wave * WNR + jj) * 4 + i / 4) * 256 + (i % 4) * 64 + lane];
+                v16f c;
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    c[4 * q4] = (t[q4].x + t[4 + q4].x) + (t[8 + q4].x + t[12 + q4].x);
+                    c[4 * q4 + 1] = (t[q4].y + t[4 + q4].y) + (t[8 + q4].y + t[12 + q4].y);
+                    c[4 * q4 + 2] = (t[q4].z + t[4 + q4].z) + (t[8 + q4].z + t[12 + q4].z);
+                    c[4 * q4 + 3] = (t[q4].w + t[4 + q4].w) + (t[8 + q4].w + t[12 + q4].w);
+                }
+                static_assert(WNR == 2 || !HALF, "two column blocks per round");
+                finish(c, n0 + (round * WNR + jj) * 32 + r32, jj ? sw_bits[round * WNR + 1] : sw_bits[round * WNR]);
+            }
+        } else {
+            static_for<NBR>([&](auto b_c) __attribute__((always_inline)) {
+                constexpr int b = decltype(b_c)::value, bi = b / WN, bj = b % WN;
+                constexpr int own = ksplit_owner(WM, WN, bi, bj);
+                if (wave != own) {
+                    const int part = ((wave - own + 4) & 3) - 1;
+                    float4 *dst = red + (b * 3 + part) * 256 + lane;
+#pragma unroll
+                    for (int q4 = 0; q4 < 4; ++q4)
+                        dst[q4 * 64] = make_float4(acc[bi][bj][4 * q4], acc[bi][bj][4 * q4 + 1], acc[bi][bj][4 * q4 + 2],
+                                                   acc[bi][bj][4 * q4 + 3]);
+                }
+            });
+            __syncthreads();
+            static_for<NBR>([&](auto b_c) __attribute__((always_inline)) {
+                constexpr int b = decltype(b_c)::value, bi = b / WN, bj = b % WN;
+                constexpr int own = ksplit_owner(WM, WN, bi, bj);
+                if (wave != own) return;
+                // all twelve reads of the three other partials in flight before the first add
+                float4 t[12];
+#pragma unroll
+                for (int i = 0; i < 12; ++i) t[i] = red[(b * 3 + i / 4) * 256 + (i % 4) * 64 + lane];
+                __builtin_amdgcn_sched_barrier(0);
+                v16f c = acc[bi][bj];
+#pragma unroll
+                for (int i = 0; i < 12; ++i) {
+                    c[4 * (i % 4)] += t[i].x; c[4 * (i % 4) + 1] += t[i].y; c[4 * (i % 4) + 2] += t[i].z; c[4 * (i % 4) + 3] += t[i].w;
+                }
+                finish(c, n0 + bj * 32 + r32, sw_bits[bj]);
+            });
         }
     });
 }

@@ -82,13 +82,27 @@ __device__ __forceinline__ uint32_t operand_dword(const uint4 (&raw)[N])
 __device__ __forceinline__ v8i widen(const v4i &v) { return v8i{v[0], v[1], v[2], v[3], 0, 0, 0, 0}; }
 __device__ __forceinline__ v8i widen(const v6i &v) { return v8i{v[0], v[1], v[2], v[3], v[4], v[5], 0, 0}; }
 // E2M3 operand of k step KS from the six slots of a field-form row: words 6 KS .. 6 KS + 5 of its 24, as they stand
-template <int KS>
-__device__ __forceinline__ v8i field_operand(const uint4 (&raw)[6])
+// (or of local k step KS of half a k block from three)
+template <int KS, int NS>
+__device__ __forceinline__ v8i field_operand(const uint4 (&raw)[NS])
 {
     constexpr int w = 6 * KS;
     return v8i{(int)vec_word<w & 3>(raw[w >> 2]), (int)vec_word<(w + 1) & 3>(raw[(w + 1) >> 2]),
                (int)vec_word<(w + 2) & 3>(raw[(w + 2) >> 2]), (int)vec_word<(w + 3) & 3>(raw[(w + 3) >> 2]),
                (int)vec_word<(w + 4) & 3>(raw[(w + 4) >> 2]), (int)vec_word<(w + 5) & 3>(raw[(w + 5) >> 2]), 0, 0};
+}
+
+// ---- The same for stages of half a k block: k steps 2 H, 2 H + 1 (KSL = 0, 1), whose words are these slots ----
+constexpr int half_slots(int n, bool field) { return field ? 3 : n <= 2 ? 1 : 2; }
+constexpr int half_slot(int n, bool field, int h, int i) { return field ? 3 * h + i : n == 1 ? 0 : n == 2 ? h : n == 3 ? (i == 0 ? h : 2) : 2 * h + i; }
+template <int N, int H, int KSL, int D, int NS>
+__device__ __forceinline__ uint32_t half_operand_dword(const uint4 (&raw)[NS])
+{
+    if constexpr (N == 1) return fp4_single_dword<2 * H + KSL, D>(raw[0]);
+    else if constexpr (N == 2) return (D & 1) ? (vec_word<2 * KSL + D / 2>(raw[0]) >> 2) & 0x33333333u : vec_word<2 * KSL + D / 2>(raw[0]) & 0x33333333u;
+    else if constexpr (N == 3)
+        return unfold_word<3, D>(vec_word<2 * KSL>(raw[0]), vec_word<2 * KSL + 1>(raw[0]), vec_word<2 * H + KSL>(raw[NS - 1]), 0u);
+    else return unfold_word<4, D>(raw[KSL].x, raw[KSL].y, raw[KSL].z, raw[KSL].w);
 }
 
 // Workgroups are dealt round-robin to the 8 XCDs; give each XCD a contiguous run of tiles so that

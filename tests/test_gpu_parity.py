@@ -839,6 +839,33 @@ def test_k_split_across_waves_full_tiles(gpu, oracle, M, N, K, want_i32, want_f1
         check_f16(c16, want, data, oracle)
 
 
+@pytest.mark.parametrize("p,q", [(p, q) for p in range(1, 5) for q in range(2, 5)])
+@pytest.mark.parametrize("M,N,outs", [(1024, 4096, "f16"), (650, 5003, "both"), (1001, 4090, "i32")])
+def test_k_split_128_by_128_tile(gpu, oracle, M, N, outs, p, q):
+    """The tile whose waves work in half k blocks and meet in two rounds: inner and border tiles, a wave with one pair of
+    k blocks more than the others, every output."""
+    torch, binding = gpu
+    K = 8192 + 130 if q == 2 else 4096 + 130
+    if 4 * (K + 382) * ((1 << p) - 1) * ((1 << q) - 1) >= 1 << 24:
+        pytest.skip("beyond the exactness bound")
+    dev = torch.device("cuda:0")
+    g = torch.Generator(device=dev).manual_seed(8600 + 10 * p + q)
+    a = torch.randint(0, 1 << p, (M, K), generator=g, device=dev, dtype=torch.uint8)
+    w = torch.randint(0, 1 << q, (N, K), generator=g, device=dev, dtype=torch.uint8)
+    sa = (0.01 + 0.09 * torch.rand(M, generator=g, device=dev)).half()
+    sw = (0.01 + 0.09 * torch.rand(N, generator=g, device=dev)).half()
+    c32, c16 = binding.apmm_gemm(M, N, K, p, q, binding.apmm_pack_activations(a, p), binding.apmm_pack_weights(w, q),
+                                 want_i32=outs != "f16", want_f16=outs != "i32", w_scale=sw, a_scale=sa)
+    assert binding.apmm_last_gemm_kernel() == "gemm_mfma_ksplit_kernel<%d,%d,4,4>" % (p, q)
+    # sums of small integers: exact in double precision
+    want = ((2.0 * a.float() - ((1 << p) - 1)).double() @ (2.0 * w.float() - ((1 << q) - 1)).double().t().contiguous()).to(torch.int64)
+    if c32 is not None:
+        assert torch.equal(c32.to(torch.int64), want)
+    if c16 is not None:
+        f = want.double() * sa.double()[:, None] * sw.double()[None, :]
+        assert bool(((c16.double() - f).abs() <= 1e-3 * f.abs() + 1e-6).all())
+
+
 def test_k_split_kernel_declines_wide_codes(gpu):
     torch, binding = gpu
     a = torch.zeros((64, 512), dtype=torch.uint8, device="cuda:0")

@@ -5,6 +5,7 @@ in the library's HIP kernels.  PyTorch supplies device memory and the stream.  T
 no fallback: if the library is missing or a call fails, an exception is raised.
 """
 import ctypes
+import functools
 import os
 
 import torch  # imported before the library so that both share one HIP runtime (same soname)
@@ -98,12 +99,15 @@ def _check(status):
         raise ApmmError(status, text)
 
 
+# A single small product is as long as its call from Python, so the marshalling is kept short: addresses go to ctypes as
+# plain integers (the argument types convert them), the stream handle is read without building a Stream object, packed
+# sizes are computed once per shape.
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(None)
+    return t.data_ptr() if t is not None else None
 
 
 def _dev_u8(t, what):
@@ -111,10 +115,12 @@ def _dev_u8(t, what):
         raise ValueError("%s must be a contiguous 2-D uint8 CUDA tensor" % what)
 
 
+@functools.lru_cache(maxsize=1024)
 def apmm_packed_bytes(rows, K, bits):
     return int(load().apmm_packed_bytes(rows, K, bits))
 
 
+@functools.lru_cache(maxsize=1024)
 def apmm_packed_activation_bytes(M, K, p):
     return int(load().apmm_packed_activation_bytes(M, K, p))
 
@@ -129,7 +135,7 @@ def _pack(fn_name, codes, bits, out):
     nbytes = (apmm_packed_activation_bytes if fn_name == "apmm_pack_activations" else apmm_packed_bytes)(rows, K, bits)
     if out is None:
         out = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=codes.device)
-    elif out.numel() * out.element_size() < nbytes:
+    elif out.nbytes < nbytes:
         raise ValueError("packed buffer too small")
     _check(getattr(load(), fn_name)(_ptr(codes), rows, K, bits, _ptr(out), _stream()))
     return out
@@ -153,7 +159,7 @@ def apmm_quantize_pack_activations(x_f16, p, out=None, scale_out=None):
     nbytes = apmm_packed_activation_bytes(M, K, p)
     if out is None:
         out = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=x_f16.device)
-    elif out.numel() * out.element_size() < nbytes:
+    elif out.nbytes < nbytes:
         raise ValueError("packed buffer too small")
     if scale_out is None:
         scale_out = torch.empty(M, dtype=torch.float16, device=x_f16.device)
@@ -193,7 +199,7 @@ def apmm_gemm(M, N, K, p, q, a_packed, w_packed, want_i32=True, want_f16=False, 
         if s is not None and (s.dtype != torch.float16 or s.numel() != n or not s.is_cuda
                               or not s.is_contiguous()):
             raise ValueError("%s must be a contiguous float16 CUDA vector of the right length" % what)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    ws_bytes = 0 if workspace is None else workspace.nbytes
     _check(load().apmm_gemm_ex(M, N, K, p, q, _ptr(a_packed), _ptr(w_packed), _ptr(c_i32), _ptr(c_f16),
                                _ptr(w_scale), _ptr(a_scale), _ptr(workspace), ws_bytes, _stream(), algo))
     return c_i32, c_f16
@@ -210,7 +216,7 @@ def apmm_gemm_from_codes(a_codes, N, p, q, w_packed, want_i32=True, want_f16=Fal
         c_i32 = torch.empty((M, N), dtype=torch.int32, device=dev)
     if want_f16 and c_f16 is None:
         c_f16 = torch.empty((M, N), dtype=torch.float16, device=dev)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    ws_bytes = 0 if workspace is None else workspace.nbytes
     _check(load().apmm_gemm_from_codes(M, N, K, p, q, _ptr(a_codes), _ptr(w_packed), _ptr(c_i32), _ptr(c_f16),
                                        _ptr(w_scale), _ptr(a_scale), _ptr(workspace), ws_bytes, _stream()))
     return c_i32, c_f16

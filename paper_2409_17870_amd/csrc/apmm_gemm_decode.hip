@@ -383,9 +383,9 @@ hipError_t launch_mt(const GroupArgs &ga, hipStream_t stream)
 }
 
 // ---------------------------------------------------------------------------------------------
-// Small-M kernel on the matrix unit (M <= 64, p, q <= 2).  With more than a couple of tokens the
+// Small-M kernel on the matrix unit (M <= 64, p, q <= 4).  With more than a couple of tokens the
 // XOR/popcount form needs 2 p q M lane-operations per weight word and becomes VALU bound; the E2M1 MFMA
-// needs one expansion of the weight words (1.25 - 1.5 operations per 8 codes) whatever M is.
+// needs one expansion of the weight words (1.25 - 1.5 operations per 8 codes, 2 - 3.25 with 3 and 4 bits) whatever M is.
 // Same split of the work as the XOR/popcount kernel (8 waves over K, lane = weight row l % 16 and k block
 // l / 16 of four), same algebra as the large-M MFMA kernel:
 //   v_mfma_scale_f32_16x16x128_f8f6f4: A = 16 weight rows x 128 k, B = 128 k x 16 tokens, codes as E2M1;
@@ -415,14 +415,14 @@ hipError_t launch_mt(const GroupArgs &ga, hipStream_t stream)
 // kernel) 4.3 -> 3.2 / 7.6 -> 4.7 / 6.1 -> 4.9, 16 tokens 5.7 -> 4.4 / 9.8 -> 7.3 / 10.1 -> 7.1.
 // ---------------------------------------------------------------------------------------------
 template <int P, int Q, int TT, int RT, int CODES, int NJ = 8>
-__global__ __launch_bounds__(kThreads, (CODES == 1 && TT == 1) ? (NJ == 1 && RT == 1 ? 6 : 4) - (Q > 2 ? 1 : 0) : 2)  // waves per SIMD aimed at (weights of two plane groups hold twice the raw words)
+__global__ __launch_bounds__(kThreads, (CODES == 1 && TT == 1) ? (NJ == 1 && RT == 1 ? 6 : 4) - (Q > 2 ? 1 : 0) : 2)  // waves per SIMD aimed at (weights of 3 and 4 bits hold twice the raw words)
 void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg, int k_arg,
                              uint32_t misc_arg /* M | problems << 12 | token groups << 24 */, int reserved_arg, uint16_t *cf_arg, int32_t *ci_arg,
                              const uint16_t *ws_arg, const uint16_t *as_arg, GroupArgs ga)
 {
     static_assert((P <= 2 || (activation_field_form(P) && NJ == 8)) && Q <= 4,
                   "one plane group per activation, or activations in the field form (ready-made E2M3 operands); "
-                  "weights of one or two plane groups");
+                  "weights of up to four bits");
     constexpr bool AF = activation_field_form(P);
     constexpr int SA = activation_slots(P);  // slots of an activation row and k block
     static_assert(NJ == 8 || (NJ == 1 && CODES == 1 && TT == 1), "NJ = 1: codes of at most two tokens");
@@ -904,7 +904,7 @@ hipError_t launch_decode_mfma(const GroupArgs &ga, int rt, hipStream_t stream)
     if (p == 3 && q == 2) return launch_decode_mfma_pq<3, 2>(ga, tt, rt, stream);
     if (p == 4 && q == 1) return launch_decode_mfma_pq<4, 1>(ga, tt, rt, stream);
     if (p == 4 && q == 2) return launch_decode_mfma_pq<4, 2>(ga, tt, rt, stream);
-    // weights of two plane groups (packed activations only)
+    // weights of 3 and 4 bits
     if (q == 3) return p == 1 ? launch_decode_mfma_pq<1, 3>(ga, tt, rt, stream) : p == 2 ? launch_decode_mfma_pq<2, 3>(ga, tt, rt, stream)
                      : p == 3 ? launch_decode_mfma_pq<3, 3>(ga, tt, rt, stream) : launch_decode_mfma_pq<4, 3>(ga, tt, rt, stream);
     return p == 1 ? launch_decode_mfma_pq<1, 4>(ga, tt, rt, stream) : p == 2 ? launch_decode_mfma_pq<2, 4>(ga, tt, rt, stream)
@@ -981,11 +981,14 @@ hipError_t launch_gemm_decode_group(const GemmArgs *problems, int count, hipStre
         // tiles as soon as single ones would need a second round of workgroups (8192 x 4096, 64 tokens: 5.9 us)
         if (!gs[0].a_codes && variant == 104 && rows > 256 * kRowsPerWg) rt = 2;
         // packed 3- and 4-bit activations: 88 registers leave two workgroups per CU, so two channel tiles as soon as single
-        // ones would need a second round of workgroups (W2A4, one token at 11008 x 4096, cold weights: 7.4 us with single tiles)
-        // (with weights of two plane groups the two-tile variant holds too many raw words: 8.8 against 8.2 us for W4A4)
-        if (!gs[0].a_codes && activation_field_form(gs[0].p) && gs[0].q <= 2 && rows > 2 * 256 * kRowsPerWg) rt = 2;
+        // ones would need a second round of workgroups (W2A4, one token at 11008 x 4096, cold weights: 7.4 us with single tiles);
+        // with 4-bit weights under one token tile: from three workgroups' worth on (128 registers and more leave one workgroup per CU;
+        // 11008 channels 8.2 against 7.9 us, 15360 x 5120 16 tokens 11.6 -> 11.0 us; W3A3 11008 x 4096 7.7 -> 6.5 us,
+        // 15360 x 5120 10.0 -> 7.9 us; 32 tokens at 15360 x 5120 W4A4 17.8 -> 13.6 us)
+        if (!gs[0].a_codes && activation_field_form(gs[0].p) &&
+            rows > (gs[0].q == 4 && variant == 101 ? 3 : 2) * 256 * kRowsPerWg) rt = 2;
         if (gs[0].a_codes && variant == 104) rt = 1;  // four token tiles from codes: two row tiles do not fit the registers
-        // weights of two plane groups from codes: the two-tile variant fits three waves per SIMD only (11008 x 4096, 4 / 16
+        // weights of 3 and 4 bits from codes: the two-tile variant fits three waves per SIMD only (11008 x 4096, 4 / 16
         // tokens: 7.8 / 9.4 us against 6.3 / 7.9 us with single tiles)
         if (gs[0].a_codes && (gs[0].q > 2 || activation_field_form(gs[0].p))) rt = 1;  // (field-form codes: single tiles only)
         if (!make_group(gs, count, kRowsPerWg * rt, [](const GemmArgs &g) { return g.nkb; }, ga))

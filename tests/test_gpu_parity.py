@@ -270,6 +270,19 @@ def test_small_m_kernel_field_form_llm_shapes(gpu, oracle, M, N, K, p, q):
     check_f16(c16, want, data, oracle)
 
 
+@pytest.mark.parametrize("M,N,K,p,q,tiles", [(1, 8193, 300, 3, 3, 2), (16, 8192, 600, 4, 3, 1), (17, 8200, 530, 4, 4, 2), (16, 12288, 260, 4, 4, 1),
+                                             (5, 12289, 1100, 3, 4, 2), (40, 8200, 512, 3, 3, 2)])
+def test_field_form_channel_tiles_per_workgroup(gpu, oracle, M, N, K, p, q, tiles):
+    """Both sides of the line from which a workgroup takes two channel tiles, 3- and 4-bit weights."""
+    case = dict(M=M, N=N, K=K, p=p, q=q, a_dist="bernoulli", scaled=True)
+    data = inputs.make_case(case, 8700 + M + 10 * p + q)
+    want = oracle.gemm_i64(data["a_codes"], data["w_codes"], p, q)
+    c32, c16 = run_case(gpu, data, case, algo=DECODE, want_i32=True, want_f16=True)
+    assert gpu[1].apmm_last_gemm_kernel().endswith(",%d,packed>" % tiles)
+    assert np.array_equal(c32.astype(np.int64), want)
+    check_f16(c16, want, data, oracle)
+
+
 @pytest.mark.parametrize("p,q", [(1, 1), (2, 1), (5, 3), (2, 4), (8, 2), (1, 4), (6, 4)])
 @pytest.mark.parametrize("M", [1, 2, 3, 5, 8, 13, 16])
 def test_decode_kernel_all_token_counts(gpu, oracle, M, p, q):

@@ -67,13 +67,13 @@ typedef enum {
 } apmm_algo;
 
 /* Bytes of the packed form of a rows x K operand of `bits`-bit codes (paper Sec. 4.1:
- * `bits` one-bit planes in 32-bit words, concatenated, plus one int32 per row).  Rows are padded
+ * `bits` bits per element in 32-bit words, concatenated, plus one int32 per row).  Rows are padded
  * to a multiple of 32 and K to a multiple of 512.  Returns 0 for invalid arguments. */
 size_t apmm_packed_bytes(int64_t rows, int64_t K, int bits);
 
 /* Bytes of the packed form of M x K activations of p bits.  Equal to apmm_packed_bytes(M, K, p) except
  * for p = 3 and 4, whose codes are stored as 6-bit fields, the matrix unit's own operand form, so that
- * the GEMM needs neither a second sweep of K nor an expansion for them. */
+ * the GEMM needs no expansion for them. */
 size_t apmm_packed_activation_bytes(int64_t M, int64_t K, int p);
 
 /* Bytes of scratch apmm_gemm needs for this problem (may be 0). */

@@ -7,18 +7,18 @@
 //     = 4 S - 2 cw PA[m] - 2 ca PW[n] + K ca cw,     S = sum_k ua_k uw_k,
 //   PA[m], PW[n] = sums of the codes of a row over the padded K (they come with the packed operands;
 //   padded k positions hold the code ca resp. cw in both operands, which is why the true K appears),
-// which equals sum_ij 2^(i+j) D_ij.  The codes are cut into plane groups of two bits (and one of a single
-// bit when the width is odd): u = sum_h 4^h u_h.  A 2-bit code is the E2M1 pattern 00uu = u/2, exactly, and
-// S = sum_{h,h'} 4^(h+h') sum_k ua_h uw_h': K is swept once per pair of groups, every sweep adds into the
-// SAME fp32 accumulator, and the factor 4^(h+h') (times 16 for the two halvings and the leading 4) is the
-// MFMA's power-of-two operand scale: the paper's shift-and-add, done by the matrix unit.  The accumulator
-// starts at -2 cw PA[m] - 2 ca PW[n] + K ca cw, so that it ends at C: every term is an integer and every
-// partial sum stays below 2^24 (checked on the host), hence exact in any order.  Nothing but C reaches
-// global memory (paper Sec. 4.2).
+// which equals sum_ij 2^(i+j) D_ij.  Every width up to four bits is ONE operand, so K is swept once: one and two bits as
+// E2M1 (fp4), where 00uu is u / 2 exactly; three and four bits as E2M3 (fp6), where u is the number u / 8.  The matrix unit
+// multiplies the two formats at the same rate in any mix.  The factor that makes the product 4 ua uw is the MFMA's
+// power-of-two operand scale.  The accumulator starts at -2 cw PA[m] - 2 ca PW[n] + K ca cw, so that it ends at C: every
+// term is an integer and every partial sum stays below 2^24 (checked on the host), hence exact in any order.  Nothing but
+// C reaches global memory (paper Sec. 4.2).
 //
-// Activations of 3 or 4 bits arrive in the field form (apmm_layout.h): their packed words ARE the E2M3 (fp6)
-// operand, a 4-bit code u being the number u / 8, and the matrix unit multiplies fp6 by fp4 at the fp4 rate.
-// They need no expansion and no sweep per activation group: K is swept once per weight group.
+// Activations of 3 or 4 bits arrive in the field form (apmm_layout.h): their packed words ARE the E2M3 operand.  Weights of 3
+// or 4 bits are unfolded to it in registers with 13 or 8 operations per 32 codes.  Before, as two plane groups in the
+// operands, they took twelve operations and two sweeps of K: 2048 x 11008 x 4096 with both outputs W4A4 110.8 -> 86.5 us,
+// W3A3 104.1 -> 76.3 us.  What bounds the tiles with 6-bit activations is L1 (64 B a clock): 80 B a clock at the full
+// matrix rate for W2A4, 112 B for W4A4.
 //
 // Data movement: no LDS.  On gfx950 a wave that owns its SIMD alone has about 17 issue cycles per
 // 32-cycle MFMA for everything else; a ds_read_b128 costs ~20 and a ds_write_b128 ~40 of them, a VALU

@@ -18,7 +18,7 @@ hipError_t launch_unpack(const uint32_t *packed, int64_t rows, int64_t K, int bi
 // Design B: plane pairs by XOR + popcount on the vector ALU (any p, q in 1..8).
 hipError_t launch_gemm_valu(const GemmArgs &args, hipStream_t stream);
 
-// Design A: plane groups recombined into E2M1 / E2M3 codes in registers, f8f6f4 MFMA, exact fp32 accumulate
+// Design A: planes recombined into E2M1 / E2M3 codes in registers, f8f6f4 MFMA, exact fp32 accumulate
 // (p, q in 1..4 while 4 K (2^p - 1)(2^q - 1) < 2^24).
 bool gemm_mfma_fp4_supported(const GemmArgs &args);
 hipError_t launch_gemm_mfma_fp4(const GemmArgs &args, hipStream_t stream);

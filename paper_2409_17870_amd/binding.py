@@ -115,12 +115,12 @@ def _dev_u8(t, what):
         raise ValueError("%s must be a contiguous 2-D uint8 CUDA tensor" % what)
 
 
-@functools.lru_cache(maxsize=1024)
+@functools.lru_cache(maxsize=1024, typed=True)
 def apmm_packed_bytes(rows, K, bits):
     return int(load().apmm_packed_bytes(rows, K, bits))
 
 
-@functools.lru_cache(maxsize=1024)
+@functools.lru_cache(maxsize=1024, typed=True)
 def apmm_packed_activation_bytes(M, K, p):
     return int(load().apmm_packed_activation_bytes(M, K, p))
 

@@ -50,6 +50,14 @@ void gemm_mfma_ksplit_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32
     constexpr int NB = WM * WN;
     constexpr bool HALF = ksplit_half(WM, WN);
     constexpr int KS = HALF ? 2 : 4;  // MFMA k steps per stage
+    // The 64 x 64 tile with 6-bit fields against folded weights: 248 of the 256 registers of a wave hold accumulators, raw words
+    // and fragments.  The lane's offset is hidden from the compiler at each use there, so that the addresses stay a scalar
+    // base and one offset register; as 64-bit vector pointers they were spilled and fetched back inside the k loop, each
+    // behind a wait for all loads in flight (W4A4, 65 x 4096 x 4096 8.3 -> 6.7 us, 256 x 4096 x 11008 16.7 -> 13.4 us; W3A3 256 x
+    // 4096 x 4096 7.9 -> 7.4 us, 256 x 4096 x 11008 13.3 -> 12.9 us.  Half stages as in the 128 x 128 tile take 6.4 and 15.3,
+    // 7.8 and 15.3 us, one workgroup to a compute unit 7.3 and 16.9, 7.6 and 13.0 us).
+    constexpr bool TIGHT = WM * WN == 4 && AF && Q > 2;
+    auto hidden = [](uint32_t v) __attribute__((always_inline)) { return TIGHT ? use_here(v) : v; };
     constexpr int LOADS_A = HALF ? half_slots(P, AF) : SLOTS_A, LOADS_B = HALF ? half_slots(Q, false) : Q;
     constexpr uint32_t ca = (1u << P) - 1, cw = (1u << Q) - 1;
     using I0 = std::integral_constant<int, 0>;
@@ -107,14 +115,14 @@ void gemm_mfma_ksplit_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32
         constexpr int buf = decltype(buf_c)::value;
 #pragma unroll
         for (int bi = 0; bi < WM; ++bi) {
-            const char *src = pa_blk[bi] + (int64_t)st * kStageBytesA + voff_a;
+            const char *src = pa_blk[bi] + (int64_t)st * kStageBytesA + hidden(voff_a);
 #pragma unroll
             for (int i = 0; i < LOADS_A; ++i)
                 ra[buf][bi][i] = *reinterpret_cast<const uint4 *>(src + (HALF ? half_slot(P, AF, buf, i) : i) * kSlotBytes);
         }
 #pragma unroll
         for (int bj = 0; bj < WN; ++bj) {
-            const char *src = pb_blk[bj] + (int64_t)st * kStageBytesB + voff_b;
+            const char *src = pb_blk[bj] + (int64_t)st * kStageBytesB + hidden(voff_b);
 #pragma unroll
             for (int i = 0; i < LOADS_B; ++i)
                 rb[buf][bj][i] = *reinterpret_cast<const uint4 *>(src + (HALF ? half_slot(Q, false, buf, i) : i) * kSlotBytes);
@@ -218,7 +226,8 @@ void gemm_mfma_ksplit_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32
     // the 16 token scales of this lane's rows (all of a wave's blocks lie in row block bi_own), one channel scale
     // per block.
     const int bi_own = WM == 1 ? 0 : WM == 2 ? wave >> 1 : wave;
-    const int64_t m_own = m0 + bi_own * 32 + 4 * kh;  // row of register v: m_own + 8 (v / 4) + v % 4
+    const int lane_out = (int)hidden((uint32_t)lane), c32 = lane_out & 31;  // (nothing of the store is kept through the k loop)
+    const int64_t m_own = m0 + bi_own * 32 + 4 * (lane_out >> 5);  // row of register v: m_own + 8 (v / 4) + v % 4
     // (Unconditional loads from clamped addresses, one uniform branch around each set: a load under a per-lane
     // condition is followed by a wait, and 26 such waits in a row cost 2 us here.)
     uint32_t sa_bits[16], sw_bits[WN];
@@ -237,7 +246,7 @@ void gemm_mfma_ksplit_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32
     if (cf_arg && ws_arg) {
 #pragma unroll
         for (int bj = 0; bj < WN; ++bj) {
-            int64_t n = n0 + bj * 32 + r32;
+            int64_t n = n0 + bj * 32 + c32;
             if (n >= N) n = N - 1;
             sw_bits[bj] = ws_arg[n];
         }
@@ -249,7 +258,7 @@ void gemm_mfma_ksplit_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32
     const bool interior = (m0 + 32 * WM <= M) && (n0 + 32 * WN <= N);
     const bool pair_ok = (N & 1) == 0 && (reinterpret_cast<uintptr_t>(cf_arg) & 3u) == 0;
     const bool single = !(ci_arg && cf_arg);
-    const bool odd = lane & 1;
+    const bool odd = lane_out & 1;
     float sa_f[16];
 #pragma unroll
     for (int v = 0; v < 16; ++v) sa_f[v] = half_bits_to_float((uint16_t)use_here(sa_bits[v]));
@@ -307,7 +316,7 @@ void gemm_mfma_ksplit_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32
             // 16.8 us.  (The smaller tiles are better off without the fourth copy: 65 x 4096 x 4096 W2A2 5.7 against 6.2 us.)
             static_for<NBR>([&](auto b_c) __attribute__((always_inline)) {
                 constexpr int b = decltype(b_c)::value, bi = b / WNR, bj = round * WNR + b % WNR;
-                float4 *dst = red + (b * 4 + wave) * 256 + lane;
+                float4 *dst = red + (b * 4 + wave) * 256 + lane_out;
 #pragma unroll
                 for (int q4 = 0; q4 < 4; ++q4)
                     dst[q4 * 64] = make_float4(acc[bi][bj][4 * q4], acc[bi][bj][4 * q4 + 1], acc[bi][bj][4 * q4 + 2], acc[bi][bj][4 * q4 + 3]);
@@ -317,7 +326,7 @@ void gemm_mfma_ksplit_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32
             for (int jj = 0; jj < WNR; ++jj) {
                 float4 t[16];
 #pragma unroll
-                for (int i = 0; i < 16; ++i) t[i] = red[((wave * WNR + jj) * 4 + i / 4) * 256 + (i % 4) * 64 + lane];
+                for (int i = 0; i < 16; ++i) t[i] = red[((wave * WNR + jj) * 4 + i / 4) * 256 + (i % 4) * 64 + lane_out];
                 v16f c;
 #pragma unroll
                 for (int q4 = 0; q4 < 4; ++q4) {
@@ -327,7 +336,7 @@ void gemm_mfma_ksplit_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32
                     c[4 * q4 + 3] = (t[q4].w + t[4 + q4].w) + (t[8 + q4].w + t[12 + q4].w);
                 }
                 static_assert(WNR == 2 || !HALF, "two column blocks per round");
-                finish(c, n0 + (round * WNR + jj) * 32 + r32, jj ? sw_bits[round * WNR + 1] : sw_bits[round * WNR]);
+                finish(c, n0 + (round * WNR + jj) * 32 + c32, jj ? sw_bits[round * WNR + 1] : sw_bits[round * WNR]);
             }
         } else {
             static_for<NBR>([&](auto b_c) __attribute__((always_inline)) {
@@ -335,7 +344,7 @@ void gemm_mfma_ksplit_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32
                 constexpr int own = ksplit_owner(WM, WN, bi, bj);
                 if (wave != own) {
                     const int part = ((wave - own + 4) & 3) - 1;
-                    float4 *dst = red + (b * 3 + part) * 256 + lane;
+                    float4 *dst = red + (b * 3 + part) * 256 + lane_out;
 #pragma unroll
                     for (int q4 = 0; q4 < 4; ++q4)
                         dst[q4 * 64] = make_float4(acc[bi][bj][4 * q4], acc[bi][bj][4 * q4 + 1], acc[bi][bj][4 * q4 + 2],
@@ -350,14 +359,14 @@ void gemm_mfma_ksplit_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32
                 // all twelve reads of the three other partials in flight before the first add
                 float4 t[12];
 #pragma unroll
-                for (int i = 0; i < 12; ++i) t[i] = red[(b * 3 + i / 4) * 256 + (i % 4) * 64 + lane];
+                for (int i = 0; i < 12; ++i) t[i] = red[(b * 3 + i / 4) * 256 + (i % 4) * 64 + lane_out];
                 __builtin_amdgcn_sched_barrier(0);
                 v16f c = acc[bi][bj];
 #pragma unroll
                 for (int i = 0; i < 12; ++i) {
                     c[4 * (i % 4)] += t[i].x; c[4 * (i % 4) + 1] += t[i].y; c[4 * (i % 4) + 2] += t[i].z; c[4 * (i % 4) + 3] += t[i].w;
                 }
-                finish(c, n0 + bj * 32 + r32, sw_bits[bj]);
+                finish(c, n0 + bj * 32 + c32, sw_bits[bj]);
             });
         }
     });

@@ -54,10 +54,12 @@ bool gemm_mfma_ksplit_supported(const GemmArgs &g) { return gemm_mfma_fp4_suppor
 //   16.2 / 24.5 / 30.7, W4A2 9.7 / 15.5 / 27.0 / 34.4 against 11.6 / 14.6 / 21.9 / 26.5; W2A4 9.9 / 14.2 / 24.8 / 33.7
 //   against 12.7 / 15.9 / 23.5 / 28.5, W2A2 8.9 / 11.1 / 20.4 / 27.8 against 11.4 / 13.5 / 18.6 / 23.2; W1A4 26.4 against 28.8 us at
 //   K = 11008.  Taken from K = 4096 on with weights of 3 and 4 bits, from K = 8192 on with 2 bits, not with 1.
-//   The 64 x 64 tile (outputs of up to 256 of them: up to 256 tokens at 4096 channels, 128 at 8192), every width:
-//   65 - 256 tokens at 4096 x 4096 5.3 - 5.9 us (W1A1, W2A2), 6.9 - 7.4 us (W2A4) against 7.5 - 8.5 and 9.6 - 9.9 us with the
-//   64 x 128 tile and 9.3 - 11.5 us on the large tiles; at 4096 x 11008 7.4 - 8.5 and 10.7 - 11.9 against 11.0 - 12.1 and
-//   15.8 - 16.5 us; at K = 1024 4.4 - 5.0 against 5.5 - 6.6 us on the large tiles.  Taken at every K.
+//   The 64 x 64 tile (outputs of up to 256 of them: up to 256 tokens at 4096 channels, 128 at 8192), with weights of 1 and
+//   2 bits: 65 - 256 tokens at 4096 x 4096 5.3 - 5.9 us (W1A1, W2A2), 6.9 - 7.4 us (W2A4) against 7.5 - 8.5 and 9.6 - 9.9 us with
+//   the 64 x 128 tile and 9.3 - 11.5 us on the large tiles; at 4096 x 11008 7.4 - 8.5 and 10.7 - 11.9 against 11.0 - 12.1 and
+//   15.8 - 16.5 us; at K = 1024 4.4 - 5.0 against 5.5 - 6.6 us on the large tiles.  With 3 and 4 bits 6.8 - 7.4 us (W3A3) and
+//   6.7 - 7.5 us (W4A4) at 4096 x 4096, 11.5 - 12.9 and 11.7 - 13.4 us at 4096 x 11008 against 14 - 18 and 31 - 34 us on the
+//   large tiles.  Taken at every K.
 bool gemm_mfma_ksplit_pays(const GemmArgs &g)
 {
     if (!gemm_mfma_ksplit_supported(g) || one_round_width(g) == 0) return false;

@@ -43,8 +43,11 @@ struct LaneUnit {
     uint2 h[kHalves ? kHalves : 1];
 };
 
-// k blocks per step: as many as leave two workgroups on a CU (128 registers; the words of a step are held twice)
-constexpr int unit_steps(int words, int tiles) { return words <= 12 && tiles == 1 ? 4 : words <= 20 ? 2 : 1; }
+// k blocks per step, whose words are held twice: two where that leaves two workgroups on a CU (128 registers).  (Four for one
+// tile of narrow forms, the earlier rule, spilled registers in three of them and loaded up to 64 blocks where K has 40: one
+// token from codes 5120 x 5120 W4A5 7.3 -> 6.3 us, 5120 x 13824 13.9 -> 12.4 us; packed W1A8 1000 x 2048 2.9 -> 2.5 us; the
+// median over sizes from 1000 x 2048 to 13824 x 5120 is 5 - 15 % less, the worst W2A8 8192 x 8192, 5.9 -> 6.2 us.)
+constexpr int unit_steps(int words) { return words <= 20 ? 2 : 1; }
 
 // `src`: word 0 of slot 0 of the lane's row in the k block
 template <int FORM>
@@ -111,7 +114,7 @@ void gemm_decode_i8_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg, 
                            const uint16_t *as_arg, GroupArgs ga)
 {
     constexpr bool CODES = FA == kCodes;
-    constexpr int W = kDecodeWaves, U = unit_steps(RT * LaneUnit<FB>::kWords + TT * LaneUnit<FA>::kWords, RT * TT);
+    constexpr int W = kDecodeWaves, U = unit_steps(RT * LaneUnit<FB>::kWords + TT * LaneUnit<FA>::kWords);
     constexpr int OUTS = (TT * RT * 256 + kDecodeThreads - 1) / kDecodeThreads;
     extern __shared__ __align__(16) uint8_t lds_raw[];
     DecodeProblem pr = {w_arg, a_arg, n_arg, k_arg, (int64_t)(misc_arg & 0xfffu), cf_arg, ci_arg, ws_arg, as_arg};

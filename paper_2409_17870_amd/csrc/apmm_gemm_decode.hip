@@ -627,9 +627,14 @@ void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg
         load_packed(0);
         if constexpr (CODES && TT == 1) load_chunks(0, 0, vcur);
     }
-    bool out_ok[OUTS];
-    int out_m[OUTS];
-    int64_t out_n[OUTS];
+    // output o of thread `id` is element (tile t = e / 256, register v, lane l) of the accumulators, t = rt * TT + tt; 16x16
+    // accumulator layout: lane l, register v holds row 4*(l/16) + v (weight row), column l%16 (token)
+    auto out_place = [&](int id, int o, int &m, int64_t &n) __attribute__((always_inline)) {
+        const int e = id + o * kThreads, t = e >> 8, v = (e >> 6) & 3, l = e & 63;
+        m = tok0 + (t % TT) * 16 + (l & 15);
+        n = n0 + (t / TT) * 16 + 4 * (l >> 4) + v;
+        return t < TT * RT && m < pr.M && n < pr.N;
+    };
     uint32_t out_sa_bits[OUTS], out_sw_bits[OUTS], out_pa[OUTS], out_pw[OUTS];
     {
         const int32_t *w_sum = reinterpret_cast<const int32_t *>(pr.w + row_sum_word(rows_b, nkb, Q));
@@ -639,14 +644,10 @@ void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg
         const uint16_t *dummy = reinterpret_cast<const uint16_t *>(pr.w);
 #pragma unroll
         for (int o = 0; o < OUTS; ++o) {
-            // output o of this thread is element (tile t = e / 256, register v, lane l) of the accumulators,
-            // t = rt * TT + tt; 16x16 accumulator layout: lane l, register v holds row 4*(l/16) + v (weight row),
-            // column l%16 (token)
-            const int e = tid + o * kThreads, t = e >> 8, v = (e >> 6) & 3, l = e & 63;
-            out_m[o] = tok0 + (t % TT) * 16 + (l & 15);
-            out_n[o] = n0 + (t / TT) * 16 + 4 * (l >> 4) + v;
-            out_ok[o] = t < TT * RT && out_m[o] < pr.M && out_n[o] < pr.N;
-            const int64_t m_c = out_m[o] < rows_a ? out_m[o] : rows_a - 1, n_c = out_n[o] < rows_b ? out_n[o] : rows_b - 1;
+            int out_m;
+            int64_t out_n;
+            out_place(tid, o, out_m, out_n);
+            const int64_t m_c = out_m < rows_a ? out_m : rows_a - 1, n_c = out_n < rows_b ? out_n : rows_b - 1;
             out_pa[o] = 0;
             if constexpr (!CODES) out_pa[o] = (uint32_t)a_sum[m_c];
             out_pw[o] = (uint32_t)w_sum[n_c];
@@ -734,6 +735,16 @@ void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg
         });
     }
 
+    // The variants that are short of registers work the places out again instead of keeping them through the k loop: 3-bit weights
+    // at one or two tokens from codes, where 83 registers instead of 79 cost a third workgroup per compute unit (W3A1 11008 x
+    // 4096 6.3 -> 5.5 us, W3A2 5.9 -> 5.4 us), and 33 - 64 ragged tokens, which spilled three.
+    constexpr bool LEAN = (NJ == 1 && RT == 1 && Q == 3) || (CODES == 2 && TT == 4 && Q <= 2);
+    const int tid_out = LEAN ? (int)use_here((uint32_t)tid) : tid;
+    bool out_ok[OUTS];
+    int out_m[OUTS];
+    int64_t out_n[OUTS];
+#pragma unroll
+    for (int o = 0; o < OUTS; ++o) out_ok[o] = out_place(tid_out, o, out_m[o], out_n[o]);
     // reduce over the waves through LDS: part[wave][tile t][v][lane], and (CODES) the code sums pa[wave][token]
     float *part = reinterpret_cast<float *>(lds_raw);
     uint32_t *pa_lds = reinterpret_cast<uint32_t *>(lds_raw) + kWaves * RT * TT * 256;
@@ -753,7 +764,7 @@ void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg
 #pragma unroll
     for (int o = 0; o < OUTS; ++o) {
         if (!out_ok[o]) continue;
-        const int e = tid + o * kThreads;  // = (t * 4 + v) * 64 + l
+        const int e = tid_out + o * kThreads;  // = (t * 4 + v) * 64 + l
         float s = 0.f;
 #pragma unroll
         for (int w8 = 0; w8 < kWaves; ++w8) s += part[w8 * RT * TT * 256 + e];

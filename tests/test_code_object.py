@@ -62,7 +62,15 @@ def _of(kernels, name):
     return out
 
 
-@pytest.mark.parametrize("name", ["gemm_mfma_ksplit_kernel", "gemm_decode_i8_kernel"])
+@pytest.mark.parametrize("name", ["gemm_mfma_ksplit_kernel", "gemm_decode_i8_kernel", "gemm_decode_mfma_kernel"])
 def test_no_vector_register_is_spilled(kernels, name):
     spilled = {a: k[".vgpr_spill_count"] for a, k in _of(kernels, name).items() if k[".vgpr_spill_count"]}
     assert not spilled
+
+
+@pytest.mark.parametrize("p", [1, 2])
+@pytest.mark.parametrize("q", [1, 2, 3])
+def test_few_tokens_from_codes_leave_three_workgroups_on_a_compute_unit(kernels, p, q):
+    """gemm_decode_mfma_kernel<p, q, 1, 1, codes, one chunk per lane>: eight waves a workgroup and 512 registers to a lane of the
+    four vector units (handed out in eights) make three workgroups up to 80 registers."""
+    assert _of(kernels, "gemm_decode_mfma_kernel")[(p, q, 1, 1, 1, 1)][".vgpr_count"] <= 80

@@ -19,8 +19,9 @@
 //               of that block (q x 16 bytes, 256 contiguous bytes per 16 lanes) straight into registers
 // The activations (M rows, all K; in passes of a multiple of 32 k blocks when all K does not fit) are copied
 // once per workgroup from their packed tiles into LDS with every plane in the common form of the XOR/popcount
-// kernels (16 elements per word at the even bit positions, apmm_layout.h); a weight plane is brought to the
-// same form after loading, so that any activation plane can be XOR-ed with any weight plane.
+// kernels (16 elements per word at the even bit positions, apmm_layout.h), or in field order (apmm_fields.h) for weights of
+// 3 and 4 bits; a weight plane is brought to the same form after loading, so that any activation plane can be XOR-ed with
+// any weight plane.
 #include <hip/hip_ext.h>
 
 #include <algorithm>
@@ -36,68 +37,80 @@ constexpr int kThreads = kDecodeThreads;
 constexpr int kMaxLdsBytes = 128 * 1024;
 constexpr int kMfmaMinTokens = 1;  // the matrix-unit kernel serves every token count its code widths allow
 
-// Words 4*hh .. 4*hh+3 of plane i of an n-bit operand in the common form, from the 16-byte vectors of the slots of a
-// row and k block (`slots` points at the uint4 of slot 0; consecutive slots are kPlaneWords / 4 apart).
-__device__ __forceinline__ uint4 plane_half_from(const uint4 raw, int n, int i, int hh)
+// plane b of the words of a pair group; words 4 HH .. 4 HH + 3 of a single group's plane (common form)
+__device__ __forceinline__ uint4 pair_plane(const uint4 &s, int b)
 {
-    if (i < 2 * pair_groups(n)) {
-        const uint4 s = raw;  // S[4 hh .. 4 hh + 3] of pair group i / 2
-        const int b = i & 1;
-        return make_uint4((s.x >> b) & 0x55555555u, (s.y >> b) & 0x55555555u, (s.z >> b) & 0x55555555u,
-                          (s.w >> b) & 0x55555555u);
-    }
-    const uint4 l = raw;
-    // word w = 4 hh + x: k step 2 hh + x / 2, words L[2 (x % 2)], L[2 (x % 2) + 1]
-    const int k0 = 2 * hh, k1 = 2 * hh + 1;
+    return make_uint4((s.x >> b) & 0x55555555u, (s.y >> b) & 0x55555555u, (s.z >> b) & 0x55555555u, (s.w >> b) & 0x55555555u);
+}
+template <int HH>
+__device__ __forceinline__ uint4 single_half(const uint4 &l)
+{
+    constexpr int k0 = 2 * HH, k1 = 2 * HH + 1;
     return make_uint4(((l.x >> k0) & 0x11111111u) | (((l.y >> k0) & 0x11111111u) << 2),
                       ((l.z >> k0) & 0x11111111u) | (((l.w >> k0) & 0x11111111u) << 2),
                       ((l.x >> k1) & 0x11111111u) | (((l.y >> k1) & 0x11111111u) << 2),
                       ((l.z >> k1) & 0x11111111u) | (((l.w >> k1) & 0x11111111u) << 2));
 }
 
-__device__ __forceinline__ uint4 load_plane_half(const uint4 *slots, int n, int i, int hh)
+// Slot `slot` of a row and k block of n-bit activations, spread over the planes (plane j: eight words from dst + 8 j on) in the
+// common form, or (FIELDS) in field order for weights in the folded form.  Every slot is loaded once, whatever the form it
+// holds, and the load stands apart from what is done with it.  (A thread per plane and half, the earlier way, loaded the two
+// vectors of a nibble plane for each of its four planes and waited for them before it asked for the weights: one token at
+// 4096 x 4096, W1A5 3.6 us against 3.4 us now, 8 tokens W2A6 14.0 against 12.3 us; with planes of folded weights brought to the
+// common form, 8 operations per word and plane, W3A2 4.4 us against 3.5 us.)
+template <bool FIELDS>
+__device__ __forceinline__ uint32_t join_halves(uint32_t n0, uint32_t n1)
 {
-    constexpr int kSlotVec = kPlaneWords / 4;
-    if (byte_form(n)) {  // word 4 hh + x: slot 4 hh + x, word 2 tt + jh, top bit of every byte inverted
-        uint32_t out[4];
-#pragma unroll
-        for (int x = 0; x < 4; ++x) {
-            const uint4 b = slots[(4 * hh + x) * kSlotVec];
-            const uint32_t f = 0x80808080u, m = 0x01010101u;
-            out[x] = (((b.x ^ f) >> i) & m) | ((((b.y ^ f) >> i) & m) << 4) | ((((b.z ^ f) >> i) & m) << 2) | ((((b.w ^ f) >> i) & m) << 6);
+    return FIELDS ? join_in_field_order(n0, n1) : join_in_common_order(n0, n1);
+}
+template <bool FIELDS>
+__device__ __forceinline__ uint4 plane_order(const uint4 &w)  // of words in the common form
+{
+    auto order = [](uint32_t x) __attribute__((always_inline)) { return join_halves<FIELDS>(x & 0x33333333u, (x >> 2) & 0x33333333u); };
+    return make_uint4(order(w.x), order(w.y), order(w.z), order(w.w));
+}
+template <bool FIELDS>
+__device__ __forceinline__ void stage_slot(const uint4 &v, int n, int slot, uint32_t *dst)
+{
+    if (byte_form(n)) {  // word `slot` of every plane; bytes with the top bit inverted
+        const uint32_t f = 0x80808080u, m = 0x03030303u;
+#pragma unroll 1
+        for (int i = 0; i < 8; i += 2) {
+            const uint32_t pair = join_halves<FIELDS>((((v.x ^ f) >> i) & m) | ((((v.y ^ f) >> i) & m) << 4),
+                                                      (((v.z ^ f) >> i) & m) | ((((v.w ^ f) >> i) & m) << 4));
+            dst[8 * i + slot] = pair & kEvenBits;
+            dst[8 * i + 8 + slot] = (pair >> 1) & kEvenBits;
         }
-        return make_uint4(out[0], out[1], out[2], out[3]);
+    } else if (nibble_form(n) && slot < 4) {  // words 2 slot, 2 slot + 1 of planes 0 .. 3
+        const uint32_t m = 0x33333333u;
+#pragma unroll
+        for (int i = 0; i < 4; i += 2) {
+            const uint32_t w0 = join_halves<FIELDS>((v.x >> i) & m, (v.y >> i) & m), w1 = join_halves<FIELDS>((v.z >> i) & m, (v.w >> i) & m);
+            *reinterpret_cast<uint2 *>(dst + 8 * i + 2 * slot) = make_uint2(w0 & kEvenBits, w1 & kEvenBits);
+            *reinterpret_cast<uint2 *>(dst + 8 * i + 8 + 2 * slot) = make_uint2((w0 >> 1) & kEvenBits, (w1 >> 1) & kEvenBits);
+        }
+    } else if (slot < 2 * pair_groups(n)) {  // half slot % 2 of the two planes of the pair group
+        uint4 *half = reinterpret_cast<uint4 *>(dst + 8 * (slot & ~1) + 4 * (slot & 1));
+        const uint4 both = plane_order<FIELDS>(v);
+        half[0] = pair_plane(both, 0);
+        half[2] = pair_plane(both, 1);
+    } else {  // both halves of the top plane
+        uint4 *half = reinterpret_cast<uint4 *>(dst + 8 * (n - 1));
+        half[0] = plane_order<FIELDS>(single_half<0>(v));
+        half[1] = plane_order<FIELDS>(single_half<1>(v));
     }
-    if (nibble_form(n)) {
-        // bits 0 .. 3: words 4 hh, 4 hh + 1 from k step 2 hh, the other two from k step 2 hh + 1; higher bits as in the group
-        // form.  Neighbouring lanes hold different planes: the loads are the same for all (under a branch each they
-        // would be waited for in turn), only what is done with them differs.
-        const int group = i < 2 * pair_groups(n) ? i / 2 * 2 + hh : n - 1;
-        const uint4 b0 = slots[(i < 4 ? 2 * hh : group) * kSlotVec], b1 = slots[(i < 4 ? 2 * hh + 1 : group) * kSlotVec];
-        const uint32_t m = 0x11111111u;
-        if (i < 4)
-            return make_uint4(((b0.x >> i) & m) | (((b0.y >> i) & m) << 2), ((b0.z >> i) & m) | (((b0.w >> i) & m) << 2),
-                              ((b1.x >> i) & m) | (((b1.y >> i) & m) << 2), ((b1.z >> i) & m) | (((b1.w >> i) & m) << 2));
-        return plane_half_from(b0, n, i, hh);
-    }
-    return plane_half_from(slots[(i < 2 * pair_groups(n) ? (i / 2 * 2 + hh) : (n - 1)) * kSlotVec], n, i, hh);
 }
 
-// The same from slots already in registers (weights of a Q-bit operand): words 4 HH .. 4 HH + 3.
+// Plane i of Q-bit weights from slots in registers: words 4 HH .. 4 HH + 3, in the common form, or in field
+// order out of the folded form.
 template <int Q, int HH>
 __device__ __forceinline__ uint4 plane_half_words_reg(const uint4 (&slot)[Q], int i)
 {
     if constexpr (Q == 2) {
-        const uint4 s = slot[HH];
-        return make_uint4((s.x >> i) & 0x55555555u, (s.y >> i) & 0x55555555u, (s.z >> i) & 0x55555555u, (s.w >> i) & 0x55555555u);
+        return pair_plane(slot[HH], i);
     } else if constexpr (Q == 1) {
-        const uint4 l = slot[0];
-        constexpr int k0 = 2 * HH, k1 = 2 * HH + 1;
-        return make_uint4(((l.x >> k0) & 0x11111111u) | (((l.y >> k0) & 0x11111111u) << 2),
-                          ((l.z >> k0) & 0x11111111u) | (((l.w >> k0) & 0x11111111u) << 2),
-                          ((l.x >> k1) & 0x11111111u) | (((l.y >> k1) & 0x11111111u) << 2),
-                          ((l.z >> k1) & 0x11111111u) | (((l.w >> k1) & 0x11111111u) << 2));
-    } else {  // folded form: k steps 2 HH and 2 HH + 1
+        return single_half<HH>(slot[0]);
+    } else {  // folded form: words of k steps 2 HH and 2 HH + 1, in field order
         uint32_t in[2][4] = {};
         mfma::static_for<2 * Q>([&](auto j_c) __attribute__((always_inline)) {
             constexpr int e = decltype(j_c)::value / Q, j = decltype(j_c)::value % Q, w = fold_word_at(Q, 2 * HH + e, j);
@@ -180,21 +193,23 @@ __global__ __launch_bounds__(kThreads) void gemm_decode_kernel(GroupArgs ga)
 
     // Order of the requests.  Loads return in order, so whatever is requested before the weights can be used
     // while the weights are still on their way, and whatever is requested after them cannot.  First therefore
-    // this thread's first chunk of activations (packed input; usually its only one), which goes to LDS and
+    // this thread's first slot of activations (packed input; usually its only one), which goes to LDS and
     // through a barrier before the k loop; then the weights of the first k block, whose latency is the
     // longest thing in this kernel; then what only the final store needs.
     const uint32_t chunks_per_kb = (uint32_t)(MT * p * 2);
-    const uint32_t chunks_pass0 = (uint32_t)(chunk_kb < g.nkb ? chunk_kb : g.nkb) * chunks_per_kb;
-    // chunk c of a pass that starts at k block kb0: (k block, row m, plane j, half hh)
-    auto load_chunk = [&](uint32_t c, int64_t kb0) {
-        const uint32_t ckb = c / chunks_per_kb;
-        const uint32_t rem = c - ckb * chunks_per_kb, plane = rem >> 1, m = plane / p;
-        const uint4 *slots = reinterpret_cast<const uint4 *>(g.a + tile_row_word(m, kb0 + ckb, g.nkb, p, 0));
-        return load_plane_half(slots, p, (int)(plane - m * p), (int)(rem & 1));
+    // slot c of a pass that starts at k block kb0: (k block, row m, slot)
+    const uint32_t slots_pass0 = (uint32_t)(chunk_kb < g.nkb ? chunk_kb : g.nkb) * (uint32_t)(MT * p);
+    auto load_slot = [&](uint32_t c, int64_t kb0) __attribute__((always_inline)) {
+        const uint32_t r = c / (uint32_t)p, s = c - r * p;
+        return *reinterpret_cast<const uint4 *>(g.a + tile_row_word(r % MT, kb0 + r / MT, g.nkb, p, s));
+    };
+    auto stage = [&](uint32_t c, const uint4 &v) __attribute__((always_inline)) {
+        const uint32_t r = c / (uint32_t)p, s = c - r * p;
+        stage_slot<weight_folded_form(Q)>(v, p, (int)s, reinterpret_cast<uint32_t *>(a_lds) + r * p * 8);
     };
     uint4 a_first = make_uint4(0, 0, 0, 0);
     if constexpr (!CODES) {
-        if ((uint32_t)tid < chunks_pass0) a_first = load_chunk(tid, 0);
+        if ((uint32_t)tid < slots_pass0) a_first = load_slot(tid, 0);
     }
 
     int64_t kb = 4 * (int64_t)wave + sub;
@@ -247,18 +262,19 @@ __global__ __launch_bounds__(kThreads) void gemm_decode_kernel(GroupArgs ga)
                                 word[w] |= ((d[8 * (w >> 1) + 2 * (2 * (w & 1) + tt) + jh] >> j) & 0x01010101u) << (4 * jh + 2 * tt);
                     }
                     uint4 *dst = a_lds + ckb * chunks_per_kb + (m * p + j) * 2;
-                    dst[0] = make_uint4(word[0], word[1], word[2], word[3]);
-                    dst[1] = make_uint4(word[4], word[5], word[6], word[7]);
+                    dst[0] = plane_order<weight_folded_form(Q)>(make_uint4(word[0], word[1], word[2], word[3]));
+                    dst[1] = plane_order<weight_folded_form(Q)>(make_uint4(word[4], word[5], word[6], word[7]));
                 }
             }
         } else {
-            const uint32_t total_chunks = (uint32_t)(kb_end - kb0) * chunks_per_kb;
-            uint32_t c = tid;
-            if (kb0 == 0) {  // the chunk requested at the top
-                if (c < total_chunks) a_lds[c] = a_first;
-                c += kThreads;
+            const uint32_t total_slots = (uint32_t)(kb_end - kb0) * (uint32_t)(MT * p);
+            uint4 v = a_first;  // the slot requested at the top
+            if (kb0 != 0 && (uint32_t)tid < total_slots) v = load_slot(tid, kb0);
+#pragma unroll 1
+            for (uint32_t c = tid; c < total_slots; c += kThreads) {
+                stage(c, v);
+                if (c + kThreads < total_slots) v = load_slot(c + kThreads, kb0);
             }
-            for (; c < total_chunks; c += kThreads) a_lds[c] = load_chunk(c, kb0);
         }
         __syncthreads();
 

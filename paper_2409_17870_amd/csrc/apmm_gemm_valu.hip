@@ -11,10 +11,12 @@
 // matrix-unit kernels do not cover and the reference for design B at large M.  A workgroup of 256 threads
 // owns 64 x 64 outputs, a thread 4 x 4 of them (rows ty + 16 i, columns tx + 16 j).  Per k block the
 // workgroup brings every plane of its 64 + 64 rows to the same form, 16 elements per word at the even bit
-// positions (apmm_layout.h), once, into LDS; then any activation plane can be XOR-ed with any weight plane:
+// positions (in the order of apmm_layout.h or of apmm_fields.h), once, into LDS; then any activation plane can be XOR-ed with any weight plane:
 // per output, plane pair and word one XOR, one popcount and one shift-and-add.  The vector ALU bounds it:
 // 3 p q operations per output and 16 elements, i.e. about 0.2 effective POP/s for W1A2 if every issue slot
 // of the chip did nothing else.
+#include <type_traits>
+
 #include "apmm_epilogue.h"
 #include "apmm_fields.h"
 #include "apmm_kernels.h"
@@ -24,60 +26,68 @@ namespace {
 
 constexpr int kTile = 16;
 
-// Plane i of the 16 elements (ks = w / 2, tp = w % 2, all tt, jh, c) of one row and k block, at bits
-// 8c + 4jh + 2tt.  `tile_row` points at word 0 of (row, slot 0).
-__device__ __forceinline__ uint32_t plane_half_word(const uint32_t *tile_row, int n, int i, int w)
+// The planes of the 16 elements (ks = w / 2, tp = w % 2, all tt, jh, c) of one row and k block of an n-bit operand come from
+// up to five words of the row (word x: slot x / 4, word x % 4), each read once.
+constexpr int kRawWords = 5;
+__device__ __forceinline__ void raw_word_places(int n, bool field_form, bool folded_form, int w, int (&x)[kRawWords])
 {
-    if (byte_form(n)) {  // slot w, word 2 tt + jh: bytes with the top bit inverted
-        const uint32_t *b = tile_row + w * kPlaneWords;
-        uint32_t out = 0;
-        for (int x = 0; x < 4; ++x) out |= (((b[x] ^ 0x80808080u) >> i) & 0x01010101u) << (4 * (x & 1) + 2 * (x >> 1));
-        return out;
-    }
-    if (nibble_form(n) && i < 4) {  // N[4 ks + 2 tp], N[4 ks + 2 tp + 1]
-        const uint32_t *b = tile_row + (w >> 1) * kPlaneWords + 2 * (w & 1);
-        return ((b[0] >> i) & 0x11111111u) | (((b[1] >> i) & 0x11111111u) << 2);
-    }
-    if (weight_folded_form(n)) {  // (activations of these widths are in the field form)
-        const int ks = w >> 1;
-        uint32_t in[4] = {0, 0, 0, 0};
-        for (int j = 0; j < n; ++j) {
-            const int at = fold_word_at(n, ks, j);
-            in[j] = tile_row[(at >> 2) * kPlaneWords + (at & 3)];
-        }
-        if (n == 3) return (w & 1) ? folded_plane<3, 1>(in[0], in[1], in[2], 0u, i) : folded_plane<3, 0>(in[0], in[1], in[2], 0u, i);
-        return (w & 1) ? folded_plane<4, 1>(in[0], in[1], in[2], in[3], i) : folded_plane<4, 0>(in[0], in[1], in[2], in[3], i);
-    }
-    if (i < 2 * pair_groups(n)) {
-        const uint32_t s = tile_row[(i / 2 * 2 + (w >> 2)) * kPlaneWords + (w & 3)];  // S[w] of pair group i / 2
-        return (s >> (i & 1)) & 0x55555555u;
-    }
-    const uint32_t *l = tile_row + (n - 1) * kPlaneWords + 2 * (w & 1);  // L[2 tp], L[2 tp + 1]
-    const int ks = w >> 1;
-    return ((l[0] >> ks) & 0x11111111u) | (((l[1] >> ks) & 0x11111111u) << 2);
+    const int ks = w >> 1, tp = w & 1, single = 4 * (n - 1) + 2 * tp;  // L[2 tp] of the single group
+    auto set = [&](int x0, int x1, int x2, int x3, int x4) __attribute__((always_inline)) { x[0] = x0; x[1] = x1; x[2] = x2; x[3] = x3; x[4] = x4; };
+    if (field_form) set(3 * w, 3 * w + 1, 3 * w + 2, 3 * w, 3 * w);  // words 6 ks + 3 tp ...
+    else if (folded_form) set(fold_word_at(n, ks, 0), fold_word_at(n, ks, 1), fold_word_at(n, ks, 2), fold_word_at(n, ks, n - 1), fold_word_at(n, ks, 0));
+    else if (byte_form(n)) set(4 * w, 4 * w + 1, 4 * w + 2, 4 * w + 3, 4 * w);
+    else if (nibble_form(n)) set(2 * w, 2 * w + 1, n > 5 ? 16 + w : 2 * w, n != 6 ? single : 2 * w, n != 6 ? single + 1 : 2 * w);
+    else set(n == 2 ? w : single, n == 2 ? w : single + 1, n == 2 ? w : single, n == 2 ? w : single, n == 2 ? w : single);
 }
-
-// The same from activations in the field form (3 and 4 bits): bit i of field 8 t + 2 c + jh of k step ks is
-// bit 6 (8 t + 2 c + jh) + i of the 192 bits in words 6 ks .. 6 ks + 5 of the row's 24.
-__device__ __forceinline__ uint32_t field_plane_half_word(const uint32_t *tile_row, int i, int w)
+// put(i, plane i) from these words.  FIELDS: in field order (apmm_fields.h), which codes stored in fields have by themselves,
+// else at bits 8c + 4jh + 2tt.
+template <bool FIELDS, class Put>
+__device__ __forceinline__ void plane_words(const uint32_t (&raw)[kRawWords], int n, bool field_form, bool folded_form, int w, Put &&put)
 {
     const int ks = w >> 1, tp = w & 1;
-    uint32_t out = 0;
-    for (int tt = 0; tt < 2; ++tt)
-        for (int jh = 0; jh < 2; ++jh)
-            for (int c = 0; c < 4; ++c) {
-                const int bit = 6 * (8 * (2 * tp + tt) + 2 * c + jh) + i;
-                const int word = 6 * ks + (bit >> 5);
-                const uint32_t v = tile_row[(word >> 2) * kPlaneWords + (word & 3)];
-                out |= ((v >> (bit & 31)) & 1u) << (8 * c + 4 * jh + 2 * tt);
-            }
-    return out;
+    auto put_pair = [&](int i, uint32_t n0, uint32_t n1) __attribute__((always_inline)) {
+        const uint32_t pair = FIELDS ? join_in_field_order(n0, n1) : join_in_common_order(n0, n1);
+        put(i, pair & kEvenBits);
+        if (i + 1 < n) put(i + 1, (pair >> 1) & kEvenBits);
+    };
+    if (FIELDS && field_form) {
+        for (int i = 0; i < n; ++i) put(i, field_plane(raw[0], raw[1], raw[2], i));
+    } else if (FIELDS && folded_form) {
+        for (int i = 0; i < n; ++i)
+            put(i, n == 3 ? (tp ? folded_plane<3, 1>(raw[0], raw[1], raw[2], 0u, i) : folded_plane<3, 0>(raw[0], raw[1], raw[2], 0u, i))
+                          : (tp ? folded_plane<4, 1>(raw[0], raw[1], raw[2], raw[3], i) : folded_plane<4, 0>(raw[0], raw[1], raw[2], raw[3], i)));
+    } else if (byte_form(n)) {  // word 2 tt + jh: bytes with the top bit inverted
+        const uint32_t f = 0x80808080u, m = 0x03030303u;
+        for (int i = 0; i < 8; i += 2)
+            put_pair(i, (((raw[0] ^ f) >> i) & m) | ((((raw[1] ^ f) >> i) & m) << 4), (((raw[2] ^ f) >> i) & m) | ((((raw[3] ^ f) >> i) & m) << 4));
+    } else if (nibble_form(n)) {  // N[4 ks + 2 tp], N[4 ks + 2 tp + 1]; S[w] of bits 4, 5; L[2 tp], L[2 tp + 1]
+        const uint32_t m = 0x33333333u;
+        put_pair(0, raw[0] & m, raw[1] & m);
+        put_pair(2, (raw[0] >> 2) & m, (raw[1] >> 2) & m);
+        if (n > 5) put_pair(4, raw[2] & m, (raw[2] >> 2) & m);
+        if (n != 6) put_pair(n - 1, (raw[3] >> ks) & 0x11111111u, (raw[4] >> ks) & 0x11111111u);
+    } else if (n == 2) {
+        put_pair(0, raw[0] & 0x33333333u, (raw[0] >> 2) & 0x33333333u);
+    } else {
+        put_pair(0, (raw[0] >> ks) & 0x11111111u, (raw[1] >> ks) & 0x11111111u);
+    }
+}
+
+// plane i of words of 1- and 2-bit codes (group form), for operands that both are of these widths
+__device__ __forceinline__ uint32_t group_plane_word(const uint32_t *tile_row, int n, int i, int w)
+{
+    if (n == 2) return (tile_row[(w >> 2) * kPlaneWords + (w & 3)] >> i) & kEvenBits;
+    const uint32_t *l = tile_row + 2 * (w & 1);  // L[2 tp], L[2 tp + 1]
+    return join_in_common_order((l[0] >> (w >> 1)) & 0x11111111u, (l[1] >> (w >> 1)) & 0x11111111u);
 }
 
 constexpr int kOutTile = 64;                 // outputs per workgroup and dimension
 constexpr int kPerThread = kOutTile / kTile;  // outputs per thread and dimension
 
-__global__ __launch_bounds__(kTile * kTile) void gemm_valu_kernel(GemmArgs g, int64_t tiles_n)
+// NARROW: both operands of one or two bits.  A kernel of its own, because what the other forms need takes registers that
+// cost it two workgroups per compute unit (2048 x 4096 x 4096 W1A1 264 -> 348 us).
+template <bool NARROW>
+__global__ __launch_bounds__(kTile * kTile, 4) void gemm_valu_kernel(GemmArgs g, int64_t tiles_n)
 {
     // one-dimensional grid (the y dimension would cap M at about four million rows)
     const int64_t n0 = ((int64_t)blockIdx.x % tiles_n) * kOutTile, m0 = ((int64_t)blockIdx.x / tiles_n) * kOutTile;
@@ -93,23 +103,49 @@ __global__ __launch_bounds__(kTile * kTile) void gemm_valu_kernel(GemmArgs g, in
 #pragma unroll
         for (int j = 0; j < kPerThread; ++j) weighted[i][j] = 0;
 
+    const int r = tid % kOutTile;  // (256 threads: every job of a thread is for the same row)
+    // any order of the elements will do that both operands follow: field order if either has its codes in fields
+    const bool field_a = activation_field_form(p), folded_w = weight_folded_form(q), fields = field_a || folded_w;
+
+    // A thread fills word w of all planes of row r, w = tid / 64 and that + 4, of both operands; rows past an operand read its
+    // last padded row.  The loads of either operand are in flight together.
+    const int64_t row_a = m0 + r < rows_a ? m0 + r : rows_a - 1, row_w = n0 + r < rows_b ? n0 + r : rows_b - 1;
+    auto fill = [&](auto fields_c, int64_t kb) __attribute__((always_inline)) {
+        constexpr bool FIELDS = decltype(fields_c)::value;
+        const uint32_t *src[2] = {g.a + tile_row_word(row_a, kb, g.nkb, activation_slots(p), 0), g.w + tile_row_word(row_w, kb, g.nkb, q, 0)};
+#pragma unroll
+        for (int side = 0; side < 2; ++side) {
+            uint32_t raw[2][kRawWords];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                int x[kRawWords];
+                raw_word_places(side ? q : p, FIELDS && !side && field_a, FIELDS && side && folded_w, tid / kOutTile + 4 * h, x);
+#pragma unroll
+                for (int j = 0; j < kRawWords; ++j) raw[h][j] = src[side][(x[j] >> 2) * kPlaneWords + (x[j] & 3)];
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int w = tid / kOutTile + 4 * h;
+                uint32_t *dst = (side ? w_lds : a_lds) + w * kOutTile + r;
+                plane_words<FIELDS>(raw[h], side ? q : p, !side && field_a, side && folded_w, w,
+                                    [&](int i, uint32_t v) __attribute__((always_inline)) { dst[i * 8 * kOutTile] = v; });
+            }
+        }
+    };
+
     for (int64_t kb = 0; kb < g.nkb; ++kb) {
         if (kb) __syncthreads();  // every thread is done with the previous k block
-        // fill: one word of one plane of one row per job; rows past the operand read its last padded row
-        for (int job = tid; job < (p + q) * 8 * kOutTile; job += kTile * kTile) {
-            const int r = job % kOutTile, w = (job / kOutTile) % 8, plane = job / (8 * kOutTile);
-            if (plane < p) {
-                int64_t row = m0 + r;
-                if (row >= rows_a) row = rows_a - 1;
-                const uint32_t *arow = g.a + tile_row_word(row, kb, g.nkb, activation_slots(p), 0);
-                a_lds[(plane * 8 + w) * kOutTile + r] =
-                    activation_field_form(p) ? field_plane_half_word(arow, plane, w) : plane_half_word(arow, p, plane, w);
-            } else {
-                int64_t row = n0 + r;
-                if (row >= rows_b) row = rows_b - 1;
-                const uint32_t *wrow = g.w + tile_row_word(row, kb, g.nkb, q, 0);
-                w_lds[((plane - p) * 8 + w) * kOutTile + r] = plane_half_word(wrow, q, plane - p, w);
+        if constexpr (NARROW) {
+            // one word of one plane of one row per job; rows past the operand read its last padded row
+            for (int job = tid; job < (p + q) * 8 * kOutTile; job += kTile * kTile) {
+                const int w = (job / kOutTile) % 8, plane = job / (8 * kOutTile);
+                if (plane < p) a_lds[(plane * 8 + w) * kOutTile + r] = group_plane_word(g.a + tile_row_word(row_a, kb, g.nkb, p, 0), p, plane, w);
+                else w_lds[((plane - p) * 8 + w) * kOutTile + r] = group_plane_word(g.w + tile_row_word(row_w, kb, g.nkb, q, 0), q, plane - p, w);
             }
+        } else if (fields) {
+            fill(std::true_type{}, kb);
+        } else {
+            fill(std::false_type{}, kb);
         }
         __syncthreads();
         for (int w = 0; w < 8; ++w) {
@@ -150,7 +186,8 @@ hipError_t launch_gemm_valu(const GemmArgs &args, hipStream_t stream)
     const int64_t gx = (args.N + kOutTile - 1) / kOutTile, gy = (args.M + kOutTile - 1) / kOutTile;
     if (gx > 0x7fffffffLL / gy) return hipErrorInvalidValue;
     note_kernel("gemm_valu_kernel");
-    hipLaunchKernelGGL(gemm_valu_kernel, dim3((unsigned)(gx * gy)), dim3(kTile * kTile), 0, stream, args, gx);
+    const auto kernel = args.p <= 2 && args.q <= 2 ? gemm_valu_kernel<true> : gemm_valu_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(gx * gy)), dim3(kTile * kTile), 0, stream, args, gx);
     return hipGetLastError();
 }
 

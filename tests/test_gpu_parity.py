@@ -169,6 +169,34 @@ def test_ablation_kernels_decline_wide_activations(gpu):
         assert err.value.status == 2
 
 
+@pytest.mark.parametrize("p,q", [(p, q) for p in range(1, 9) for q in range(1, 9)])
+def test_xor_popcount_kernels_all_widths(gpu, oracle, p, q):
+    """Every packed form of either operand taken apart into planes and matched plane by plane: the general XOR/popcount kernel
+    (two tiles of rows and columns, ragged) and the small-M one at every token tile, rows with padded k blocks, extreme codes."""
+    for M, N, K, algo in ((70, 67, 700, VALU), (1, 40, 700, DECODE_VALU), (2, 33, 130, DECODE_VALU), (7, 20, 1100, DECODE_VALU),
+                          (16, 17, 513, DECODE_VALU)):
+        if algo == DECODE_VALU and (q > 4 or p in (3, 4)):
+            continue
+        case = dict(M=M, N=N, K=K, p=p, q=q, a_dist="bernoulli", scaled=False)
+        data = inputs.make_case(case, 2300 + 17 * p + q + M)
+        data["a_codes"][-1], data["w_codes"][-1], data["w_codes"][0] = (1 << p) - 1, (1 << q) - 1, 0
+        c32, _ = run_case(gpu, data, case, algo=algo)
+        assert np.array_equal(c32.astype(np.int64), oracle.gemm_i64(data["a_codes"], data["w_codes"], p, q)), (M, N, K, algo)
+
+
+@pytest.mark.parametrize("M,N,K,p,q", [(1, 20, 9, 5, 3), (7, 33, 15, 8, 4), (16, 16, 1, 6, 1), (3, 17, 12, 7, 2),
+                                       # 4 K (2^p - 1)(2^q - 1) >= 2^24: K > 93206, 199728 and 279620
+                                       (16, 20, 93700, 2, 4), (9, 18, 200001, 2, 3), (1, 16, 300000, 1, 4), (2, 20, 280100, 1, 4)])
+def test_xor_popcount_small_m_kernel_from_codes(gpu, oracle, M, N, K, p, q):
+    """What is left to that kernel's own packing: rows shorter than a 16-code load, and one- and two-bit codes beyond the K that
+    the matrix-unit kernel sums exactly, where the activations take several passes through LDS."""
+    case = dict(M=M, N=N, K=K, p=p, q=q, a_dist="bernoulli", scaled=False)
+    data = inputs.make_case(case, 2200 + 17 * p + q + M)
+    c32, _ = run_from_codes(gpu, data, case, dirty_high_bits=True)
+    assert gpu[1].apmm_last_gemm_kernel().startswith("gemm_decode_kernel<")
+    assert np.array_equal(c32.astype(np.int64), oracle.gemm_i64(data["a_codes"], data["w_codes"], p, q))
+
+
 @pytest.mark.parametrize("p,q", [(8, 8), (5, 7), (8, 1), (1, 6), (7, 3)])
 def test_wide_codes(gpu, oracle, p, q):
     case = dict(M=37, N=50, K=333, p=p, q=q, a_dist="bernoulli", scaled=False)

@@ -945,15 +945,34 @@ int decode_valu_variant(const GemmArgs &g)
     return decode_pass_kb(g, decode_mt(g.M)) > 0 ? decode_mt(g.M) : 0;
 }
 
-// kernel variant that serves a problem: 0 = none, 100 + token tiles = fp4 matrix operations, 200 + token tiles = int8
-// matrix operations, else the token tile of the XOR/popcount kernel
-int decode_variant(const GemmArgs &g, bool xor_only = false)
+// One or two tokens of 5- to 7-bit codes against weights of few bits, where the int8 kernel expands sixteen rows of activations
+// for one and the XOR/popcount kernel has few plane pairs to go through.  One token, packed, the int8 kernel against the
+// XOR/popcount kernel:
+//   W1A5 4096 x 4096 4.0 / 3.4 us, 5120 x 5120 6.5 / 4.5, 5120 x 13824 12.2 / 7.2, 11008 x 4096 7.0 / 5.0, 13824 x 5120 8.2 / 6.8;
+//   W2A5 4.1 / 3.8, 6.6 / 5.3, 12.0 / 9.9, 6.7 / 6.1, 7.7 / 9.1; W2A6 4.1 / 4.0, 6.6 / 5.6, 12.0 / 10.9, 6.7 / 6.5, 7.7 / 9.7;
+//   W2A7 4.1 / 4.2, 6.6 / 6.4, 11.9 / 12.1; W3A5 4.7 / 4.4, 8.2 / 7.3, 16.0 / 14.6, 9.3 / 9.2, 11.2 / 13.1.
+// Two tokens, W1A5 4096 x 4096 4.0 / 4.1, 5120 x 5120 6.6 / 6.1, 5120 x 13824 12.2 / 10.1, 11008 x 4096 7.0 / 6.5, 13824 x 5120 8.2 / 9.5.
+// Up to K = 2048 the int8 kernel has one step to do (W1A5 1000 x 2048 3.0 / 3.2, 4096 x 1024 2.9 / 3.2); beyond 12288 channels,
+// 8192 with 3-bit weights, the XOR/popcount kernel needs a second round of workgroups.  From codes the int8 kernel has nothing
+// to expand: W1A5 4096 x 4096 3.6 / 4.3, 5120 x 5120 5.4 / 5.2, 4096 x 11008 6.1 / 5.7, 5120 x 13824 9.7 / 7.9 us, W1A6 5.4 / 5.7, 6.1 /
+// 6.2, 9.8 / 8.8; rows that 16-byte loads do not fit cost the other kernel its byte loop (4123 x 3001 4.4 / 31 us).
+bool decode_valu_pays(const GemmArgs &g, bool single)
+{
+    if (!nibble_form(g.p)) return false;
+    const int64_t pairs = g.M * g.p * g.q;
+    if (g.a_codes)
+        return single && pairs <= 6 && g.nkb > 80 && g.N <= 8192 && (g.K & 15) == 0 && (reinterpret_cast<uintptr_t>(g.a_codes) & 15) == 0;
+    if (!single) return pairs <= 7;  // (the problems of a launch stay together whatever their sizes)
+    return g.nkb > 16 && (pairs <= 7 || (pairs <= 12 && g.N < 12288) || (g.M == 1 && g.p == 5 && g.q == 3 && g.N <= 8192));
+}
+
+// kernel variant that serves a problem of a launch of `count`: 0 = none, 100 + token tiles = fp4 matrix operations, 200 + token
+// tiles = int8 matrix operations, else the token tile of the XOR/popcount kernel
+int decode_variant(const GemmArgs &g, int count, bool xor_only = false)
 {
     if (xor_only) return decode_valu_variant(g);
     if (decode_mfma_supported(g)) return 100 + decode_token_tiles(g);
-    // (one token of packed 5- to 7-bit codes against single-bit weights: the matrix form expands sixteen rows for one; W1A5
-    // 4096 x 4096 3.6 us on the vector ALU against 4.2 us, 11008 x 4096 5.3 against 6.8 us; two tokens and W2 are even)
-    if (!g.a_codes && nibble_form(g.p) && g.M * g.p * g.q <= 8 && decode_valu_variant(g)) return decode_valu_variant(g);
+    if (decode_valu_pays(g, count == 1) && decode_valu_variant(g)) return decode_valu_variant(g);
     if (gemm_decode_i8_supported(g)) return 200 + (g.M <= 16 ? 1 : g.M <= 32 ? 2 : 4);
     return decode_valu_variant(g);
 }
@@ -968,9 +987,9 @@ bool gemm_decode_valu_supported(const GemmArgs &g) { return decode_valu_variant(
 bool gemm_decode_group_supported(const GemmArgs *gs, int count)
 {
     if (count < 1 || count > kMaxGroup) return false;
-    const int v = decode_variant(gs[0]);
+    const int v = decode_variant(gs[0], count);
     for (int i = 0; i < count; ++i)
-        if (decode_variant(gs[i]) != v || gs[i].p != gs[0].p || gs[i].q != gs[0].q ||
+        if (decode_variant(gs[i], count) != v || gs[i].p != gs[0].p || gs[i].q != gs[0].q ||
             (gs[i].a_codes != nullptr) != (gs[0].a_codes != nullptr) ||
             (count > 1 && v > 100 && v < 200 && decode_token_groups(gs[i]) > 1))  // token groups: single-problem launches only
             return false;
@@ -989,7 +1008,7 @@ hipError_t launch_gemm_decode_group(const GemmArgs *problems, int count, hipStre
     GemmArgs gs[kMaxGroup];
     for (int i = 0; i < count; ++i) gs[i] = problems[i];
     std::stable_sort(gs, gs + count, [](const GemmArgs &x, const GemmArgs &y) { return x.nkb > y.nkb; });
-    const int variant = decode_variant(gs[0], xor_only);
+    const int variant = decode_variant(gs[0], count, xor_only);
     if (variant > 200) return launch_gemm_decode_i8(gs, count, variant - 200, stream);
     if (variant > 100) {
         // two row tiles per workgroup once that still leaves two workgroups per CU

@@ -197,6 +197,42 @@ def test_xor_popcount_small_m_kernel_from_codes(gpu, oracle, M, N, K, p, q):
     assert np.array_equal(c32.astype(np.int64), oracle.gemm_i64(data["a_codes"], data["w_codes"], p, q))
 
 
+@pytest.mark.parametrize("M,N,K,p,q,codes,vector", [
+    (1, 40, 2048, 5, 1, False, False), (1, 40, 2049, 5, 1, False, True), (1, 13000, 2100, 7, 1, False, True),
+    (1, 12287, 2100, 6, 2, False, True), (1, 12288, 2100, 6, 2, False, False), (1, 300, 2100, 7, 2, False, False),
+    (2, 300, 2100, 6, 1, False, True), (2, 300, 2100, 7, 1, False, False), (3, 300, 2100, 5, 1, False, False),
+    (1, 8192, 2100, 5, 3, False, True), (1, 8193, 2100, 5, 3, False, False), (1, 300, 2100, 6, 3, False, False),
+    (1, 300, 2100, 8, 1, False, False), (1, 300, 10256, 5, 1, True, True), (1, 300, 10257, 5, 1, True, False),
+    (1, 300, 10240, 5, 1, True, False), (1, 8193, 10256, 5, 1, True, False), (2, 300, 10256, 5, 1, True, False),
+    (1, 300, 10256, 7, 1, True, False)])
+def test_one_token_of_wide_codes_route(gpu, oracle, M, N, K, p, q, codes, vector):
+    """Both sides of each line of the rule that sends one and two tokens of 5- to 7-bit codes to the XOR/popcount kernel."""
+    case = dict(M=M, N=N, K=K, p=p, q=q, a_dist="bernoulli", scaled=False)
+    data = inputs.make_case(case, 2100 + 17 * p + q + M)
+    c32, _ = run_from_codes(gpu, data, case, workspace=True) if codes else run_case(gpu, data, case)
+    assert gpu[1].apmm_last_gemm_kernel().startswith("gemm_decode_kernel<" if vector else "gemm_decode_i8_kernel<")
+    assert np.array_equal(c32.astype(np.int64), oracle.gemm_i64(data["a_codes"], data["w_codes"], p, q))
+
+
+def test_grouped_one_token_of_wide_codes(gpu, oracle):
+    """A launch of several problems keeps them together: the XOR/popcount kernel for single-bit weights, the int8 kernel for
+    two-bit ones, whatever each would take alone."""
+    torch, binding = gpu
+    dev = torch.device("cuda:0")
+    for q, kernel in ((1, "gemm_decode_kernel<"), (2, "gemm_decode_i8_kernel<")):
+        problems, wants = [], []
+        for N, K in ((300, 2100), (70, 4000), (50, 600)):
+            data = inputs.make_case(dict(M=1, N=N, K=K, p=5, q=q, a_dist="bernoulli", scaled=False), 2150 + N + q)
+            wants.append(oracle.gemm_i64(data["a_codes"], data["w_codes"], 5, q))
+            problems.append(dict(M=1, N=N, K=K, a_packed=binding.apmm_pack_activations(torch.from_numpy(data["a_codes"]).to(dev), 5),
+                                 w_packed=binding.apmm_pack_weights(torch.from_numpy(data["w_codes"]).to(dev), q),
+                                 c_i32=torch.empty((1, N), dtype=torch.int32, device=dev)))
+        binding.apmm_gemm_grouped(problems, 5, q)
+        assert binding.apmm_last_gemm_kernel().startswith(kernel)
+        for pr, want in zip(problems, wants):
+            assert np.array_equal(pr["c_i32"].cpu().numpy().astype(np.int64), want)
+
+
 @pytest.mark.parametrize("p,q", [(8, 8), (5, 7), (8, 1), (1, 6), (7, 3)])
 def test_wide_codes(gpu, oracle, p, q):
     case = dict(M=37, N=50, K=333, p=p, q=q, a_dist="bernoulli", scaled=False)

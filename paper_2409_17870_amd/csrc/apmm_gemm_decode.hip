@@ -954,14 +954,14 @@ int decode_valu_variant(const GemmArgs &g)
 // Two tokens, W1A5 4096 x 4096 4.0 / 4.1, 5120 x 5120 6.6 / 6.1, 5120 x 13824 12.2 / 10.1, 11008 x 4096 7.0 / 6.5, 13824 x 5120 8.2 / 9.5.
 // Up to K = 2048 the int8 kernel has one step to do (W1A5 1000 x 2048 3.0 / 3.2, 4096 x 1024 2.9 / 3.2); beyond 12288 channels,
 // 8192 with 3-bit weights, the XOR/popcount kernel needs a second round of workgroups.  From codes the int8 kernel has nothing
-// to expand: W1A5 4096 x 4096 3.6 / 4.3, 5120 x 5120 5.4 / 5.2, 4096 x 11008 6.1 / 5.7, 5120 x 13824 9.7 / 7.9 us, W1A6 5.4 / 5.7, 6.1 /
-// 6.2, 9.8 / 8.8; rows that 16-byte loads do not fit cost the other kernel its byte loop (4123 x 3001 4.4 / 31 us).
+// to expand: W1A5 2048 x 8192 4.8 / 4.8, 4096 x 4096 3.6 / 4.3, 5120 x 5120 5.4 / 5.2, 4096 x 11008 6.1 / 5.7, 8192 x 8192 6.9 / 5.9, 5120 x
+// 13824 9.7 / 7.9 us, W1A6 4.7 / 5.1, 3.6 / 4.6, 5.4 / 5.7, 6.1 / 6.2, 7.0 / 6.4, 9.8 / 8.8; rows that 16-byte loads do not fit cost the other kernel its byte loop (4123 x 3001 4.4 / 31 us).
 bool decode_valu_pays(const GemmArgs &g, bool single)
 {
     if (!nibble_form(g.p)) return false;
     const int64_t pairs = g.M * g.p * g.q;
     if (g.a_codes)
-        return single && pairs <= 6 && g.nkb > 80 && g.N <= 8192 && (g.K & 15) == 0 && (reinterpret_cast<uintptr_t>(g.a_codes) & 15) == 0;
+        return single && pairs <= 6 && g.nkb >= (g.p == 5 ? 40 : 64) && g.N >= 4096 && g.N <= 8192 && (g.K & 15) == 0 && (reinterpret_cast<uintptr_t>(g.a_codes) & 15) == 0;
     if (!single) return pairs <= 7;  // (the problems of a launch stay together whatever their sizes)
     return g.nkb > 16 && (pairs <= 7 || (pairs <= 12 && g.N < 12288) || (g.M == 1 && g.p == 5 && g.q == 3 && g.N <= 8192));
 }

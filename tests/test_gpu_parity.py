@@ -202,9 +202,10 @@ def test_xor_popcount_small_m_kernel_from_codes(gpu, oracle, M, N, K, p, q):
     (1, 12287, 2100, 6, 2, False, True), (1, 12288, 2100, 6, 2, False, False), (1, 300, 2100, 7, 2, False, False),
     (2, 300, 2100, 6, 1, False, True), (2, 300, 2100, 7, 1, False, False), (3, 300, 2100, 5, 1, False, False),
     (1, 8192, 2100, 5, 3, False, True), (1, 8193, 2100, 5, 3, False, False), (1, 300, 2100, 6, 3, False, False),
-    (1, 300, 2100, 8, 1, False, False), (1, 300, 10256, 5, 1, True, True), (1, 300, 10257, 5, 1, True, False),
-    (1, 300, 10240, 5, 1, True, False), (1, 8193, 10256, 5, 1, True, False), (2, 300, 10256, 5, 1, True, False),
-    (1, 300, 10256, 7, 1, True, False)])
+    (1, 300, 2100, 8, 1, False, False), (1, 4096, 5120, 5, 1, True, True), (1, 4095, 5120, 5, 1, True, False),
+    (1, 4096, 4608, 5, 1, True, False), (1, 4096, 5121, 5, 1, True, False), (1, 8192, 4624, 5, 1, True, True),
+    (1, 8193, 5120, 5, 1, True, False), (2, 4096, 5120, 5, 1, True, False), (1, 4100, 7680, 6, 1, True, False),
+    (1, 4100, 7696, 6, 1, True, True), (1, 4096, 8192, 7, 1, True, False)])
 def test_one_token_of_wide_codes_route(gpu, oracle, M, N, K, p, q, codes, vector):
     """Both sides of each line of the rule that sends one and two tokens of 5- to 7-bit codes to the XOR/popcount kernel."""
     case = dict(M=M, N=N, K=K, p=p, q=q, a_dist="bernoulli", scaled=False)

@@ -28,7 +28,7 @@ int one_round_width(const GemmArgs &g)
         }
     }
     // 128 x 128 tiles (16 here) where all narrower ones need a second round
-    if (best == 0 && g.nkb >= (g.q == 1 ? 1 << 30 : g.q == 2 ? 64 : 32) && ((g.M + 127) / 128) * ((g.N + 127) / 128) <= 256) return 16;
+    if (best == 0 && g.nkb >= (g.q == 1 ? 1 << 30 : g.q == 2 ? (activation_field_form(g.p) ? 88 : 76) : 32) && ((g.M + 127) / 128) * ((g.N + 127) / 128) <= 256) return 16;
     return best;
 }
 
@@ -51,9 +51,12 @@ bool gemm_mfma_ksplit_supported(const GemmArgs &g) { return gemm_mfma_fp4_suppor
 //   against 7.9 us at K = 4096).  Taken from K = 3072 on, and at every K up to 128 tokens.
 //   The 128 x 128 tile (1024 x 4096 outputs and the like, every width; large tiles against this, K = 2048 / 4096 / 8192 /
 //   11008): W4A4 12.1 / 19.1 / 34.6 / 45.3 against 13.2 / 16.8 / 25.7 / 32.3 us, W3A3 11.2 / 16.6 / 29.9 / 41.0 against 12.8 /
-//   16.2 / 24.5 / 30.7, W4A2 9.7 / 15.5 / 27.0 / 34.4 against 11.6 / 14.6 / 21.9 / 26.5; W2A4 9.9 / 14.2 / 24.8 / 33.7
-//   against 12.7 / 15.9 / 23.5 / 28.5, W2A2 8.9 / 11.1 / 20.4 / 27.8 against 11.4 / 13.5 / 18.6 / 23.2; W1A4 26.4 against 28.8 us at
-//   K = 11008.  Taken from K = 4096 on with weights of 3 and 4 bits, from K = 8192 on with 2 bits, not with 1.
+//   16.2 / 24.5 / 30.7, W4A2 9.7 / 15.5 / 27.0 / 34.4 against 11.6 / 14.6 / 21.9 / 26.5: taken from K = 4096 on with weights of 3
+//   and 4 bits.  2 bits: this over the large tiles, 512 x 6144 / 640 x 5120 / 768 x 4096 / 512 x 8192 / 1024 x 4096 outputs, W2A1
+//   1.07 / 1.05 / 1.05 / 1.04 / 1.06 at K = 8192, 0.99 - 1.02 at 9216, 0.98 - 1.03 at 9728, 0.94 - 0.99 at 11264; W2A2 1.01 -
+//   1.04, 0.96 - 1.02, 0.96 - 1.03, 0.92 - 0.99; W2A4 (the last three) 1.10, 1.04, 1.03 - 1.05 and 1.00 - 1.01: taken from K =
+//   9728 on, with 3- and 4-bit activations from 11264 on (13824: 0.96 - 1.00).  W1A4 26.4 against 28.8 us at K = 11008: not
+//   taken with 1 bit.
 //   The 64 x 64 tile (outputs of up to 256 of them: up to 256 tokens at 4096 channels, 128 at 8192), with weights of 1 and
 //   2 bits: 65 - 256 tokens at 4096 x 4096 5.3 - 5.9 us (W1A1, W2A2), 6.9 - 7.4 us (W2A4) against 7.5 - 8.5 and 9.6 - 9.9 us with
 //   the 64 x 128 tile and 9.3 - 11.5 us on the large tiles; at 4096 x 11008 7.4 - 8.5 and 10.7 - 11.9 against 11.0 - 12.1 and

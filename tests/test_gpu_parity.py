@@ -923,7 +923,7 @@ def test_k_split_128_by_128_tile(gpu, oracle, M, N, outs, p, q):
     """The tile whose waves work in half k blocks and meet in two rounds: inner and border tiles, a wave with one pair of
     k blocks more than the others, every output."""
     torch, binding = gpu
-    K = 8192 + 130 if q == 2 else 4096 + 130
+    K = 4096 + 130 if q > 2 else 9216 + 130 if p <= 2 else 10752 + 130  # the first stage of K for which each is taken
     if 4 * (K + 382) * ((1 << p) - 1) * ((1 << q) - 1) >= 1 << 24:
         pytest.skip("beyond the exactness bound")
     dev = torch.device("cuda:0")
@@ -942,6 +942,20 @@ def test_k_split_128_by_128_tile(gpu, oracle, M, N, outs, p, q):
     if c16 is not None:
         f = want.double() * sa.double()[:, None] * sw.double()[None, :]
         assert bool(((c16.double() - f).abs() <= 1e-3 * f.abs() + 1e-6).all())
+
+
+@pytest.mark.parametrize("p,q,K", [(1, 2, 9216), (2, 2, 9216), (4, 2, 10752), (3, 2, 10752), (2, 3, 3584), (4, 1, 12800)])
+def test_k_split_128_by_128_tile_leaves_smaller_k_to_the_large_tiles(gpu, p, q, K):
+    """The other side of each line."""
+    torch, binding = gpu
+    dev = torch.device("cuda:0")
+    g = torch.Generator(device=dev).manual_seed(8650 + 10 * p + q)
+    a = torch.randint(0, 1 << p, (1024, K), generator=g, device=dev, dtype=torch.uint8)
+    w = torch.randint(0, 1 << q, (4096, K), generator=g, device=dev, dtype=torch.uint8)
+    c32, _ = binding.apmm_gemm(1024, 4096, K, p, q, binding.apmm_pack_activations(a, p), binding.apmm_pack_weights(w, q))
+    assert binding.apmm_last_gemm_kernel().startswith("gemm_mfma_direct_kernel<%d,%d," % (p, q))
+    want = ((2.0 * a.float() - ((1 << p) - 1)).double() @ (2.0 * w.float() - ((1 << q) - 1)).double().t().contiguous()).to(torch.int64)
+    assert torch.equal(c32.to(torch.int64), want)
 
 
 def test_k_split_kernel_declines_wide_codes(gpu):

@@ -28,7 +28,7 @@ int one_round_width(const GemmArgs &g)
         }
     }
     // 128 x 128 tiles (16 here) where all narrower ones need a second round
-    if (best == 0 && g.nkb >= (g.q == 1 ? 1 << 30 : g.q == 2 ? (activation_field_form(g.p) ? 88 : 76) : 32) && ((g.M + 127) / 128) * ((g.N + 127) / 128) <= 256) return 16;
+    if (best == 0 && g.q >= 2 && g.nkb >= (g.q > 2 ? 32 : activation_field_form(g.p) ? 88 : 76) && ((g.M + 127) / 128) * ((g.N + 127) / 128) <= 256) return 16;
     return best;
 }
 

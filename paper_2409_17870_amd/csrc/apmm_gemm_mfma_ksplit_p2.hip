@@ -8,7 +8,9 @@ template <int Q>
 hipError_t launch_q(const GemmArgs &g, hipStream_t stream, int wn)
 {
     // activations in the group form: the 64 x 64 and 64 x 128 tiles (the wider ones measured slower)
-    if (wn == 16) return mfma::launch_ksplit_variant<2, Q, 4, 4>(g, stream);
+    if constexpr (Q >= 2) {  // (never taken with single-bit weights)
+        if (wn == 16) return mfma::launch_ksplit_variant<2, Q, 4, 4>(g, stream);
+    }
     if (wn == 2) return mfma::launch_ksplit_variant<2, Q, 2, 2>(g, stream);
     return mfma::launch_ksplit_variant<2, Q, 2, 4>(g, stream);
 }

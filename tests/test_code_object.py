@@ -74,3 +74,12 @@ def test_few_tokens_from_codes_leave_three_workgroups_on_a_compute_unit(kernels,
     """gemm_decode_mfma_kernel<p, q, 1, 1, codes, one chunk per lane>: eight waves a workgroup and 512 registers to a lane of the
     four vector units (handed out in eights) make three workgroups up to 80 registers."""
     assert _of(kernels, "gemm_decode_mfma_kernel")[(p, q, 1, 1, 1, 1)][".vgpr_count"] <= 80
+
+
+def test_only_tiles_that_a_launch_rule_names_are_built(kernels):
+    """gemm_mfma_ksplit_kernel<P, Q, row blocks, column blocks>"""
+    for p, q, wm, wn in _of(kernels, "gemm_mfma_ksplit_kernel"):
+        if wm == 4:
+            assert wn == 4 and q >= 2
+        else:
+            assert wm == 2 and wn in ((2, 4) if p <= 2 else (2, 4, 5, 6) if q <= 2 else (2, 4, 5))

@@ -220,6 +220,10 @@ const char *apmm_last_gemm_kernel(void);
 const char *apmm_status_string(apmm_status status);
 /* Text of the last error on the calling thread ("" if none). */
 const char *apmm_last_error(void);
+/* Version of the library and of its packed form.  A packed buffer is opaque and carries no mark of its own: one that was
+ * written by another version is neither recognised nor refused, and is multiplied wrongly where the form differs, so a program
+ * that keeps packed weights in a file keeps this number beside them and packs anew when it has changed.
+ * 101: other contents than 100 in packed weights of 3 to 8 bits and packed activations of 5 to 8 bits, sizes as before. */
 int apmm_version(void);
 
 #ifdef __cplusplus

@@ -406,6 +406,7 @@ const char *apmm_last_error(void) { return g_error; }
 
 const char *apmm_last_gemm_kernel(void) { return apmm::last_kernel(); }
 
-int apmm_version(void) { return 100; }
+// 101: packed weights of 3 to 8 bits and packed activations of 5 to 8 bits in the forms of apmm_layout.h (folded, nibbles, bytes)
+int apmm_version(void) { return 101; }
 
 }  // extern "C"

@@ -5,6 +5,8 @@ Integer outputs must be bit-exact.  The fp16 epilogue must be within 1e-3 relati
 statement fixes (one fp32 product chain plus one rounding to binary16 is <= 2^-11 + a few
 2^-24 relative).
 """
+import zlib
+
 import numpy as np
 import pytest
 
@@ -64,6 +66,27 @@ def algos_for(case):
 
 
 # ------------------------------------------------------------- pack layout --
+# crc32 of the packed form of the codes below, as weights and as activations, by apmm_version() and bits
+PACKED_FORM = {
+    100: {1: (0xaedf7677, 0xaedf7677), 2: (0x4b435df1, 0x4b435df1), 3: (0x9c938e13, 0xc0e63cdc), 4: (0x989c17bf, 0x3a1a0935),
+          5: (0x36383da5, 0x36383da5), 6: (0x9dc4611e, 0x9dc4611e), 7: (0x01425857, 0x01425857), 8: (0x00b683ff, 0x00b683ff)},
+    101: {1: (0xaedf7677, 0xaedf7677), 2: (0x4b435df1, 0x4b435df1), 3: (0x4ba6e539, 0xc0e63cdc), 4: (0xd2d81d72, 0x3a1a0935),
+          5: (0xed6a71c7, 0xed6a71c7), 6: (0x4dd2d590, 0x4dd2d590), 7: (0x2aa7a0fd, 0x2aa7a0fd), 8: (0x4b963e92, 0x4b963e92)},
+}
+
+
+@pytest.mark.parametrize("bits", range(1, 9))
+def test_packed_form_belongs_to_the_version(gpu, bits):
+    """A program that keeps packed weights in a file tells by the version whether they still fit: other contents, another version."""
+    torch, binding = gpu
+    codes = torch.from_numpy(inputs.bernoulli_codes(8800 + bits, inputs.TAG_W, 33, 700, bits)).to("cuda:0")
+    w = torch.zeros(binding.apmm_packed_bytes(33, 700, bits), dtype=torch.uint8, device="cuda:0")
+    a = torch.zeros(binding.apmm_packed_activation_bytes(33, 700, bits), dtype=torch.uint8, device="cuda:0")
+    binding.apmm_pack_weights(codes, bits, out=w)
+    binding.apmm_pack_activations(codes, bits, out=a)
+    assert tuple(zlib.crc32(t.cpu().numpy().tobytes()) for t in (w, a)) == PACKED_FORM[binding.apmm_version()][bits]
+
+
 @pytest.mark.parametrize("rows,K,bits", [(1, 1, 1), (5, 31, 3), (32, 128, 2), (33, 129, 4), (70, 500, 8),
                                          (16, 512, 2), (100, 4096, 1), (257, 1000, 5), (37, 4097, 2), (5, 11008, 4),
                                          (3, 20000, 3), (40, 16400, 1), (9, 70000, 7)])

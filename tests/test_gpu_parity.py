@@ -297,6 +297,60 @@ def test_int8_kernel_large_tiles(gpu, oracle, p, q, M, N, K):
     check_f16(c16, want, data, oracle)
 
 
+@pytest.mark.parametrize("p,q,K", [(8, 8, 32768), (8, 7, 66048), (7, 8, 66048), (7, 7, 133120), (5, 8, 271360)])
+@pytest.mark.parametrize("M,N,kernel", [(5, 40, "gemm_decode_i8_kernel"), (40, 40, "gemm_decode_i8_kernel"), (70, 140, "ksplit>"), (1100, 4000, "tiles>")])
+def test_int8_kernels_at_the_32_bit_limit(gpu, M, N, kernel, p, q, K):
+    """The largest padded K that is admitted, K (2^p - 1)(2^q - 1) just below 2^31: all-ones and all-zeros rows against each other
+    reach both ends of int32, and every term of the recovery wraps on the way there."""
+    torch, binding = gpu
+    unit = ((1 << p) - 1) * ((1 << q) - 1)
+    assert K % 512 == 0 and K * unit < 1 << 31 <= (K + 512) * unit + unit
+    dev = torch.device("cuda:0")
+    g = torch.Generator(device=dev).manual_seed(2600 + 17 * p + q)
+    a = torch.randint(0, 1 << p, (M, K), generator=g, device=dev, dtype=torch.uint8)
+    w = torch.randint(0, 1 << q, (16, K), generator=g, device=dev, dtype=torch.uint8)
+    a[0], a[1], a[-1], a[-2] = 0, (1 << p) - 1, (1 << p) - 1, 0
+    w[0], w[1] = (1 << q) - 1, 0
+    # integers below 2^31 and their sums: exact in double precision; the weights repeat their first sixteen rows
+    want = ((2.0 * a.double() - ((1 << p) - 1)) @ (2.0 * w.double() - ((1 << q) - 1)).t().contiguous()).to(torch.int64)
+    want = want.repeat(1, (N + 15) // 16)[:, :N]
+    assert int(want.max()) == K * unit and int(want.min()) == -K * unit
+    wp = binding.apmm_pack_weights(w.repeat((N + 15) // 16, 1)[:N].contiguous(), q)
+    packed = binding.apmm_pack_activations(a, p)
+    c32, _ = binding.apmm_gemm(M, N, K, p, q, packed, wp)
+    name = binding.apmm_last_gemm_kernel()
+    assert name.startswith(kernel) or name.endswith(kernel), name
+    assert torch.equal(c32.to(torch.int64), want)
+    if M <= 16:
+        c32, _ = binding.apmm_gemm_from_codes(a, N, p, q, wp, workspace=packed)
+        assert binding.apmm_last_gemm_kernel().endswith(",codes>")
+        assert torch.equal(c32.to(torch.int64), want)
+
+
+@pytest.mark.parametrize("p,q", [(3, 3), (3, 4), (4, 3), (4, 4)])
+@pytest.mark.parametrize("M,N", [(3, 20), (16, 8200), (20, 33), (33, 50), (64, 17), (30, 8195)])
+def test_int8_small_m_kernel_narrow_codes_beyond_the_bound(gpu, M, N, p, q):
+    """3- and 4-bit codes at a K that the fp4 kernels cannot sum exactly (4 K (2^p - 1)(2^q - 1) >= 2^24): every token tile, one and
+    two channel tiles, packed and, up to 32 tokens, from codes."""
+    K = ((1 << 24) // (4 * ((1 << p) - 1) * ((1 << q) - 1)) // 512 + 1) * 512 + 17
+    torch, binding = gpu
+    dev = torch.device("cuda:0")
+    g = torch.Generator(device=dev).manual_seed(2700 + 17 * p + q + M)
+    a = torch.randint(0, 1 << p, (M, K), generator=g, device=dev, dtype=torch.uint8)
+    w = torch.randint(0, 1 << q, (N, K), generator=g, device=dev, dtype=torch.uint8)
+    a[0], w[0], w[-1] = (1 << p) - 1, (1 << q) - 1, 0
+    want = ((2.0 * a.double() - ((1 << p) - 1)) @ (2.0 * w.double() - ((1 << q) - 1)).t().contiguous()).to(torch.int64)
+    wp, packed = binding.apmm_pack_weights(w, q), binding.apmm_pack_activations(a, p)
+    tiles = (1 if M <= 16 else 2 if M <= 32 else 4, 2 if N > 8192 else 1)
+    c32, _ = binding.apmm_gemm(M, N, K, p, q, packed, wp)
+    assert binding.apmm_last_gemm_kernel() == "gemm_decode_i8_kernel<%d,%d,%d,%d,packed>" % ((p, q) + tiles)
+    assert torch.equal(c32.to(torch.int64), want)
+    c32, _ = binding.apmm_gemm_from_codes(a, N, p, q, wp, workspace=torch.empty_like(packed))
+    if M <= 16:
+        assert binding.apmm_last_gemm_kernel() == "gemm_decode_i8_kernel<%d,%d,%d,%d,codes>" % ((p, q) + tiles)
+    assert torch.equal(c32.to(torch.int64), want)
+
+
 @pytest.mark.parametrize("p,q", [(8, 1), (8, 3), (8, 8), (7, 2), (6, 6), (5, 4), (7, 8), (8, 5), (1, 8), (2, 6), (3, 8), (4, 7), (1, 5)])
 @pytest.mark.parametrize("M,N,K", [(1, 33, 16), (3, 16, 17), (16, 100, 513), (17, 48, 700), (32, 8200, 130), (33, 50, 2100), (64, 40, 5000),
                                    (2, 8199, 1040), (15, 31, 127)])

@@ -283,6 +283,22 @@ def test_int8_kernel_all_wide_widths(gpu, oracle, p, q):
     check_f16(c16, want, data, oracle)
 
 
+@pytest.mark.parametrize("p,q,kernel", [(8, 8, "tiles"), (5, 8, "tiles"), (8, 2, "tiles"), (5, 1, "tiles"), (8, 5, "ksplit"), (6, 6, "ksplit"),
+                                        (2, 7, "ksplit"), (5, 3, "ksplit"), (7, 4, "ksplit"), (8, 3, "ksplit")])
+def test_int8_kernel_arrangement_by_forms(gpu, p, q, kernel):
+    """One output on both sides of the line, which depends on what the operands' bytes cost to form."""
+    torch, binding = gpu
+    M, N, K = 1000, 4090, 600
+    dev = torch.device("cuda:0")
+    g = torch.Generator(device=dev).manual_seed(2800 + 17 * p + q)
+    a = torch.randint(0, 1 << p, (M, K), generator=g, device=dev, dtype=torch.uint8)
+    w = torch.randint(0, 1 << q, (N, K), generator=g, device=dev, dtype=torch.uint8)
+    c32, _ = binding.apmm_gemm(M, N, K, p, q, binding.apmm_pack_activations(a, p), binding.apmm_pack_weights(w, q))
+    assert binding.apmm_last_gemm_kernel() == "gemm_mfma_i8_kernel<%d,%d,%s>" % (p, q, kernel)
+    want = ((2.0 * a.double() - ((1 << p) - 1)) @ (2.0 * w.double() - ((1 << q) - 1)).t().contiguous()).to(torch.int64)
+    assert torch.equal(c32.to(torch.int64), want)
+
+
 @pytest.mark.parametrize("p,q,M,N,K", [(8, 8, 1100, 4000, 600), (6, 5, 1001, 4123, 515), (4, 7, 1100, 4000, 129), (4, 4, 1100, 4000, 18500)])
 def test_int8_kernel_large_tiles(gpu, oracle, p, q, M, N, K):
     """The int8 kernel's 128 x 256 tile, whole and ragged borders, and narrow codes at a K beyond the fp32 exactness bound."""
@@ -298,7 +314,8 @@ def test_int8_kernel_large_tiles(gpu, oracle, p, q, M, N, K):
 
 
 @pytest.mark.parametrize("p,q,K", [(8, 8, 32768), (8, 7, 66048), (7, 8, 66048), (7, 7, 133120), (5, 8, 271360)])
-@pytest.mark.parametrize("M,N,kernel", [(5, 40, "gemm_decode_i8_kernel"), (40, 40, "gemm_decode_i8_kernel"), (70, 140, "ksplit>"), (1100, 4000, "tiles>")])
+@pytest.mark.parametrize("M,N,kernel", [(5, 40, "gemm_decode_i8_kernel"), (40, 40, "gemm_decode_i8_kernel"), (70, 140, "ksplit>"),
+                                          (2000, 4090, "tiles>")])  # four rounds of the split arrangement's tiles, one of the other's
 def test_int8_kernels_at_the_32_bit_limit(gpu, M, N, kernel, p, q, K):
     """The largest padded K that is admitted, K (2^p - 1)(2^q - 1) just below 2^31: all-ones and all-zeros rows against each other
     reach both ends of int32, and every term of the recovery wraps on the way there."""

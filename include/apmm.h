@@ -46,8 +46,10 @@ typedef enum {
 typedef enum {
     APMM_ALGO_AUTO = 0,
     APMM_ALGO_VALU_POPCOUNT = 1, /* plane pairs by XOR + popcount on the vector ALU, D_ij = K - 2*popc */
-    APMM_ALGO_DECODE = 3,        /* small-M weight-streaming kernels: on the matrix unit for p, q <= 4 and M <= 64 (unpacked
-                                    activation codes of 3 and 4 bits: M <= 32); else XOR + popcount for M <= 16, q <= 4 and p not 3 or 4 */
+    APMM_ALGO_DECODE = 3,        /* small-M weight-streaming kernels: p, q <= 4 and M <= 64 (unpacked activation codes of 3 and
+                                    4 bits: M <= 32) within the K bound of APMM_ALGO_MFMA_FP4, else M <= 16, q <= 4 and p not 3
+                                    or 4; on the fp4 or int8 matrix operations, or XOR + popcount where that is faster or K is
+                                    beyond the bound */
     APMM_ALGO_MFMA_FP4 = 4,      /* plane groups recombined to E2M1 codes in registers, f8f6f4 MFMA, exact fp32 accumulate
                                     (p, q <= 4 and 4 * roundup(K,512) * (2^p-1)(2^q-1) < 2^24); the large-tile kernel, every
                                     wave sweeping all of K */
@@ -150,12 +152,13 @@ apmm_status apmm_gemm_ex(int64_t M, int64_t N, int64_t K, int p, int q,
  * ignored, no alignment needed).  Result and all other arguments as in apmm_gemm.
  *   - For a few tokens the small-M kernels regroup the codes into the packed form on their way into
  *     on-chip memory: one launch, no packed buffer.  The separate packing launch costs as much as such a
- *     GEMM.  Taken when the small-M kernels cover the shape (M <= 16 with q <= 4 and p not 3 or 4, or
- *     M <= 64 with p, q <= 2) and M <= 16 or M * N <= 65536.
+ *     GEMM.  Taken for shapes of APMM_ALGO_DECODE when M <= 16 (3- and 4-bit activations: M <= 8) or M * N <=
+ *     65536, and, with a workspace, for every other pair of widths with a code of more than four bits (or with 3 and 4 bits on
+ *     both sides beyond the K bound) when K >= 16 and M <= 16 (M <= 32 if K <= 8192).
  *   - Otherwise the codes are packed into `workspace` (device, 16-byte aligned, at least
  *     apmm_packed_activation_bytes(M, K, p) bytes, overwritten) and apmm_gemm runs on that: two launches.
- * Without such a workspace the call still takes the one-launch path wherever the small-M kernels cover the
- * shape, and returns APMM_ERR_WORKSPACE (nothing launched) where they do not. */
+ * Without such a workspace the call still takes the one-launch path for every shape of APMM_ALGO_DECODE, and returns
+ * APMM_ERR_WORKSPACE (nothing launched) for all others, also those that a workspace of that size would send the same way. */
 apmm_status apmm_gemm_from_codes(int64_t M, int64_t N, int64_t K, int p, int q,
                                  const uint8_t *a_codes, const void *w_packed,
                                  int32_t *c_i32, uint16_t *c_f16,
@@ -200,8 +203,8 @@ typedef struct apmm_problem {
  * small-M kernel covers are launched eight at a time; all others are launched one by one.  The outputs
  * of different entries must not overlap.  At most 256 entries.  On an argument error nothing is launched.
  * An entry with a_codes takes its activations unpacked, as apmm_gemm_from_codes does in its one-launch
- * form (no packing launch, no packed buffer); such an entry must be a shape the small-M kernels cover,
- * else the call returns APMM_ERR_UNSUPPORTED.  Entries with and without a_codes do not share a launch. */
+ * form (no packing launch, no packed buffer); such an entry must be a shape of APMM_ALGO_DECODE, else the call
+ * returns APMM_ERR_UNSUPPORTED.  Entries with and without a_codes do not share a launch. */
 apmm_status apmm_gemm_grouped(int count, const apmm_problem *problems, int p, int q,
                               void *workspace, size_t workspace_bytes, void *stream);
 

@@ -54,7 +54,7 @@ __device__ __forceinline__ uint4 shift_past(uint4 v, int past)
                       __builtin_amdgcn_alignbit(v.w, v.z, s), __builtin_amdgcn_alignbit(~0u, v.w, s));
 }
 
-// Builds the launch descriptor of `count` problems (16 output channels per workgroup each).
+// Builds the launch descriptor of `count` problems, `rows_per_wg` output channels per workgroup.
 template <class PassKb>
 inline bool make_group(const GemmArgs *gs, int count, int rows_per_wg, PassKb pass_kb, GroupArgs &ga)
 {

@@ -883,7 +883,7 @@ hipError_t launch_decode_mfma_v(const GroupArgs &ga, hipStream_t stream)
         if constexpr (TT == 4 && RT == 2) {
             return hipErrorInvalidValue;
         } else {
-            // one aligned 16-byte load per chunk when every problem's rows allow it, else the byte-wise variant
+            // one aligned 16-byte load per chunk when every problem's rows allow it, else the variant that clamps its loads to the row
             bool vec_ok = true;
             for (int i = 0; i < ga.count; ++i)
                 vec_ok = vec_ok && (ga.g[i].K & 15) == 0 && (reinterpret_cast<uintptr_t>(ga.g[i].a_codes) & 15) == 0;

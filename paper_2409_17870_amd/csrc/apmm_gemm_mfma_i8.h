@@ -15,8 +15,9 @@
 // a compute unit's L1 delivers 64.  Narrower forms load less and compute more: 1.5 - 6.5 operations per operand dword,
 // three dwords per MFMA.
 // Measured (fp16 output, one launch inside a graph; before: the general XOR/popcount kernel): W8A8 512 x 4096 x 4096
-// 3350 -> 15.5 us, 2048 x 4096 x 4096 42 us, 2048 x 11008 x 4096 115 us (1.6 POP/s); W4A8 13.3 / 37 / 101 us; W8A4 15.3 / 43 /
-// 121 us; W6A6 22 / 67 / 183 us (bound by forming the bytes).  A variant with both operands expanded through LDS (64 x 128
+// 3350 -> 15.3 us, 2048 x 4096 x 4096 40 us, 2048 x 11008 x 4096 112 us (1.65 POP/s); W4A8 15.1 / 41 / 113 us (13.3 / 37 /
+// 101 us while 4-bit weights were plane groups: a word of fields takes more operations to unfold than a pair group to cut);
+// W8A4 14.4 / 39 / 111 us; W6A6 21 / 63 / 184 us (bound by forming the bytes).  A variant with both operands expanded through LDS (64 x 128
 // and 128 x 256 tiles, eight waves, one barrier per k block) took 24.3 and 129 us for W8A8 at the first and third size:
 // the chain barrier, LDS read, MFMA, LDS write of every k block was not covered.
 #pragma once

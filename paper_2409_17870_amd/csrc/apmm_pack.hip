@@ -347,13 +347,13 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const uint8_t *__restric
 }
 
 // Fused quantise + pack (paper Sec. 3.1: the feature matrix is quantised onto the symmetric bipolar-INT
-// grid; Sec. 4.1: decomposition and reassembly).  One wave per row (token):
+// grid; Sec. 4.1: decomposition and reassembly).  One, two or four waves per row (token):
 //   1. max |x| over the row (on the bit patterns, two halves per operation);
 //      scale = half(max|x| / (2^bits - 1)), stored per token; r = 1 / scale;
 //   2. u = clamp(floor(x / (2 scale)) + 2^(bits-1), 0, 2^bits - 1): x / scale moved to the nearest odd
 //      integer (ties upward), as a code; the floor is that of the exact quotient (computed as x * (r / 2)
 //      with a correction that covers the rounding of r and of the product); then the same packing as pack_kernel.
-// Rows of up to 8192 elements stay in registers between the two steps; longer rows are read again (from
+// Rows of up to 16384 elements (4096 for each wave) stay in registers between the two steps; longer rows are read again (from
 // L2).  The codes are those of exact arithmetic on the binary16 inputs and the binary16 scale.  A row whose
 // scale rounds to zero gets the code of +1 everywhere.
 //

@@ -611,7 +611,8 @@ def test_two_phase_kernels(gpu, oracle, p, q, K):
 
 
 def test_long_k_beyond_the_fp32_exactness_bound(gpu, oracle):
-    """4 K (2^p - 1)(2^q - 1) >= 2^24: the MFMA kernel declines, auto falls back to XOR/popcount."""
+    """4 K (2^p - 1)(2^q - 1) >= 2^24: the fp4 kernels decline, auto takes the int8 kernels (3 and 4 bits on both
+    sides) or XOR/popcount (1 or 2 bits on one)."""
     torch, binding = gpu
     case = dict(M=20, N=24, K=20000, p=4, q=4, a_dist="bernoulli", scaled=True)
     data = inputs.make_case(case, 7100)

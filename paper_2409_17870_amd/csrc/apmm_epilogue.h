@@ -40,6 +40,12 @@ __device__ __forceinline__ uint32_t use_here(uint32_t v)
     return v;
 }
 
+// A copy in a register of its own: a lane permute that moves nothing, which the compiler does not see through.
+__device__ __forceinline__ uint32_t copy_here(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xE4, 0xf, 0xf, true);  // quad_perm [0, 1, 2, 3]
+}
+
 __device__ __forceinline__ void store_output(const GemmArgs &g, int64_t m, int64_t n, int32_t c, float sa,
                                              float sw)
 {

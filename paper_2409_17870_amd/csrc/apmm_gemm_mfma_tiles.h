@@ -2,6 +2,7 @@
 // unit per activation width instantiates the kernels, so that they compile in parallel.
 #pragma once
 #include "apmm_gemm_mfma_direct.h"
+#include "apmm_gemm_mfma_lds.h"
 
 namespace apmm {
 namespace mfma {
@@ -18,57 +19,57 @@ inline const char *debug_switch(const char *name)
 #endif
 }
 
-// Tile choice: estimate each candidate as (rounds of 256 tiles) x (tile area) x (measured relative
-// cost per MFMA of that tile shape) and take the cheapest.  (Debug builds: APMM_MFMA_TILE=0..3 forces one.)
+// Tile choice.  Outputs of more than one round of the direct kernel's best tile go to the kernel that shares its operands through
+// LDS (apmm_gemm_mfma_lds.h), 128 x 128 with two or three workgroups to a compute unit; so do nearly all with 3- and 4-bit
+// activations.  Microseconds, direct against LDS, operands and outputs in rotation (M x N x K):
+//   W4A4 1024 x 11008 x 4096 fp16 54 / 39, both outputs 68 / 39; 512 x 13824 x 5120 34.8 / 32.0; 4096 x 4096 x 4096 53 / 43
+//   W2A4 700 x 8000 x 1000 fp16 11.9 / 9.9, 1024 x 11008 x 4096 35 / 28; W3A3 1000 x 5003 x 3001 both 29.7 / 26.0
+//   W2A2 1024 x 11008 x 4096 28.1 / 23.9, both 40 / 27; 2048 x 11008 x 4096 both 67 / 54; 3000 x 8000 x 700 26.3 / 21.6
+//   one round, W2A2, operands warm: 2048 x 4096 x 4096 (256 x 128) 17.2 / 17.6, 512 x 13824 x 5120 18.6 / 20.1, 2048 x 2048 x 2048 (128 x
+//   128) 7.5 / 8.4: direct.
 template <int P, int Q>
 hipError_t launch_tiles(const GemmArgs &g, hipStream_t stream)
 {
-    struct Cand { int bm, bn; double cost; };
-    // activations in the field form need 24 raw registers per row block: only the tiles with two row blocks
-    // per wave are built for them (the others are given a cost no choice survives)
-    constexpr bool AF = activation_field_form(P);
-    // (4-bit weights: the words of four column blocks beside 256 accumulators would spill)
-    const Cand cands[4] = {{256, 256, AF || Q == 4 ? 1e9 : 1.0}, {256, 128, AF ? 1e9 : 1.2}, {128, 256, AF ? 1.0 : 1.2},
-                           {128, 128, AF ? 1.15 : 1.2}};
-    int best = 0;
-    double best_t = 0;
+    const int64_t tiles128 = ((g.M + 127) / 128) * ((g.N + 127) / 128);
     static const char *forced = debug_switch("APMM_MFMA_TILE");
     static const char *no_split = debug_switch("APMM_MFMA_SPLIT");
-    if (forced && forced[0] >= '0' && forced[0] <= '3' && !(AF && forced[0] < '2') && !(Q == 4 && forced[0] == '0')) {
-        best = forced[0] - '0';
+    if constexpr (activation_field_form(P)) {
+        (void)forced; (void)no_split;
+        if constexpr (Q <= 2) {
+            // One workgroup to a compute unit at most: the direct kernel's 128 x 128 tile (four wave tiles of 32 x 128, every
+            // activation row block loaded by one wave) starts and ends faster, 1024 x 4096 x 512 / 1024 W2A4 5.8 / 7.2 against 6.1 /
+            // 7.2 us, W1A4 5.4 / 6.2 against 5.7 / 6.7, and from K = 2048 on is slower: W2A4 0.80 - 0.99 of its time through LDS over six
+            // outputs and K = 2048 - 8192, W1A4 0.82 - 1.04.  From K = 10240 on, where it has the outputs that the K split leaves, the
+            // two are within 8 %.
+            if (tiles128 <= 256 && (g.K < 2048 || g.K >= 10240)) return launch_direct_variant<P, Q, 1, 4>(g, stream);
+            // With four tiles and more to a compute unit the 128 x 256 tile, two workgroups to a compute unit: fewer bytes from L2 and
+            // LDS per product, longer runs per store.  W2A4 4096 x 4096 x 4096 39.4 -> 35.0 us, W1A4 35.3 -> 32.5; at three tiles equal
+            // (1024 x 11008 x 4096 W2A4 30.0 / 29.1); below K = 2048 only with both outputs (4096 x 11008 x 1024 W2A4 81 -> 69 us, its
+            // fp16 output alone 46 / 46, at K = 512 35 / 40).
+            if (tiles128 > 3 * 256 && (g.K >= 2048 || (g.c_i32 && g.c_f16))) return launch_lds_variant<P, Q, 2, 4, 2>(g, stream);
+        }
+        return launch_lds_variant<P, Q, 2, 2, 2>(g, stream);
     } else {
-        for (int c = 0; c < 4; ++c) {
+        // Direct tiles: estimate each candidate as (rounds of 256 tiles) x (tile area) x (measured relative cost per MFMA of that tile
+        // shape) and take the cheapest.  (Debug builds: APMM_MFMA_TILE=0..3 forces one.)
+        struct Cand { int bm, bn; double cost; };
+        // (4-bit weights: the words of four column blocks beside 256 accumulators would spill)
+        const Cand cands[4] = {{256, 256, Q == 4 ? 1e9 : 1.0}, {256, 128, 1.2}, {128, 256, 1.2}, {128, 128, 1.2}};
+        int best = 0;
+        double best_t = 0;
+        int64_t best_tiles = 0;
+        const bool force = forced && forced[0] >= '0' && forced[0] <= '3' && !(Q == 4 && forced[0] == '0');
+        if (force) best = forced[0] - '0';
+        for (int c = 0; !force && c < 4; ++c) {
             const int64_t tiles = ((g.M + cands[c].bm - 1) / cands[c].bm) * ((g.N + cands[c].bn - 1) / cands[c].bn);
             const double t = (double)((tiles + 255) / 256) * cands[c].bm * cands[c].bn * cands[c].cost;
             if (c == 0 || t < best_t) {
                 best = c;
                 best_t = t;
+                best_tiles = tiles;
             }
         }
-    }
-    if constexpr (AF) {
-        (void)no_split;
-        static const char *square = debug_switch("APMM_MFMA_AF_2X2");
-        const bool old_arrangement = square && square[0] == '1';
-        if (best == 2) {
-            // 1-bit weights: four wave tiles of 32 x 256 need 3.5 instead of 4 KB per wave and k step (with wider
-            // weights the 2 x 2 arrangement of 64 x 128 wave tiles is the lighter one).  Measured at M = 2048 with both
-            // outputs: 8 % faster at K = 11008, 2 - 5 % slower at K = 4096, where the store of the tile weighs more
-            // than the k loop: taken from K = 8192 on.
-            if constexpr (Q == 1) {
-                if (!old_arrangement && g.nkb >= 64) return launch_direct_variant<P, Q, 1, 8>(g, stream);
-            }
-            return launch_direct_variant<P, Q, 2, 4>(g, stream);
-        }
-        // The 128 x 128 tile as four wave tiles of 32 x 128 one above the other: every activation row block (6 bits per
-        // element, three quarters of the bytes) is loaded by one wave only, 14 instead of 16 KB through L1 per k step,
-        // and these tiles are bound by L1: measured 12 % faster than 2 x 2 wave tiles of 64 x 64
-        // (APMM_MFMA_AF_2X2=1 brings those back, for comparison).
-        // With weights of 3 and 4 bits they are nearly as heavy: 2 x 2 needs 20 instead of 22 KB with 4 bits (1024 x 4096 x 11008
-        // W4A4 46.8 -> 44.8 us, 768 x 4096 x 4096 18.6 -> 17.7 us), the same with 3 (within 3 %).
-        if (old_arrangement || Q > 2) return launch_direct_variant<P, Q, 2, 2>(g, stream);
-        return launch_direct_variant<P, Q, 1, 4>(g, stream);
-    } else {
+        if (best_tiles > 256) return launch_lds_variant<P, Q, 2, 2, 3>(g, stream);
         switch (best) {
         case 0: {
             // Two-phase kernels (part of the store under the k loop).  APMM_MFMA_SPLIT=0, 2, 3 forces the one-phase,

@@ -91,6 +91,16 @@ __device__ __forceinline__ v8i field_operand(const uint4 (&raw)[NS])
                (int)vec_word<(w + 2) & 3>(raw[(w + 2) >> 2]), (int)vec_word<(w + 3) & 3>(raw[(w + 3) >> 2]),
                (int)vec_word<(w + 4) & 3>(raw[(w + 4) >> 2]), (int)vec_word<(w + 5) & 3>(raw[(w + 5) >> 2]), 0, 0};
 }
+// The same for local k step KS of half a k block.  The middle slot of the three belongs half to either k step: `mid` is this step's
+// half of it, copied a step ahead (copy_here).  Left to itself the compiler makes these copies right behind the loads, each behind
+// a wait, and the look-ahead is lost.
+template <int KS>
+__device__ __forceinline__ v8i field_operand(const uint4 (&raw)[3], const uint2 &mid)
+{
+    const uint4 &own = raw[2 * KS];
+    if constexpr (KS == 1) return v8i{(int)mid.x, (int)mid.y, (int)own.x, (int)own.y, (int)own.z, (int)own.w, 0, 0};
+    else return v8i{(int)own.x, (int)own.y, (int)own.z, (int)own.w, (int)mid.x, (int)mid.y, 0, 0};
+}
 
 // ---- The same for stages of half a k block: k steps 2 H, 2 H + 1 (KSL = 0, 1), whose words are these slots ----
 constexpr int half_slots(int n, bool field) { return field ? 3 : n <= 2 ? 1 : 2; }

@@ -62,7 +62,7 @@ def _of(kernels, name):
     return out
 
 
-@pytest.mark.parametrize("name", ["gemm_mfma_ksplit_kernel", "gemm_decode_i8_kernel", "gemm_decode_mfma_kernel"])
+@pytest.mark.parametrize("name", ["gemm_mfma_ksplit_kernel", "gemm_decode_i8_kernel", "gemm_decode_mfma_kernel", "gemm_mfma_lds_kernel"])
 def test_no_vector_register_is_spilled(kernels, name):
     spilled = {a: k[".vgpr_spill_count"] for a, k in _of(kernels, name).items() if k[".vgpr_spill_count"]}
     assert not spilled

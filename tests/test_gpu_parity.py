@@ -1053,6 +1053,39 @@ def test_k_split_128_by_128_tile_leaves_smaller_k_to_the_large_tiles(gpu, p, q, 
     assert torch.equal(c32.to(torch.int64), want)
 
 
+# (M, N, K, tile width in 64 columns); two tile rows, the second of them two or 65 rows, and more tiles than one round of any other tile
+LDS_SHAPES = ([(130, 33025, 600, 2), (193, 33100, 512, 2), (257, 22000, 1500, 2)],  # 1- and 2-bit activations
+              [(130, 333, 2048, 2), (100, 1000, 2600, 2), (257, 33200, 2100, 4), (1025, 11100, 130, 4)],  # 3, 4 bits against 1, 2 bits
+              [(130, 333, 100, 2), (65, 129, 1100, 2), (193, 33100, 512, 2)])  # 3, 4 bits against 3, 4 bits
+
+
+@pytest.mark.parametrize("p,q", [(p, q) for p in range(1, 5) for q in range(1, 5)])
+@pytest.mark.parametrize("outs", ["i32", "f16", "both"])
+def test_operands_shared_through_lds(gpu, p, q, outs):
+    """The kernel that shares its operands through LDS: borders in M and N, K of one ring of half stages, of two and of a part,
+    outputs with pairs of columns and without, every element."""
+    torch, binding = gpu
+    dev = torch.device("cuda:0")
+    for M, N, K, wide in LDS_SHAPES[0 if p <= 2 else 1 if q <= 2 else 2]:
+        if wide == 4 and K < 2048 and outs != "both":
+            continue
+        g = torch.Generator(device=dev).manual_seed(8700 + 10 * p + q + M)
+        a = torch.randint(0, 1 << p, (M, K), generator=g, device=dev, dtype=torch.uint8)
+        w = torch.randint(0, 1 << q, (N, K), generator=g, device=dev, dtype=torch.uint8)
+        sa = (0.01 + 0.09 * torch.rand(M, generator=g, device=dev)).half()
+        sw = (0.01 + 0.09 * torch.rand(N, generator=g, device=dev)).half()
+        c32, c16 = binding.apmm_gemm(M, N, K, p, q, binding.apmm_pack_activations(a, p), binding.apmm_pack_weights(w, q),
+                                     want_i32=outs != "f16", want_f16=outs != "i32", w_scale=sw, a_scale=sa, algo=FP4)
+        assert binding.apmm_last_gemm_kernel() == "gemm_mfma_lds_kernel<%d,%d,2,%d>" % (p, q, wide)
+        # sums of small integers: exact in double precision
+        want = ((2.0 * a.float() - ((1 << p) - 1)).double() @ (2.0 * w.float() - ((1 << q) - 1)).double().t().contiguous()).to(torch.int64)
+        if c32 is not None:
+            assert torch.equal(c32.to(torch.int64), want)
+        if c16 is not None:
+            f = want.double() * sa.double()[:, None] * sw.double()[None, :]
+            assert bool(((c16.double() - f).abs() <= 1e-3 * f.abs() + 1e-6).all())
+
+
 def test_k_split_kernel_declines_wide_codes(gpu):
     torch, binding = gpu
     a = torch.zeros((64, 512), dtype=torch.uint8, device="cuda:0")

@@ -16,7 +16,7 @@
 #pragma once
 #include <hip/hip_ext.h>
 
-#include "apmm_mfma_common.h"
+#include "apmm_gemm_mfma_lds.h"
 
 namespace apmm {
 namespace mfma {
@@ -35,16 +35,13 @@ constexpr int ksplit_rounds(int wm, int wn) { return ksplit_half(wm, wn) ? 2 : 1
 constexpr int ksplit_lds_bytes(int wm, int wn) { return wm * wn / ksplit_rounds(wm, wn) * (ksplit_half(wm, wn) ? 4 : 3) * 4 * 64 * 16; }
 
 template <int P, int Q, int WM, int WN>
-__global__ __launch_bounds__(256, WN == 2 ? 2 : 1)  // two workgroups of the 64 x 64 tile share a compute unit
-void gemm_mfma_ksplit_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32_t *ci_arg,
-                                                               uint16_t *cf_arg, int m_arg, int n_arg, int k_arg, int nkb_arg,
-                                                               int tiles_n, int tiles_m_xn, const uint16_t *ws_arg,
-                                                               const uint16_t *as_arg)
+__device__ __forceinline__ void ksplit_tile(float4 *red, const uint32_t *a_arg, const uint32_t *w_arg, int32_t *ci_arg, uint16_t *cf_arg, int m_arg, int n_arg,
+                                            int k_arg, int nkb_arg, int tiles_n, int tiles_m_xn, const uint16_t *ws_arg, const uint16_t *as_arg)
 {
+    // red: [block][partial 0..2][register quad 0..3][lane]
     static_assert(P >= 1 && P <= 4 && Q >= 1 && Q <= 4, "instantiated for codes of up to four bits");
     static_assert(WM == 1 || WM == 2 || WM == 4, "row blocks per tile");
     static_assert(ksplit_lds_bytes(WM, WN) <= 160 * 1024, "the partial copies of every block of a round must fit the LDS");
-    extern __shared__ __align__(16) float4 red[];  // [block][partial 0..2][register quad 0..3][lane]
     constexpr bool AF = activation_field_form(P);
     constexpr int SLOTS_A = activation_slots(P);
     constexpr int NB = WM * WN;
@@ -372,13 +369,65 @@ void gemm_mfma_ksplit_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32
     });
 }
 
+// The 128 x 128 tile (4 x 4 blocks) in two forms.  Up to K = 9216, and with 2-bit weights at every K: two groups of four waves, each with half
+// of K, that share their operands through LDS (apmm_gemm_mfma_lds.h).  It starts and ends faster and, with twice the waves, waits
+// less, but a product needs 1.25 KB of LDS reads (W4A4) where the four waves with 256 accumulators read their words from L1 once for
+// sixteen.  Microseconds, LDS / registers: K = 4096, 1024 x 4096 outputs W4A4 14.3 / 16.9, W3A3 14.3 / 16.7, W4A2 12.9 / 15.2; K = 8192 25.2 / 25.8,
+// 23.7 / 25.1, 21.2 / 22.0; K = 11008 33.5 / 32.6, 30.8 / 30.9, 27.6 / 27.1; with 2 bits at K = 11008 W2A4 27.9 / 30.0, W2A2 22.0 / 22.6, W2A1
+// 20.5 / 21.8.
+constexpr int64_t kKsplitLdsMaxK = 9216;
+template <int P, int Q, int WM, int WN>
+__global__ __launch_bounds__(WM == 4 ? 512 : 256, WN == 2 ? 2 : 1)  // two workgroups of the 64 x 64 tile share a compute unit
+void gemm_mfma_ksplit_kernel(const uint32_t *a, const uint32_t *w, int32_t *c_i32, uint16_t *c_f16, int m, int n, int k, int nkb, int tiles_n, int tiles_m_xn,
+                             const uint16_t *w_scale, const uint16_t *a_scale)
+{
+    extern __shared__ __align__(16) float4 red[];
+    if constexpr (WM == 4) lds_tile<P, Q, 2, WN / 2, 2>(reinterpret_cast<uint4 *>(red), a, w, c_i32, c_f16, m, n, k, nkb, tiles_n, tiles_m_xn, w_scale, a_scale);
+    else ksplit_tile<P, Q, WM, WN>(red, a, w, c_i32, c_f16, m, n, k, nkb, tiles_n, tiles_m_xn, w_scale, a_scale);
+}
+template <int P, int Q>
+__global__ __launch_bounds__(256) void gemm_mfma_ksplit_long_kernel(const uint32_t *a, const uint32_t *w, int32_t *c_i32, uint16_t *c_f16, int m, int n, int k,
+                                                                    int nkb, int tiles_n, int tiles_m_xn, const uint16_t *w_scale,
+                                                                    const uint16_t *a_scale)
+{
+    extern __shared__ __align__(16) float4 red[];
+    ksplit_tile<P, Q, 4, 4>(red, a, w, c_i32, c_f16, m, n, k, nkb, tiles_n, tiles_m_xn, w_scale, a_scale);
+}
+
 template <int P, int Q, int WM, int WN>
 hipError_t launch_ksplit_variant(const GemmArgs &g, hipStream_t stream)
 {
     constexpr int BM = 32 * WM, BN = 32 * WN;
-    constexpr int lds = ksplit_lds_bytes(WM, WN);
     const int64_t tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
     if (tiles_m >= (1 << 28) || tiles_n >= (1 << 28) || g.K > 0x7fffffffLL) return hipErrorInvalidValue;
+    auto launch = [&](auto kernel, int64_t tiles, int threads, int lds, int order, int &prepared_device) {
+        if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
+        int dev = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess) return e;
+        if (prepared_device != dev) {  // the LDS limit is a per-device attribute of the function
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+            if (e != hipSuccess) return e;
+            prepared_device = dev;
+        }
+        const KernelTiming timing = take_kernel_timing();
+        if (timing.start || timing.stop)
+            hipExtLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(threads), lds, stream, timing.start, timing.stop, 0, g.a, g.w,
+                                  g.c_i32, g.c_f16, (int)g.M, (int)g.N, (int)g.K, (int)g.nkb, (int)tiles_n, order, g.w_scale, g.a_scale);
+        else
+            hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(threads), lds, stream, g.a, g.w, g.c_i32, g.c_f16, (int)g.M, (int)g.N,
+                               (int)g.K, (int)g.nkb, (int)tiles_n, order, g.w_scale, g.a_scale);
+        return hipGetLastError();
+    };
+    static thread_local int prepared = -1, prepared_long = -1;
+    if constexpr (WM == 4) {
+        constexpr int lds = lds_tile_bytes<P, Q, 2, WN / 2, 2>();
+        static_assert(lds <= 160 * 1024, "LDS of a compute unit");
+        if (Q == 2 || g.K <= kKsplitLdsMaxK) {
+            note_kernel("gemm_mfma_ksplit_kernel<%d,%d,%d,%d>", P, Q, WM, WN);
+            return launch(gemm_mfma_ksplit_kernel<P, Q, WM, WN>, tiles_m * tiles_n, 512, lds, lds_tile_order<P, Q>(tiles_m, g.K), prepared);
+        }
+    }
     // Parts of the tile grid per XCD: 8 / xn along M times xn along N, the cut that leaves an XCD the fewest packed
     // bytes to read (its row tiles of A plus its column tiles of W).
     int xn_log = 0;
@@ -389,29 +438,15 @@ hipError_t launch_ksplit_variant(const GemmArgs &g, hipStream_t stream)
         if (l == 0 || bytes < best) { best = bytes; xn_log = l; }
     }
     const int64_t part_m = (tiles_m + (8 >> xn_log) - 1) / (8 >> xn_log), part_n = (tiles_n + (1 << xn_log) - 1) / (1 << xn_log);
-    const int64_t tiles = 8 * part_m * part_n;
-    if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
-    const int tiles_m_xn = (int)tiles_m | (xn_log << 28);
-    auto kernel = gemm_mfma_ksplit_kernel<P, Q, WM, WN>;
-    static thread_local int prepared_device = -1;  // the LDS limit is a per-device attribute of the function
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    if (prepared_device != dev) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (e != hipSuccess) return e;
-        prepared_device = dev;
+    const int order = (int)tiles_m | (xn_log << 28);
+    if constexpr (WM != 4) {
+        note_kernel("gemm_mfma_ksplit_kernel<%d,%d,%d,%d>", P, Q, WM, WN);
+        return launch(gemm_mfma_ksplit_kernel<P, Q, WM, WN>, 8 * part_m * part_n, 256, ksplit_lds_bytes(WM, WN), order, prepared);
+    } else if constexpr (Q > 2) {
+        note_kernel("gemm_mfma_ksplit_long_kernel<%d,%d>", P, Q);
+        return launch(gemm_mfma_ksplit_long_kernel<P, Q>, 8 * part_m * part_n, 256, ksplit_lds_bytes(WM, WN), order, prepared_long);
     }
-    const KernelTiming timing = take_kernel_timing();
-    note_kernel("gemm_mfma_ksplit_kernel<%d,%d,%d,%d>", P, Q, WM, WN);
-    if (timing.start || timing.stop)
-        hipExtLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(256), lds, stream, timing.start, timing.stop, 0, g.a, g.w,
-                              g.c_i32, g.c_f16, (int)g.M, (int)g.N, (int)g.K, (int)g.nkb, (int)tiles_n, tiles_m_xn, g.w_scale,
-                              g.a_scale);
-    else
-        hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(256), lds, stream, g.a, g.w, g.c_i32, g.c_f16, (int)g.M,
-                           (int)g.N, (int)g.K, (int)g.nkb, (int)tiles_n, tiles_m_xn, g.w_scale, g.a_scale);
-    return hipGetLastError();
+    return hipErrorInvalidValue;  // (not reached)
 }
 
 }  // namespace mfma

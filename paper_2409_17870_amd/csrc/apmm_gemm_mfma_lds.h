@@ -20,6 +20,8 @@
 #pragma once
 #include <hip/hip_ext.h>
 
+#include <algorithm>
+
 #include "apmm_mfma_common.h"
 
 namespace apmm {
@@ -60,24 +62,33 @@ __device__ __forceinline__ void wait_and_meet()
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
-template <int P, int Q, int WM, int WN, int OCC>
-__global__ __launch_bounds__(256, OCC) void gemm_mfma_lds_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32_t *ci_arg, uint16_t *cf_arg,
-                                                                 int m_arg, int n_arg, int k_arg, int nkb_arg, int tiles_n, int tiles_m_band,
-                                                                 const uint16_t *ws_arg, const uint16_t *as_arg)
+// One workgroup tile of 64 WM x 64 WN.  KG = 2: eight waves, the second four of which work on the second half of K with a ring of
+// their own, for outputs of one round of tiles; in the end either group of waves adds up and stores one row block of each wave tile.
+constexpr int lds_exchange_bytes(int wn) { return 8 * wn * 16 * 64 * 4; }
+template <int P, int Q, int WM, int WN, int KG>
+constexpr int lds_tile_bytes() { return KG == 1 ? LdsTile<P, Q, WM, WN>::BYTES : std::max(2 * LdsTile<P, Q, WM, WN>::BYTES, lds_exchange_bytes(WN)); }
+
+template <int P, int Q, int WM, int WN, int KG>
+__device__ __forceinline__ void lds_tile(uint4 *ring_of_workgroup, const uint32_t *a_arg, const uint32_t *w_arg, int32_t *ci_arg, uint16_t *cf_arg, int m_arg,
+                                         int n_arg, int k_arg, int nkb_arg, int tiles_n, int tiles_m_band, const uint16_t *ws_arg,
+                                         const uint16_t *as_arg)
 {
     using L = LdsTile<P, Q, WM, WN>;
     constexpr bool AF = L::AF;
     constexpr int SLOTS_A = activation_slots(P);
     constexpr int BM = 64 * WM, BN = 64 * WN;
     constexpr uint32_t ca = (1u << P) - 1, cw = (1u << Q) - 1;
-    extern __shared__ __align__(16) uint4 ring[];  // [half stage % 4][row block][slot][lane], A before B; then the shared slots by stage % 2
+    static_assert(KG == 1 || (KG == 2 && WM == 2), "the two groups of waves store a row block each");
     using I0 = std::integral_constant<int, 0>;
 
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave_of_workgroup = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = KG == 1 ? wave_of_workgroup : wave_of_workgroup & 3, group = KG == 1 ? 0 : wave_of_workgroup >> 2;
+    // [half stage % 4][row block][slot][lane], A before B; then the shared slots by stage % 2
+    uint4 *ring = ring_of_workgroup + group * (L::BYTES / 16);
     const int wave_m = wave >> 1, wave_n = wave & 1;
     const int r32 = lane & 31, kh = lane >> 5;
-    // An XCD takes a contiguous run of tiles in an order that walks `band` tile rows column by column (see launch_lds_variant).
+    // An XCD takes a contiguous run of tiles in an order that walks `band` tile rows column by column (see lds_tile_order).
     const int tiles_m = tiles_m_band & 0x0fffffff, band = 1 << (tiles_m_band >> 28);
     const int lid = xcd_tile_id(blockIdx.x, tiles_n * tiles_m);
     const int m_band = lid / (band * tiles_n), in_band = lid - m_band * band * tiles_n;
@@ -94,23 +105,24 @@ __global__ __launch_bounds__(256, OCC) void gemm_mfma_lds_kernel(const uint32_t 
     constexpr int kSlotBytes = kPlaneWords * 4;
     uint32_t voff_a = (uint32_t)(kh * SLOTS_A * kSlotBytes + r32 * 16);
     uint32_t voff_b = (uint32_t)(kh * Q * kSlotBytes + r32 * 16);
+    const int stages = nkb_arg / 2 / KG;  // this group's (nkb is a multiple of four)
     const char *src_a[L::RA / 4], *src_b[L::RB / 4];
 #pragma unroll
     for (int i = 0; i < L::RA / 4; ++i) {
         int64_t rb = m0 / 32 + wave * (L::RA / 4) + i;
         if (rb >= nrb_a) rb = nrb_a - 1;
-        src_a[i] = reinterpret_cast<const char *>(a_arg) + rb * nkb_arg * (int64_t)(SLOTS_A * kSlotBytes);
+        src_a[i] = reinterpret_cast<const char *>(a_arg) + (rb * nkb_arg + group * 2 * stages) * (int64_t)(SLOTS_A * kSlotBytes);
     }
 #pragma unroll
     for (int i = 0; i < L::RB / 4; ++i) {
         int64_t rb = n0 / 32 + wave * (L::RB / 4) + i;
         if (rb >= nrb_b) rb = nrb_b - 1;
-        src_b[i] = reinterpret_cast<const char *>(w_arg) + rb * nkb_arg * (int64_t)(Q * kSlotBytes);
+        src_b[i] = reinterpret_cast<const char *>(w_arg) + (rb * nkb_arg + group * 2 * stages) * (int64_t)(Q * kSlotBytes);
     }
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint4 *)ring;
     // Requests go half stage by half stage; this one is for ring place `r` (its parity is the half).  Past the last stage every lane
     // asks for the same 16 bytes, so that the number of requests under way stays what the waits count on.
-    int to_request = nkb_arg / 2;  // stages; an even number
+    int to_request = stages;
     auto request_one = [&](auto r_c, auto n_c) __attribute__((always_inline)) {
         constexpr int r = decltype(r_c)::value, h = r & 1, n = decltype(n_c)::value;
         constexpr int per_a = L::OWN_A + (h == 0 ? L::SH_A : 0), per_b = L::OWN_B + (h == 0 ? L::SH_B : 0), all_a = L::RA / 4 * per_a;
@@ -147,8 +159,9 @@ __global__ __launch_bounds__(256, OCC) void gemm_mfma_lds_kernel(const uint32_t 
     static_for<kLdsRing - 1>(request);
 
     // For the end of the tile, requested now: code sums and scales of this lane's columns and rows.
-    const int64_t m_lane = m0 + wave_m * WM * 32 + kh * 4, n_lane = n0 + wave_n * WN * 32 + r32;
-    uint32_t w_sum_raw[WN], a_sum_raw[WM], sw_raw[WN], sa_raw[WM / 2];
+    constexpr int WMO = WM / KG;  // row blocks of the wave tile that this wave finishes, the first of them:
+    const int64_t m_own = m0 + (wave_m * WM + group) * 32, m_lane = m_own + kh * 4, n_lane = n0 + wave_n * WN * 32 + r32;
+    uint32_t w_sum_raw[WN], a_sum_raw[WMO], sw_raw[WN], sa_raw[(WMO + 1) / 2];
 #pragma unroll
     for (int bj = 0; bj < WN; ++bj) {
         const int64_t n = n_lane + bj * 32;
@@ -156,12 +169,12 @@ __global__ __launch_bounds__(256, OCC) void gemm_mfma_lds_kernel(const uint32_t 
         sw_raw[bj] = 0x3c00u;  // 1.0
     }
 #pragma unroll
-    for (int bi = 0; bi < WM; ++bi) {
-        const int64_t m = m0 + (wave_m * WM + bi) * 32 + r32;
+    for (int bi = 0; bi < WMO; ++bi) {
+        const int64_t m = m_own + bi * 32 + r32;
         a_sum_raw[bi] = (uint32_t)a_sum[m < nrb_a * 32 ? m : nrb_a * 32 - 1];
     }
 #pragma unroll
-    for (int i = 0; i < WM / 2; ++i) sa_raw[i] = 0x3c00u;
+    for (int i = 0; i < (WMO + 1) / 2; ++i) sa_raw[i] = 0x3c00u;
     if (cf_arg && ws_arg) {
 #pragma unroll
         for (int bj = 0; bj < WN; ++bj) {
@@ -171,8 +184,8 @@ __global__ __launch_bounds__(256, OCC) void gemm_mfma_lds_kernel(const uint32_t 
     }
     if (cf_arg && as_arg) {
 #pragma unroll
-        for (int i = 0; i < WM / 2; ++i) {
-            const int64_t m = m0 + wave_m * WM * 32 + 64 * i + lane;
+        for (int i = 0; i < (WMO + 1) / 2; ++i) {
+            const int64_t m = m_own + 64 * i + lane;
             sa_raw[i] = as_arg[m < M ? m : M - 1];
         }
     }
@@ -282,12 +295,51 @@ __global__ __launch_bounds__(256, OCC) void gemm_mfma_lds_kernel(const uint32_t 
     wait_and_meet<L::loads(1) + L::loads(0)>();
     fetch_range(I0{}, I0{}, std::integral_constant<int, kFetches[0]>{});
     static_for<TASKS>([&](auto t_c) __attribute__((always_inline)) { form(I0{}, I0{}, t_c); });
-    for (int st = 0; st < nkb_arg / 2; st += kLdsRing / 2) static_for<kLdsRing>(half);
+    int st = 0;
+    for (; st + 1 < stages; st += kLdsRing / 2) static_for<kLdsRing>(half);
+    if constexpr (KG == 2) {
+        if (st < stages) static_for<kLdsRing / 2>(half);
+    }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing may still be on its way to LDS when the workgroup ends
+
+    v16f c[WMO][WN];
+    if constexpr (KG == 1) {
+#pragma unroll
+        for (int bi = 0; bi < WM; ++bi)
+#pragma unroll
+            for (int bj = 0; bj < WN; ++bj) c[bi][bj] = acc[bi][bj];
+    } else {
+        // Either group hands the other one's row block over (fp32 sums of integers below 2^24: exact in any order).
+        float4 *there = reinterpret_cast<float4 *>(ring_of_workgroup) + (wave_of_workgroup ^ 4) * WN * 256 + lane;
+        const float4 *here = reinterpret_cast<const float4 *>(ring_of_workgroup) + wave_of_workgroup * WN * 256 + lane;
+        __syncthreads();  // the rings are read
+#pragma unroll
+        for (int bj = 0; bj < WN; ++bj)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float4 give;
+                give.x = group ? acc[0][bj][4 * i] : acc[1][bj][4 * i];
+                give.y = group ? acc[0][bj][4 * i + 1] : acc[1][bj][4 * i + 1];
+                give.z = group ? acc[0][bj][4 * i + 2] : acc[1][bj][4 * i + 2];
+                give.w = group ? acc[0][bj][4 * i + 3] : acc[1][bj][4 * i + 3];
+                there[(bj * 4 + i) * 64] = give;
+            }
+        __syncthreads();
+#pragma unroll
+        for (int bj = 0; bj < WN; ++bj)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float4 got = here[(bj * 4 + i) * 64];
+                c[0][bj][4 * i] = (group ? acc[1][bj][4 * i] : acc[0][bj][4 * i]) + got.x;
+                c[0][bj][4 * i + 1] = (group ? acc[1][bj][4 * i + 1] : acc[0][bj][4 * i + 1]) + got.y;
+                c[0][bj][4 * i + 2] = (group ? acc[1][bj][4 * i + 2] : acc[0][bj][4 * i + 2]) + got.z;
+                c[0][bj][4 * i + 3] = (group ? acc[1][bj][4 * i + 3] : acc[0][bj][4 * i + 3]) + got.w;
+            }
+    }
 
     // The recovery terms rt[m] + ct[n], rt = -2 cw PA, ct = K ca cw - 2 ca PW: one fp32 MFMA with k = 2 per block, A = (rt[m], 1),
     // B = (1, ct[n]); lane l supplies row resp. column l % 32 of k index l / 32.
-    float b_fin[WN], a_fin[WM], sw[WN];
+    float b_fin[WN], a_fin[WMO], sw[WN];
 #pragma unroll
     for (int bj = 0; bj < WN; ++bj) {
         const float ct = (float)(int32_t)((uint32_t)k_arg * ca * cw - 2u * ca * use_here(w_sum_raw[bj]));
@@ -295,14 +347,14 @@ __global__ __launch_bounds__(256, OCC) void gemm_mfma_lds_kernel(const uint32_t 
         sw[bj] = half_bits_to_float((uint16_t)use_here(sw_raw[bj]));
     }
 #pragma unroll
-    for (int bi = 0; bi < WM; ++bi) {
+    for (int bi = 0; bi < WMO; ++bi) {
         const float rt = -(float)(2u * cw * use_here(a_sum_raw[bi]));
         a_fin[bi] = kh == 0 ? rt : 1.0f;
     }
 #pragma unroll
-    for (int bi = 0; bi < WM; ++bi)
+    for (int bi = 0; bi < WMO; ++bi)
 #pragma unroll
-        for (int bj = 0; bj < WN; ++bj) acc[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x2f32(a_fin[bi], b_fin[bj], acc[bi][bj], 0, 0, 0);
+        for (int bj = 0; bj < WN; ++bj) c[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x2f32(a_fin[bi], b_fin[bj], c[bi][bj], 0, 0, 0);
 
     // Store, as in apmm_gemm_mfma_direct.h: one pass per output, fp16 in pairs of columns where the addresses allow it.  Inner tiles
     // with streaming stores whatever is written: with outputs that are not in the last-level cache from the call before, plain ones
@@ -320,7 +372,7 @@ __global__ __launch_bounds__(256, OCC) void gemm_mfma_lds_kernel(const uint32_t 
             return half_bits_to_float((uint16_t)h);
         };
 #pragma unroll
-        for (int bi = 0; bi < WM; ++bi) {
+        for (int bi = 0; bi < WMO; ++bi) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int64_t row = (int64_t)(bi * 32 + 8 * (v / 4) + (v % 4));
@@ -331,17 +383,17 @@ __global__ __launch_bounds__(256, OCC) void gemm_mfma_lds_kernel(const uint32_t 
 #pragma unroll
                 for (int bj = 0; bj < WN; ++bj) {
                     if (GUARD && n_lane + bj * 32 >= N) continue;
-                    const float c = acc[bi][bj][v];
-                    if constexpr (I32 && NT) __builtin_nontemporal_store((int32_t)c, &ci[row * N + bj * 32]);
-                    if constexpr (I32 && !NT) ci[row * N + bj * 32] = (int32_t)c;
+                    const float x = c[bi][bj][v];
+                    if constexpr (I32 && NT) __builtin_nontemporal_store((int32_t)x, &ci[row * N + bj * 32]);
+                    if constexpr (I32 && !NT) ci[row * N + bj * 32] = (int32_t)x;
                     if constexpr (F16 && !PAIR) {
-                        if constexpr (NT) __builtin_nontemporal_store(float_to_half_bits(c * sa * sw[bj]), &ch[row * N + bj * 32]);
-                        else ch[row * N + bj * 32] = float_to_half_bits(c * sa * sw[bj]);
+                        if constexpr (NT) __builtin_nontemporal_store(float_to_half_bits(x * sa * sw[bj]), &ch[row * N + bj * 32]);
+                        else ch[row * N + bj * 32] = float_to_half_bits(x * sa * sw[bj]);
                     }
                     if constexpr (F16 && PAIR) {
                         if (v % 2 == 0) {
-                            const uint32_t h0 = float_to_half_bits(c * sa * sw[bj]);
-                            const uint32_t h1 = float_to_half_bits(acc[bi][bj][(v + 1) & 15] * sa_next * sw[bj]);
+                            const uint32_t h0 = float_to_half_bits(x * sa * sw[bj]);
+                            const uint32_t h1 = float_to_half_bits(c[bi][bj][(v + 1) & 15] * sa_next * sw[bj]);
                             const uint32_t give = odd ? h0 : h1, keep = odd ? h1 : h0;
                             const uint32_t got = (uint32_t)__builtin_amdgcn_mov_dpp((int)give, 0xB1, 0xf, 0xf, true);
                             const uint32_t word = odd ? (got | (keep << 16)) : (keep | (got << 16));
@@ -371,6 +423,27 @@ __global__ __launch_bounds__(256, OCC) void gemm_mfma_lds_kernel(const uint32_t 
 }
 
 template <int P, int Q, int WM, int WN, int OCC>
+__global__ __launch_bounds__(256, OCC) void gemm_mfma_lds_kernel(const uint32_t *a, const uint32_t *w, int32_t *c_i32, uint16_t *c_f16, int m, int n, int k,
+                                                                 int nkb, int tiles_n, int tiles_m_band, const uint16_t *w_scale,
+                                                                 const uint16_t *a_scale)
+{
+    extern __shared__ __align__(16) uint4 lds_ring[];
+    lds_tile<P, Q, WM, WN, 1>(lds_ring, a, w, c_i32, c_f16, m, n, k, nkb, tiles_n, tiles_m_band, w_scale, a_scale);
+}
+
+template <int P, int Q>
+inline int lds_tile_order(int64_t tiles_m, int64_t K)  // tiles_m < 2^28
+{
+    // Order of the tiles.  Four tile rows walked column by column let the workgroups that run together on an XCD share the packed rows
+    // of four tile rows and of the columns under way in its L2; row by row, they write longer runs of C.  The latter pays where the
+    // operands are light.  Microseconds, row by row / in fours, both outputs: 4096 x 11008 x 1024 W2A4 65 / 71, W2A2 65 / 69, W1A2 64 /
+    // 69, W4A4 76 / 69; 3000 x 8000 x 700 W2A4 40 / 39, W4A4 44 / 40; 2048 x 11008 x 4096 W2A2 57 / 53, W4A4 79 / 71.  (In eights: W2A4 4096 x
+    // 11008 x 1024 78, 2048 x 11008 x 4096 W2A4 63 against 60.)
+    const int band_log = Q <= 2 && K <= 1024 ? 0 : 2;
+    return (int)tiles_m | band_log << 28;
+}
+
+template <int P, int Q, int WM, int WN, int OCC>
 hipError_t launch_lds_variant(const GemmArgs &g, hipStream_t stream)
 {
     using L = LdsTile<P, Q, WM, WN>;
@@ -378,13 +451,7 @@ hipError_t launch_lds_variant(const GemmArgs &g, hipStream_t stream)
     const int64_t tiles_m = (g.M + 64 * WM - 1) / (64 * WM), tiles_n = (g.N + 64 * WN - 1) / (64 * WN);
     const int64_t tiles = tiles_m * tiles_n;
     if (tiles > 0x7fffffffLL || tiles_m >= (1 << 28) || g.M > 0x7fffffffLL || g.N > 0x7fffffffLL || g.K > 0x7fffffffLL) return hipErrorInvalidValue;
-    // Order of the tiles.  Four tile rows walked column by column let the workgroups that run together on an XCD share the packed rows
-    // of four tile rows and of the columns under way in its L2; row by row, they write longer runs of C.  The latter pays where the
-    // operands are light.  Microseconds, row by row / in fours, both outputs: 4096 x 11008 x 1024 W2A4 65 / 71, W2A2 65 / 69, W1A2 64 /
-    // 69, W4A4 76 / 69; 3000 x 8000 x 700 W2A4 40 / 39, W4A4 44 / 40; 2048 x 11008 x 4096 W2A2 57 / 53, W4A4 79 / 71.  (In eights: W2A4 4096 x
-    // 11008 x 1024 78, 2048 x 11008 x 4096 W2A4 63 against 60.)
-    const int band_log = Q <= 2 && g.K <= 1024 ? 0 : 2;
-    const int tiles_m_band = (int)tiles_m | band_log << 28;
+    const int tiles_m_band = lds_tile_order<P, Q>(tiles_m, g.K);
     auto kernel = gemm_mfma_lds_kernel<P, Q, WM, WN, OCC>;
     static thread_local int prepared_device = -1;  // the LDS limit is a per-device attribute of the function
     int dev = 0;

@@ -1039,6 +1039,24 @@ def test_k_split_128_by_128_tile(gpu, oracle, M, N, outs, p, q):
         assert bool(((c16.double() - f).abs() <= 1e-3 * f.abs() + 1e-6).all())
 
 
+@pytest.mark.parametrize("p,q,K,long", [(1, 3, 9216, False), (3, 4, 9216, False), (1, 4, 9217, True), (2, 3, 9400, True), (4, 4, 9730, True),
+                                        (3, 3, 11008, True), (2, 2, 13000, False)])
+def test_k_split_128_by_128_tile_from_lds_and_from_registers(gpu, p, q, K, long):
+    """Both sides of the line between the two forms of the tile, and half of K an odd and an even number of stages."""
+    torch, binding = gpu
+    dev = torch.device("cuda:0")
+    M, N = 770, 4100
+    g = torch.Generator(device=dev).manual_seed(8660 + 10 * p + q)
+    a = torch.randint(0, 1 << p, (M, K), generator=g, device=dev, dtype=torch.uint8)
+    w = torch.randint(0, 1 << q, (N, K), generator=g, device=dev, dtype=torch.uint8)
+    c32, c16 = binding.apmm_gemm(M, N, K, p, q, binding.apmm_pack_activations(a, p), binding.apmm_pack_weights(w, q), want_f16=True)
+    name = "gemm_mfma_ksplit_long_kernel<%d,%d>" % (p, q) if long else "gemm_mfma_ksplit_kernel<%d,%d,4,4>" % (p, q)
+    assert binding.apmm_last_gemm_kernel() == name
+    want = ((2.0 * a.float() - ((1 << p) - 1)).double() @ (2.0 * w.float() - ((1 << q) - 1)).double().t().contiguous()).to(torch.int64)
+    assert torch.equal(c32.to(torch.int64), want)
+    assert torch.equal(c16, want.float().half())
+
+
 @pytest.mark.parametrize("p,q,K", [(1, 2, 9216), (2, 2, 9216), (4, 2, 10752), (3, 2, 10752), (2, 3, 3584), (4, 1, 12800)])
 def test_k_split_128_by_128_tile_leaves_smaller_k_to_the_large_tiles(gpu, p, q, K):
     """The other side of each line."""

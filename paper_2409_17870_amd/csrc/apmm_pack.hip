@@ -360,11 +360,114 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const uint8_t *__restric
 // WAVES waves of a workgroup share a row, one 32-element group per lane and step, so that a row takes one or two round
 // trips to memory however long it is.  With one wave per row, the earlier form, a lane worked through up to eleven groups
 // in turn.  Four bits, one launch inside a graph: 16 x 5120 6.0 -> 3.2 us, 16 x 13824 12.5 -> 4.1 us, 1024 x 11008 15.1 ->
-// 13.0 us; two bits 4096 x 4096 12.5 -> 10.0 us.  Large matrices are bound by the phases (read, quantise, write) that every
-// resident workgroup goes through at the same time: 2.4 - 3.8 TB/s.
+// 13.0 us; two bits 4096 x 4096 12.5 -> 10.0 us.  Large matrices in the field form are bound by their scattered stores: those go to
+// quantize_fields_kernel.
 // The eight rows that share the 128-byte lines of a slot are packed on one XCD, whose L2 joins their 16-byte pieces.
 typedef unsigned short us2 __attribute__((ext_vector_type(2)));
 constexpr int kCachedGroups = 2;  // 32-element groups per lane kept in registers
+
+// h[i] = elements 2i, 2i+1 of group kg as two binary16 bit patterns; elements past K read as +0
+template <bool WHOLE>
+__device__ __forceinline__ void load_halves(const uint16_t *xrow, int64_t K, int64_t kg, uint32_t (&h)[16])
+{
+    const int64_t k0 = kg * 32;
+    if (k0 + 32 <= K) {
+        const AnyVec *src = reinterpret_cast<const AnyVec *>(xrow + k0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const AnyVec q = src[v];
+            h[4 * v] = q.x; h[4 * v + 1] = q.y; h[4 * v + 2] = q.z; h[4 * v + 3] = q.w;
+        }
+    } else if (!WHOLE && K >= 2) {  // the row's end: dwords clamped to the last two elements, those before position k shifted out
+        const int last = (int)(K - 2 - k0);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) h[i] = reinterpret_cast<const AnyWord *>(xrow + k0 + (2 * i < last ? 2 * i : last))->x;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int past = 2 * i - last;
+            h[i] = past <= 0 ? h[i] : past == 1 ? h[i] >> 16 : 0u;
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) h[i] = 0u;
+        if (!WHOLE && kg == 0) h[0] = xrow[0];
+    }
+}
+
+__device__ __forceinline__ us2 fold_max(us2 m, const uint32_t (&h)[16])
+{
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const uint32_t mag = h[i] & 0x7fff7fffu;  // |x| orders like its bit pattern
+        m = __builtin_elementwise_max(m, us2{(unsigned short)(mag & 0xffffu), (unsigned short)(mag >> 16)});
+    }
+    return m;
+}
+
+// The grid of a row from its largest magnitude
+struct Grid {
+    float half_r, mid, top;
+    uint16_t scale;
+    __device__ __forceinline__ Grid(uint32_t max_bits, int bits)
+    {
+        const float amax = __half2float(__ushort_as_half((uint16_t)max_bits));
+        mid = (float)(1u << (bits - 1));
+        top = (float)((1u << bits) - 1u);
+        const __half sh = __float2half_rn(amax / top);
+        const float s = __half2float(sh);
+        scale = __half_as_ushort(sh);
+        half_r = s > 0.0f ? (1.0f / s) * 0.5f : 0.0f;  // scale 0: every code becomes 2^(bits-1)
+    }
+    // code of element i of a group as a float
+    __device__ __forceinline__ float code(const uint32_t (&h)[16], int i) const
+    {
+        const uint32_t pair = h[i >> 1];
+        const float xf = __half2float(__ushort_as_half((uint16_t)((i & 1) ? pair >> 16 : pair & 0xffffu)));
+        // t = x / (2 s) up to 2^-23 relative (rounded reciprocal, rounded product); the cell is floor of
+        // the exact quotient.  An exact quotient that is an integer c (x on a border, ties upward) may
+        // come out just below c; any other exact quotient is at least 2^-12 away from every integer
+        // (x and 2 c s are binary16 numbers times small integers), and |t| <= 129.  Moving t up by
+        // 2^-21 |t| (between 2^-23 |t| and 2^-12) therefore gives the exact floor in every case.
+        const float t = fmaf(xf, half_r, 0.0f);  // the rounded product, with the conversion of xf in the same instruction
+        const float u = floorf(fmaf(fabsf(t), 0x1p-21f, t)) + mid;  // exact: |floor| is far below 2^24
+        return __builtin_amdgcn_fmed3f(u, 0.0f, top);
+    }
+};
+
+// The six field words of group kg from its halves h (elements past K: the all-ones padding code); adds the codes to `sum`.
+// Four fields of six bits make an integer below 2^24, which a float holds: three fused multiply-adds and one conversion for four
+// codes, and the group's code sum.
+template <bool WHOLE>
+__device__ __forceinline__ void quantize_fields(const Grid &grid, int64_t K, int64_t kg, const uint32_t (&h)[16], uint32_t &sum, uint32_t (&dw)[6])
+{
+    const bool whole = WHOLE || kg * 32 + 32 <= K;
+    auto code = [&](int i) __attribute__((always_inline)) { return !whole && kg * 32 + i >= K ? grid.top : grid.code(h, i); };
+    uint32_t quad[8];
+    float total = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {  // fields 4 i .. 4 i + 3: elements c = 2 (i % 2), 2 (i % 2) + 1, jh = 0, 1 of t = i / 2
+        const int at = 8 * (i >> 1) + 2 * (i & 1);
+        const float u0 = code(at), u1 = code(at + 4), u2 = code(at + 1), u3 = code(at + 5);
+        total += (u0 + u1) + (u2 + u3);
+        quad[i] = (uint32_t)fmaf(u3, 262144.f, fmaf(u2, 4096.f, fmaf(u1, 64.f, u0)));
+    }
+    sum += (uint32_t)total;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        dw[3 * i] = quad[4 * i] | (quad[4 * i + 1] << 24);
+        dw[3 * i + 1] = (quad[4 * i + 1] >> 8) | (quad[4 * i + 2] << 16);
+        dw[3 * i + 2] = (quad[4 * i + 2] >> 16) | (quad[4 * i + 3] << 8);
+    }
+}
+// The same of a group of padding (every plane bit set), or zero words for a padding row
+__device__ __forceinline__ void fill_fields(uint32_t fill, uint32_t &sum, uint32_t (&dw)[6])
+{
+    const uint32_t quad = fill * 0x41041u;
+    dw[0] = dw[3] = quad | (quad << 24);
+    dw[1] = dw[4] = (quad >> 8) | (quad << 16);
+    dw[2] = dw[5] = (quad >> 16) | (quad << 8);
+    sum += 32u * fill;
+}
 
 template <int WAVES, bool WHOLE, bool FIELD>
 __global__ __launch_bounds__(kThreads) void quantize_pack_kernel(const uint16_t *__restrict__ x, int64_t rows,
@@ -381,40 +484,6 @@ __global__ __launch_bounds__(kThreads) void quantize_pack_kernel(const uint16_t 
     const int64_t groups = nkb * kWordsPerRow;
     const uint16_t *xrow = x + row * K;
 
-    // h[i] = elements 2i, 2i+1 of group kg as two binary16 bit patterns; elements past K read as +0
-    auto load_halves = [&](int64_t kg, uint32_t (&h)[16]) __attribute__((always_inline)) {
-        const int64_t k0 = kg * 32;
-        if (k0 + 32 <= K) {
-            const AnyVec *src = reinterpret_cast<const AnyVec *>(xrow + k0);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const AnyVec q = src[v];
-                h[4 * v] = q.x; h[4 * v + 1] = q.y; h[4 * v + 2] = q.z; h[4 * v + 3] = q.w;
-            }
-        } else if (!WHOLE && K >= 2) {  // the row's end: dwords clamped to the last two elements, those before position k shifted out
-            const int last = (int)(K - 2 - k0);
-#pragma unroll
-            for (int i = 0; i < 16; ++i) h[i] = reinterpret_cast<const AnyWord *>(xrow + k0 + (2 * i < last ? 2 * i : last))->x;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int past = 2 * i - last;
-                h[i] = past <= 0 ? h[i] : past == 1 ? h[i] >> 16 : 0u;
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) h[i] = 0u;
-            if (!WHOLE && kg == 0) h[0] = xrow[0];
-        }
-    };
-    auto fold_max = [](us2 m, const uint32_t (&h)[16]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const uint32_t mag = h[i] & 0x7fff7fffu;  // |x| orders like its bit pattern
-            m = __builtin_elementwise_max(m, us2{(unsigned short)(mag & 0xffffu), (unsigned short)(mag >> 16)});
-        }
-        return m;
-    };
-
     const bool live = row < rows;
     const int64_t live_groups = live ? (K + 31) / 32 : 0;  // groups that hold at least one element
     uint32_t cache[kCachedGroups][16];
@@ -423,13 +492,13 @@ __global__ __launch_bounds__(kThreads) void quantize_pack_kernel(const uint16_t 
     for (int it = 0; it < kCachedGroups; ++it) {
         const int64_t kg = tid + T * it;
         if (kg < live_groups) {
-            load_halves(kg, cache[it]);
+            load_halves<WHOLE>(xrow, K, kg, cache[it]);
             m2 = fold_max(m2, cache[it]);
         }
     }
     for (int64_t kg = tid + T * kCachedGroups; kg < live_groups; kg += T) {
         uint32_t h[16];
-        load_halves(kg, h);
+        load_halves<WHOLE>(xrow, K, kg, h);
         m2 = fold_max(m2, h);
     }
     uint32_t mbits = m2[0] > m2[1] ? m2[0] : m2[1];
@@ -448,53 +517,20 @@ __global__ __launch_bounds__(kThreads) void quantize_pack_kernel(const uint16_t 
             mbits = o > mbits ? o : mbits;
         }
     }
-    const float amax = __half2float(__ushort_as_half((uint16_t)mbits));
-    const uint32_t top = (1u << bits) - 1u;
-    const __half sh = __float2half_rn(amax / (float)top);
-    const float s = __half2float(sh);
-    if (live && tid == 0) scale_out[row] = __half_as_ushort(sh);
-    const float half_r = s > 0.0f ? (1.0f / s) * 0.5f : 0.0f;  // scale 0: every code becomes 2^(bits-1)
-    const float mid = (float)(1u << (bits - 1)), ftop = (float)top;
+    const Grid grid(mbits, bits);
+    if (live && tid == 0) scale_out[row] = grid.scale;
 
     const uint32_t flip = byte_form(bits) && live ? 0x80808080u : 0u;
     uint32_t sum = 0;
     // codes of group kg from its halves h (elements past K: the all-ones padding code), then the packing
     auto quantize_group = [&](int64_t kg, const uint32_t (&h)[16]) __attribute__((always_inline)) {
-        const bool whole = WHOLE || kg * 32 + 32 <= K;
-        auto code = [&](int i) __attribute__((always_inline)) {  // of element i, as a float
-            const uint32_t pair = h[i >> 1];
-            const float xf = __half2float(__ushort_as_half((uint16_t)((i & 1) ? pair >> 16 : pair & 0xffffu)));
-            // t = x / (2 s) up to 2^-23 relative (rounded reciprocal, rounded product); the cell is floor of
-            // the exact quotient.  An exact quotient that is an integer c (x on a border, ties upward) may
-            // come out just below c; any other exact quotient is at least 2^-12 away from every integer
-            // (x and 2 c s are binary16 numbers times small integers), and |t| <= 129.  Moving t up by
-            // 2^-21 |t| (between 2^-23 |t| and 2^-12) therefore gives the exact floor in every case.
-            const float t = fmaf(xf, half_r, 0.0f);  // the rounded product, with the conversion of xf in the same instruction
-            const float u = floorf(fmaf(fabsf(t), 0x1p-21f, t)) + mid;  // exact: |floor| is far below 2^24
-            return !whole && kg * 32 + i >= K ? ftop : __builtin_amdgcn_fmed3f(u, 0.0f, ftop);
-        };
         if constexpr (FIELD) {
-            // four fields of six bits make an integer below 2^24, which a float holds: three fused multiply-adds and one
-            // conversion for four codes, and the group's code sum
-            uint32_t quad[8];
-            float total = 0.f;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {  // fields 4 i .. 4 i + 3: elements c = 2 (i % 2), 2 (i % 2) + 1, jh = 0, 1 of t = i / 2
-                const int at = 8 * (i >> 1) + 2 * (i & 1);
-                const float u0 = code(at), u1 = code(at + 4), u2 = code(at + 1), u3 = code(at + 5);
-                total += (u0 + u1) + (u2 + u3);
-                quad[i] = (uint32_t)fmaf(u3, 262144.f, fmaf(u2, 4096.f, fmaf(u1, 64.f, u0)));
-            }
-            sum += (uint32_t)total;
             uint32_t dw[6];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                dw[3 * i] = quad[4 * i] | (quad[4 * i + 1] << 24);
-                dw[3 * i + 1] = (quad[4 * i + 1] >> 8) | (quad[4 * i + 2] << 16);
-                dw[3 * i + 2] = (quad[4 * i + 2] >> 16) | (quad[4 * i + 3] << 8);
-            }
+            quantize_fields<WHOLE>(grid, K, kg, h, sum, dw);
             store_fields(packed, row, nkb, kg, dw);
         } else {
+            const bool whole = WHOLE || kg * 32 + 32 <= K;
+            auto code = [&](int i) __attribute__((always_inline)) { return !whole && kg * 32 + i >= K ? grid.top : grid.code(h, i); };
             uint32_t d[8];
 #pragma unroll
             for (int t4 = 0; t4 < 8; ++t4) {
@@ -507,12 +543,10 @@ __global__ __launch_bounds__(kThreads) void quantize_pack_kernel(const uint16_t 
     };
     auto fill_group = [&](int64_t kg) __attribute__((always_inline)) {
         // a whole group of padding (every plane bit set) or a padding row (zero words)
-        const uint32_t fill = live ? top : 0u;
+        const uint32_t fill = live ? (1u << bits) - 1u : 0u;
         if constexpr (FIELD) {
-            const uint32_t quad = fill * 0x41041u;
-            const uint32_t w0 = quad | (quad << 24), w1 = (quad >> 8) | (quad << 16), w2 = (quad >> 16) | (quad << 8);
-            const uint32_t dw[6] = {w0, w1, w2, w0, w1, w2};
-            sum += 32u * fill;
+            uint32_t dw[6];
+            fill_fields(fill, sum, dw);
             store_fields(packed, row, nkb, kg, dw);
         } else {
             uint32_t d[8];
@@ -542,7 +576,7 @@ __global__ __launch_bounds__(kThreads) void quantize_pack_kernel(const uint16_t 
             uint32_t h[16];
 #pragma unroll
             for (int i = 0; i < 16; ++i) h[i] = 0u;
-            if (kg < live_groups) load_halves(kg, h);
+            if (kg < live_groups) load_halves<WHOLE>(xrow, K, kg, h);
             quantize_group(kg, h);
         } else {
             fill_group(kg);
@@ -558,6 +592,90 @@ __global__ __launch_bounds__(kThreads) void quantize_pack_kernel(const uint16_t 
         for (int w = 0; w < WAVES; ++w) sum += joint[1][sub * WAVES + w];
     }
     if (tid == 0) packed[row_sum_word(rows_p, nkb, FIELD ? 6 : bits) + row] = sum;
+}
+
+// The same for the field form of many rows: the words of four rows meet in LDS and are written in runs of 64 bytes (a slot of four rows),
+// where the kernel above writes pieces of 16 and 8 bytes, 3 KB apart.  Those pieces were what bound it: 1024 x 11008 13.1 us, without
+// its stores 8.8.  Eight waves to a workgroup, two to a row; a row stays in registers (GROUPS of 32 elements to a lane).
+constexpr int kQuantRows = 4;
+constexpr int kQuantThreads = 512, kQuantLanes = kQuantThreads / kQuantRows;       // of a row
+constexpr int kQuantBlockWords = 6 * kQuantRows * kWordsPerRow + kWordsPerRow;  // a k block in LDS, with 16 bytes against bank conflicts
+template <int GROUPS, bool WHOLE>
+__global__ __launch_bounds__(kQuantThreads) void quantize_fields_kernel(const uint16_t *__restrict__ x, int64_t rows, int64_t K, int bits,
+                                                                        uint32_t *__restrict__ packed, uint16_t *__restrict__ scale_out,
+                                                                        int64_t rows_p, int64_t nkb)
+{
+    extern __shared__ __align__(16) uint32_t fields[];  // [k block][slot][row of the workgroup][word]
+    __shared__ uint32_t joint[2][kQuantThreads / 64];
+    constexpr int C = 8 / kQuantRows;
+    const int sub = threadIdx.x / kQuantLanes, tid = threadIdx.x % kQuantLanes, wave = threadIdx.x / 64;
+    const int xcd = blockIdx.x % 8, turn = blockIdx.x / 8;  // the eight rows that share a 128-byte line: on one XCD
+    const int64_t row0 = (((int64_t)(turn / C) * 8 + xcd) * C + turn % C) * kQuantRows, row = row0 + sub;
+    if (row0 >= rows_p) return;  // (rows_p is a multiple of the workgroup's rows)
+    const bool live = row < rows;
+    const int groups = (int)nkb * kWordsPerRow, live_groups = live ? (int)((K + 31) / 32) : 0;
+    const uint16_t *xrow = x + row * K;
+    uint32_t h[GROUPS][16];
+    us2 m2 = {0, 0};
+#pragma unroll
+    for (int it = 0; it < GROUPS; ++it) {
+        const int kg = tid + kQuantLanes * it;
+        if (kg < live_groups) {
+            load_halves<WHOLE>(xrow, K, kg, h[it]);
+            m2 = fold_max(m2, h[it]);
+        }
+    }
+    uint32_t mbits = m2[0] > m2[1] ? m2[0] : m2[1];
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        const uint32_t o = __shfl_xor(mbits, off);
+        mbits = o > mbits ? o : mbits;
+    }
+    if ((threadIdx.x & 63) == 0) joint[0][wave] = mbits;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kQuantLanes / 64; ++w) {
+        const uint32_t o = joint[0][sub * (kQuantLanes / 64) + w];
+        mbits = o > mbits ? o : mbits;
+    }
+    const Grid grid(mbits, bits);
+    if (live && tid == 0) scale_out[row] = grid.scale;
+    uint32_t sum = 0;
+#pragma unroll
+    for (int it = 0; it < GROUPS; ++it) {
+        const int kg = tid + kQuantLanes * it;
+        if (kg >= groups) continue;
+        uint32_t dw[6];
+        if (kg < live_groups) quantize_fields<WHOLE>(grid, K, kg, h[it], sum, dw);
+        else fill_fields(live ? (1u << bits) - 1u : 0u, sum, dw);
+        const int kb = kg / kWordsPerRow, ks = kg % kWordsPerRow;
+        constexpr int slot = kQuantRows * kWordsPerRow;
+        uint32_t *base = fields + kb * kQuantBlockWords + 3 * (ks >> 1) * slot + sub * kWordsPerRow;
+        if ((ks & 1) == 0) {
+            *reinterpret_cast<uint4 *>(base) = make_uint4(dw[0], dw[1], dw[2], dw[3]);
+            *reinterpret_cast<uint2 *>(base + slot) = make_uint2(dw[4], dw[5]);
+        } else {
+            *reinterpret_cast<uint2 *>(base + slot + 2) = make_uint2(dw[0], dw[1]);
+            *reinterpret_cast<uint4 *>(base + 2 * slot) = make_uint4(dw[2], dw[3], dw[4], dw[5]);
+        }
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
+    if ((threadIdx.x & 63) == 0) joint[1][wave] = sum;
+    __syncthreads();
+    if (tid == 0) {
+        uint32_t all = 0;
+#pragma unroll
+        for (int w = 0; w < kQuantLanes / 64; ++w) all += joint[1][sub * (kQuantLanes / 64) + w];
+        packed[row_sum_word(rows_p, nkb, 6) + row] = all;
+    }
+    const int pieces = (int)nkb * 6 * kQuantRows;
+    uint32_t *out = packed + tile_row_word(row0, 0, nkb, 6, 0);
+    for (int i = threadIdx.x; i < pieces; i += kQuantThreads) {
+        const int of_row = i % kQuantRows, slot = i / kQuantRows;  // slot of all k blocks
+        const uint4 v = *reinterpret_cast<const uint4 *>(fields + slot / 6 * kQuantBlockWords + (slot % 6 * kQuantRows + of_row) * kWordsPerRow);
+        *reinterpret_cast<uint4 *>(out + (int64_t)slot * kPlaneWords + of_row * kWordsPerRow) = v;
+    }
 }
 
 __global__ __launch_bounds__(kThreads) void unpack_kernel(const uint32_t *__restrict__ packed, int64_t rows,
@@ -691,11 +809,26 @@ hipError_t launch_quantize_pack(const uint16_t *x, int64_t rows, int64_t K, int 
     const int64_t rows_p = round_up(rows, kRowBlock);
     const int64_t nkb = round_up(K, kKPad) / kKBlock;
     if (rows_p == 0) return hipSuccess;
+    const bool whole = K % 128 == 0;  // every k block is packed whole or is all padding
+    const int64_t lane_groups = (nkb * kWordsPerRow + kQuantLanes - 1) / kQuantLanes;
+    // Many rows in the field form: four rows to a workgroup.  Old / new, microseconds: 640 x 4096 5.2 / 4.6, 1024 x 4096 6.0 / 5.1, 1024 x 11008
+    // 13.1 / 10.1, 4096 x 2048 9.5 / 7.6, 4096 x 11008 48.5 / 28.7; on the other side 512 x 5120 4.8 / 5.8, 512 x 13824 8.9 / 9.4, 1024 x 2048 4.1 /
+    // 4.4, 4096 x 1500 9.8 / 10.5, 16 x 5120 3.2 / 4.9.
+    if (field && rows > 512 && K >= 2048 && rows * K >= 2500000 && lane_groups <= 4) {
+        const size_t lds = (size_t)nkb * kQuantBlockWords * 4;  // at most 51 KB
+        const int64_t blocks = (rows_p / kQuantRows + 15) / 16 * 16;  // pairs for each of the eight XCDs
+        if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+        auto kernel = lane_groups == 1 ? (whole ? quantize_fields_kernel<1, true> : quantize_fields_kernel<1, false>)
+                    : lane_groups == 2 ? (whole ? quantize_fields_kernel<2, true> : quantize_fields_kernel<2, false>)
+                    : lane_groups == 3 ? (whole ? quantize_fields_kernel<3, true> : quantize_fields_kernel<3, false>)
+                                       : (whole ? quantize_fields_kernel<4, true> : quantize_fields_kernel<4, false>);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kQuantThreads), lds, stream, x, rows, K, bits, packed, scale, rows_p, nkb);
+        return hipGetLastError();
+    }
     // waves per row: a group of 32 elements for every lane, as far as the row goes
     const int waves = nkb <= 16 ? 1 : nkb <= 32 ? 2 : 4;
     const int64_t blocks = (rows_p + 63) / 64 * 64 * waves / (kThreads / 64);  // eight rows for each of the eight XCDs
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    const bool whole = K % 128 == 0;  // every k block is packed whole or is all padding
     decltype(&quantize_pack_kernel<1, true, true>) kernel;
     if (field)
         kernel = waves == 1 ? (whole ? quantize_pack_kernel<1, true, true> : quantize_pack_kernel<1, false, true>)

@@ -672,6 +672,27 @@ def test_packing_row_ends_and_alignments(gpu, oracle, M, K, shift, p):
     assert torch.equal(got, binding.apmm_pack_activations(torch.from_numpy(want_codes).to(dev), p))
 
 
+@pytest.mark.parametrize("M,K,p,shift", [(641, 4097, 4, 1), (700, 3600, 3, 0), (1225, 2048, 4, 0), (513, 16384, 4, 0), (520, 15800, 3, 3),
+                                         (515, 8193, 3, 1), (642, 4096, 4, 5), (514, 12288, 4, 0)])
+def test_quantize_many_rows_in_the_field_form(gpu, oracle, M, K, p, shift):
+    """The kernel for many rows (one to four groups of 32 elements to a lane, whole and ragged rows, any alignment, padding rows in
+    its last workgroups, idle workgroups) and its border rows: codes, scales and packed words as the oracle has them."""
+    torch, binding = gpu
+    dev = torch.device("cuda:0")
+    x = inputs.normal_features_f16(8050 + M + K + p, inputs.TAG_A, M, K, outlier_every=37)
+    x[3] = 0
+    x[4, :-1] = 0                                                      # the largest magnitude is the row's last element
+    want_codes, want_scale = oracle.quantize_rows(x, p)
+    flat = torch.zeros(M * K + shift, dtype=torch.float16, device=dev)
+    flat[shift:] = torch.from_numpy(x).to(dev).flatten()
+    packed = torch.full((binding.apmm_packed_activation_bytes(M, K, p),), 0xa5, dtype=torch.uint8, device=dev)
+    packed, scale = binding.apmm_quantize_pack_activations(flat[shift:].view(M, K), p, out=packed)
+    assert np.array_equal(scale.cpu().numpy().view(np.uint16), want_scale)
+    again = torch.full_like(packed, 0x5a)
+    binding.apmm_pack_activations(torch.from_numpy(want_codes).to(dev), p, out=again)
+    assert torch.equal(packed, again)
+
+
 def test_quantized_activations_through_the_gemm(gpu, oracle):
     """float16 activations -> quantise + pack -> GEMM with the fp16 epilogue, against the oracle's
     quantiser, integer GEMM and double-precision scaling."""

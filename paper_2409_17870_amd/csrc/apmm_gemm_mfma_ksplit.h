@@ -56,6 +56,11 @@ __device__ __forceinline__ void ksplit_tile(float4 *red, const uint32_t *a_arg, 
     constexpr bool TIGHT = WM * WN == 4 && AF && Q > 2;
     auto hidden = [](uint32_t v) __attribute__((always_inline)) { return TIGHT ? use_here(v) : v; };
     constexpr int LOADS_A = HALF ? half_slots(P, AF) : SLOTS_A, LOADS_B = HALF ? half_slots(Q, false) : Q;
+    // Fields: the slot that two k steps share is copied by hand, a step ahead.  Left to itself the compiler copies it right behind the
+    // loads of a stage, in every second stage, and waits there for all of them.  512 x 5120 x 5120 W2A4 13.1 -> 12.6 us, W4A4 15.9 -> 15.2,
+    // W3A3 15.7 -> 14.6, 512 x 5120 x 13824 W2A4 24.0 -> 23.1.  (The 64 x 64 tile with 4-bit weights has no registers for the copies,
+    // the 128 x 128 tile is not faster.)
+    constexpr bool MID = AF && !HALF && !(WM * WN == 4 && Q == 4);
     constexpr uint32_t ca = (1u << P) - 1, cw = (1u << Q) - 1;
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
@@ -106,6 +111,7 @@ __device__ __forceinline__ void ksplit_tile(float4 *red, const uint32_t *a_arg, 
     v16f acc[WM][WN];
     uint4 ra[2][WM][LOADS_A], rb[2][WN][LOADS_B];  // raw words of a stage, by stage parity (HALF: by half of the k block)
     v4i af[2][AF ? 1 : WM];                  // formed fragments, by k step parity
+    uint2 am[2][MID ? WM : 1];               // fields: the words of an operand that share a slot with the neighbouring k step
     OperandFrag<Q> bf[2][WN];
 
     auto load_stage = [&](auto buf_c, int st) __attribute__((always_inline)) {
@@ -158,14 +164,16 @@ __device__ __forceinline__ void ksplit_tile(float4 *red, const uint32_t *a_arg, 
     // This wave's stages of the sweep of K.
     if (s_count > 0) {
         constexpr int PER_KS = NB;
-        constexpr int TASKS_A = AF ? 0 : 4 * WM, DB = operand_dwords(Q);
+        constexpr int TASKS_A = (MID ? 2 : AF ? 0 : 4) * WM, DB = operand_dwords(Q);
         constexpr int TASKS = TASKS_A + DB * WN;  // operand dwords to form per k step, A blocks first
         constexpr int TPM = (TASKS + PER_KS - 1) / PER_KS;
         auto form = [&](auto buf_c, auto ks_c, auto task_c) __attribute__((always_inline)) {
             constexpr int buf = decltype(buf_c)::value, ks = decltype(ks_c)::value, task = decltype(task_c)::value;
             if constexpr (task < TASKS_A) {
-                constexpr int f = task / 4, d = task % 4;
-                if constexpr (AF) {
+                constexpr int f = task / (MID ? 2 : 4), d = task % (MID ? 2 : 4);
+                if constexpr (MID) {
+                    if constexpr (d == 0) am[ks & 1][f].x = copy_here(vec_word<2 * (ks & 1)>(ra[buf][f][3 * (ks / 2) + 1]));
+                    else am[ks & 1][f].y = copy_here(vec_word<2 * (ks & 1) + 1>(ra[buf][f][3 * (ks / 2) + 1]));
                 } else if constexpr (HALF) af[ks & 1][f][d] = (int)half_operand_dword<P, buf, ks, d>(ra[buf][f]);
                 else af[ks & 1][f][d] = (int)operand_dword<P, ks, d>(ra[buf][f]);
             } else {
@@ -184,7 +192,8 @@ __device__ __forceinline__ void ksplit_tile(float4 *red, const uint32_t *a_arg, 
                 constexpr int ks = i / PER_KS, j = i % PER_KS, bi = j / WN, bj = j % WN;
                 constexpr int format_a = operand_format(P), format_b = operand_format(Q);
                 v8i a8;
-                if constexpr (AF) a8 = field_operand<ks>(ra[buf][bi]);
+                if constexpr (MID) a8 = field_operand<ks>(ra[buf][bi], am[ks & 1][bi]);
+                else if constexpr (AF) a8 = field_operand<ks>(ra[buf][bi]);
                 else a8 = widen(af[ks & 1][bi]);
                 acc[bi][bj] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
                     a8, widen(bf[ks & 1][bj]), acc[bi][bj], format_a, format_b, 0, operand_exponent(P, HALF ? 2 * buf + ks : ks), 0,

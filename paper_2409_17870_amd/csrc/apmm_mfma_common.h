@@ -94,11 +94,11 @@ __device__ __forceinline__ v8i field_operand(const uint4 (&raw)[NS])
 // The same for local k step KS of half a k block.  The middle slot of the three belongs half to either k step: `mid` is this step's
 // half of it, copied a step ahead (copy_here).  Left to itself the compiler makes these copies right behind the loads, each behind
 // a wait, and the look-ahead is lost.
-template <int KS>
-__device__ __forceinline__ v8i field_operand(const uint4 (&raw)[3], const uint2 &mid)
+template <int KS, int NS>
+__device__ __forceinline__ v8i field_operand(const uint4 (&raw)[NS], const uint2 &mid)
 {
-    const uint4 &own = raw[2 * KS];
-    if constexpr (KS == 1) return v8i{(int)mid.x, (int)mid.y, (int)own.x, (int)own.y, (int)own.z, (int)own.w, 0, 0};
+    const uint4 &own = raw[3 * (KS / 2) + 2 * (KS & 1)];
+    if constexpr (KS & 1) return v8i{(int)mid.x, (int)mid.y, (int)own.x, (int)own.y, (int)own.z, (int)own.w, 0, 0};
     else return v8i{(int)own.x, (int)own.y, (int)own.z, (int)own.w, (int)mid.x, (int)mid.y, 0, 0};
 }
 

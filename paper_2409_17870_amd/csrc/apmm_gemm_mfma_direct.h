@@ -368,8 +368,9 @@ __global__ __launch_bounds__(256) void gemm_mfma_direct_kernel(const uint32_t *a
     // runs (a 16 MiB fp16 output cost 7 us that way).  Rows are taken in pairs: the even lane of a lane pair
     // collects both columns of the first row, the odd lane both columns of the second row (one lane exchange),
     // and each stores one dword.
-    // NT (interior tiles, a single output): streaming stores.  They gain 3 - 15 % when one output is written (more
-    // the larger the output), and lose as much when the int32 and the fp16 pass follow each other.
+    // NT (interior tiles): streaming stores, but not for both outputs of the 256 x 256 tile.  Operands and outputs in rotation, both
+    // outputs, plain against streaming: 1024 x 4096 x 1024 W2A4 (128 x 128) 11.5 / 9.9 us, 1000 x 3000 x 2000 W2A2 14.1 / 12.9, 2048 x 4096 x
+    // 4096 (256 x 128) 22.9 / 22.8, 4096 x 4096 x 4096 (256 x 256) 40.4 / 42.6.
     auto emit = [&](auto guard_c, auto i32_c, auto f16_c, auto pair_c, auto nt_c) __attribute__((always_inline)) {
         constexpr bool GUARD = decltype(guard_c)::value, I32 = decltype(i32_c)::value, F16 = decltype(f16_c)::value,
                        PAIR = decltype(pair_c)::value, NT = decltype(nt_c)::value;
@@ -427,15 +428,15 @@ __global__ __launch_bounds__(256) void gemm_mfma_direct_kernel(const uint32_t *a
     } else {
         const bool interior = (m0 + BM <= g.M) && (n0 + BN <= g.N);
         const bool pair = (g.N & 1) == 0 && (reinterpret_cast<uintptr_t>(g.c_f16) & 3u) == 0;
-        const bool single = !(g.c_i32 && g.c_f16);
+        const bool stream = !(WM == 4 && WN == 4) || !(g.c_i32 && g.c_f16);
         // both outputs: one pass per output (a combined pass needs more registers than there are)
         if (g.c_i32) {
-            if (interior && single) emit(F{}, T{}, F{}, F{}, T{});
+            if (interior && stream) emit(F{}, T{}, F{}, F{}, T{});
             else if (interior) emit(F{}, T{}, F{}, F{}, F{});
             else emit(T{}, T{}, F{}, F{}, F{});
         }
         if (g.c_f16) {
-            if (interior && pair && single) emit(F{}, F{}, T{}, T{}, T{});
+            if (interior && pair && stream) emit(F{}, F{}, T{}, T{}, T{});
             else if (interior && pair) emit(F{}, F{}, T{}, T{}, F{});
             else if (interior) emit(F{}, F{}, T{}, F{}, F{});
             else emit(T{}, F{}, T{}, F{}, F{});

@@ -208,7 +208,6 @@ __global__ __launch_bounds__(256) void gemm_mfma_i8_kernel(const uint32_t *a_arg
     const uint16_t *sa_src = as_arg ? as_arg : reinterpret_cast<const uint16_t *>(a_sum);
     const uint16_t *sw_src = ws_arg ? ws_arg : reinterpret_cast<const uint16_t *>(w_sum);
     const bool pair_ok = (N & 1) == 0 && (reinterpret_cast<uintptr_t>(cf_arg) & 3u) == 0;
-    const bool single = !(ci_arg && cf_arg);
     uint32_t pa[16], sa_bits[16], pw[kWN], sw_bits[kWN];
     auto request_rows = [&](int64_t mb) __attribute__((always_inline)) {
 #pragma unroll
@@ -226,7 +225,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_i8_kernel(const uint32_t *a_arg
         pw[bj] = (uint32_t)w_sum[n];
         sw_bits[bj] = sw_src[n];
     }
-    // one 32 x 32 block; GUARD: border, every element tested; NT: streaming stores when one output is written
+    // one 32 x 32 block, an inner one with streaming stores
     auto store_block = [&](const v16i &s, int64_t mb, auto bj_c) __attribute__((always_inline)) {
         constexpr int bj = decltype(bj_c)::value;
         const int64_t n = n0 + 32 * bj + r32;
@@ -239,13 +238,13 @@ __global__ __launch_bounds__(256) void gemm_mfma_i8_kernel(const uint32_t *a_arg
         auto row = [&](int v) __attribute__((always_inline)) { return mb + 8 * (v / 4) + 4 * kh + (v % 4); };
         auto sa = [&](int v) __attribute__((always_inline)) { return half_bits_to_float((uint16_t)(as_arg ? sa_bits[v] : 0x3c00u)); };
         if (ci_arg) {
-            if (interior && single) {
+            if (interior) {
 #pragma unroll
                 for (int v = 0; v < 16; ++v) __builtin_nontemporal_store(c[v], ci_arg + row(v) * N + n);
             } else {
 #pragma unroll
                 for (int v = 0; v < 16; ++v)
-                    if (interior || (row(v) < M && n < N)) ci_arg[row(v) * N + n] = c[v];
+                    if (row(v) < M && n < N) ci_arg[row(v) * N + n] = c[v];
             }
         }
         if (cf_arg && interior && pair_ok) {
@@ -258,8 +257,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_i8_kernel(const uint32_t *a_arg
                 const uint32_t got = (uint32_t)__builtin_amdgcn_mov_dpp((int)give, 0xB1, 0xf, 0xf, true);
                 const uint32_t word = odd ? (got | (keep << 16)) : (keep | (got << 16));
                 uint32_t *dst = reinterpret_cast<uint32_t *>(cf_arg + (row(v) + (odd ? 1 : 0)) * N + n - (odd ? 1 : 0));
-                if (single) __builtin_nontemporal_store(word, dst);
-                else *dst = word;
+                __builtin_nontemporal_store(word, dst);
             }
         } else if (cf_arg) {
 #pragma unroll

@@ -38,12 +38,34 @@ __device__ __forceinline__ uint32_t nibble_word(uint32_t lo, uint32_t hi)
 // and product: 103 -> 47 us).
 struct __attribute__((packed, aligned(1))) AnyVec { uint32_t x, y, z, w; };
 struct __attribute__((packed, aligned(1))) AnyWord { uint32_t x; };
+struct __attribute__((packed, aligned(4))) WordVec { uint32_t x, y, z, w; };
+
+// The 4 NW bytes from `src` on, at any alignment, out of whole dwords: a 16-byte load that does not start at a dword takes several
+// times as long (5003 x 3001 three-bit codes 9.6 -> 7.1 us; 5003 x 3008 5.9).  Every dword read holds one of the bytes.
+template <int NW>
+__device__ __forceinline__ void load_bytes(const void *src, uint32_t (&d)[NW])
+{
+    const uint32_t shift = (uint32_t)reinterpret_cast<uintptr_t>(src) & 3u;
+    const uint32_t *words = reinterpret_cast<const uint32_t *>(reinterpret_cast<uintptr_t>(src) - shift);
+    uint32_t w[NW + 1];
+#pragma unroll
+    for (int i = 0; i < NW / 4; ++i) {
+        const WordVec v = reinterpret_cast<const WordVec *>(words)[i];
+        w[4 * i] = v.x; w[4 * i + 1] = v.y; w[4 * i + 2] = v.z; w[4 * i + 3] = v.w;
+    }
+    w[NW] = words[shift ? NW : NW - 1];
+#pragma unroll
+    for (int i = 0; i < NW; ++i) d[i] = __builtin_amdgcn_alignbyte(w[i + 1], w[i], shift);
+}
 
 template <bool WHOLE, int NW>
 __device__ __forceinline__ void load_codes(const uint8_t *__restrict__ row, int64_t K, int64_t k0, uint32_t (&d)[NW])
 {
     const uint8_t *src = row + k0;
-    if (k0 + 4 * NW <= K) {
+    // (eight dwords in a row of a wave's own are not faster that way: 200 x 5001 two-bit codes 3.3 -> 3.5 us)
+    if (!WHOLE && NW > 8 && k0 + 4 * NW <= K && ((K | (int64_t)reinterpret_cast<uintptr_t>(row)) & 3) != 0) {
+        load_bytes<NW>(src, d);
+    } else if (k0 + 4 * NW <= K) {
 #pragma unroll
         for (int i = 0; i < NW / 4; ++i) {
             const AnyVec v = reinterpret_cast<const AnyVec *>(src)[i];
@@ -329,13 +351,20 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const uint8_t *__restric
         if (row < rows) {
             const uint8_t *src = codes + row * K;
             const int64_t vecs = K / 16;
+            auto add = [&](uint32_t w) __attribute__((always_inline)) { sum = __builtin_amdgcn_sad_u8(w & code_mask, 0u, sum); };
+            if (WHOLE || (reinterpret_cast<uintptr_t>(src) & 3u) == 0) {
 #pragma unroll 8
-            for (int64_t i = lane; i < vecs; i += 64) {
-                const AnyVec v = reinterpret_cast<const AnyVec *>(src)[i];
-                sum = __builtin_amdgcn_sad_u8(v.x & code_mask, 0u, sum);
-                sum = __builtin_amdgcn_sad_u8(v.y & code_mask, 0u, sum);
-                sum = __builtin_amdgcn_sad_u8(v.z & code_mask, 0u, sum);
-                sum = __builtin_amdgcn_sad_u8(v.w & code_mask, 0u, sum);
+                for (int64_t i = lane; i < vecs; i += 64) {
+                    const AnyVec v = reinterpret_cast<const AnyVec *>(src)[i];
+                    add(v.x); add(v.y); add(v.z); add(v.w);
+                }
+            } else {
+#pragma unroll 4
+                for (int64_t i = lane; i < vecs; i += 64) {
+                    uint32_t v[4];
+                    load_bytes<4>(src + 16 * i, v);
+                    add(v[0]); add(v[1]); add(v[2]); add(v[3]);
+                }
             }
             if (16 * vecs + lane < K) sum += src[16 * vecs + lane] & (code_mask & 0xffu);  // at most 15 codes
 #pragma unroll
@@ -371,7 +400,9 @@ template <bool WHOLE>
 __device__ __forceinline__ void load_halves(const uint16_t *xrow, int64_t K, int64_t kg, uint32_t (&h)[16])
 {
     const int64_t k0 = kg * 32;
-    if (k0 + 32 <= K) {
+    if (!WHOLE && k0 + 32 <= K && ((2 * K | (int64_t)reinterpret_cast<uintptr_t>(xrow)) & 3) != 0) {
+        load_bytes<16>(xrow + k0, h);
+    } else if (k0 + 32 <= K) {
         const AnyVec *src = reinterpret_cast<const AnyVec *>(xrow + k0);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {

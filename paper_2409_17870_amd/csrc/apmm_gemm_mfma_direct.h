@@ -14,11 +14,9 @@
 // term is an integer and every partial sum stays below 2^24 (checked on the host), hence exact in any order.  Nothing but
 // C reaches global memory (paper Sec. 4.2).
 //
-// Activations of 3 or 4 bits arrive in the field form (apmm_layout.h): their packed words ARE the E2M3 operand.  Weights of 3
-// or 4 bits are unfolded to it in registers with 13 or 8 operations per 32 codes.  Before, as two plane groups in the
-// operands, they took twelve operations and two sweeps of K: 2048 x 11008 x 4096 with both outputs W4A4 110.8 -> 86.5 us,
-// W3A3 104.1 -> 76.3 us.  What bounds the tiles with 6-bit activations is L1 (64 B a clock): 80 B a clock at the full
-// matrix rate for W2A4, 112 B for W4A4.
+// Activations of 3 or 4 bits arrive in the field form (apmm_layout.h): their packed words ARE the E2M3 operand.  Weights of 3 or 4 bits
+// are unfolded to it in registers with 13 or 8 operations per 32 codes.  Outputs of several rounds of tiles, and nearly all with 3- and
+// 4-bit activations, go to apmm_gemm_mfma_lds.h (rule and figures: apmm_gemm_mfma_tiles.h).
 //
 // Data movement: no LDS.  On gfx950 a wave that owns its SIMD alone has about 17 issue cycles per
 // 32-cycle MFMA for everything else; a ds_read_b128 costs ~20 and a ds_write_b128 ~40 of them, a VALU

@@ -49,6 +49,8 @@ bool gemm_mfma_ksplit_supported(const GemmArgs &g) { return gemm_mfma_fp4_suppor
 //   these outputs: 512 x 4096 outputs 5.9 / 7.3 / 9.9 / 16.6 us against 6.7 / 7.5 / 8.6 / 11.6 us here at K = 1024 / 2048 /
 //   4096 / 8192; 512 x 4096 x 11008 22.0 against 13.8 us; 65 x 4096 and 96 x 11008 outputs faster at every K (10.7
 //   against 7.9 us at K = 4096).  Taken from K = 3072 on, and at every K up to 128 tokens.
+//   (Figures of the 128 x 128 tile in this paragraph: its register form; apmm_gemm_mfma_ksplit.h has those of the form that serves K up
+//   to 9216 and 2-bit weights now.)
 //   The 128 x 128 tile (1024 x 4096 outputs and the like, every width; large tiles against this, K = 2048 / 4096 / 8192 /
 //   11008): W4A4 12.1 / 19.1 / 34.6 / 45.3 against 13.2 / 16.8 / 25.7 / 32.3 us, W3A3 11.2 / 16.6 / 29.9 / 41.0 against 12.8 /
 //   16.2 / 24.5 / 30.7, W4A2 9.7 / 15.5 / 27.0 / 34.4 against 11.6 / 14.6 / 21.9 / 26.5: taken from K = 4096 on with weights of 3

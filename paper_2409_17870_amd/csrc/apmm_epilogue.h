@@ -46,6 +46,10 @@ __device__ __forceinline__ uint32_t copy_here(uint32_t v)
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xE4, 0xf, 0xf, true);  // quad_perm [0, 1, 2, 3]
 }
 
+// Before and behind a run of streaming stores: without them the compiler takes the run and the same run of plain stores on the other
+// side of a branch for one, from either end, and drops the hint.
+__device__ __forceinline__ void edge_of_streaming() { asm volatile("; streaming stores"); }
+
 __device__ __forceinline__ void store_output(const GemmArgs &g, int64_t m, int64_t n, int32_t c, float sa,
                                              float sw)
 {

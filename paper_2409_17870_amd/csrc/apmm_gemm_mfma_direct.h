@@ -69,7 +69,7 @@ constexpr int split_store_stages(int wm, int wn, int split)
 template <int P, int Q, int WM, int WN, int SPLIT>
 __global__ __launch_bounds__(256) void gemm_mfma_direct_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32_t *ci_arg,
                                                                uint16_t *cf_arg, int m_arg, int n_arg, int k_arg, int nkb_arg,
-                                                               int tiles_n, int tiles_total, const uint16_t *ws_arg,
+                                                               int tiles_n_plain, int tiles_total, const uint16_t *ws_arg,
                                                                const uint16_t *as_arg)
 {
     GemmArgs g;
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_direct_kernel(const uint32_t *a
     const int wave_m = wave / waves_n(WM), wave_n = wave % waves_n(WM);
     const int r32 = lane & 31, kh = lane >> 5;
     const int lid = xcd_tile_id(blockIdx.x, tiles_total);
-    const int tm = lid / tiles_n, tn = lid % tiles_n;
+    const int tiles_n = tiles_n_plain & ~kPlainStores, tm = lid / tiles_n, tn = lid % tiles_n;
     const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
 
     // per row block: address of (row, slot 0) in this lane's k block of stage 0
@@ -366,12 +366,11 @@ __global__ __launch_bounds__(256) void gemm_mfma_direct_kernel(const uint32_t *a
     // runs (a 16 MiB fp16 output cost 7 us that way).  Rows are taken in pairs: the even lane of a lane pair
     // collects both columns of the first row, the odd lane both columns of the second row (one lane exchange),
     // and each stores one dword.
-    // NT (interior tiles): streaming stores, but not for both outputs of the 256 x 256 tile.  Operands and outputs in rotation, both
-    // outputs, plain against streaming: 1024 x 4096 x 1024 W2A4 (128 x 128) 11.5 / 9.9 us, 1000 x 3000 x 2000 W2A2 14.1 / 12.9, 2048 x 4096 x
-    // 4096 (256 x 128) 22.9 / 22.8, 4096 x 4096 x 4096 (256 x 256) 40.4 / 42.6.
+    // NT (interior tiles): streaming stores (rule: direct_streams).
     auto emit = [&](auto guard_c, auto i32_c, auto f16_c, auto pair_c, auto nt_c) __attribute__((always_inline)) {
         constexpr bool GUARD = decltype(guard_c)::value, I32 = decltype(i32_c)::value, F16 = decltype(f16_c)::value,
                        PAIR = decltype(pair_c)::value, NT = decltype(nt_c)::value;
+        if constexpr (NT) edge_of_streaming();
         int32_t *ci = I32 ? g.c_i32 + m_last * g.N + n_lane : nullptr;
         uint16_t *ch = F16 ? g.c_f16 + m_last * g.N + n_lane : nullptr;
         const bool odd = lane & 1;
@@ -420,13 +419,14 @@ __global__ __launch_bounds__(256) void gemm_mfma_direct_kernel(const uint32_t *a
                 }
             }
         }
+        if constexpr (NT) edge_of_streaming();
     };
     if constexpr (PHASES > 1) {
         emit(F{}, T{}, F{}, F{}, T{});  // interior tiles, int32 output only (checked by the launcher)
     } else {
         const bool interior = (m0 + BM <= g.M) && (n0 + BN <= g.N);
         const bool pair = (g.N & 1) == 0 && (reinterpret_cast<uintptr_t>(g.c_f16) & 3u) == 0;
-        const bool stream = !(WM == 4 && WN == 4) || !(g.c_i32 && g.c_f16);
+        const bool stream = !(tiles_n_plain & kPlainStores);
         // both outputs: one pass per output (a combined pass needs more registers than there are)
         if (g.c_i32) {
             if (interior && stream) emit(F{}, T{}, F{}, F{}, T{});
@@ -451,6 +451,16 @@ inline bool direct_split_usable(const GemmArgs &g)
            nst >= split_store_stages(WM, WN, SPLIT);
 }
 
+// Streaming stores.  One output: always.  Both outputs: of whole lines up to 45 MB (operands and outputs in rotation, plain against
+// streaming: 1024 x 4096 x 1024 W2A4 11.5 / 9.9 us; 25 MB 1.03 - 1.17 of the streaming time over six widths and K = 512 - 3072, 34 MB 0.97 - 1.08,
+// 50 MB 0.89 - 0.97), of parts of lines up to 22 MB (256 x 128 tiles up to 32: 1024 x 4098 x 2000 W2A2 20.4 / 18.7; 128 x 128 tiles at 25 MB 512 x
+// 8010 x 2000 13.1 / 16.4), not for the 256 x 256 tile (4096 x 4096 x 4096 40.4 / 42.6 us).
+inline bool direct_streams(int wm, int wn, const GemmArgs &g)
+{
+    const OutputRows rows(g);
+    return !rows.both || (!(wm == 4 && wn == 4) && (rows.whole ? rows.bytes < 45000000 : rows.fit_l2(wm == 4 ? 32000000 : 22000000)));
+}
+
 template <int P, int Q, int WM, int WN, int SPLIT = 1>
 hipError_t launch_direct_variant(const GemmArgs &g, hipStream_t stream)
 {
@@ -463,10 +473,10 @@ hipError_t launch_direct_variant(const GemmArgs &g, hipStream_t stream)
     if (timing.start || timing.stop)
         hipExtLaunchKernelGGL((gemm_mfma_direct_kernel<P, Q, WM, WN, SPLIT>), dim3((unsigned)tiles), dim3(256), 0,
                               stream, timing.start, timing.stop, 0, g.a, g.w, g.c_i32, g.c_f16, (int)g.M, (int)g.N, (int)g.K,
-                              (int)g.nkb, (int)tiles_n, (int)tiles, g.w_scale, g.a_scale);
+                              (int)g.nkb, tiles_n_arg(tiles_n, direct_streams(WM, WN, g)), (int)tiles, g.w_scale, g.a_scale);
     else
         hipLaunchKernelGGL((gemm_mfma_direct_kernel<P, Q, WM, WN, SPLIT>), dim3((unsigned)tiles), dim3(256), 0,
-                           stream, g.a, g.w, g.c_i32, g.c_f16, (int)g.M, (int)g.N, (int)g.K, (int)g.nkb, (int)tiles_n,
+                           stream, g.a, g.w, g.c_i32, g.c_f16, (int)g.M, (int)g.N, (int)g.K, (int)g.nkb, tiles_n_arg(tiles_n, direct_streams(WM, WN, g)),
                            (int)tiles, g.w_scale, g.a_scale);
     return hipGetLastError();
 }

@@ -86,7 +86,7 @@ constexpr int ksplit_lds_bytes() { return kWM * kWN * 3 * 4 * 64 * 16; }
 template <int FA, int FB, bool KSPLIT>
 __global__ __launch_bounds__(256) void gemm_mfma_i8_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32_t *ci_arg,
                                                            uint16_t *cf_arg, int m_arg, int n_arg, int k_arg, int nkb,
-                                                           int tiles_n, int tiles_m_xn, const uint16_t *ws_arg,
+                                                           int tiles_n_plain, int tiles_m_xn, const uint16_t *ws_arg,
                                                            const uint16_t *as_arg, int p, int q)
 {
     extern __shared__ __align__(16) int4 red[];  // KSPLIT: [block][partial 0..2][register quad 0..3][lane]
@@ -98,7 +98,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_i8_kernel(const uint32_t *a_arg
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r32 = lane & 31, kh = lane >> 5;
     // XCD-aware tile map: the tile grid in 8 / xn x xn parts, one per XCD, walked down their columns
-    const int tiles_m = tiles_m_xn & 0x0fffffff, xn_log = tiles_m_xn >> 28;
+    const int tiles_n = tiles_n_plain & ~mfma::kPlainStores, tiles_m = tiles_m_xn & 0x0fffffff, xn_log = tiles_m_xn >> 28;
     const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
     const int part_m = (tiles_m + (8 >> xn_log) - 1) >> (3 - xn_log), part_n = (tiles_n + (1 << xn_log) - 1) >> xn_log;
     const int tm = (xcd >> xn_log) * part_m + idx % part_m, tn = (xcd & ((1 << xn_log) - 1)) * part_n + idx / part_m;
@@ -225,7 +225,8 @@ __global__ __launch_bounds__(256) void gemm_mfma_i8_kernel(const uint32_t *a_arg
         pw[bj] = (uint32_t)w_sum[n];
         sw_bits[bj] = sw_src[n];
     }
-    // one 32 x 32 block, an inner one with streaming stores
+    // one 32 x 32 block, inner ones with streaming stores by the launcher's rule
+    const bool stream = !(tiles_n_plain & mfma::kPlainStores);
     auto store_block = [&](const v16i &s, int64_t mb, auto bj_c) __attribute__((always_inline)) {
         constexpr int bj = decltype(bj_c)::value;
         const int64_t n = n0 + 32 * bj + r32;
@@ -238,9 +239,14 @@ __global__ __launch_bounds__(256) void gemm_mfma_i8_kernel(const uint32_t *a_arg
         auto row = [&](int v) __attribute__((always_inline)) { return mb + 8 * (v / 4) + 4 * kh + (v % 4); };
         auto sa = [&](int v) __attribute__((always_inline)) { return half_bits_to_float((uint16_t)(as_arg ? sa_bits[v] : 0x3c00u)); };
         if (ci_arg) {
-            if (interior) {
+            if (interior && stream) {
+                edge_of_streaming();
 #pragma unroll
                 for (int v = 0; v < 16; ++v) __builtin_nontemporal_store(c[v], ci_arg + row(v) * N + n);
+                edge_of_streaming();
+            } else if (interior) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) ci_arg[row(v) * N + n] = c[v];
             } else {
 #pragma unroll
                 for (int v = 0; v < 16; ++v)
@@ -250,14 +256,25 @@ __global__ __launch_bounds__(256) void gemm_mfma_i8_kernel(const uint32_t *a_arg
         if (cf_arg && interior && pair_ok) {
             // rows in pairs: the even lane of a lane pair stores both columns of the first row, the odd lane both of the second
             const bool odd = lane & 1;
+            uint32_t word[8];
 #pragma unroll
             for (int v = 0; v < 16; v += 2) {
                 const uint32_t h0 = float_to_half_bits((float)c[v] * sa(v) * sw), h1 = float_to_half_bits((float)c[v + 1] * sa(v + 1) * sw);
                 const uint32_t give = odd ? h0 : h1, keep = odd ? h1 : h0;
                 const uint32_t got = (uint32_t)__builtin_amdgcn_mov_dpp((int)give, 0xB1, 0xf, 0xf, true);
-                const uint32_t word = odd ? (got | (keep << 16)) : (keep | (got << 16));
-                uint32_t *dst = reinterpret_cast<uint32_t *>(cf_arg + (row(v) + (odd ? 1 : 0)) * N + n - (odd ? 1 : 0));
-                __builtin_nontemporal_store(word, dst);
+                word[v / 2] = odd ? (got | (keep << 16)) : (keep | (got << 16));
+            }
+            auto dst = [&](int i) __attribute__((always_inline)) {
+                return reinterpret_cast<uint32_t *>(cf_arg + (row(2 * i) + (odd ? 1 : 0)) * N + n - (odd ? 1 : 0));
+            };
+            if (stream) {
+                edge_of_streaming();
+#pragma unroll
+                for (int i = 0; i < 8; ++i) __builtin_nontemporal_store(word[i], dst(i));
+                edge_of_streaming();
+            } else {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) *dst(i) = word[i];
             }
         } else if (cf_arg) {
 #pragma unroll
@@ -321,6 +338,12 @@ hipError_t launch_variant(const GemmArgs &g, hipStream_t stream)
     const int64_t grid = 8 * part_m * part_n;
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
     const int tiles_m_xn = (int)tiles_m | (xn_log << 28);
+    // Streaming stores where the rows are whole lines (W8A8 2048 x 11008 x 4096 both 156 -> 119 us).  Rows of parts of lines: int32 up to 22 MB
+    // of outputs, whole tiles also before an fp16 output (both outputs of the K split 0.94 - 0.97 of the streaming time at 10 - 18 MB, fp16
+    // alone 0.97 up to 3 MB and 0.85 at 30).
+    const mfma::OutputRows rows(g);
+    const bool streaming = rows.whole || (g.c_i32 && (KSPLIT ? !g.c_f16 : rows.up_to_l2(22000000)));
+    const int columns = mfma::tiles_n_arg(tiles_n, streaming);
     auto kernel = gemm_mfma_i8_kernel<FA, FB, KSPLIT>;
     if constexpr (KSPLIT) {
         static thread_local int prepared_device = -1;  // the LDS limit is a per-device attribute of the function
@@ -338,10 +361,10 @@ hipError_t launch_variant(const GemmArgs &g, hipStream_t stream)
     const dim3 blocks((unsigned)grid), threads(256);
     if (timing.start || timing.stop)
         hipExtLaunchKernelGGL(kernel, blocks, threads, lds, stream, timing.start, timing.stop, 0, g.a, g.w, g.c_i32, g.c_f16, (int)g.M,
-                              (int)g.N, (int)g.K, (int)g.nkb, (int)tiles_n, tiles_m_xn, g.w_scale, g.a_scale, g.p, g.q);
+                              (int)g.N, (int)g.K, (int)g.nkb, columns, tiles_m_xn, g.w_scale, g.a_scale, g.p, g.q);
     else
         hipLaunchKernelGGL(kernel, blocks, threads, lds, stream, g.a, g.w, g.c_i32, g.c_f16, (int)g.M, (int)g.N, (int)g.K, (int)g.nkb,
-                           (int)tiles_n, tiles_m_xn, g.w_scale, g.a_scale, g.p, g.q);
+                           columns, tiles_m_xn, g.w_scale, g.a_scale, g.p, g.q);
     return hipGetLastError();
 }
 

@@ -34,9 +34,20 @@ constexpr bool ksplit_half(int wm, int wn) { return wm * wn > 12; }
 constexpr int ksplit_rounds(int wm, int wn) { return ksplit_half(wm, wn) ? 2 : 1; }
 constexpr int ksplit_lds_bytes(int wm, int wn) { return wm * wn / ksplit_rounds(wm, wn) * (ksplit_half(wm, wn) ? 4 : 3) * 4 * 64 * 16; }
 
+// Streaming stores, also when both outputs are written (512 x 5120 x 5120 W2A4 16.7 -> 13.3 us, 512 x 4096 x 4096 W2A2 10.7 -> 9.1, 203 x 4096 x
+// 4096 7.2 -> 6.8).  Plain ones for both outputs with rows of parts of lines, up to 8 MB (128 x 4098 x 512 W2A2 4.9 against 5.1 us) and in the
+// 128 x 128 tile in registers (2048 x 1500 x 11008 W4A2 24.0 / 27.9).  Not in the tiles of 160 and 192 columns, whose outputs are larger than
+// that: one more form of the store of every block makes 67 KB of code 80 (512 x 5120 x 11008 W4A4 both 4 - 6 % slower).
+constexpr bool ksplit_always_streams(int wm, int wn) { return wm * wn > 8 && !ksplit_half(wm, wn); }
+inline bool ksplit_streams(int wm, int wn, const GemmArgs &g)
+{
+    const OutputRows rows(g);
+    return ksplit_always_streams(wm, wn) || !rows.both || rows.whole || (!ksplit_half(wm, wn) && rows.fit_l2());
+}
+
 template <int P, int Q, int WM, int WN>
 __device__ __forceinline__ void ksplit_tile(float4 *red, const uint32_t *a_arg, const uint32_t *w_arg, int32_t *ci_arg, uint16_t *cf_arg, int m_arg, int n_arg,
-                                            int k_arg, int nkb_arg, int tiles_n, int tiles_m_xn, const uint16_t *ws_arg, const uint16_t *as_arg)
+                                            int k_arg, int nkb_arg, int tiles_n_plain, int tiles_m_xn, const uint16_t *ws_arg, const uint16_t *as_arg)
 {
     // red: [block][partial 0..2][register quad 0..3][lane]
     static_assert(P >= 1 && P <= 4 && Q >= 1 && Q <= 4, "instantiated for codes of up to four bits");
@@ -71,7 +82,7 @@ __device__ __forceinline__ void ksplit_tile(float4 *red, const uint32_t *a_arg, 
     // Workgroups are dealt round-robin to the 8 XCDs, each with an L2 of its own.  The tile grid is cut into
     // 8 / xn x xn parts, one per XCD, and a part is walked down its columns: the workgroups that run together on an
     // XCD share the packed rows of a few column tiles and of the part's row tiles (tiles_m_xn = tiles_m | log2(xn) << 28).
-    const int tiles_m = tiles_m_xn & 0x0fffffff, xn_log = tiles_m_xn >> 28;
+    const int tiles_n = tiles_n_plain & ~kPlainStores, tiles_m = tiles_m_xn & 0x0fffffff, xn_log = tiles_m_xn >> 28;
     const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
     const int part_m = (tiles_m + (8 >> xn_log) - 1) >> (3 - xn_log), part_n = (tiles_n + (1 << xn_log) - 1) >> xn_log;
     const int tm = (xcd >> xn_log) * part_m + idx % part_m, tn = (xcd & ((1 << xn_log) - 1)) * part_n + idx / part_m;
@@ -260,10 +271,10 @@ __device__ __forceinline__ void ksplit_tile(float4 *red, const uint32_t *a_arg, 
     // Store of one owned block.  GUARD: border tile, every element tested.  PAIR (interior, even N, 4-byte aligned
     // fp16 output): neighbouring lanes hold neighbouring columns; rows are taken in pairs, the even lane of a lane
     // pair collects both columns of the first row, the odd lane both columns of the second (one lane exchange),
-    // and each stores one dword instead of two halves.  NT: streaming stores of inner tiles, also
-    // when both outputs are written (512 x 5120 x 5120 W2A4 16.7 -> 13.3 us, 512 x 4096 x 4096 W2A2 10.7 -> 9.1, 203 x 4096 x 4096 7.2 -> 6.8).
+    // and each stores one dword instead of two halves.  NT: streaming stores of inner tiles (rule: ksplit_streams).
     const bool interior = (m0 + 32 * WM <= M) && (n0 + 32 * WN <= N);
     const bool pair_ok = (N & 1) == 0 && (reinterpret_cast<uintptr_t>(cf_arg) & 3u) == 0;
+    const bool stream = ksplit_always_streams(WM, WN) || !(tiles_n_plain & kPlainStores);
     const bool odd = lane_out & 1;
     float sa_f[16];
 #pragma unroll
@@ -273,6 +284,7 @@ __device__ __forceinline__ void ksplit_tile(float4 *red, const uint32_t *a_arg, 
         auto emit = [&](auto guard_c, auto i32_c, auto f16_c, auto pair_c, auto nt_c) __attribute__((always_inline)) {
             constexpr bool GUARD = decltype(guard_c)::value, I32 = decltype(i32_c)::value, F16 = decltype(f16_c)::value,
                            PAIR = decltype(pair_c)::value, NT = decltype(nt_c)::value;
+            if constexpr (NT) edge_of_streaming();
             const float sw = half_bits_to_float((uint16_t)use_here(sw_h));
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
@@ -298,13 +310,16 @@ __device__ __forceinline__ void ksplit_tile(float4 *red, const uint32_t *a_arg, 
                     }
                 }
             }
+            if constexpr (NT) edge_of_streaming();
         };
         if (ci_arg) {
-            if (interior) emit(F{}, T{}, F{}, F{}, T{});
+            if (interior && stream) emit(F{}, T{}, F{}, F{}, T{});
+            else if (interior) emit(F{}, T{}, F{}, F{}, F{});
             else emit(T{}, T{}, F{}, F{}, F{});
         }
         if (cf_arg) {
-            if (interior && pair_ok) emit(F{}, F{}, T{}, T{}, T{});
+            if (interior && pair_ok && stream) emit(F{}, F{}, T{}, T{}, T{});
+            else if (interior && pair_ok) emit(F{}, F{}, T{}, T{}, F{});
             else if (interior) emit(F{}, F{}, T{}, F{}, F{});
             else emit(T{}, F{}, T{}, F{}, F{});
         }
@@ -407,7 +422,7 @@ hipError_t launch_ksplit_variant(const GemmArgs &g, hipStream_t stream)
     constexpr int BM = 32 * WM, BN = 32 * WN;
     const int64_t tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
     if (tiles_m >= (1 << 28) || tiles_n >= (1 << 28) || g.K > 0x7fffffffLL) return hipErrorInvalidValue;
-    auto launch = [&](auto kernel, int64_t tiles, int threads, int lds, int order, int &prepared_device) {
+    auto launch = [&](auto kernel, int64_t tiles, int threads, int lds, int order, bool streaming, int &prepared_device) {
         if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
         int dev = 0;
         hipError_t e = hipGetDevice(&dev);
@@ -420,10 +435,10 @@ hipError_t launch_ksplit_variant(const GemmArgs &g, hipStream_t stream)
         const KernelTiming timing = take_kernel_timing();
         if (timing.start || timing.stop)
             hipExtLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(threads), lds, stream, timing.start, timing.stop, 0, g.a, g.w,
-                                  g.c_i32, g.c_f16, (int)g.M, (int)g.N, (int)g.K, (int)g.nkb, (int)tiles_n, order, g.w_scale, g.a_scale);
+                                  g.c_i32, g.c_f16, (int)g.M, (int)g.N, (int)g.K, (int)g.nkb, tiles_n_arg(tiles_n, streaming), order, g.w_scale, g.a_scale);
         else
             hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(threads), lds, stream, g.a, g.w, g.c_i32, g.c_f16, (int)g.M, (int)g.N,
-                               (int)g.K, (int)g.nkb, (int)tiles_n, order, g.w_scale, g.a_scale);
+                               (int)g.K, (int)g.nkb, tiles_n_arg(tiles_n, streaming), order, g.w_scale, g.a_scale);
         return hipGetLastError();
     };
     static thread_local int prepared = -1, prepared_long = -1;
@@ -432,7 +447,8 @@ hipError_t launch_ksplit_variant(const GemmArgs &g, hipStream_t stream)
         static_assert(lds <= 160 * 1024, "LDS of a compute unit");
         if (Q == 2 || g.K <= kKsplitLdsMaxK) {
             note_kernel("gemm_mfma_ksplit_kernel<%d,%d,%d,%d>", P, Q, WM, WN);
-            return launch(gemm_mfma_ksplit_kernel<P, Q, WM, WN>, tiles_m * tiles_n, 512, lds, lds_tile_order<P, Q>(tiles_m, g.K), prepared);
+            return launch(gemm_mfma_ksplit_kernel<P, Q, WM, WN>, tiles_m * tiles_n, 512, lds, lds_tile_order<P, Q>(tiles_m, g.K),
+                          lds_streams<P, Q, 2, WN / 2, 2>(g), prepared);
         }
     }
     // Parts of the tile grid per XCD: 8 / xn along M times xn along N, the cut that leaves an XCD the fewest packed
@@ -448,10 +464,10 @@ hipError_t launch_ksplit_variant(const GemmArgs &g, hipStream_t stream)
     const int order = (int)tiles_m | (xn_log << 28);
     if constexpr (WM != 4) {
         note_kernel("gemm_mfma_ksplit_kernel<%d,%d,%d,%d>", P, Q, WM, WN);
-        return launch(gemm_mfma_ksplit_kernel<P, Q, WM, WN>, 8 * part_m * part_n, 256, ksplit_lds_bytes(WM, WN), order, prepared);
+        return launch(gemm_mfma_ksplit_kernel<P, Q, WM, WN>, 8 * part_m * part_n, 256, ksplit_lds_bytes(WM, WN), order, ksplit_streams(WM, WN, g), prepared);
     } else if constexpr (Q > 2) {
         note_kernel("gemm_mfma_ksplit_long_kernel<%d,%d>", P, Q);
-        return launch(gemm_mfma_ksplit_long_kernel<P, Q>, 8 * part_m * part_n, 256, ksplit_lds_bytes(WM, WN), order, prepared_long);
+        return launch(gemm_mfma_ksplit_long_kernel<P, Q>, 8 * part_m * part_n, 256, ksplit_lds_bytes(WM, WN), order, ksplit_streams(WM, WN, g), prepared_long);
     }
     return hipErrorInvalidValue;  // (not reached)
 }

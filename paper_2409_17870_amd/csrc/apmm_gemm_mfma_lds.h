@@ -70,7 +70,7 @@ constexpr int lds_tile_bytes() { return KG == 1 ? LdsTile<P, Q, WM, WN>::BYTES :
 
 template <int P, int Q, int WM, int WN, int KG>
 __device__ __forceinline__ void lds_tile(uint4 *ring_of_workgroup, const uint32_t *a_arg, const uint32_t *w_arg, int32_t *ci_arg, uint16_t *cf_arg, int m_arg,
-                                         int n_arg, int k_arg, int nkb_arg, int tiles_n, int tiles_m_band, const uint16_t *ws_arg,
+                                         int n_arg, int k_arg, int nkb_arg, int tiles_n_plain, int tiles_m_band, const uint16_t *ws_arg,
                                          const uint16_t *as_arg)
 {
     using L = LdsTile<P, Q, WM, WN>;
@@ -89,7 +89,7 @@ __device__ __forceinline__ void lds_tile(uint4 *ring_of_workgroup, const uint32_
     const int wave_m = wave >> 1, wave_n = wave & 1;
     const int r32 = lane & 31, kh = lane >> 5;
     // An XCD takes a contiguous run of tiles in an order that walks `band` tile rows column by column (see lds_tile_order).
-    const int tiles_m = tiles_m_band & 0x0fffffff, band = 1 << (tiles_m_band >> 28);
+    const int tiles_n = tiles_n_plain & ~kPlainStores, tiles_m = tiles_m_band & 0x0fffffff, band = 1 << (tiles_m_band >> 28);
     const int lid = xcd_tile_id(blockIdx.x, tiles_n * tiles_m);
     const int m_band = lid / (band * tiles_n), in_band = lid - m_band * band * tiles_n;
     const int rows = min(tiles_m - m_band * band, band);
@@ -356,13 +356,13 @@ __device__ __forceinline__ void lds_tile(uint4 *ring_of_workgroup, const uint32_
 #pragma unroll
         for (int bj = 0; bj < WN; ++bj) c[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x2f32(a_fin[bi], b_fin[bj], c[bi][bj], 0, 0, 0);
 
-    // Store, as in apmm_gemm_mfma_direct.h: one pass per output, fp16 in pairs of columns where the addresses allow it.  Inner tiles
-    // with streaming stores whatever is written: with outputs that are not in the last-level cache from the call before, plain ones
-    // push the operands out of L2 (W2A4 1024 x 11008 x 4096 both 33.6 -> 43.4 us, int32 28.8 -> 37.0, fp16 28.0 -> 35.7).  Single
-    // fp16 elements (odd widths) behind an int32 output are the exception: 1500 x 5003 x 3001 W2A4 28.8 against 23.3 us.
+    // Store, as in apmm_gemm_mfma_direct.h: one pass per output, fp16 in pairs of columns where the addresses allow it, streaming stores by
+    // the rule of lds_streams (but single fp16 elements behind an int32 output, odd widths: plain, 1500 x 5003 x 3001 W2A4 28.8 against
+    // 23.3 us).
     auto emit = [&](auto guard_c, auto i32_c, auto f16_c, auto pair_c, auto nt_c) __attribute__((always_inline)) {
         constexpr bool GUARD = decltype(guard_c)::value, I32 = decltype(i32_c)::value, F16 = decltype(f16_c)::value,
                        PAIR = decltype(pair_c)::value, NT = decltype(nt_c)::value;
+        if constexpr (NT) edge_of_streaming();
         int32_t *ci = I32 ? ci_arg + m_lane * N + n_lane : nullptr;
         uint16_t *ch = F16 ? cf_arg + m_lane * N + n_lane : nullptr;
         const bool odd = lane & 1;
@@ -405,18 +405,22 @@ __device__ __forceinline__ void lds_tile(uint4 *ring_of_workgroup, const uint32_
                 }
             }
         }
+        if constexpr (NT) edge_of_streaming();
     };
     using T = std::true_type;
     using F = std::false_type;
     const bool interior = (m0 + BM <= M) && (n0 + BN <= N);
     const bool pair = (N & 1) == 0 && (reinterpret_cast<uintptr_t>(cf_arg) & 3u) == 0;
+    const bool stream = !(tiles_n_plain & kPlainStores);
     if (ci_arg) {
-        if (interior) emit(F{}, T{}, F{}, F{}, T{});
+        if (interior && stream) emit(F{}, T{}, F{}, F{}, T{});
+        else if (interior) emit(F{}, T{}, F{}, F{}, F{});
         else emit(T{}, T{}, F{}, F{}, F{});
     }
     if (cf_arg) {
-        if (interior && pair) emit(F{}, F{}, T{}, T{}, T{});
-        else if (interior && !ci_arg) emit(F{}, F{}, T{}, F{}, T{});
+        if (interior && pair && stream) emit(F{}, F{}, T{}, T{}, T{});
+        else if (interior && pair) emit(F{}, F{}, T{}, T{}, F{});
+        else if (interior && stream && !ci_arg) emit(F{}, F{}, T{}, F{}, T{});
         else if (interior) emit(F{}, F{}, T{}, F{}, F{});
         else emit(T{}, F{}, T{}, F{}, F{});
     }
@@ -443,6 +447,24 @@ inline int lds_tile_order(int64_t tiles_m, int64_t K)  // tiles_m < 2^28
     return (int)tiles_m | band_log << 28;
 }
 
+// Streaming stores where the rows are whole lines: with outputs that are not in the last-level cache from the call before, plain ones
+// push the operands out of L2 (W2A4 1024 x 11008 x 4096 both 33.6 -> 43.4 us, int32 28.8 -> 37.0, fp16 28.0 -> 35.7).  Not where a short sum
+// leaves both outputs to be all there is to do, K up to 512 or up to 2.4e10 products, from 45 MB on (128 x 128 with fields: up to 80 MB): plain
+// over streaming at 60 - 80 MB 0.84 / 0.86 / 0.91 / 0.98 with K = 512 / 1024 / 2048 / 3072 (1- and 2-bit activations; 3 and 4 bits 0.91 - 0.96), at 80 -
+// 120 MB 0.89 / 0.96 / 1.03 / 1.06 (0.97 / 1.06 / 1.08 / 1.09), at 200 MB 0.86 / 0.99 / 1.20 (1.08 / 1.24 / 1.34).  Rows of parts of lines: also where the
+// operands of a tile row and column, K slots wide, fill an L2 and lose more to plain stores (W4A4 1024 x 11016 with K = 4096 / 6144 / 8192 /
+// 11008 both plain over streaming 1.02 / 1.17 / 1.18 / 1.13, W2A4 0.85 / 0.95 / 1.10 / 1.20).
+template <int P, int Q, int WM, int WN, int KG>
+inline bool lds_streams(const GemmArgs &g)
+{
+    const OutputRows rows(g);
+    if (KG == 2 && !rows.both) return true;
+    if (!rows.whole) return rows.fit_l2() || g.K * (activation_slots(P) + Q) >= 60000;
+    const bool few = g.M * g.N * g.K <= 24000000000;
+    const bool short_sum = activation_field_form(P) && WN == 2 ? few && rows.bytes < 80000000 : few || g.K <= 512;
+    return !rows.both || rows.bytes < 45000000 || !short_sum;
+}
+
 template <int P, int Q, int WM, int WN, int OCC>
 hipError_t launch_lds_variant(const GemmArgs &g, hipStream_t stream)
 {
@@ -452,6 +474,7 @@ hipError_t launch_lds_variant(const GemmArgs &g, hipStream_t stream)
     const int64_t tiles = tiles_m * tiles_n;
     if (tiles > 0x7fffffffLL || tiles_m >= (1 << 28) || g.M > 0x7fffffffLL || g.N > 0x7fffffffLL || g.K > 0x7fffffffLL) return hipErrorInvalidValue;
     const int tiles_m_band = lds_tile_order<P, Q>(tiles_m, g.K);
+    const int columns = tiles_n_arg(tiles_n, lds_streams<P, Q, WM, WN, 1>(g));
     auto kernel = gemm_mfma_lds_kernel<P, Q, WM, WN, OCC>;
     static thread_local int prepared_device = -1;  // the LDS limit is a per-device attribute of the function
     int dev = 0;
@@ -466,10 +489,10 @@ hipError_t launch_lds_variant(const GemmArgs &g, hipStream_t stream)
     note_kernel("gemm_mfma_lds_kernel<%d,%d,%d,%d>", P, Q, WM, WN);
     if (timing.start || timing.stop)
         hipExtLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(256), L::BYTES, stream, timing.start, timing.stop, 0, g.a, g.w, g.c_i32,
-                              g.c_f16, (int)g.M, (int)g.N, (int)g.K, (int)g.nkb, (int)tiles_n, tiles_m_band, g.w_scale, g.a_scale);
+                              g.c_f16, (int)g.M, (int)g.N, (int)g.K, (int)g.nkb, columns, tiles_m_band, g.w_scale, g.a_scale);
     else
         hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(256), L::BYTES, stream, g.a, g.w, g.c_i32, g.c_f16, (int)g.M, (int)g.N,
-                           (int)g.K, (int)g.nkb, (int)tiles_n, tiles_m_band, g.w_scale, g.a_scale);
+                           (int)g.K, (int)g.nkb, columns, tiles_m_band, g.w_scale, g.a_scale);
     return hipGetLastError();
 }
 

@@ -123,5 +123,27 @@ __device__ __forceinline__ int xcd_tile_id(int block, int tiles_total)
     return block;
 }
 
+// ---- Streaming stores of inner tiles: the launcher's choice, passed in tiles_n ----
+// A streaming store leaves the operands in L2 alone and is written back early, but a line that it fills only in part is written in
+// parts: rows that do not begin at a line (N no multiple of 32, or an output that begins elsewhere) share their lines with the wave
+// tile next to them.  Plain stores meet in L2.  Both outputs, all streaming against all plain, operands and outputs in rotation:
+// 1500 x 11010 x 512 W2A2 57 against 30 us, 2048 x 4098 x 512 26 / 16, 1536 x 5002 x 512 24 / 18; W8A8 1500 x 5002 x 512 1.7 times.
+// The outputs of a call that fit the L2 of all XCDs (32 MB) well, but are not small, are the exception: 3 - 10 % faster streaming at 8 to
+// 22 MB (an int32 output of half lines up to 30), as much slower below (203 x 4098 x 512 both 6 %).
+struct OutputRows {
+    int64_t bytes;  // of all outputs of the call
+    bool both, whole, half_lines;  // whole: every row begins and ends at a line (fp16: at half of one, the run of a wave's row); half_lines: int32 alone
+    explicit OutputRows(const GemmArgs &g)
+        : bytes(g.M * g.N * ((g.c_i32 ? 4 : 0) + (g.c_f16 ? 2 : 0))), both(g.c_i32 && g.c_f16),
+          whole((g.N & 31) == 0 && (reinterpret_cast<uintptr_t>(g.c_i32) & 127) == 0 && (reinterpret_cast<uintptr_t>(g.c_f16) & 63) == 0),
+          half_lines((g.N & 15) == 0 && !g.c_f16)
+    {
+    }
+    bool up_to_l2(int64_t most) const { return bytes < (half_lines ? 30000000 : most); }
+    bool fit_l2(int64_t most = 22000000) const { return bytes >= 8000000 && up_to_l2(most); }
+};
+constexpr int kPlainStores = 1 << 30;
+inline int tiles_n_arg(int64_t tiles_n, bool streaming) { return (int)tiles_n | (streaming ? 0 : kPlainStores); }
+
 }  // namespace mfma
 }  // namespace apmm

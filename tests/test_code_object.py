@@ -1,8 +1,11 @@
 """What the compiler made of the kernels, read from the code objects inside the library (its own build): registers that did not
 suffice show up as spills, which cost a kernel of a few microseconds more than a wrong tile."""
+import collections
 import os
 import re
+import shutil
 import struct
+import subprocess
 
 import pytest
 
@@ -28,13 +31,13 @@ def _notes(elf):
 
 
 @pytest.fixture(scope="module")
-def kernels():
+def code_objects():
     from paper_2409_17870_amd import binding
     if not os.path.exists(binding.LIB_PATH):
         import __graft_entry__
         __graft_entry__.build()
     data = open(binding.LIB_PATH, "rb").read()
-    found = {}
+    found = []
     pos = data.find(BUNDLE)
     while pos >= 0:
         count, = struct.unpack_from("<Q", data, pos + 24)
@@ -44,10 +47,39 @@ def kernels():
             triple = data[at + 24:at + 24 + length]
             at += 24 + length
             if b"amdgcn" in triple and size:
-                for meta in _notes(data[pos + offset:pos + offset + size]):
-                    found.update((k[".name"], k) for k in meta["amdhsa.kernels"])
+                found.append(data[pos + offset:pos + offset + size])
         pos = data.find(BUNDLE, pos + 24)
+    return found
+
+
+@pytest.fixture(scope="module")
+def kernels(code_objects):
+    found = {k[".name"]: k for elf in code_objects for meta in _notes(elf) for k in meta["amdhsa.kernels"]}
     assert found
+    return found
+
+
+@pytest.fixture(scope="module")
+def dword_stores(code_objects, tmp_path_factory):
+    """{mangled kernel name: Counter(plain=, nt=)} of the dword stores of the tiled kernels"""
+    objdump = shutil.which("llvm-objdump", path="/opt/rocm/llvm/bin" + os.pathsep + os.environ.get("PATH", ""))
+    if objdump is None:
+        pytest.skip("no llvm-objdump")
+    path = str(tmp_path_factory.mktemp("co") / "kernels.co")
+    found = {}
+    for elf in code_objects:
+        if b"gemm_mfma_" not in elf:
+            continue
+        with open(path, "wb") as f:
+            f.write(elf)
+        text = subprocess.run([objdump, "-d", "--no-show-raw-insn", path], capture_output=True, text=True, check=True).stdout
+        count = None
+        for line in text.splitlines():
+            m = re.match(r"[0-9a-f]+ <(.*)>:$", line)
+            if m:
+                count = found[m.group(1)] = collections.Counter()
+            elif count is not None and "global_store_dword " in line:
+                count["nt" if line.split("//")[0].rstrip().endswith(" nt") else "plain"] += 1
     return found
 
 
@@ -83,3 +115,18 @@ def test_only_tiles_that_a_launch_rule_names_are_built(kernels):
             assert wn == 4 and q >= 2
         else:
             assert wm == 2 and wn in ((2, 4) if p <= 2 else (2, 4, 5, 6) if q <= 2 else (2, 4, 5))
+
+
+@pytest.mark.parametrize("name", ["gemm_mfma_i8_kernel", "gemm_mfma_lds_kernel", "gemm_mfma_direct_kernel", "gemm_mfma_ksplit_kernel",
+                                  "gemm_mfma_ksplit_long_kernel"])
+def test_inner_tiles_have_streaming_and_plain_stores(dword_stores, name):
+    """A block of 32 x 32 takes 16 dword stores a lane of int32 and 8 of fp16 in pairs.  Every inner tile has both in a streaming and in a
+    plain form (rows that are no whole lines), the border has int32 in plain stores: 24 streaming to 40 plain.  Two forms that
+    differ in the hint alone are one to the compiler unless it is kept from joining them."""
+    for args, count in _of(dword_stores, name).items():
+        if name == "gemm_mfma_direct_kernel" and args[4] > 1:
+            continue                                     # two phases: int32 in whole tiles alone
+        if name == "gemm_mfma_ksplit_kernel" and args[2:] in ((2, 5), (2, 6)):
+            assert count["nt"] * 2 == count["plain"] * 3  # outputs of a size that always streams: the border alone is plain
+            continue
+        assert count["nt"] > 0 and count["nt"] * 5 == count["plain"] * 3, (args, count)

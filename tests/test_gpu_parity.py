@@ -1125,6 +1125,47 @@ def test_operands_shared_through_lds(gpu, p, q, outs):
             assert bool(((c16.double() - f).abs() <= 1e-3 * f.abs() + 1e-6).all())
 
 
+# (kernel, p, q, M, N, K): inner tiles of each kernel with streaming and with plain stores; N in whole, half and parts of lines, odd
+STORE_FORMS = [("direct_kernel<2,2,2,2,1>", 2, 2, 390, N, 512) for N in (4224, 4098, 4112, 4101)] + [
+    ("direct_kernel<2,2,4,2,1>", 2, 2, 1030, N, 512) for N in (4128, 4098, 6024)] + [
+    ("direct_kernel<4,2,1,4,1>", 4, 2, 520, N, 512) for N in (4128, 4098)] + [
+    ("ksplit_kernel<2,2,2,2>", 2, 2, 130, N, 600) for N in (4096, 4098, 4099)] + [
+    ("ksplit_kernel<4,4,2,5>", 4, 4, 450, 5002, 5200), ("ksplit_kernel<2,1,2,4>", 2, 1, 500, 3010, 3100)] + [
+    ("ksplit_kernel<3,3,4,4>", 3, 3, 1000, N, 4200) for N in (4096, 2946, 3970)] + [
+    ("ksplit_long_kernel<2,4>", 2, 4, 1000, N, 9300) for N in (4096, 4090, 4091)] + [
+    ("lds_kernel<2,2,2,2>", 2, 2, 1300, N, 512) for N in (11040, 11016, 8336, 11011)] + [
+    ("lds_kernel<4,4,2,2>", 4, 4, 1030, N, K) for N, K in ((4128, 512), (4130, 6000), (4130, 5900))] + [
+    ("lds_kernel<4,2,2,4>", 4, 2, 1100, 11010, 600)] + [
+    ("i8_kernel<8,8,ksplit>", 8, 8, 300, N, 1100) for N in (2080, 2082, 2083)] + [
+    ("i8_kernel<8,8,tiles>", 8, 8, 700, N, 300) for N in (8032, 8034, 8035, 8016)]
+
+
+@pytest.mark.parametrize("case", STORE_FORMS, ids=lambda c: "%s-%dx%dx%d" % (c[0], *c[3:]))
+def test_streaming_and_plain_stores(gpu, case):
+    """Every output in each form of the store: both outputs, either alone, and both at addresses inside a line."""
+    torch, binding = gpu
+    name, p, q, M, N, K = case
+    dev = torch.device("cuda:0")
+    g = torch.Generator(device=dev).manual_seed(8800 + N + K)
+    a = torch.randint(0, 1 << p, (M, K), generator=g, device=dev, dtype=torch.uint8)
+    w = torch.randint(0, 1 << q, (N, K), generator=g, device=dev, dtype=torch.uint8)
+    sa = (0.01 + 0.09 * torch.rand(M, generator=g, device=dev)).half()
+    sw = (0.01 + 0.09 * torch.rand(N, generator=g, device=dev)).half()
+    ap, wp = binding.apmm_pack_activations(a, p), binding.apmm_pack_weights(w, q)
+    want = ((2.0 * a.float() - ((1 << p) - 1)).double() @ (2.0 * w.float() - ((1 << q) - 1)).double().t().contiguous()).to(torch.int64)
+    f = want.double() * sa.double()[:, None] * sw.double()[None, :]
+    for i32, f16, shift in ((True, True, 0), (True, False, 0), (False, True, 0), (True, True, 1)):
+        c32 = torch.full((M * N + 32,), -1, dtype=torch.int32, device=dev)[shift:shift + M * N].view(M, N) if i32 else None
+        c16 = torch.full((M * N + 32,), -1, dtype=torch.float16, device=dev)[2 * shift:2 * shift + M * N].view(M, N) if f16 else None
+        binding.apmm_gemm(M, N, K, p, q, ap, wp, want_i32=i32, want_f16=f16, w_scale=sw, a_scale=sa, c_i32=c32, c_f16=c16)
+        if i32 and f16:
+            assert binding.apmm_last_gemm_kernel() == "gemm_mfma_" + name
+        if i32:
+            assert torch.equal(c32.to(torch.int64), want)
+        if f16:
+            assert bool(((c16.double() - f).abs() <= 1e-3 * f.abs() + 1e-6).all())
+
+
 def test_k_split_kernel_declines_wide_codes(gpu):
     torch, binding = gpu
     a = torch.zeros((64, 512), dtype=torch.uint8, device="cuda:0")

@@ -391,13 +391,21 @@ __device__ __forceinline__ void ksplit_tile(float4 *red, const uint32_t *a_arg, 
     });
 }
 
-// The 128 x 128 tile (4 x 4 blocks) in two forms.  Up to K = 9216, and with 2-bit weights at every K: two groups of four waves, each with half
+// The 128 x 128 tile (4 x 4 blocks) in two forms.  Up to K = 9216 (ksplit_lds_max_k), and with 2-bit weights at every K: two groups of four waves, each with half
 // of K, that share their operands through LDS (apmm_gemm_mfma_lds.h).  It starts and ends faster and, with twice the waves, waits
 // less, but a product needs 1.25 KB of LDS reads (W4A4) where the four waves with 256 accumulators read their words from L1 once for
 // sixteen.  Microseconds, LDS / registers: K = 4096, 1024 x 4096 outputs W4A4 14.3 / 16.9, W3A3 14.3 / 16.7, W4A2 12.9 / 15.2; K = 8192 25.2 / 25.8,
 // 23.7 / 25.1, 21.2 / 22.0; K = 11008 33.5 / 32.6, 30.8 / 30.9, 27.6 / 27.1; with 2 bits at K = 11008 W2A4 27.9 / 30.0, W2A2 22.0 / 22.6, W2A1
 // 20.5 / 21.8.
-constexpr int64_t kKsplitLdsMaxK = 9216;
+// With 1- and 2-bit activations the registers catch up earlier, operands and outputs in rotation over seven outputs, LDS / registers: W3A2 fp16 0.97 -
+// 1.03 at K = 8704 and 1.00 - 1.05 at 9216, int32 alone 0.99 - 1.03 at 6144, 1.02 - 1.05 at 7168, 1.03 - 1.09 beyond; W4A2 int32 0.96 - 1.03 at 7168, 0.97 - 1.05
+// beyond; W3A1 int32 0.99 - 1.02 at 8192, 1.02 - 1.05 at 9216; W4A1 0.86 - 0.99 throughout.
+inline int64_t ksplit_lds_max_k(int p, int q, const GemmArgs &g)
+{
+    const bool i32_alone = !g.c_f16;
+    if (p == 2) return !i32_alone ? 8704 : q == 3 ? 5632 : 7168;
+    return p == 1 && q == 3 && i32_alone ? 8192 : 9216;
+}
 template <int P, int Q, int WM, int WN>
 __global__ __launch_bounds__(WM == 4 ? 512 : 256, WN == 2 ? 2 : 1)  // two workgroups of the 64 x 64 tile share a compute unit
 void gemm_mfma_ksplit_kernel(const uint32_t *a, const uint32_t *w, int32_t *c_i32, uint16_t *c_f16, int m, int n, int k, int nkb, int tiles_n, int tiles_m_xn,
@@ -445,7 +453,7 @@ hipError_t launch_ksplit_variant(const GemmArgs &g, hipStream_t stream)
     if constexpr (WM == 4) {
         constexpr int lds = lds_tile_bytes<P, Q, 2, WN / 2, 2>();
         static_assert(lds <= 160 * 1024, "LDS of a compute unit");
-        if (Q == 2 || g.K <= kKsplitLdsMaxK) {
+        if (Q == 2 || g.K <= ksplit_lds_max_k(P, Q, g)) {
             note_kernel("gemm_mfma_ksplit_kernel<%d,%d,%d,%d>", P, Q, WM, WN);
             return launch(gemm_mfma_ksplit_kernel<P, Q, WM, WN>, tiles_m * tiles_n, 512, lds, lds_tile_order<P, Q>(tiles_m, g.K),
                           lds_streams<P, Q, 2, WN / 2, 2>(g), prepared);

@@ -451,7 +451,8 @@ inline int lds_tile_order(int64_t tiles_m, int64_t K)  // tiles_m < 2^28
 // push the operands out of L2 (W2A4 1024 x 11008 x 4096 both 33.6 -> 43.4 us, int32 28.8 -> 37.0, fp16 28.0 -> 35.7).  Not where a short sum
 // leaves both outputs to be all there is to do, K up to 512 or up to 2.4e10 products, from 45 MB on (128 x 128 with fields: up to 80 MB): plain
 // over streaming at 60 - 80 MB 0.84 / 0.86 / 0.91 / 0.98 with K = 512 / 1024 / 2048 / 3072 (1- and 2-bit activations; 3 and 4 bits 0.91 - 0.96), at 80 -
-// 120 MB 0.89 / 0.96 / 1.03 / 1.06 (0.97 / 1.06 / 1.08 / 1.09), at 200 MB 0.86 / 0.99 / 1.20 (1.08 / 1.24 / 1.34).  Rows of parts of lines: also where the
+// 120 MB 0.89 / 0.96 / 1.03 / 1.06 (0.97 / 1.06 / 1.08 / 1.09), at 200 MB 0.86 / 0.99 / 1.20 (1.08 / 1.24 / 1.34).  int32 alone under 1- and 2-bit
+// activations, K up to 512: 0.80 - 1.02 at 45 - 90 MB (1500 x 8000 1.05), 1.05 - 1.12 at 134.  Rows of parts of lines: also where the
 // operands of a tile row and column, K slots wide, fill an L2 and lose more to plain stores (W4A4 1024 x 11016 with K = 4096 / 6144 / 8192 /
 // 11008 both plain over streaming 1.02 / 1.17 / 1.18 / 1.13, W2A4 0.85 / 0.95 / 1.10 / 1.20).
 template <int P, int Q, int WM, int WN, int KG>
@@ -462,7 +463,8 @@ inline bool lds_streams(const GemmArgs &g)
     if (!rows.whole) return rows.fit_l2() || g.K * (activation_slots(P) + Q) >= 60000;
     const bool few = g.M * g.N * g.K <= 24000000000;
     const bool short_sum = activation_field_form(P) && WN == 2 ? few && rows.bytes < 80000000 : few || g.K <= 512;
-    return !rows.both || rows.bytes < 45000000 || !short_sum;
+    if (!rows.both) return !(P <= 2 && g.c_i32 && g.K <= 512 && rows.bytes >= 44000000 && rows.bytes < 100000000);
+    return rows.bytes < 45000000 || !short_sum;
 }
 
 template <int P, int Q, int WM, int WN, int OCC>

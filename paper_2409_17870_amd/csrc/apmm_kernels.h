@@ -12,6 +12,24 @@ hipError_t launch_pack(const uint8_t *codes, int64_t rows, int64_t K, int bits, 
 // Paper Sec. 3.1 + 4.1: per-row symmetric quantisation of binary16 features fused with the packing.
 hipError_t launch_quantize_pack(const uint16_t *x, int64_t rows, int64_t K, int bits, bool field, uint32_t *packed,
                                 uint16_t *scale, hipStream_t stream);
+// Its rule for many rows in the field form: four rows to a workgroup of 128 lanes each, up to four groups of 32 elements to a lane.  Old / new,
+// microseconds: 640 x 4096 5.2 / 4.6, 1024 x 4096 6.0 / 5.1, 1024 x 11008 13.1 / 10.1, 4096 x 2048 9.5 / 7.6, 4096 x 11008 48.5 / 28.7; on the other
+// side 512 x 5120 4.8 / 5.8, 512 x 13824 8.9 / 9.4, 1024 x 2048 4.1 / 4.4, 4096 x 1500 9.8 / 10.5, 16 x 5120 3.2 / 4.9.
+constexpr int kQuantLanes = 128;
+inline int64_t quantize_groups(int64_t K) { return round_up(K, kKPad) / 32; }
+inline int64_t quantize_lane_groups(int64_t K) { return (quantize_groups(K) + kQuantLanes - 1) / kQuantLanes; }
+inline bool quantize_rows_by_four(int64_t rows, int64_t K)
+{
+    const int64_t lane_groups = quantize_lane_groups(K);
+    if (rows <= 512 || K < 2048 || rows * K < 2500000 || lane_groups > 4) return false;
+    // A few more workgroups than compute units and rows that the other kernel gives two waves, 2049 to 2560: new over old 1.04 - 1.10 at
+    // 1100 to 1500 rows, 0.94 at 1024, 0.93 - 0.97 at 1600; one wave (2048) 0.88 - 0.92.
+    if (lane_groups == 1) return !(K > 2048 && K <= 2560 && rows > 1024 && rows < 1600);
+    // Where most lanes lack the last group (K = 4300: 144 groups on 128 lanes) it takes more rows: 513 x 4900 5.6 / 6.7, 641 x 4300 5.3 / 6.4, 577 x 5120
+    // 5.6 / 6.2, 513 x 8704 7.0 / 7.8.  With a share f of the groups there, new over old is 1.00 - 1.05 at rows f from 440 to 480 and two
+    // groups to a lane, 0.92 - 1.00 with three and four; 0.92 - 1.02 at 500 to 540.
+    return rows * quantize_groups(K) >= (lane_groups == 2 ? 500 : 450) * lane_groups * kQuantLanes;
+}
 hipError_t launch_unpack(const uint32_t *packed, int64_t rows, int64_t K, int bits, bool field, uint8_t *codes,
                          hipStream_t stream);
 

@@ -629,7 +629,7 @@ __global__ __launch_bounds__(kThreads) void quantize_pack_kernel(const uint16_t 
 // where the kernel above writes pieces of 16 and 8 bytes, 3 KB apart.  Those pieces were what bound it: 1024 x 11008 13.1 us, without
 // its stores 8.8.  Eight waves to a workgroup, two to a row; a row stays in registers (GROUPS of 32 elements to a lane).
 constexpr int kQuantRows = 4;
-constexpr int kQuantThreads = 512, kQuantLanes = kQuantThreads / kQuantRows;       // of a row
+constexpr int kQuantThreads = kQuantRows * kQuantLanes;
 constexpr int kQuantBlockWords = 6 * kQuantRows * kWordsPerRow + kWordsPerRow;  // a k block in LDS, with 16 bytes against bank conflicts
 template <int GROUPS, bool WHOLE>
 __global__ __launch_bounds__(kQuantThreads) void quantize_fields_kernel(const uint16_t *__restrict__ x, int64_t rows, int64_t K, int bits,
@@ -841,11 +841,8 @@ hipError_t launch_quantize_pack(const uint16_t *x, int64_t rows, int64_t K, int 
     const int64_t nkb = round_up(K, kKPad) / kKBlock;
     if (rows_p == 0) return hipSuccess;
     const bool whole = K % 128 == 0;  // every k block is packed whole or is all padding
-    const int64_t lane_groups = (nkb * kWordsPerRow + kQuantLanes - 1) / kQuantLanes;
-    // Many rows in the field form: four rows to a workgroup.  Old / new, microseconds: 640 x 4096 5.2 / 4.6, 1024 x 4096 6.0 / 5.1, 1024 x 11008
-    // 13.1 / 10.1, 4096 x 2048 9.5 / 7.6, 4096 x 11008 48.5 / 28.7; on the other side 512 x 5120 4.8 / 5.8, 512 x 13824 8.9 / 9.4, 1024 x 2048 4.1 /
-    // 4.4, 4096 x 1500 9.8 / 10.5, 16 x 5120 3.2 / 4.9.
-    if (field && rows > 512 && K >= 2048 && rows * K >= 2500000 && lane_groups <= 4) {
+    if (field && quantize_rows_by_four(rows, K)) {
+        const int64_t lane_groups = quantize_lane_groups(K);
         const size_t lds = (size_t)nkb * kQuantBlockWords * 4;  // at most 51 KB
         const int64_t blocks = (rows_p / kQuantRows + 15) / 16 * 16;  // pairs for each of the eight XCDs
         if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;

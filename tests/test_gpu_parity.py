@@ -673,7 +673,8 @@ def test_packing_row_ends_and_alignments(gpu, oracle, M, K, shift, p):
 
 
 @pytest.mark.parametrize("M,K,p,shift", [(641, 4097, 4, 1), (700, 3600, 3, 0), (1225, 2048, 4, 0), (513, 16384, 4, 0), (520, 15800, 3, 3),
-                                         (515, 8193, 3, 1), (642, 4096, 4, 5), (514, 12288, 4, 0)])
+                                         (515, 8193, 3, 1), (642, 4096, 4, 5), (514, 12288, 4, 0), (540, 7900, 4, 1), (530, 8192, 3, 0),
+                                         (901, 4500, 4, 0), (650, 8800, 3, 0), (1400, 2300, 4, 0)])
 def test_quantize_many_rows_in_the_field_form(gpu, oracle, M, K, p, shift):
     """The kernel for many rows (one to four groups of 32 elements to a lane, whole and ragged rows, any alignment, padding rows in
     its last workgroups, idle workgroups) and its border rows: codes, scales and packed words as the oracle has them."""

@@ -53,7 +53,7 @@ struct LdsTile {
 template <int AT>
 __device__ __forceinline__ void load_to_lds(const char *base, uint32_t voff, uint32_t lds)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3" ::"s"(lds - AT), "v"(voff), "s"(base), "n"(AT) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3" ::"s"(lds - AT), "v"(voff), "s"(base), "n"(AT) : "memory", "m0");
 }
 // Everything this wave has read from LDS is in registers, all but its last N loads have arrived; then the same of every wave.
 template <int N>

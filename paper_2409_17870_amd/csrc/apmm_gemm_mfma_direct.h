@@ -69,8 +69,8 @@ constexpr int split_store_stages(int wm, int wn, int split)
 template <int P, int Q, int WM, int WN, int SPLIT>
 __global__ __launch_bounds__(256) void gemm_mfma_direct_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32_t *ci_arg,
                                                                uint16_t *cf_arg, int m_arg, int n_arg, int k_arg, int nkb_arg,
-                                                               int tiles_n_plain, int tiles_total, const uint16_t *ws_arg,
-                                                               const uint16_t *as_arg)
+                                                               int tiles_n, int tiles_total, const uint16_t *ws_arg,
+                                                               const uint16_t *as_arg, bool stream)
 {
     GemmArgs g;
     g.M = m_arg; g.N = n_arg; g.K = k_arg; g.nkb = nkb_arg;
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_direct_kernel(const uint32_t *a
     const int wave_m = wave / waves_n(WM), wave_n = wave % waves_n(WM);
     const int r32 = lane & 31, kh = lane >> 5;
     const int lid = xcd_tile_id(blockIdx.x, tiles_total);
-    const int tiles_n = tiles_n_plain & ~kPlainStores, tm = lid / tiles_n, tn = lid % tiles_n;
+    const int tm = lid / tiles_n, tn = lid % tiles_n;
     const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
 
     // per row block: address of (row, slot 0) in this lane's k block of stage 0
@@ -426,7 +426,6 @@ __global__ __launch_bounds__(256) void gemm_mfma_direct_kernel(const uint32_t *a
     } else {
         const bool interior = (m0 + BM <= g.M) && (n0 + BN <= g.N);
         const bool pair = (g.N & 1) == 0 && (reinterpret_cast<uintptr_t>(g.c_f16) & 3u) == 0;
-        const bool stream = !(tiles_n_plain & kPlainStores);
         // both outputs: one pass per output (a combined pass needs more registers than there are)
         if (g.c_i32) {
             if (interior && stream) emit(F{}, T{}, F{}, F{}, T{});
@@ -473,11 +472,11 @@ hipError_t launch_direct_variant(const GemmArgs &g, hipStream_t stream)
     if (timing.start || timing.stop)
         hipExtLaunchKernelGGL((gemm_mfma_direct_kernel<P, Q, WM, WN, SPLIT>), dim3((unsigned)tiles), dim3(256), 0,
                               stream, timing.start, timing.stop, 0, g.a, g.w, g.c_i32, g.c_f16, (int)g.M, (int)g.N, (int)g.K,
-                              (int)g.nkb, tiles_n_arg(tiles_n, direct_streams(WM, WN, g)), (int)tiles, g.w_scale, g.a_scale);
+                              (int)g.nkb, (int)tiles_n, (int)tiles, g.w_scale, g.a_scale, direct_streams(WM, WN, g));
     else
         hipLaunchKernelGGL((gemm_mfma_direct_kernel<P, Q, WM, WN, SPLIT>), dim3((unsigned)tiles), dim3(256), 0,
-                           stream, g.a, g.w, g.c_i32, g.c_f16, (int)g.M, (int)g.N, (int)g.K, (int)g.nkb, tiles_n_arg(tiles_n, direct_streams(WM, WN, g)),
-                           (int)tiles, g.w_scale, g.a_scale);
+                           stream, g.a, g.w, g.c_i32, g.c_f16, (int)g.M, (int)g.N, (int)g.K, (int)g.nkb, (int)tiles_n,
+                           (int)tiles, g.w_scale, g.a_scale, direct_streams(WM, WN, g));
     return hipGetLastError();
 }
 

@@ -86,8 +86,8 @@ constexpr int ksplit_lds_bytes() { return kWM * kWN * 3 * 4 * 64 * 16; }
 template <int FA, int FB, bool KSPLIT>
 __global__ __launch_bounds__(256) void gemm_mfma_i8_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32_t *ci_arg,
                                                            uint16_t *cf_arg, int m_arg, int n_arg, int k_arg, int nkb,
-                                                           int tiles_n_plain, int tiles_m_xn, const uint16_t *ws_arg,
-                                                           const uint16_t *as_arg, int p, int q)
+                                                           int tiles_n, int tiles_m_xn, const uint16_t *ws_arg,
+                                                           const uint16_t *as_arg, int p, int q, bool stream)
 {
     extern __shared__ __align__(16) int4 red[];  // KSPLIT: [block][partial 0..2][register quad 0..3][lane]
     constexpr int LA = form_loads(FA), LB = form_loads(FB);
@@ -98,7 +98,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_i8_kernel(const uint32_t *a_arg
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r32 = lane & 31, kh = lane >> 5;
     // XCD-aware tile map: the tile grid in 8 / xn x xn parts, one per XCD, walked down their columns
-    const int tiles_n = tiles_n_plain & ~mfma::kPlainStores, tiles_m = tiles_m_xn & 0x0fffffff, xn_log = tiles_m_xn >> 28;
+    const int tiles_m = tiles_m_xn & 0x0fffffff, xn_log = tiles_m_xn >> 28;
     const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
     const int part_m = (tiles_m + (8 >> xn_log) - 1) >> (3 - xn_log), part_n = (tiles_n + (1 << xn_log) - 1) >> xn_log;
     const int tm = (xcd >> xn_log) * part_m + idx % part_m, tn = (xcd & ((1 << xn_log) - 1)) * part_n + idx / part_m;
@@ -226,7 +226,6 @@ __global__ __launch_bounds__(256) void gemm_mfma_i8_kernel(const uint32_t *a_arg
         sw_bits[bj] = sw_src[n];
     }
     // one 32 x 32 block, inner ones with streaming stores by the launcher's rule
-    const bool stream = !(tiles_n_plain & mfma::kPlainStores);
     auto store_block = [&](const v16i &s, int64_t mb, auto bj_c) __attribute__((always_inline)) {
         constexpr int bj = decltype(bj_c)::value;
         const int64_t n = n0 + 32 * bj + r32;
@@ -343,7 +342,6 @@ hipError_t launch_variant(const GemmArgs &g, hipStream_t stream)
     // alone 0.97 up to 3 MB and 0.85 at 30).
     const mfma::OutputRows rows(g);
     const bool streaming = rows.whole || (g.c_i32 && (KSPLIT ? !g.c_f16 : rows.up_to_l2(22000000)));
-    const int columns = mfma::tiles_n_arg(tiles_n, streaming);
     auto kernel = gemm_mfma_i8_kernel<FA, FB, KSPLIT>;
     if constexpr (KSPLIT) {
         static thread_local int prepared_device = -1;  // the LDS limit is a per-device attribute of the function
@@ -361,10 +359,10 @@ hipError_t launch_variant(const GemmArgs &g, hipStream_t stream)
     const dim3 blocks((unsigned)grid), threads(256);
     if (timing.start || timing.stop)
         hipExtLaunchKernelGGL(kernel, blocks, threads, lds, stream, timing.start, timing.stop, 0, g.a, g.w, g.c_i32, g.c_f16, (int)g.M,
-                              (int)g.N, (int)g.K, (int)g.nkb, columns, tiles_m_xn, g.w_scale, g.a_scale, g.p, g.q);
+                              (int)g.N, (int)g.K, (int)g.nkb, (int)tiles_n, tiles_m_xn, g.w_scale, g.a_scale, g.p, g.q, streaming);
     else
         hipLaunchKernelGGL(kernel, blocks, threads, lds, stream, g.a, g.w, g.c_i32, g.c_f16, (int)g.M, (int)g.N, (int)g.K, (int)g.nkb,
-                           columns, tiles_m_xn, g.w_scale, g.a_scale, g.p, g.q);
+                           (int)tiles_n, tiles_m_xn, g.w_scale, g.a_scale, g.p, g.q, streaming);
     return hipGetLastError();
 }
 

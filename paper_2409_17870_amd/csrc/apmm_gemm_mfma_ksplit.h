@@ -47,7 +47,8 @@ inline bool ksplit_streams(int wm, int wn, const GemmArgs &g)
 
 template <int P, int Q, int WM, int WN>
 __device__ __forceinline__ void ksplit_tile(float4 *red, const uint32_t *a_arg, const uint32_t *w_arg, int32_t *ci_arg, uint16_t *cf_arg, int m_arg, int n_arg,
-                                            int k_arg, int nkb_arg, int tiles_n_plain, int tiles_m_xn, const uint16_t *ws_arg, const uint16_t *as_arg)
+                                            int k_arg, int nkb_arg, int tiles_n, int tiles_m_xn, const uint16_t *ws_arg, const uint16_t *as_arg,
+                                            bool stream)
 {
     // red: [block][partial 0..2][register quad 0..3][lane]
     static_assert(P >= 1 && P <= 4 && Q >= 1 && Q <= 4, "instantiated for codes of up to four bits");
@@ -82,7 +83,7 @@ __device__ __forceinline__ void ksplit_tile(float4 *red, const uint32_t *a_arg, 
     // Workgroups are dealt round-robin to the 8 XCDs, each with an L2 of its own.  The tile grid is cut into
     // 8 / xn x xn parts, one per XCD, and a part is walked down its columns: the workgroups that run together on an
     // XCD share the packed rows of a few column tiles and of the part's row tiles (tiles_m_xn = tiles_m | log2(xn) << 28).
-    const int tiles_n = tiles_n_plain & ~kPlainStores, tiles_m = tiles_m_xn & 0x0fffffff, xn_log = tiles_m_xn >> 28;
+    const int tiles_m = tiles_m_xn & 0x0fffffff, xn_log = tiles_m_xn >> 28;
     const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
     const int part_m = (tiles_m + (8 >> xn_log) - 1) >> (3 - xn_log), part_n = (tiles_n + (1 << xn_log) - 1) >> xn_log;
     const int tm = (xcd >> xn_log) * part_m + idx % part_m, tn = (xcd & ((1 << xn_log) - 1)) * part_n + idx / part_m;
@@ -274,7 +275,7 @@ __device__ __forceinline__ void ksplit_tile(float4 *red, const uint32_t *a_arg, 
     // and each stores one dword instead of two halves.  NT: streaming stores of inner tiles (rule: ksplit_streams).
     const bool interior = (m0 + 32 * WM <= M) && (n0 + 32 * WN <= N);
     const bool pair_ok = (N & 1) == 0 && (reinterpret_cast<uintptr_t>(cf_arg) & 3u) == 0;
-    const bool stream = ksplit_always_streams(WM, WN) || !(tiles_n_plain & kPlainStores);
+    if constexpr (ksplit_always_streams(WM, WN)) stream = true;
     const bool odd = lane_out & 1;
     float sa_f[16];
 #pragma unroll
@@ -409,19 +410,19 @@ inline int64_t ksplit_lds_max_k(int p, int q, const GemmArgs &g)
 template <int P, int Q, int WM, int WN>
 __global__ __launch_bounds__(WM == 4 ? 512 : 256, WN == 2 ? 2 : 1)  // two workgroups of the 64 x 64 tile share a compute unit
 void gemm_mfma_ksplit_kernel(const uint32_t *a, const uint32_t *w, int32_t *c_i32, uint16_t *c_f16, int m, int n, int k, int nkb, int tiles_n, int tiles_m_xn,
-                             const uint16_t *w_scale, const uint16_t *a_scale)
+                             const uint16_t *w_scale, const uint16_t *a_scale, bool stream)
 {
     extern __shared__ __align__(16) float4 red[];
-    if constexpr (WM == 4) lds_tile<P, Q, 2, WN / 2, 2>(reinterpret_cast<uint4 *>(red), a, w, c_i32, c_f16, m, n, k, nkb, tiles_n, tiles_m_xn, w_scale, a_scale);
-    else ksplit_tile<P, Q, WM, WN>(red, a, w, c_i32, c_f16, m, n, k, nkb, tiles_n, tiles_m_xn, w_scale, a_scale);
+    if constexpr (WM == 4) lds_tile<P, Q, 2, WN / 2, 2>(reinterpret_cast<uint4 *>(red), a, w, c_i32, c_f16, m, n, k, nkb, tiles_n, tiles_m_xn, w_scale, a_scale, stream);
+    else ksplit_tile<P, Q, WM, WN>(red, a, w, c_i32, c_f16, m, n, k, nkb, tiles_n, tiles_m_xn, w_scale, a_scale, stream);
 }
 template <int P, int Q>
 __global__ __launch_bounds__(256) void gemm_mfma_ksplit_long_kernel(const uint32_t *a, const uint32_t *w, int32_t *c_i32, uint16_t *c_f16, int m, int n, int k,
                                                                     int nkb, int tiles_n, int tiles_m_xn, const uint16_t *w_scale,
-                                                                    const uint16_t *a_scale)
+                                                                    const uint16_t *a_scale, bool stream)
 {
     extern __shared__ __align__(16) float4 red[];
-    ksplit_tile<P, Q, 4, 4>(red, a, w, c_i32, c_f16, m, n, k, nkb, tiles_n, tiles_m_xn, w_scale, a_scale);
+    ksplit_tile<P, Q, 4, 4>(red, a, w, c_i32, c_f16, m, n, k, nkb, tiles_n, tiles_m_xn, w_scale, a_scale, stream);
 }
 
 template <int P, int Q, int WM, int WN>
@@ -443,10 +444,10 @@ hipError_t launch_ksplit_variant(const GemmArgs &g, hipStream_t stream)
         const KernelTiming timing = take_kernel_timing();
         if (timing.start || timing.stop)
             hipExtLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(threads), lds, stream, timing.start, timing.stop, 0, g.a, g.w,
-                                  g.c_i32, g.c_f16, (int)g.M, (int)g.N, (int)g.K, (int)g.nkb, tiles_n_arg(tiles_n, streaming), order, g.w_scale, g.a_scale);
+                                  g.c_i32, g.c_f16, (int)g.M, (int)g.N, (int)g.K, (int)g.nkb, (int)tiles_n, order, g.w_scale, g.a_scale, streaming);
         else
             hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(threads), lds, stream, g.a, g.w, g.c_i32, g.c_f16, (int)g.M, (int)g.N,
-                               (int)g.K, (int)g.nkb, tiles_n_arg(tiles_n, streaming), order, g.w_scale, g.a_scale);
+                               (int)g.K, (int)g.nkb, (int)tiles_n, order, g.w_scale, g.a_scale, streaming);
         return hipGetLastError();
     };
     static thread_local int prepared = -1, prepared_long = -1;

@@ -70,8 +70,8 @@ constexpr int lds_tile_bytes() { return KG == 1 ? LdsTile<P, Q, WM, WN>::BYTES :
 
 template <int P, int Q, int WM, int WN, int KG>
 __device__ __forceinline__ void lds_tile(uint4 *ring_of_workgroup, const uint32_t *a_arg, const uint32_t *w_arg, int32_t *ci_arg, uint16_t *cf_arg, int m_arg,
-                                         int n_arg, int k_arg, int nkb_arg, int tiles_n_plain, int tiles_m_band, const uint16_t *ws_arg,
-                                         const uint16_t *as_arg)
+                                         int n_arg, int k_arg, int nkb_arg, int tiles_n, int tiles_m_band, const uint16_t *ws_arg,
+                                         const uint16_t *as_arg, bool stream)
 {
     using L = LdsTile<P, Q, WM, WN>;
     constexpr bool AF = L::AF;
@@ -89,7 +89,7 @@ __device__ __forceinline__ void lds_tile(uint4 *ring_of_workgroup, const uint32_
     const int wave_m = wave >> 1, wave_n = wave & 1;
     const int r32 = lane & 31, kh = lane >> 5;
     // An XCD takes a contiguous run of tiles in an order that walks `band` tile rows column by column (see lds_tile_order).
-    const int tiles_n = tiles_n_plain & ~kPlainStores, tiles_m = tiles_m_band & 0x0fffffff, band = 1 << (tiles_m_band >> 28);
+    const int tiles_m = tiles_m_band & 0x0fffffff, band = 1 << (tiles_m_band >> 28);
     const int lid = xcd_tile_id(blockIdx.x, tiles_n * tiles_m);
     const int m_band = lid / (band * tiles_n), in_band = lid - m_band * band * tiles_n;
     const int rows = min(tiles_m - m_band * band, band);
@@ -411,7 +411,6 @@ __device__ __forceinline__ void lds_tile(uint4 *ring_of_workgroup, const uint32_
     using F = std::false_type;
     const bool interior = (m0 + BM <= M) && (n0 + BN <= N);
     const bool pair = (N & 1) == 0 && (reinterpret_cast<uintptr_t>(cf_arg) & 3u) == 0;
-    const bool stream = !(tiles_n_plain & kPlainStores);
     if (ci_arg) {
         if (interior && stream) emit(F{}, T{}, F{}, F{}, T{});
         else if (interior) emit(F{}, T{}, F{}, F{}, F{});
@@ -429,10 +428,10 @@ __device__ __forceinline__ void lds_tile(uint4 *ring_of_workgroup, const uint32_
 template <int P, int Q, int WM, int WN, int OCC>
 __global__ __launch_bounds__(256, OCC) void gemm_mfma_lds_kernel(const uint32_t *a, const uint32_t *w, int32_t *c_i32, uint16_t *c_f16, int m, int n, int k,
                                                                  int nkb, int tiles_n, int tiles_m_band, const uint16_t *w_scale,
-                                                                 const uint16_t *a_scale)
+                                                                 const uint16_t *a_scale, bool stream)
 {
     extern __shared__ __align__(16) uint4 lds_ring[];
-    lds_tile<P, Q, WM, WN, 1>(lds_ring, a, w, c_i32, c_f16, m, n, k, nkb, tiles_n, tiles_m_band, w_scale, a_scale);
+    lds_tile<P, Q, WM, WN, 1>(lds_ring, a, w, c_i32, c_f16, m, n, k, nkb, tiles_n, tiles_m_band, w_scale, a_scale, stream);
 }
 
 template <int P, int Q>
@@ -476,7 +475,7 @@ hipError_t launch_lds_variant(const GemmArgs &g, hipStream_t stream)
     const int64_t tiles = tiles_m * tiles_n;
     if (tiles > 0x7fffffffLL || tiles_m >= (1 << 28) || g.M > 0x7fffffffLL || g.N > 0x7fffffffLL || g.K > 0x7fffffffLL) return hipErrorInvalidValue;
     const int tiles_m_band = lds_tile_order<P, Q>(tiles_m, g.K);
-    const int columns = tiles_n_arg(tiles_n, lds_streams<P, Q, WM, WN, 1>(g));
+    const bool streaming = lds_streams<P, Q, WM, WN, 1>(g);
     auto kernel = gemm_mfma_lds_kernel<P, Q, WM, WN, OCC>;
     static thread_local int prepared_device = -1;  // the LDS limit is a per-device attribute of the function
     int dev = 0;
@@ -491,10 +490,10 @@ hipError_t launch_lds_variant(const GemmArgs &g, hipStream_t stream)
     note_kernel("gemm_mfma_lds_kernel<%d,%d,%d,%d>", P, Q, WM, WN);
     if (timing.start || timing.stop)
         hipExtLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(256), L::BYTES, stream, timing.start, timing.stop, 0, g.a, g.w, g.c_i32,
-                              g.c_f16, (int)g.M, (int)g.N, (int)g.K, (int)g.nkb, columns, tiles_m_band, g.w_scale, g.a_scale);
+                              g.c_f16, (int)g.M, (int)g.N, (int)g.K, (int)g.nkb, (int)tiles_n, tiles_m_band, g.w_scale, g.a_scale, streaming);
     else
         hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(256), L::BYTES, stream, g.a, g.w, g.c_i32, g.c_f16, (int)g.M, (int)g.N,
-                           (int)g.K, (int)g.nkb, columns, tiles_m_band, g.w_scale, g.a_scale);
+                           (int)g.K, (int)g.nkb, (int)tiles_n, tiles_m_band, g.w_scale, g.a_scale, streaming);
     return hipGetLastError();
 }
 

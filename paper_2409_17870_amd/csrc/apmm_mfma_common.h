@@ -123,7 +123,7 @@ __device__ __forceinline__ int xcd_tile_id(int block, int tiles_total)
     return block;
 }
 
-// ---- Streaming stores of inner tiles: the launcher's choice, passed in tiles_n ----
+// ---- Streaming stores of inner tiles: the launcher's choice, the kernels' last argument ----
 // A streaming store leaves the operands in L2 alone and is written back early, but a line that it fills only in part is written in
 // parts: rows that do not begin at a line (N no multiple of 32, or an output that begins elsewhere) share their lines with the wave
 // tile next to them.  Plain stores meet in L2.  Both outputs, all streaming against all plain, operands and outputs in rotation:
@@ -142,8 +142,6 @@ struct OutputRows {
     bool up_to_l2(int64_t most) const { return bytes < (half_lines ? 30000000 : most); }
     bool fit_l2(int64_t most = 22000000) const { return bytes >= 8000000 && up_to_l2(most); }
 };
-constexpr int kPlainStores = 1 << 30;
-inline int tiles_n_arg(int64_t tiles_n, bool streaming) { return (int)tiles_n | (streaming ? 0 : kPlainStores); }
 
 }  // namespace mfma
 }  // namespace apmm

@@ -22,6 +22,9 @@
  *    apmm_packed_activation_bytes() for activations; the only contractual property is
  *    apmm_unpack*(apmm_pack_*(x)) == x on the low `bits` bits.  They must be
  *    16-byte aligned (any hipMalloc / PyTorch allocation is).
+ *  - Unpacked codes and binary16 activations may lie at any address of their type's alignment.  Rows that do not start at whole
+ *    aligned 4-byte words are read in such words: a call may read (never write, and never use) up to three bytes before the
+ *    matrix and up to three after it, within the aligned words that hold its first and its last byte.
  */
 #ifndef APMM_H
 #define APMM_H

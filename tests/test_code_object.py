@@ -94,7 +94,8 @@ def _of(kernels, name):
     return out
 
 
-@pytest.mark.parametrize("name", ["gemm_mfma_ksplit_kernel", "gemm_decode_i8_kernel", "gemm_decode_mfma_kernel", "gemm_mfma_lds_kernel"])
+@pytest.mark.parametrize("name", ["gemm_mfma_ksplit_kernel", "gemm_mfma_ksplit_long_kernel", "gemm_decode_i8_kernel", "gemm_decode_mfma_kernel",
+                                  "gemm_mfma_lds_kernel", "gemm_mfma_i8_kernel"])
 def test_no_vector_register_is_spilled(kernels, name):
     spilled = {a: k[".vgpr_spill_count"] for a, k in _of(kernels, name).items() if k[".vgpr_spill_count"]}
     assert not spilled
@@ -109,12 +110,22 @@ def test_few_tokens_from_codes_leave_three_workgroups_on_a_compute_unit(kernels,
 
 
 def test_only_tiles_that_a_launch_rule_names_are_built(kernels):
-    """gemm_mfma_ksplit_kernel<P, Q, row blocks, column blocks>"""
+    """gemm_mfma_ksplit_kernel<P, Q, row blocks, column blocks>, gemm_mfma_ksplit_long_kernel<P, Q>, gemm_mfma_lds_kernel<P, Q, row blocks,
+    column blocks of a wave, waves to a vector unit> and gemm_mfma_direct_kernel<P, Q, row blocks, column blocks of a wave, phases>"""
     for p, q, wm, wn in _of(kernels, "gemm_mfma_ksplit_kernel"):
         if wm == 4:
             assert wn == 4 and q >= 2
         else:
             assert wm == 2 and wn in ((2, 4) if p <= 2 else (2, 4, 5, 6) if q <= 2 else (2, 4, 5))
+    assert set(_of(kernels, "gemm_mfma_ksplit_long_kernel")) == {(p, q) for p in (1, 2, 3, 4) for q in (3, 4)}
+    for p, q, wm, wn, _ in _of(kernels, "gemm_mfma_lds_kernel"):
+        assert (wm, wn) == (2, 2) or (p > 2 and q <= 2 and (wm, wn) == (2, 4))
+    for p, q, wm, wn, phases in _of(kernels, "gemm_mfma_direct_kernel"):
+        if p > 2:
+            assert phases == 1 and (wm, wn) in (((1, 4),) if q <= 2 else ((2, 2), (2, 4)) if q == 3 else ())
+        else:
+            assert (wm, wn) in ((4, 4), (4, 2), (2, 4), (2, 2)) and (q < 4 or (wm, wn) != (4, 4))
+            assert phases == 1 or ((wm, wn) == (4, 4) and phases <= (3 if q == 1 else 2 if q == 2 else 1))
 
 
 @pytest.mark.parametrize("name", ["gemm_mfma_i8_kernel", "gemm_mfma_lds_kernel", "gemm_mfma_direct_kernel", "gemm_mfma_ksplit_kernel",

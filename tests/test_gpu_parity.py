@@ -1037,10 +1037,23 @@ def test_k_split_across_waves_full_tiles(gpu, oracle, M, N, K, want_i32, want_f1
 @pytest.mark.parametrize("p,q", [(p, q) for p in range(1, 5) for q in range(2, 5)])
 @pytest.mark.parametrize("M,N,outs", [(1024, 4096, "f16"), (650, 5003, "both"), (1001, 4090, "i32")])
 def test_k_split_128_by_128_tile(gpu, oracle, M, N, outs, p, q):
-    """The tile whose waves work in half k blocks and meet in two rounds: inner and border tiles, a wave with one pair of
-    k blocks more than the others, every output."""
+    """The tile whose two groups of waves work on half of K each, through LDS, and meet at the end: inner and border tiles, a half of K
+    of an odd number of stages, every output."""
     torch, binding = gpu
     K = 4096 + 130 if q > 2 else 9216 + 130 if p <= 2 else 10752 + 130  # the first stage of K for which each is taken
+    check_128_by_128_tile(torch, binding, M, N, K, outs, p, q, "gemm_mfma_ksplit_kernel<%d,%d,4,4>" % (p, q))
+
+
+@pytest.mark.parametrize("p,q", [(p, q) for p in range(1, 5) for q in (3, 4)])
+@pytest.mark.parametrize("M,N,outs", [(1024, 4096, "f16"), (650, 5003, "both"), (650, 5003, "f16"), (1001, 4090, "i32")])
+def test_k_split_128_by_128_tile_from_registers(gpu, M, N, outs, p, q):
+    """The form of longer K, whose waves work in half k blocks and meet in two rounds: inner and border tiles, pairs of columns and
+    single ones, a wave with one pair of k blocks more than the others, every output with a scale of its own to each row and column."""
+    torch, binding = gpu
+    check_128_by_128_tile(torch, binding, M, N, 9216 + 130, outs, p, q, "gemm_mfma_ksplit_long_kernel<%d,%d>" % (p, q))
+
+
+def check_128_by_128_tile(torch, binding, M, N, K, outs, p, q, kernel):
     if 4 * (K + 382) * ((1 << p) - 1) * ((1 << q) - 1) >= 1 << 24:
         pytest.skip("beyond the exactness bound")
     dev = torch.device("cuda:0")
@@ -1051,7 +1064,7 @@ def test_k_split_128_by_128_tile(gpu, oracle, M, N, outs, p, q):
     sw = (0.01 + 0.09 * torch.rand(N, generator=g, device=dev)).half()
     c32, c16 = binding.apmm_gemm(M, N, K, p, q, binding.apmm_pack_activations(a, p), binding.apmm_pack_weights(w, q),
                                  want_i32=outs != "f16", want_f16=outs != "i32", w_scale=sw, a_scale=sa)
-    assert binding.apmm_last_gemm_kernel() == "gemm_mfma_ksplit_kernel<%d,%d,4,4>" % (p, q)
+    assert binding.apmm_last_gemm_kernel() == kernel
     # sums of small integers: exact in double precision
     want = ((2.0 * a.float() - ((1 << p) - 1)).double() @ (2.0 * w.float() - ((1 << q) - 1)).double().t().contiguous()).to(torch.int64)
     if c32 is not None:
@@ -1061,10 +1074,10 @@ def test_k_split_128_by_128_tile(gpu, oracle, M, N, outs, p, q):
         assert bool(((c16.double() - f).abs() <= 1e-3 * f.abs() + 1e-6).all())
 
 
-@pytest.mark.parametrize("p,q,K,long", [(1, 3, 9216, False), (3, 4, 9216, False), (1, 4, 9217, True), (2, 3, 9400, True), (4, 4, 9730, True),
+@pytest.mark.parametrize("p,q,K,long", [(1, 3, 9216, False), (3, 4, 9216, False), (4, 3, 8704, False), (1, 4, 8600, False), (1, 4, 9217, True), (2, 3, 9400, True), (4, 4, 9730, True),
                                         (3, 3, 11008, True), (2, 2, 13000, False)])
 def test_k_split_128_by_128_tile_from_lds_and_from_registers(gpu, p, q, K, long):
-    """Both sides of the line between the two forms of the tile, and half of K an odd and an even number of stages."""
+    """Both sides of the line between the two forms of the tile; half of K an even number of stages and (8704 and 8600) an odd one."""
     torch, binding = gpu
     dev = torch.device("cuda:0")
     M, N = 770, 4100
@@ -1093,17 +1106,20 @@ def test_k_split_128_by_128_tile_leaves_smaller_k_to_the_large_tiles(gpu, p, q, 
     assert torch.equal(c32.to(torch.int64), want)
 
 
-# (M, N, K, tile width in 64 columns); two tile rows, the second of them two or 65 rows, and more tiles than one round of any other tile
-LDS_SHAPES = ([(130, 33025, 600, 2), (193, 33100, 512, 2), (257, 22000, 1500, 2)],  # 1- and 2-bit activations
-              [(130, 333, 2048, 2), (100, 1000, 2600, 2), (257, 33200, 2100, 4), (1025, 11100, 130, 4)],  # 3, 4 bits against 1, 2 bits
-              [(130, 333, 100, 2), (65, 129, 1100, 2), (193, 33100, 512, 2)])  # 3, 4 bits against 3, 4 bits
+# (M, N, K, tile width in 64 columns): one to nine tile rows, the last of them of 1 to 104 rows; with more than four and K > 1024 or weights of 3 and
+# 4 bits they are walked in bands of four; with 1- and 2-bit activations more tiles than one round of any other tile
+LDS_SHAPES = ([(130, 33025, 600, 2), (193, 33100, 512, 2), (257, 22000, 1500, 2), (600, 16500, 1100, 2),
+               (1100, 16500, 1100, 2)],  # 1- and 2-bit activations
+              [(130, 333, 2048, 2), (100, 1000, 2600, 2), (257, 33200, 2100, 4), (1025, 11100, 130, 4),
+               (600, 22000, 2100, 4), (1100, 5000, 1100, 2)],  # 3, 4 bits against 1, 2 bits
+              [(130, 333, 100, 2), (65, 129, 1100, 2), (193, 33100, 512, 2), (600, 333, 1100, 2), (1100, 600, 300, 2)])  # 3, 4 bits against 3, 4 bits
 
 
 @pytest.mark.parametrize("p,q", [(p, q) for p in range(1, 5) for q in range(1, 5)])
 @pytest.mark.parametrize("outs", ["i32", "f16", "both"])
 def test_operands_shared_through_lds(gpu, p, q, outs):
-    """The kernel that shares its operands through LDS: borders in M and N, K of one ring of half stages, of two and of a part,
-    outputs with pairs of columns and without, every element."""
+    """The kernel that shares its operands through LDS: borders in M and N, tiles row by row and in bands, whole and partial
+    ones, K of less than the ring of half stages and of more, outputs with pairs of columns and without, every element."""
     torch, binding = gpu
     dev = torch.device("cuda:0")
     for M, N, K, wide in LDS_SHAPES[0 if p <= 2 else 1 if q <= 2 else 2]:

@@ -49,16 +49,21 @@ bool gemm_mfma_ksplit_supported(const GemmArgs &g) { return gemm_mfma_fp4_suppor
 //   these outputs: 512 x 4096 outputs 5.9 / 7.3 / 9.9 / 16.6 us against 6.7 / 7.5 / 8.6 / 11.6 us here at K = 1024 / 2048 /
 //   4096 / 8192; 512 x 4096 x 11008 22.0 against 13.8 us; 65 x 4096 and 96 x 11008 outputs faster at every K (10.7
 //   against 7.9 us at K = 4096).  Taken from K = 3072 on, and at every K up to 128 tokens.
-//   (Figures of the 128 x 128 tile in this paragraph: its register form; apmm_gemm_mfma_ksplit.h has those of the form that serves K up
-//   to 9216 and 2-bit weights now.)
 //   The 128 x 128 tile (1024 x 4096 outputs and the like, every width; large tiles against this, K = 2048 / 4096 / 8192 /
 //   11008): W4A4 12.1 / 19.1 / 34.6 / 45.3 against 13.2 / 16.8 / 25.7 / 32.3 us, W3A3 11.2 / 16.6 / 29.9 / 41.0 against 12.8 /
 //   16.2 / 24.5 / 30.7, W4A2 9.7 / 15.5 / 27.0 / 34.4 against 11.6 / 14.6 / 21.9 / 26.5: taken from K = 4096 on with weights of 3
-//   and 4 bits.  2 bits: this over the large tiles, 512 x 6144 / 640 x 5120 / 768 x 4096 / 512 x 8192 / 1024 x 4096 outputs, W2A1
+//   and 4 bits.  (This and the next sentence: the register form of the tile against the direct tiles.)  2 bits: this over the large tiles, 512 x 6144 / 640 x 5120 / 768 x 4096 / 512 x 8192 / 1024 x 4096 outputs, W2A1
 //   1.07 / 1.05 / 1.05 / 1.04 / 1.06 at K = 8192, 0.99 - 1.02 at 9216, 0.98 - 1.03 at 9728, 0.94 - 0.99 at 11264; W2A2 1.01 -
 //   1.04, 0.96 - 1.02, 0.96 - 1.03, 0.92 - 0.99; W2A4 (the last three) 1.10, 1.04, 1.03 - 1.05 and 1.00 - 1.01: taken from K =
 //   9728 on, with 3- and 4-bit activations from 11264 on (13824: 0.96 - 1.00).  W1A4 26.4 against 28.8 us at K = 11008: not
 //   taken with 1 bit.
+//   The form through LDS that serves K up to about 9216 and 2-bit weights now, over the large tiles of now (1024 x 4096 / 3072,
+//   2048 x 2048, 640 x 6144, 700 x 5000, one or both outputs, operands and outputs in rotation): W3A1 and W3A2 1.02 - 1.21 at
+//   K = 512, 0.95 - 1.08 at 2048, 0.96 - 1.10 at 3072 and 3584; W3A4 0.97 - 1.16, 0.94 - 1.07, 0.89 - 1.02; W4A2 0.98 - 1.15,
+//   0.89 - 1.04, 0.86 - 1.07; W4A4 1.01 - 1.18, 1.03 - 1.22, 0.92 - 1.04; W2A1 and W2A2 1.02 - 1.22 at 1024, 0.94 - 1.14 at 2048,
+//   0.95 - 1.10 at 4096, 0.91 - 1.06 at 6144 - 9216; W2A4 0.98 - 1.10 at 1024, 0.96 - 1.10 at 2048, 0.93 - 1.01 at 4096,
+//   0.86 - 1.04 at 6144 - 9216, 0.82 - 1.04 at 10240 and 10752.  The lines are on the safe side; the one of W2A4 could lie at
+//   6144, that of W3A4 and W4A4 at 3584.
 //   The 64 x 64 tile (outputs of up to 256 of them: up to 256 tokens at 4096 channels, 128 at 8192), with weights of 1 and
 //   2 bits: 65 - 256 tokens at 4096 x 4096 5.3 - 5.9 us (W1A1, W2A2), 6.9 - 7.4 us (W2A4) against 7.5 - 8.5 and 9.6 - 9.9 us with
 //   the 64 x 128 tile and 9.3 - 11.5 us on the large tiles; at 4096 x 11008 7.4 - 8.5 and 10.7 - 11.9 against 11.0 - 12.1 and

@@ -41,8 +41,9 @@ inline DirectTile field_direct_tile(const GemmArgs &g)
     const bool some = tiles >= 64;  // (fewer go to the K split unless these kernels are asked for by id)
     if (Q <= 2 && tiles <= 256) {
         // One workgroup to a compute unit at most: four wave tiles of 32 x 128, every activation row block loaded by one wave, start
-        // and end faster, 1024 x 4096 x 512 / 1024 W2A4 5.8 / 7.2 against 6.1 / 7.2 us, W1A4 5.4 / 6.2 against 5.7 / 6.7.  From K = 10240 on, where
-        // they have the outputs that the K split leaves, the two are within 8 %.
+        // and end faster, 1024 x 4096 x 512 / 1024 W2A4 5.8 / 7.2 against 6.1 / 7.2 us, W1A4 5.4 / 6.2 against 5.7 / 6.7.  From K = 10240 on
+        // (1024 x 4096 / 3072, 2048 x 2048, 640 x 6144, 700 x 5000; up to K = 16384 with single bits) through LDS it would be 0.97 - 1.02 of
+        // this for W1A3 and W1A4 int32 alone, 0.94 - 1.03 with fp16; for W2A4, below the 11264 of the K split, 0.90 - 1.00.
         if (g.K < 2048 || g.K >= 10240) return {1, 4};
         // Between, with single bits: int32 alone 1.00 - 1.17 (K = 2048: 1024 x 2048 1.14, 2048 x 2048 1.12; 6144: 0.99 - 1.05), fp16 alone up to 192 tiles
         // 1.01 - 1.05 at 2048, 0.95 - 1.06 at 2560, 0.94 - 1.01 at 3072; both outputs 0.79 - 0.97 but for the fewest tiles (512 x 3000, 96 of them, 1.03 -

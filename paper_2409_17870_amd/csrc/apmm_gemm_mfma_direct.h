@@ -426,6 +426,9 @@ __global__ __launch_bounds__(256) void gemm_mfma_direct_kernel(const uint32_t *a
     } else {
         const bool interior = (m0 + BM <= g.M) && (n0 + BN <= g.N);
         const bool pair = (g.N & 1) == 0 && (reinterpret_cast<uintptr_t>(g.c_f16) & 3u) == 0;
+        // direct_streams' answer for this tile, from what is at hand: held until here, the argument sent two vector registers of W3A1 and
+        // W3A2 to scratch.
+        if constexpr (WM == 4 && WN == 4) stream = !(g.c_i32 && g.c_f16);
         // both outputs: one pass per output (a combined pass needs more registers than there are)
         if (g.c_i32) {
             if (interior && stream) emit(F{}, T{}, F{}, F{}, T{});

@@ -95,9 +95,12 @@ def _of(kernels, name):
 
 
 @pytest.mark.parametrize("name", ["gemm_mfma_ksplit_kernel", "gemm_mfma_ksplit_long_kernel", "gemm_decode_i8_kernel", "gemm_decode_mfma_kernel",
-                                  "gemm_mfma_lds_kernel", "gemm_mfma_i8_kernel"])
+                                  "gemm_mfma_lds_kernel", "gemm_mfma_i8_kernel", "gemm_mfma_direct_kernel"])
 def test_no_vector_register_is_spilled(kernels, name):
+    """But for the 256 x 256 tile of single bits on both sides in one phase, which keeps 16 in scratch."""
     spilled = {a: k[".vgpr_spill_count"] for a, k in _of(kernels, name).items() if k[".vgpr_spill_count"]}
+    if name == "gemm_mfma_direct_kernel":
+        assert spilled.pop((1, 1, 4, 4, 1), 0) <= 16
     assert not spilled
 
 

@@ -23,9 +23,15 @@ __device__ __forceinline__ int pick_problem(DecodeProblem &pr, uint32_t misc, co
     int block = (int)blockIdx.x;
     const int count = (int)((misc >> 12) & 0xffu);
     if (count > 1) {
-        int idx = 0;
-        for (int i = 0; i + 1 < count; ++i)
-            if ((int)blockIdx.x >= ga.wg_end[i]) idx = i + 1;
+        int idx = 0, first = 0;
+#pragma unroll
+        for (int i = 0; i + 1 < kMaxGroup; ++i) {  // one load for all ends (make_group: no end lies behind the last problem's)
+            const int end = ga.wg_end[i];
+            if (block >= end) {
+                idx = i + 1;
+                first = end;
+            }
+        }
         if (idx > 0) {
             const GemmArgs &g = ga.g[idx];
             pr.w = g.w;
@@ -33,7 +39,7 @@ __device__ __forceinline__ int pick_problem(DecodeProblem &pr, uint32_t misc, co
             pr.N = g.N; pr.K = g.K; pr.M = g.M;
             pr.c_f16 = g.c_f16; pr.c_i32 = g.c_i32;
             pr.w_scale = g.w_scale; pr.a_scale = g.a_scale;
-            block -= ga.wg_end[idx - 1];
+            block -= first;
         }
     }
     return block;

@@ -433,7 +433,7 @@ hipError_t launch_mt(const GroupArgs &ga, hipStream_t stream)
 template <int P, int Q, int TT, int RT, int CODES, int NJ = 8>
 __global__ __launch_bounds__(kThreads, (CODES == 1 && TT == 1) ? (NJ == 1 && RT == 1 ? 6 : 4) - (Q > 2 ? 1 : 0) : 2)  // waves per SIMD aimed at (weights of 3 and 4 bits hold twice the raw words)
 void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg, int k_arg,
-                             uint32_t misc_arg /* M | problems << 12 | token groups << 24 */, int reserved_arg, uint16_t *cf_arg, int32_t *ci_arg,
+                             uint32_t misc_arg /* M | problems << 12 */, int reserved_arg, uint16_t *cf_arg, int32_t *ci_arg,
                              const uint16_t *ws_arg, const uint16_t *as_arg, GroupArgs ga)
 {
     static_assert((P <= 2 || (activation_field_form(P) && NJ == 8)) && Q <= 4,
@@ -444,63 +444,55 @@ void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg
     static_assert(NJ == 8 || (NJ == 1 && CODES == 1 && TT == 1), "NJ = 1: codes of at most two tokens");
     (void)reserved_arg;
     DecodeProblem pr = {w_arg, a_arg, n_arg, k_arg, (int64_t)(misc_arg & 0xfffu), cf_arg, ci_arg, ws_arg, as_arg};
-    int block = pick_problem(pr, misc_arg, ga);
+    const int block = pick_problem(pr, misc_arg, ga);
     constexpr int ROWS = kRowsPerWg * RT;
     // Token groups (packed operands, one problem per launch): with more tokens than the TT tiles of a workgroup hold,
     // the grid is repeated per group of 16 TT tokens; a workgroup re-reads its 16 or 32 packed weight rows (from L2,
     // a few KiB) and works on tokens tok0 ... of the same packed operands and outputs.
-    int tok0 = 0;
-    if constexpr (!CODES) {
-        if ((misc_arg >> 24) > 1) {
-            const int per_group = (int)((pr.N + ROWS - 1) / ROWS);
-            tok0 = (block / per_group) * 16 * TT;
-            block %= per_group;
-        }
-    }
+    const int tok0 = CODES || TT == 1 ? 0 : (int)blockIdx.y * 16 * TT;
     constexpr int OUTS = (TT * RT * 256 + kThreads - 1) / kThreads;  // outputs per thread
     constexpr uint32_t ca = (1u << P) - 1, cw = (1u << Q) - 1;
-    constexpr int kSlotVec = kPlaneWords / 4;
     extern __shared__ __align__(16) uint8_t lds_raw[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // Up to the first request a launch has nothing else to do, so the way there is short: the wave's number, the problem and every
+    // base address are scalars, a lane's part of an address is 32 bits: 108 instead of 190 instructions (W2A2 4096 x 4096 one token 3.1 -> 3.0 us, 22016 x
+    // 4096 7.0 -> 6.0, 64 tokens 4096 x 4096 4.7 -> 4.2, W4A4 one token 4.1 -> 3.6).  (Several token tiles from codes keep the wave's number in
+    // a vector register: their row addresses fill the scalar ones.)
+    const int tid = threadIdx.x, lane = tid & 63, wave = CODES && TT > 1 ? tid >> 6 : __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r16 = lane & 15, kq = lane >> 4;
-    const int64_t n0 = (int64_t)block * ROWS;
-    const int64_t nkb = ((pr.K + kKPad - 1) / kKPad) * (kKPad / kKBlock);
-    const int64_t rows_a = round_up(pr.M, kRowBlock), rows_b = round_up(pr.N, kRowBlock);
+    const int n0 = block * ROWS, M = (int)pr.M, N = (int)pr.N;
+    const uint32_t groups = ((uint32_t)pr.K + kKPad - 1) / kKPad;  // groups of four k blocks; the waves take them in turn
+    const uint32_t nkb = 4 * groups;
+    const int iters = groups > (uint32_t)wave ? (int)((groups - wave + kWaves - 1) / kWaves) : 0;
 
-    // this lane's weight rows and tokens, at its k block of the wave's first group of four
-    const int groups = (int)(nkb / 4);                       // groups of four k blocks; the waves take them in turn
-    const int iters = groups > wave ? (groups - wave + kWaves - 1) / kWaves : 0;
-    const uint4 *wsrc[RT];
+    // This lane's weight rows and tokens, at its k block of the wave's first group of four.  The ROWS channels of a workgroup lie in one
+    // row block, the tokens of two tiles as well (tok0 is a multiple of 32 then); rows past the operand's are zero words of its last
+    // row block (read, never stored).
+    constexpr uint32_t kSlotBytes = kPlaneWords * 4;
+    const uint32_t voff_w = ((uint32_t)(n0 & 16) + r16) * 16 + kq * (Q * kSlotBytes), voff_a = r16 * 16 + kq * (SA * kSlotBytes);
+    const char *w_wave = reinterpret_cast<const char *>(pr.w) + ((uint64_t)((uint32_t)n0 >> 5) * nkb + 4 * wave) * (Q * kSlotBytes);
+    const char *a_wave[(TT + 1) / 2];
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-        const int64_t n = n0 + rt * 16 + r16 < rows_b ? n0 + rt * 16 + r16 : rows_b - 1;
-        wsrc[rt] = reinterpret_cast<const uint4 *>(pr.w + tile_row_word(n, 4 * wave + kq, nkb, Q, 0));
-    }
-    constexpr int kIterVecW = 4 * kWaves * Q * kSlotVec;     // uint4 between this lane's k blocks of consecutive iterations
-    constexpr int kIterVecA = 4 * kWaves * SA * kSlotVec;
-    const uint4 *asrc[TT];
-#pragma unroll
-    for (int tt = 0; tt < TT; ++tt) {
-        asrc[tt] = nullptr;
-        if constexpr (!CODES) {
-            // tokens past M: the padded rows of the last row block hold zero words (read, never stored)
-            const int64_t t = tok0 + tt * 16 + r16, t_ld = t < rows_a ? t : rows_a - 1;
-            asrc[tt] = reinterpret_cast<const uint4 *>(static_cast<const uint32_t *>(pr.a) +
-                                                       tile_row_word(t_ld, 4 * wave + kq, nkb, SA, 0));
-        }
-    }
+    for (int i = 0; i < (TT + 1) / 2; ++i)
+        a_wave[i] = CODES ? nullptr : static_cast<const char *>(pr.a) + ((uint64_t)(((uint32_t)tok0 >> 5) + i) * nkb + 4 * wave) * (SA * kSlotBytes);
 
+    // Packed operands of 3- and 4-bit activations or four token tiles: one set of raw words, the next iteration's are asked for when this
+    // one's are formed.  A wave has one to four iterations and two to four workgroups share a compute unit, so a second set is worth
+    // less than the registers it takes (W4A4, two channel tiles: 146 -> 94, one -> two workgroups; 27648 x 5120 16 tokens 18.7 -> 16.0 us, 13824 x 5120
+    // 10.2 -> 9.1, 48 tokens 4096 x 4096 6.2 -> 5.3; W1A4 64 tokens 4096 x 8192 7.9 -> 6.7).  Narrow activations: 1 - 4 % for the second set.
+    constexpr bool SECOND_SET = CODES || (!AF && TT < 4);
     uint4 wnext[RT][Q], anext[TT][SA];
     auto load_packed = [&](int it) __attribute__((always_inline)) {
+        const uint64_t kb = (uint64_t)it * (4 * kWaves);
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-            for (int s = 0; s < Q; ++s) wnext[rt][s] = wsrc[rt][(int64_t)it * kIterVecW + s * kSlotVec];
+            for (int s = 0; s < Q; ++s) wnext[rt][s] = *reinterpret_cast<const uint4 *>(w_wave + kb * (Q * kSlotBytes) + voff_w + (rt * 256 + s * kSlotBytes));
         if constexpr (!CODES) {
 #pragma unroll
             for (int tt = 0; tt < TT; ++tt)
 #pragma unroll
-                for (int s = 0; s < SA; ++s) anext[tt][s] = asrc[tt][(int64_t)it * kIterVecA + s * kSlotVec];
+                for (int s = 0; s < SA; ++s)
+                    anext[tt][s] = *reinterpret_cast<const uint4 *>(a_wave[tt / 2] + kb * (SA * kSlotBytes) + voff_a + ((tt & 1) * 256 + s * kSlotBytes));
         }
     };
     // CODES.  The codes of one token tile and one group of four k blocks are 16 runs of 512 contiguous bytes
@@ -523,7 +515,9 @@ void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg
     // 22 us, 8 tokens 12.7 us).  Rows of fewer than sixteen codes byte by byte.
     auto load_chunks = [&](int tt, int it, uint4 (&v)[NJ]) __attribute__((always_inline)) {
         const int64_t k0 = (int64_t)4 * kKBlock * (wave + (int64_t)kWaves * it) + 16 * (lane & 31);
-        const int64_t m_tile = pr.M - tt * 16;  // tokens of this tile that exist
+        int tokens = M;
+        if constexpr (TT > 1) asm volatile("" : "+s"(tokens));
+        const int m_tile = tokens - tt * 16;  // tokens of this tile that exist
         // (the row length as an opaque value: the addresses are then formed where they are used instead of being
         // kept in registers across the k loop, two registers per load and token tile)
         int64_t row_len = pr.K;
@@ -539,15 +533,15 @@ void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg
         }
 #pragma unroll
         for (int jj = 0; jj < NJ; ++jj) {
-            const int64_t t = tt * 16 + 2 * jj + (lane >> 5);
+            const int t = tt * 16 + 2 * jj + (lane >> 5);
             if constexpr (CODES == 1) {
                 const uint8_t *pair_row = static_cast<const uint8_t *>(pr.a) + (int64_t)(tt * 16 + 2 * jj) * row_len;  // uniform
-                const uint32_t off = t < pr.M ? lane_off : 0u;
+                const uint32_t off = t < tokens ? lane_off : 0u;
                 if (2 * jj < m_tile) v[jj] = *reinterpret_cast<const uint4 *>(pair_row + off);  // uniform: token pairs that exist
                 else v[jj] = make_uint4(0, 0, 0, 0);
             } else if (row_len >= 16) {
                 const uint8_t *pair_row = static_cast<const uint8_t *>(pr.a) + (int64_t)(tt * 16 + 2 * jj) * row_len;
-                const uint32_t off = t < pr.M ? lane_off : lane_off - (uint32_t)((lane >> 5) * row_len);  // (an odd last token's neighbour reads its row)
+                const uint32_t off = t < tokens ? lane_off : lane_off - (uint32_t)((lane >> 5) * row_len);  // (an odd last token's neighbour reads its row)
                 v[jj] = make_uint4(0, 0, 0, 0);
                 if (2 * jj < m_tile) {
                     const Codes16 c = *reinterpret_cast<const Codes16 *>(pair_row + off);
@@ -555,9 +549,9 @@ void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg
                 }
             } else {
                 uint32_t d[4] = {~0u, ~0u, ~0u, ~0u};
-                if (t < pr.M && k0 == 0)
+                if (t < tokens && k0 == 0)
                     for (int e = 0; e < (int)row_len; ++e) {
-                        const uint32_t flip = (uint32_t)(static_cast<const uint8_t *>(pr.a)[t * row_len + e] ^ 0xffu) << (8 * (e & 3));
+                        const uint32_t flip = (uint32_t)(static_cast<const uint8_t *>(pr.a)[(int64_t)t * row_len + e] ^ 0xffu) << (8 * (e & 3));
 #pragma unroll
                         for (int i = 0; i < 4; ++i)
                             if (i == (e >> 2)) d[i] ^= flip;
@@ -575,13 +569,15 @@ void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg
         const int w = lane & 7, slot = ((lane >> 5) * 4 + ((lane & 31) >> 3)) * 8 + w;  // + 64 jj: token 2 jj + l / 32
         const int64_t k0 = (int64_t)4 * kKBlock * (wave + (int64_t)kWaves * it) + 16 * (lane & 31);
         const bool inside = k0 + 16 <= pr.K;
-        const int64_t m_tile = pr.M - tt * 16;
+        int tokens = M;
+        if constexpr (TT > 1) asm volatile("" : "+s"(tokens));  // (as row_len above)
+        const int m_tile = tokens - tt * 16;
 #pragma unroll
         for (int jj = 0; jj < NJ; ++jj) {
             if (2 * jj >= m_tile) continue;  // uniform; the slots of tokens that do not exist are never stored outputs
             // what the lane loaded counts only for a token that exists and a chunk inside the row; a chunk in the
             // padding of an existing token holds the all-ones code, a token past M zero words
-            const bool valid = tt * 16 + 2 * jj + (lane >> 5) < pr.M;
+            const bool valid = tt * 16 + 2 * jj + (lane >> 5) < tokens;
             uint32_t m_and = valid ? code_mask : 0u, m_or = 0u;
             uint4 c = v[jj];
             if constexpr (CODES == 1) {
@@ -645,30 +641,29 @@ void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg
     }
     // output o of thread `id` is element (tile t = e / 256, register v, lane l) of the accumulators, t = rt * TT + tt; 16x16
     // accumulator layout: lane l, register v holds row 4*(l/16) + v (weight row), column l%16 (token)
-    auto out_place = [&](int id, int o, int &m, int64_t &n) __attribute__((always_inline)) {
-        const int e = id + o * kThreads, t = e >> 8, v = (e >> 6) & 3, l = e & 63;
+    // (a wave without a tile, where there are fewer than two, stands at the last one and stores nothing)
+    auto out_place = [&](int o, int l, int &m, int &n) __attribute__((always_inline)) {
+        const int t_all = (wave >> 2) + o * (kWaves / 4), t = t_all < TT * RT ? t_all : TT * RT - 1;
         m = tok0 + (t % TT) * 16 + (l & 15);
-        n = n0 + (t / TT) * 16 + 4 * (l >> 4) + v;
-        return t < TT * RT && m < pr.M && n < pr.N;
+        n = n0 + (t / TT) * 16 + (wave & 3) + 4 * (l >> 4);
+        return t_all < TT * RT && m < M && n < N;
     };
     uint32_t out_sa_bits[OUTS], out_sw_bits[OUTS], out_pa[OUTS], out_pw[OUTS];
     {
-        const int32_t *w_sum = reinterpret_cast<const int32_t *>(pr.w + row_sum_word(rows_b, nkb, Q));
-        const int32_t *a_sum = CODES ? nullptr
-                                     : reinterpret_cast<const int32_t *>(static_cast<const uint32_t *>(pr.a) +
-                                                                         row_sum_word(rows_a, nkb, SA));
-        const uint16_t *dummy = reinterpret_cast<const uint16_t *>(pr.w);
+        const uint32_t rows_a = (M + 31u) & ~31u, rows_b = (N + 31u) & ~31u;
+        const int32_t *w_sum = reinterpret_cast<const int32_t *>(pr.w) + (uint64_t)rows_b * nkb * (Q * 4);
+        const int32_t *a_sum = CODES ? nullptr : static_cast<const int32_t *>(pr.a) + (uint64_t)rows_a * nkb * (SA * 4);
+        const uint16_t *sa = pr.a_scale ? pr.a_scale : reinterpret_cast<const uint16_t *>(pr.w), *sw = pr.w_scale ? pr.w_scale : reinterpret_cast<const uint16_t *>(pr.w);
+        const uint32_t last_m = pr.a_scale ? M - 1 : 0, last_n = pr.w_scale ? N - 1 : 0;
 #pragma unroll
         for (int o = 0; o < OUTS; ++o) {
-            int out_m;
-            int64_t out_n;
-            out_place(tid, o, out_m, out_n);
-            const int64_t m_c = out_m < rows_a ? out_m : rows_a - 1, n_c = out_n < rows_b ? out_n : rows_b - 1;
+            int out_m, out_n;
+            out_place(o, lane, out_m, out_n);
             out_pa[o] = 0;
-            if constexpr (!CODES) out_pa[o] = (uint32_t)a_sum[m_c];
-            out_pw[o] = (uint32_t)w_sum[n_c];
-            out_sa_bits[o] = *(pr.a_scale ? pr.a_scale + (m_c < pr.M ? m_c : pr.M - 1) : dummy);
-            out_sw_bits[o] = *(pr.w_scale ? pr.w_scale + (n_c < pr.N ? n_c : pr.N - 1) : dummy);
+            if constexpr (!CODES) out_pa[o] = (uint32_t)a_sum[(uint32_t)out_m];
+            out_pw[o] = (uint32_t)w_sum[(uint32_t)out_n];
+            out_sa_bits[o] = sa[(uint32_t)out_m < last_m ? (uint32_t)out_m : last_m];
+            out_sw_bits[o] = sw[(uint32_t)out_n < last_n ? (uint32_t)out_n : last_n];
         }
     }
 
@@ -700,7 +695,7 @@ void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg
             chunks_to_fragment(0, it, vcur, aq[0]);
             if (it + 1 < iters) load_chunks(0, it + 1, vcur);
         } else {
-            if (it + 1 < iters) load_packed(it + 1);
+            if (SECOND_SET && it + 1 < iters) load_packed(it + 1);
             if constexpr (CODES) {
 #pragma unroll
                 for (int tt = 0; tt < TT; ++tt) {
@@ -718,7 +713,9 @@ void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg
 #pragma unroll
             for (int tt = 0; tt < TT; ++tt) {
                 if constexpr (AF) {
-                    b8[tt] = mfma::field_operand<ks>(aq[tt]);
+                    // (a copy by hand: the compiler's own stood behind the loads and waited there for the first of them)
+                    const uint4 &shared = aq[tt][3 * (ks / 2) + 1];
+                    b8[tt] = mfma::field_operand<ks>(aq[tt], make_uint2(copy_here(mfma::vec_word<2 * (ks & 1)>(shared)), copy_here(mfma::vec_word<2 * (ks & 1) + 1>(shared))));
                 } else {
                     mfma::v4i b;
                     mfma::static_for<4>([&](auto d_c) __attribute__((always_inline)) {
@@ -748,19 +745,27 @@ void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg
                     acc_pa[tt] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
                         ones, b8[tt], acc_pa[tt], 4, format_a, 0, 129, 0, mfma::operand_exponent(P, ks));
             }
+            if constexpr (!SECOND_SET && AF && Q > 2) __builtin_amdgcn_sched_barrier(0);  // one k step's fragments at a time
         });
+        if constexpr (!SECOND_SET) {
+            // (the products before the requests: the compiler moved these up and copied all words out of their way)
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int tt = 0; tt < TT; ++tt) asm volatile("" : "+v"(acc[rt][tt])::"memory");
+            if (it + 1 < iters) load_packed(it + 1);
+        }
     }
 
     // The variants that are short of registers work the places out again instead of keeping them through the k loop: 3-bit weights
     // at one or two tokens from codes, where 83 registers instead of 79 cost a third workgroup per compute unit (W3A1 11008 x
     // 4096 6.3 -> 5.5 us, W3A2 5.9 -> 5.4 us), and 33 - 64 ragged tokens, which spilled three.
     constexpr bool LEAN = (NJ == 1 && RT == 1 && Q == 3) || (CODES == 2 && TT == 4 && Q <= 2);
-    const int tid_out = LEAN ? (int)use_here((uint32_t)tid) : tid;
+    const int lane_out = LEAN ? (int)use_here((uint32_t)lane) : lane;
     bool out_ok[OUTS];
-    int out_m[OUTS];
-    int64_t out_n[OUTS];
+    int out_m[OUTS], out_n[OUTS];
 #pragma unroll
-    for (int o = 0; o < OUTS; ++o) out_ok[o] = out_place(tid_out, o, out_m[o], out_n[o]);
+    for (int o = 0; o < OUTS; ++o) out_ok[o] = out_place(o, lane_out, out_m[o], out_n[o]);
     // reduce over the waves through LDS: part[wave][tile t][v][lane], and (CODES) the code sums pa[wave][token]
     float *part = reinterpret_cast<float *>(lds_raw);
     uint32_t *pa_lds = reinterpret_cast<uint32_t *>(lds_raw) + kWaves * RT * TT * 256;
@@ -780,7 +785,7 @@ void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg
 #pragma unroll
     for (int o = 0; o < OUTS; ++o) {
         if (!out_ok[o]) continue;
-        const int e = tid_out + o * kThreads;  // = (t * 4 + v) * 64 + l
+        const int e = wave * 64 + lane_out + o * kThreads;  // = (t * 4 + v) * 64 + l
         float s = 0.f;
 #pragma unroll
         for (int w8 = 0; w8 < kWaves; ++w8) s += part[w8 * RT * TT * 256 + e];
@@ -843,9 +848,9 @@ hipError_t launch_group_scalars(Kernel kernel, bool &attr_set, const GroupArgs &
     const GemmArgs &g = ga.g[0];
     const void *a = g.a_codes ? static_cast<const void *>(g.a_codes) : static_cast<const void *>(g.a);
     const int groups = ga.count == 1 && !g.a_codes ? decode_token_groups(g) : 1;
-    const uint32_t misc = (uint32_t)g.M | ((uint32_t)ga.count << 12) | ((uint32_t)groups << 24);
+    const uint32_t misc = (uint32_t)g.M | ((uint32_t)ga.count << 12);
     if ((int64_t)ga.wg_end[ga.count - 1] * groups > 0x7fffffffLL) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)(ga.wg_end[ga.count - 1] * groups)), block(kThreads);
+    const dim3 grid((unsigned)ga.wg_end[ga.count - 1], (unsigned)groups), block(kThreads);
     const KernelTiming timing = take_kernel_timing();
     if (timing.start || timing.stop)
         hipExtLaunchKernelGGL(kernel, grid, block, lds, stream, timing.start, timing.stop, 0, g.w, a, (int)g.N, (int)g.K,
@@ -1011,28 +1016,32 @@ hipError_t launch_gemm_decode_group(const GemmArgs *problems, int count, hipStre
     const int variant = decode_variant(gs[0], count, xor_only);
     if (variant > 200) return launch_gemm_decode_i8(gs, count, variant - 200, stream);
     if (variant > 100) {
-        // two row tiles per workgroup once that still leaves two workgroups per CU
+        // Two row tiles per workgroup once single ones would need more than three workgroups on a compute unit (single / two tiles, W2A2, one
+        // token at 11008 x 4096 4.0 / 4.2 us, 13824 x 4096 4.5 / 4.4, 22016 x 4096 6.4 / 6.0; 32 tokens at 11008 x 4096 5.4 / 5.45, 13824 x 4096 6.3 / 5.7; W4A1
+        // one token at 13824 x 5120 8.2 / 8.1).
         int64_t rows = 0;
         for (int i = 0; i < count; ++i) rows += gs[i].N;
         // (from unpacked codes already at half as many channels: every workgroup regroups all the codes for itself,
         // so fewer, larger workgroups pay: 7.7 -> 6.7 us for 4 tokens at 11008 x 4096, a loss at 4096 channels)
-        int rt = rows >= (gs[0].a_codes ? 256 * 2 * kRowsPerWg : 2 * 256 * 2 * kRowsPerWg) ? 2 : 1;
+        int rt = (gs[0].a_codes ? rows >= 256 * 2 * kRowsPerWg : rows > 3 * 256 * kRowsPerWg) ? 2 : 1;
         if (gs[0].a_codes) {
             // at most two tokens from codes: that kernel variant fits three workgroups per CU
             bool two = true;
             for (int i = 0; i < count; ++i) two = two && gs[i].M <= 2;
             if (two) rt = rows > 3 * 256 * kRowsPerWg ? 2 : 1;
         }
-        // four token tiles (33 - 64 tokens) with packed operands: that variant fits one workgroup per CU, so two row
-        // tiles as soon as single ones would need a second round of workgroups (8192 x 4096, 64 tokens: 5.9 us)
-        if (!gs[0].a_codes && variant == 104 && rows > 256 * kRowsPerWg) rt = 2;
-        // packed 3- and 4-bit activations: 88 registers leave two workgroups per CU, so two channel tiles as soon as single
-        // ones would need a second round of workgroups (W2A4, one token at 11008 x 4096, cold weights: 7.4 us with single tiles);
-        // with 4-bit weights under one token tile: from three workgroups' worth on (128 registers and more leave one workgroup per CU;
-        // 11008 channels 8.2 against 7.9 us, 15360 x 5120 16 tokens 11.6 -> 11.0 us; W3A3 11008 x 4096 7.7 -> 6.5 us,
-        // 15360 x 5120 10.0 -> 7.9 us; 32 tokens at 15360 x 5120 W4A4 17.8 -> 13.6 us)
-        if (!gs[0].a_codes && activation_field_form(gs[0].p) &&
-            rows > (gs[0].q == 4 && variant == 101 ? 3 : 2) * 256 * kRowsPerWg) rt = 2;
+        // four token tiles (33 - 64 tokens) with packed operands: two workgroups share a compute unit (64 tokens W2A2 5120 x 4096 5.2 / 5.3 us,
+        // 8192 x 4096 5.6 / 5.75)
+        if (!gs[0].a_codes && variant == 104 && rows > 2 * 256 * kRowsPerWg) rt = 2;
+        // Packed 3- and 4-bit activations (56 - 138 registers), long K: two channel tiles as soon as single ones would need a second workgroup on a
+        // compute unit.  Single / two tiles, K = 4096 and 5120: 16 tokens W4A4 4096 channels 3.9 / 4.3 us, 5120 5.1 / 4.5, 8192 6.7 / 6.2, 11008 8.8 /
+        // 8.8, 13824 11.0 / 9.8, 27648 18.8 / 16.3; one token W2A4 5120 3.6 / 3.25; 8 tokens W3A3 5120 4.0 / 3.7, 8192 4.3 / 4.4; 32 tokens W2A4 8192 5.2 / 4.7,
+        // W4A4 8192 8.6 / 7.2.  K = 2048: W2A4 one token 5120 3.0 / 2.8, 32 tokens 12288 5.3 / 4.6.  Below, a workgroup has little to read and its end
+        // weighs more: from the third one (4-bit weights under one token tile: the fourth) on; W4A4 K = 1024 16 tokens 8192 3.0 / 3.1, 12288 3.4 / 3.6.
+        if (!gs[0].a_codes && activation_field_form(gs[0].p)) {
+            const bool long_k = gs[count - 1].nkb >= (gs[0].q <= 2 ? 16 : 32);  // (the shortest)
+            if (rows > (long_k ? 1 : gs[0].q == 4 && variant == 101 ? 3 : 2) * 256 * kRowsPerWg) rt = 2;
+        }
         if (gs[0].a_codes && variant == 104) rt = 1;  // four token tiles from codes: two row tiles do not fit the registers
         // weights of 3 and 4 bits from codes: the two-tile variant fits three waves per SIMD only (11008 x 4096, 4 / 16
         // tokens: 7.8 / 9.4 us against 6.3 / 7.9 us with single tiles)

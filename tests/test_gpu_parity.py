@@ -442,6 +442,19 @@ def test_field_form_channel_tiles_per_workgroup(gpu, oracle, M, N, K, p, q, tile
     check_f16(c16, want, data, oracle)
 
 
+@pytest.mark.parametrize("M,N,K,p,q,tiles", [(16, 4096, 4096, 4, 4, 1), (16, 4097, 3600, 4, 4, 2), (3, 4112, 2000, 4, 2, 2), (3, 4112, 1500, 4, 2, 1), (50, 4098, 3585, 3, 3, 2),
+                                             (5, 12288, 600, 2, 2, 1), (16, 12289, 600, 1, 4, 2), (30, 12301, 130, 2, 1, 2), (64, 8192, 300, 1, 1, 1), (33, 8193, 300, 2, 2, 2)])
+def test_channel_tiles_per_workgroup_by_rows_and_k(gpu, oracle, M, N, K, p, q, tiles):
+    """Both sides of the lines in channels and K; last workgroups of one channel and of a part of one tile."""
+    case = dict(M=M, N=N, K=K, p=p, q=q, a_dist="bernoulli", scaled=True)
+    data = inputs.make_case(case, 8800 + M + 10 * p + q)
+    want = oracle.gemm_i64(data["a_codes"], data["w_codes"], p, q)
+    c32, c16 = run_case(gpu, data, case, algo=DECODE, want_i32=True, want_f16=True)
+    assert gpu[1].apmm_last_gemm_kernel().endswith(",%d,packed>" % tiles)
+    assert np.array_equal(c32.astype(np.int64), want)
+    check_f16(c16, want, data, oracle)
+
+
 @pytest.mark.parametrize("p,q", [(1, 1), (2, 1), (5, 3), (2, 4), (8, 2), (1, 4), (6, 4)])
 @pytest.mark.parametrize("M", [1, 2, 3, 5, 8, 13, 16])
 def test_decode_kernel_all_token_counts(gpu, oracle, M, p, q):

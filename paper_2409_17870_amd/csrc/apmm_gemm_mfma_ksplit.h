@@ -47,7 +47,7 @@ inline bool ksplit_streams(int wm, int wn, const GemmArgs &g)
 
 template <int P, int Q, int WM, int WN>
 __device__ __forceinline__ void ksplit_tile(float4 *red, const uint32_t *a_arg, const uint32_t *w_arg, int32_t *ci_arg, uint16_t *cf_arg, int m_arg, int n_arg,
-                                            int k_arg, int nkb_arg, int tiles_n, int tiles_m_xn, const uint16_t *ws_arg, const uint16_t *as_arg,
+                                            int k_arg, uint32_t part_magic, int tiles_n, int tiles_m_xn, const uint16_t *ws_arg, const uint16_t *as_arg,
                                             bool stream)
 {
     // red: [block][partial 0..2][register quad 0..3][lane]
@@ -83,21 +83,22 @@ __device__ __forceinline__ void ksplit_tile(float4 *red, const uint32_t *a_arg, 
     // Workgroups are dealt round-robin to the 8 XCDs, each with an L2 of its own.  The tile grid is cut into
     // 8 / xn x xn parts, one per XCD, and a part is walked down its columns: the workgroups that run together on an
     // XCD share the packed rows of a few column tiles and of the part's row tiles (tiles_m_xn = tiles_m | log2(xn) << 28).
-    const int tiles_m = tiles_m_xn & 0x0fffffff, xn_log = tiles_m_xn >> 28;
-    const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
-    const int part_m = (tiles_m + (8 >> xn_log) - 1) >> (3 - xn_log), part_n = (tiles_n + (1 << xn_log) - 1) >> xn_log;
-    const int tm = (xcd >> xn_log) * part_m + idx % part_m, tn = (xcd & ((1 << xn_log) - 1)) * part_n + idx / part_m;
-    if (tm >= tiles_m || tn >= tiles_n) return;  // the grid is padded to 8 equal parts
+    // (The way to the first request is scalar arithmetic in 32 bits, 145 instead of 215 instructions for 64 x 160: 203 x 4096 x 4096 W2A2 6.4 -> 6.1 us, 300 x
+    // 2000 x 700 W2A3 5.7 -> 5.4, 1024 x 4096 x 11008 W4A4 33.3 -> 31.9.)
+    const uint32_t tiles_m = tiles_m_xn & 0x0fffffff, xn_log = (uint32_t)tiles_m_xn >> 28;
+    const uint32_t xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
+    const uint32_t part_m = (tiles_m + (8 >> xn_log) - 1) >> (3 - xn_log), part_n = (tiles_n + (1 << xn_log) - 1) >> xn_log;
+    const uint32_t row_of_parts = quotient(idx, part_m, part_magic);
+    const uint32_t tm = (xcd >> xn_log) * part_m + idx - row_of_parts * part_m, tn = (xcd & ((1 << xn_log) - 1)) * part_n + row_of_parts;
+    if (tm >= tiles_m || tn >= (uint32_t)tiles_n) return;  // the grid is padded to 8 equal parts
     const int64_t M = m_arg, N = n_arg;
     const int64_t m0 = (int64_t)tm * (32 * WM), n0 = (int64_t)tn * (32 * WN);
-    const int64_t nrb_a = (M + 31) / 32, nrb_b = (N + 31) / 32;
-    const int32_t *a_sum = reinterpret_cast<const int32_t *>(a_arg + row_sum_word(nrb_a * 32, nkb_arg, SLOTS_A));
-    const int32_t *w_sum = reinterpret_cast<const int32_t *>(w_arg + row_sum_word(nrb_b * 32, nkb_arg, Q));
+    const uint32_t nkb = padded_k_blocks(k_arg), nrb_a = ((uint32_t)m_arg + 31) / 32, nrb_b = ((uint32_t)n_arg + 31) / 32;
 
     // this wave's stages of K: nst stages of two k blocks, dealt as evenly as they go
-    const int nst = nkb_arg / 2;
-    const int s_begin = wave * (nst / 4) + (wave < nst % 4 ? wave : nst % 4);
-    const int s_count = nst / 4 + (wave < nst % 4 ? 1 : 0);
+    const uint32_t nst = nkb / 2;
+    const int s_begin = wave * (nst / 4) + min((uint32_t)wave, nst % 4);
+    const int s_count = nst / 4 + ((uint32_t)wave < nst % 4 ? 1 : 0);
     const int s_end = s_begin + s_count;
 
     // Addresses: a uniform pointer per block (row blocks past the operand read the last one; never stored) plus
@@ -109,15 +110,13 @@ __device__ __forceinline__ void ksplit_tile(float4 *red, const uint32_t *a_arg, 
     const char *pa_blk[WM], *pb_blk[WN];
 #pragma unroll
     for (int bi = 0; bi < WM; ++bi) {
-        int64_t rb = m0 / 32 + bi;
-        if (rb >= nrb_a) rb = nrb_a - 1;
-        pa_blk[bi] = reinterpret_cast<const char *>(a_arg) + rb * nkb_arg * (int64_t)(SLOTS_A * kSlotBytes);
+        const uint32_t rb = min(tm * WM + bi, nrb_a - 1);
+        pa_blk[bi] = reinterpret_cast<const char *>(a_arg) + (uint64_t)(rb * nkb) * (SLOTS_A * kSlotBytes);
     }
 #pragma unroll
     for (int bj = 0; bj < WN; ++bj) {
-        int64_t rb = n0 / 32 + bj;
-        if (rb >= nrb_b) rb = nrb_b - 1;
-        pb_blk[bj] = reinterpret_cast<const char *>(w_arg) + rb * nkb_arg * (int64_t)(Q * kSlotBytes);
+        const uint32_t rb = min(tn * WN + bj, nrb_b - 1);
+        pb_blk[bj] = reinterpret_cast<const char *>(w_arg) + (uint64_t)(rb * nkb) * (Q * kSlotBytes);
     }
 
     v16f acc[WM][WN];
@@ -148,18 +147,18 @@ __device__ __forceinline__ void ksplit_tile(float4 *red, const uint32_t *a_arg, 
     // accumulators with the recovery terms, the others start at zero).
     if (s_count > 0) load_stage(I0{}, s_begin);
     {
+        const int32_t *a_sum = reinterpret_cast<const int32_t *>(a_arg) + (uint64_t)(nrb_a * nkb) * (kRowBlock * SLOTS_A * 4);
+        const int32_t *w_sum = reinterpret_cast<const int32_t *>(w_arg) + (uint64_t)(nrb_b * nkb) * (kRowBlock * Q * 4);
         float a_init[WM], b_init[WN];
 #pragma unroll
         for (int bj = 0; bj < WN; ++bj) {
-            int64_t n = n0 + bj * 32 + r32;
-            if (n >= nrb_b * 32) n = nrb_b * 32 - 1;
+            const uint32_t n = min((tn * WN + bj) * 32 + r32, nrb_b * 32 - 1);
             const float ct = (float)(int32_t)((uint32_t)k_arg * ca * cw - 2u * ca * (uint32_t)w_sum[n]);
             b_init[bj] = wave != 0 ? 0.f : kh == 0 ? 1.0f : ct;
         }
 #pragma unroll
         for (int bi = 0; bi < WM; ++bi) {
-            int64_t m = m0 + bi * 32 + r32;
-            if (m >= nrb_a * 32) m = nrb_a * 32 - 1;
+            const uint32_t m = min((tm * WM + bi) * 32 + r32, nrb_a * 32 - 1);
             const float rt = -(float)(2u * cw * (uint32_t)a_sum[m]);
             a_init[bi] = wave != 0 ? 0.f : kh == 0 ? rt : 1.0f;
         }
@@ -256,17 +255,13 @@ __device__ __forceinline__ void ksplit_tile(float4 *red, const uint32_t *a_arg, 
     if (cf_arg && as_arg) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            int64_t m = m_own + 8 * (v / 4) + (v % 4);
-            if (m >= M) m = M - 1;
-            sa_bits[v] = as_arg[m];
+            sa_bits[v] = as_arg[min((uint32_t)m_own + 8 * (v / 4) + (v % 4), (uint32_t)m_arg - 1)];
         }
     }
     if (cf_arg && ws_arg) {
 #pragma unroll
         for (int bj = 0; bj < WN; ++bj) {
-            int64_t n = n0 + bj * 32 + c32;
-            if (n >= N) n = N - 1;
-            sw_bits[bj] = ws_arg[n];
+            sw_bits[bj] = ws_arg[min((uint32_t)n0 + bj * 32 + c32, (uint32_t)n_arg - 1)];
         }
     }
     // Store of one owned block.  GUARD: border tile, every element tested.  PAIR (interior, even N, 4-byte aligned
@@ -409,20 +404,20 @@ inline int64_t ksplit_lds_max_k(int p, int q, const GemmArgs &g)
 }
 template <int P, int Q, int WM, int WN>
 __global__ __launch_bounds__(WM == 4 ? 512 : 256, WN == 2 ? 2 : 1)  // two workgroups of the 64 x 64 tile share a compute unit
-void gemm_mfma_ksplit_kernel(const uint32_t *a, const uint32_t *w, int32_t *c_i32, uint16_t *c_f16, int m, int n, int k, int nkb, int tiles_n, int tiles_m_xn,
+void gemm_mfma_ksplit_kernel(const uint32_t *a, const uint32_t *w, int32_t *c_i32, uint16_t *c_f16, int m, int n, int k, uint32_t magic, int tiles_n, int tiles_m_xn,
                              const uint16_t *w_scale, const uint16_t *a_scale, bool stream)
 {
     extern __shared__ __align__(16) float4 red[];
-    if constexpr (WM == 4) lds_tile<P, Q, 2, WN / 2, 2>(reinterpret_cast<uint4 *>(red), a, w, c_i32, c_f16, m, n, k, nkb, tiles_n, tiles_m_xn, w_scale, a_scale, stream);
-    else ksplit_tile<P, Q, WM, WN>(red, a, w, c_i32, c_f16, m, n, k, nkb, tiles_n, tiles_m_xn, w_scale, a_scale, stream);
+    if constexpr (WM == 4) lds_tile<P, Q, 2, WN / 2, 2>(reinterpret_cast<uint4 *>(red), a, w, c_i32, c_f16, m, n, k, magic, tiles_n, tiles_m_xn, w_scale, a_scale, stream);
+    else ksplit_tile<P, Q, WM, WN>(red, a, w, c_i32, c_f16, m, n, k, magic, tiles_n, tiles_m_xn, w_scale, a_scale, stream);
 }
 template <int P, int Q>
 __global__ __launch_bounds__(256) void gemm_mfma_ksplit_long_kernel(const uint32_t *a, const uint32_t *w, int32_t *c_i32, uint16_t *c_f16, int m, int n, int k,
-                                                                    int nkb, int tiles_n, int tiles_m_xn, const uint16_t *w_scale,
+                                                                    uint32_t magic, int tiles_n, int tiles_m_xn, const uint16_t *w_scale,
                                                                     const uint16_t *a_scale, bool stream)
 {
     extern __shared__ __align__(16) float4 red[];
-    ksplit_tile<P, Q, 4, 4>(red, a, w, c_i32, c_f16, m, n, k, nkb, tiles_n, tiles_m_xn, w_scale, a_scale, stream);
+    ksplit_tile<P, Q, 4, 4>(red, a, w, c_i32, c_f16, m, n, k, magic, tiles_n, tiles_m_xn, w_scale, a_scale, stream);
 }
 
 template <int P, int Q, int WM, int WN>
@@ -431,7 +426,7 @@ hipError_t launch_ksplit_variant(const GemmArgs &g, hipStream_t stream)
     constexpr int BM = 32 * WM, BN = 32 * WN;
     const int64_t tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
     if (tiles_m >= (1 << 28) || tiles_n >= (1 << 28) || g.K > 0x7fffffffLL) return hipErrorInvalidValue;
-    auto launch = [&](auto kernel, int64_t tiles, int threads, int lds, int order, bool streaming, int &prepared_device) {
+    auto launch = [&](auto kernel, int64_t tiles, int threads, int lds, int order, uint32_t magic, bool streaming, int &prepared_device) {
         if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
         int dev = 0;
         hipError_t e = hipGetDevice(&dev);
@@ -444,10 +439,10 @@ hipError_t launch_ksplit_variant(const GemmArgs &g, hipStream_t stream)
         const KernelTiming timing = take_kernel_timing();
         if (timing.start || timing.stop)
             hipExtLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(threads), lds, stream, timing.start, timing.stop, 0, g.a, g.w,
-                                  g.c_i32, g.c_f16, (int)g.M, (int)g.N, (int)g.K, (int)g.nkb, (int)tiles_n, order, g.w_scale, g.a_scale, streaming);
+                                  g.c_i32, g.c_f16, (int)g.M, (int)g.N, (int)g.K, magic, (int)tiles_n, order, g.w_scale, g.a_scale, streaming);
         else
             hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(threads), lds, stream, g.a, g.w, g.c_i32, g.c_f16, (int)g.M, (int)g.N,
-                               (int)g.K, (int)g.nkb, (int)tiles_n, order, g.w_scale, g.a_scale, streaming);
+                               (int)g.K, magic, (int)tiles_n, order, g.w_scale, g.a_scale, streaming);
         return hipGetLastError();
     };
     static thread_local int prepared = -1, prepared_long = -1;
@@ -456,7 +451,8 @@ hipError_t launch_ksplit_variant(const GemmArgs &g, hipStream_t stream)
         static_assert(lds <= 160 * 1024, "LDS of a compute unit");
         if (Q == 2 || g.K <= ksplit_lds_max_k(P, Q, g)) {
             note_kernel("gemm_mfma_ksplit_kernel<%d,%d,%d,%d>", P, Q, WM, WN);
-            return launch(gemm_mfma_ksplit_kernel<P, Q, WM, WN>, tiles_m * tiles_n, 512, lds, lds_tile_order<P, Q>(tiles_m, g.K),
+            const int lds_order = lds_tile_order<P, Q>(tiles_m, g.K);
+            return launch(gemm_mfma_ksplit_kernel<P, Q, WM, WN>, tiles_m * tiles_n, 512, lds, lds_order, lds_band_magic(lds_order, tiles_n, tiles_m * tiles_n),
                           lds_streams<P, Q, 2, WN / 2, 2>(g), prepared);
         }
     }
@@ -471,12 +467,13 @@ hipError_t launch_ksplit_variant(const GemmArgs &g, hipStream_t stream)
     }
     const int64_t part_m = (tiles_m + (8 >> xn_log) - 1) / (8 >> xn_log), part_n = (tiles_n + (1 << xn_log) - 1) / (1 << xn_log);
     const int order = (int)tiles_m | (xn_log << 28);
+    const uint32_t magic = divisor_magic(part_m, part_m * part_n);
     if constexpr (WM != 4) {
         note_kernel("gemm_mfma_ksplit_kernel<%d,%d,%d,%d>", P, Q, WM, WN);
-        return launch(gemm_mfma_ksplit_kernel<P, Q, WM, WN>, 8 * part_m * part_n, 256, ksplit_lds_bytes(WM, WN), order, ksplit_streams(WM, WN, g), prepared);
+        return launch(gemm_mfma_ksplit_kernel<P, Q, WM, WN>, 8 * part_m * part_n, 256, ksplit_lds_bytes(WM, WN), order, magic, ksplit_streams(WM, WN, g), prepared);
     } else if constexpr (Q > 2) {
         note_kernel("gemm_mfma_ksplit_long_kernel<%d,%d>", P, Q);
-        return launch(gemm_mfma_ksplit_long_kernel<P, Q>, 8 * part_m * part_n, 256, ksplit_lds_bytes(WM, WN), order, ksplit_streams(WM, WN, g), prepared_long);
+        return launch(gemm_mfma_ksplit_long_kernel<P, Q>, 8 * part_m * part_n, 256, ksplit_lds_bytes(WM, WN), order, magic, ksplit_streams(WM, WN, g), prepared_long);
     }
     return hipErrorInvalidValue;  // (not reached)
 }

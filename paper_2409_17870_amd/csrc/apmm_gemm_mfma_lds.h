@@ -71,7 +71,7 @@ constexpr int lds_tile_bytes() { return KG == 1 ? LdsTile<P, Q, WM, WN>::BYTES :
 
 template <int P, int Q, int WM, int WN, int KG>
 __device__ __forceinline__ void lds_tile(uint4 *ring_of_workgroup, const uint32_t *a_arg, const uint32_t *w_arg, int32_t *ci_arg, uint16_t *cf_arg, int m_arg,
-                                         int n_arg, int k_arg, int nkb_arg, int tiles_n, int tiles_m_band, const uint16_t *ws_arg,
+                                         int n_arg, int k_arg, uint32_t band_magic, int tiles_n, int tiles_m_band, const uint16_t *ws_arg,
                                          const uint16_t *as_arg, bool stream)
 {
     using L = LdsTile<P, Q, WM, WN>;
@@ -90,35 +90,34 @@ __device__ __forceinline__ void lds_tile(uint4 *ring_of_workgroup, const uint32_
     const int wave_m = wave >> 1, wave_n = wave & 1;
     const int r32 = lane & 31, kh = lane >> 5;
     // An XCD takes a contiguous run of tiles in an order that walks `band` tile rows column by column (see lds_tile_order).
-    const int tiles_m = tiles_m_band & 0x0fffffff, band = 1 << (tiles_m_band >> 28);
-    const int lid = xcd_tile_id(blockIdx.x, tiles_n * tiles_m);
-    const int m_band = lid / (band * tiles_n), in_band = lid - m_band * band * tiles_n;
-    const int rows = min(tiles_m - m_band * band, band);
-    const int tm = m_band * band + in_band % rows, tn = in_band / rows;
+    // (All of the way to the first request is scalar arithmetic in 32 bits where the sizes allow it.  Start to first request, median of the
+    // waves of a cold launch, 1.0 -> 0.6 us.)
+    const uint32_t nkb = padded_k_blocks(k_arg);
+    const uint32_t tiles_m = tiles_m_band & 0x0fffffff, band_log = (uint32_t)tiles_m_band >> 28, band = 1u << band_log;
+    const uint32_t lid = xcd_tile_id(blockIdx.x, tiles_n * (int)tiles_m);
+    const uint32_t m_band = quotient(lid, (uint32_t)tiles_n << band_log, band_magic), in_band = lid - (m_band * tiles_n << band_log);
+    const uint32_t rows = min(tiles_m - (m_band << band_log), band);  // 1, 2, 3 or 4
+    const uint32_t tn = rows == 3 ? __umulhi(in_band, 0xaaaaaaabu) >> 1 : in_band >> (rows >> 1), tm = (m_band << band_log) + in_band - tn * rows;
     const int64_t M = m_arg, N = n_arg;
     const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
-    const int64_t nrb_a = (M + 31) / 32, nrb_b = (N + 31) / 32;
-    const int32_t *a_sum = reinterpret_cast<const int32_t *>(a_arg + row_sum_word(nrb_a * 32, nkb_arg, SLOTS_A));
-    const int32_t *w_sum = reinterpret_cast<const int32_t *>(w_arg + row_sum_word(nrb_b * 32, nkb_arg, Q));
+    const uint32_t nrb_a = ((uint32_t)m_arg + 31) / 32, nrb_b = ((uint32_t)n_arg + 31) / 32;
 
     // What this wave brings to LDS: row blocks wave * RA / 4 ... of A and wave * RB / 4 ... of W (past the operand: the last one,
     // never stored).  Lane l takes row l % 32 of k block l / 32 of the stage, as it will read it.
     constexpr int kSlotBytes = kPlaneWords * 4;
     uint32_t voff_a = (uint32_t)(kh * SLOTS_A * kSlotBytes + r32 * 16);
     uint32_t voff_b = (uint32_t)(kh * Q * kSlotBytes + r32 * 16);
-    const int stages = nkb_arg / 2 / KG;  // this group's (nkb is a multiple of four)
+    const int stages = nkb / 2 / KG;  // this group's (nkb is a multiple of four)
     const char *src_a[L::RA / 4], *src_b[L::RB / 4];
 #pragma unroll
     for (int i = 0; i < L::RA / 4; ++i) {
-        int64_t rb = m0 / 32 + wave * (L::RA / 4) + i;
-        if (rb >= nrb_a) rb = nrb_a - 1;
-        src_a[i] = reinterpret_cast<const char *>(a_arg) + (rb * nkb_arg + group * 2 * stages) * (int64_t)(SLOTS_A * kSlotBytes);
+        const uint32_t rb = min(tm * (BM / 32) + wave * (L::RA / 4) + i, nrb_a - 1);
+        src_a[i] = reinterpret_cast<const char *>(a_arg) + (uint64_t)(rb * nkb + group * 2 * stages) * (SLOTS_A * kSlotBytes);
     }
 #pragma unroll
     for (int i = 0; i < L::RB / 4; ++i) {
-        int64_t rb = n0 / 32 + wave * (L::RB / 4) + i;
-        if (rb >= nrb_b) rb = nrb_b - 1;
-        src_b[i] = reinterpret_cast<const char *>(w_arg) + (rb * nkb_arg + group * 2 * stages) * (int64_t)(Q * kSlotBytes);
+        const uint32_t rb = min(tn * (BN / 32) + wave * (L::RB / 4) + i, nrb_b - 1);
+        src_b[i] = reinterpret_cast<const char *>(w_arg) + (uint64_t)(rb * nkb + group * 2 * stages) * (Q * kSlotBytes);
     }
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint4 *)ring;
     // Requests go half stage by half stage; this one is for ring place `r` (its parity is the half).  Past the last stage every lane
@@ -160,34 +159,32 @@ __device__ __forceinline__ void lds_tile(uint4 *ring_of_workgroup, const uint32_
     static_for<kLdsRing - 1>(request);
 
     // For the end of the tile, requested now: code sums and scales of this lane's columns and rows.
+    const int32_t *a_sum = reinterpret_cast<const int32_t *>(a_arg) + (uint64_t)(nrb_a * nkb) * (kRowBlock * SLOTS_A * 4);
+    const int32_t *w_sum = reinterpret_cast<const int32_t *>(w_arg) + (uint64_t)(nrb_b * nkb) * (kRowBlock * Q * 4);
     constexpr int WMO = WM / KG;  // row blocks of the wave tile that this wave finishes, the first of them:
     const int64_t m_own = m0 + (wave_m * WM + group) * 32, m_lane = m_own + kh * 4, n_lane = n0 + wave_n * WN * 32 + r32;
     uint32_t w_sum_raw[WN], a_sum_raw[WMO], sw_raw[WN], sa_raw[(WMO + 1) / 2];
 #pragma unroll
     for (int bj = 0; bj < WN; ++bj) {
-        const int64_t n = n_lane + bj * 32;
-        w_sum_raw[bj] = (uint32_t)w_sum[n < nrb_b * 32 ? n : nrb_b * 32 - 1];
+        w_sum_raw[bj] = (uint32_t)w_sum[min((uint32_t)n_lane + bj * 32, nrb_b * 32 - 1)];
         sw_raw[bj] = 0x3c00u;  // 1.0
     }
 #pragma unroll
     for (int bi = 0; bi < WMO; ++bi) {
-        const int64_t m = m_own + bi * 32 + r32;
-        a_sum_raw[bi] = (uint32_t)a_sum[m < nrb_a * 32 ? m : nrb_a * 32 - 1];
+        a_sum_raw[bi] = (uint32_t)a_sum[min((uint32_t)m_own + bi * 32 + r32, nrb_a * 32 - 1)];
     }
 #pragma unroll
     for (int i = 0; i < (WMO + 1) / 2; ++i) sa_raw[i] = 0x3c00u;
     if (cf_arg && ws_arg) {
 #pragma unroll
         for (int bj = 0; bj < WN; ++bj) {
-            const int64_t n = n_lane + bj * 32;
-            sw_raw[bj] = ws_arg[n < N ? n : N - 1];
+            sw_raw[bj] = ws_arg[min((uint32_t)n_lane + bj * 32, (uint32_t)n_arg - 1)];
         }
     }
     if (cf_arg && as_arg) {
 #pragma unroll
         for (int i = 0; i < (WMO + 1) / 2; ++i) {
-            const int64_t m = m_own + 64 * i + lane;
-            sa_raw[i] = as_arg[m < M ? m : M - 1];
+            sa_raw[i] = as_arg[min((uint32_t)m_own + 64 * i + lane, (uint32_t)m_arg - 1)];
         }
     }
 
@@ -428,11 +425,11 @@ __device__ __forceinline__ void lds_tile(uint4 *ring_of_workgroup, const uint32_
 
 template <int P, int Q, int WM, int WN, int OCC>
 __global__ __launch_bounds__(256, OCC) void gemm_mfma_lds_kernel(const uint32_t *a, const uint32_t *w, int32_t *c_i32, uint16_t *c_f16, int m, int n, int k,
-                                                                 int nkb, int tiles_n, int tiles_m_band, const uint16_t *w_scale,
+                                                                 uint32_t band_magic, int tiles_n, int tiles_m_band, const uint16_t *w_scale,
                                                                  const uint16_t *a_scale, bool stream)
 {
     extern __shared__ __align__(16) uint4 lds_ring[];
-    lds_tile<P, Q, WM, WN, 1>(lds_ring, a, w, c_i32, c_f16, m, n, k, nkb, tiles_n, tiles_m_band, w_scale, a_scale, stream);
+    lds_tile<P, Q, WM, WN, 1>(lds_ring, a, w, c_i32, c_f16, m, n, k, band_magic, tiles_n, tiles_m_band, w_scale, a_scale, stream);
 }
 
 template <int P, int Q>
@@ -446,6 +443,7 @@ inline int lds_tile_order(int64_t tiles_m, int64_t K)  // tiles_m < 2^28
     const int band_log = Q <= 2 && K <= 1024 ? 0 : 2;
     return (int)tiles_m | band_log << 28;
 }
+inline uint32_t lds_band_magic(int tiles_m_band, int64_t tiles_n, int64_t tiles) { return divisor_magic(tiles_n << (tiles_m_band >> 28), tiles); }
 
 // Streaming stores where the rows are whole lines: with outputs that are not in the last-level cache from the call before, plain ones
 // push the operands out of L2 (W2A4 1024 x 11008 x 4096 both 33.6 -> 43.4 us, int32 28.8 -> 37.0, fp16 28.0 -> 35.7).  Not where a short sum
@@ -476,6 +474,7 @@ hipError_t launch_lds_variant(const GemmArgs &g, hipStream_t stream)
     const int64_t tiles = tiles_m * tiles_n;
     if (tiles > 0x7fffffffLL || tiles_m >= (1 << 28) || g.M > 0x7fffffffLL || g.N > 0x7fffffffLL || g.K > 0x7fffffffLL) return hipErrorInvalidValue;
     const int tiles_m_band = lds_tile_order<P, Q>(tiles_m, g.K);
+    const uint32_t magic = lds_band_magic(tiles_m_band, tiles_n, tiles);
     const bool streaming = lds_streams<P, Q, WM, WN, 1>(g);
     auto kernel = gemm_mfma_lds_kernel<P, Q, WM, WN, OCC>;
     static thread_local int prepared_device = -1;  // the LDS limit is a per-device attribute of the function
@@ -491,10 +490,10 @@ hipError_t launch_lds_variant(const GemmArgs &g, hipStream_t stream)
     note_kernel("gemm_mfma_lds_kernel<%d,%d,%d,%d>", P, Q, WM, WN);
     if (timing.start || timing.stop)
         hipExtLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(256), L::BYTES, stream, timing.start, timing.stop, 0, g.a, g.w, g.c_i32,
-                              g.c_f16, (int)g.M, (int)g.N, (int)g.K, (int)g.nkb, (int)tiles_n, tiles_m_band, g.w_scale, g.a_scale, streaming);
+                              g.c_f16, (int)g.M, (int)g.N, (int)g.K, magic, (int)tiles_n, tiles_m_band, g.w_scale, g.a_scale, streaming);
     else
         hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(256), L::BYTES, stream, g.a, g.w, g.c_i32, g.c_f16, (int)g.M, (int)g.N,
-                           (int)g.K, (int)g.nkb, (int)tiles_n, tiles_m_band, g.w_scale, g.a_scale, streaming);
+                           (int)g.K, magic, (int)tiles_n, tiles_m_band, g.w_scale, g.a_scale, streaming);
     return hipGetLastError();
 }
 

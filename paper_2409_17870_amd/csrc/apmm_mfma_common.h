@@ -115,6 +115,20 @@ __device__ __forceinline__ uint32_t half_operand_dword(const uint4 (&raw)[NS])
     else return unfold_word<4, D>(raw[KSL].x, raw[KSL].y, raw[KSL].z, raw[KSL].w);
 }
 
+// x / d for the tile maps, where the way to the first request counts: the launcher passes ceil(2^32 / d), or 0 where d = 1 or x d does not
+// stay below 2^32 (then the quotient of x and this could be one too high).  A division takes 25 instructions in a row.
+inline uint32_t divisor_magic(int64_t d, int64_t most_x)
+{
+    return d > 1 && d * most_x < ((int64_t)1 << 32) ? (uint32_t)((((int64_t)1 << 32) + d - 1) / d) : 0u;
+}
+__device__ __forceinline__ uint32_t quotient(uint32_t x, uint32_t d, uint32_t magic)
+{
+    if (magic != 0) return __umulhi(x, magic);
+    return d <= 1 ? x : x / d;
+}
+// k blocks of a row
+__device__ __forceinline__ uint32_t padded_k_blocks(uint32_t k) { return (k + (kKPad - 1)) / kKPad * (kKPad / kKBlock); }
+
 // Workgroups are dealt round-robin to the 8 XCDs; give each XCD a contiguous run of tiles so that
 // the packed rows it re-reads stay in its own L2.
 __device__ __forceinline__ int xcd_tile_id(int block, int tiles_total)

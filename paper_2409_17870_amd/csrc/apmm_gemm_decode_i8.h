@@ -49,13 +49,14 @@ struct LaneUnit {
 // median over sizes from 1000 x 2048 to 13824 x 5120 is 5 - 15 % less, the worst W2A8 8192 x 8192, 5.9 -> 6.2 us.)
 constexpr int unit_steps(int words) { return words <= 20 ? 2 : 1; }
 
-// `src`: word 0 of slot 0 of the lane's row in the k block
+// `src`: the k block (a scalar), `row`: bytes from there to word 0 of slot 0 of the lane's row
 template <int FORM>
-__device__ __forceinline__ void load_unit(const Operand &o, const uint32_t *src, int ks, LaneUnit<FORM> &u)
+__device__ __forceinline__ void load_unit(const Operand &o, const char *src, uint32_t row, uint32_t ks, LaneUnit<FORM> &u)
 {
-    auto vec = [&](int slot) __attribute__((always_inline)) { return *reinterpret_cast<const uint4 *>(src + slot * kPlaneWords); };
-    auto words = [&](int w) __attribute__((always_inline)) {  // words w, w + 1 (w even) of the row, four to a slot
-        return *reinterpret_cast<const uint2 *>(src + (w >> 2) * kPlaneWords + (w & 3));
+    constexpr uint32_t kSlotBytes = kPlaneWords * 4;
+    auto vec = [&](uint32_t slot) __attribute__((always_inline)) { return *reinterpret_cast<const uint4 *>(src + (row + slot * kSlotBytes)); };
+    auto words = [&](uint32_t w) __attribute__((always_inline)) {  // words w, w + 1 (w even) of the row, four to a slot
+        return *reinterpret_cast<const uint2 *>(src + (row + (w >> 2) * kSlotBytes + (w & 3) * 4));
     };
     if constexpr (FORM == 1) {
         u.v[0] = vec(0);
@@ -63,7 +64,7 @@ __device__ __forceinline__ void load_unit(const Operand &o, const uint32_t *src,
         u.h[0] = words(2 * ks);
     } else if constexpr (FORM == 3) {
         u.h[0] = words(2 * ks);
-        u.s[0] = src[2 * kPlaneWords + ks];
+        u.s[0] = *reinterpret_cast<const uint32_t *>(src + (row + 2 * kSlotBytes + ks * 4));
     } else if constexpr (FORM == 4) {
         u.v[0] = vec(ks);
     } else if constexpr (FORM == kNibbles) {
@@ -122,29 +123,20 @@ void gemm_decode_i8_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg, 
     const int p = pq_arg & 0xff, q = pq_arg >> 8;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r16 = lane & 15, ks = lane >> 4;
-    const int64_t n0 = (int64_t)block * (kRowsPerWg * RT);
-    const int nkb = (int)((pr.K + kKPad - 1) / kKPad) * (kKPad / kKBlock);
-    const int64_t rows_a = round_up(pr.M, kRowBlock), rows_b = round_up(pr.N, kRowBlock);
+    // (the way to the first request as in the fp4 small-M kernel: bases are scalars, a lane's part of an address is 32 bits; the channels
+    // of a workgroup and the tokens of two tiles lie in one row block, whose rows past the operand's are zero words.  W4A8 from codes 8 x 11008 x
+    // 4096 9.3 -> 9.1 us, W8A8 packed 8 x 4096 x 4096 5.4 -> 5.2, W8A7 40 x 1000 x 2000 6.1 -> 5.7)
+    const int n0 = block * (kRowsPerWg * RT), M = (int)pr.M, N = (int)pr.N;
+    const int nkb = (int)mfma::padded_k_blocks((uint32_t)pr.K);
     const Operand ob = make_operand<FB>(q), oa = make_operand<CODES ? 1 : FA>(p);
 
-    const uint32_t *wsrc[RT];
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-        const int64_t n = n0 + rt * 16 + r16 < rows_b ? n0 + rt * 16 + r16 : rows_b - 1;
-        wsrc[rt] = pr.w + tile_row_word(n, 0, nkb, ob.slots, 0);
-    }
-    const uint32_t *asrc[TT];
+    constexpr uint32_t kSlotBytes = kPlaneWords * 4;
+    const uint32_t w_row = ((uint32_t)(n0 & 16) + r16) * 16, a_row = r16 * 16;
+    const char *w_base = reinterpret_cast<const char *>(pr.w) + (uint64_t)(((uint32_t)n0 >> 5) * (uint32_t)nkb) * (ob.slots * kSlotBytes);
     const uint8_t *crow[TT];
 #pragma unroll
-    for (int tt = 0; tt < TT; ++tt) {
-        if constexpr (CODES) {
-            const int64_t t = tt * 16 + r16 < pr.M ? tt * 16 + r16 : pr.M - 1;  // tokens past M: the last one, never stored
-            crow[tt] = static_cast<const uint8_t *>(pr.a) + t * pr.K;
-        } else {
-            const int64_t t = tt * 16 + r16 < rows_a ? tt * 16 + r16 : rows_a - 1;
-            asrc[tt] = static_cast<const uint32_t *>(pr.a) + tile_row_word(t, 0, nkb, oa.slots, 0);
-        }
-    }
+    for (int tt = 0; tt < TT; ++tt)
+        if constexpr (CODES) crow[tt] = static_cast<const uint8_t *>(pr.a) + (int64_t)min(tt * 16 + r16, M - 1) * pr.K;  // tokens past M: the last one, never stored
     const int last = (int)pr.K - 16;  // CODES: K >= 16 (the launcher's rule)
 
     LaneUnit<FB> wn[U][RT];
@@ -152,7 +144,7 @@ void gemm_decode_i8_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg, 
     auto load_block = [&](int u, int kb) __attribute__((always_inline)) {
         kb = kb < nkb ? kb : nkb - 1;  // (blocks past the end are loaded from the last one and not multiplied)
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) load_unit<FB>(ob, wsrc[rt] + (int64_t)kb * ob.slots * kPlaneWords, ks, wn[u][rt]);
+        for (int rt = 0; rt < RT; ++rt) load_unit<FB>(ob, w_base + (uint64_t)kb * (ob.slots * kSlotBytes), w_row + rt * 256, ks, wn[u][rt]);
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt) {
             if constexpr (CODES) {
@@ -163,7 +155,7 @@ void gemm_decode_i8_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg, 
                     an[u][tt].v[tp] = make_uint4(c.x, c.y, c.z, c.w);
                 }
             } else {
-                load_unit<FA>(oa, asrc[tt] + (int64_t)kb * oa.slots * kPlaneWords, ks, an[u][tt]);
+                load_unit<FA>(oa, static_cast<const char *>(pr.a) + (uint64_t)((tt / 2) * nkb + kb) * (oa.slots * kSlotBytes), a_row + (tt & 1) * 256, ks, an[u][tt]);
             }
         }
     };
@@ -172,25 +164,26 @@ void gemm_decode_i8_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg, 
 
     // what only the final store needs is requested behind the first operands and kept as loaded
     bool out_ok[OUTS];
-    int out_m[OUTS];
-    int64_t out_n[OUTS];
+    int out_m[OUTS], out_n[OUTS];
     uint32_t out_sa_bits[OUTS], out_sw_bits[OUTS], out_pa[OUTS], out_pw[OUTS];
     {
-        const int32_t *w_sum = reinterpret_cast<const int32_t *>(pr.w + row_sum_word(rows_b, nkb, ob.slots));
-        const int32_t *a_sum = CODES ? w_sum : reinterpret_cast<const int32_t *>(static_cast<const uint32_t *>(pr.a) + row_sum_word(rows_a, nkb, oa.slots));
-        const uint16_t *dummy = reinterpret_cast<const uint16_t *>(pr.w);
+        const uint32_t rows_a = (M + 31u) & ~31u, rows_b = (N + 31u) & ~31u;
+        const int32_t *w_sum = reinterpret_cast<const int32_t *>(pr.w) + (uint64_t)rows_b * nkb * (ob.slots * 4);
+        const int32_t *a_sum = CODES ? w_sum : static_cast<const int32_t *>(pr.a) + (uint64_t)rows_a * nkb * (oa.slots * 4);
+        const uint16_t *sa = pr.a_scale ? pr.a_scale : reinterpret_cast<const uint16_t *>(pr.w), *sw = pr.w_scale ? pr.w_scale : reinterpret_cast<const uint16_t *>(pr.w);
+        const uint32_t last_m = pr.a_scale ? M - 1 : 0, last_n = pr.w_scale ? N - 1 : 0;
 #pragma unroll
         for (int o = 0; o < OUTS; ++o) {
             // element (tile t = e / 256, register v, lane l) of the accumulators: row 4 (l / 16) + v (channel), column l % 16 (token)
-            const int e = tid + o * kDecodeThreads, t = e >> 8, v = (e >> 6) & 3, l = e & 63;
-            out_m[o] = (t % TT) * 16 + (l & 15);
-            out_n[o] = n0 + (t / TT) * 16 + 4 * (l >> 4) + v;
-            out_ok[o] = t < TT * RT && out_m[o] < pr.M && out_n[o] < pr.N;
-            const int64_t m_c = out_m[o] < pr.M ? out_m[o] : pr.M - 1, n_c = out_n[o] < pr.N ? out_n[o] : pr.N - 1;
-            out_pa[o] = CODES ? 0u : (uint32_t)a_sum[m_c];
-            out_pw[o] = (uint32_t)w_sum[n_c];
-            out_sa_bits[o] = *(pr.a_scale ? pr.a_scale + m_c : dummy);
-            out_sw_bits[o] = *(pr.w_scale ? pr.w_scale + n_c : dummy);
+            // (a wave without a tile, where there are fewer than two, stands at the last one and stores nothing)
+            const int t_all = (wave >> 2) + o * (W / 4), t = t_all < TT * RT ? t_all : TT * RT - 1;
+            out_m[o] = (t % TT) * 16 + r16;
+            out_n[o] = n0 + (t / TT) * 16 + (wave & 3) + 4 * ks;
+            out_ok[o] = t_all < TT * RT && out_m[o] < M && out_n[o] < N;
+            out_pa[o] = CODES ? 0u : (uint32_t)a_sum[(uint32_t)out_m[o]];
+            out_pw[o] = (uint32_t)w_sum[(uint32_t)out_n[o]];
+            out_sa_bits[o] = sa[min((uint32_t)out_m[o], last_m)];
+            out_sw_bits[o] = sw[min((uint32_t)out_n[o], last_n)];
         }
     }
 
@@ -288,7 +281,7 @@ void gemm_decode_i8_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg, 
         const int32_t c = (int32_t)(4u * s - 2u * cw * pa - 2u * ca * pw + full);
         const uint32_t sa_bits = pr.a_scale ? use_here(out_sa_bits[o]) : 0x3c00u;  // 1.0
         const uint32_t sw_bits = pr.w_scale ? use_here(out_sw_bits[o]) : 0x3c00u;
-        const int64_t at = (int64_t)out_m[o] * pr.N + out_n[o];
+        const int64_t at = (int64_t)out_m[o] * N + out_n[o];
         if (pr.c_i32) pr.c_i32[at] = c;
         if (pr.c_f16)
             pr.c_f16[at] = float_to_half_bits((float)c * half_bits_to_float((uint16_t)sa_bits) * half_bits_to_float((uint16_t)sw_bits));

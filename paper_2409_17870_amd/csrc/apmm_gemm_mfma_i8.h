@@ -85,7 +85,7 @@ constexpr int ksplit_lds_bytes() { return kWM * kWN * 3 * 4 * 64 * 16; }
 
 template <int FA, int FB, bool KSPLIT>
 __global__ __launch_bounds__(256) void gemm_mfma_i8_kernel(const uint32_t *a_arg, const uint32_t *w_arg, int32_t *ci_arg,
-                                                           uint16_t *cf_arg, int m_arg, int n_arg, int k_arg, int nkb,
+                                                           uint16_t *cf_arg, int m_arg, int n_arg, int k_arg, uint32_t part_magic,
                                                            int tiles_n, int tiles_m_xn, const uint16_t *ws_arg,
                                                            const uint16_t *as_arg, int p, int q, bool stream)
 {
@@ -98,15 +98,19 @@ __global__ __launch_bounds__(256) void gemm_mfma_i8_kernel(const uint32_t *a_arg
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r32 = lane & 31, kh = lane >> 5;
     // XCD-aware tile map: the tile grid in 8 / xn x xn parts, one per XCD, walked down their columns
-    const int tiles_m = tiles_m_xn & 0x0fffffff, xn_log = tiles_m_xn >> 28;
-    const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
-    const int part_m = (tiles_m + (8 >> xn_log) - 1) >> (3 - xn_log), part_n = (tiles_n + (1 << xn_log) - 1) >> xn_log;
-    const int tm = (xcd >> xn_log) * part_m + idx % part_m, tn = (xcd & ((1 << xn_log) - 1)) * part_n + idx / part_m;
-    if (tm >= tiles_m || tn >= tiles_n) return;  // the grid is padded to 8 equal parts
+    // (The way to the first request is scalar arithmetic in 32 bits: 2048 x 4096 x 4096 W8A8 44.0 -> 42.8 us, 300 x 5003 x 3001 W7A5 both 22.1 -> 21.3.  Code sums and
+    // scales asked for there as well, 40 loads between the first two stages, cost 1 - 17 %: they are asked for at the end.)
+    const uint32_t tiles_m = tiles_m_xn & 0x0fffffff, xn_log = (uint32_t)tiles_m_xn >> 28;
+    const uint32_t xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
+    const uint32_t part_m = (tiles_m + (8 >> xn_log) - 1) >> (3 - xn_log), part_n = (tiles_n + (1 << xn_log) - 1) >> xn_log;
+    const uint32_t row_of_parts = mfma::quotient(idx, part_m, part_magic);
+    const uint32_t tm = (xcd >> xn_log) * part_m + idx - row_of_parts * part_m, tn = (xcd & ((1 << xn_log) - 1)) * part_n + row_of_parts;
+    if (tm >= tiles_m || tn >= (uint32_t)tiles_n) return;  // the grid is padded to 8 equal parts
     const int64_t M = m_arg, N = n_arg;
     const int64_t m0 = (int64_t)tm * BM + (KSPLIT ? 0 : (wave >> 1) * 32 * kWM);
     const int64_t n0 = (int64_t)tn * BN + (KSPLIT ? 0 : (wave & 1) * 32 * kWN);
-    const int64_t nrb_a = (M + 31) / 32, nrb_b = (N + 31) / 32;
+    const uint32_t nrb_a = ((uint32_t)m_arg + 31) / 32, nrb_b = ((uint32_t)n_arg + 31) / 32;
+    const int nkb = (int)mfma::padded_k_blocks(k_arg);
     const Operand oa = make_operand<FA>(p), ob = make_operand<FB>(q);
 
     // this wave's stages: pairs of k blocks, two stages each
@@ -119,15 +123,13 @@ __global__ __launch_bounds__(256) void gemm_mfma_i8_kernel(const uint32_t *a_arg
     const char *pa_blk[kWM], *pb_blk[kWN];
 #pragma unroll
     for (int bi = 0; bi < kWM; ++bi) {
-        int64_t rb = m0 / 32 + bi;
-        if (rb >= nrb_a) rb = nrb_a - 1;  // blocks past the operand: read the last one, never stored
-        pa_blk[bi] = reinterpret_cast<const char *>(a_arg) + rb * nkb * (int64_t)(oa.slots * kSlotBytes);
+        const uint32_t rb = min((uint32_t)(m0 / 32) + bi, nrb_a - 1);  // blocks past the operand: read the last one, never stored
+        pa_blk[bi] = reinterpret_cast<const char *>(a_arg) + (uint64_t)(rb * (uint32_t)nkb) * (oa.slots * kSlotBytes);
     }
 #pragma unroll
     for (int bj = 0; bj < kWN; ++bj) {
-        int64_t rb = n0 / 32 + bj;
-        if (rb >= nrb_b) rb = nrb_b - 1;
-        pb_blk[bj] = reinterpret_cast<const char *>(w_arg) + rb * nkb * (int64_t)(ob.slots * kSlotBytes);
+        const uint32_t rb = min((uint32_t)(n0 / 32) + bj, nrb_b - 1);
+        pb_blk[bj] = reinterpret_cast<const char *>(w_arg) + (uint64_t)(rb * (uint32_t)nkb) * (ob.slots * kSlotBytes);
     }
 
     v16i acc[kWM][kWN];
@@ -202,29 +204,27 @@ __global__ __launch_bounds__(256) void gemm_mfma_i8_kernel(const uint32_t *a_arg
     // ---- recovery and store ----
     const uint32_t ca = value_offset(p), cw = value_offset(q), k_pad = (uint32_t)nkb * kKBlock;
     const uint32_t full = k_pad * ca * cw - (k_pad - (uint32_t)k_arg) * ((1u << p) - 1u) * ((1u << q) - 1u);
-    const int32_t *a_sum = reinterpret_cast<const int32_t *>(a_arg + row_sum_word(nrb_a * 32, nkb, oa.slots));
-    const int32_t *w_sum = reinterpret_cast<const int32_t *>(w_arg + row_sum_word(nrb_b * 32, nkb, ob.slots));
+    const int32_t *a_sum = reinterpret_cast<const int32_t *>(a_arg) + (uint64_t)(nrb_a * (uint32_t)nkb) * (uint32_t)(kRowBlock * 4 * oa.slots);
+    const int32_t *w_sum = reinterpret_cast<const int32_t *>(w_arg) + (uint64_t)(nrb_b * (uint32_t)nkb) * (uint32_t)(kRowBlock * 4 * ob.slots);
     // a missing scale vector reads code sums instead, so that every load is unconditional
     const uint16_t *sa_src = as_arg ? as_arg : reinterpret_cast<const uint16_t *>(a_sum);
     const uint16_t *sw_src = ws_arg ? ws_arg : reinterpret_cast<const uint16_t *>(w_sum);
-    const bool pair_ok = (N & 1) == 0 && (reinterpret_cast<uintptr_t>(cf_arg) & 3u) == 0;
     uint32_t pa[16], sa_bits[16], pw[kWN], sw_bits[kWN];
-    auto request_rows = [&](int64_t mb) __attribute__((always_inline)) {
+    auto request_rows = [&](uint32_t mb) __attribute__((always_inline)) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            int64_t m = mb + 8 * (v / 4) + 4 * kh + (v % 4);  // row of register v
-            if (m >= M) m = M - 1;
+            const uint32_t m = min(mb + 8 * (v / 4) + 4 * kh + (v % 4), (uint32_t)m_arg - 1);  // row of register v
             pa[v] = (uint32_t)a_sum[m];
             sa_bits[v] = sa_src[m];
         }
     };
 #pragma unroll
     for (int bj = 0; bj < kWN; ++bj) {
-        int64_t n = n0 + 32 * bj + r32;
-        if (n >= N) n = N - 1;
+        const uint32_t n = min((uint32_t)n0 + 32 * bj + r32, (uint32_t)n_arg - 1);
         pw[bj] = (uint32_t)w_sum[n];
         sw_bits[bj] = sw_src[n];
     }
+    const bool pair_ok = (N & 1) == 0 && (reinterpret_cast<uintptr_t>(cf_arg) & 3u) == 0;
     // one 32 x 32 block, inner ones with streaming stores by the launcher's rule
     auto store_block = [&](const v16i &s, int64_t mb, auto bj_c) __attribute__((always_inline)) {
         constexpr int bj = decltype(bj_c)::value;
@@ -283,8 +283,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_i8_kernel(const uint32_t *a_arg
     };
     if constexpr (KSPLIT) {
         // the partial tiles meet: wave w finishes blocks 2 (w % 2), + 1 of row block w / 2
-        const int bi_own = wave >> 1;
-        request_rows(m0 + 32 * bi_own);
+        request_rows((uint32_t)m0 + 32 * (wave >> 1));
         static_for<kWM * kWN>([&](auto b_c) __attribute__((always_inline)) {
             constexpr int b = decltype(b_c)::value, bi = b / kWN, bj = b % kWN, own = 2 * bi + bj / 2;
             if (wave != own) {
@@ -312,7 +311,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_i8_kernel(const uint32_t *a_arg
     } else {
         static_for<kWM>([&](auto bi_c) __attribute__((always_inline)) {
             constexpr int bi = decltype(bi_c)::value;
-            request_rows(m0 + 32 * bi);
+            request_rows((uint32_t)m0 + 32 * bi);
             __builtin_amdgcn_sched_barrier(0);
             static_for<kWN>([&](auto bj_c) __attribute__((always_inline)) { store_block(acc[bi][decltype(bj_c)::value], m0 + 32 * bi, bj_c); });
         });
@@ -337,6 +336,7 @@ hipError_t launch_variant(const GemmArgs &g, hipStream_t stream)
     const int64_t grid = 8 * part_m * part_n;
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
     const int tiles_m_xn = (int)tiles_m | (xn_log << 28);
+    const uint32_t magic = mfma::divisor_magic(part_m, part_m * part_n);
     // Streaming stores where the rows are whole lines (W8A8 2048 x 11008 x 4096 both 156 -> 119 us).  Rows of parts of lines: int32 up to 22 MB
     // of outputs, whole tiles also before an fp16 output (both outputs of the K split 0.94 - 0.97 of the streaming time at 10 - 18 MB, fp16
     // alone 0.97 up to 3 MB and 0.85 at 30).
@@ -359,9 +359,9 @@ hipError_t launch_variant(const GemmArgs &g, hipStream_t stream)
     const dim3 blocks((unsigned)grid), threads(256);
     if (timing.start || timing.stop)
         hipExtLaunchKernelGGL(kernel, blocks, threads, lds, stream, timing.start, timing.stop, 0, g.a, g.w, g.c_i32, g.c_f16, (int)g.M,
-                              (int)g.N, (int)g.K, (int)g.nkb, (int)tiles_n, tiles_m_xn, g.w_scale, g.a_scale, g.p, g.q, streaming);
+                              (int)g.N, (int)g.K, magic, (int)tiles_n, tiles_m_xn, g.w_scale, g.a_scale, g.p, g.q, streaming);
     else
-        hipLaunchKernelGGL(kernel, blocks, threads, lds, stream, g.a, g.w, g.c_i32, g.c_f16, (int)g.M, (int)g.N, (int)g.K, (int)g.nkb,
+        hipLaunchKernelGGL(kernel, blocks, threads, lds, stream, g.a, g.w, g.c_i32, g.c_f16, (int)g.M, (int)g.N, (int)g.K, magic,
                            (int)tiles_n, tiles_m_xn, g.w_scale, g.a_scale, g.p, g.q, streaming);
     return hipGetLastError();
 }

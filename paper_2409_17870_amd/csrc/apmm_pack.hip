@@ -25,6 +25,31 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kRowsPerWg = kThreads / 64;
 
+// The wave's number as a scalar, and with it everything that follows from it: rows, bases, the branches between kinds of waves.
+__device__ __forceinline__ int wave_of_workgroup() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+
+// Sum and maximum over the 64 lanes, as a scalar: lane permutes inside the vector unit, six instructions where a shuffle through LDS
+// is six round trips of about 100 clocks.  0 is neutral for both.
+template <class Op>
+__device__ __forceinline__ uint32_t over_wave(uint32_t v, Op op)
+{
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false));  // row_shr 1, 2, 4, 8: lane 15 of 16 has its row's
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false));
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false));
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false));
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));  // row_bcast 15 into rows 1 and 3
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));  // row_bcast 31 into rows 2 and 3
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ uint32_t sum_over_wave(uint32_t v)
+{
+    return over_wave(v, [](uint32_t a, uint32_t b) __attribute__((always_inline)) { return a + b; });
+}
+__device__ __forceinline__ uint32_t max_over_wave(uint32_t v)
+{
+    return over_wave(v, [](uint32_t a, uint32_t b) __attribute__((always_inline)) { return a > b ? a : b; });
+}
+
 // nibbles of the four codes in lo (jh = 0) and in hi (jh = 1)
 __device__ __forceinline__ uint32_t nibble_word(uint32_t lo, uint32_t hi)
 {
@@ -177,7 +202,7 @@ __global__ __launch_bounds__(kThreads) void pack_rows_kernel(const uint8_t *__re
                                                         int64_t rows_p, int64_t nkb)
 {
     const int lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)blockIdx.x * kRowsPerWg + (threadIdx.x >> 6);
+    const int64_t row = (int64_t)blockIdx.x * kRowsPerWg + wave_of_workgroup();
     if (row >= rows_p) return;
     const int64_t groups = nkb * kWordsPerRow;  // 32-element groups per row, a multiple of 16
     const uint32_t code_mask = 0x01010101u * ((1u << bits) - 1u);
@@ -204,8 +229,7 @@ __global__ __launch_bounds__(kThreads) void pack_rows_kernel(const uint8_t *__re
         pack_group(packed, row, nkb, bits, kg, d0, 0u, sum);
         if (second) pack_group(packed, row, nkb, bits, kg + 64, d1, 0u, sum);
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
+    sum = sum_over_wave(sum);
     if (lane == 0) packed[row_sum_word(rows_p, nkb, bits) + row] = sum;
 }
 
@@ -220,18 +244,18 @@ __global__ __launch_bounds__(kThreads) void pack_rows_kernel(const uint8_t *__re
 //   form reaches the bandwidth of the copy.)
 //   Sum wave: adds the codes of one row and the padding; the sum waves of a row block follow its tile waves in
 //   the grid, so that they find the rows in L2.
+constexpr int kRowBlocksPerZ = 32768;  // size of the grid's y where z is needed
 enum PackForm { kFieldForm, kFold3, kFold4, kByteForm, kOtherForm };  // compile-time: a launch fetches the code of its own form only
 
 template <PackForm FORM, bool WHOLE>
-__global__ __launch_bounds__(kThreads) void pack_kernel(const uint8_t *__restrict__ codes, int64_t rows,
+__global__ __launch_bounds__(kThreads, 8) void pack_kernel(const uint8_t *__restrict__ codes, int64_t rows,
                                                         int64_t K, int bits, uint32_t *__restrict__ packed,
                                                         int64_t rows_p, int64_t nkb)
 {
     const int lane = threadIdx.x & 63;
-    // jobs of a row block: its nkb tiles, then the sums of its 32 rows (which find the rows in L2)
-    const int64_t job = (int64_t)blockIdx.x * kRowsPerWg + (threadIdx.x >> 6);
-    const int64_t jobs_per_rb = nkb + kRowBlock;
-    const int64_t rb = job / jobs_per_rb, j = job % jobs_per_rb;
+    // jobs of a row block: its nkb tiles, then the sums of its 32 rows (which find the rows in L2); a row block to each blockIdx.y and z
+    const int64_t j = (int64_t)blockIdx.x * kRowsPerWg + wave_of_workgroup();
+    const int64_t rb = (int64_t)blockIdx.z * kRowBlocksPerZ + blockIdx.y;
     if (rb >= rows_p / kRowBlock) return;
     const uint32_t code_mask = 0x01010101u * ((1u << bits) - 1u);
     if (j < nkb) {
@@ -242,7 +266,7 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const uint8_t *__restric
         uint32_t d[2][8];
         if (row < rows) {
             uint32_t v[16];
-            load_codes<WHOLE>(codes + row * K, K, kb * kKBlock + 64 * h, v);
+            load_codes<WHOLE>(codes + rb * kRowBlock * K + r * K, K, kb * kKBlock + 64 * h, v);
 #pragma unroll
             for (int i = 0; i < 16; ++i) d[i >> 3][i & 7] = v[i] & code_mask;
         } else {
@@ -250,6 +274,8 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const uint8_t *__restric
             for (int i = 0; i < 16; ++i) d[i >> 3][i & 7] = 0u;  // rows past the operand are zero words
         }
         constexpr int kSlotVec = kPlaneWords / 4;
+        // word 0 of the lane's row in a slot of the tile
+        auto slot_of = [&](int n, int slot) __attribute__((always_inline)) { return packed + (rb * nkb + kb) * (n * kPlaneWords) + (uint32_t)(slot * kPlaneWords + r * kWordsPerRow); };
         if constexpr (FORM == kFieldForm || FORM == kFold3 || FORM == kFold4) {
             // k step ks: words 6 ks .. 6 ks + 5 of the row's 24, the 32 codes as 6-bit fields, field 8t + 2c + jh
             uint32_t dw[12];
@@ -267,7 +293,7 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const uint8_t *__restric
                 dw[6 * e + 5] = (uint32_t)(chunk[3] >> 16);
             }
             if constexpr (FORM == kFold4) {
-                uint4 *dst = reinterpret_cast<uint4 *>(packed + tile_row_word(row, kb, nkb, 4, 2 * h));
+                uint4 *dst = reinterpret_cast<uint4 *>(slot_of(4, 2 * h));
 #pragma unroll
                 for (int e = 0; e < 2; ++e) {
                     const uint32_t f[6] = {dw[6 * e], dw[6 * e + 1], dw[6 * e + 2], dw[6 * e + 3], dw[6 * e + 4], dw[6 * e + 5]};
@@ -284,17 +310,17 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const uint8_t *__restric
                     const uint32_t f[6] = {dw[6 * e], dw[6 * e + 1], dw[6 * e + 2], dw[6 * e + 3], dw[6 * e + 4], dw[6 * e + 5]};
                     fold_words<3>(f, w[e]);
                 }
-                uint32_t *dst = packed + tile_row_word(row, kb, nkb, 3, 0);
+                uint32_t *dst = slot_of(3, 0);
                 *reinterpret_cast<uint4 *>(dst + h * kPlaneWords) = make_uint4(w[0][0], w[0][1], w[1][0], w[1][1]);
                 *reinterpret_cast<uint2 *>(dst + 2 * kPlaneWords + 2 * h) = make_uint2(w[0][2], w[1][2]);
                 return;
             }
-            uint4 *dst = reinterpret_cast<uint4 *>(packed + tile_row_word(row, kb, nkb, 6, 3 * h));
+            uint4 *dst = reinterpret_cast<uint4 *>(slot_of(6, 3 * h));
 #pragma unroll
             for (int v = 0; v < 3; ++v) dst[v * kSlotVec] = make_uint4(dw[4 * v], dw[4 * v + 1], dw[4 * v + 2], dw[4 * v + 3]);
         } else if constexpr (FORM == kByteForm) {
             const uint32_t flip = row < rows ? 0x80808080u : 0u;
-            uint4 *dst = reinterpret_cast<uint4 *>(packed + tile_row_word(row, kb, nkb, bits, 4 * h));
+            uint4 *dst = reinterpret_cast<uint4 *>(slot_of(bits, 4 * h));
 #pragma unroll
             for (int e = 0; e < 2; ++e)
 #pragma unroll
@@ -303,7 +329,7 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const uint8_t *__restric
                                                               d[e][4 * tp + 3] ^ flip);
         } else {
             if (nibble_form(bits)) {
-                uint4 *dst = reinterpret_cast<uint4 *>(packed + tile_row_word(row, kb, nkb, bits, 2 * h));
+                uint4 *dst = reinterpret_cast<uint4 *>(slot_of(bits, 2 * h));
 #pragma unroll
                 for (int e = 0; e < 2; ++e)
                     dst[e * kSlotVec] = make_uint4(nibble_word(d[e][0], d[e][1]), nibble_word(d[e][2], d[e][3]),
@@ -324,7 +350,7 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const uint8_t *__restric
                                 word |= ((d[e][2 * (2 * tp + tt) + jh] >> (2 * g)) & 0x03030303u) << (4 * jh + 2 * tt);
                         sw[2 * e + tp] = word;
                     }
-                *reinterpret_cast<uint4 *>(packed + tile_row_word(row, kb, nkb, bits, 2 * g + h)) =
+                *reinterpret_cast<uint4 *>(slot_of(bits, 2 * g + h)) =
                     make_uint4(sw[0], sw[1], sw[2], sw[3]);
             }
             if (has_single_group(bits)) {
@@ -341,7 +367,7 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const uint8_t *__restric
                     l[t] = word | __shfl_xor(word, 32);
                 }
                 if (h == 0)
-                    *reinterpret_cast<uint4 *>(packed + tile_row_word(row, kb, nkb, bits, bits - 1)) =
+                    *reinterpret_cast<uint4 *>(slot_of(bits, bits - 1)) =
                         make_uint4(l[0], l[1], l[2], l[3]);
             }
         }
@@ -351,24 +377,41 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const uint8_t *__restric
         if (row < rows) {
             const uint8_t *src = codes + row * K;
             const int64_t vecs = K / 16;
-            auto add = [&](uint32_t w) __attribute__((always_inline)) { sum = __builtin_amdgcn_sad_u8(w & code_mask, 0u, sum); };
+            // Eight loads under way, past the end the last vector's again: a loop that is only unrolled ends in single steps, each a round trip to
+            // memory, and 5120 codes were nothing but its end (four bits 512 x 5120 4.1 -> 3.4 us, 512 x 13824 6.4 -> 5.0).  The last 4096 codes one by
+            // one: their tile waves are not much longer, and loads that go ahead of the tiles' cost more where there are many rows (2048 x 4096 5.3 us,
+            // this way 5.2, four at a time 5.7).
+            int64_t i0 = 0;
+            auto step = [&](auto u_c, auto load) __attribute__((always_inline)) {
+                constexpr int U = decltype(u_c)::value;
+                uint32_t v[U][4];
+                const uint32_t last = vecs - i0 > 64 * U ? 64 * U - 1 : (uint32_t)(vecs - i0) - 1;
+#pragma unroll
+                for (int u = 0; u < U; ++u) load(src + 16 * i0 + 16 * min(64u * u + lane, last), v[u]);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const uint32_t mask = 64u * u + lane <= last ? code_mask : 0u;
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) sum = __builtin_amdgcn_sad_u8(v[u][w] & mask, 0u, sum);
+                }
+                i0 += 64 * U;
+            };
+            using U1 = std::integral_constant<int, 1>;
+            using U4 = std::integral_constant<int, 4>;
+            using U8 = std::integral_constant<int, 8>;
             if (WHOLE || (reinterpret_cast<uintptr_t>(src) & 3u) == 0) {
-#pragma unroll 8
-                for (int64_t i = lane; i < vecs; i += 64) {
-                    const AnyVec v = reinterpret_cast<const AnyVec *>(src)[i];
-                    add(v.x); add(v.y); add(v.z); add(v.w);
-                }
+                auto load = [](const uint8_t *at, uint32_t (&d)[4]) __attribute__((always_inline)) {
+                    const AnyVec v = *reinterpret_cast<const AnyVec *>(at);
+                    d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
+                };
+                while (vecs - i0 > 64 * 4) step(U8{}, load);
+                while (i0 < vecs) step(U1{}, load);
             } else {
-#pragma unroll 4
-                for (int64_t i = lane; i < vecs; i += 64) {
-                    uint32_t v[4];
-                    load_bytes<4>(src + 16 * i, v);
-                    add(v[0]); add(v[1]); add(v[2]); add(v[3]);
-                }
+                auto load = [](const uint8_t *at, uint32_t (&d)[4]) __attribute__((always_inline)) { load_bytes<4>(at, d); };
+                while (i0 < vecs) step(U4{}, load);
             }
             if (16 * vecs + lane < K) sum += src[16 * vecs + lane] & (code_mask & 0xffu);  // at most 15 codes
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
+            sum = sum_over_wave(sum);
             sum += (uint32_t)(nkb * kKBlock - K) * (code_mask & 0xffu);  // the all-ones codes of the padding
         }
         if (lane == 0) packed[row_sum_word(rows_p, nkb, FORM == kFieldForm ? 6 : bits) + row] = sum;
@@ -508,7 +551,7 @@ __global__ __launch_bounds__(kThreads) void quantize_pack_kernel(const uint16_t 
                                                                  int64_t nkb)
 {
     constexpr int T = 64 * WAVES, ROWS = kThreads / T, C = 8 / ROWS;  // threads of a row, rows of a workgroup, workgroups of eight rows
-    const int tid = threadIdx.x % T, sub = threadIdx.x / T;
+    const int tid = threadIdx.x % T, sub = wave_of_workgroup() / WAVES;
     const int xcd = blockIdx.x % 8, turn = blockIdx.x / 8;  // workgroups go to the XCDs in turn
     const int64_t row = (((int64_t)(turn / C) * 8 + xcd) * C + turn % C) * ROWS + sub;
     if (row >= rows_p) return;  // (rows_p is a multiple of ROWS: the whole workgroup leaves)
@@ -533,11 +576,7 @@ __global__ __launch_bounds__(kThreads) void quantize_pack_kernel(const uint16_t 
         m2 = fold_max(m2, h);
     }
     uint32_t mbits = m2[0] > m2[1] ? m2[0] : m2[1];
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const uint32_t o = __shfl_xor(mbits, off);
-        mbits = o > mbits ? o : mbits;
-    }
+    mbits = max_over_wave(mbits);
     __shared__ uint32_t joint[2][kThreads / 64];
     if constexpr (WAVES > 1) {
         if ((threadIdx.x & 63) == 0) joint[0][threadIdx.x / 64] = mbits;
@@ -613,8 +652,7 @@ __global__ __launch_bounds__(kThreads) void quantize_pack_kernel(const uint16_t 
             fill_group(kg);
         }
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
+    sum = sum_over_wave(sum);
     if constexpr (WAVES > 1) {
         if ((threadIdx.x & 63) == 0) joint[1][threadIdx.x / 64] = sum;
         __syncthreads();
@@ -639,7 +677,7 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_fields_kernel(const ui
     extern __shared__ __align__(16) uint32_t fields[];  // [k block][slot][row of the workgroup][word]
     __shared__ uint32_t joint[2][kQuantThreads / 64];
     constexpr int C = 8 / kQuantRows;
-    const int sub = threadIdx.x / kQuantLanes, tid = threadIdx.x % kQuantLanes, wave = threadIdx.x / 64;
+    const int wave = wave_of_workgroup(), sub = wave / (kQuantLanes / 64), tid = threadIdx.x % kQuantLanes;
     const int xcd = blockIdx.x % 8, turn = blockIdx.x / 8;  // the eight rows that share a 128-byte line: on one XCD
     const int64_t row0 = (((int64_t)(turn / C) * 8 + xcd) * C + turn % C) * kQuantRows, row = row0 + sub;
     if (row0 >= rows_p) return;  // (rows_p is a multiple of the workgroup's rows)
@@ -657,11 +695,7 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_fields_kernel(const ui
         }
     }
     uint32_t mbits = m2[0] > m2[1] ? m2[0] : m2[1];
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const uint32_t o = __shfl_xor(mbits, off);
-        mbits = o > mbits ? o : mbits;
-    }
+    mbits = max_over_wave(mbits);
     if ((threadIdx.x & 63) == 0) joint[0][wave] = mbits;
     __syncthreads();
 #pragma unroll
@@ -690,8 +724,7 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_fields_kernel(const ui
             *reinterpret_cast<uint4 *>(base + 2 * slot) = make_uint4(dw[2], dw[3], dw[4], dw[5]);
         }
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
+    sum = sum_over_wave(sum);
     if ((threadIdx.x & 63) == 0) joint[1][wave] = sum;
     __syncthreads();
     if (tid == 0) {
@@ -821,16 +854,18 @@ hipError_t launch_pack(const uint8_t *codes, int64_t rows, int64_t K, int bits, 
         hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, codes, rows, K, packed, rows_p, nkb);
         return hipGetLastError();
     }
-    const int64_t jobs = rows_p / kRowBlock * (nkb + kRowBlock);  // per row block: tile waves, then sum waves
-    const int64_t blocks = (jobs + kRowsPerWg - 1) / kRowsPerWg;
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    // Per row block: tile waves, then sum waves (a multiple of kRowsPerWg in all).  The grid's y and z count the row blocks, so that no wave
+    // divides its number.
+    const int64_t blocks = (nkb + kRowBlock) / kRowsPerWg, row_blocks = rows_p / kRowBlock;
+    const int64_t ny = row_blocks < kRowBlocksPerZ ? row_blocks : kRowBlocksPerZ, nz = (row_blocks + ny - 1) / ny;
+    if (blocks * row_blocks > 0x7fffffffLL || nz > 32768) return hipErrorInvalidValue;
     const bool whole = K % 64 == 0;
     const auto kernel = field ? (whole ? pack_kernel<kFieldForm, true> : pack_kernel<kFieldForm, false>)
                       : bits == 3 ? (whole ? pack_kernel<kFold3, true> : pack_kernel<kFold3, false>)
                       : bits == 4 ? (whole ? pack_kernel<kFold4, true> : pack_kernel<kFold4, false>)
                       : byte_form(bits) ? (whole ? pack_kernel<kByteForm, true> : pack_kernel<kByteForm, false>)
                                         : (whole ? pack_kernel<kOtherForm, true> : pack_kernel<kOtherForm, false>);
-    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, codes, rows, K, bits, packed, rows_p, nkb);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks, (unsigned)ny, (unsigned)nz), dim3(kThreads), 0, stream, codes, rows, K, bits, packed, rows_p, nkb);
     return hipGetLastError();
 }
 

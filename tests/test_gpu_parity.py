@@ -110,6 +110,19 @@ def test_pack_unpack_roundtrip(gpu, rows, K, bits):
         assert np.array_equal(sums[:rows].astype(np.int64), want) and not sums[rows:].any()
 
 
+@pytest.mark.parametrize("rows,K,bits", [(32768 * 32 + 40, 5, 3), (33, 4096 + 16, 4), (40, 12303, 3), (33, 16 * 769, 8)])
+def test_pack_row_blocks_and_code_sums(gpu, rows, K, bits):
+    """More row blocks than the second dimension of the packing grid takes; rows whose code sums take eight loads at a time, whole and not."""
+    torch, binding = gpu
+    g = torch.Generator(device="cuda:0").manual_seed(rows + K)
+    codes = torch.randint(0, 1 << bits, (rows, K), generator=g, device="cuda:0", dtype=torch.uint8)
+    packed = binding.apmm_pack_weights(codes, bits)
+    assert torch.equal(binding.apmm_unpack(packed, rows, K, bits), codes)
+    rows_p, k_p = (rows + 31) // 32 * 32, (K + 511) // 512 * 512
+    sums = packed[rows_p * k_p * bits // 8:][:4 * rows].view(torch.int32).long()
+    assert torch.equal(sums, codes.long().sum(1) + (k_p - K) * ((1 << bits) - 1))
+
+
 def test_pack_is_plane_decomposition(gpu):
     """Sec. 4.1: the packed buffer holds exactly `bits` one-bit planes (popcount per plane matches).
 

@@ -103,7 +103,9 @@ def _check(status):
 # plain integers (the argument types convert them), the stream handle is read without building a Stream object, packed
 # sizes are computed once per shape.
 def _stream():
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if not torch.cuda.is_initialized():
+        torch.cuda.init()
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ptr(t):
@@ -113,6 +115,11 @@ def _ptr(t):
 def _dev_u8(t, what):
     if t.dtype != torch.uint8 or not t.is_cuda or not t.is_contiguous() or t.dim() != 2:
         raise ValueError("%s must be a contiguous 2-D uint8 CUDA tensor" % what)
+
+
+def _check_scale(s, n, what):
+    if s.dtype != torch.float16 or s.numel() != n or not s.is_cuda or not s.is_contiguous():
+        raise ValueError("%s must be a contiguous float16 CUDA vector of the right length" % what)
 
 
 @functools.lru_cache(maxsize=1024, typed=True)
@@ -195,10 +202,10 @@ def apmm_gemm(M, N, K, p, q, a_packed, w_packed, want_i32=True, want_f16=False, 
         c_i32 = torch.empty((M, N), dtype=torch.int32, device=dev)
     if want_f16 and c_f16 is None:
         c_f16 = torch.empty((M, N), dtype=torch.float16, device=dev)
-    for s, n, what in ((w_scale, N, "w_scale"), (a_scale, M, "a_scale")):
-        if s is not None and (s.dtype != torch.float16 or s.numel() != n or not s.is_cuda
-                              or not s.is_contiguous()):
-            raise ValueError("%s must be a contiguous float16 CUDA vector of the right length" % what)
+    if w_scale is not None:
+        _check_scale(w_scale, N, "w_scale")
+    if a_scale is not None:
+        _check_scale(a_scale, M, "a_scale")
     ws_bytes = 0 if workspace is None else workspace.nbytes
     _check(load().apmm_gemm_ex(M, N, K, p, q, _ptr(a_packed), _ptr(w_packed), _ptr(c_i32), _ptr(c_f16),
                                _ptr(w_scale), _ptr(a_scale), _ptr(workspace), ws_bytes, _stream(), algo))

@@ -1012,7 +1012,7 @@ hipError_t launch_gemm_decode_group(const GemmArgs *problems, int count, hipStre
     // leads instead of trailing).
     GemmArgs gs[kMaxGroup];
     for (int i = 0; i < count; ++i) gs[i] = problems[i];
-    std::stable_sort(gs, gs + count, [](const GemmArgs &x, const GemmArgs &y) { return x.nkb > y.nkb; });
+    if (count > 1) std::stable_sort(gs, gs + count, [](const GemmArgs &x, const GemmArgs &y) { return x.nkb > y.nkb; });
     const int variant = decode_variant(gs[0], count, xor_only);
     if (variant > 200) return launch_gemm_decode_i8(gs, count, variant - 200, stream);
     if (variant > 100) {

@@ -411,6 +411,16 @@ void gemm_mfma_ksplit_kernel(const uint32_t *a, const uint32_t *w, int32_t *c_i3
     if constexpr (WM == 4) lds_tile<P, Q, 2, WN / 2, 2>(reinterpret_cast<uint4 *>(red), a, w, c_i32, c_f16, m, n, k, magic, tiles_n, tiles_m_xn, w_scale, a_scale, stream);
     else ksplit_tile<P, Q, WM, WN>(red, a, w, c_i32, c_f16, m, n, k, magic, tiles_n, tiles_m_xn, w_scale, a_scale, stream);
 }
+// The 128 x 256 tile (rule and figures: one_round_width): the same two groups of waves, each wave 64 x 128.  Start 2.5, k loop 17, exchange 1.4,
+// store 2.6 us of W2A4 512 x 13824 x 5120; the loop reads and writes LDS at three quarters of its rate.
+template <int P, int Q>
+__global__ __launch_bounds__(512, 1) void gemm_mfma_ksplit_wide_kernel(const uint32_t *a, const uint32_t *w, int32_t *c_i32, uint16_t *c_f16, int m, int n, int k,
+                                                                       uint32_t magic, int tiles_n, int tiles_m_band, const uint16_t *w_scale,
+                                                                       const uint16_t *a_scale, bool stream)
+{
+    extern __shared__ __align__(16) float4 red[];
+    lds_tile<P, Q, 2, 4, 2>(reinterpret_cast<uint4 *>(red), a, w, c_i32, c_f16, m, n, k, magic, tiles_n, tiles_m_band, w_scale, a_scale, stream);
+}
 template <int P, int Q>
 __global__ __launch_bounds__(256) void gemm_mfma_ksplit_long_kernel(const uint32_t *a, const uint32_t *w, int32_t *c_i32, uint16_t *c_f16, int m, int n, int k,
                                                                     uint32_t magic, int tiles_n, int tiles_m_xn, const uint16_t *w_scale,
@@ -449,9 +459,13 @@ hipError_t launch_ksplit_variant(const GemmArgs &g, hipStream_t stream)
     if constexpr (WM == 4) {
         constexpr int lds = lds_tile_bytes<P, Q, 2, WN / 2, 2>();
         static_assert(lds <= 160 * 1024, "LDS of a compute unit");
-        if (Q == 2 || g.K <= ksplit_lds_max_k(P, Q, g)) {
+        const int lds_order = lds_tile_order<P, Q>(tiles_m, g.K);
+        if constexpr (WN == 8) {
+            note_kernel("gemm_mfma_ksplit_wide_kernel<%d,%d>", P, Q);
+            return launch(gemm_mfma_ksplit_wide_kernel<P, Q>, tiles_m * tiles_n, 512, lds, lds_order, lds_band_magic(lds_order, tiles_n, tiles_m * tiles_n),
+                          lds_streams<P, Q, 2, WN / 2, 2>(g), prepared);
+        } else if (Q == 2 || g.K <= ksplit_lds_max_k(P, Q, g)) {
             note_kernel("gemm_mfma_ksplit_kernel<%d,%d,%d,%d>", P, Q, WM, WN);
-            const int lds_order = lds_tile_order<P, Q>(tiles_m, g.K);
             return launch(gemm_mfma_ksplit_kernel<P, Q, WM, WN>, tiles_m * tiles_n, 512, lds, lds_order, lds_band_magic(lds_order, tiles_n, tiles_m * tiles_n),
                           lds_streams<P, Q, 2, WN / 2, 2>(g), prepared);
         }
@@ -471,7 +485,7 @@ hipError_t launch_ksplit_variant(const GemmArgs &g, hipStream_t stream)
     if constexpr (WM != 4) {
         note_kernel("gemm_mfma_ksplit_kernel<%d,%d,%d,%d>", P, Q, WM, WN);
         return launch(gemm_mfma_ksplit_kernel<P, Q, WM, WN>, 8 * part_m * part_n, 256, ksplit_lds_bytes(WM, WN), order, magic, ksplit_streams(WM, WN, g), prepared);
-    } else if constexpr (Q > 2) {
+    } else if constexpr (Q > 2 && WN == 4) {
         note_kernel("gemm_mfma_ksplit_long_kernel<%d,%d>", P, Q);
         return launch(gemm_mfma_ksplit_long_kernel<P, Q>, 8 * part_m * part_n, 256, ksplit_lds_bytes(WM, WN), order, magic, ksplit_streams(WM, WN, g), prepared_long);
     }

@@ -28,7 +28,16 @@ int one_round_width(const GemmArgs &g)
         }
     }
     // 128 x 128 tiles (16 here) where all narrower ones need a second round
-    if (best == 0 && g.q >= 2 && g.nkb >= (g.q > 2 ? 32 : activation_field_form(g.p) ? 88 : 76) && ((g.M + 127) / 128) * ((g.N + 127) / 128) <= 256) return 16;
+    const int64_t tiles128 = ((g.M + 127) / 128) * ((g.N + 127) / 128), tiles256 = ((g.M + 127) / 128) * ((g.N + 255) / 256);
+    // 128 x 256 tiles (32 here), one to a compute unit, for an fp16 output of 2-bit weights under 3- and 4-bit activations that has more than one
+    // round of 128 x 128: 160 bytes of operands per K for what two tiles of 128 x 128 take 256, in a longer start and end.  Time over that of the
+    // kernel with two 128 x 128 tiles to a compute unit, operands and outputs in rotation, W2A4: K = 4096 / 5120 / 8192 / 11008, 512 x 13824 0.85 / 0.80 / 0.79 /
+    // 0.74, 512 x 11008 0.92 / 0.80 / 0.78 / 0.75, 384 x 12000 0.95 / 0.85, 640 x 11008 0.97 / 0.87 / 0.88 / 0.80, 256 x 22016 0.87 / 0.82 / 0.78 / 0.74; 1024 x 7680 1.03 / 0.96 /
+    // 0.92 / 0.83, 768 x 8192 0.98 / 1.03 / 0.82 / 0.79, 512 x 8448 1.02 / 1.02; at K = 6144 0.86 - 0.91.  Below: K = 3584 512 x 13824 1.03, 640 x 11008 1.10.  int32
+    // alone 0.96 - 1.06, both outputs 1.00 - 1.17.  (Operands that fit the last-level cache: 512 x 13824 x 5120 1.02, 512 x 16384 x 4096 1.08.)
+    if (best == 0 && activation_field_form(g.p) && g.q == 2 && !g.c_i32 && tiles128 > 256 && tiles256 <= 256 &&
+        (g.nkb >= 48 || (g.nkb >= 32 && g.M <= 640 && g.N >= 10240))) return 32;
+    if (best == 0 && g.q >= 2 && g.nkb >= (g.q > 2 ? 32 : activation_field_form(g.p) ? 88 : 76) && tiles128 <= 256) return 16;
     return best;
 }
 
@@ -73,8 +82,9 @@ bool gemm_mfma_ksplit_supported(const GemmArgs &g) { return gemm_mfma_fp4_suppor
 bool gemm_mfma_ksplit_pays(const GemmArgs &g)
 {
     if (!gemm_mfma_ksplit_supported(g) || one_round_width(g) == 0) return false;
-    if (one_round_width(g) == 2 || one_round_width(g) == 16) return true;
-    if (activation_field_form(g.p)) return g.nkb >= 40 || (one_round_width(g) == 4 && g.nkb >= 24);
+    const int width = one_round_width(g);
+    if (width == 2 || width >= 16) return true;
+    if (activation_field_form(g.p)) return g.nkb >= 40 || (width == 4 && g.nkb >= 24);
     return g.nkb >= 24 || g.M <= 128;
 }
 

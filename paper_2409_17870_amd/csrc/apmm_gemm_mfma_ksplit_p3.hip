@@ -11,6 +11,9 @@ hipError_t launch_q(const GemmArgs &g, hipStream_t stream, int wn)
     case 16:
         if constexpr (Q >= 2) return mfma::launch_ksplit_variant<3, Q, 4, 4>(g, stream);  // (never taken with single-bit weights)
         return hipErrorInvalidValue;
+    case 32:
+        if constexpr (Q == 2) return mfma::launch_ksplit_variant<3, Q, 4, 8>(g, stream);
+        return hipErrorInvalidValue;
     case 2: return mfma::launch_ksplit_variant<3, Q, 2, 2>(g, stream);
     case 4: return mfma::launch_ksplit_variant<3, Q, 2, 4>(g, stream);
     case 5: return mfma::launch_ksplit_variant<3, Q, 2, 5>(g, stream);

@@ -1118,6 +1118,32 @@ def test_k_split_128_by_128_tile_from_lds_and_from_registers(gpu, p, q, K, long)
     assert torch.equal(c16, want.float().half())
 
 
+# (M, N, K, int32 output too, 128 x 256 tiles taken): both sides of the rule's lines; full and partial tiles, rows of whole lines, pairs and single columns
+WIDE_TILES = [(512, 11008, 4096, False, True), (512, 11008, 3584, False, False), (500, 10251, 4200, False, True), (640, 10242, 4608, False, True), (641, 10242, 4608, False, False),
+              (1000, 6146, 6144, False, True), (1000, 6146, 5632, False, False), (257, 21760, 5000, False, True), (257, 22020, 5000, False, False),
+              (512, 11008, 4096, True, False), (1024, 4096, 6144, False, False)]
+
+
+@pytest.mark.parametrize("p", [3, 4])
+@pytest.mark.parametrize("M,N,K,i32,wide", WIDE_TILES)
+def test_k_split_128_by_256_tile(gpu, p, M, N, K, i32, wide):
+    torch, binding = gpu
+    dev = torch.device("cuda:0")
+    g = torch.Generator(device=dev).manual_seed(8670 + p + M)
+    a = torch.randint(0, 1 << p, (M, K), generator=g, device=dev, dtype=torch.uint8)
+    w = torch.randint(0, 4, (N, K), generator=g, device=dev, dtype=torch.uint8)
+    sa = (0.01 + 0.09 * torch.rand(M, generator=g, device=dev)).half()
+    sw = (0.01 + 0.09 * torch.rand(N, generator=g, device=dev)).half()
+    c32, c16 = binding.apmm_gemm(M, N, K, p, 2, binding.apmm_pack_activations(a, p), binding.apmm_pack_weights(w, 2), want_i32=i32, want_f16=True,
+                                 w_scale=sw, a_scale=sa)
+    assert (binding.apmm_last_gemm_kernel() == "gemm_mfma_ksplit_wide_kernel<%d,2>" % p) == wide
+    want = (2.0 * a.double() - ((1 << p) - 1)) @ (2.0 * w.double() - 3).t().contiguous()  # sums of small integers: exact
+    # two single-precision products and one rounding to binary16: a unit in the last place, 2^-10, of the product in double precision
+    f = want * sa.double()[:, None] * sw.double()[None, :]
+    assert bool(((c16.double() - f).abs() <= 1e-3 * f.abs() + 1e-6).all())
+    assert c32 is None or torch.equal(c32.double(), want)
+
+
 @pytest.mark.parametrize("p,q,K", [(1, 2, 9216), (2, 2, 9216), (4, 2, 10752), (3, 2, 10752), (2, 3, 3584), (4, 1, 12800)])
 def test_k_split_128_by_128_tile_leaves_smaller_k_to_the_large_tiles(gpu, p, q, K):
     """The other side of each line."""

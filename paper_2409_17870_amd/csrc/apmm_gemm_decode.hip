@@ -1030,6 +1030,14 @@ hipError_t launch_gemm_decode_group(const GemmArgs *problems, int count, hipStre
             for (int i = 0; i < count; ++i) two = two && gs[i].M <= 2;
             if (two) rt = rows > 3 * 256 * kRowsPerWg ? 2 : 1;
         }
+        // Narrow activations, long K, where every workgroup reads all tokens for itself: earlier.  Two tiles over single ones, K = 5120 / 8192 / 11008 / 13824: 5120
+        // channels W2A2 one token 0.97 / 0.89 / 0.90 / 0.86, W4A1 8 tokens 0.98 / 0.94 / 0.87 / 0.92, W1A2 16 tokens 0.99 / 0.97 / 0.96 / 0.97; 8192 channels W2A2 one token 0.99 / 0.97 / 0.92 /
+        // 0.93, W4A1 1.01 - 1.03, W1A2 0.99 - 1.03; 32 tokens W2A2 5120 0.98 / 0.94 / 0.89 / 0.85, 8192 1.06 / 0.94 / 0.82 / 0.80, 12288 0.97 / 0.89 / 0.87 / 0.88; 12288 channels, up to 16
+        // tokens 0.91 - 1.12.
+        if (!gs[0].a_codes && gs[0].p <= 2 && variant <= 102 && rows > 256 * kRowsPerWg) {
+            const int64_t shortest = gs[count - 1].nkb;
+            if (rows <= 22 * 256 ? shortest >= 40 : shortest >= 64 && (variant == 102 || (rows <= 8192 && gs[0].q == 2))) rt = 2;
+        }
         // four token tiles (33 - 64 tokens) with packed operands: two workgroups share a compute unit (64 tokens W2A2 5120 x 4096 5.2 / 5.3 us,
         // 8192 x 4096 5.6 / 5.75)
         if (!gs[0].a_codes && variant == 104 && rows > 2 * 256 * kRowsPerWg) rt = 2;

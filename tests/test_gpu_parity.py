@@ -456,7 +456,8 @@ def test_field_form_channel_tiles_per_workgroup(gpu, oracle, M, N, K, p, q, tile
 
 
 @pytest.mark.parametrize("M,N,K,p,q,tiles", [(16, 4096, 4096, 4, 4, 1), (16, 4097, 3600, 4, 4, 2), (3, 4112, 2000, 4, 2, 2), (3, 4112, 1500, 4, 2, 1), (50, 4098, 3585, 3, 3, 2),
-                                             (5, 12288, 600, 2, 2, 1), (16, 12289, 600, 1, 4, 2), (30, 12301, 130, 2, 1, 2), (64, 8192, 300, 1, 1, 1), (33, 8193, 300, 2, 2, 2)])
+                                             (5, 12288, 600, 2, 2, 1), (16, 12289, 600, 1, 4, 2), (30, 12301, 130, 2, 1, 2), (64, 8192, 300, 1, 1, 1), (33, 8193, 300, 2, 2, 2),
+                                             (2, 5632, 5100, 1, 3, 2), (2, 5632, 4600, 1, 3, 1), (1, 5633, 8000, 2, 2, 2), (1, 8193, 8000, 2, 2, 1), (20, 8200, 7700, 2, 1, 2)])
 def test_channel_tiles_per_workgroup_by_rows_and_k(gpu, oracle, M, N, K, p, q, tiles):
     """Both sides of the lines in channels and K; last workgroups of one channel and of a part of one tile."""
     case = dict(M=M, N=N, K=K, p=p, q=q, a_dist="bernoulli", scaled=True)

@@ -10,7 +10,7 @@ namespace apmm {
 namespace {
 thread_local KernelTiming g_timing = {nullptr, nullptr};
 // The name of the last kernel as its format (a literal) and arguments: written out when it is asked for, since a product's call
-// is not much longer than its launch (one token 4096 x 4096 from Python 5.1 -> 4.9 us).
+// is not much longer than its launch (16 x 256 x 512 from Python 5.1 -> 4.7 us, with a shorter binding).
 struct KernelName {
     const char *fmt = "";
     union { int number; const char *text; } arg[8];

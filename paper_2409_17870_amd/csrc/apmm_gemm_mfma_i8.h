@@ -99,7 +99,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_i8_kernel(const uint32_t *a_arg
     const int r32 = lane & 31, kh = lane >> 5;
     // XCD-aware tile map: the tile grid in 8 / xn x xn parts, one per XCD, walked down their columns
     // (The way to the first request is scalar arithmetic in 32 bits: 2048 x 4096 x 4096 W8A8 44.0 -> 42.8 us, 300 x 5003 x 3001 W7A5 both 22.1 -> 21.3.  Code sums and
-    // scales asked for there as well, 40 loads between the first two stages, cost 1 - 17 %: they are asked for at the end.)
+    // scales asked for there as well, 40 loads between the first two stages, cost 3 - 18 %: they are asked for at the end.)
     const uint32_t tiles_m = tiles_m_xn & 0x0fffffff, xn_log = (uint32_t)tiles_m_xn >> 28;
     const uint32_t xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
     const uint32_t part_m = (tiles_m + (8 >> xn_log) - 1) >> (3 - xn_log), part_n = (tiles_n + (1 << xn_log) - 1) >> xn_log;

@@ -411,8 +411,8 @@ void gemm_mfma_ksplit_kernel(const uint32_t *a, const uint32_t *w, int32_t *c_i3
     if constexpr (WM == 4) lds_tile<P, Q, 2, WN / 2, 2>(reinterpret_cast<uint4 *>(red), a, w, c_i32, c_f16, m, n, k, magic, tiles_n, tiles_m_xn, w_scale, a_scale, stream);
     else ksplit_tile<P, Q, WM, WN>(red, a, w, c_i32, c_f16, m, n, k, magic, tiles_n, tiles_m_xn, w_scale, a_scale, stream);
 }
-// The 128 x 256 tile (rule and figures: one_round_width): the same two groups of waves, each wave 64 x 128.  Start 2.5, k loop 17, exchange 1.4,
-// store 2.6 us of W2A4 512 x 13824 x 5120; the loop reads and writes LDS at three quarters of its rate.
+// The 128 x 256 tile (rule and figures: one_round_width): the same two groups of waves, each wave 64 x 128.  Start 3, k loop 17, exchange 1.4,
+// store 2.6 us of W2A4 512 x 13824 x 5120; the products alone would take 10 in the loop, its LDS traffic 9.
 template <int P, int Q>
 __global__ __launch_bounds__(512, 1) void gemm_mfma_ksplit_wide_kernel(const uint32_t *a, const uint32_t *w, int32_t *c_i32, uint16_t *c_f16, int m, int n, int k,
                                                                        uint32_t magic, int tiles_n, int tiles_m_band, const uint16_t *w_scale,

@@ -455,9 +455,13 @@ void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg
     extern __shared__ __align__(16) uint8_t lds_raw[];
     // Up to the first request a launch has nothing else to do, so the way there is short: the wave's number, the problem and every
     // base address are scalars, a lane's part of an address is 32 bits: 108 instead of 190 instructions (W2A2 4096 x 4096 one token 3.1 -> 3.0 us, 22016 x
-    // 4096 7.0 -> 6.0, 64 tokens 4096 x 4096 4.7 -> 4.2, W4A4 one token 4.1 -> 3.6).  (Several token tiles from codes keep the wave's number in
-    // a vector register: their row addresses fill the scalar ones.)
-    const int tid = threadIdx.x, lane = tid & 63, wave = CODES && TT > 1 ? tid >> 6 : __builtin_amdgcn_readfirstlane(tid >> 6);
+    // 4096 7.0 -> 6.0, 64 tokens 4096 x 4096 4.7 -> 4.2, W4A4 one token 4.1 -> 3.6).
+    // From codes, four token tiles or two of any alignment have more row addresses than scalar registers: there the wave's number stays in a
+    // vector register and the number of tokens is an opaque value, compared where it is used.  Two tiles of aligned codes fit them: done this
+    // way they take 91 - 133 vector registers instead of 105 - 156, two workgroups to a compute unit for most widths instead of one (32 tokens
+    // x 4096: W1A4 27648 channels 37.0 -> 27.8 us, W2A4 11008 16.9 -> 14.0, W1A1 11008 10.8 -> 8.9, W2A2 11008 10.9 -> 9.2).
+    constexpr bool SCALARS_FULL = CODES && TT > 1 && !(CODES == 1 && TT == 2);
+    const int tid = threadIdx.x, lane = tid & 63, wave = SCALARS_FULL ? tid >> 6 : __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r16 = lane & 15, kq = lane >> 4;
     const int n0 = block * ROWS, M = (int)pr.M, N = (int)pr.N;
     const uint32_t groups = ((uint32_t)pr.K + kKPad - 1) / kKPad;  // groups of four k blocks; the waves take them in turn
@@ -516,7 +520,7 @@ void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg
     auto load_chunks = [&](int tt, int it, uint4 (&v)[NJ]) __attribute__((always_inline)) {
         const int64_t k0 = (int64_t)4 * kKBlock * (wave + (int64_t)kWaves * it) + 16 * (lane & 31);
         int tokens = M;
-        if constexpr (TT > 1) asm volatile("" : "+s"(tokens));
+        if constexpr (SCALARS_FULL) asm volatile("" : "+s"(tokens));
         const int m_tile = tokens - tt * 16;  // tokens of this tile that exist
         // (the row length as an opaque value: the addresses are then formed where they are used instead of being
         // kept in registers across the k loop, two registers per load and token tile)
@@ -570,7 +574,7 @@ void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg
         const int64_t k0 = (int64_t)4 * kKBlock * (wave + (int64_t)kWaves * it) + 16 * (lane & 31);
         const bool inside = k0 + 16 <= pr.K;
         int tokens = M;
-        if constexpr (TT > 1) asm volatile("" : "+s"(tokens));  // (as row_len above)
+        if constexpr (SCALARS_FULL) asm volatile("" : "+s"(tokens));  // (as row_len above)
         const int m_tile = tokens - tt * 16;
 #pragma unroll
         for (int jj = 0; jj < NJ; ++jj) {

@@ -112,6 +112,18 @@ def test_few_tokens_from_codes_leave_three_workgroups_on_a_compute_unit(kernels,
     assert _of(kernels, "gemm_decode_mfma_kernel")[(p, q, 1, 1, 1, 1)][".vgpr_count"] <= 80
 
 
+@pytest.mark.parametrize("p", [1, 2, 3, 4])
+@pytest.mark.parametrize("q", [1, 2, 3, 4])
+def test_17_to_32_tokens_from_codes_leave_two_workgroups_on_a_compute_unit(kernels, p, q):
+    """gemm_decode_mfma_kernel<p, q, 2, channel tiles, aligned codes, 8>: two workgroups up to 128 registers.  Not 4-bit weights under field-form
+    codes, and not single-bit codes under 2-bit weights with two channel tiles, where one register is missing."""
+    of = _of(kernels, "gemm_decode_mfma_kernel")
+    if p <= 2 or q < 4:
+        assert of[(p, q, 2, 1, 1, 8)][".vgpr_count"] <= 128
+    if p <= 2 and q <= 2 and (p, q) != (1, 2):
+        assert of[(p, q, 2, 2, 1, 8)][".vgpr_count"] <= 128
+
+
 def test_only_tiles_that_a_launch_rule_names_are_built(kernels):
     """gemm_mfma_ksplit_kernel<P, Q, row blocks, column blocks>, gemm_mfma_ksplit_long_kernel<P, Q>, gemm_mfma_lds_kernel<P, Q, row blocks,
     column blocks of a wave, waves to a vector unit> and gemm_mfma_direct_kernel<P, Q, row blocks, column blocks of a wave, phases>"""

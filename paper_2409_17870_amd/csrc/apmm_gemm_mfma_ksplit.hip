@@ -11,6 +11,30 @@ hipError_t launch_gemm_mfma_ksplit_p4(const GemmArgs &g, hipStream_t stream, int
 
 namespace {
 
+// 128 x 256 tiles (32 below), one to a compute unit, for an fp16 output of 2-bit weights under 3- and 4-bit activations that has more than one
+// round of 128 x 128: 160 bytes of operands per K for what two tiles of 128 x 128 take 256, in a longer start and end.  Time over that of the
+// kernel with two 128 x 128 tiles to a compute unit, operands and outputs in rotation, W2A4: K = 4096 / 5120 / 8192 / 11008, 512 x 13824 0.85 / 0.80 / 0.79 /
+// 0.74, 512 x 11008 1.03 / 0.82 / 0.78 / 0.75, 384 x 13824 0.92 / 0.84, 640 x 12288 0.91 / 0.86, 256 x 22016 0.87 / 0.82 / 0.78 / 0.74; at K = 6144 1024 x 5120 0.92,
+// 1024 x 7680 0.86 - 0.91.  Up to 64 tokens the small-M kernel is the other one (33 and 64 tokens x 49160 - 65536, K = 4096 and 6144: 0.38 - 0.48); 65 - 128
+// tokens from 33000 channels on 0.81 - 0.96 at K = 6144.  int32 alone 0.96 - 1.06, both outputs 1.00 - 1.17.  (Operands that fit the
+// last-level cache: 512 x 13824 x 5120 1.02, 512 x 16384 x 4096 1.08.)
+// Not where few compute units would have a second 128 x 128 tile: three rows of tiles and up to 264 tiles 1.07 / 1.04 / 1.05 / 1.04 / 1.02 at K = 4096 / 5120 /
+// 6144 / 8192 / 11008 (384 x 11264).  At K = 6144 513 to 640 tokens 1.03 at 265 tiles and 0.97 at 280, 512 x 8448 and 8704 1.02 and 0.90 at 280, more tokens
+// 1.04 - 1.06 at 258 - 264 tiles, 0.95 - 1.03 at 304, 0.92 - 1.0 at 320; from K = 6656 on 0.99 - 1.02 at 264.  At K = 4096 the other kernel's time is one of two by
+// where its operands lie (512 x 11776 17.3 or 20.6 us, this one 18.5): over five placings each 1.10 at 257 x 11008 and 385 x 11008, 1.06 at 384 x 11776, 0.98
+// at 384 x 12288, 0.95 at 320 x 14336; 1.12 at 257 x 17408; 512 x 10240 - 11776 0.98 - 1.05, 512 x 12288 0.95; 513 x 12288 1.05, 640 x 11520 1.04, 640 x
+// 12288 0.90; 65 x 40000 1.04, 129 x 32768 0.98, 256 x 17408 0.89: the line lies at outputs of 4.4, 4.6 and 7.5 million.  Below: K = 3584 512 x 13824 1.03, 640 x 11008 1.10.
+bool wide_tile_pays(const GemmArgs &g)
+{
+    if (!activation_field_form(g.p) || g.q != 2 || g.c_i32) return false;
+    const int64_t rows = (g.M + 127) / 128, tiles128 = rows * ((g.N + 127) / 128), tiles256 = rows * ((g.N + 255) / 256);
+    if (tiles128 <= 256 || tiles256 > 256 || (rows == 3 && tiles128 <= 264)) return false;
+    if (g.nkb >= 52) return true;
+    if (g.nkb >= 48 && tiles128 >= (g.M <= 640 ? 276 : 320)) return true;
+    if (g.M > 640 || g.N < 10240) return false;
+    return g.nkb >= 36 || (g.nkb == 32 && (g.M <= 64 || g.M * g.N >= (g.M <= 256 ? 4400000 : g.M <= 512 ? 4600000 : 7500000)));
+}
+
 // Tile width (column blocks of 32: 2, 4, 5 or 6; the tile has two row blocks): the one that fills most of the 256
 // compute units in a single round of tiles, i.e. the narrowest with at most 256 tiles, or 0 when every width needs
 // more than one round.  Activations in the group form (1 and 2 bits) have the 64 x 64 and 64 x 128 tiles only, weights of
@@ -27,16 +51,9 @@ int one_round_width(const GemmArgs &g)
             best_tiles = tiles;
         }
     }
+    if (best == 0 && wide_tile_pays(g)) return 32;
     // 128 x 128 tiles (16 here) where all narrower ones need a second round
-    const int64_t tiles128 = ((g.M + 127) / 128) * ((g.N + 127) / 128), tiles256 = ((g.M + 127) / 128) * ((g.N + 255) / 256);
-    // 128 x 256 tiles (32 here), one to a compute unit, for an fp16 output of 2-bit weights under 3- and 4-bit activations that has more than one
-    // round of 128 x 128: 160 bytes of operands per K for what two tiles of 128 x 128 take 256, in a longer start and end.  Time over that of the
-    // kernel with two 128 x 128 tiles to a compute unit, operands and outputs in rotation, W2A4: K = 4096 / 5120 / 8192 / 11008, 512 x 13824 0.85 / 0.80 / 0.79 /
-    // 0.74, 512 x 11008 0.92 / 0.80 / 0.78 / 0.75, 384 x 12000 0.95 / 0.85, 640 x 11008 0.97 / 0.87 / 0.88 / 0.80, 256 x 22016 0.87 / 0.82 / 0.78 / 0.74; 1024 x 7680 1.03 / 0.96 /
-    // 0.92 / 0.83, 768 x 8192 0.98 / 1.03 / 0.82 / 0.79, 512 x 8448 1.02 / 1.02; at K = 6144 0.86 - 0.91.  Below: K = 3584 512 x 13824 1.03, 640 x 11008 1.10.  int32
-    // alone 0.96 - 1.06, both outputs 1.00 - 1.17.  (Operands that fit the last-level cache: 512 x 13824 x 5120 1.02, 512 x 16384 x 4096 1.08.)
-    if (best == 0 && activation_field_form(g.p) && g.q == 2 && !g.c_i32 && tiles128 > 256 && tiles256 <= 256 &&
-        (g.nkb >= 48 || (g.nkb >= 32 && g.M <= 640 && g.N >= 10240))) return 32;
+    const int64_t tiles128 = ((g.M + 127) / 128) * ((g.N + 127) / 128);
     if (best == 0 && g.q >= 2 && g.nkb >= (g.q > 2 ? 32 : activation_field_form(g.p) ? 88 : 76) && tiles128 <= 256) return 16;
     return best;
 }

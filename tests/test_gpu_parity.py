@@ -1122,7 +1122,11 @@ def test_k_split_128_by_128_tile_from_lds_and_from_registers(gpu, p, q, K, long)
 # (M, N, K, int32 output too, 128 x 256 tiles taken): both sides of the rule's lines; full and partial tiles, rows of whole lines, pairs and single columns
 WIDE_TILES = [(512, 11008, 4096, False, True), (512, 11008, 3584, False, False), (500, 10251, 4200, False, True), (640, 10242, 4608, False, True), (641, 10242, 4608, False, False),
               (1000, 6146, 6144, False, True), (1000, 6146, 5632, False, False), (257, 21760, 5000, False, True), (257, 22020, 5000, False, False),
-              (512, 11008, 4096, True, False), (1024, 4096, 6144, False, False)]
+              (512, 11008, 4096, True, False), (1024, 4096, 6144, False, False),
+              (384, 11264, 5120, False, False), (384, 11265, 4608, False, True), (512, 8704, 6144, False, False), (512, 8706, 6144, False, True),
+              (1000, 5000, 6144, False, True), (1000, 4866, 6000, False, False), (1000, 4233, 6200, False, True), (384, 11776, 4096, False, False),
+              (384, 12034, 4096, False, True), (640, 11520, 4096, False, False), (640, 11776, 4096, False, True), (256, 17000, 4096, False, False),
+              (250, 17602, 4096, False, True), (65, 40000, 4096, False, False), (33, 49153, 4096, False, True)]
 
 
 @pytest.mark.parametrize("p", [3, 4])

@@ -480,8 +480,9 @@ void gemm_decode_mfma_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg
         a_wave[i] = CODES ? nullptr : static_cast<const char *>(pr.a) + ((uint64_t)(((uint32_t)tok0 >> 5) + i) * nkb + 4 * wave) * (SA * kSlotBytes);
 
     // Packed operands of 3- and 4-bit activations or four token tiles: one set of raw words, the next iteration's are asked for when this
-    // one's are formed.  A wave has one to four iterations and two to four workgroups share a compute unit, so a second set is worth
-    // less than the registers it takes (W4A4, two channel tiles: 146 -> 94, one -> two workgroups; 27648 x 5120 16 tokens 18.7 -> 16.0 us, 13824 x 5120
+    // one's are formed.  A wave has one to four iterations up to K = 16384 and two to four workgroups share a compute unit, so a second set is worth
+    // less than the registers it takes; of fifteen iterations (K = 60000) two sets over one are 1.02 - 1.04 (W2A4 16 tokens 256 - 1024 channels, W2A2 64 tokens
+    // 4096), but 0.93 at W1A1 64 tokens 4096 channels (W4A4, two channel tiles: 146 -> 94, one -> two workgroups; 27648 x 5120 16 tokens 18.7 -> 16.0 us, 13824 x 5120
     // 10.2 -> 9.1, 48 tokens 4096 x 4096 6.2 -> 5.3; W1A4 64 tokens 4096 x 8192 7.9 -> 6.7).  Narrow activations: 1 - 4 % for the second set.
     constexpr bool SECOND_SET = CODES || (!AF && TT < 4);
     uint4 wnext[RT][Q], anext[TT][SA];
@@ -1037,22 +1038,33 @@ hipError_t launch_gemm_decode_group(const GemmArgs *problems, int count, hipStre
         // Narrow activations, long K, where every workgroup reads all tokens for itself: earlier.  Two tiles over single ones, K = 5120 / 8192 / 11008 / 13824: 5120
         // channels W2A2 one token 0.97 / 0.89 / 0.90 / 0.86, W4A1 8 tokens 0.98 / 0.94 / 0.87 / 0.92, W1A2 16 tokens 0.99 / 0.97 / 0.96 / 0.97; 8192 channels W2A2 one token 0.99 / 0.97 / 0.92 /
         // 0.93, W4A1 1.01 - 1.03, W1A2 0.99 - 1.03; 32 tokens W2A2 5120 0.98 / 0.94 / 0.89 / 0.85, 8192 1.06 / 0.94 / 0.82 / 0.80, 12288 0.97 / 0.89 / 0.87 / 0.88; 12288 channels, up to 16
-        // tokens 0.91 - 1.12.
+        // tokens 0.91 - 1.12.  At K = 5120 the gain ends between 5120 and 6144 channels (W2A2 one token 0.95 / 0.98, 32 tokens 0.98 / 1.03, W4A1 8 tokens 0.98 / 1.01).
+        // Beyond 8192 channels at 32 tokens not under single-bit activations or weights of 3 and 4 bits: K = 8192 and 11008, 9216 - 12288 channels, W1A2 and W2A2 0.90 -
+        // 1.05, W1A1 and W2A1 1.07 - 1.12, W4A1 1.17 - 1.24, W4A2 1.15 - 1.24.
         if (!gs[0].a_codes && gs[0].p <= 2 && variant <= 102 && rows > 256 * kRowsPerWg) {
             const int64_t shortest = gs[count - 1].nkb;
-            if (rows <= 22 * 256 ? shortest >= 40 : shortest >= 64 && (variant == 102 || (rows <= 8192 && gs[0].q == 2))) rt = 2;
+            if (rows <= 22 * 256 ? shortest >= 40
+                                 : shortest >= 64 && (rows <= 8192 ? variant == 102 || gs[0].q == 2 : variant == 102 && gs[0].p == 2 && gs[0].q <= 2)) rt = 2;
+            // more than 128 registers with two channel tiles, one workgroup to a compute unit: 32 tokens W4A1 13824 channels K = 2048 / 8192 1.17 / 1.07, W4A2 1.11 /
+            // 1.05, W3A2 1.14 / 1.04
+            if (variant == 102 && rows < 2 * 256 * 2 * kRowsPerWg && (gs[0].q == 4 || (gs[0].q == 3 && gs[0].p == 2))) rt = rows <= 8192 ? rt : 1;
         }
         // four token tiles (33 - 64 tokens) with packed operands: two workgroups share a compute unit (64 tokens W2A2 5120 x 4096 5.2 / 5.3 us,
-        // 8192 x 4096 5.6 / 5.75)
-        if (!gs[0].a_codes && variant == 104 && rows > 2 * 256 * kRowsPerWg) rt = 2;
+        // 8192 x 4096 5.6 / 5.75), so two channel tiles as soon as single ones would need a third; from K = 7168 on as soon as they would need a
+        // second (4352 - 8192 channels, K = 7168 / 9216 / 16384: W1A2 0.89 / 0.87 / 0.83, W2A2 0.96 / 0.88 / 0.85, W1A1 0.96 / 0.96 / 0.92, W4A1 1.00 / 0.94 / 0.92; at K = 5632
+        // 0.94, 0.96, 1.03 and 1.00)
+        if (!gs[0].a_codes && variant == 104 && rows > (gs[count - 1].nkb >= 56 ? 1 : 2) * 256 * kRowsPerWg) rt = 2;
         // Packed 3- and 4-bit activations (56 - 138 registers), long K: two channel tiles as soon as single ones would need a second workgroup on a
         // compute unit.  Single / two tiles, K = 4096 and 5120: 16 tokens W4A4 4096 channels 3.9 / 4.3 us, 5120 5.1 / 4.5, 8192 6.7 / 6.2, 11008 8.8 /
         // 8.8, 13824 11.0 / 9.8, 27648 18.8 / 16.3; one token W2A4 5120 3.6 / 3.25; 8 tokens W3A3 5120 4.0 / 3.7, 8192 4.3 / 4.4; 32 tokens W2A4 8192 5.2 / 4.7,
         // W4A4 8192 8.6 / 7.2.  K = 2048: W2A4 one token 5120 3.0 / 2.8, 32 tokens 12288 5.3 / 4.6.  Below, a workgroup has little to read and its end
         // weighs more: from the third one (4-bit weights under one token tile: the fourth) on; W4A4 K = 1024 16 tokens 8192 3.0 / 3.1, 12288 3.4 / 3.6.
+        // (4-bit weights under one token tile between 8192 and 12288 channels: single tiles all run at once, three workgroups to a compute unit, double ones one or
+        // two; W4A4 16 tokens K = 4096 / 8192 / 11008 9216 channels 1.08 / 1.06 / 1.08, 12288 1.04 / 1.05 / 1.08)
         if (!gs[0].a_codes && activation_field_form(gs[0].p)) {
-            const bool long_k = gs[count - 1].nkb >= (gs[0].q <= 2 ? 16 : 32);  // (the shortest)
-            if (rows > (long_k ? 1 : gs[0].q == 4 && variant == 101 ? 3 : 2) * 256 * kRowsPerWg) rt = 2;
+            const bool long_k = gs[count - 1].nkb >= (gs[0].q <= 2 ? 16 : 32), wide = gs[0].q == 4 && variant == 101;  // (the shortest)
+            if (rows > (long_k ? 1 : wide ? 3 : 2) * 256 * kRowsPerWg) rt = 2;
+            if (wide && rows > 2 * 256 * kRowsPerWg && rows <= 3 * 256 * kRowsPerWg) rt = 1;
         }
         if (gs[0].a_codes && variant == 104) rt = 1;  // four token tiles from codes: two row tiles do not fit the registers
         // weights of 3 and 4 bits from codes: the two-tile variant fits three waves per SIMD only (11008 x 4096, 4 / 16

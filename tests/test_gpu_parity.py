@@ -469,6 +469,20 @@ def test_channel_tiles_per_workgroup_by_rows_and_k(gpu, oracle, M, N, K, p, q, t
     check_f16(c16, want, data, oracle)
 
 
+@pytest.mark.parametrize("M,N,K,p,q,tiles", [(20, 8200, 7700, 1, 4, 1), (32, 12288, 7700, 2, 3, 1), (17, 8208, 7700, 1, 1, 1), (20, 8192, 7700, 1, 4, 2), (24, 12289, 600, 1, 4, 1),
+                                             (24, 12289, 600, 2, 3, 1), (24, 12289, 600, 1, 3, 2), (24, 16384, 600, 2, 4, 2), (33, 4097, 6657, 1, 2, 2), (64, 4097, 6656, 1, 2, 1),
+                                             (40, 4112, 7168, 2, 4, 2), (16, 8193, 3600, 4, 4, 1), (3, 12288, 3600, 3, 4, 1), (3, 12289, 3600, 4, 4, 2), (20, 8193, 3600, 4, 4, 2)])
+def test_channel_tiles_per_workgroup_at_long_k(gpu, oracle, M, N, K, p, q, tiles):
+    """Both sides of the lines of 17 to 64 tokens and of 4-bit weights under one token tile."""
+    case = dict(M=M, N=N, K=K, p=p, q=q, a_dist="bernoulli", scaled=True)
+    data = inputs.make_case(case, 9300 + M + 10 * p + q)
+    want = oracle.gemm_i64(data["a_codes"], data["w_codes"], p, q)
+    c32, c16 = run_case(gpu, data, case, algo=DECODE, want_i32=True, want_f16=True)
+    assert gpu[1].apmm_last_gemm_kernel().endswith(",%d,packed>" % tiles)
+    assert np.array_equal(c32.astype(np.int64), want)
+    check_f16(c16, want, data, oracle)
+
+
 @pytest.mark.parametrize("p,q", [(1, 1), (2, 1), (5, 3), (2, 4), (8, 2), (1, 4), (6, 4)])
 @pytest.mark.parametrize("M", [1, 2, 3, 5, 8, 13, 16])
 def test_decode_kernel_all_token_counts(gpu, oracle, M, p, q):

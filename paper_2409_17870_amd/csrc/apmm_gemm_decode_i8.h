@@ -141,6 +141,10 @@ void gemm_decode_i8_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg, 
 
     LaneUnit<FB> wn[U][RT];
     LaneUnit<FA> an[U][TT];
+    // Four token tiles of several loads each: the block's place as an opaque scalar per tile, or the compiler asks for the tiles in pairs and carries
+    // six 64-bit lane addresses through the k loop instead of three (33 - 64 tokens, W8A5 64 x 1024 x 16384 26.7 -> 24.3 us, 64 x 4096 x 11008 21.1 ->
+    // 19.8, W4A5 27.0 -> 24.6, W1A5 24.7 -> 23.2, W5A3 0.86 - 0.97 of the time).  Nibbles on both sides: 1.00 - 1.06, left alone.
+    constexpr bool SCALAR_BLOCK = TT == 4 && (FA == kFields || (FA == kNibbles && FB != kNibbles));
     auto load_block = [&](int u, int kb) __attribute__((always_inline)) {
         kb = kb < nkb ? kb : nkb - 1;  // (blocks past the end are loaded from the last one and not multiplied)
 #pragma unroll
@@ -155,7 +159,9 @@ void gemm_decode_i8_kernel(const uint32_t *w_arg, const void *a_arg, int n_arg, 
                     an[u][tt].v[tp] = make_uint4(c.x, c.y, c.z, c.w);
                 }
             } else {
-                load_unit<FA>(oa, static_cast<const char *>(pr.a) + (uint64_t)((tt / 2) * nkb + kb) * (oa.slots * kSlotBytes), a_row + (tt & 1) * 256, ks, an[u][tt]);
+                uint64_t block_at = (uint64_t)((tt / 2) * nkb + kb) * (oa.slots * kSlotBytes);
+                if constexpr (SCALAR_BLOCK) asm volatile("" : "+s"(block_at));
+                load_unit<FA>(oa, static_cast<const char *>(pr.a) + block_at, a_row + (tt & 1) * 256, ks, an[u][tt]);
             }
         }
     };

@@ -124,6 +124,12 @@ def test_17_to_32_tokens_from_codes_leave_two_workgroups_on_a_compute_unit(kerne
         assert of[(p, q, 2, 2, 1, 8)][".vgpr_count"] <= 128
 
 
+@pytest.mark.parametrize("q,registers", [(1, 144), (2, 140), (3, 148), (4, 144), (8, 148)])
+def test_lane_addresses_of_four_token_tiles(kernels, q, registers):
+    """gemm_decode_i8_kernel<nibbles, q, 4, 1>: three 64-bit lane addresses in the k loop, not six (six more registers and up to a tenth of the time)."""
+    assert _of(kernels, "gemm_decode_i8_kernel")[(5, q, 4, 1)][".vgpr_count"] <= registers
+
+
 def test_only_tiles_that_a_launch_rule_names_are_built(kernels):
     """gemm_mfma_ksplit_kernel<P, Q, row blocks, column blocks>, gemm_mfma_ksplit_long_kernel<P, Q>, gemm_mfma_lds_kernel<P, Q, row blocks,
     column blocks of a wave, waves to a vector unit> and gemm_mfma_direct_kernel<P, Q, row blocks, column blocks of a wave, phases>"""

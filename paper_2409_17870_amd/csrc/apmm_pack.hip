@@ -901,7 +901,8 @@ hipError_t launch_quantize_pack(const uint16_t *x, int64_t rows, int64_t K, int 
         kernel = waves == 1 ? (whole ? quantize_pack_kernel<1, true, false> : quantize_pack_kernel<1, false, false>)
                : waves == 2 ? (whole ? quantize_pack_kernel<2, true, false> : quantize_pack_kernel<2, false, false>)
                             : (whole ? quantize_pack_kernel<4, true, false> : quantize_pack_kernel<4, false, false>);
-    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, x, rows, K, bits, packed, scale, rows_p, nkb);
+    const size_t lds = quantize_few_workgroups(rows, K, bits, field) ? 32000 : 0;  // not read: it leaves room for five workgroups
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kThreads), lds, stream, x, rows, K, bits, packed, scale, rows_p, nkb);
     return hipGetLastError();
 }
 

@@ -735,6 +735,17 @@ def test_quantize_many_rows_in_the_field_form(gpu, oracle, M, K, p, shift):
     assert torch.equal(packed, again)
 
 
+@pytest.mark.parametrize("M,K,p", [(4151, 4096, 8), (4400, 6656, 5), (1300, 20000, 7), (2048, 16385, 4)])
+def test_quantize_with_few_workgroups_to_a_compute_unit(gpu, oracle, M, K, p):
+    torch, binding = gpu
+    dev = torch.device("cuda:0")
+    x = inputs.normal_features_f16(8060 + M + K + p, inputs.TAG_A, M, K, outlier_every=37)
+    want_codes, want_scale = oracle.quantize_rows(x, p)
+    packed, scale = binding.apmm_quantize_pack_activations(torch.from_numpy(x).to(dev), p)
+    assert np.array_equal(scale.cpu().numpy().view(np.uint16), want_scale)
+    assert torch.equal(packed, binding.apmm_pack_activations(torch.from_numpy(want_codes).to(dev), p))
+
+
 def test_quantized_activations_through_the_gemm(gpu, oracle):
     """float16 activations -> quantise + pack -> GEMM with the fp16 epilogue, against the oracle's
     quantiser, integer GEMM and double-precision scaling."""

@@ -1,5 +1,5 @@
 """The launchers' rules, host functions of sizes, addresses and widths, compiled for the host alone and asked on both sides of their
-lines: which calls store their inner tiles streaming, which quantise four rows to a workgroup, and which take the direct tiles or the register form of the 128 x 128 K split where the
+lines: which calls store their inner tiles streaming, which quantise four rows to a workgroup and which with few workgroups to a compute unit, and which take the direct tiles or the register form of the 128 x 128 K split where the
 kernels that share operands through LDS are slower."""
 import os
 import shutil
@@ -41,6 +41,7 @@ int main()
         else if (k == "r22") std::printf("%d\n", rounds(rounds_go_direct<2, 2>, 256, 256));
         else if (k == "r11") std::printf("%d\n", rounds(rounds_go_direct<1, 1>, 256, 256));
         else if (k == "quant") std::printf("%d\n", (int)quantize_rows_by_four(M, K));
+        else if (k == "few") std::printf("%d\n", (int)quantize_few_workgroups(M, K, (int)N, N == 3 || N == 4));
         else if (k == "max13") std::printf("%lld\n", (long long)ksplit_lds_max_k(1, 3, g));
         else if (k == "max23") std::printf("%lld\n", (long long)ksplit_lds_max_k(2, 3, g));
         else if (k == "max24") std::printf("%lld\n", (long long)ksplit_lds_max_k(2, 4, g));
@@ -95,6 +96,8 @@ RULES = [
     ("quant", 513, 0, 4900, 0, 0, 0), ("quant", 800, 0, 4900, 0, 0, 1), ("quant", 513, 0, 8704, 0, 0, 0), ("quant", 641, 0, 8704, 0, 0, 1),
     ("quant", 1024, 0, 2560, 0, 0, 1), ("quant", 1025, 0, 2560, 0, 0, 0), ("quant", 1599, 0, 2049, 0, 0, 0), ("quant", 1600, 0, 2049, 0, 0, 1),
     ("quant", 1300, 0, 2561, 0, 0, 1), ("quant", 513, 0, 16384, 0, 0, 1), ("quant", 4096, 0, 16385, 0, 0, 0),
+    ("few", 4096, 8, 4096, 0, 0, 0), ("few", 4151, 8, 4096, 0, 0, 1), ("few", 4150, 8, 4096, 0, 0, 0), ("few", 4096, 5, 6912, 0, 0, 1), ("few", 4096, 5, 6144, 0, 0, 0),
+    ("few", 12000, 8, 9000, 0, 0, 0), ("few", 2048, 8, 20000, 0, 0, 1), ("few", 2048, 4, 20000, 0, 0, 1), ("few", 16384, 2, 11008, 0, 0, 0),
     ("max13", 1, 1, 1, AT, 0, 8192), ("max13", 1, 1, 1, 0, AT, 9216), ("max23", 1, 1, 1, AT, 0, 5632), ("max23", 1, 1, 1, AT, AT, 8704),
     ("max24", 1, 1, 1, AT, 0, 7168), ("max44", 1, 1, 1, AT, 0, 9216),
 ]

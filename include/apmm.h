@@ -220,7 +220,7 @@ apmm_status apmm_time_next_gemm(void *start_event, void *stop_event);
 
 /* Measurement aid.  Name, with its template arguments, of the GEMM kernel that the last GEMM call of the calling
  * thread launched ("" before the first), e.g. "gemm_mfma_direct_kernel<2,1,4,4,3>" (activation bits, weight bits,
- * wave tile in 32-row and 32-column blocks, store phases).  The string is overwritten by the next GEMM call. */
+ * wave tile in 32-row and 32-column blocks, store phases).  The string is the calling thread's and stays until it asks again. */
 const char *apmm_last_gemm_kernel(void);
 
 const char *apmm_status_string(apmm_status status);

@@ -1,6 +1,5 @@
 // Dispatch of the MFMA GEMMs (design A).  The kernels are instantiated in apmm_gemm_mfma_p<P>.hip,
 // one translation unit per activation width, so that they compile in parallel.
-#include <cstdarg>
 #include <cstdio>
 
 #include "apmm_kernels.h"
@@ -9,28 +8,22 @@ namespace apmm {
 
 namespace {
 thread_local KernelTiming g_timing = {nullptr, nullptr};
-// The name of the last kernel as its format (a literal) and arguments: written out when it is asked for, since a product's call
-// is not much longer than its launch (16 x 256 x 512 from Python 5.1 -> 4.7 us, with a shorter binding).
+// The name of the last kernel as its format and arguments: written out when it is asked for, since a product's call is not much longer than
+// its launch (16 x 256 x 512 from Python 5.1 -> 4.7 us, with a shorter binding, the two in turn in one process).
 struct KernelName {
     const char *fmt = "";
-    union { int number; const char *text; } arg[8];
+    KernelNameArg arg[kMaxKernelNameArgs];
+    int count = 0;
     char written[96];
 };
 thread_local KernelName g_last_kernel;
 }
-void note_kernel(const char *fmt, ...)
+void keep_kernel_name(const char *fmt, const KernelNameArg *args, int count)
 {
     KernelName &k = g_last_kernel;
     k.fmt = fmt;
-    va_list ap;
-    va_start(ap, fmt);
-    int n = 0;
-    for (const char *c = fmt; *c && n < 8; ++c) {
-        if (*c != '%') continue;
-        if (*++c == 's') k.arg[n++].text = va_arg(ap, const char *);
-        else k.arg[n++].number = va_arg(ap, int);
-    }
-    va_end(ap);
+    k.count = count;
+    for (int i = 0; i < count; ++i) k.arg[i] = args[i];
 }
 const char *last_kernel()
 {
@@ -42,11 +35,12 @@ const char *last_kernel()
             k.written[at++] = *c;
             continue;
         }
-        const bool text = *++c == 's';
-        const int w = text ? std::snprintf(k.written + at, sizeof(k.written) - at, "%s", k.arg[n].text)
-                           : std::snprintf(k.written + at, sizeof(k.written) - at, "%d", k.arg[n].number);
-        ++n;
-        at = at + w < sizeof(k.written) ? at + w : sizeof(k.written) - 1;
+        if (c[1]) ++c;
+        if (n == k.count) continue;
+        const KernelNameArg &a = k.arg[n++];
+        const size_t room = sizeof(k.written) - at;
+        const size_t w = (size_t)(a.text ? std::snprintf(k.written + at, room, "%s", a.text) : std::snprintf(k.written + at, room, "%d", a.number));
+        at += w < room ? w : room - 1;
     }
     k.written[at] = 0;
     return k.written;

@@ -1,6 +1,9 @@
 // Host-side launchers of the library's kernels (internal; the public ABI is include/apmm.h).
 #pragma once
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
+
 #include "apmm_layout.h"
 
 namespace apmm {
@@ -76,8 +79,25 @@ struct KernelTiming {
 };
 void set_kernel_timing(hipEvent_t start, hipEvent_t stop);
 KernelTiming take_kernel_timing();  // returns the pair and clears it
-// Measurement aid: name (with template arguments) of the GEMM kernel the calling thread launched last.
-void note_kernel(const char *fmt, ...) __attribute__((format(printf, 1, 2)));
+// Measurement aid: name (with template arguments) of the GEMM kernel the calling thread launched last.  The format and the arguments are kept
+// and written out when the name is asked for: both are string literals, or int.  Every %d or %s takes the next argument, whatever its
+// kind, and nothing where there is none left.
+struct KernelNameArg {
+    const char *text = nullptr;
+    int number = 0;
+};
+inline KernelNameArg kernel_name_arg(int number) { return {nullptr, number}; }
+inline KernelNameArg kernel_name_arg(const char *literal) { return {literal, 0}; }
+constexpr int kMaxKernelNameArgs = 5;
+void keep_kernel_name(const char *fmt, const KernelNameArg *args, int count);
+template <class... Args>
+inline void note_kernel(const char *fmt, Args... args)
+{
+    static_assert(sizeof...(Args) <= kMaxKernelNameArgs, "arguments of a kernel's name");
+    static_assert(((std::is_same<Args, int>::value || std::is_same<Args, const char *>::value) && ...), "int or a literal");
+    const KernelNameArg list[sizeof...(Args) + 1] = {kernel_name_arg(args)...};
+    keep_kernel_name(fmt, list, (int)sizeof...(Args));
+}
 const char *last_kernel();
 
 // Small-M weight-streaming kernels: on the fp4 matrix operations for p, q <= 4 (M <= 64; unpacked activation codes of 3 and 4

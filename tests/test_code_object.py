@@ -94,7 +94,7 @@ def _of(kernels, name):
     return out
 
 
-@pytest.mark.parametrize("name", ["gemm_mfma_ksplit_kernel", "gemm_mfma_ksplit_long_kernel", "gemm_decode_i8_kernel", "gemm_decode_mfma_kernel",
+@pytest.mark.parametrize("name", ["gemm_mfma_ksplit_kernel", "gemm_mfma_ksplit_long_kernel", "gemm_mfma_ksplit_wide_kernel", "gemm_decode_i8_kernel", "gemm_decode_mfma_kernel",
                                   "gemm_mfma_lds_kernel", "gemm_mfma_i8_kernel", "gemm_mfma_direct_kernel"])
 def test_no_vector_register_is_spilled(kernels, name):
     """But for the 256 x 256 tile of single bits on both sides in one phase, which keeps 16 in scratch."""
@@ -102,6 +102,14 @@ def test_no_vector_register_is_spilled(kernels, name):
     if name == "gemm_mfma_direct_kernel":
         assert spilled.pop((1, 1, 4, 4, 1), 0) <= 16
     assert not spilled
+
+
+def test_packing_and_quantising_kernels_spill_nothing(kernels):
+    """pack_kernel is bound to eight waves to a vector unit, 64 registers."""
+    found = {name: k for name, k in kernels.items() if re.search(r"\d(un)?pack_(rows_)?kernel|quantize_(pack|fields)_kernel", name)}
+    assert len(found) == 10 + 4 + 12 + 8 + 1
+    assert not [name for name, k in found.items() if k[".vgpr_spill_count"] or k[".private_segment_fixed_size"]]
+    assert all(k[".vgpr_count"] <= 64 for name, k in found.items() if "11pack_kernel" in name)
 
 
 @pytest.mark.parametrize("p", [1, 2])
@@ -131,7 +139,7 @@ def test_lane_addresses_of_four_token_tiles(kernels, q, registers):
 
 
 def test_only_tiles_that_a_launch_rule_names_are_built(kernels):
-    """gemm_mfma_ksplit_kernel<P, Q, row blocks, column blocks>, gemm_mfma_ksplit_long_kernel<P, Q>, gemm_mfma_lds_kernel<P, Q, row blocks,
+    """gemm_mfma_ksplit_kernel<P, Q, row blocks, column blocks>, gemm_mfma_ksplit_long_kernel<P, Q>, gemm_mfma_ksplit_wide_kernel<P, Q>, gemm_mfma_lds_kernel<P, Q, row blocks,
     column blocks of a wave, waves to a vector unit> and gemm_mfma_direct_kernel<P, Q, row blocks, column blocks of a wave, phases>"""
     for p, q, wm, wn in _of(kernels, "gemm_mfma_ksplit_kernel"):
         if wm == 4:
@@ -139,6 +147,7 @@ def test_only_tiles_that_a_launch_rule_names_are_built(kernels):
         else:
             assert wm == 2 and wn in ((2, 4) if p <= 2 else (2, 4, 5, 6) if q <= 2 else (2, 4, 5))
     assert set(_of(kernels, "gemm_mfma_ksplit_long_kernel")) == {(p, q) for p in (1, 2, 3, 4) for q in (3, 4)}
+    assert set(_of(kernels, "gemm_mfma_ksplit_wide_kernel")) == {(3, 2), (4, 2)}
     for p, q, wm, wn, _ in _of(kernels, "gemm_mfma_lds_kernel"):
         assert (wm, wn) == (2, 2) or (p > 2 and q <= 2 and (wm, wn) == (2, 4))
     for p, q, wm, wn, phases in _of(kernels, "gemm_mfma_direct_kernel"):
@@ -162,3 +171,9 @@ def test_inner_tiles_have_streaming_and_plain_stores(dword_stores, name):
             assert count["nt"] * 2 == count["plain"] * 3  # outputs of a size that always streams: the border alone is plain
             continue
         assert count["nt"] > 0 and count["nt"] * 5 == count["plain"] * 3, (args, count)
+
+
+def test_128_by_256_tile_stores_fp16_alone(dword_stores):
+    """Four blocks a wave, 8 dword stores of pairs each, streaming and plain; no int32 store, which the launch rule never asks for."""
+    for args, count in _of(dword_stores, "gemm_mfma_ksplit_wide_kernel").items():
+        assert count["nt"] == count["plain"] == 32, (args, count)

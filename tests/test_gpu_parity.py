@@ -1174,6 +1174,33 @@ def test_k_split_128_by_256_tile(gpu, p, M, N, K, i32, wide):
     assert c32 is None or torch.equal(c32.double(), want)
 
 
+@pytest.mark.parametrize("p", [3, 4])
+@pytest.mark.parametrize("M,N,K", [(512, 12288, 4096), (500, 10251, 4200), (640, 10242, 4650)])
+def test_k_split_128_by_256_tile_to_the_integer(gpu, p, M, N, K):
+    """Sums that all but cancel, so that binary16 holds each of them: the second half of the columns undoes the first, all but the last forty, and the
+    columns are shuffled over both halves of K.  Without scales and with either one alone: sums below 2^11 times 11 significant bits are exact in
+    single precision, so the one rounding to binary16 is all there is."""
+    torch, binding = gpu
+    dev = torch.device("cuda:0")
+    g = torch.Generator(device=dev).manual_seed(8680 + p + M)
+    half = (K - 40) // 2
+    a = torch.randint(0, 1 << p, (M, K), generator=g, device=dev, dtype=torch.uint8)
+    w = torch.randint(0, 4, (N, K), generator=g, device=dev, dtype=torch.uint8)
+    a[:, half:2 * half] = (1 << p) - 1 - a[:, :half]
+    w[:, half:2 * half] = w[:, :half]
+    order = torch.randperm(K, generator=g, device=dev)
+    a, w = a[:, order].contiguous(), w[:, order].contiguous()
+    sa = (0.01 + 0.09 * torch.rand(M, generator=g, device=dev)).half()
+    sw = (0.01 + 0.09 * torch.rand(N, generator=g, device=dev)).half()
+    want = ((2.0 * a.double() - ((1 << p) - 1)) @ (2.0 * w.double() - 3).t().contiguous()).float()
+    assert float(want.abs().max()) <= 2048 and len(want.unique()) > 100
+    ap, wp = binding.apmm_pack_activations(a, p), binding.apmm_pack_weights(w, 2)
+    for scales, factor in (({}, 1.0), ({"w_scale": sw}, sw.float()[None, :]), ({"a_scale": sa}, sa.float()[:, None])):
+        _, c16 = binding.apmm_gemm(M, N, K, p, 2, ap, wp, want_i32=False, want_f16=True, **scales)
+        assert binding.apmm_last_gemm_kernel() == "gemm_mfma_ksplit_wide_kernel<%d,2>" % p
+        assert torch.equal(c16, (want * factor).half())
+
+
 @pytest.mark.parametrize("p,q,K", [(1, 2, 9216), (2, 2, 9216), (4, 2, 10752), (3, 2, 10752), (2, 3, 3584), (4, 1, 12800)])
 def test_k_split_128_by_128_tile_leaves_smaller_k_to_the_large_tiles(gpu, p, q, K):
     """The other side of each line."""

@@ -164,8 +164,10 @@ constexpr int kAlgoMfmaI8 = -1, kAlgoDecodeI8 = -2;  // chosen by APMM_ALGO_AUTO
 apmm_status run_gemm(const apmm::GemmArgs &g, int algo, hipStream_t s, void *workspace = nullptr, size_t workspace_bytes = 0)
 {
     if (algo == APMM_ALGO_AUTO) {
-        // (33 - 64 tokens at more than 8192 channels: the small-M kernel needs a second round of its one-per-CU workgroups
-        // there, 10.0 us at 11008 x 4096, and the K-split kernel's 86 tiles take 7.9 - 8.6 us)
+        // 33 - 64 tokens go to the K-split kernel beyond 8192 channels, where single channel tiles of the small-M kernel need a third workgroup on a
+        // compute unit and double ones a second.  64 tokens, K = 4096, small-M kernel / K split at 8192, 9216, 11008 and 16384 channels: W1A1 5.1 / 5.8, 6.5 / 5.9, 6.6 /
+        // 5.9, 6.9 / 6.0 us; W2A2 5.8 / 6.0, 7.3 / 6.2, 7.5 / 6.3, 8.4 / 7.3; W2A4 6.2 / 7.3, 8.3 / 7.4, 8.7 / 7.7, 11.4 / 8.8; W4A4 9.3 / 9.5, 11.9 / 9.9, 12.5 / 10.2, 17.6 /
+        // 11.2.  (33 tokens of single bits 1 - 2 % either way up to 16384.)
         if (apmm::gemm_decode_supported(g) && !(g.M > 32 && g.N > 8192 && !g.a_codes && apmm::gemm_mfma_ksplit_pays(g)))
             algo = APMM_ALGO_DECODE;
         else if (apmm::gemm_mfma_fp4_supported(g)) algo = apmm::gemm_mfma_ksplit_pays(g) ? APMM_ALGO_MFMA_KSPLIT : APMM_ALGO_MFMA_FP4;

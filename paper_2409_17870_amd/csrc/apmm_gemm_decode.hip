@@ -1030,7 +1030,9 @@ hipError_t launch_gemm_decode_group(const GemmArgs *problems, int count, hipStre
         // so fewer, larger workgroups pay: 7.7 -> 6.7 us for 4 tokens at 11008 x 4096, a loss at 4096 channels)
         int rt = (gs[0].a_codes ? rows >= 256 * 2 * kRowsPerWg : rows > 3 * 256 * kRowsPerWg) ? 2 : 1;
         if (gs[0].a_codes) {
-            // at most two tokens from codes: that kernel variant fits three workgroups per CU
+            // At most two tokens from codes: that kernel variant fits three or four workgroups per CU (54 - 80 registers), which hold 12288 channels of single tiles.
+            // One token, K = 4096, single / two tiles at 11008, 12288, 12800 and 16384 channels: W2A2 4.5 / 4.65, 4.65 / 4.9, 4.95 / 4.85, 5.35 / 5.25 us; W1A2 4.15 / 3.9,
+            // 4.2 / 3.95, 4.6 / 3.95, 4.7 / 4.15; W2A1 4.95 / 4.9, 5.0 / 4.95, 5.7 / 5.05, 6.1 / 5.45 (single-bit weights would take two tiles from 8192 on, 0.93 - 0.95).
             bool two = true;
             for (int i = 0; i < count; ++i) two = two && gs[i].M <= 2;
             if (two) rt = rows > 3 * 256 * kRowsPerWg ? 2 : 1;

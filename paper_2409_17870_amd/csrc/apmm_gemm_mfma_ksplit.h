@@ -83,8 +83,8 @@ __device__ __forceinline__ void ksplit_tile(float4 *red, const uint32_t *a_arg, 
     // Workgroups are dealt round-robin to the 8 XCDs, each with an L2 of its own.  The tile grid is cut into
     // 8 / xn x xn parts, one per XCD, and a part is walked down its columns: the workgroups that run together on an
     // XCD share the packed rows of a few column tiles and of the part's row tiles (tiles_m_xn = tiles_m | log2(xn) << 28).
-    // (The way to the first request is scalar arithmetic in 32 bits, 145 instead of 215 instructions for 64 x 160: 203 x 4096 x 4096 W2A2 6.4 -> 6.1 us, 300 x
-    // 2000 x 700 W2A3 5.7 -> 5.4, 1024 x 4096 x 11008 W4A4 33.3 -> 31.9.)
+    // (The way to the first request is scalar arithmetic in 32 bits, 145 instead of 215 instructions for 64 x 160: 203 x 4096 x 4096 W2A2 6.6 -> 6.25 us, 300 x
+    // 2000 x 700 W2A3 5.7 -> 5.3, 1024 x 4096 x 11008 W4A4 33.7 -> 32.8.)
     const uint32_t tiles_m = tiles_m_xn & 0x0fffffff, xn_log = (uint32_t)tiles_m_xn >> 28;
     const uint32_t xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
     const uint32_t part_m = (tiles_m + (8 >> xn_log) - 1) >> (3 - xn_log), part_n = (tiles_n + (1 << xn_log) - 1) >> xn_log;

@@ -91,7 +91,7 @@ __device__ __forceinline__ void lds_tile(uint4 *ring_of_workgroup, const uint32_
     const int r32 = lane & 31, kh = lane >> 5;
     // An XCD takes a contiguous run of tiles in an order that walks `band` tile rows column by column (see lds_tile_order).
     // (All of the way to the first request is scalar arithmetic in 32 bits where the sizes allow it, 112 instead of 176 instructions for 128 x 256, with
-    // which the median wave of a cold launch spent 1.0 us: W2A2 1024 x 11008 x 4096 int32 26.7 -> 26.0 us, W2A4 2048 x 11008 x 4096 both 58.5 -> 57.5.)
+    // which the median wave of a cold launch spent 1.0 us: W2A2 1024 x 11008 x 4096 int32 26.0 -> 25.7 us, W2A4 2048 x 11008 x 4096 both 62.3 -> 61.8.)
     const uint32_t nkb = padded_k_blocks(k_arg);
     const uint32_t tiles_m = tiles_m_band & 0x0fffffff, band_log = (uint32_t)tiles_m_band >> 28, band = 1u << band_log;
     const uint32_t lid = xcd_tile_id(blockIdx.x, tiles_n * (int)tiles_m);

@@ -194,7 +194,7 @@ __device__ __forceinline__ void store_fields(uint32_t *__restrict__ packed, int6
 
 // pack_rows_kernel: one wave per row: lane l packs the 32-element groups l, l+64, ... (two 16-byte loads of codes
 // each, 1 KB contiguous per load instruction) and keeps a running code sum; the wave adds the 64 partial sums
-// with lane shuffles.  Reads are ideal, writes are 8- and 16-byte pieces that other waves complete to whole
+// with lane permutes (over_wave).  Reads are ideal, writes are 8- and 16-byte pieces that other waves complete to whole
 // lines later.  Used for group-form operands of one or two bits, where little is written.
 template <int bits, bool WHOLE>
 __global__ __launch_bounds__(kThreads) void pack_rows_kernel(const uint8_t *__restrict__ codes, int64_t rows,

@@ -18,6 +18,27 @@ __device__ __forceinline__ uint16_t float_to_half_bits(float x)
     return __half_as_ushort(__float2half_rn(x));
 }
 
+// fp16 results in pairs of columns: lane l holds column l of rows r (x0) and r + 1 (x1), and stores one dword, the even lane of a lane
+// pair both columns of row r, the odd lane both of row r + 1.  half_pair rounds the two into one register (low, high half), swap_pair
+// exchanges halves between the lanes: a lane permute and a byte permute, whose selector is the lane's for good.  Six operations a pair of results (two of
+// them products with the token scales) where selects, masks and shifts took twelve, and that much less code for the K-split kernels to
+// fetch at their end: W2A4 512 x 5120 x 5120 12.42 -> 12.21 us, 512 x 5120 x 13824 23.3 -> 22.6, W8A8 512 x 4096 x 4096 15.8 -> 15.5, 2048 x 11008 x 2048 67.8 ->
+// 65.9, W2A2 1024 x 11008 x 4096 24.1 -> 23.7.  (By hand: left to itself the compiler makes four products and a conversion of two, which rounds once
+// more than the single results' mixed multiplication.  Not in the direct tiles: the 256 x 256 ones spill with it.)
+__device__ __forceinline__ uint32_t half_pair(float x0, float x1, float y)
+{
+    uint32_t h;
+    asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(h) : "v"(x0), "v"(y));
+    asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(h) : "v"(x1), "v"(y));
+    return h;
+}
+__device__ __forceinline__ uint32_t swap_pair_selector(bool odd) { return odd ? 0x03020706u : 0x05040100u; }
+__device__ __forceinline__ uint32_t swap_pair(uint32_t mine, uint32_t selector)
+{
+    const uint32_t other = (uint32_t)__builtin_amdgcn_mov_dpp((int)mine, 0xB1, 0xf, 0xf, true);  // quad_perm [1, 0, 3, 2]
+    return __builtin_amdgcn_perm(other, mine, selector);
+}
+
 // scale for row m / column n (1.0f when the vector is absent)
 __device__ __forceinline__ float load_scale(const uint16_t *scale, int64_t idx)
 {

@@ -255,13 +255,11 @@ __global__ __launch_bounds__(256) void gemm_mfma_i8_kernel(const uint32_t *a_arg
         if (cf_arg && interior && pair_ok) {
             // rows in pairs: the even lane of a lane pair stores both columns of the first row, the odd lane both of the second
             const bool odd = lane & 1;
+            const uint32_t selector = swap_pair_selector(odd);
             uint32_t word[8];
 #pragma unroll
             for (int v = 0; v < 16; v += 2) {
-                const uint32_t h0 = float_to_half_bits((float)c[v] * sa(v) * sw), h1 = float_to_half_bits((float)c[v + 1] * sa(v + 1) * sw);
-                const uint32_t give = odd ? h0 : h1, keep = odd ? h1 : h0;
-                const uint32_t got = (uint32_t)__builtin_amdgcn_mov_dpp((int)give, 0xB1, 0xf, 0xf, true);
-                word[v / 2] = odd ? (got | (keep << 16)) : (keep | (got << 16));
+                word[v / 2] = swap_pair(half_pair((float)c[v] * sa(v), (float)c[v + 1] * sa(v + 1), sw), selector);
             }
             auto dst = [&](int i) __attribute__((always_inline)) {
                 return reinterpret_cast<uint32_t *>(cf_arg + (row(2 * i) + (odd ? 1 : 0)) * N + n - (odd ? 1 : 0));

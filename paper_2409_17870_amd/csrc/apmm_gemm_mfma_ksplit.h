@@ -272,6 +272,7 @@ __device__ __forceinline__ void ksplit_tile(float4 *red, const uint32_t *a_arg, 
     const bool pair_ok = (N & 1) == 0 && (reinterpret_cast<uintptr_t>(cf_arg) & 3u) == 0;
     if constexpr (ksplit_always_streams(WM, WN)) stream = true;
     const bool odd = lane_out & 1;
+    const uint32_t selector = swap_pair_selector(odd);
     float sa_f[16];
 #pragma unroll
     for (int v = 0; v < 16; ++v) sa_f[v] = half_bits_to_float((uint16_t)use_here(sa_bits[v]));
@@ -294,11 +295,7 @@ __device__ __forceinline__ void ksplit_tile(float4 *red, const uint32_t *a_arg, 
                 if constexpr (F16 && !PAIR) cf_arg[m * N + n] = float_to_half_bits(c[v] * sa_f[v] * sw);
                 if constexpr (F16 && PAIR) {
                     if (v % 2 == 0) {
-                        const uint32_t h0 = float_to_half_bits(c[v] * sa_f[v] * sw);
-                        const uint32_t h1 = float_to_half_bits(c[(v + 1) & 15] * sa_f[(v + 1) & 15] * sw);
-                        const uint32_t give = odd ? h0 : h1, keep = odd ? h1 : h0;
-                        const uint32_t got = (uint32_t)__builtin_amdgcn_mov_dpp((int)give, 0xB1, 0xf, 0xf, true);
-                        const uint32_t word = odd ? (got | (keep << 16)) : (keep | (got << 16));
+                        const uint32_t word = swap_pair(half_pair(c[v] * sa_f[v], c[(v + 1) & 15] * sa_f[(v + 1) & 15], sw), selector);
                         // odd lanes write the row below at the column to the left
                         uint32_t *dst = reinterpret_cast<uint32_t *>(cf_arg + (m + (odd ? 1 : 0)) * N + n - (odd ? 1 : 0));
                         if constexpr (NT) __builtin_nontemporal_store(word, dst);

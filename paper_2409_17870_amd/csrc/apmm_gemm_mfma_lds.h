@@ -365,6 +365,7 @@ __device__ __forceinline__ void lds_tile(uint4 *ring_of_workgroup, const uint32_
         uint16_t *ch = F16 ? cf_arg + m_lane * N + n_lane : nullptr;
         const bool odd = lane & 1;
         uint16_t *ch_pair = F16 ? ch + (odd ? N - 1 : 0) : nullptr;  // odd lanes write the row below at the column to the left
+        const uint32_t selector = swap_pair_selector(odd);
         auto token_scale = [&](int bi, int v) __attribute__((always_inline)) {
             const uint32_t h = (uint32_t)__shfl((int)sa_raw[bi / 2], (bi & 1) * 32 + 8 * (v / 4) + 4 * kh + (v % 4));
             return half_bits_to_float((uint16_t)h);
@@ -390,11 +391,7 @@ __device__ __forceinline__ void lds_tile(uint4 *ring_of_workgroup, const uint32_
                     }
                     if constexpr (F16 && PAIR) {
                         if (v % 2 == 0) {
-                            const uint32_t h0 = float_to_half_bits(x * sa * sw[bj]);
-                            const uint32_t h1 = float_to_half_bits(c[bi][bj][(v + 1) & 15] * sa_next * sw[bj]);
-                            const uint32_t give = odd ? h0 : h1, keep = odd ? h1 : h0;
-                            const uint32_t got = (uint32_t)__builtin_amdgcn_mov_dpp((int)give, 0xB1, 0xf, 0xf, true);
-                            const uint32_t word = odd ? (got | (keep << 16)) : (keep | (got << 16));
+                            const uint32_t word = swap_pair(half_pair(x * sa, c[bi][bj][(v + 1) & 15] * sa_next, sw[bj]), selector);
                             uint32_t *dst = reinterpret_cast<uint32_t *>(ch_pair + row * N + bj * 32);
                             if constexpr (NT) __builtin_nontemporal_store(word, dst);
                             else *dst = word;

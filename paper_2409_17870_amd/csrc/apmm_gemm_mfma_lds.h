@@ -157,6 +157,28 @@ __device__ __forceinline__ void lds_tile(uint4 *ring_of_workgroup, const uint32_
         if constexpr (h == 1) next_stage();
     };
     static_for<kLdsRing - 1>(request);
+    // Two workgroups to a compute unit (AF), a round of 512 and up to 0.44 of a second: the workgroup that holds the first wave slots goes ahead of the
+    // other at every issue, so that it ends early and the tile of the second round runs under the other one's k loop; two that run in step store together
+    // and leave that tile alone.  Time over that without, 640 / 704 / 768 tiles: 128 x 256 W2A4 fp16 0.96 - 0.97 / 0.96 - 0.98 / 0.97 - 0.99, both outputs
+    // 0.92 - 0.94 / 0.95 - 0.96 / 0.97 - 1.03, int32 0.89 / 0.94 / 0.95; W1A4 0.91 - 0.98 / 0.95 - 0.99 / 0.98 - 1.01 (K = 2048 - 8192; 2048 x 11008 x 4096 W2A4 both 62.5 ->
+    // 57.9 us).  864 and 960 tiles 0.99 - 1.02 and, both outputs, 1.06 - 1.18; 1376 1.02 - 1.05, 512 1.00 - 1.01.  128 x 128, 544 - 736 tiles, K = 2048 - 8192: W3A3 and
+    // W3A4 0.93 - 0.99, W4A4 0.96 - 1.00 (1.01 at K = 2048), W2A4 0.96 - 1.00, W1A3 0.96 - 1.01; K = 1024 0.99 - 1.04.
+    // Three workgroups (1- and 2-bit activations), 1.25 to 1.44 rounds of 768, in three steps: W2A2 1500 x 11008 (1032 tiles) 0.93 - 0.99; 946 tiles 0.98 - 1.01,
+    // with 4-bit weights 0.98 - 1.01.
+    if constexpr (KG == 1 && (AF || Q <= 2)) {
+        constexpr int kLeast = AF ? 512 : 960, kMost = AF ? 736 : 1104;
+        const int tiles = tiles_n * (int)tiles_m;
+        if (tiles > kLeast && tiles <= kMost && (WN == 4 || k_arg >= 2048)) {
+            constexpr int kHwId = 4, kSlotBits = 4;  // the register that says where a wave runs; its lowest field is the slot in the vector unit
+            const uint32_t slot = __builtin_amdgcn_s_getreg(kHwId | (kSlotBits - 1) << 11);
+            if constexpr (AF) {
+                if ((slot & 1) == 0) __builtin_amdgcn_s_setprio(1);
+            } else {
+                if (slot == 0) __builtin_amdgcn_s_setprio(2);
+                else if (slot == 1) __builtin_amdgcn_s_setprio(1);
+            }
+        }
+    }
 
     // For the end of the tile, requested now: code sums and scales of this lane's columns and rows.
     const int32_t *a_sum = reinterpret_cast<const int32_t *>(a_arg) + (uint64_t)(nrb_a * nkb) * (kRowBlock * SLOTS_A * 4);

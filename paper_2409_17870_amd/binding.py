@@ -33,6 +33,12 @@ class ApmmProblem(ctypes.Structure):
 
 
 _lib = None
+try:  # the marshalling of the calls below in C++ (csrc/apmm_call.cpp); without it they go through ctypes, with the same results
+    from . import _apmm_call as _call
+except ImportError:
+    _call = None
+_CALL_FUNCTIONS = ("apmm_packed_bytes", "apmm_packed_activation_bytes", "apmm_pack_weights", "apmm_pack_activations",
+                   "apmm_quantize_pack_activations", "apmm_gemm_ex", "apmm_gemm_from_codes")
 
 
 class ApmmError(RuntimeError):
@@ -89,6 +95,8 @@ def load():
     lib.apmm_version.restype = ci
     lib.apmm_version.argtypes = []
     _lib = lib
+    if _call is not None:
+        _call.set_library(tuple(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _CALL_FUNCTIONS), _check)
     return lib
 
 
@@ -99,9 +107,10 @@ def _check(status):
         raise ApmmError(status, text)
 
 
-# A single small product is as long as its call from Python, so the marshalling is kept short: addresses go to ctypes as
-# plain integers (the argument types convert them), the stream handle is read without building a Stream object, packed
-# sizes are computed once per shape.
+# A single small product is as long as its call from Python, so the plain cases of the calls that a decode step is made of (every tensor there, on
+# the GPU, nothing to allocate) are marshalled in C++ (csrc/apmm_call.cpp; the end of this file); what is not plain comes to the functions
+# here.  They are kept short as well: addresses go to ctypes as plain integers (the argument types convert them), the stream handle
+# is read without building a Stream object, packed sizes are computed once per shape.
 def _stream():
     if not torch.cuda.is_initialized():
         torch.cuda.init()
@@ -272,3 +281,8 @@ def apmm_time_next_gemm(start_event, stop_event):
     handles exist) to the kernel dispatch of the next large-tile MFMA GEMM call of this thread."""
     _check(load().apmm_time_next_gemm(ctypes.c_void_p(start_event.cuda_event), ctypes.c_void_p(stop_event.cuda_event)))
 
+
+if _call is not None:
+    for _name in ("apmm_pack_weights", "apmm_pack_activations", "apmm_quantize_pack_activations", "apmm_gemm", "apmm_gemm_from_codes"):
+        _call.set_general(_name, globals()[_name])
+        globals()[_name] = getattr(_call, _name)

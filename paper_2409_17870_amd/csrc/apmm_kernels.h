@@ -12,6 +12,20 @@ namespace apmm {
 // `field`: the field form of 3- and 4-bit activations instead of the group form (apmm_layout.h).
 hipError_t launch_pack(const uint8_t *codes, int64_t rows, int64_t K, int bits, bool field, uint32_t *packed,
                        hipStream_t stream);
+// Its rule for many rows: eight rows to a workgroup, code sums on the way, against a wave per packed tile and waves of their own for the sums (1 and 2
+// bits: against a wave per row).  Eights over the other, 3 to 8 bits: 2048 x 4096 0.87 - 0.90, 4096 x 6000 0.76, 5003 x 3001 0.80 - 0.83, 11008 x 4096 0.76 -
+// 0.91, 1500 x 5120 0.96, 2048 x 2500 0.96; fewer rows leave compute units without a workgroup, 512 x 4096 1.12 - 1.16, 1024 x 4096 1.03 - 1.07, 1024 x 11008 0.98 -
+// 1.02; short matrices have little to save, 2048 x 2048 and 4096 x 1024 0.99 - 1.02.  Six slots and more with long rows, where operand and output are beyond
+// the last-level cache: 5003 x 8192 0.98 - 1.08, 5003 x 11008 1.10, 4096 x 11008 0.95 - 1.02, 11008 x 11008 1.03 - 1.05 (11008 x 6000 0.94 - 0.98; four slots and fewer
+// 5003 x 11008 0.90, 11008 x 11008 1.00).  Two bits: 4096 x 4096 1.06, 4096 x 11008 0.98, 11008 x 4096 0.86, 11008 x 11008 0.76; one bit 11008 x 4096 1.06, 11008 x
+// 11008 0.86.
+inline bool pack_by_eights(int64_t rows, int64_t K, int bits, bool field)
+{
+    const int64_t codes = rows * K;
+    if (!field && bits <= 2) return rows >= 2048 && codes >= (bits == 2 ? 40000000 : 100000000);
+    const int slots = field ? 6 : bits;
+    return rows >= 1500 && codes >= 4500000 && !(slots >= 6 && K > 7000 && codes > 40000000);
+}
 // Paper Sec. 3.1 + 4.1: per-row symmetric quantisation of binary16 features fused with the packing.
 hipError_t launch_quantize_pack(const uint16_t *x, int64_t rows, int64_t K, int bits, bool field, uint32_t *packed,
                                 uint16_t *scale, hipStream_t stream);

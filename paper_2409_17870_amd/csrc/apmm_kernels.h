@@ -47,6 +47,16 @@ inline bool quantize_rows_by_four(int64_t rows, int64_t K)
     // groups to a lane, 0.92 - 1.00 with three and four; 0.92 - 1.02 at 500 to 540.
     return rows * quantize_groups(K) >= (lane_groups == 2 ? 500 : 450) * lane_groups * kQuantLanes;
 }
+// Waves of a row in the kernel of one row to some waves: a group of 32 elements for every lane, as far as the row goes.  Beyond 8192 elements eight over
+// four: one to 203 rows 0.88 - 0.95 (16 x 13824 four bits 4.11 -> 3.81 us, 16 x 11008 two bits 4.16 -> 3.65; 16 x 60000 0.61), 512 and 1024 rows 0.92 - 1.00, more rows
+// 0.92 - 0.99 where most lanes have a group (11008, 16384 and beyond), 1.02 - 1.24 where they have not (9000).  Beyond 16384 sixteen over eight: up to 100
+// rows 0.85 - 0.99, 512 and 1024 rows 0.93 - 1.4.
+inline int quantize_waves(int64_t rows, int64_t nkb)
+{
+    if (nkb <= 64) return nkb <= 16 ? 1 : nkb <= 32 ? 2 : 4;
+    if (nkb > 128 && rows <= 256) return 16;
+    return nkb < 84 && rows > 1024 ? 4 : 8;
+}
 // Five workgroups to a compute unit instead of the seven or eight that its registers leave room for, in the kernel of one row to some waves,
 // from 17 MB of packed output on: its stores are pieces of lines that other waves complete, and more rows under way push them out of L2 before.
 // Eight over five, eight bits 4096 x 4608 / 4096 x 5632 / 4096 x 8192 / 2048 x 11008 / 2048 x 13824 / 4096 x 20000 0.97 / 1.08 / 1.13 / 1.01 / 1.04 / 1.14,

@@ -599,14 +599,12 @@ __device__ __forceinline__ void fill_fields(uint32_t fill, uint32_t &sum, uint32
     sum += 32u * fill;
 }
 
+constexpr int quantize_threads(int waves) { return waves > kThreads / 64 ? 64 * waves : kThreads; }
 template <int WAVES, bool WHOLE, bool FIELD>
-__global__ __launch_bounds__(kThreads) void quantize_pack_kernel(const uint16_t *__restrict__ x, int64_t rows,
-                                                                 int64_t K, int bits,
-                                                                 uint32_t *__restrict__ packed,
-                                                                 uint16_t *__restrict__ scale_out, int64_t rows_p,
-                                                                 int64_t nkb)
+__device__ __forceinline__ void quantize_rows(const uint16_t *__restrict__ x, int64_t rows, int64_t K, int bits, uint32_t *__restrict__ packed,
+                                              uint16_t *__restrict__ scale_out, int64_t rows_p, int64_t nkb)
 {
-    constexpr int T = 64 * WAVES, ROWS = kThreads / T, C = 8 / ROWS;  // threads of a row, rows of a workgroup, workgroups of eight rows
+    constexpr int THREADS = quantize_threads(WAVES), T = 64 * WAVES, ROWS = THREADS / T, C = 8 / ROWS;  // threads of a row, rows of a workgroup, workgroups of eight rows
     const int tid = threadIdx.x % T, sub = wave_of_workgroup() / WAVES;
     const int xcd = blockIdx.x % 8, turn = blockIdx.x / 8;  // workgroups go to the XCDs in turn
     const int64_t row = (((int64_t)(turn / C) * 8 + xcd) * C + turn % C) * ROWS + sub;
@@ -633,7 +631,7 @@ __global__ __launch_bounds__(kThreads) void quantize_pack_kernel(const uint16_t 
     }
     uint32_t mbits = m2[0] > m2[1] ? m2[0] : m2[1];
     mbits = max_over_wave(mbits);
-    __shared__ uint32_t joint[2][kThreads / 64];
+    __shared__ uint32_t joint[2][THREADS / 64];
     if constexpr (WAVES > 1) {
         if ((threadIdx.x & 63) == 0) joint[0][threadIdx.x / 64] = mbits;
         __syncthreads();
@@ -717,6 +715,21 @@ __global__ __launch_bounds__(kThreads) void quantize_pack_kernel(const uint16_t 
         for (int w = 0; w < WAVES; ++w) sum += joint[1][sub * WAVES + w];
     }
     if (tid == 0) packed[row_sum_word(rows_p, nkb, FIELD ? 6 : bits) + row] = sum;
+}
+
+template <int WAVES, bool WHOLE, bool FIELD>
+__global__ __launch_bounds__(kThreads) void quantize_pack_kernel(const uint16_t *__restrict__ x, int64_t rows, int64_t K, int bits,
+                                                                 uint32_t *__restrict__ packed, uint16_t *__restrict__ scale_out, int64_t rows_p, int64_t nkb)
+{
+    quantize_rows<WAVES, WHOLE, FIELD>(x, rows, K, bits, packed, scale_out, rows_p, nkb);
+}
+// Rows beyond 8192 elements, eight or sixteen waves to a row: a lane's groups, one behind the other, were what a few rows took their time for (rule and
+// figures: quantize_waves).
+template <int WAVES, bool WHOLE, bool FIELD>
+__global__ __launch_bounds__(64 * WAVES) void quantize_long_kernel(const uint16_t *__restrict__ x, int64_t rows, int64_t K, int bits,
+                                                                   uint32_t *__restrict__ packed, uint16_t *__restrict__ scale_out, int64_t rows_p, int64_t nkb)
+{
+    quantize_rows<WAVES, WHOLE, FIELD>(x, rows, K, bits, packed, scale_out, rows_p, nkb);
 }
 
 // The same for the field form of many rows: the words of four rows meet in LDS and are written in runs of 64 bytes (a slot of four rows),
@@ -958,21 +971,24 @@ hipError_t launch_quantize_pack(const uint16_t *x, int64_t rows, int64_t K, int 
         hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kQuantThreads), lds, stream, x, rows, K, bits, packed, scale, rows_p, nkb);
         return hipGetLastError();
     }
-    // waves per row: a group of 32 elements for every lane, as far as the row goes
-    const int waves = nkb <= 16 ? 1 : nkb <= 32 ? 2 : 4;
-    const int64_t blocks = (rows_p + 63) / 64 * 64 * waves / (kThreads / 64);  // eight rows for each of the eight XCDs
+    const int waves = quantize_waves(rows, nkb), threads = quantize_threads(waves);
+    const int64_t blocks = (rows_p + 63) / 64 * 64 * waves / (threads / 64);  // eight rows for each of the eight XCDs
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     decltype(&quantize_pack_kernel<1, true, true>) kernel;
     if (field)
         kernel = waves == 1 ? (whole ? quantize_pack_kernel<1, true, true> : quantize_pack_kernel<1, false, true>)
                : waves == 2 ? (whole ? quantize_pack_kernel<2, true, true> : quantize_pack_kernel<2, false, true>)
-                            : (whole ? quantize_pack_kernel<4, true, true> : quantize_pack_kernel<4, false, true>);
+               : waves == 4 ? (whole ? quantize_pack_kernel<4, true, true> : quantize_pack_kernel<4, false, true>)
+               : waves == 8 ? (whole ? quantize_long_kernel<8, true, true> : quantize_long_kernel<8, false, true>)
+                            : (whole ? quantize_long_kernel<16, true, true> : quantize_long_kernel<16, false, true>);
     else
         kernel = waves == 1 ? (whole ? quantize_pack_kernel<1, true, false> : quantize_pack_kernel<1, false, false>)
                : waves == 2 ? (whole ? quantize_pack_kernel<2, true, false> : quantize_pack_kernel<2, false, false>)
-                            : (whole ? quantize_pack_kernel<4, true, false> : quantize_pack_kernel<4, false, false>);
+               : waves == 4 ? (whole ? quantize_pack_kernel<4, true, false> : quantize_pack_kernel<4, false, false>)
+               : waves == 8 ? (whole ? quantize_long_kernel<8, true, false> : quantize_long_kernel<8, false, false>)
+                            : (whole ? quantize_long_kernel<16, true, false> : quantize_long_kernel<16, false, false>);
     const size_t lds = quantize_few_workgroups(rows, K, bits, field) ? 32000 : 0;  // not read: it leaves room for five workgroups
-    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kThreads), lds, stream, x, rows, K, bits, packed, scale, rows_p, nkb);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3((unsigned)threads), lds, stream, x, rows, K, bits, packed, scale, rows_p, nkb);
     return hipGetLastError();
 }
 

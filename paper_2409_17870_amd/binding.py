@@ -1,4 +1,4 @@
-"""ctypes binding of libapmm.so (C ABI in include/apmm.h).
+"""Binding of libapmm.so (C ABI in include/apmm.h): ctypes, and csrc/apmm_call.cpp for the plain cases of the calls made most often.
 
 Argument marshalling only: every step of the path (pack, GEMM, recovery, epilogue) runs
 in the library's HIP kernels.  PyTorch supplies device memory and the stream.  There is

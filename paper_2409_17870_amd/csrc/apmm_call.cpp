@@ -1,7 +1,8 @@
 // The calls of the Python binding that a decode step or a small product makes, without an interpreter between the tensors and the C ABI.
 //
 // A single product from Python was bound by its marshalling: attribute look-ups on tensors, checks and the conversion of thirteen
-// arguments took 2 to 3 us of a call whose kernel takes 2 to 5.  Here an argument is looked at where it lies, in the tensor's own structure.
+// arguments took 2 to 3 us of a call whose kernel takes 2 to 5.  Here an argument is looked at where it lies, in the tensor's own structure: W1A2 16 x 256 x 512
+// (pack + product) 10.9 -> 8.2 us, W2A2 1 x 11008 x 4096 from codes 6.2 -> 4.6, of which the kernel takes 4.4.
 //
 // Every function takes the arguments of the Python function of the same name in binding.py and has that function as its `general` form: whatever
 // is not the plain case (a missing output that has to be allocated, anything that is not a torch.Tensor, an integer of another type, a check
@@ -123,7 +124,11 @@ bool called(Call call)
 {
     apmm_status status;
     Py_BEGIN_ALLOW_THREADS
-    status = call();
+    try {
+        status = call();
+    } catch (...) {  // nothing may pass here without the interpreter's lock
+        status = APMM_ERR_HIP;
+    }
     Py_END_ALLOW_THREADS
     if (status == APMM_OK) return true;
     PyObject *r = PyObject_CallFunction(check, "i", (int)status);

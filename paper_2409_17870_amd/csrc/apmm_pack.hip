@@ -10,7 +10,7 @@
 // 2.2 us, 64 rows 2.6 -> 2.3 us).
 //
 // pack_kernel works tile by tile (one wave per 32 rows x 128 k, whole cache lines written by one instruction)
-// with separate waves for the code sums; pack_rows_kernel and the fused quantise + pack kernel work row by row
+// with separate waves for the code sums, pack_eights_kernel by eight rows with the sums on the way; pack_rows_kernel and the fused quantise + pack kernel work row by row
 // (one wave or a few per row; the quantiser has to see the whole row for its scale first).  No atomics.  The work is HBM bound: 1 byte
 // read and bits/8 bytes written per element.
 #include <hip/hip_fp16.h>

@@ -405,12 +405,17 @@ __global__ __launch_bounds__(256) void gemm_mfma_direct_kernel(const uint32_t *a
                     if constexpr (F16 && !PAIR) ch[row * g.N + bj * 32] = float_to_half_bits(c * sa * sw[bj]);
                     if constexpr (F16 && PAIR) {
                         if (v % 2 == 0) {  // folds once the loop is unrolled
-                            const uint32_t h0 = float_to_half_bits(c * sa * sw[bj]);
-                            const uint32_t h1 = float_to_half_bits(acc[ROWL + bi][bj][(v + 1) & 15] * sa_next * sw[bj]);
-                            const uint32_t give = odd ? h0 : h1, keep = odd ? h1 : h0;
-                            // quad_perm [1, 0, 3, 2]: the value of the other lane of the pair
-                            const uint32_t got = (uint32_t)__builtin_amdgcn_mov_dpp((int)give, 0xB1, 0xf, 0xf, true);
-                            const uint32_t word = odd ? (got | (keep << 16)) : (keep | (got << 16));
+                            uint32_t word;
+                            if constexpr (WM * WN < 16) {
+                                word = swap_pair(half_pair(c * sa, acc[ROWL + bi][bj][(v + 1) & 15] * sa_next, sw[bj]), swap_pair_selector(odd));
+                            } else {  // (256 x 256: spills with it)
+                                const uint32_t h0 = float_to_half_bits(c * sa * sw[bj]);
+                                const uint32_t h1 = float_to_half_bits(acc[ROWL + bi][bj][(v + 1) & 15] * sa_next * sw[bj]);
+                                const uint32_t give = odd ? h0 : h1, keep = odd ? h1 : h0;
+                                // quad_perm [1, 0, 3, 2]: the value of the other lane of the pair
+                                const uint32_t got = (uint32_t)__builtin_amdgcn_mov_dpp((int)give, 0xB1, 0xf, 0xf, true);
+                                word = odd ? (got | (keep << 16)) : (keep | (got << 16));
+                            }
                             uint32_t *dst = reinterpret_cast<uint32_t *>(ch_pair + row * g.N + bj * 32);
                             if constexpr (NT) __builtin_nontemporal_store(word, dst);
                             else *dst = word;

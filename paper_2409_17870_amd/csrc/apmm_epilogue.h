@@ -24,7 +24,8 @@ __device__ __forceinline__ uint16_t float_to_half_bits(float x)
 // them products with the token scales) where selects, masks and shifts took twelve, and that much less code for the K-split kernels to
 // fetch at their end: W2A4 512 x 5120 x 5120 12.42 -> 12.21 us, 512 x 5120 x 13824 23.3 -> 22.6, W8A8 512 x 4096 x 4096 15.8 -> 15.5, 2048 x 11008 x 2048 67.8 ->
 // 65.9, W2A2 1024 x 11008 x 4096 24.1 -> 23.7.  (By hand: left to itself the compiler makes four products and a conversion of two, which rounds once
-// more than the single results' mixed multiplication.  Not in the direct tiles: the 256 x 256 ones spill with it.)
+// more than the single results' mixed multiplication.)  The direct tiles, but for the 256 x 256 ones, which spill with it: W2A2 2048 x 4096 x 2048 12.4 ->
+// 11.9, 512 x 13824 x 5120 18.6 -> 18.1, W2A4 1024 x 4096 x 1024 7.9 -> 7.7, W1A4 1024 x 4096 x 512 6.3 -> 6.1.
 __device__ __forceinline__ uint32_t half_pair(float x0, float x1, float y)
 {
     uint32_t h;

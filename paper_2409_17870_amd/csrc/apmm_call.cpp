@@ -17,6 +17,7 @@
 #include <cstring>
 
 #include "../../include/apmm.h"
+#include "apmm_call_guard.h"
 
 namespace {
 
@@ -124,11 +125,7 @@ bool called(Call call)
 {
     apmm_status status;
     Py_BEGIN_ALLOW_THREADS
-    try {
-        status = call();
-    } catch (...) {  // nothing may pass here without the interpreter's lock
-        status = APMM_ERR_HIP;
-    }
+    status = end_exceptions(call, [] { return APMM_ERR_HIP; });  // nothing may pass here without the interpreter's lock
     Py_END_ALLOW_THREADS
     if (status == APMM_OK) return true;
     PyObject *r = PyObject_CallFunction(check, "i", (int)status);
@@ -231,12 +228,12 @@ PyObject *entry(PyObject *, PyObject *const *args, Py_ssize_t nargs, PyObject *n
 {
     const Signature &s = signatures[F];
     PyObject *v[kMaxArgs], *result = nullptr;
-    int done = 0;
-    try {
-        if (place(s, args, nargs, names, v)) done = F <= kPackActivations ? pack(F, v, result) : F == kQuantize ? quantize(v, result) : F == kGemm ? gemm(v, result) : from_codes(v, result);
-    } catch (...) {
-        done = 0;  // (torch's own refusal of a tensor: the general form meets the same one and reports it)
-    }
+    const int done = end_exceptions(
+        [&] {
+            if (!place(s, args, nargs, names, v)) return 0;
+            return F <= kPackActivations ? pack(F, v, result) : F == kQuantize ? quantize(v, result) : F == kGemm ? gemm(v, result) : from_codes(v, result);
+        },
+        [] { return 0; });  // (torch's own refusal of a tensor: the general form meets the same one and reports it)
     if (done > 0) return result;
     return done < 0 ? nullptr : general(s, args, nargs, names);
 }

@@ -37,6 +37,7 @@ PyMODINIT_FUNC PyInit_guarded() { return PyModule_Create(&module); }
 """
 
 LOAD = """
+import importlib.machinery, importlib.util
 loader = importlib.machinery.ExtensionFileLoader("guarded", %r)
 guarded = importlib.util.module_from_spec(importlib.util.spec_from_loader("guarded", loader))
 """

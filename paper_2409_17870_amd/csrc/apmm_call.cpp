@@ -119,22 +119,8 @@ PyObject *general(const Signature &s, PyObject *const *args, Py_ssize_t nargs, P
     return PyObject_Vectorcall(s.general, args, (size_t)nargs, names);
 }
 
-// The call itself and what follows from its status: true if it went well.
 template <class Call>
-bool called(Call call)
-{
-    apmm_status status;
-    Py_BEGIN_ALLOW_THREADS
-    status = end_exceptions(call, [] { return APMM_ERR_HIP; });  // nothing may pass here without the interpreter's lock
-    Py_END_ALLOW_THREADS
-    if (status == APMM_OK) return true;
-    PyObject *r = PyObject_CallFunction(check, "i", (int)status);
-    if (r) {
-        Py_DECREF(r);
-        PyErr_SetString(PyExc_RuntimeError, "apmm: a call failed");
-    }
-    return false;
-}
+bool called(Call call) { return call_and_check(check, call); }
 
 PyObject *pair(PyObject *a, PyObject *b)
 {

@@ -1,6 +1,8 @@
 // Where C++ exceptions end in the calls of the Python binding (apmm_call.cpp).
 #pragma once
 
+#include <Python.h>
+
 #include <cxxabi.h>
 
 // What body returns, or what failed returns if body throws.  Handlers of every exception stand here only, because one kind has to go on: a
@@ -16,4 +18,27 @@ auto end_exceptions(Body body, Failed failed) -> decltype(body())
     } catch (...) {
         return failed();
     }
+}
+
+// The call itself, without the interpreter's lock, and what follows from its status: true if it is 0, else check(status) has set an error.  An exception
+// of the call has no status and no text in the library, so it is reported here and not through check.
+template <class Call>
+bool call_and_check(PyObject *check, Call call)
+{
+    constexpr int kThrown = -1;
+    int status;
+    Py_BEGIN_ALLOW_THREADS
+    status = end_exceptions([&] { return (int)call(); }, [] { return (int)kThrown; });  // nothing may pass here without the lock
+    Py_END_ALLOW_THREADS
+    if (status == 0) return true;
+    if (status == kThrown) {
+        PyErr_SetString(PyExc_RuntimeError, "apmm: a C++ exception ended the call");
+        return false;
+    }
+    PyObject *r = PyObject_CallFunction(check, "i", status);
+    if (r) {
+        Py_DECREF(r);
+        PyErr_SetString(PyExc_RuntimeError, "apmm: a call failed");
+    }
+    return false;
 }

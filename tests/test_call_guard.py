@@ -31,7 +31,16 @@ static PyObject *call(PyObject *, PyObject *throws)
         [] { return 0; });
     return PyLong_FromLong(r);
 }
-static PyMethodDef methods[] = {{"call", call, METH_O, nullptr}, {nullptr, nullptr, 0, nullptr}};
+// checked(check, status), a negative one thrown
+static PyObject *checked(PyObject *, PyObject *args)
+{
+    PyObject *check;
+    int status;
+    if (!PyArg_ParseTuple(args, "Oi", &check, &status)) return nullptr;
+    if (!call_and_check(check, [&] { return status < 0 ? throw std::runtime_error("") : status; })) return nullptr;
+    Py_RETURN_TRUE;
+}
+static PyMethodDef methods[] = {{"call", call, METH_O, nullptr}, {"checked", checked, METH_VARARGS, nullptr}, {nullptr, nullptr, 0, nullptr}};
 static PyModuleDef module = {PyModuleDef_HEAD_INIT, "guarded", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 PyMODINIT_FUNC PyInit_guarded() { return PyModule_Create(&module); }
 """
@@ -60,6 +69,27 @@ def test_exceptions_end(library):
     assert space["guarded"].call(False) == 1 and space["guarded"].call(True) == 0
 
 
+def test_status_and_exception_of_a_call(library):
+    space = {}
+    exec(LOAD % library, space)
+    checked, seen = space["guarded"].checked, []
+
+    def check(status):
+        seen.append(status)
+        if status == 3:
+            raise KeyError(status)
+
+    assert checked(check, 0) is True and seen == []
+    with pytest.raises(KeyError):
+        checked(check, 3)
+    with pytest.raises(RuntimeError, match="a call failed"):
+        checked(check, 5)
+    assert seen == [3, 5]
+    with pytest.raises(RuntimeError, match="exception"):  # its own text: the library's last error belongs to another call
+        checked(check, -7)
+    assert seen == [3, 5]
+
+
 def test_daemon_threads_at_exit(library):
     program = LOAD % library + """
 import threading, time
@@ -77,4 +107,4 @@ time.sleep(0.2)
 
 def test_no_other_handler():
     source = open(os.path.join(CSRC, "apmm_call.cpp")).read()
-    assert "end_exceptions(" in source and "catch" not in source
+    assert "end_exceptions(" in source and "call_and_check(" in source and "catch" not in source

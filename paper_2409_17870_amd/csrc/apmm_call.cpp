@@ -6,10 +6,11 @@
 //
 // Every function takes the arguments of the Python function of the same name in binding.py and has that function as its `general` form: whatever
 // is not the plain case (a missing output that has to be allocated, anything that is not a torch.Tensor, an integer of another type, a check
-// that fails, an unknown keyword, a torch-function mode, the library not loaded yet) is handed to it with the very arguments, so that
+// that fails, an unknown keyword, a torch-function mode, a process forked from one that uses the GPU, the library not loaded yet) is handed to it with the very arguments, so that
 // results and errors are its own.  A status other than 0 goes to binding.py's _check, on the same thread.  As through ctypes, the interpreter's lock is
 // released around the call.
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/utils/device_lazy_init.h>
 
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <c10/hip/HIPStream.h>
@@ -54,7 +55,7 @@ Signature signatures[kFunctions] = {
 // Arguments by place, null where not given; false: not the plain case.
 bool place(const Signature &s, PyObject *const *args, Py_ssize_t nargs, PyObject *names, PyObject **out)
 {
-    if (!loaded || nargs > s.count || at::impl::torch_function_mode_enabled()) return false;
+    if (!loaded || nargs > s.count || at::impl::torch_function_mode_enabled() || torch::utils::is_device_in_bad_fork(at::kCUDA)) return false;
     for (int i = 0; i < s.count; ++i) out[i] = i < nargs ? args[i] : nullptr;
     const Py_ssize_t named = names ? PyTuple_GET_SIZE(names) : 0;
     for (Py_ssize_t i = 0; i < named; ++i) {

@@ -1,6 +1,7 @@
 """The binding's calls in C++ (csrc/apmm_call.cpp) against the Python functions that they stand for: the same results and the same errors
 for every way to give the arguments, plain or not."""
 import inspect
+import os
 
 import pytest
 import torch
@@ -115,3 +116,29 @@ def test_results_and_errors_alike():
                 assert type(s) is type(t) and s.dtype == t.dtype and torch.equal(s, t), name
             else:
                 assert s == t, (name, s, t)
+
+
+@pytest.mark.gpu
+def test_forked_process_refused_alike():
+    """A process forked from one that uses the GPU must not use it: torch's own refusal comes before anything is launched there."""
+    dev = torch.device("cuda:0")
+    a, w = (torch.ones((n, 64), dtype=torch.uint8, device=dev) for n in (3, 40))
+    x, sa = torch.ones((3, 64), dtype=torch.float16, device=dev), torch.ones(3, dtype=torch.float16, device=dev)
+    ap, wp = binding.apmm_pack_activations(a, 2), binding.apmm_pack_weights(w, 2)
+    c = torch.zeros((3, 40), dtype=torch.int32, device=dev)
+    calls = [("apmm_pack_weights", (w, 2, wp), {}), ("apmm_pack_activations", (a, 2, ap), {}), ("apmm_quantize_pack_activations", (x, 2, ap, sa), {}),
+             ("apmm_gemm", (3, 40, 64, 2, 2, ap, wp), dict(c_i32=c)), ("apmm_gemm_from_codes", (a, 40, 2, 2, wp), dict(c_i32=c))]
+    torch.cuda.synchronize()
+    end, begin = os.pipe()
+    child = os.fork()
+    if child == 0:  # nothing here touches the GPU
+        try:
+            outcomes = [outcome(getattr(binding, name), *args, **kw) for name, args, kw in calls]
+            os.write(begin, "\n".join("%s %s" % (o[0], str(o[1])[:30]) if isinstance(o[0], str) else "launched" for o in outcomes).encode())
+        finally:
+            os._exit(0)
+    os.close(begin)
+    with os.fdopen(end) as f:
+        lines = f.read().split("\n")
+    os.waitpid(child, 0)
+    assert lines == ["RuntimeError Cannot re-initialize CUDA in f"] * len(calls)

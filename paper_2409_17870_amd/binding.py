@@ -7,6 +7,7 @@ no fallback: if the library is missing or a call fails, an exception is raised.
 import ctypes
 import functools
 import os
+import warnings
 
 import torch  # imported before the library so that both share one HIP runtime (same soname)
 
@@ -35,8 +36,9 @@ class ApmmProblem(ctypes.Structure):
 _lib = None
 try:  # the marshalling of the calls below in C++ (csrc/apmm_call.cpp); without it they go through ctypes, with the same results
     from . import _apmm_call as _call
-except ImportError:
+except ImportError as _reason:  # not built, or built for another torch or Python
     _call = None
+    warnings.warn("the calls' C++ marshalling is not used, each takes 2 to 3 us longer: %s" % _reason, RuntimeWarning)
 _CALL_FUNCTIONS = ("apmm_packed_bytes", "apmm_packed_activation_bytes", "apmm_pack_weights", "apmm_pack_activations",
                    "apmm_quantize_pack_activations", "apmm_gemm_ex", "apmm_gemm_from_codes")
 

@@ -15,7 +15,8 @@ def general(name):
     """The Python function behind a call: binding.py once more, without the C++ module."""
     spec = inspect.getsource(binding).replace("from . import _apmm_call as _call", "raise ImportError")
     space = {"__name__": "binding_general", "__file__": binding.__file__}
-    exec(compile(spec, binding.__file__, "exec"), space)
+    with pytest.warns(RuntimeWarning, match="C\\+\\+ marshalling is not used"):  # a program without it is told
+        exec(compile(spec, binding.__file__, "exec"), space)
     return space[name]
 
 

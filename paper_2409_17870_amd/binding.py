@@ -284,7 +284,9 @@ def apmm_time_next_gemm(start_event, stop_event):
     _check(load().apmm_time_next_gemm(ctypes.c_void_p(start_event.cuda_event), ctypes.c_void_p(stop_event.cuda_event)))
 
 
+_general = {}  # the Python functions behind the C++ calls
 if _call is not None:
     for _name in ("apmm_pack_weights", "apmm_pack_activations", "apmm_quantize_pack_activations", "apmm_gemm", "apmm_gemm_from_codes"):
-        _call.set_general(_name, globals()[_name])
+        _general[_name] = globals()[_name]
+        _call.set_general(_name, _general[_name])
         globals()[_name] = getattr(_call, _name)

@@ -49,6 +49,9 @@ def test_refused_alike(name, args, kw):
     assert isinstance(got, tuple) and got == want
 
 
+PLAIN, GENERAL = 0, 1  # marshalled in C++, or handed to the Python function once
+
+
 @pytest.mark.gpu
 def test_results_and_errors_alike():
     dev = torch.device("cuda:0")
@@ -71,45 +74,56 @@ def test_results_and_errors_alike():
         pass
 
     calls = [
-        ("apmm_pack_weights", lambda: ((w, q), dict(out=empty(nw)))),
-        ("apmm_pack_weights", lambda: ((w, q, empty(nw)), {})),
-        ("apmm_pack_weights", lambda: ((w,), dict(q=q))),
-        ("apmm_pack_weights", lambda: ((w, q), dict(out=empty(nw - 1)))),
-        ("apmm_pack_weights", lambda: ((w, 9), dict(out=empty(nw)))),
-        ("apmm_pack_weights", lambda: ((w.t(), q), dict(out=empty(nw)))),
-        ("apmm_pack_weights", lambda: ((w.int(), q), dict(out=empty(nw)))),
-        ("apmm_pack_activations", lambda: ((a, p), dict(out=empty(na + 64)[16:]))),
-        ("apmm_pack_activations", lambda: ((a, p), dict(out=empty(na + 64)[8:]))),
-        ("apmm_pack_activations", lambda: ((a.as_subclass(Sub), p), dict(out=empty(na)))),
-        ("apmm_quantize_pack_activations", lambda: ((x, p), dict(out=empty(na), scale_out=torch.zeros(M, dtype=torch.float16, device=dev)))),
-        ("apmm_quantize_pack_activations", lambda: ((x, p, empty(na), torch.zeros(M - 1, dtype=torch.float16, device=dev)), {})),
-        ("apmm_quantize_pack_activations", lambda: ((x, p), {})),
-        ("apmm_gemm", lambda: ((M, N, K, p, q, ap, wp), dict(c_i32=c32()))),
-        ("apmm_gemm", lambda: ((M, N, K, p, q, ap, wp), dict(want_i32=False, want_f16=True, w_scale=sw, a_scale=sa, c_f16=c16()))),
-        ("apmm_gemm", lambda: ((M, N, K, p, q, ap, wp, True, True, sw, sa, c32(), c16()), {})),
-        ("apmm_gemm", lambda: ((M, N, K, p, q, ap, wp), {})),
-        ("apmm_gemm", lambda: ((M, N, K, p, q, ap, wp), dict(want_i32=False))),
-        ("apmm_gemm", lambda: ((M, N, K, p, q, ap, wp), dict(c_i32=c32(), w_scale=sw[:-1]))),
-        ("apmm_gemm", lambda: ((M, N, K, p, q, ap, wp), dict(c_i32=c32(), a_scale=sa.float()))),
-        ("apmm_gemm", lambda: ((M, N, K, p, q, ap[1:], wp), dict(c_i32=c32()))),
-        ("apmm_gemm", lambda: ((M, N, 1 << 40, p, q, ap, wp), dict(c_i32=c32()))),
-        ("apmm_gemm", lambda: ((0, N, K, p, q, ap, wp), dict(c_i32=c32()))),
-        ("apmm_gemm", lambda: ((M, N, K, p, q, ap, wp), dict(c_i32=c32(), algo=binding.ALGO_DECODE))),
-        ("apmm_gemm_from_codes", lambda: ((a, N, p, q, wp), dict(c_i32=c32(), workspace=empty(na)))),
-        ("apmm_gemm_from_codes", lambda: ((a, N, p, q, wp), dict(want_i32=False, want_f16=True, c_f16=c16(), w_scale=sw, a_scale=sa))),
-        ("apmm_gemm_from_codes", lambda: ((a, N, p, q, wp), {})),
-        ("apmm_gemm_from_codes", lambda: ((a, N, p, 9, wp), dict(c_i32=c32()))),
+        ("apmm_pack_weights", PLAIN, lambda: ((w, q), dict(out=empty(nw)))),
+        ("apmm_pack_weights", PLAIN, lambda: ((w, q, empty(nw)), {})),
+        ("apmm_pack_weights", GENERAL, lambda: ((w,), dict(q=q))),
+        ("apmm_pack_weights", GENERAL, lambda: ((w, q), dict(out=empty(nw - 1)))),
+        ("apmm_pack_weights", GENERAL, lambda: ((w, 9), dict(out=empty(nw)))),
+        ("apmm_pack_weights", GENERAL, lambda: ((w.t(), q), dict(out=empty(nw)))),
+        ("apmm_pack_weights", GENERAL, lambda: ((w.int(), q), dict(out=empty(nw)))),
+        ("apmm_pack_activations", PLAIN, lambda: ((a, p), dict(out=empty(na + 64)[16:]))),
+        ("apmm_pack_activations", PLAIN, lambda: ((a, p), dict(out=empty(na + 64)[8:]))),
+        ("apmm_pack_activations", GENERAL, lambda: ((a.as_subclass(Sub), p), dict(out=empty(na)))),
+        ("apmm_quantize_pack_activations", PLAIN, lambda: ((x, p), dict(out=empty(na), scale_out=torch.zeros(M, dtype=torch.float16, device=dev)))),
+        ("apmm_quantize_pack_activations", GENERAL, lambda: ((x, p, empty(na), torch.zeros(M - 1, dtype=torch.float16, device=dev)), {})),
+        ("apmm_quantize_pack_activations", GENERAL, lambda: ((x, p), {})),
+        ("apmm_gemm", PLAIN, lambda: ((M, N, K, p, q, ap, wp), dict(c_i32=c32()))),
+        ("apmm_gemm", PLAIN, lambda: ((M, N, K, p, q, ap, wp), dict(want_i32=False, want_f16=True, w_scale=sw, a_scale=sa, c_f16=c16()))),
+        ("apmm_gemm", PLAIN, lambda: ((M, N, K, p, q, ap, wp, True, True, sw, sa, c32(), c16()), {})),
+        ("apmm_gemm", GENERAL, lambda: ((M, N, K, p, q, ap, wp), {})),
+        ("apmm_gemm", PLAIN, lambda: ((M, N, K, p, q, ap, wp), dict(want_i32=False))),
+        ("apmm_gemm", GENERAL, lambda: ((M, N, K, p, q, ap, wp), dict(c_i32=c32(), w_scale=sw[:-1]))),
+        ("apmm_gemm", GENERAL, lambda: ((M, N, K, p, q, ap, wp), dict(c_i32=c32(), a_scale=sa.float()))),
+        ("apmm_gemm", PLAIN, lambda: ((M, N, K, p, q, ap[1:], wp), dict(c_i32=c32()))),
+        ("apmm_gemm", PLAIN, lambda: ((M, N, 1 << 40, p, q, ap, wp), dict(c_i32=c32()))),
+        ("apmm_gemm", PLAIN, lambda: ((0, N, K, p, q, ap, wp), dict(c_i32=c32()))),
+        ("apmm_gemm", GENERAL, lambda: ((M, N, K, p, q, ap, wp), dict(c_i32=c32(), algo=binding.ALGO_DECODE))),
+        ("apmm_gemm_from_codes", PLAIN, lambda: ((a, N, p, q, wp), dict(c_i32=c32(), workspace=empty(na)))),
+        ("apmm_gemm_from_codes", PLAIN, lambda: ((a, N, p, q, wp), dict(want_i32=False, want_f16=True, c_f16=c16(), w_scale=sw, a_scale=sa))),
+        ("apmm_gemm_from_codes", GENERAL, lambda: ((a, N, p, q, wp), {})),
+        ("apmm_gemm_from_codes", PLAIN, lambda: ((a, N, p, 9, wp), dict(c_i32=c32()))),
     ]
     stream = torch.cuda.Stream()
-    for name, make in calls:
+    for name, route, make in calls:
         results = []
-        for fn in (getattr(binding, name), general_of[name]):
-            args, kw = make()
-            stream.wait_stream(torch.cuda.current_stream())
-            with torch.cuda.stream(stream):
-                r = outcome(fn, *args, **kw)
-            stream.synchronize()
-            results.append(r if isinstance(r, tuple) else (r,))
+        asked = []  # times that the C++ call handed over to the Python function
+
+        def handed_over(*args, **kw):
+            asked.append(name)
+            return general_of[name](*args, **kw)
+
+        binding._call.set_general(name, handed_over)
+        try:
+            for fn in (getattr(binding, name), general_of[name]):
+                args, kw = make()
+                stream.wait_stream(torch.cuda.current_stream())
+                with torch.cuda.stream(stream):
+                    r = outcome(fn, *args, **kw)
+                stream.synchronize()
+                results.append(r if isinstance(r, tuple) else (r,))
+        finally:
+            binding._call.set_general(name, binding._general[name])
+        assert len(asked) == route, (name, asked)
         got, want = results
         assert len(got) == len(want), (name, got, want)
         for s, t in zip(got, want):

@@ -1,5 +1,5 @@
 """The launchers' rules, host functions of sizes, addresses and widths, compiled for the host alone and asked on both sides of their
-lines: which calls store their inner tiles streaming, which quantise four rows to a workgroup and which with few workgroups to a compute unit, and which take the direct tiles or the register form of the 128 x 128 K split where the
+lines: which calls store their inner tiles streaming, which quantise four rows to a workgroup, with how many waves to a row and which with few workgroups to a compute unit, and which take the direct tiles or the register form of the 128 x 128 K split where the
 kernels that share operands through LDS are slower."""
 import os
 import shutil
@@ -42,6 +42,7 @@ int main()
         else if (k == "r11") std::printf("%d\n", rounds(rounds_go_direct<1, 1>, 256, 256));
         else if (k == "quant") std::printf("%d\n", (int)quantize_rows_by_four(M, K));
         else if (k == "few") std::printf("%d\n", (int)quantize_few_workgroups(M, K, (int)N, N == 3 || N == 4));
+        else if (k == "waves") std::printf("%d\n", quantize_waves(M, K));
         else if (k == "max13") std::printf("%lld\n", (long long)ksplit_lds_max_k(1, 3, g));
         else if (k == "max23") std::printf("%lld\n", (long long)ksplit_lds_max_k(2, 3, g));
         else if (k == "max24") std::printf("%lld\n", (long long)ksplit_lds_max_k(2, 4, g));
@@ -98,6 +99,10 @@ RULES = [
     ("quant", 1300, 0, 2561, 0, 0, 1), ("quant", 513, 0, 16384, 0, 0, 1), ("quant", 4096, 0, 16385, 0, 0, 0),
     ("few", 4096, 8, 4096, 0, 0, 0), ("few", 4151, 8, 4096, 0, 0, 1), ("few", 4150, 8, 4096, 0, 0, 0), ("few", 4096, 5, 6912, 0, 0, 1), ("few", 4096, 5, 6144, 0, 0, 0),
     ("few", 12000, 8, 9000, 0, 0, 0), ("few", 2048, 8, 20000, 0, 0, 1), ("few", 2048, 4, 20000, 0, 0, 1), ("few", 16384, 2, 11008, 0, 0, 0),
+    ("waves", 1, 0, 2048, 0, 0, 1), ("waves", 4096, 0, 2049, 0, 0, 2), ("waves", 4096, 0, 4097, 0, 0, 4), ("waves", 1, 0, 8192, 0, 0, 4), ("waves", 1, 0, 8193, 0, 0, 8),
+    ("waves", 1024, 0, 8704, 0, 0, 8), ("waves", 1025, 0, 8704, 0, 0, 4), ("waves", 1025, 0, 10240, 0, 0, 4), ("waves", 1025, 0, 10752, 0, 0, 8),
+    ("waves", 1, 0, 16384, 0, 0, 8), ("waves", 256, 0, 16385, 0, 0, 16), ("waves", 257, 0, 16896, 0, 0, 8),
+    ("waves", 8388544, 0, 11008, 0, 0, 8), ("waves", 8388545, 0, 11008, 0, 0, 4), ("waves", 16000000, 0, 20480, 0, 0, 4),  # 2^32 work items of a launch
     ("max13", 1, 1, 1, AT, 0, 8192), ("max13", 1, 1, 1, 0, AT, 9216), ("max23", 1, 1, 1, AT, 0, 5632), ("max23", 1, 1, 1, AT, AT, 8704),
     ("max24", 1, 1, 1, AT, 0, 7168), ("max44", 1, 1, 1, AT, 0, 9216),
 ]

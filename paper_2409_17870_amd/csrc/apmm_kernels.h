@@ -49,15 +49,19 @@ inline bool quantize_rows_by_four(int64_t rows, int64_t K)
 }
 constexpr int64_t kMostWorkItems = 0xffffffffLL;  // of one dimension of a launch
 // Waves of a row in the kernel of one row to some waves: a group of 32 elements for every lane, as far as the row goes.  Beyond 8192 elements eight over
-// four: one to 203 rows 0.88 - 0.95 (16 x 13824 four bits 4.11 -> 3.81 us, 16 x 11008 two bits 4.16 -> 3.65; 16 x 60000 0.61), 512 and 1024 rows 0.92 - 1.00, more rows
-// 0.92 - 0.99 where most lanes have a group (11008, 16384 and beyond), 1.02 - 1.24 where they have not (9000).  Beyond 16384 sixteen over eight: up to 100
-// rows 0.85 - 0.99, 512 and 1024 rows 0.93 - 1.4.
+// four: one to 203 rows 0.77 - 0.98 (16 x 13824 four bits 4.11 -> 3.81 us, 16 x 11008 two bits 4.16 -> 3.65; 16 x 40000 0.56 - 0.61), 300 to 1024 rows 0.86 - 1.03, more rows
+// 0.89 - 1.00 where most lanes have a group (10752, 11008, 16384 and beyond), 1.02 - 1.24 where they have not (8704).  Rows that end inside a k block take the
+// kernel with more registers, of which a compute unit holds three workgroups: 768 rows are one round.  Up to there 0.88 - 0.98 (K = 8200 - 16383), with 800 rows and
+// more 1.00 - 1.09 at two and five bits, 1.03 - 1.21 at eight; beyond 16384 0.92 - 1.16 at 800 to 1024 rows up to K = 22001 (four and eight bits above 1), 0.76 - 1.04 with
+// more rows or longer ones.  Beyond 16384 sixteen over eight: up to 100 rows 0.85 - 0.99, 512 and 1024 rows 0.93 - 1.4.
 inline int quantize_waves(int64_t rows, int64_t K)
 {
     const int64_t nkb = round_up(K, kKPad) / kKBlock;
     if (nkb <= 64) return nkb <= 16 ? 1 : nkb <= 32 ? 2 : 4;
     if (nkb > 128 && rows <= 256) return 16;
     if (round_up(rows, 64) * 512 > kMostWorkItems) return 4;  // 8 388 545 rows and more
+    const bool ragged = K % kKBlock != 0;
+    if (ragged && rows > 768 && nkb <= (rows <= 1024 ? 176 : 128)) return 4;
     return nkb < 84 && rows > 1024 ? 4 : 8;
 }
 // Five workgroups to a compute unit instead of the seven or eight that its registers leave room for, in the kernel of one row to some waves,

@@ -102,6 +102,8 @@ RULES = [
     ("waves", 1, 0, 2048, 0, 0, 1), ("waves", 4096, 0, 2049, 0, 0, 2), ("waves", 4096, 0, 4097, 0, 0, 4), ("waves", 1, 0, 8192, 0, 0, 4), ("waves", 1, 0, 8193, 0, 0, 8),
     ("waves", 1024, 0, 8704, 0, 0, 8), ("waves", 1025, 0, 8704, 0, 0, 4), ("waves", 1025, 0, 10240, 0, 0, 4), ("waves", 1025, 0, 10752, 0, 0, 8),
     ("waves", 1, 0, 16384, 0, 0, 8), ("waves", 256, 0, 16385, 0, 0, 16), ("waves", 257, 0, 16896, 0, 0, 8),
+    ("waves", 768, 0, 9000, 0, 0, 8), ("waves", 769, 0, 9000, 0, 0, 4), ("waves", 4096, 0, 16383, 0, 0, 4), ("waves", 1024, 0, 16383, 0, 0, 4),  # rows that end in a k block
+    ("waves", 1024, 0, 20001, 0, 0, 4), ("waves", 1024, 0, 22527, 0, 0, 4), ("waves", 1024, 0, 22529, 0, 0, 8), ("waves", 1025, 0, 16385, 0, 0, 8), ("waves", 769, 0, 16384, 0, 0, 8),
     ("waves", 8388544, 0, 11008, 0, 0, 8), ("waves", 8388545, 0, 11008, 0, 0, 4), ("waves", 16000000, 0, 20480, 0, 0, 4),  # 2^32 work items of a launch
     ("max13", 1, 1, 1, AT, 0, 8192), ("max13", 1, 1, 1, 0, AT, 9216), ("max23", 1, 1, 1, AT, 0, 5632), ("max23", 1, 1, 1, AT, AT, 8704),
     ("max24", 1, 1, 1, AT, 0, 7168), ("max44", 1, 1, 1, AT, 0, 9216),

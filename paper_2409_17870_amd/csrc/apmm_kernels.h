@@ -64,15 +64,16 @@ inline int quantize_waves(int64_t rows, int64_t K)
     if (ragged && rows > 768 && nkb <= (rows <= 1024 ? 176 : 128)) return 4;
     return nkb < 84 && rows > 1024 ? 4 : 8;
 }
-// Five workgroups to a compute unit instead of the seven or eight that its registers leave room for, in the kernel of one row to some waves,
+// Five workgroups to a compute unit instead of the seven or eight that its registers leave room for, in the kernel of one row to up to four waves,
 // from 17 MB of packed output on: its stores are pieces of lines that other waves complete, and more rows under way push them out of L2 before.
-// Eight over five, eight bits 4096 x 4608 / 4096 x 5632 / 4096 x 8192 / 2048 x 11008 / 2048 x 13824 / 4096 x 20000 0.97 / 1.08 / 1.13 / 1.01 / 1.04 / 1.14,
-// six bits 4096 x 6656 / 4096 x 8192 1.10 / 1.15, five bits 4096 x 6144 / 4096 x 8192 / 8192 x 8192 0.98 / 1.05 / 1.13, four bits 2048 x 20000 1.05; not where
-// most lanes lack a second group and row ends are ragged (five and eight bits 12000 x 9000 0.87 / 0.96), nor for one and two bits, which write little
-// (4096 x 11008 0.95).  (Below the line 3000 x 7168, 13 MB at five bits and 16 at six, 1.05.)
+// Eight over five, eight bits 4096 x 4608 / 4096 x 5632 / 4096 x 8192 / 4096 x 9216 / 3000 x 10240 0.97 / 1.08 / 1.12 / 1.06 / 1.04,
+// six bits 4096 x 6656 / 4096 x 8192 1.10 / 1.15, five bits 4096 x 6144 / 4096 x 8192 / 8192 x 8192 0.98 / 1.05 / 1.13 (4096 x 8704 0.94); not where
+// most lanes lack a second group and row ends are ragged (five and eight bits 12000 x 9000 0.87 / 0.96; eight bits 1024 x 20001 1.00), nor for one and two bits, which
+// write little (4096 x 11008 0.95).  (Below the line 3000 x 7168, 13 MB at five bits and 16 at six, 1.05.)  Workgroups of eight and sixteen waves: a compute unit holds
+// no more than four and two by their waves alone, and they are not held back further.
 inline bool quantize_few_workgroups(int64_t rows, int64_t K, int bits, bool field)
 {
-    return bits > 2 && (K % 128 == 0 || K > 16384) && rows * round_up(K, kKPad) / 8 * (field ? 6 : bits) > 17000000;
+    return bits > 2 && K % 128 == 0 && quantize_waves(rows, K) <= 4 && rows * round_up(K, kKPad) / 8 * (field ? 6 : bits) > 17000000;
 }
 hipError_t launch_unpack(const uint32_t *packed, int64_t rows, int64_t K, int bits, bool field, uint8_t *codes,
                          hipStream_t stream);

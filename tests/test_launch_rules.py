@@ -98,7 +98,8 @@ RULES = [
     ("quant", 1024, 0, 2560, 0, 0, 1), ("quant", 1025, 0, 2560, 0, 0, 0), ("quant", 1599, 0, 2049, 0, 0, 0), ("quant", 1600, 0, 2049, 0, 0, 1),
     ("quant", 1300, 0, 2561, 0, 0, 1), ("quant", 513, 0, 16384, 0, 0, 1), ("quant", 4096, 0, 16385, 0, 0, 0),
     ("few", 4096, 8, 4096, 0, 0, 0), ("few", 4151, 8, 4096, 0, 0, 1), ("few", 4150, 8, 4096, 0, 0, 0), ("few", 4096, 5, 6912, 0, 0, 1), ("few", 4096, 5, 6144, 0, 0, 0),
-    ("few", 12000, 8, 9000, 0, 0, 0), ("few", 2048, 8, 20000, 0, 0, 0), ("few", 2048, 4, 20000, 0, 0, 0), ("few", 2048, 8, 11008, 0, 0, 0), ("few", 2048, 8, 10240, 0, 0, 1), ("few", 1024, 8, 20001, 0, 0, 0),  # eight waves to a row; ragged ("few", 16384, 2, 11008, 0, 0, 0),
+    ("few", 12000, 8, 9000, 0, 0, 0), ("few", 2048, 8, 20000, 0, 0, 0), ("few", 2048, 4, 20000, 0, 0, 0), ("few", 2048, 8, 11008, 0, 0, 0), ("few", 2048, 8, 10240, 0, 0, 1), ("few", 1024, 8, 20001, 0, 0, 0),  # eight waves to a row; ragged
+    ("few", 16384, 2, 11008, 0, 0, 0),
     ("waves", 1, 0, 2048, 0, 0, 1), ("waves", 4096, 0, 2049, 0, 0, 2), ("waves", 4096, 0, 4097, 0, 0, 4), ("waves", 1, 0, 8192, 0, 0, 4), ("waves", 1, 0, 8193, 0, 0, 8),
     ("waves", 1024, 0, 8704, 0, 0, 8), ("waves", 1025, 0, 8704, 0, 0, 4), ("waves", 1025, 0, 10240, 0, 0, 4), ("waves", 1025, 0, 10752, 0, 0, 8),
     ("waves", 1, 0, 16384, 0, 0, 8), ("waves", 256, 0, 16385, 0, 0, 16), ("waves", 257, 0, 16896, 0, 0, 8),

@@ -8,6 +8,8 @@
 
 namespace apmm {
 
+constexpr int64_t kMostWorkItems = 0xffffffffLL;  // of one dimension of a launch
+
 // Paper Sec. 4.1: decomposition into planes, reassembly into 32-bit words, concatenation.
 // `field`: the field form of 3- and 4-bit activations instead of the group form (apmm_layout.h).
 hipError_t launch_pack(const uint8_t *codes, int64_t rows, int64_t K, int bits, bool field, uint32_t *packed,
@@ -18,9 +20,12 @@ hipError_t launch_pack(const uint8_t *codes, int64_t rows, int64_t K, int bits, 
 // 1.02; short matrices have little to save, 2048 x 2048 and 4096 x 1024 0.99 - 1.02.  Six slots and more with long rows, where operand and output are beyond
 // the last-level cache: 5003 x 8192 0.98 - 1.08, 5003 x 11008 1.10, 4096 x 11008 0.95 - 1.02, 11008 x 11008 1.03 - 1.05 (11008 x 6000 0.94 - 0.98; four slots and fewer
 // 5003 x 11008 0.90, 11008 x 11008 1.00).  Two bits: 4096 x 4096 1.06, 4096 x 11008 0.98, 11008 x 4096 0.86, 11008 x 11008 0.76; one bit 11008 x 4096 1.06, 11008 x
-// 11008 0.86.
+// 11008 0.86.  Not where its launch would pass 2^32 work items, which the other's grid of three dimensions does not.
+constexpr int kEightWaves = 8;  // most waves of pack_eights_kernel
+inline int64_t pack_eights_threads(int64_t K) { return 64 * (K <= kEightWaves * kKPad ? round_up(K, kKPad) / kKPad : kEightWaves); }  // of eight rows
 inline bool pack_by_eights(int64_t rows, int64_t K, int bits, bool field)
 {
+    if (round_up(rows, kRowBlock) / 8 * pack_eights_threads(K) > kMostWorkItems) return false;
     const int64_t codes = rows * K;
     if (!field && bits <= 2) return rows >= 2048 && codes >= (bits == 2 ? 40000000 : 100000000);
     const int slots = field ? 6 : bits;
@@ -47,7 +52,6 @@ inline bool quantize_rows_by_four(int64_t rows, int64_t K)
     // groups to a lane, 0.92 - 1.00 with three and four; 0.92 - 1.02 at 500 to 540.
     return rows * quantize_groups(K) >= (lane_groups == 2 ? 500 : 450) * lane_groups * kQuantLanes;
 }
-constexpr int64_t kMostWorkItems = 0xffffffffLL;  // of one dimension of a launch
 // Waves of a row in the kernel of one row to some waves: a group of 32 elements for every lane, as far as the row goes.  Beyond 8192 elements eight over
 // four: one to 203 rows 0.77 - 0.98 (16 x 13824 four bits 4.11 -> 3.81 us, 16 x 11008 two bits 4.16 -> 3.65; 16 x 40000 0.56 - 0.61), 300 to 1024 rows 0.86 - 1.03, more rows
 // 0.89 - 1.00 where most lanes have a group (10752, 11008, 16384 and beyond), 1.02 - 1.24 where they have not (8704).  Rows that end inside a k block take the

@@ -245,7 +245,6 @@ __global__ __launch_bounds__(kThreads) void pack_rows_kernel(const uint8_t *__re
 //   Sum wave: adds the codes of one row and the padding; the sum waves of a row block follow its tile waves in
 //   the grid, so that they find the rows in L2.
 constexpr int kRowBlocksPerZ = 32768;  // size of the grid's y where z is needed
-constexpr int kEightWaves = 8;  // most waves of pack_eights_kernel
 enum PackForm { kFieldForm, kFold3, kFold4, kByteForm, kOtherForm };  // compile-time: a launch fetches the code of its own form only
 
 // The 64 codes of k steps 2h, 2h + 1 of row r of a tile (the tile'th of the operand), d[e][2t + jh] = the four codes 8t + 4jh + (0..3) of k step 2h + e,
@@ -926,15 +925,12 @@ hipError_t launch_pack(const uint8_t *codes, int64_t rows, int64_t K, int bits, 
     }
     if (by_eights) {
         const bool whole = K % 64 == 0;
-        const int64_t pieces = nkb / 4;
         const auto kernel = field ? (whole ? pack_eights_kernel<kFieldForm, true> : pack_eights_kernel<kFieldForm, false>)
                           : bits == 3 ? (whole ? pack_eights_kernel<kFold3, true> : pack_eights_kernel<kFold3, false>)
                           : bits == 4 ? (whole ? pack_eights_kernel<kFold4, true> : pack_eights_kernel<kFold4, false>)
                           : byte_form(bits) ? (whole ? pack_eights_kernel<kByteForm, true> : pack_eights_kernel<kByteForm, false>)
                                             : (whole ? pack_eights_kernel<kOtherForm, true> : pack_eights_kernel<kOtherForm, false>);
-        if (rows_p / 8 > 0x7fffffffLL) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)(rows_p / 8)), dim3((unsigned)(64 * (pieces < kEightWaves ? pieces : kEightWaves))), 0, stream, codes, rows, K, bits,
-                           packed, rows_p, nkb);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(rows_p / 8)), dim3((unsigned)pack_eights_threads(K)), 0, stream, codes, rows, K, bits, packed, rows_p, nkb);
         return hipGetLastError();
     }
     // Per row block: tile waves, then sum waves (a multiple of kRowsPerWg in all).  The grid's y and z count the row blocks, so that no wave

@@ -1,5 +1,5 @@
 """The launchers' rules, host functions of sizes, addresses and widths, compiled for the host alone and asked on both sides of their
-lines: which calls store their inner tiles streaming, which quantise four rows to a workgroup, with how many waves to a row and which with few workgroups to a compute unit, and which take the direct tiles or the register form of the 128 x 128 K split where the
+lines: which calls store their inner tiles streaming, which quantise four rows to a workgroup, with how many waves to a row and which with few workgroups to a compute unit, which pack by eight rows, and which take the direct tiles or the register form of the 128 x 128 K split where the
 kernels that share operands through LDS are slower."""
 import os
 import shutil
@@ -43,6 +43,7 @@ int main()
         else if (k == "quant") std::printf("%d\n", (int)quantize_rows_by_four(M, K));
         else if (k == "few") std::printf("%d\n", (int)quantize_few_workgroups(M, K, (int)N, N == 3 || N == 4));
         else if (k == "waves") std::printf("%d\n", quantize_waves(M, K));
+        else if (k == "eights" || k == "eightsf") std::printf("%d\n", (int)pack_by_eights(M, K, (int)N, k == "eightsf"));
         else if (k == "max13") std::printf("%lld\n", (long long)ksplit_lds_max_k(1, 3, g));
         else if (k == "max23") std::printf("%lld\n", (long long)ksplit_lds_max_k(2, 3, g));
         else if (k == "max24") std::printf("%lld\n", (long long)ksplit_lds_max_k(2, 4, g));
@@ -106,6 +107,8 @@ RULES = [
     ("waves", 768, 0, 9000, 0, 0, 8), ("waves", 769, 0, 9000, 0, 0, 4), ("waves", 4096, 0, 16383, 0, 0, 4), ("waves", 1024, 0, 16383, 0, 0, 4),  # rows that end in a k block
     ("waves", 1024, 0, 20001, 0, 0, 4), ("waves", 1024, 0, 22527, 0, 0, 4), ("waves", 1024, 0, 22529, 0, 0, 8), ("waves", 1025, 0, 16385, 0, 0, 8), ("waves", 769, 0, 16384, 0, 0, 8),
     ("waves", 8388544, 0, 11008, 0, 0, 8), ("waves", 8388545, 0, 11008, 0, 0, 4), ("waves", 16000000, 0, 20480, 0, 0, 4),  # 2^32 work items of a launch
+    ("eights", 536870880, 3, 64, 0, 0, 1), ("eights", 536870912, 3, 64, 0, 0, 0), ("eights", 67108832, 8, 4000, 0, 0, 1), ("eights", 67108864, 8, 4000, 0, 0, 0),  # 2^32 work items
+    ("eights", 600000000, 2, 200, 0, 0, 0), ("eightsf", 536870880, 4, 3, 0, 0, 1), ("eightsf", 536870912, 4, 3, 0, 0, 0), ("eights", 178956960, 5, 1400, 0, 0, 1), ("eights", 178956992, 5, 1400, 0, 0, 0),
     ("max13", 1, 1, 1, AT, 0, 8192), ("max13", 1, 1, 1, 0, AT, 9216), ("max23", 1, 1, 1, AT, 0, 5632), ("max23", 1, 1, 1, AT, AT, 8704),
     ("max24", 1, 1, 1, AT, 0, 7168), ("max44", 1, 1, 1, AT, 0, 9216),
 ]

@@ -18,7 +18,7 @@ def tiles_and_sums(packed, rows, K, slots):
 @pytest.mark.parametrize("kind, bits, rows, K", [
     ("w", 3, 1500, 3001), ("w", 4, 1531, 3008), ("w", 5, 2048, 2499), ("w", 6, 1633, 4096), ("w", 7, 4500, 1001), ("w", 8, 1503, 3200),
     ("a", 3, 9001, 511), ("a", 4, 2048, 4096), ("a", 4, 1601, 3333), ("a", 8, 1700, 5003), ("a", 4, 1499, 4096),
-    ("w", 2, 10003, 4001), ("w", 2, 2049, 20000), ("w", 1, 33000, 3072),
+    ("w", 2, 10003, 4001), ("w", 2, 2049, 20000), ("w", 1, 33000, 3072), ("w", 3, 1500003, 3), ("a", 4, 1500001, 3),
 ])
 def test_many_rows(kind, bits, rows, K):
     g = torch.Generator(device="cuda").manual_seed(rows)

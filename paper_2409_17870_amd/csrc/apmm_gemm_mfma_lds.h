@@ -63,6 +63,25 @@ __device__ __forceinline__ void wait_and_meet()
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
+// Whether the workgroup that holds the first wave slots of a compute unit goes ahead of the others at every issue, so that it ends early and
+// the tile of the second round runs under the others' k loop; those that run in step store together and leave that tile alone.  Each wave goes by
+// its own slot: where waves of the kernel before still hold slots of some vector units, those of one workgroup differ and the gain is less
+// (W2A4 2048 x 11008 x 4096 both, one behind the other 0.89 - 0.92, behind a packing 0.91 - 0.96, behind an elementwise kernel 0.95 - 0.98; one output
+// 0.94 - 0.97 and 3-bit weights 0.91 - 0.98 in all three).
+// Time with over without, operands and outputs in rotation:
+// Two workgroups to a compute unit (3- and 4-bit activations), a round of 512 and up to 0.44 of a second.  128 x 256, 640 to 688 tiles, K = 2048 - 8192: both
+// outputs 0.85 - 1.00, int32 0.91 - 1.00, fp16 0.94 - 1.01; K = 512 - 1536, where both are asked for, 0.97 - 1.05: not there.  864 and 960 tiles 0.99 - 1.02 and,
+// both outputs, 1.06 - 1.18; 1376 1.02 - 1.05, 512 1.00 - 1.01.  128 x 128, 544 to 736 tiles: 3-bit weights 0.91 - 1.00 from K = 2048 on, 4-bit 0.95 - 1.01 from
+// 2560 on (fp16 at 2048 up to 1.02); 1- and 2-bit 0.94 - 1.00 from 4096 on, at 2048 to 3072 0.96 - 1.03.
+// Three workgroups (1- and 2-bit activations), 1.25 to 1.44 rounds of 768, in three steps, K = 2048 - 8192, 1032 to 1062 tiles: W2A2, W1A2 and W2A1 0.91 - 1.00 (946 tiles
+// 0.98 - 1.01), with 4-bit weights 0.98 - 1.01; W1A1 0.97 - 1.06: not there.
+template <int P, int Q, int WN>
+__host__ __device__ constexpr bool lds_goes_ahead(int tiles, int k)
+{
+    if (activation_field_form(P)) return tiles > 512 && tiles <= 736 && k >= (WN == 4 || Q == 3 ? 2048 : Q == 4 ? 2560 : 4096);
+    return Q <= 2 && P + Q > 2 && tiles > 960 && tiles <= 1104 && k >= 2048;
+}
+
 // One workgroup tile of 64 WM x 64 WN.  KG = 2: eight waves, the second four of which work on the second half of K with a ring of
 // their own, for outputs of one round of tiles; in the end either group of waves adds up and stores one row block of each wave tile.
 constexpr int lds_exchange_bytes(int wn) { return 8 * wn * 16 * 64 * 4; }
@@ -157,18 +176,8 @@ __device__ __forceinline__ void lds_tile(uint4 *ring_of_workgroup, const uint32_
         if constexpr (h == 1) next_stage();
     };
     static_for<kLdsRing - 1>(request);
-    // Two workgroups to a compute unit (AF), a round of 512 and up to 0.44 of a second: the workgroup that holds the first wave slots goes ahead of the
-    // other at every issue, so that it ends early and the tile of the second round runs under the other one's k loop; two that run in step store together
-    // and leave that tile alone.  Time over that without, 640 / 704 / 768 tiles: 128 x 256 W2A4 fp16 0.96 - 0.97 / 0.96 - 0.98 / 0.97 - 0.99, both outputs
-    // 0.92 - 0.94 / 0.95 - 0.96 / 0.97 - 1.03, int32 0.89 / 0.94 / 0.95; W1A4 0.91 - 0.98 / 0.95 - 0.99 / 0.98 - 1.01 (K = 2048 - 8192; 2048 x 11008 x 4096 W2A4 both 62.5 ->
-    // 57.9 us).  864 and 960 tiles 0.99 - 1.02 and, both outputs, 1.06 - 1.18; 1376 1.02 - 1.05, 512 1.00 - 1.01.  128 x 128, 544 - 736 tiles, K = 2048 - 8192: W3A3 and
-    // W3A4 0.93 - 0.99, W4A4 0.96 - 1.00 (1.01 at K = 2048), W2A4 0.96 - 1.00, W1A3 0.96 - 1.01; K = 1024 0.99 - 1.04.
-    // Three workgroups (1- and 2-bit activations), 1.25 to 1.44 rounds of 768, in three steps: W2A2 1500 x 11008 (1032 tiles) 0.93 - 0.99; 946 tiles 0.98 - 1.01,
-    // with 4-bit weights 0.98 - 1.01.
-    if constexpr (KG == 1 && (AF || Q <= 2)) {
-        constexpr int kLeast = AF ? 512 : 960, kMost = AF ? 736 : 1104;
-        const int tiles = tiles_n * (int)tiles_m;
-        if (tiles > kLeast && tiles <= kMost && (WN == 4 || k_arg >= 2048)) {
+    if constexpr (KG == 1) {
+        if (lds_goes_ahead<P, Q, WN>(tiles_n * (int)tiles_m, k_arg)) {
             constexpr int kHwId = 4, kSlotBits = 4;  // the register that says where a wave runs; its lowest field is the slot in the vector unit
             const uint32_t slot = __builtin_amdgcn_s_getreg(kHwId | (kSlotBits - 1) << 11);
             if constexpr (AF) {

@@ -1,5 +1,5 @@
 """The launchers' rules, host functions of sizes, addresses and widths, compiled for the host alone and asked on both sides of their
-lines: which calls store their inner tiles streaming, which quantise four rows to a workgroup, with how many waves to a row and which with few workgroups to a compute unit, which pack by eight rows, and which take the direct tiles or the register form of the 128 x 128 K split where the
+lines: which calls store their inner tiles streaming, which quantise four rows to a workgroup, with how many waves to a row and which with few workgroups to a compute unit, which pack by eight rows, in which tiles through LDS one workgroup goes ahead, and which take the direct tiles or the register form of the 128 x 128 K split where the
 kernels that share operands through LDS are slower."""
 import os
 import shutil
@@ -43,6 +43,13 @@ int main()
         else if (k == "quant") std::printf("%d\n", (int)quantize_rows_by_four(M, K));
         else if (k == "few") std::printf("%d\n", (int)quantize_few_workgroups(M, K, (int)N, N == 3 || N == 4));
         else if (k == "waves") std::printf("%d\n", quantize_waves(M, K));
+        else if (k.compare(0, 5, "ahead") == 0) {
+            const int tiles = (int)M, kk = (int)K;
+            const std::string v = k.substr(5);
+            std::printf("%d\n", v == "11" ? (int)lds_goes_ahead<1, 1, 2>(tiles, kk) : v == "21" ? (int)lds_goes_ahead<2, 1, 2>(tiles, kk) : v == "12" ? (int)lds_goes_ahead<1, 2, 2>(tiles, kk)
+                              : v == "24" ? (int)lds_goes_ahead<2, 4, 2>(tiles, kk) : v == "42" ? (int)lds_goes_ahead<4, 2, 2>(tiles, kk) : v == "42wide" ? (int)lds_goes_ahead<4, 2, 4>(tiles, kk)
+                              : v == "33" ? (int)lds_goes_ahead<3, 3, 2>(tiles, kk) : v == "44" ? (int)lds_goes_ahead<4, 4, 2>(tiles, kk) : -1);
+        }
         else if (k == "eights" || k == "eightsf") std::printf("%d\n", (int)pack_by_eights(M, K, (int)N, k == "eightsf"));
         else if (k == "max13") std::printf("%lld\n", (long long)ksplit_lds_max_k(1, 3, g));
         else if (k == "max23") std::printf("%lld\n", (long long)ksplit_lds_max_k(2, 3, g));
@@ -109,6 +116,10 @@ RULES = [
     ("waves", 8388544, 0, 11008, 0, 0, 8), ("waves", 8388545, 0, 11008, 0, 0, 4), ("waves", 16000000, 0, 20480, 0, 0, 4),  # 2^32 work items of a launch
     ("eights", 536870880, 3, 64, 0, 0, 1), ("eights", 536870912, 3, 64, 0, 0, 0), ("eights", 67108832, 8, 4000, 0, 0, 1), ("eights", 67108864, 8, 4000, 0, 0, 0),  # 2^32 work items
     ("eights", 600000000, 2, 200, 0, 0, 0), ("eightsf", 536870880, 4, 3, 0, 0, 1), ("eightsf", 536870912, 4, 3, 0, 0, 0), ("eights", 178956960, 5, 1400, 0, 0, 1), ("eights", 178956992, 5, 1400, 0, 0, 0),
+    ("ahead42wide", 688, 0, 2048, 0, 0, 1), ("ahead42wide", 688, 0, 2047, 0, 0, 0), ("ahead42wide", 512, 0, 4096, 0, 0, 0), ("ahead42wide", 737, 0, 4096, 0, 0, 0),
+    ("ahead42", 513, 0, 4096, 0, 0, 1), ("ahead42", 513, 0, 4095, 0, 0, 0), ("ahead33", 736, 0, 2048, 0, 0, 1), ("ahead33", 736, 0, 2047, 0, 0, 0), ("ahead44", 736, 0, 2560, 0, 0, 1),
+    ("ahead44", 736, 0, 2559, 0, 0, 0), ("ahead11", 1032, 0, 4096, 0, 0, 0), ("ahead21", 1032, 0, 2048, 0, 0, 1), ("ahead12", 961, 0, 4096, 0, 0, 1), ("ahead12", 960, 0, 4096, 0, 0, 0),
+    ("ahead12", 1105, 0, 4096, 0, 0, 0), ("ahead24", 1032, 0, 4096, 0, 0, 0),
     ("max13", 1, 1, 1, AT, 0, 8192), ("max13", 1, 1, 1, 0, AT, 9216), ("max23", 1, 1, 1, AT, 0, 5632), ("max23", 1, 1, 1, AT, AT, 8704),
     ("max24", 1, 1, 1, AT, 0, 7168), ("max44", 1, 1, 1, AT, 0, 9216),
 ]

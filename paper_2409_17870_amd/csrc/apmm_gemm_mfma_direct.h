@@ -366,10 +366,12 @@ __global__ __launch_bounds__(256) void gemm_mfma_direct_kernel(const uint32_t *a
     // runs (a 16 MiB fp16 output cost 7 us that way).  Rows are taken in pairs: the even lane of a lane pair
     // collects both columns of the first row, the odd lane both columns of the second row (one lane exchange),
     // and each stores one dword.
-    // NT (interior tiles): streaming stores (rule: direct_streams).
+    // NT (interior tiles): streaming stores (rule: direct_streams); fp16 pairs of two rows at a time, as in apmm_gemm_mfma_lds.h (2048 x 4096 x 1024, piece by
+    // piece / together: W1A1 8.3 / 8.1 us, W2A2 9.6 / 9.1; 1024 x 7936 x 1024 W1A1 8.5 / 8.3).
     auto emit = [&](auto guard_c, auto i32_c, auto f16_c, auto pair_c, auto nt_c) __attribute__((always_inline)) {
         constexpr bool GUARD = decltype(guard_c)::value, I32 = decltype(i32_c)::value, F16 = decltype(f16_c)::value,
                        PAIR = decltype(pair_c)::value, NT = decltype(nt_c)::value;
+        constexpr bool TOGETHER = F16 && PAIR && NT;  // the 64-byte pieces of a line leave one right behind the other
         if constexpr (NT) edge_of_streaming();
         int32_t *ci = I32 ? g.c_i32 + m_last * g.N + n_lane : nullptr;
         uint16_t *ch = F16 ? g.c_f16 + m_last * g.N + n_lane : nullptr;
@@ -389,12 +391,20 @@ __global__ __launch_bounds__(256) void gemm_mfma_direct_kernel(const uint32_t *a
             sw[bj] = half_bits_to_float((uint16_t)((bj & 1) ? sw_raw[bj / 2] >> 16 : sw_raw[bj / 2] & 0xffffu));
 #pragma unroll
         for (int bi = 0; bi < WML; ++bi) {
+            float sa_of[16];
+            if constexpr (TOGETHER) {  // (one wait for all of them)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) sa_of[v] = token_scale(bi, v);
+#pragma unroll
+                for (int v = 0; v < 16; ++v) asm volatile("" : "+v"(sa_of[v]));
+            }
+            auto scale_of = [&](int v) __attribute__((always_inline)) { return TOGETHER ? sa_of[v & 15] : token_scale(bi, v); };
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int64_t row = (int64_t)(bi * 32 + 8 * (v / 4) + (v % 4));  // relative to m_last
                 // the lane permutes come before any lane leaves the iteration: a lane that has left supplies nothing
-                const float sa = F16 ? token_scale(bi, v) : 1.0f;
-                const float sa_next = (F16 && PAIR && v % 2 == 0) ? token_scale(bi, v + 1) : 1.0f;
+                const float sa = F16 ? scale_of(v) : 1.0f;
+                const float sa_next = (F16 && PAIR && v % 2 == 0) ? scale_of(v + 1) : 1.0f;
                 if (GUARD && m_last + row >= g.M) continue;
 #pragma unroll
                 for (int bj = 0; bj < WN; ++bj) {
@@ -403,22 +413,32 @@ __global__ __launch_bounds__(256) void gemm_mfma_direct_kernel(const uint32_t *a
                     if constexpr (I32 && NT) __builtin_nontemporal_store((int32_t)c, &ci[row * g.N + bj * 32]);
                     if constexpr (I32 && !NT) ci[row * g.N + bj * 32] = (int32_t)c;
                     if constexpr (F16 && !PAIR) ch[row * g.N + bj * 32] = float_to_half_bits(c * sa * sw[bj]);
-                    if constexpr (F16 && PAIR) {
-                        if (v % 2 == 0) {  // folds once the loop is unrolled
-                            uint32_t word;
+                }
+                if constexpr (F16 && PAIR) {
+                    if (v % 2 == 0) {  // folds once the loop is unrolled
+                        uint32_t word[WN];
+#pragma unroll
+                        for (int bj = 0; bj < WN; ++bj) {
+                            const float c = acc[ROWL + bi][bj][v], c_next = acc[ROWL + bi][bj][(v + 1) & 15];
                             if constexpr (WM * WN < 16) {
-                                word = swap_pair(half_pair(c * sa, acc[ROWL + bi][bj][(v + 1) & 15] * sa_next, sw[bj]), swap_pair_selector(odd));
+                                word[bj] = swap_pair(half_pair(c * sa, c_next * sa_next, sw[bj]), swap_pair_selector(odd));
                             } else {  // (256 x 256: spills with it)
                                 const uint32_t h0 = float_to_half_bits(c * sa * sw[bj]);
-                                const uint32_t h1 = float_to_half_bits(acc[ROWL + bi][bj][(v + 1) & 15] * sa_next * sw[bj]);
+                                const uint32_t h1 = float_to_half_bits(c_next * sa_next * sw[bj]);
                                 const uint32_t give = odd ? h0 : h1, keep = odd ? h1 : h0;
                                 // quad_perm [1, 0, 3, 2]: the value of the other lane of the pair
                                 const uint32_t got = (uint32_t)__builtin_amdgcn_mov_dpp((int)give, 0xB1, 0xf, 0xf, true);
-                                word = odd ? (got | (keep << 16)) : (keep | (got << 16));
+                                word[bj] = odd ? (got | (keep << 16)) : (keep | (got << 16));
                             }
+                        }
+#pragma unroll
+                        for (int bj = 0; bj < WN; ++bj)
+                            if constexpr (TOGETHER && WM * WN < 16) asm volatile("" : "+v"(word[bj]));
+#pragma unroll
+                        for (int bj = 0; bj < WN; ++bj) {
                             uint32_t *dst = reinterpret_cast<uint32_t *>(ch_pair + row * g.N + bj * 32);
-                            if constexpr (NT) __builtin_nontemporal_store(word, dst);
-                            else *dst = word;
+                            if constexpr (NT) __builtin_nontemporal_store(word[bj], dst);
+                            else *dst = word[bj];
                         }
                     }
                 }

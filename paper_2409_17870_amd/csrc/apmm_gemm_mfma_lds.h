@@ -387,10 +387,15 @@ __device__ __forceinline__ void lds_tile(uint4 *ring_of_workgroup, const uint32_
 
     // Store, as in apmm_gemm_mfma_direct.h: one pass per output, fp16 in pairs of columns where the addresses allow it, streaming stores by
     // the rule of lds_streams (but single fp16 elements behind an int32 output, odd widths: plain, 1500 x 5003 x 3001 W2A4 28.8 against
-    // 23.3 us).
+    // 23.3 us).  Streaming fp16 pairs: all words of two rows, then their stores, so that the pieces of a line, 64 bytes of each row, leave one right behind the
+    // other; apart by the operations for a piece the memory system joins fewer of them.  That needs the token scales of a block at hand, their lane permutes
+    // requested together, or a workgroup that is alone waits for each.  2048 x 4096 fp16, piece by piece with twelve operations a pair / with six / together:
+    // W2A4 K = 512 8.2 / 9.0 / 7.6 us, K = 1024 10.0 / 10.7 / 9.2, W4A4 K = 512 10.4 / 10.5 / 9.6; 2048 x 12288 x 512 W1A1 17.0 / 18.6 / 15.3, W2A4 20.5 / 21.9 / 19.9; 512 x 4096 x 512
+    // W4A4 5.7 / 5.7 / 5.7, without the scales at hand 5.9.  (Plain stores meet in L2 in any order: both outputs 1.00 - 1.02 with it.)
     auto emit = [&](auto guard_c, auto i32_c, auto f16_c, auto pair_c, auto nt_c) __attribute__((always_inline)) {
         constexpr bool GUARD = decltype(guard_c)::value, I32 = decltype(i32_c)::value, F16 = decltype(f16_c)::value,
                        PAIR = decltype(pair_c)::value, NT = decltype(nt_c)::value;
+        constexpr bool TOGETHER = F16 && PAIR && NT;  // the 64-byte pieces of a line leave one right behind the other
         if constexpr (NT) edge_of_streaming();
         int32_t *ci = I32 ? ci_arg + m_lane * N + n_lane : nullptr;
         uint16_t *ch = F16 ? cf_arg + m_lane * N + n_lane : nullptr;
@@ -403,12 +408,20 @@ __device__ __forceinline__ void lds_tile(uint4 *ring_of_workgroup, const uint32_
         };
 #pragma unroll
         for (int bi = 0; bi < WMO; ++bi) {
+            float sa_of[16];
+            if constexpr (TOGETHER) {  // (one wait for all of them)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) sa_of[v] = token_scale(bi, v);
+#pragma unroll
+                for (int v = 0; v < 16; ++v) asm volatile("" : "+v"(sa_of[v]));
+            }
+            auto scale_of = [&](int v) __attribute__((always_inline)) { return TOGETHER ? sa_of[v & 15] : token_scale(bi, v); };
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int64_t row = (int64_t)(bi * 32 + 8 * (v / 4) + (v % 4));
                 // the lane permutes come before any lane leaves the iteration: a lane that has left supplies nothing
-                const float sa = F16 ? token_scale(bi, v) : 1.0f;
-                const float sa_next = (F16 && PAIR && v % 2 == 0) ? token_scale(bi, v + 1) : 1.0f;
+                const float sa = F16 ? scale_of(v) : 1.0f;
+                const float sa_next = (F16 && PAIR && v % 2 == 0) ? scale_of(v + 1) : 1.0f;
                 if (GUARD && m_lane + row >= M) continue;
 #pragma unroll
                 for (int bj = 0; bj < WN; ++bj) {
@@ -420,12 +433,20 @@ __device__ __forceinline__ void lds_tile(uint4 *ring_of_workgroup, const uint32_
                         if constexpr (NT) __builtin_nontemporal_store(float_to_half_bits(x * sa * sw[bj]), &ch[row * N + bj * 32]);
                         else ch[row * N + bj * 32] = float_to_half_bits(x * sa * sw[bj]);
                     }
-                    if constexpr (F16 && PAIR) {
-                        if (v % 2 == 0) {
-                            const uint32_t word = swap_pair(half_pair(x * sa, c[bi][bj][(v + 1) & 15] * sa_next, sw[bj]), selector);
+                }
+                if constexpr (F16 && PAIR) {
+                    if (v % 2 == 0) {
+                        uint32_t word[WN];
+#pragma unroll
+                        for (int bj = 0; bj < WN; ++bj) word[bj] = swap_pair(half_pair(c[bi][bj][v] * sa, c[bi][bj][(v + 1) & 15] * sa_next, sw[bj]), selector);
+#pragma unroll
+                        for (int bj = 0; bj < WN; ++bj)
+                            if constexpr (TOGETHER) asm volatile("" : "+v"(word[bj]));
+#pragma unroll
+                        for (int bj = 0; bj < WN; ++bj) {
                             uint32_t *dst = reinterpret_cast<uint32_t *>(ch_pair + row * N + bj * 32);
-                            if constexpr (NT) __builtin_nontemporal_store(word, dst);
-                            else *dst = word;
+                            if constexpr (NT) __builtin_nontemporal_store(word[bj], dst);
+                            else *dst = word[bj];
                         }
                     }
                 }

@@ -61,7 +61,8 @@ def kernels(code_objects):
 
 @pytest.fixture(scope="module")
 def dword_stores(code_objects, tmp_path_factory):
-    """{mangled kernel name: Counter(plain=, nt=)} of the dword stores of the tiled kernels"""
+    """{mangled kernel name: Counter(plain=, nt=, pair=, behind=)} of the dword stores of the tiled kernels: streaming ones of two fp16 results (nt and
+    pair), and of those the ones that follow another within three instructions (behind)"""
     objdump = shutil.which("llvm-objdump", path="/opt/rocm/llvm/bin" + os.pathsep + os.environ.get("PATH", ""))
     if objdump is None:
         pytest.skip("no llvm-objdump")
@@ -78,8 +79,20 @@ def dword_stores(code_objects, tmp_path_factory):
             m = re.match(r"[0-9a-f]+ <(.*)>:$", line)
             if m:
                 count = found[m.group(1)] = collections.Counter()
-            elif count is not None and "global_store_dword " in line:
-                count["nt" if line.split("//")[0].rstrip().endswith(" nt") else "plain"] += 1
+                pairs, since = set(), 99  # registers that a byte permute wrote last, instructions since the last store of one
+            elif count is not None and line.startswith("\t"):
+                since += 1
+                op, args = (line.split("//")[0].split(None, 1) + [""])[:2]
+                if op == "global_store_dword":
+                    nt = args.rstrip().endswith(" nt")
+                    count["nt" if nt else "plain"] += 1
+                    if nt and args.split(", ")[1] in pairs:
+                        count["pair"] += 1
+                        count["behind"] += since <= 3
+                        since = 0
+                elif op.startswith("v_"):
+                    to = args.split(",")[0].strip()
+                    (pairs.add if op.startswith("v_perm_b32") else pairs.discard)(to)
     return found
 
 
@@ -177,3 +190,16 @@ def test_128_by_256_tile_stores_fp16_alone(dword_stores):
     """Four blocks a wave, 8 dword stores of pairs each, streaming and plain; no int32 store, which the launch rule never asks for."""
     for args, count in _of(dword_stores, "gemm_mfma_ksplit_wide_kernel").items():
         assert count["nt"] == count["plain"] == 32, (args, count)
+
+
+@pytest.mark.parametrize("name", ["gemm_mfma_lds_kernel", "gemm_mfma_direct_kernel"])
+def test_streaming_fp16_pairs_leave_together(kernels, dword_stores, name):
+    """The pieces of 64 bytes that make up a row's line: further apart, fewer of them are joined on their way to memory."""
+    seen = 0
+    for (p, q, wm, wn, last), meta in _of(kernels, name).items():
+        count = dword_stores[meta[".name"]]
+        if wm * wn == 16 or (name == "gemm_mfma_direct_kernel" and last > 1):
+            continue  # (with other operations, for want of registers; int32 output alone)
+        seen += 1
+        assert count["pair"] >= 8 * wm * wn and count["behind"] * wn >= 0.9 * count["pair"] * (wn - 1), (p, q, wm, wn, count)
+    assert seen

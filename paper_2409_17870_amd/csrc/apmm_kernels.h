@@ -15,21 +15,30 @@ constexpr int64_t kMostWorkItems = 0xffffffffLL;  // of one dimension of a launc
 hipError_t launch_pack(const uint8_t *codes, int64_t rows, int64_t K, int bits, bool field, uint32_t *packed,
                        hipStream_t stream);
 // Its rule for many rows: eight rows to a workgroup, code sums on the way, against a wave per packed tile and waves of their own for the sums (1 and 2
-// bits: against a wave per row).  Eights over the other, 3 to 8 bits: 2048 x 4096 0.87 - 0.90, 4096 x 6000 0.76, 5003 x 3001 0.80 - 0.83, 11008 x 4096 0.76 -
-// 0.91, 1500 x 5120 0.96, 2048 x 2500 0.96; fewer rows leave compute units without a workgroup, 512 x 4096 1.12 - 1.16, 1024 x 4096 1.03 - 1.07, 1024 x 11008 0.98 -
-// 1.02; short matrices have little to save, 2048 x 2048 and 4096 x 1024 0.99 - 1.02.  Six slots and more with long rows, where operand and output are beyond
-// the last-level cache: 5003 x 8192 0.98 - 1.08, 5003 x 11008 1.10, 4096 x 11008 0.95 - 1.02, 11008 x 11008 1.03 - 1.05 (11008 x 6000 0.94 - 0.98; four slots and fewer
-// 5003 x 11008 0.90, 11008 x 11008 1.00).  Two bits: 4096 x 4096 1.06, 4096 x 11008 0.98, 11008 x 4096 0.86, 11008 x 11008 0.76; one bit 11008 x 4096 1.06, 11008 x
-// 11008 0.86.  Not where its launch would pass 2^32 work items, which the other's grid of three dimensions does not.
+// bits: against a wave per row).  Time of eights over the other's, least and most of three settings: the same codes again and again, several states in the
+// last-level cache, codes and output from and to memory.  What decides is how evenly its workgroups, all alike, fill the 256 compute units: `full`, the share of the
+// last round of 256 that is there.
+// 3 to 8 bits, K up to 4096 (a piece of 512 codes or none for each of eight waves): from 6144 rows on 0.34 - 0.96, of which fewer than 512 codes a row 0.34 - 0.91; 3072
+// to 6143 rows, 0.8 full, 0.70 - 1.03 from 10 million codes on (7 million 0.85 - 1.05; 0.7 to 0.75 full 0.80 - 1.07); one round, 1700 rows and K = 3300 at least, 0.57 - 0.99 (1500 x
+// 3072 0.90 - 1.03, 2048 x 3001 0.83 - 1.07); little more than one, 2100 to 2800 x 4096, 0.85 - 1.07.
+// Longer rows: 0.95 full in one or two rounds, 0.88 in more, 0.63 - 1.05 (2048 x 5120 0.86 - 0.97, 2048 x 11008 0.69 - 0.77, from memory 0.99 - 1.05; 4096 x 8192 0.67 - 0.97, 5504 x 8192
+// 0.75 - 0.96, 11008 x 11008 0.69 - 1.01); else from memory up to 1.08 (3600 and 6400 x 11008), 1.14 (4200 x 11008) and 1.35 (2100 x 11008).  Six slots and more, K beyond 7000, operand and output beyond the last-level cache: 4096 x 11008 0.95 - 1.02, 11008 x 11008 1.03 - 1.05.
+// Two bits: from 45 million codes on, 0.88 full, 0.67 - 1.01 (8192 x 8192, the same codes again, 1.05; fewer codes 0.71 - 1.03; 2500 rows 0.84 - 1.27).  One bit: from 100 million
+// on 0.71 - 0.91, the same codes again 0.91 - 1.06 (2500 rows 1.06 - 1.32).  Not where its launch would pass 2^32 work items, which the other's grid of three dimensions does not.
 constexpr int kEightWaves = 8;  // most waves of pack_eights_kernel
 inline int64_t pack_eights_threads(int64_t K) { return 64 * (K <= kEightWaves * kKPad ? round_up(K, kKPad) / kKPad : kEightWaves); }  // of eight rows
 inline bool pack_by_eights(int64_t rows, int64_t K, int bits, bool field)
 {
-    if (round_up(rows, kRowBlock) / 8 * pack_eights_threads(K) > kMostWorkItems) return false;
-    const int64_t codes = rows * K;
-    if (!field && bits <= 2) return rows >= 2048 && codes >= (bits == 2 ? 40000000 : 100000000);
+    const int64_t codes = rows * K, groups = round_up(rows, kRowBlock) / 8, rounds = (groups + 255) / 256;
+    if (groups * pack_eights_threads(K) > kMostWorkItems) return false;
+    auto full = [&](int percent) { return groups * 100 >= rounds * 256 * percent; };
+    if (!field && bits <= 2) return rows >= 2048 && full(88) && codes >= (bits == 2 ? 45000000 : 100000000);
+    if (K <= 4096) {
+        if (rows >= 6144) return codes >= 4500000;
+        return rows >= 3072 ? full(80) && codes >= 10000000 : rows >= 1700 && rows <= 2048 && K >= 3300;
+    }
     const int slots = field ? 6 : bits;
-    return rows >= 1500 && codes >= 4500000 && !(slots >= 6 && K > 7000 && codes > 40000000);
+    return rows >= 1700 && full(rounds <= 2 ? 95 : 88) && !(slots >= 6 && K > 7000 && codes > 40000000);
 }
 // Paper Sec. 3.1 + 4.1: per-row symmetric quantisation of binary16 features fused with the packing.
 hipError_t launch_quantize_pack(const uint16_t *x, int64_t rows, int64_t K, int bits, bool field, uint32_t *packed,

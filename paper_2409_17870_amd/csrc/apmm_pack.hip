@@ -428,8 +428,9 @@ __global__ __launch_bounds__(kThreads, 8) void pack_kernel(const uint8_t *__rest
 
 // pack_eights_kernel: a workgroup packs eight rows, a wave eight rows x 512 codes at a time: lane l takes row l % 8 and the 64 codes of piece l / 8.  The
 // eight rows' 16 bytes of a slot are one line, written whole, as by pack_kernel, and the code sums fall out on the way: no code is read twice.  Bound by
-// memory: three bits 5003 x 3001 8.8 -> 7.1 us, four 11008 x 4096 17.9 -> 13.6 (3.3 -> 4.3 TB/s), activations of four bits 2048 x 4096 5.4 -> 4.8, 4096 x 6000 12.5 -> 9.5, two
-// bits 11008 x 11008 46.9 -> 35.8 (rule: pack_by_eights).  (The four workgroups of a row block on one XCD, one behind the other: 0.96 - 1.09 of this.)
+// memory.  Launches inside a graph, codes and output in the last-level cache / from and to memory: three bits 5003 x 3001 8.7 -> 7.0 / 9.8 -> 8.3 us, four bits 11008 x 4096
+// 17.1 -> 13.2 / 19.1 -> 15.9, activations of four bits 2048 x 4096 5.3 -> 4.7 / 6.0 -> 5.8, two bits 11008 x 11008 26.6 -> 24.8 / 46.8 -> 35.6 (rule: pack_by_eights).  (The four
+// workgroups of a row block on one XCD, one behind the other: 0.96 - 1.09 of this.)
 template <PackForm FORM, bool WHOLE>
 __global__ __launch_bounds__(64 * kEightWaves) void pack_eights_kernel(const uint8_t *__restrict__ codes, int64_t rows, int64_t K, int bits,
                                                                        uint32_t *__restrict__ packed, int64_t rows_p, int64_t nkb)

@@ -7,6 +7,8 @@ import subprocess
 
 import pytest
 
+from test_pack_eights import SHAPES as PACKED
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2409_17870_amd", "csrc")
 
@@ -116,6 +118,12 @@ RULES = [
     ("waves", 8388544, 0, 11008, 0, 0, 8), ("waves", 8388545, 0, 11008, 0, 0, 4), ("waves", 16000000, 0, 20480, 0, 0, 4),  # 2^32 work items of a launch
     ("eights", 536870880, 3, 64, 0, 0, 1), ("eights", 536870912, 3, 64, 0, 0, 0), ("eights", 67108832, 8, 4000, 0, 0, 1), ("eights", 67108864, 8, 4000, 0, 0, 0),  # 2^32 work items
     ("eights", 600000000, 2, 200, 0, 0, 0), ("eightsf", 536870880, 4, 3, 0, 0, 1), ("eightsf", 536870912, 4, 3, 0, 0, 0), ("eights", 178956960, 5, 1400, 0, 0, 1), ("eights", 178956992, 5, 1400, 0, 0, 0),
+    ("eights", 5003, 3, 3001, 0, 0, 1), ("eightsf", 2048, 4, 4096, 0, 0, 1), ("eights", 1000, 3, 4096, 0, 0, 0), ("eights", 1700, 3, 3300, 0, 0, 1), ("eights", 1699, 3, 3300, 0, 0, 0),
+    ("eights", 1700, 3, 3299, 0, 0, 0), ("eights", 2049, 3, 4096, 0, 0, 0), ("eights", 3071, 3, 4096, 0, 0, 0), ("eights", 3300, 3, 4096, 0, 0, 1), ("eights", 4200, 3, 4096, 0, 0, 0),
+    ("eights", 5003, 3, 1998, 0, 0, 0), ("eights", 6144, 3, 733, 0, 0, 1), ("eights", 6144, 3, 732, 0, 0, 0), ("eights", 9001, 3, 511, 0, 0, 1),
+    ("eights", 2048, 5, 5120, 0, 0, 1), ("eights", 1920, 5, 5120, 0, 0, 0), ("eights", 1921, 5, 5120, 0, 0, 1), ("eights", 3872, 5, 5120, 0, 0, 0), ("eights", 3873, 5, 5120, 0, 0, 1), ("eights", 5376, 5, 5120, 0, 0, 0), ("eights", 2500, 5, 11008, 0, 0, 0), ("eights", 5003, 5, 11008, 0, 0, 0), ("eights", 5504, 5, 11008, 0, 0, 1),
+    ("eights", 11008, 6, 8192, 0, 0, 0), ("eights", 11008, 6, 7000, 0, 0, 1), ("eightsf", 11008, 4, 8192, 0, 0, 0), ("eights", 11008, 4, 8192, 0, 0, 1),
+    ("eights", 2048, 2, 24576, 0, 0, 1), ("eights", 2500, 2, 24576, 0, 0, 0), ("eights", 8192, 2, 5120, 0, 0, 0), ("eights", 8192, 1, 12207, 0, 0, 0), ("eights", 8192, 1, 12208, 0, 0, 1),
     ("ahead42wide", 688, 0, 2048, 0, 0, 1), ("ahead42wide", 688, 0, 2047, 0, 0, 0), ("ahead42wide", 512, 0, 4096, 0, 0, 0), ("ahead42wide", 737, 0, 4096, 0, 0, 0),
     ("ahead42", 513, 0, 4096, 0, 0, 1), ("ahead42", 513, 0, 4095, 0, 0, 0), ("ahead33", 736, 0, 2048, 0, 0, 1), ("ahead33", 736, 0, 2047, 0, 0, 0), ("ahead44", 736, 0, 2560, 0, 0, 1),
     ("ahead44", 736, 0, 2559, 0, 0, 0), ("ahead11", 1032, 0, 4096, 0, 0, 0), ("ahead21", 1032, 0, 2048, 0, 0, 1), ("ahead12", 961, 0, 4096, 0, 0, 1), ("ahead12", 960, 0, 4096, 0, 0, 0),
@@ -123,7 +131,7 @@ RULES = [
     ("max13", 1, 1, 1, AT, 0, 8192), ("max13", 1, 1, 1, 0, AT, 9216), ("max23", 1, 1, 1, AT, 0, 5632), ("max23", 1, 1, 1, AT, AT, 8704),
     ("max24", 1, 1, 1, AT, 0, 7168), ("max44", 1, 1, 1, AT, 0, 9216),
 ]
-CASES = STREAMS + RULES
+CASES = STREAMS + RULES + [("eightsf" if kind == "a" and bits in (3, 4) else "eights", rows, bits, K, 0, 0, by_eights) for kind, bits, rows, K, by_eights in PACKED]
 
 
 @pytest.fixture(scope="module")

@@ -61,20 +61,23 @@ inline bool quantize_rows_by_four(int64_t rows, int64_t K)
     // groups to a lane, 0.92 - 1.00 with three and four; 0.92 - 1.02 at 500 to 540.
     return rows * quantize_groups(K) >= (lane_groups == 2 ? 500 : 450) * lane_groups * kQuantLanes;
 }
-// Waves of a row in the kernel of one row to some waves: a group of 32 elements for every lane, as far as the row goes.  Beyond 8192 elements eight over
-// four: one to 203 rows 0.77 - 0.98 (16 x 13824 four bits 4.11 -> 3.81 us, 16 x 11008 two bits 4.16 -> 3.65; 16 x 40000 0.56 - 0.61), 300 to 1024 rows 0.86 - 1.03, more rows
-// 0.89 - 1.00 where most lanes have a group (10752, 11008, 16384 and beyond), 1.02 - 1.24 where they have not (8704).  Rows that end inside a k block take the
-// kernel with more registers, of which a compute unit holds three workgroups: 768 rows are one round.  Up to there 0.88 - 0.98 (K = 8200 - 16383), with 800 rows and
-// more 1.00 - 1.09 at two and five bits, 1.03 - 1.21 at eight; beyond 16384 0.92 - 1.16 at 800 to 1024 rows up to K = 22001 (four and eight bits above 1), 0.76 - 1.04 with
-// more rows or longer ones.  Beyond 16384 sixteen over eight: up to 100 rows 0.85 - 0.99, 512 and 1024 rows 0.93 - 1.4.
-inline int quantize_waves(int64_t rows, int64_t K)
+// Waves of a row in the kernel of one row to some waves: a group of 32 elements for every lane, as far as the row goes.  Beyond 8192 elements, time with eight over
+// with four, least and most of three settings (the same features again and again, several states, from memory).  Up to 256 rows 0.75 - 1.01 (16 x 13824 four bits 4.11 -> 3.81 us,
+// 16 x 11008 two bits 4.16 -> 3.65).  Whole k blocks: the field form, 300 to 512 rows, 0.91 - 1.00; the others, 300 to 1500 rows up to K = 16384, 0.91 - 1.11 (eight bits 800 x 13824 from
+// memory 1.15): four; 2048 rows and more 0.91 - 0.99 where most lanes have a group (10752 and beyond), 1.02 - 1.24 where they have not (8704).  Rows that end inside a k
+// block take the kernel with more registers, of which a compute unit holds three workgroups: 768 rows are one round.  Up to there 0.81 - 0.99, with 800 rows and more 1.00 - 1.09
+// at two and five bits, 1.03 - 1.21 at eight; beyond 16384 0.92 - 1.16 at 800 to 1024 rows up to K = 22001 (four and eight bits above 1), 0.76 - 1.04 with more rows or longer
+// ones.  Whole k blocks beyond 16384, 300 rows and more 0.80 - 1.03 (800 x 20480 from memory 0.90 - 1.11).  There sixteen over four up to 256 rows 0.56 - 0.96; over eight up to 100 rows 0.85 - 0.99,
+// 512 and 1024 rows 0.93 - 1.4.
+inline int quantize_waves(int64_t rows, int64_t K, bool field)
 {
     const int64_t nkb = round_up(K, kKPad) / kKBlock;
     if (nkb <= 64) return nkb <= 16 ? 1 : nkb <= 32 ? 2 : 4;
     if (nkb > 128 && rows <= 256) return 16;
     if (round_up(rows, 64) * 512 > kMostWorkItems) return 4;  // 8 388 545 rows and more
     const bool ragged = K % kKBlock != 0;
-    if (ragged && rows > 768 && nkb <= (rows <= 1024 ? 176 : 128)) return 4;
+    if (ragged) return (rows > 768 && nkb <= (rows <= 1024 ? 176 : 128)) ? 4 : 8;
+    if (!field && nkb <= 128 && rows > 256 && rows < 2048) return 4;
     return nkb < 84 && rows > 1024 ? 4 : 8;
 }
 // Five workgroups to a compute unit instead of the seven or eight that its registers leave room for, in the kernel of one row to up to four waves,
@@ -86,7 +89,7 @@ inline int quantize_waves(int64_t rows, int64_t K)
 // no more than four and two by their waves alone, and they are not held back further.
 inline bool quantize_few_workgroups(int64_t rows, int64_t K, int bits, bool field)
 {
-    return bits > 2 && K % 128 == 0 && quantize_waves(rows, K) <= 4 && rows * round_up(K, kKPad) / 8 * (field ? 6 : bits) > 17000000;
+    return bits > 2 && K % 128 == 0 && quantize_waves(rows, K, field) <= 4 && rows * round_up(K, kKPad) / 8 * (field ? 6 : bits) > 17000000;
 }
 hipError_t launch_unpack(const uint32_t *packed, int64_t rows, int64_t K, int bits, bool field, uint8_t *codes,
                          hipStream_t stream);

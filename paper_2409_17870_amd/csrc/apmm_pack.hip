@@ -968,7 +968,7 @@ hipError_t launch_quantize_pack(const uint16_t *x, int64_t rows, int64_t K, int 
         hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kQuantThreads), lds, stream, x, rows, K, bits, packed, scale, rows_p, nkb);
         return hipGetLastError();
     }
-    const int waves = quantize_waves(rows, K), threads = quantize_threads(waves);
+    const int waves = quantize_waves(rows, K, field), threads = quantize_threads(waves);
     const int64_t blocks = (rows_p + 63) / 64 * 64 * waves / (threads / 64);  // eight rows for each of the eight XCDs
     if (blocks * threads > kMostWorkItems) return hipErrorInvalidValue;
     decltype(&quantize_pack_kernel<1, true, true>) kernel;

@@ -44,7 +44,7 @@ int main()
         else if (k == "r11") std::printf("%d\n", rounds(rounds_go_direct<1, 1>, 256, 256));
         else if (k == "quant") std::printf("%d\n", (int)quantize_rows_by_four(M, K));
         else if (k == "few") std::printf("%d\n", (int)quantize_few_workgroups(M, K, (int)N, N == 3 || N == 4));
-        else if (k == "waves") std::printf("%d\n", quantize_waves(M, K));
+        else if (k == "waves" || k == "wavesf") std::printf("%d\n", quantize_waves(M, K, k == "wavesf"));
         else if (k.compare(0, 5, "ahead") == 0) {
             const int tiles = (int)M, kk = (int)K;
             const std::string v = k.substr(5);
@@ -111,10 +111,11 @@ RULES = [
     ("few", 12000, 8, 9000, 0, 0, 0), ("few", 2048, 8, 20000, 0, 0, 0), ("few", 2048, 4, 20000, 0, 0, 0), ("few", 2048, 8, 11008, 0, 0, 0), ("few", 2048, 8, 10240, 0, 0, 1), ("few", 1024, 8, 20001, 0, 0, 0),  # eight waves to a row; ragged
     ("few", 16384, 2, 11008, 0, 0, 0),
     ("waves", 1, 0, 2048, 0, 0, 1), ("waves", 4096, 0, 2049, 0, 0, 2), ("waves", 4096, 0, 4097, 0, 0, 4), ("waves", 1, 0, 8192, 0, 0, 4), ("waves", 1, 0, 8193, 0, 0, 8),
-    ("waves", 1024, 0, 8704, 0, 0, 8), ("waves", 1025, 0, 8704, 0, 0, 4), ("waves", 1025, 0, 10240, 0, 0, 4), ("waves", 1025, 0, 10752, 0, 0, 8),
+    ("wavesf", 1024, 0, 8704, 0, 0, 8), ("wavesf", 1025, 0, 8704, 0, 0, 4), ("wavesf", 1025, 0, 10240, 0, 0, 4), ("wavesf", 1025, 0, 10752, 0, 0, 8),
+    ("waves", 256, 0, 11008, 0, 0, 8), ("waves", 257, 0, 11008, 0, 0, 4), ("waves", 2047, 0, 16384, 0, 0, 4), ("waves", 2048, 0, 16384, 0, 0, 8), ("waves", 2048, 0, 10240, 0, 0, 4),
     ("waves", 1, 0, 16384, 0, 0, 8), ("waves", 256, 0, 16385, 0, 0, 16), ("waves", 257, 0, 16896, 0, 0, 8),
     ("waves", 768, 0, 9000, 0, 0, 8), ("waves", 769, 0, 9000, 0, 0, 4), ("waves", 4096, 0, 16383, 0, 0, 4), ("waves", 1024, 0, 16383, 0, 0, 4),  # rows that end in a k block
-    ("waves", 1024, 0, 20001, 0, 0, 4), ("waves", 1024, 0, 22527, 0, 0, 4), ("waves", 1024, 0, 22529, 0, 0, 8), ("waves", 1025, 0, 16385, 0, 0, 8), ("waves", 769, 0, 16384, 0, 0, 8),
+    ("waves", 1024, 0, 20001, 0, 0, 4), ("waves", 1024, 0, 22527, 0, 0, 4), ("waves", 1024, 0, 22529, 0, 0, 8), ("waves", 1025, 0, 16385, 0, 0, 8), ("waves", 769, 0, 16896, 0, 0, 8),
     ("waves", 8388544, 0, 11008, 0, 0, 8), ("waves", 8388545, 0, 11008, 0, 0, 4), ("waves", 16000000, 0, 20480, 0, 0, 4),  # 2^32 work items of a launch
     ("eights", 536870880, 3, 64, 0, 0, 1), ("eights", 536870912, 3, 64, 0, 0, 0), ("eights", 67108832, 8, 4000, 0, 0, 1), ("eights", 67108864, 8, 4000, 0, 0, 0),  # 2^32 work items
     ("eights", 600000000, 2, 200, 0, 0, 0), ("eightsf", 536870880, 4, 3, 0, 0, 1), ("eightsf", 536870912, 4, 3, 0, 0, 0), ("eights", 178956960, 5, 1400, 0, 0, 1), ("eights", 178956992, 5, 1400, 0, 0, 0),

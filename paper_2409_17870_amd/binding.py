@@ -109,8 +109,8 @@ def _check(status):
         raise ApmmError(status, text)
 
 
-# A single small product is as long as its call from Python, so the plain cases of the calls that a decode step is made of (every tensor there, on
-# the GPU, nothing to allocate) are marshalled in C++ (csrc/apmm_call.cpp; the end of this file); what is not plain comes to the functions
+# A single small product is as long as its call from Python, so the plain cases of the calls that a decode step is made of (torch tensors on the GPU,
+# integers and flags) are marshalled in C++ (csrc/apmm_call.cpp; the end of this file); what is not plain comes to the functions
 # here.  They are kept short as well: addresses go to ctypes as plain integers (the argument types convert them), the stream handle
 # is read without building a Stream object, packed sizes are computed once per shape.
 def _stream():

@@ -2,10 +2,11 @@
 //
 // A single product from Python was bound by its marshalling: attribute look-ups on tensors, checks and the conversion of thirteen
 // arguments took 2 to 3 us of a call whose kernel takes 2 to 5.  Here an argument is looked at where it lies, in the tensor's own structure: W1A2 16 x 256 x 512
-// (pack + product) 10.9 -> 8.2 us, W2A2 1 x 11008 x 4096 from codes 6.2 -> 4.6, of which the kernel takes 4.4.
+// (pack + product) 10.9 -> 8.2 us, W2A2 1 x 11008 x 4096 from codes 6.2 -> 4.6, of which the kernel takes 4.4.  Outputs that are not given are allocated here:
+// handed over, such a call took 0.1 to 0.3 us longer than without this module (W2A2 1 x 1024 x 1024 6.9 -> 7.1 us, from codes 7.3 -> 7.6, quantisation 6.7 -> 7.0), now 5.0, 5.0 and 4.5.
 //
 // Every function takes the arguments of the Python function of the same name in binding.py and has that function as its `general` form: whatever
-// is not the plain case (a missing output that has to be allocated, anything that is not a torch.Tensor, an integer of another type, a check
+// is not the plain case (anything that is not a torch.Tensor, an integer of another type, an output that cannot be allocated, a check
 // that fails, an unknown keyword, a torch-function mode, a process forked from one that uses the GPU, the library not loaded yet) is handed to it with the very arguments, so that
 // results and errors are its own.  A status other than 0 goes to binding.py's _check, on the same thread.  As through ctypes, the interpreter's lock is
 // released around the call.
@@ -13,6 +14,7 @@
 #include <torch/csrc/utils/device_lazy_init.h>
 
 #include <ATen/PythonTorchFunctionTLS.h>
+#include <ATen/ops/empty.h>
 #include <c10/hip/HIPStream.h>
 
 #include <cstring>
@@ -35,7 +37,7 @@ Library lib = {};
 bool loaded = false;
 PyObject *check = nullptr;  // binding.py's _check
 
-constexpr int kMaxArgs = 13;
+constexpr int kMaxArgs = 15;
 enum Function { kPackWeights, kPackActivations, kQuantize, kGemm, kFromCodes, kFunctions };
 struct Signature {
     const char *name;
@@ -48,7 +50,8 @@ Signature signatures[kFunctions] = {
     {"apmm_pack_weights", 3, 2, {"w_codes", "q", "out"}, {}, nullptr},
     {"apmm_pack_activations", 3, 2, {"a_codes", "p", "out"}, {}, nullptr},
     {"apmm_quantize_pack_activations", 4, 2, {"x_f16", "p", "out", "scale_out"}, {}, nullptr},
-    {"apmm_gemm", 13, 7, {"M", "N", "K", "p", "q", "a_packed", "w_packed", "want_i32", "want_f16", "w_scale", "a_scale", "c_i32", "c_f16"}, {}, nullptr},
+    {"apmm_gemm", 15, 7,
+     {"M", "N", "K", "p", "q", "a_packed", "w_packed", "want_i32", "want_f16", "w_scale", "a_scale", "c_i32", "c_f16", "workspace", "algo"}, {}, nullptr},
     {"apmm_gemm_from_codes", 12, 5, {"a_codes", "N", "p", "q", "w_packed", "want_i32", "want_f16", "w_scale", "a_scale", "c_i32", "c_f16", "workspace"}, {}, nullptr},
 };
 
@@ -123,91 +126,122 @@ PyObject *general(const Signature &s, PyObject *const *args, Py_ssize_t nargs, P
 template <class Call>
 bool called(Call call) { return call_and_check(check, call); }
 
-PyObject *pair(PyObject *a, PyObject *b)
+// An output by the place of its argument: the caller's, or a new tensor as the Python function allocates it.  Nothing is given back by a destructor:
+// a thread that ends inside the call is unwound without the interpreter's lock.
+struct Output {
+    PyObject *object = nullptr;  // None where neither given nor wanted
+    void *address = nullptr;
+    bool made = false;
+};
+// false: not the plain case
+bool output(Output &o, PyObject *arg, bool wanted, const at::Tensor &like, at::IntArrayRef size, at::ScalarType type)
 {
-    PyObject *r = PyTuple_New(2);
-    if (!r) return nullptr;
-    PyObject *items[2] = {a ? a : Py_None, b ? b : Py_None};
-    for (int i = 0; i < 2; ++i) {
-        Py_INCREF(items[i]);
-        PyTuple_SET_ITEM(r, i, items[i]);
+    o.object = arg ? arg : Py_None;
+    if (given(arg) || !wanted) return address(arg, o.address);
+    at::Tensor t;
+    bool allocated;
+    Py_BEGIN_ALLOW_THREADS
+    allocated = end_exceptions([&] { t = at::empty(size, like.options().dtype(type)); return true; }, [] { return false; });
+    Py_END_ALLOW_THREADS
+    if (!allocated) return false;
+    o.object = THPVariable_Wrap(std::move(t));
+    o.made = o.object != nullptr;
+    if (!o.made) {
+        PyErr_Clear();
+        return false;
     }
-    return r;
+    return address(o.object, o.address);
 }
+// The result of a call that went well (one output, or two as a tuple), or what stands for one that did not: 1 and the result, else `done`
+int result_of(int done, Output &a, Output *b, PyObject *&result)
+{
+    if (done == 1) {
+        result = b ? PyTuple_Pack(2, a.object, b->object) : a.object;
+        if (!b) Py_INCREF(result);
+        if (!result) done = -1;
+    }
+    if (a.made) Py_DECREF(a.object);
+    if (b && b->made) Py_DECREF(b->object);
+    return done;
+}
+int64_t at_least_one(size_t n) { return n > 1 ? (int64_t)n : 1; }
 
 // Each returns 1 and the result, 0 for the general form, -1 with an error set.
 int pack(Function f, PyObject **v, PyObject *&result)
 {
     int64_t bits;
-    const at::Tensor *codes = tensor(v[0]), *out = tensor(v[2]);
-    if (!matrix(codes, at::kByte) || !out || !integer(v[1], 1, 8, bits)) return 0;
+    const at::Tensor *codes = tensor(v[0]);
+    if (!matrix(codes, at::kByte) || !integer(v[1], 1, 8, bits) || (given(v[2]) && !tensor(v[2]))) return 0;
     const int64_t rows = codes->size(0), K = codes->size(1);
     const bool weights = f == kPackWeights;
-    if (bytes(*out) < (weights ? lib.packed_bytes : lib.packed_activation_bytes)(rows, K, (int)bits)) return 0;
+    const size_t need = (weights ? lib.packed_bytes : lib.packed_activation_bytes)(rows, K, (int)bits);
+    if (given(v[2]) && bytes(*tensor(v[2])) < need) return 0;
     const uint8_t *src = static_cast<const uint8_t *>(codes->data_ptr());
-    void *dst = out->data_ptr(), *s = stream();
-    if (!called([&] { return (weights ? lib.pack_weights : lib.pack_activations)(src, rows, K, (int)bits, dst, s); })) return -1;
-    result = v[2];
-    Py_INCREF(result);
-    return 1;
+    Output out;
+    if (!output(out, v[2], true, *codes, {at_least_one(need)}, at::kByte)) return result_of(0, out, nullptr, result);
+    void *s = stream();
+    const bool went = called([&] { return (weights ? lib.pack_weights : lib.pack_activations)(src, rows, K, (int)bits, out.address, s); });
+    return result_of(went ? 1 : -1, out, nullptr, result);
 }
 
 int quantize(PyObject **v, PyObject *&result)
 {
     int64_t p;
-    const at::Tensor *x = tensor(v[0]), *out = tensor(v[2]), *scale = tensor(v[3]);
-    if (!matrix(x, at::kHalf) || !out || !scale || !integer(v[1], 1, 8, p)) return 0;
+    const at::Tensor *x = tensor(v[0]);
+    if (!matrix(x, at::kHalf) || !integer(v[1], 1, 8, p) || (given(v[2]) && !tensor(v[2])) || (given(v[3]) && !tensor(v[3]))) return 0;
     const int64_t M = x->size(0), K = x->size(1);
-    if (bytes(*out) < lib.packed_activation_bytes(M, K, (int)p) || scale->scalar_type() != at::kHalf || scale->numel() < M) return 0;
+    const size_t need = lib.packed_activation_bytes(M, K, (int)p);
+    if (given(v[2]) && bytes(*tensor(v[2])) < need) return 0;
+    if (given(v[3]) && (tensor(v[3])->scalar_type() != at::kHalf || tensor(v[3])->numel() < M)) return 0;
     const uint16_t *src = static_cast<const uint16_t *>(x->data_ptr());
-    void *dst = out->data_ptr(), *s = stream();
-    uint16_t *sc = static_cast<uint16_t *>(scale->data_ptr());
-    if (!called([&] { return lib.quantize_pack_activations(src, M, K, (int)p, dst, sc, s); })) return -1;
-    result = pair(v[2], v[3]);
-    return result ? 1 : -1;
+    Output out, scale;
+    if (!output(out, v[2], true, *x, {at_least_one(need)}, at::kByte) || !output(scale, v[3], true, *x, {M}, at::kHalf)) return result_of(0, out, &scale, result);
+    void *s = stream();
+    const bool went = called([&] { return lib.quantize_pack_activations(src, M, K, (int)p, out.address, static_cast<uint16_t *>(scale.address), s); });
+    return result_of(went ? 1 : -1, out, &scale, result);
 }
 
 int gemm(PyObject **v, PyObject *&result)
 {
-    int64_t M, N, K, p, q;
+    int64_t M, N, K, p, q, algo = APMM_ALGO_AUTO;
     bool want_i32, want_f16;
-    void *a, *w, *ws, *as, *ci, *cf;
+    void *a, *w, *ws, *as, *space;
     if (!integer(v[0], 0, kAny, M) || !integer(v[1], 0, kAny, N) || !integer(v[2], 0, kAny, K) || !integer(v[3], 0, 255, p) || !integer(v[4], 0, 255, q) ||
-        !flag(v[7], true, want_i32) || !flag(v[8], false, want_f16) || !given(v[5]) || !given(v[6]) || (want_i32 && !given(v[11])) ||
-        (want_f16 && !given(v[12])) || !scale_ok(v[9], N) || !scale_ok(v[10], M) || !address(v[5], a) || !address(v[6], w) || !address(v[9], ws) ||
-        !address(v[10], as) || !address(v[11], ci) || !address(v[12], cf))
+        !flag(v[7], true, want_i32) || !flag(v[8], false, want_f16) || !given(v[5]) || !given(v[6]) || (v[14] && !integer(v[14], 0, 255, algo)) ||
+        !scale_ok(v[9], N) || !scale_ok(v[10], M) || !address(v[5], a) || !address(v[6], w) || !address(v[9], ws) || !address(v[10], as) || !address(v[13], space))
         return 0;
+    const size_t room = given(v[13]) ? bytes(*tensor(v[13])) : 0;
+    const at::Tensor &like = *tensor(v[5]);
+    Output ci, cf;
+    if (!output(ci, v[11], want_i32, like, {M, N}, at::kInt) || !output(cf, v[12], want_f16, like, {M, N}, at::kHalf)) return result_of(0, ci, &cf, result);
     void *s = stream();
-    if (!called([&] {
-            return lib.gemm_ex(M, N, K, (int)p, (int)q, a, w, static_cast<int32_t *>(ci), static_cast<uint16_t *>(cf), static_cast<const uint16_t *>(ws),
-                               static_cast<const uint16_t *>(as), nullptr, 0, s, APMM_ALGO_AUTO);
-        }))
-        return -1;
-    result = pair(v[11], v[12]);
-    return result ? 1 : -1;
+    const bool went = called([&] {
+        return lib.gemm_ex(M, N, K, (int)p, (int)q, a, w, static_cast<int32_t *>(ci.address), static_cast<uint16_t *>(cf.address), static_cast<const uint16_t *>(ws),
+                           static_cast<const uint16_t *>(as), space, room, s, (int)algo);
+    });
+    return result_of(went ? 1 : -1, ci, &cf, result);
 }
 
 int from_codes(PyObject **v, PyObject *&result)
 {
     int64_t N, p, q;
     bool want_i32, want_f16;
-    void *w, *ws, *as, *ci, *cf, *space;
+    void *w, *ws, *as, *space;
     const at::Tensor *codes = tensor(v[0]);
     if (!matrix(codes, at::kByte) || !integer(v[1], 0, kAny, N) || !integer(v[2], 0, 255, p) || !integer(v[3], 0, 255, q) || !given(v[4]) ||
-        !flag(v[5], true, want_i32) || !flag(v[6], false, want_f16) || (want_i32 && !given(v[9])) || (want_f16 && !given(v[10])) || !address(v[4], w) ||
-        !address(v[7], ws) || !address(v[8], as) || !address(v[9], ci) || !address(v[10], cf) || !address(v[11], space))
+        !flag(v[5], true, want_i32) || !flag(v[6], false, want_f16) || !address(v[4], w) || !address(v[7], ws) || !address(v[8], as) || !address(v[11], space))
         return 0;
     const int64_t M = codes->size(0), K = codes->size(1);
     const uint8_t *a = static_cast<const uint8_t *>(codes->data_ptr());
     const size_t room = given(v[11]) ? bytes(*tensor(v[11])) : 0;
+    Output ci, cf;
+    if (!output(ci, v[9], want_i32, *codes, {M, N}, at::kInt) || !output(cf, v[10], want_f16, *codes, {M, N}, at::kHalf)) return result_of(0, ci, &cf, result);
     void *s = stream();
-    if (!called([&] {
-            return lib.gemm_from_codes(M, N, K, (int)p, (int)q, a, w, static_cast<int32_t *>(ci), static_cast<uint16_t *>(cf), static_cast<const uint16_t *>(ws),
-                                       static_cast<const uint16_t *>(as), space, room, s);
-        }))
-        return -1;
-    result = pair(v[9], v[10]);
-    return result ? 1 : -1;
+    const bool went = called([&] {
+        return lib.gemm_from_codes(M, N, K, (int)p, (int)q, a, w, static_cast<int32_t *>(ci.address), static_cast<uint16_t *>(cf.address), static_cast<const uint16_t *>(ws),
+                                   static_cast<const uint16_t *>(as), space, room, s);
+    });
+    return result_of(went ? 1 : -1, ci, &cf, result);
 }
 
 template <Function F>

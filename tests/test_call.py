@@ -76,7 +76,7 @@ def test_results_and_errors_alike():
     calls = [
         ("apmm_pack_weights", PLAIN, lambda: ((w, q), dict(out=empty(nw)))),
         ("apmm_pack_weights", PLAIN, lambda: ((w, q, empty(nw)), {})),
-        ("apmm_pack_weights", GENERAL, lambda: ((w,), dict(q=q))),
+        ("apmm_pack_weights", PLAIN, lambda: ((w,), dict(q=q))),
         ("apmm_pack_weights", GENERAL, lambda: ((w, q), dict(out=empty(nw - 1)))),
         ("apmm_pack_weights", GENERAL, lambda: ((w, 9), dict(out=empty(nw)))),
         ("apmm_pack_weights", GENERAL, lambda: ((w.t(), q), dict(out=empty(nw)))),
@@ -86,21 +86,29 @@ def test_results_and_errors_alike():
         ("apmm_pack_activations", GENERAL, lambda: ((a.as_subclass(Sub), p), dict(out=empty(na)))),
         ("apmm_quantize_pack_activations", PLAIN, lambda: ((x, p), dict(out=empty(na), scale_out=torch.zeros(M, dtype=torch.float16, device=dev)))),
         ("apmm_quantize_pack_activations", GENERAL, lambda: ((x, p, empty(na), torch.zeros(M - 1, dtype=torch.float16, device=dev)), {})),
-        ("apmm_quantize_pack_activations", GENERAL, lambda: ((x, p), {})),
+        ("apmm_quantize_pack_activations", PLAIN, lambda: ((x, p), {})),
+        ("apmm_quantize_pack_activations", PLAIN, lambda: ((x, p), dict(out=empty(na), scale_out=None))),
         ("apmm_gemm", PLAIN, lambda: ((M, N, K, p, q, ap, wp), dict(c_i32=c32()))),
         ("apmm_gemm", PLAIN, lambda: ((M, N, K, p, q, ap, wp), dict(want_i32=False, want_f16=True, w_scale=sw, a_scale=sa, c_f16=c16()))),
         ("apmm_gemm", PLAIN, lambda: ((M, N, K, p, q, ap, wp, True, True, sw, sa, c32(), c16()), {})),
-        ("apmm_gemm", GENERAL, lambda: ((M, N, K, p, q, ap, wp), {})),
+        ("apmm_gemm", PLAIN, lambda: ((M, N, K, p, q, ap, wp), {})),
+        ("apmm_gemm", PLAIN, lambda: ((M, N, K, p, q, ap, wp), dict(want_f16=True, w_scale=sw, a_scale=None, c_i32=c32()))),
+        ("apmm_gemm", PLAIN, lambda: ((M, N, K, 9, q, ap, wp), {})),
+        ("apmm_gemm", GENERAL, lambda: ((1 << 62, N, K, p, q, ap, wp), {})),  # no such tensor
+        ("apmm_gemm", PLAIN, lambda: ((M, N, K, p, q, ap, wp), dict(c_i32=c32(), workspace=empty(64)))),
+        ("apmm_gemm", GENERAL, lambda: ((M, N, K, p, q, ap, wp), dict(c_i32=c32(), workspace=torch.zeros(64, dtype=torch.uint8)))),
+        ("apmm_gemm", GENERAL, lambda: ((M, N, K, p, q, ap, wp), dict(c_i32=c32(), algo=None))),
         ("apmm_gemm", PLAIN, lambda: ((M, N, K, p, q, ap, wp), dict(want_i32=False))),
         ("apmm_gemm", GENERAL, lambda: ((M, N, K, p, q, ap, wp), dict(c_i32=c32(), w_scale=sw[:-1]))),
         ("apmm_gemm", GENERAL, lambda: ((M, N, K, p, q, ap, wp), dict(c_i32=c32(), a_scale=sa.float()))),
         ("apmm_gemm", PLAIN, lambda: ((M, N, K, p, q, ap[1:], wp), dict(c_i32=c32()))),
         ("apmm_gemm", PLAIN, lambda: ((M, N, 1 << 40, p, q, ap, wp), dict(c_i32=c32()))),
         ("apmm_gemm", PLAIN, lambda: ((0, N, K, p, q, ap, wp), dict(c_i32=c32()))),
-        ("apmm_gemm", GENERAL, lambda: ((M, N, K, p, q, ap, wp), dict(c_i32=c32(), algo=binding.ALGO_DECODE))),
+        ("apmm_gemm", PLAIN, lambda: ((M, N, K, p, q, ap, wp), dict(c_i32=c32(), algo=binding.ALGO_DECODE))),
         ("apmm_gemm_from_codes", PLAIN, lambda: ((a, N, p, q, wp), dict(c_i32=c32(), workspace=empty(na)))),
         ("apmm_gemm_from_codes", PLAIN, lambda: ((a, N, p, q, wp), dict(want_i32=False, want_f16=True, c_f16=c16(), w_scale=sw, a_scale=sa))),
-        ("apmm_gemm_from_codes", GENERAL, lambda: ((a, N, p, q, wp), {})),
+        ("apmm_gemm_from_codes", PLAIN, lambda: ((a, N, p, q, wp), {})),
+        ("apmm_gemm_from_codes", PLAIN, lambda: ((a, N, p, q, wp), dict(want_f16=True, a_scale=sa))),
         ("apmm_gemm_from_codes", PLAIN, lambda: ((a, N, p, 9, wp), dict(c_i32=c32()))),
     ]
     stream = torch.cuda.Stream()

@@ -22,10 +22,10 @@ __device__ __forceinline__ uint16_t float_to_half_bits(float x)
 // pair both columns of row r, the odd lane both of row r + 1.  half_pair rounds the two into one register (low, high half), swap_pair
 // exchanges halves between the lanes: a lane permute and a byte permute, whose selector is the lane's for good.  Six operations a pair of results (two of
 // them products with the token scales) where selects, masks and shifts took twelve, and that much less code for the K-split kernels to
-// fetch at their end: W2A4 512 x 5120 x 5120 12.42 -> 12.21 us, 512 x 5120 x 13824 23.3 -> 22.6, W8A8 512 x 4096 x 4096 15.8 -> 15.5, 2048 x 11008 x 2048 67.8 ->
-// 65.9, W2A2 1024 x 11008 x 4096 24.1 -> 23.7.  (By hand: left to itself the compiler makes four products and a conversion of two, which rounds once
-// more than the single results' mixed multiplication.)  The direct tiles, but for the 256 x 256 ones, which spill with it: W2A2 2048 x 4096 x 2048 12.4 ->
-// 11.9, 512 x 13824 x 5120 18.6 -> 18.1, W2A4 1024 x 4096 x 1024 7.9 -> 7.7, W1A4 1024 x 4096 x 512 6.3 -> 6.1.
+// fetch at their end.  Launches inside a graph: W2A4 512 x 5120 x 5120 13.4 -> 13.2 us, 512 x 5120 x 13824 23.8 -> 23.6, W8A8 512 x 4096 x 4096 15.3 -> 15.2, 2048 x 11008 x 2048 66.1 ->
+// 64.1; through LDS and in the direct tiles with a line's pieces stored together (apmm_gemm_mfma_lds.h), W2A2 1024 x 11008 x 4096 24.9 -> 24.6.  (By hand: left to itself the compiler makes four products and a conversion of two, which rounds once
+// more than the single results' mixed multiplication.)  The direct tiles, but for the 256 x 256 ones, which spill with it: W2A2 2048 x 4096 x 2048 12.7 ->
+// 12.2, 512 x 13824 x 5120 19.0 -> 18.5, W2A4 1024 x 4096 x 1024 8.1 -> 7.9, W1A4 1024 x 4096 x 512 5.6 -> 5.4.
 __device__ __forceinline__ uint32_t half_pair(float x0, float x1, float y)
 {
     uint32_t h;

@@ -66,7 +66,7 @@ __device__ __forceinline__ void wait_and_meet()
 // Whether the workgroup that holds the first wave slots of a compute unit goes ahead of the others at every issue, so that it ends early and
 // the tile of the second round runs under the others' k loop; those that run in step store together and leave that tile alone.  Each wave goes by
 // its own slot: where waves of the kernel before still hold slots of some vector units, those of one workgroup differ and the gain is less
-// (W2A4 2048 x 11008 x 4096 both, one behind the other 0.89 - 0.92, behind a packing 0.91 - 0.96, behind an elementwise kernel 0.95 - 0.98; one output
+// (W2A4 2048 x 11008 x 4096 both, one behind the other 0.89 - 0.97, 61 - 65 -> 57 - 60 us, behind a packing 0.91 - 0.96, behind an elementwise kernel 0.95 - 0.98; one output
 // 0.94 - 0.97 and 3-bit weights 0.91 - 0.98 in all three).
 // Time with over without, operands and outputs in rotation:
 // Two workgroups to a compute unit (3- and 4-bit activations), a round of 512 and up to 0.44 of a second.  128 x 256, 640 to 688 tiles, K = 2048 - 8192: both

@@ -10,7 +10,7 @@
 // 2.2 us, 64 rows 2.6 -> 2.3 us).
 //
 // pack_kernel works tile by tile (one wave per 32 rows x 128 k, whole cache lines written by one instruction)
-// with separate waves for the code sums, pack_eights_kernel by eight rows with the sums on the way; pack_rows_kernel and the fused quantise + pack kernel work row by row
+// with separate waves for the code sums, pack_eights_kernel by eight rows with the sums on the way (many rows); pack_rows_kernel and the fused quantise + pack kernel work row by row
 // (one wave or a few per row; the quantiser has to see the whole row for its scale first).  No atomics.  The work is HBM bound: 1 byte
 // read and bits/8 bytes written per element.
 #include <hip/hip_fp16.h>
@@ -195,7 +195,8 @@ __device__ __forceinline__ void store_fields(uint32_t *__restrict__ packed, int6
 // pack_rows_kernel: one wave per row: lane l packs the 32-element groups l, l+64, ... (two 16-byte loads of codes
 // each, 1 KB contiguous per load instruction) and keeps a running code sum; the wave adds the 64 partial sums
 // with lane permutes (over_wave).  Reads are ideal, writes are 8- and 16-byte pieces that other waves complete to whole
-// lines later.  Used for group-form operands of one or two bits, where little is written.
+// lines later.  Used for group-form operands of one or two bits, where little is written, but for the largest (rule:
+// pack_by_eights).
 template <int bits, bool WHOLE>
 __global__ __launch_bounds__(kThreads) void pack_rows_kernel(const uint8_t *__restrict__ codes, int64_t rows,
                                                         int64_t K, uint32_t *__restrict__ packed,
@@ -475,19 +476,19 @@ __global__ __launch_bounds__(64 * kEightWaves) void pack_eights_kernel(const uin
 }
 
 // Fused quantise + pack (paper Sec. 3.1: the feature matrix is quantised onto the symmetric bipolar-INT
-// grid; Sec. 4.1: decomposition and reassembly).  One, two or four waves per row (token):
+// grid; Sec. 4.1: decomposition and reassembly).  One to sixteen waves per row (token; rule: quantize_waves):
 //   1. max |x| over the row (on the bit patterns, two halves per operation);
 //      scale = half(max|x| / (2^bits - 1)), stored per token; r = 1 / scale;
 //   2. u = clamp(floor(x / (2 scale)) + 2^(bits-1), 0, 2^bits - 1): x / scale moved to the nearest odd
 //      integer (ties upward), as a code; the floor is that of the exact quotient (computed as x * (r / 2)
 //      with a correction that covers the rounding of r and of the product); then the same packing as pack_kernel.
-// Rows of up to 16384 elements (4096 for each wave) stay in registers between the two steps; longer rows are read again (from
+// Up to 4096 elements for each wave stay in registers between the two steps; what is beyond is read again (from
 // L2).  The codes are those of exact arithmetic on the binary16 inputs and the binary16 scale.  A row whose
 // scale rounds to zero gets the code of +1 everywhere.
 //
 // WAVES waves of a workgroup share a row, one 32-element group per lane and step, so that a row takes one or two round
 // trips to memory however long it is.  With one wave per row, the earlier form, a lane worked through up to eleven groups
-// in turn.  Four bits, one launch inside a graph: 16 x 5120 6.0 -> 3.2 us, 16 x 13824 12.5 -> 4.1 us, 1024 x 11008 15.1 ->
+// in turn.  Four bits, one launch inside a graph: 16 x 5120 6.0 -> 3.2 us, 16 x 13824 12.5 -> 4.1 us (4.0 with eight waves), 1024 x 11008 15.1 ->
 // 13.0 us; two bits 4096 x 4096 12.5 -> 10.0 us.  Large matrices in the field form are bound by their scattered stores: those go to
 // quantize_fields_kernel.
 // The eight rows that share the 128-byte lines of a slot are packed on one XCD, whose L2 joins their 16-byte pieces.
@@ -914,8 +915,8 @@ hipError_t launch_pack(const uint8_t *codes, int64_t rows, int64_t K, int bits, 
     if (rows_p == 0) return hipSuccess;
     const bool by_eights = pack_by_eights(rows, K, bits, field);
     if (!field && bits <= 2 && !by_eights) {
-        // measured: 4.7 us against 6.8 us for 4096 x 4096 two-bit codes (the row kernel reads in 1 KB runs and
-        // takes the code sums on the way); 22.6 us against 12.0 us for 2048 x 11008 four-bit activations
+        // Row by row against tile by tile: 4096 x 4096 two-bit codes 4.7 / 6.8 us (reads in 1 KB runs, code sums on the way); four-bit activations
+        // 2048 x 11008 22.6 / 12.0, where more is written.
         const int64_t blocks = (rows_p + kRowsPerWg - 1) / kRowsPerWg;
         if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
         const bool whole = K % 32 == 0;

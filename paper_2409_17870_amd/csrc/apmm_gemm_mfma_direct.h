@@ -371,7 +371,9 @@ __global__ __launch_bounds__(256) void gemm_mfma_direct_kernel(const uint32_t *a
     auto emit = [&](auto guard_c, auto i32_c, auto f16_c, auto pair_c, auto nt_c) __attribute__((always_inline)) {
         constexpr bool GUARD = decltype(guard_c)::value, I32 = decltype(i32_c)::value, F16 = decltype(f16_c)::value,
                        PAIR = decltype(pair_c)::value, NT = decltype(nt_c)::value;
-        constexpr bool TOGETHER = F16 && PAIR && NT;  // the 64-byte pieces of a line leave one right behind the other
+        // FULL: 256 x 256, whose registers are all taken: the pair's halves by selects (the permutes spill), scales and stores as they come (scales at hand
+        // cost its border tiles 2 - 13 %).  TOGETHER: the 64-byte pieces of a line leave one right behind the other.
+        constexpr bool FULL = WM * WN == 16, TOGETHER = F16 && PAIR && NT && !FULL;
         if constexpr (NT) edge_of_streaming();
         int32_t *ci = I32 ? g.c_i32 + m_last * g.N + n_lane : nullptr;
         uint16_t *ch = F16 ? g.c_f16 + m_last * g.N + n_lane : nullptr;
@@ -413,27 +415,29 @@ __global__ __launch_bounds__(256) void gemm_mfma_direct_kernel(const uint32_t *a
                     if constexpr (I32 && NT) __builtin_nontemporal_store((int32_t)c, &ci[row * g.N + bj * 32]);
                     if constexpr (I32 && !NT) ci[row * g.N + bj * 32] = (int32_t)c;
                     if constexpr (F16 && !PAIR) ch[row * g.N + bj * 32] = float_to_half_bits(c * sa * sw[bj]);
+                    if constexpr (F16 && PAIR && FULL) {
+                        if (v % 2 == 0) {  // folds once the loop is unrolled
+                            const uint32_t h0 = float_to_half_bits(c * sa * sw[bj]);
+                            const uint32_t h1 = float_to_half_bits(acc[ROWL + bi][bj][(v + 1) & 15] * sa_next * sw[bj]);
+                            const uint32_t give = odd ? h0 : h1, keep = odd ? h1 : h0;
+                            // quad_perm [1, 0, 3, 2]: the value of the other lane of the pair
+                            const uint32_t got = (uint32_t)__builtin_amdgcn_mov_dpp((int)give, 0xB1, 0xf, 0xf, true);
+                            const uint32_t word = odd ? (got | (keep << 16)) : (keep | (got << 16));
+                            uint32_t *dst = reinterpret_cast<uint32_t *>(ch_pair + row * g.N + bj * 32);
+                            if constexpr (NT) __builtin_nontemporal_store(word, dst);
+                            else *dst = word;
+                        }
+                    }
                 }
-                if constexpr (F16 && PAIR) {
-                    if (v % 2 == 0) {  // folds once the loop is unrolled
+                if constexpr (F16 && PAIR && !FULL) {
+                    if (v % 2 == 0) {
                         uint32_t word[WN];
 #pragma unroll
-                        for (int bj = 0; bj < WN; ++bj) {
-                            const float c = acc[ROWL + bi][bj][v], c_next = acc[ROWL + bi][bj][(v + 1) & 15];
-                            if constexpr (WM * WN < 16) {
-                                word[bj] = swap_pair(half_pair(c * sa, c_next * sa_next, sw[bj]), swap_pair_selector(odd));
-                            } else {  // (256 x 256: spills with it)
-                                const uint32_t h0 = float_to_half_bits(c * sa * sw[bj]);
-                                const uint32_t h1 = float_to_half_bits(c_next * sa_next * sw[bj]);
-                                const uint32_t give = odd ? h0 : h1, keep = odd ? h1 : h0;
-                                // quad_perm [1, 0, 3, 2]: the value of the other lane of the pair
-                                const uint32_t got = (uint32_t)__builtin_amdgcn_mov_dpp((int)give, 0xB1, 0xf, 0xf, true);
-                                word[bj] = odd ? (got | (keep << 16)) : (keep | (got << 16));
-                            }
-                        }
+                        for (int bj = 0; bj < WN; ++bj)
+                            word[bj] = swap_pair(half_pair(acc[ROWL + bi][bj][v] * sa, acc[ROWL + bi][bj][(v + 1) & 15] * sa_next, sw[bj]), swap_pair_selector(odd));
 #pragma unroll
                         for (int bj = 0; bj < WN; ++bj)
-                            if constexpr (TOGETHER && WM * WN < 16) asm volatile("" : "+v"(word[bj]));
+                            if constexpr (TOGETHER) asm volatile("" : "+v"(word[bj]));
 #pragma unroll
                         for (int bj = 0; bj < WN; ++bj) {
                             uint32_t *dst = reinterpret_cast<uint32_t *>(ch_pair + row * g.N + bj * 32);
